@@ -193,7 +193,7 @@ int a2ats_decode_prologue(const a2ats_dims* dims, const float* keys, int32_t n_n
  * a2ats_decode_prologue followed by a2ats_score_topk (without its debug output) as one call: steps
  * 1-3 of a decode step plus the append of the current token's key (paper sections 4.1-4.3).  Where
  * a2ats_score_topk takes its streaming route (product quantisation, at least 16384 candidates,
- * 1 <= top_k <= 2048, 4 top_k <= candidates) the call needs one launch less than the two: the
+ * 1 <= top_k, 4 top_k <= candidates) the call needs one launch less than the two: the
  * workgroups that sample the thresholds build their problem's tables themselves and keep the coarse
  * copy in LDS.  That is done while (a) those workgroups, batch * n_kv_heads * head groups * sampling
  * parts, number at most 256, one per CU, and (b) no appended row can be a candidate of any sequence,
@@ -436,8 +436,8 @@ int a2ats_codebook_update(const a2ats_dims* dims, const float* keys, int32_t n_n
  * write per head into cand_counts [dev, out, uint32 B*Hq] (asynchronously, on `stream`): bits 0-27
  * the number of rows the streaming pass kept for that head, bits 28-31 the route the final kernel
  * took (0 = fast; 1 = too few survivors, 2 = too many, 3 = a segment overflowed, 4 = completeness
- * proof failed: 1-4 end in the exact fallback).  For shapes served by the exact route alone every
- * entry is 0xFFFFFFFF.
+ * proof failed: 1-4 end in the exact fallback).  For shapes served by the exact route alone, and for
+ * top_k > 2048, every entry is 0xFFFFFFFF.
  */
 int a2ats_score_topk_stats(const a2ats_dims* dims, int32_t top_k, int32_t window, int32_t n_sink,
                            const void* ws, uint32_t* cand_counts, void* stream);
@@ -445,7 +445,8 @@ int a2ats_score_topk_stats(const a2ats_dims* dims, int32_t top_k, int32_t window
 /*
  * Host only, no GPU needed: how a2ats_score_topk would lay out its work for these dims / top_k /
  * window / n_sink.  Writes 11 numbers to plan [host, out, int32 11]:
- * [0] 1 if the sampled-threshold + streaming route is used (0: the exact route alone, the rest is 0),
+ * [0] 1 if the sampled-threshold + streaming route is used for top_k <= 2048 (else the rest is 0: the exact
+ * route alone, or for larger top_k the streaming route if the workspace is there for it),
  * [1] groups of four query heads per KV head, [2] sampling workgroups per (sequence, KV head, group),
  * [3] rows each of them scores, [4] streaming workgroups (chunks) per problem, [5] rows per chunk,
  * [6] survivor segments per wave of a chunk (always 1), [7] rows per segment, [8] entries a segment can hold,

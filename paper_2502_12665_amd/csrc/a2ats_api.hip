@@ -48,6 +48,13 @@ int check_dims(const a2ats_dims* d) {
 
 bool misaligned16(const void* p) { return ((uintptr_t)p & 15u) != 0; }
 
+// Whether `ws` can hold a selection plan's workspace.  The streaming route refuses to run without; a
+// wide plan then takes the exact route instead, which needs none (selections of more than 2048 tokens
+// used to ask for no workspace at all).
+bool holds(const a2ats::TopkPlan& plan, const void* ws, size_t ws_bytes) {
+  return ws && !misaligned16(ws) && ws_bytes >= plan.bytes;
+}
+
 }  // namespace
 
 extern "C" {
@@ -85,7 +92,7 @@ size_t a2ats_workspace_bytes(const a2ats_dims* d, int op, int32_t top_k, int32_t
       size_t need = 0;
       for (int n_sink = 0; n_sink <= 64; ++n_sink) {
         const a2ats::TopkPlan p = a2ats::make_topk_plan(*d, top_k, window, n_sink);
-        if (p.fast && p.bytes > need) need = p.bytes;
+        if (p.bytes > need) need = p.bytes;
       }
       return need;
     }
@@ -294,8 +301,8 @@ int a2ats_decode_select(const a2ats_dims* d, const float* keys, int32_t n_new, i
   if (!codes || !lut || !lut_scale || !topk_count || (top_k > 0 && !topk_idx)) return A2ATS_ERR_INVALID_ARG;
   if (misaligned16(codes)) return A2ATS_ERR_INVALID_ARG;
   const a2ats::TopkPlan plan = a2ats::make_topk_plan(*d, top_k, window, n_sink);
-  if (!a2ats::single_codebook(*d) && plan.fast && (!ws || misaligned16(ws) || ws_bytes < plan.bytes))
-    return A2ATS_ERR_WORKSPACE;
+  if (!a2ats::single_codebook(*d) && plan.fast && !holds(plan, ws, ws_bytes)) return A2ATS_ERR_WORKSPACE;
+  const bool streams = plan.fast || (plan.wide && holds(plan, ws, ws_bytes));
   // The fused launch has every sampling workgroup build its problem's tables: worth it while those
   // workgroups fit the 256 CUs in one round, a loss when they queue up behind each other.  Its
   // sampling workgroups read candidate rows while others write the appended rows, so it is only
@@ -303,7 +310,7 @@ int a2ats_decode_select(const a2ats_dims* d, const float* keys, int32_t n_new, i
   // usual append of the current token); otherwise the two calls run one after the other.
   const long n_sample = (long)d->batch * d->n_kv_heads * plan.NG * plan.P0;
   const bool appended_rows_compete = n_new > 0 && (int64_t)pos0 < (int64_t)d->ctx_len - window;
-  if (a2ats::single_codebook(*d) || !plan.fast || n_sample > 256 || appended_rows_compete) {   // the two calls, with their own checks
+  if (a2ats::single_codebook(*d) || !streams || n_sample > 256 || appended_rows_compete) {   // the two calls, with their own checks
     rc = a2ats_decode_prologue(d, keys, n_new, pos0, codebook, weights, weight_mode, codes, q, q_dtype, cos_b,
                                sin_b, q_rot, lut, lut_scale, ws, ws_bytes, stream);
     if (rc != A2ATS_OK) return rc;
@@ -323,7 +330,6 @@ int a2ats_decode_select(const a2ats_dims* d, const float* keys, int32_t n_new, i
   if (misaligned16(codebook) || misaligned16(lut) || misaligned16(codes) || (n_new > 0 && misaligned16(keys)))
     return A2ATS_ERR_INVALID_ARG;
   if (n_new > 32) return A2ATS_ERR_UNSUPPORTED;
-  if (!ws || misaligned16(ws) || ws_bytes < plan.bytes) return A2ATS_ERR_WORKSPACE;
   hipError_t e = a2ats::launch_decode_select_prologue(
       *d, keys, n_new, pos0, codebook, weights, weight_mode, codes, q, q_dtype, cos_b, sin_b, q_rot, lut, lut_scale,
       seq_lens, (int32_t*)((unsigned char*)ws + plan.off_thr), plan.P0, plan.sample_rows, top_k, window, n_sink,
@@ -360,11 +366,13 @@ int a2ats_decode_select_shared(const a2ats_dims* d, const float* keys, int32_t n
   a2ats_dims dk = *d;   // the score/top-K side sees one table head per KV head
   dk.n_q_heads = d->n_kv_heads;
   const a2ats::TopkPlan plan = a2ats::make_topk_plan(dk, top_k, window, n_sink);
-  if (plan.fast && (!ws || misaligned16(ws) || ws_bytes < plan.bytes)) return A2ATS_ERR_WORKSPACE;
+  if (plan.fast && !holds(plan, ws, ws_bytes)) return A2ATS_ERR_WORKSPACE;
+  if (plan.wide && !holds(plan, ws, ws_bytes)) ws = nullptr;   // the exact route
+  const bool streams = plan.fast || (plan.wide && ws);
   const long n_sample = (long)d->batch * d->n_kv_heads * plan.P0;
   const bool appended_rows_compete = n_new > 0 && (int64_t)pos0 < (int64_t)d->ctx_len - window;
   hipError_t e;
-  if (!plan.fast || n_sample > 256 || appended_rows_compete) {   // the three launches one after the other
+  if (!streams || n_sample > 256 || appended_rows_compete) {   // the three launches one after the other
     // (at most 32 keys per sequence: the append-time encoder, which needs no workspace)
     if ((e = a2ats::launch_encode(*d, keys, n_new, pos0, codebook, weights, mode, codes, nullptr,
                                   (hipStream_t)stream)) != hipSuccess)
@@ -422,9 +430,8 @@ static int score_topk_impl(const a2ats_dims* d, const uint8_t* codes, const int3
     return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
   }
   const a2ats::TopkPlan plan = a2ats::make_topk_plan(*d, top_k, window, n_sink);
-  if (plan.fast) {
-    if (!ws || misaligned16(ws) || ws_bytes < plan.bytes) return A2ATS_ERR_WORKSPACE;
-  }
+  if (plan.fast && !holds(plan, ws, ws_bytes)) return A2ATS_ERR_WORKSPACE;
+  if (plan.wide && !holds(plan, ws, ws_bytes)) ws = nullptr;   // the exact route
   const hipError_t e = a2ats::launch_score_topk(*d, codes, pg, lut, lut_scale, top_k, window, n_sink, seq_lens,
                                                 topk_idx, topk_count, topk_score, scores_out, ws, false,
                                                 (hipStream_t)stream, (hipEvent_t)ev_start, (hipEvent_t)ev_stop);

@@ -15,7 +15,8 @@ namespace a2ats {
 
 // How a2ats_score_topk runs for a shape, and how it carves its workspace.
 struct TopkPlan {
-  bool fast;            // sampled threshold + one streaming pass (else: exact route only)
+  bool fast;            // sampled threshold + one streaming pass, up to 2048 winners
+  bool wide;            // the same for more winners; without a workspace it falls back to the exact route
   int NG;               // head groups of 4 per KV head
   int P0;               // sampling workgroups per (sequence, KV head, head group)
   int sample_rows;      // rows each of them scores
@@ -59,6 +60,7 @@ hipError_t launch_build_lut(const a2ats_dims& d, const void* q, int q_dtype, con
                             const float* sin_b, const float* codebook, float* q_rot, int32_t* lut,
                             float* lut_scale, hipStream_t stream);
 // `pg.table` null: `codes` is the contiguous matrix; else a pool of pages (see CodePages).
+// `ws` null where the plan is wide: the exact route, which needs none.
 hipError_t launch_score_topk(const a2ats_dims& d, const uint8_t* codes, const CodePages& pg, const int32_t* lut,
                              const float* lut_scale, int top_k, int window, int n_sink,
                              const int32_t* seq_lens, int32_t* topk_idx, int32_t* topk_count,

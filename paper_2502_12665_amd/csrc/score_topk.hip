@@ -3,7 +3,7 @@
 //
 // Two routes, chosen on the host from the shape:
 //
-//  exact route (short contexts, very large K; also the in-kernel fallback of the fast route):
+//  exact route (short contexts; also the in-kernel fallback of the fast route):
 //  one workgroup per query head runs an MSB-first radix select over the 32-bit score keys by
 //  re-streaming its sequence (<= 3 histogram passes), then one ordered pass that emits the
 //  winners in ascending position, equal scores going to the lower position.
@@ -53,8 +53,15 @@ TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink) 
   long ncand = (long)d.ctx_len - window - n_sink;
   if (ncand < 0) ncand = 0;
   p.cap = 8192;
-  p.fast = !single_codebook(d) && ncand >= 16384 && top_k >= 1 && top_k <= 2048 && 4L * top_k <= ncand;
-  if (p.fast) {
+  // The streaming route: the selection is at most a quarter of at least 16384 candidates.  Up to 4096
+  // winners leave the final kernel room: its list holds 8192 survivors, and the sampled threshold lets
+  // 1.3 to 1.65 K through there.  Above 2048 the route is called wide and reports no survivor statistics.
+  // (2 sequences of 98301 tokens, 32 heads, K 2949: the step takes 65 us; 347 us on the exact route, which
+  // streams and scores a head's rows four times on one CU.)
+  const bool streams = !single_codebook(d) && ncand >= 16384 && top_k >= 1 && top_k <= 4096 && 4L * top_k <= ncand;
+  p.fast = streams && top_k <= 2048;
+  p.wide = streams && top_k > 2048;
+  if (streams) {
     // Sample an eighth of the candidates (at most 65536 rows; in units of 512 rows, at least
     // kSampleRows), shared by at most 8 workgroups of at most 8192 rows each.  The survivors the
     // streaming pass writes and the final kernel reads back shrink with the sample (1.95 K per head
@@ -1018,7 +1025,7 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
     if ((err = hipGetLastError()) != hipSuccess) return err;
   }
 
-  if (!plan.fast) {
+  if (!plan.fast && !(plan.wide && ws)) {
     if ((err = allow_dynamic_lds(select_exact_kernel<M>, lut1_bytes, s_exact)) != hipSuccess) return err;
     hipLaunchKernelGGL((select_exact_kernel<M>), dim3(heads), dim3(kExactThreads), lut1_bytes, stream,
                        codes, lut, lut_scale, seq_lens, topk_idx, topk_count, topk_score, pg, B, Hq, Hkv,

@@ -198,7 +198,8 @@ int a2ats_decode_prologue(const a2ats_dims* dims, const float* keys, int32_t n_n
  * copy in LDS.  That is done while (a) those workgroups, batch * n_kv_heads * head groups * sampling
  * parts, number at most 256, one per CU, and (b) no appended row can be a candidate of any sequence,
  * pos0 >= ctx_len - window (the usual append of the current token; the sampling workgroups read
- * candidate rows while others write the appended ones).  Elsewhere it simply makes the two calls.
+ * candidate rows while others write the appended ones).  With at most 16384 candidates, and (b), the whole
+ * call is one launch.  Elsewhere it simply makes the two calls.
  * Arguments are the union of theirs and are all checked before anything is enqueued; every output
  * (codes, q_rot, lut, lut_scale, topk_*) is bit for bit what the two calls write.
  * `ws`: a2ats_workspace_bytes(dims, A2ATS_OP_SCORE_TOPK, top_k, window) bytes for product

@@ -310,27 +310,35 @@ int a2ats_decode_select(const a2ats_dims* d, const float* keys, int32_t n_new, i
   // usual append of the current token); otherwise the two calls run one after the other.
   const long n_sample = (long)d->batch * d->n_kv_heads * plan.NG * plan.P0;
   const bool appended_rows_compete = n_new > 0 && (int64_t)pos0 < (int64_t)d->ctx_len - window;
-  if (a2ats::single_codebook(*d) || !streams || n_sample > 256 || appended_rows_compete) {   // the two calls, with their own checks
+  // (short contexts have a launch of their own for the whole call, under the same condition)
+  const bool in_one = !streams && a2ats::decode_select_group_fits(*d, window, n_sink);
+  if (a2ats::single_codebook(*d) || appended_rows_compete || (!in_one && (!streams || n_sample > 256))) {   // the two calls, with their own checks
     rc = a2ats_decode_prologue(d, keys, n_new, pos0, codebook, weights, weight_mode, codes, q, q_dtype, cos_b,
                                sin_b, q_rot, lut, lut_scale, ws, ws_bytes, stream);
     if (rc != A2ATS_OK) return rc;
     return a2ats_score_topk(d, codes, lut, lut_scale, top_k, window, n_sink, seq_lens, topk_idx, topk_count,
                             topk_score, nullptr, ws, ws_bytes, stream);
   }
-  // the checks of a2ats_decode_prologue and a2ats_score_topk for the streaming route
+  // the checks of a2ats_decode_prologue and a2ats_score_topk
   if (n_new < 0 || pos0 < 0 || (int64_t)pos0 + n_new > d->ctx_stride) return A2ATS_ERR_INVALID_ARG;
   weight_mode &= ~A2ATS_W_PREPARED;
   if (weight_mode != A2ATS_W_NONE && weight_mode != A2ATS_W_DIAG && weight_mode != A2ATS_W_BLOCK)
     return A2ATS_ERR_INVALID_ARG;
   if (q_dtype != A2ATS_F32 && q_dtype != A2ATS_BF16) return A2ATS_ERR_INVALID_ARG;
-  if (!codebook || !q || !cos_b || !sin_b || !q_rot || !lut || !lut_scale || !codes || !topk_idx || !topk_count)
-    return A2ATS_ERR_INVALID_ARG;
+  if (!codebook || !q || !cos_b || !sin_b || !q_rot) return A2ATS_ERR_INVALID_ARG;
   if (n_new > 0 && !keys) return A2ATS_ERR_INVALID_ARG;
   if (weight_mode != A2ATS_W_NONE && !weights) return A2ATS_ERR_INVALID_ARG;
   if (misaligned16(codebook) || misaligned16(lut) || misaligned16(codes) || (n_new > 0 && misaligned16(keys)))
     return A2ATS_ERR_INVALID_ARG;
   if (n_new > 32) return A2ATS_ERR_UNSUPPORTED;
-  hipError_t e = a2ats::launch_decode_select_prologue(
+  hipError_t e;
+  if (in_one) {
+    e = a2ats::launch_decode_select_group(*d, keys, n_new, pos0, codebook, weights, weight_mode, codes, q, q_dtype, cos_b,
+                                          sin_b, q_rot, lut, lut_scale, seq_lens, top_k, window, n_sink, topk_idx,
+                                          topk_count, topk_score, false, (hipStream_t)stream);
+    return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
+  }
+  e = a2ats::launch_decode_select_prologue(
       *d, keys, n_new, pos0, codebook, weights, weight_mode, codes, q, q_dtype, cos_b, sin_b, q_rot, lut, lut_scale,
       seq_lens, (int32_t*)((unsigned char*)ws + plan.off_thr), plan.P0, plan.sample_rows, top_k, window, n_sink,
       false, (hipStream_t)stream);
@@ -372,6 +380,12 @@ int a2ats_decode_select_shared(const a2ats_dims* d, const float* keys, int32_t n
   const long n_sample = (long)d->batch * d->n_kv_heads * plan.P0;
   const bool appended_rows_compete = n_new > 0 && (int64_t)pos0 < (int64_t)d->ctx_len - window;
   hipError_t e;
+  if (!streams && !appended_rows_compete && a2ats::decode_select_group_fits(dk, window, n_sink)) {
+    e = a2ats::launch_decode_select_group(*d, keys, n_new, pos0, codebook, weights, mode, codes, q, q_dtype, cos_b, sin_b,
+                                          q_rot, lut, lut_scale, seq_lens, top_k, window, n_sink, topk_idx, topk_count,
+                                          topk_score, true, (hipStream_t)stream);
+    return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
+  }
   if (!streams || n_sample > 256 || appended_rows_compete) {   // the three launches one after the other
     // (at most 32 keys per sequence: the append-time encoder, which needs no workspace)
     if ((e = a2ats::launch_encode(*d, keys, n_new, pos0, codebook, weights, mode, codes, nullptr,

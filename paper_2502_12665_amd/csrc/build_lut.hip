@@ -13,6 +13,7 @@
 #include "internal.hpp"
 #include "encode_few.hpp"
 #include "coarse_score.hpp"
+#include "group_select.hpp"
 
 namespace a2ats {
 
@@ -336,6 +337,100 @@ __global__ __launch_bounds__(kLutThreads) void decode_select_prologue_kernel(
                        ctx_stride);
 }
 
+// A whole a2ats_decode_select for short contexts (group_select.hpp) in one launch: a workgroup builds its
+// problem's tables, keeps the coarse one in LDS and selects from it at once.  Against the prologue and the
+// selection as two launches this saves a launch and the copy of the table.  The appended keys are encoded as in
+// decode_prologue_kernel.
+template <int DS, bool QBF16, bool SHARED>
+__global__ __launch_bounds__(kLutThreads) void decode_select_group_kernel(
+    const void* __restrict__ q_in, const float* __restrict__ cos_b, const float* __restrict__ sin_b,
+    const float* __restrict__ codebook, float* __restrict__ q_rot, int32_t* __restrict__ lut,
+    float* __restrict__ lut_scale, int B, int Hq, int Hkv, int NG, int n_lut, GridMap gm,
+    const float* __restrict__ keys, const float* __restrict__ weights, int mode,
+    uint8_t* __restrict__ codes, int n_new, int pos0, int64_t ctx_stride, int sweeps, int folded,
+    const int32_t* __restrict__ seq_lens, int32_t* __restrict__ topk_idx, int32_t* __restrict__ topk_count,
+    float* __restrict__ topk_score, int ctx_len, int top_k, int window, int n_sink) {
+  constexpr int M = 128 / DS;
+  static_assert(kGroupThreads == kLutThreads, "one workgroup does both");
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
+  if ((int)blockIdx.x < n_lut) {
+    int prob, part, b, kv, g4;
+    map_block(blockIdx.x, gm, prob, part);
+    split_problem(prob, gm, b, kv, g4);
+    build_lut_body<DS, QBF16, SHARED>(prob, q_in, cos_b, sin_b, codebook, q_rot, lut, lut_scale, B, Hq, Hkv, NG, true,
+                                      dyn_lds);
+    group_select_body<M, true>(b, kv, g4, prob, codes, CodePages{nullptr, 0, 0}, lut, lut_scale, seq_lens, topk_idx,
+                               topk_count, topk_score, B, SHARED ? Hkv : Hq, Hkv, ctx_len, ctx_stride, top_k, window,
+                               n_sink, dyn_lds);
+    if (folded)
+      encode_few_block<DS>((int)blockIdx.x, sweeps, keys, codebook, weights, mode, codes, B, Hkv, n_new, pos0,
+                           ctx_stride);
+    return;
+  }
+  encode_few_block<DS>((int)blockIdx.x - n_lut, sweeps, keys, codebook, weights, mode, codes, B, Hkv, n_new, pos0,
+                       ctx_stride);
+}
+
+// How the append-time encoding shares a launch with n_lut table workgroups: workgroups of its own, or
+// (folded) the table workgroups, where both kinds would not fit one round of the CUs.
+struct AppendPlan {
+  int sweeps, folded;
+  unsigned n_enc;
+};
+static AppendPlan append_plan(long n_pairs, int n_lut) {
+  AppendPlan p;
+  p.sweeps = encode_few_sweeps(n_pairs);
+  const long per_wg = (long)kFewPairsPerSweep * p.sweeps, n_enc = (n_pairs + per_wg - 1) / per_wg;
+  p.folded = n_lut > 0 && n_lut + n_enc > 256;
+  if (p.folded) p.sweeps = (int)((n_pairs + (long)kFewPairsPerSweep * n_lut - 1) / ((long)kFewPairsPerSweep * n_lut));
+  p.n_enc = p.folded ? 0u : (unsigned)n_enc;
+  return p;
+}
+
+bool decode_select_group_fits(const a2ats_dims& d, int window, int n_sink) {
+  return !single_codebook(d) && (long)d.ctx_len - window - n_sink <= kGroupMaxCand;
+}
+
+hipError_t launch_decode_select_group(const a2ats_dims& d, const float* keys, int n_new, int pos0,
+                                      const float* codebook, const float* weights, int mode, uint8_t* codes,
+                                      const void* q, int q_dtype, const float* cos_b, const float* sin_b, float* q_rot,
+                                      int32_t* lut, float* lut_scale, const int32_t* seq_lens, int top_k, int window,
+                                      int n_sink, int32_t* topk_idx, int32_t* topk_count, float* topk_score,
+                                      bool shared, hipStream_t stream) {
+  const int G = d.n_q_heads / d.n_kv_heads;
+  const int NG = shared ? 1 : (G + kHeadsPerGroup - 1) / kHeadsPerGroup;
+  const int n_lut = d.batch * d.n_kv_heads * NG;
+  const AppendPlan ap = append_plan((long)d.batch * d.n_kv_heads * n_new * d.n_sub, n_lut);
+  const dim3 grid(n_lut + ap.n_enc), block(kLutThreads);
+  if (grid.x == 0) return hipSuccess;
+  static LdsSlot s_lds[8][16];
+  hipError_t err;
+#define A2ATS_LAUNCH_GRP(DS, BF, SH, SLOT)                                                                      \
+  do {                                                                                                          \
+    if ((err = allow_dynamic_lds(decode_select_group_kernel<DS, BF, SH>, kGroupLdsBytes, s_lds[SLOT])) !=       \
+        hipSuccess)                                                                                             \
+      return err;                                                                                               \
+    hipLaunchKernelGGL((decode_select_group_kernel<DS, BF, SH>), grid, block, kGroupLdsBytes, stream, q, cos_b, \
+                       sin_b, codebook, q_rot, lut, lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, NG, n_lut,   \
+                       make_grid_map(1, n_lut, NG, d.n_kv_heads), keys, weights, mode, codes, n_new, pos0,      \
+                       d.ctx_stride, ap.sweeps, ap.folded, seq_lens, topk_idx, topk_count, topk_score, d.ctx_len, \
+                       top_k, window, n_sink);                                                                  \
+  } while (0)
+#define A2ATS_LAUNCH_GRP2(DS, BF, SLOT)                   \
+  do {                                                    \
+    if (shared) A2ATS_LAUNCH_GRP(DS, BF, true, SLOT + 4); \
+    else A2ATS_LAUNCH_GRP(DS, BF, false, SLOT);           \
+  } while (0)
+  if (d.sub_dim == 8) {
+    if (q_dtype == A2ATS_BF16) A2ATS_LAUNCH_GRP2(8, true, 0); else A2ATS_LAUNCH_GRP2(8, false, 1);
+  } else {
+    if (q_dtype == A2ATS_BF16) A2ATS_LAUNCH_GRP2(4, true, 2); else A2ATS_LAUNCH_GRP2(4, false, 3);
+  }
+#undef A2ATS_LAUNCH_GRP2
+#undef A2ATS_LAUNCH_GRP
+  return hipGetLastError();
+}
+
 hipError_t launch_decode_select_prologue(const a2ats_dims& d, const float* keys, int n_new, int pos0,
                                          const float* codebook, const float* weights, int mode, uint8_t* codes,
                                          const void* q, int q_dtype, const float* cos_b, const float* sin_b,
@@ -420,20 +515,13 @@ hipError_t launch_decode_prologue(const a2ats_dims& d, const float* keys, int n_
   const int G = d.n_q_heads / d.n_kv_heads;
   const int NG = (G + kHeadsPerGroup - 1) / kHeadsPerGroup;
   const int n_lut = d.batch * d.n_kv_heads * NG;
-  const long n_pairs = (long)d.batch * d.n_kv_heads * n_new * d.n_sub;
-  int sweeps = encode_few_sweeps(n_pairs);
-  long n_enc = (n_pairs + (long)kFewPairsPerSweep * sweeps - 1) / ((long)kFewPairsPerSweep * sweeps);
-  const int folded = n_lut > 0 && n_lut + n_enc > 256;
-  if (folded) {
-    sweeps = (int)((n_pairs + (long)kFewPairsPerSweep * n_lut - 1) / ((long)kFewPairsPerSweep * n_lut));
-    n_enc = 0;
-  }
-  const dim3 grid(n_lut + (unsigned)n_enc), block(kLutThreads);
+  const AppendPlan ap = append_plan((long)d.batch * d.n_kv_heads * n_new * d.n_sub, n_lut);
+  const dim3 grid(n_lut + ap.n_enc), block(kLutThreads);
   if (grid.x == 0) return hipSuccess;
 #define A2ATS_LAUNCH_PRO(DS, BF)                                                                       \
   hipLaunchKernelGGL((decode_prologue_kernel<DS, BF>), grid, block, 0, stream, q, cos_b, sin_b, codebook, \
                      q_rot, lut, lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, NG, n_lut, keys, weights, \
-                     mode, codes, n_new, pos0, d.ctx_stride, sweeps, folded)
+                     mode, codes, n_new, pos0, d.ctx_stride, ap.sweeps, ap.folded)
   if (d.sub_dim == 8) {
     if (q_dtype == A2ATS_BF16) A2ATS_LAUNCH_PRO(8, true); else A2ATS_LAUNCH_PRO(8, false);
   } else {

@@ -108,6 +108,33 @@ __device__ __forceinline__ void load_coarse_table(const int32_t* __restrict__ lu
   }
 }
 
+// The bin that holds the k-th largest of the scores counted in a 2048-bin histogram of coarse scores >> 5
+// (16-bit counts: `shift` 0 or 16 picks the head's half of a word), -1 if fewer than k are counted.  By one
+// whole wave: lane l owns bins [32 l, 32 l + 32); a suffix scan over the lanes finds the one whose range
+// holds the rank; the wave then searches that range.
+__device__ __forceinline__ int wave_find_bin(const uint32_t* hist, int shift, uint32_t k, int lane) {
+  uint32_t sum = 0;
+#pragma unroll
+  for (int i = 0; i < 32; ++i) {
+    const int ii = (i + lane) & 31;   // rotate the walk so the lanes of a read hit different banks
+    sum += (hist[32 * lane + ii] >> shift) & 0xffffu;
+  }
+  // inclusive suffix sum over lanes (higher lanes hold higher bins) = total - exclusive prefix
+  const uint32_t pre = wave_inclusive_scan(sum);
+  const uint32_t inc = (uint32_t)__builtin_amdgcn_readlane((int)pre, 63) - pre + sum;
+  const uint32_t above_lane = inc - sum;
+  const uint64_t owner = __ballot(above_lane < k && k <= inc);   // the lane whose 32 bins hold the rank
+  if (owner == 0) return -1;
+  // Second level: lane i < 32 takes bin 31 - i of the owner's range (so bins descend with the lane
+  // index) and a prefix sum finds the first lane that reaches k.
+  const int src = __ffsll((unsigned long long)owner) - 1;
+  const uint32_t above = (uint32_t)__builtin_amdgcn_readlane((int)above_lane, src);
+  const uint32_t c = lane < 32 ? (hist[32 * src + 31 - lane] >> shift) & 0xffffu : 0u;
+  const uint32_t incl = wave_inclusive_scan(c);   // lanes >= 32 hold zeros
+  const uint64_t reach = __ballot(lane < 32 && above + incl >= k);
+  return 32 * src + 31 - (__ffsll((unsigned long long)reach) - 1);
+}
+
 // One sampling workgroup: part p of the P0 parts of problem `prob` (a sequence, KV head and group
 // of four query heads).  `tbl`: kCoarseLdsBytes of LDS for the group's coarse table; TABLE_IN_LDS:
 // the caller has put the table there already (and synchronised), otherwise it is copied from `lut`.
@@ -196,38 +223,17 @@ __device__ __forceinline__ void sample_threshold_body(
     }
   }
   __syncthreads();
-  // Rank search, one wave per head: lane l owns bins [32 l, 32 l + 32); a suffix scan over the
-  // lanes finds the one whose range holds the r_p-th largest sample; the wave then searches that range.
+  // Rank search, one wave per head.
   if (wv < kHeadsPerGroup) {
     const int r = wv;
     const int hg = g4 * kHeadsPerGroup + r;
     const uint32_t* hrow = s_hist[r >> 1];
     const int fsh = 16 * (r & 1);
-    uint32_t sum = 0;
-#pragma unroll
-    for (int i = 0; i < 32; ++i) {
-      const int ii = (i + lane) & 31;   // rotate the walk so the lanes of a read hit different banks
-      sum += (hrow[32 * lane + ii] >> fsh) & 0xffffu;
-    }
-    // inclusive suffix sum over lanes (higher lanes hold higher bins) = total - exclusive prefix
-    const uint32_t pre = wave_inclusive_scan(sum);
-    const uint32_t inc = (uint32_t)__builtin_amdgcn_readlane((int)pre, 63) - pre + sum;
-    const uint32_t k = (uint32_t)r_p, above_lane = inc - sum;
-    const uint64_t owner = __ballot(above_lane < k && k <= inc);   // the lane whose 32 bins hold the rank
-    if (owner != 0 && hg < G) {
-      // Second level, by the whole wave: lane i < 32 takes bin 31 - i of the owner's range (so
-      // bins descend with the lane index) and a prefix sum finds the first lane that reaches k.
-      const int src = __ffsll((unsigned long long)owner) - 1;
-      const uint32_t above = (uint32_t)__builtin_amdgcn_readlane((int)above_lane, src);
-      const uint32_t c = lane < 32 ? (hrow[32 * src + 31 - lane] >> fsh) & 0xffffu : 0u;
-      const uint32_t incl = wave_inclusive_scan(c);   // lanes >= 32 hold zeros
-      const uint64_t reach = __ballot(lane < 32 && above + incl >= k);
-      const int bin = 32 * src + 31 - (__ffsll((unsigned long long)reach) - 1);
-      // Lower edge of the bin holding the r_p-th largest sample (at least r_p samples reach it),
-      // lowered by M: a row's coarse score is below its exact score by less than M coarse units,
-      // and the final kernel needs that much slack to prove its result complete.
-      if (lane == 0) thr[((size_t)b * Hq + kv * G + hg) * P0 + p] = max(0, (bin << 5) - M);
-    }
+    const int bin = wave_find_bin(hrow, fsh, (uint32_t)r_p, lane);
+    // Lower edge of the bin holding the r_p-th largest sample (at least r_p samples reach it),
+    // lowered by M: a row's coarse score is below its exact score by less than M coarse units,
+    // and the final kernel needs that much slack to prove its result complete.
+    if (lane == 0 && bin >= 0 && hg < G) thr[((size_t)b * Hq + kv * G + hg) * P0 + p] = max(0, (bin << 5) - M);
   }
 }
 

@@ -1,0 +1,276 @@
+// The top-K of the (up to) four query heads of a group by one workgroup, for sequences whose candidates fit
+// its registers (at most 16384): the short-context route of a2ats_score_topk.
+//
+// Every row is scored once for the four heads (one 8-byte LDS read per code byte, coarse_score.hpp) and the
+// coarse scores stay in registers.  A histogram over them gives, per head, the 32-wide bin of the K-th largest
+// coarse score, and since exact = base + (coarse << s) + rem with 0 <= rem < M 2^s
+//   - a row at least M units above that bin is a winner: every row with a score as high has a coarse score
+//     above the bin, and there are fewer than K of those;
+//   - a row at least M units below the bin is not: K rows have coarse scores in the bin or above, hence
+//     exact scores above its own;
+//   - only the rows in between (the band, 32 + 2 M units wide: some tens of rows) are scored exactly and
+//     ranked among themselves, by (score, position).
+// Winners are marked in a bitmap over the positions, from which they are written in ascending order.
+//
+// What bounds it: one workgroup per CU (the tables and 108 registers a thread), its phases one after the other.
+// At 16384 tokens, K 491: table and first rows 1.7 us (5 with all CUs asking at once), scores and histogram 12.3
+// (LDS: 16 gathers and four atomics a row), bin 0.8, winners and band 4.6, exact band 3.1, ranks 1.4, output 1.2.
+// The exact route, which served these contexts before, scores every row once per head (four times the LDS reads)
+// and needs a workgroup per head: 64 sequences of 16384 tokens, 32 heads: 187 us, and 34 us for the tables before
+// it, against 99 us for tables and selection in one launch (build_lut.hip); one sequence of 4096 tokens, 4 heads:
+// 21 us in two launches against 20 us in one.
+// Counting only rows above a floor taken from a sample, to save atomics, was slower (15.8 us for scores and
+// histogram): the branches cost more than the atomics.
+#pragma once
+#include "common.hpp"
+#include "coarse_score.hpp"
+#include "exact_select.hpp"
+
+namespace a2ats {
+
+// `old` with lane `lane` (a constant) replaced by the wave-uniform `value`.
+__device__ uint32_t write_lane(uint32_t value, uint32_t lane, uint32_t old) __asm("llvm.amdgcn.writelane.i32");
+
+constexpr int kGroupThreads = 1024;
+constexpr int kGroupWaves = kGroupThreads / 64;
+constexpr int kGroupRows = 16;                               // rows per thread
+constexpr int kGroupMaxCand = kGroupThreads * kGroupRows;    // candidates of a sequence, at most
+constexpr int kBandCap = 1024;                               // band rows per head
+struct GroupLds {
+  uint32_t hist[2][kHistBins];   // two heads per word, 16-bit counts (at most 16384 rows)
+  uint64_t won[kHeadsPerGroup][kGroupMaxCand / 64];
+  uint64_t band[kHeadsPerGroup][kBandCap];   // a position, then (exact key, position complemented)
+  uint32_t n_band[kHeadsPerGroup];
+  uint32_t n_sure[kHeadsPerGroup];
+  int32_t bin[kHeadsPerGroup];
+  uint32_t wave_tot[kGroupWaves];
+};
+// Behind the coarse table; a head whose band overflows is redone by the exact route in the same memory.
+constexpr size_t kGroupWorkBytes = sizeof(GroupLds) > sizeof(ExactLds) ? sizeof(GroupLds) : sizeof(ExactLds);
+constexpr size_t kGroupLdsBytes = kCoarseLdsBytes + (kGroupWorkBytes + 15) / 16 * 16;
+static_assert(kExactLdsBytes <= kCoarseLdsBytes, "the exact table of a redone head takes the coarse table's place");
+
+// Called by all kGroupThreads threads of a workgroup.  dyn_lds: kGroupLdsBytes.  TABLE_IN_LDS: the caller has
+// put the group's coarse table at its start (a barrier follows here), otherwise it is copied from `lut`.
+template <int M, bool TABLE_IN_LDS>
+__device__ __forceinline__ void group_select_body(
+    int b, int kv, int g4, int prob, const uint8_t* __restrict__ codes, const CodePages& pg,
+    const int32_t* __restrict__ lut, const float* __restrict__ lut_scale, const int32_t* __restrict__ seq_lens,
+    int32_t* __restrict__ topk_idx, int32_t* __restrict__ topk_count, float* __restrict__ topk_score, int B, int Hq,
+    int Hkv, int ctx_len, int64_t ctx_stride, int top_k, int window, int n_sink, unsigned char* dyn_lds) {
+  constexpr int NT = kGroupThreads;
+  constexpr int U = M == 16 ? 4 : 1;   // rows a thread requests together
+  unsigned char* tbl = dyn_lds;
+  GroupLds& L = *(GroupLds*)(dyn_lds + kCoarseLdsBytes);
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int G = Hq / Hkv, head0 = b * Hq + kv * G + g4 * kHeadsPerGroup;
+  const int n_real = min(kHeadsPerGroup, G - g4 * kHeadsPerGroup);   // heads of this group that exist
+  const SeqRange sr = seq_range(ctx_len, seq_lens, b, window, n_sink, top_k);
+  const SeqCodes seq_codes = seq_codes_of<M>(codes, pg, b, kv, Hkv, ctx_stride);
+  const LutLayout lay = lut_layout(B, Hq, Hkv, M);
+
+  if (tid < n_real) topk_count[head0 + tid] = sr.kk;
+  for (int r = 0; r < n_real; ++r)
+    for (int t = sr.kk + tid; t < top_k; t += NT) {
+      topk_idx[(size_t)(head0 + r) * top_k + t] = -1;
+      if (topk_score) topk_score[(size_t)(head0 + r) * top_k + t] = 0.f;
+    }
+  if (sr.kk == 0) return;   // (uniform)
+
+  // Wave w owns chunks w n_i .. w n_i + n_i - 1 of 64 consecutive rows, so the chunks of a wave, and the waves,
+  // follow each other in position.
+  const int lo = sr.sink_end, hi = sr.win_start;
+  const int n_i = (sr.ncand + NT - 1) / NT;   // 1 .. kGroupRows
+  const int row0 = lo + wv * n_i * 64 + lane;
+  LaneSwizzle<M> sw;
+  sw.init(lane);
+  auto load_rows = [&](int i0, uint4 (&dst)[U][M / 16]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint8_t* row = row_ptr<M>(seq_codes, min(row0 + (i0 + u) * 64, hi - 1));
+#pragma unroll
+      for (int qd = 0; qd < M / 16; ++qd) dst[u][qd] = *(const uint4*)(row + ((uint32_t)(qd * 16) ^ sw.row_swz));
+    }
+  };
+  uint4 rows[2][U][M / 16];
+  load_rows(0, rows[0]);   // (before the table, so that the latencies overlap)
+  if (!TABLE_IN_LDS) load_coarse_table<M, NT>(lut, lay, prob, tbl);
+  for (int i = tid; i < 2 * kHistBins; i += NT) (&L.hist[0][0])[i] = 0;
+  if (tid < kHeadsPerGroup) {
+    L.n_band[tid] = 0;
+    L.n_sure[tid] = 0;
+  }
+  __syncthreads();
+
+  // --- coarse scores of every row, and their histogram
+  uint32_t a01[kGroupRows], a23[kGroupRows];
+  const bool take_all = sr.kk >= sr.ncand;   // (uniform)
+#pragma unroll
+  for (int q = 0; q < kGroupRows / U; ++q) {
+    const int i0 = q * U;
+    if (i0 < n_i) {   // (uniform, as the conditions below)
+      if (i0 + U < n_i) load_rows(i0 + U, rows[(q + 1) & 1]);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (i0 + u >= n_i) continue;   // (a chunk past the wave's last is another wave's)
+        score_coarse<M, false>(rows[q & 1][u], tbl, sw, a01[i0 + u], a23[i0 + u]);
+        if (!take_all && row0 + (i0 + u) * 64 < hi) {
+          const uint32_t w01 = a01[i0 + u], w23 = a23[i0 + u];
+          atomicAdd(&L.hist[0][(w01 & 0xffffu) >> 5], 1u);
+          if (n_real > 1) atomicAdd(&L.hist[0][w01 >> 21], 1u << 16);
+          if (n_real > 2) atomicAdd(&L.hist[1][(w23 & 0xffffu) >> 5], 1u);
+          if (n_real > 3) atomicAdd(&L.hist[1][w23 >> 21], 1u << 16);
+        }
+        if ((u & 1) || M == 32) __builtin_amdgcn_sched_barrier(0);   // 32 gathers at a time: bounds live registers
+      }
+    }
+  }
+  __syncthreads();
+  if (wv < n_real && !take_all) {
+    const int bin = wave_find_bin(L.hist[wv >> 1], 16 * (wv & 1), (uint32_t)sr.kk, lane);
+    if (lane == 0) L.bin[wv] = bin;
+  }
+  __syncthreads();
+
+  // --- winners and band rows.  Lane r 16 + i collects the winners of head r in chunk i.
+  // (No coarse score is above 65520: 0xffff keeps the slots past the group's last head empty.)
+  uint32_t t_lo[kHeadsPerGroup], t_hi[kHeadsPerGroup];
+#pragma unroll
+  for (int r = 0; r < kHeadsPerGroup; ++r) {
+    const int bin = take_all ? 0 : __builtin_amdgcn_readfirstlane(L.bin[min(r, n_real - 1)]);
+    t_lo[r] = r >= n_real ? 0xffffu : (take_all ? 0u : (uint32_t)max(0, (bin << 5) - M + 1));
+    t_hi[r] = r >= n_real ? 0xffffu : (take_all ? 0u : (uint32_t)min(0xffff, (bin << 5) + 32 + M));
+  }
+  // The low half of a word is compared as 16 bits, the high half as the whole word against the threshold
+  // shifted up: no extraction.
+  auto reaches = [](uint32_t word, int half, uint32_t t) {
+    return __builtin_amdgcn_ballot_w64(half ? word >= (t << 16) : (uint16_t)word >= (uint16_t)t);
+  };
+  {
+    // (two compares, two scalar ands and four lane writes per head and chunk, no branch: a branch on "any
+    // band row here" costs a dependent scalar chain each, 7.1 us instead of 4.6 for 16384 rows)
+    uint32_t s_lo = 0, s_hi = 0, b_lo = 0, b_hi = 0;
+#pragma unroll
+    for (int i = 0; i < kGroupRows; ++i) {
+      if (i < n_i) {
+        const uint64_t valid = __builtin_amdgcn_ballot_w64(row0 + i * 64 < hi);
+#pragma unroll
+        for (int r = 0; r < kHeadsPerGroup; ++r) {
+          const uint64_t sure = reaches(r < 2 ? a01[i] : a23[i], r & 1, t_hi[r]) & valid;
+          const uint64_t some = reaches(r < 2 ? a01[i] : a23[i], r & 1, t_lo[r]) & valid;
+          s_lo = write_lane((uint32_t)sure, r * kGroupRows + i, s_lo);
+          s_hi = write_lane((uint32_t)(sure >> 32), r * kGroupRows + i, s_hi);
+          b_lo = write_lane((uint32_t)some, r * kGroupRows + i, b_lo);
+          b_hi = write_lane((uint32_t)(some >> 32), r * kGroupRows + i, b_hi);
+        }
+      }
+    }
+    const int r = lane / kGroupRows, i = lane % kGroupRows;
+    const uint64_t sure = ((uint64_t)s_hi << 32) | s_lo;
+    uint64_t band = (((uint64_t)b_hi << 32) | b_lo) & ~sure;
+    if (i < n_i) {   // (lanes of chunks past the wave's last hold zeros)
+      L.won[r][wv * n_i + i] = sure;
+      if (sure) atomicAdd(&L.n_sure[r], (uint32_t)__popcll(sure));
+    }
+    if (band) {
+      uint32_t slot = atomicAdd(&L.n_band[r], (uint32_t)__popcll(band));
+      const uint32_t j0 = (uint32_t)(lo + (wv * n_i + i) * 64 - 1);
+      for (; band && slot < (uint32_t)kBandCap; ++slot, band &= band - 1)
+        L.band[r][slot] = j0 + (uint32_t)__ffsll((unsigned long long)band);
+    }
+  }
+  __syncthreads();
+
+  // --- the band: exact keys, then every row counts those before it in (score, position) order
+  uint32_t first[kHeadsPerGroup + 1];
+  uint32_t redo = 0;
+  first[0] = 0;
+#pragma unroll
+  for (int r = 0; r < kHeadsPerGroup; ++r) {
+    const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.n_band[r]);
+    redo |= n > (uint32_t)kBandCap ? 1u << r : 0u;
+    first[r + 1] = first[r] + (n > (uint32_t)kBandCap ? 0u : n);
+  }
+  auto head_of = [&](uint32_t e) {
+    return (e >= first[1] ? 1 : 0) + (e >= first[2] ? 1 : 0) + (e >= first[3] ? 1 : 0);
+  };
+  auto first_of = [&](int r) { return r == 0 ? 0u : (r == 1 ? first[1] : (r == 2 ? first[2] : first[3])); };
+  auto exact_at = [&](int r, int j) {
+    const int32_t* t = lut + lay.off_exact + (size_t)(head0 + r) * (kCentroids * M);
+    const uint8_t* row = row_ptr<M>(seq_codes, j);
+    uint4 w[M / 16];
+    int32_t s = 0;
+#pragma unroll
+    for (int qd = 0; qd < M / 16; ++qd) w[qd] = *(const uint4*)(row + qd * 16);
+#pragma unroll
+    for (int qd = 0; qd < M / 16; ++qd) {
+      const uint32_t d[4] = {w[qd].x, w[qd].y, w[qd].z, w[qd].w};
+#pragma unroll
+      for (int t4 = 0; t4 < 16; ++t4) s += t[((d[t4 >> 2] >> (8 * (t4 & 3))) & 0xffu) * M + qd * 16 + t4];
+    }
+    return s;
+  };
+  for (uint32_t e = tid; e < first[4]; e += NT) {
+    const int r = head_of(e);
+    const uint32_t i = e - first_of(r);
+    const uint32_t j = (uint32_t)L.band[r][i];
+    L.band[r][i] = ((uint64_t)score_key(exact_at(r, (int)j)) << 32) | ~j;   // (of equal scores the lower position is larger)
+  }
+  __syncthreads();
+  // (eight lanes share a row: the lists are short and every step is an LDS round trip)
+  for (uint32_t e = tid >> 3; e < first[4]; e += NT / 8) {
+    const int r = head_of(e);
+    const uint32_t f = first_of(r), i = e - f, n = (r == 0 ? first[1] : (r == 1 ? first[2] : (r == 2 ? first[3] : first[4]))) - f;
+    const uint64_t own = L.band[r][i];
+    int32_t before = 0;
+#pragma unroll 4
+    for (uint32_t u = tid & 7; u < n; u += 8) before += L.band[r][u] > own ? 1 : 0;
+    before = group8_sum(before);
+    if ((tid & 7) == 0 && (uint32_t)before < (uint32_t)sr.kk - L.n_sure[r]) {
+      const uint32_t bit = ~(uint32_t)own - (uint32_t)lo;
+      atomicOr((uint32_t*)&L.won[r][0] + (bit >> 5), 1u << (bit & 31));
+    }
+  }
+  __syncthreads();
+
+  // --- winners in ascending position: head tid / 256, 64 positions per thread
+  {
+    const int r = tid >> 8, q = tid & 255;
+    uint64_t word = (q < kGroupWaves * n_i && r < n_real && !((redo >> r) & 1u)) ? L.won[r][q] : 0ull;
+    const uint32_t n = (uint32_t)__popcll(word);
+    const uint32_t inc = wave_inclusive_scan(n);
+    if (lane == 63) L.wave_tot[wv] = inc;
+    __syncthreads();
+    uint32_t at = inc - n;
+    for (int w = wv & ~3; w < wv; ++w) at += L.wave_tot[w];
+    int32_t* oi = topk_idx + (size_t)(head0 + r) * top_k;
+    while (word) {
+      if (at < (uint32_t)sr.kk) oi[at] = lo + q * 64 + __ffsll((unsigned long long)word) - 1;
+      ++at;
+      word &= word - 1;
+    }
+  }
+  if (topk_score) {
+    __syncthreads();
+    for (int r = 0; r < n_real; ++r)
+      if (!((redo >> r) & 1u))
+        for (int t = tid; t < sr.kk; t += NT)
+          topk_score[(size_t)(head0 + r) * top_k + t] =
+              (float)exact_at(r, topk_idx[(size_t)(head0 + r) * top_k + t]) * lut_scale[head0 + r];
+  }
+  // --- heads with more band rows than the list holds (many equal scores): the exact route
+#pragma unroll 1
+  for (int r = 0; r < n_real; ++r)
+    if ((redo >> r) & 1u) {
+      const size_t bh = (size_t)(head0 + r);
+      SeqCodes rows = seq_codes;
+      SeqRange range = sr;
+      // (else the addresses of all rows are formed before the loop, and spilled)
+      asm volatile("" : "+s"(rows.base), "+s"(range.sink_end));
+      exact_select_block<M>(rows, lut + lay.off_exact + bh * (kCentroids * M), lut + lay.off_meta + bh * 4,
+                            lut_scale[bh], range, topk_idx + bh * top_k, topk_score ? topk_score + bh * top_k : nullptr,
+                            tbl, *(ExactLds*)(dyn_lds + kCoarseLdsBytes));
+    }
+}
+
+}  // namespace a2ats

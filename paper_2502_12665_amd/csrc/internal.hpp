@@ -76,6 +76,15 @@ hipError_t launch_decode_select_prologue(const a2ats_dims& d, const float* keys,
                                          float* q_rot, int32_t* lut, float* lut_scale, const int32_t* seq_lens,
                                          int32_t* thr, int P0, int sample_rows, int top_k, int window, int n_sink,
                                          bool shared, hipStream_t stream);
+// The whole of a2ats_decode_select (shared: a2ats_decode_select_shared) in one launch, for contexts whose
+// candidates fit one workgroup (decode_select_group_fits) and no appended row among the candidates.
+bool decode_select_group_fits(const a2ats_dims& d, int window, int n_sink);
+hipError_t launch_decode_select_group(const a2ats_dims& d, const float* keys, int n_new, int pos0,
+                                      const float* codebook, const float* weights, int mode, uint8_t* codes,
+                                      const void* q, int q_dtype, const float* cos_b, const float* sin_b, float* q_rot,
+                                      int32_t* lut, float* lut_scale, const int32_t* seq_lens, int top_k, int window,
+                                      int n_sink, int32_t* topk_idx, int32_t* topk_count, float* topk_score,
+                                      bool shared, hipStream_t stream);
 hipError_t launch_sparse_attn(const a2ats_dims& d, const void* q, const float* q_rot, const void* k_cache,
                               const void* v_cache, int kv_dtype, const int32_t* topk_idx,
                               const int32_t* topk_count, int top_k, int window, int n_sink,

@@ -1,9 +1,11 @@
 // Step 3 of a decode step: approximate scores by gather-summing fixed-point table entries
 // through the uint8 codes (section 4.2 last equation), and exact per-head top-K (section 4).
 //
-// Two routes, chosen on the host from the shape:
+// Three routes, chosen on the host from the shape:
 //
-//  exact route (short contexts; also the in-kernel fallback of the fast route):
+//  group route (at most 16384 candidates): one workgroup for the four heads of a group, group_select.hpp.
+//
+//  exact route (the in-kernel fallback of the others, and more than 2048 winners without a workspace):
 //  one workgroup per query head runs an MSB-first radix select over the 32-bit score keys by
 //  re-streaming its sequence (<= 3 histogram passes), then one ordered pass that emits the
 //  winners in ascending position, equal scores going to the lower position.
@@ -35,16 +37,16 @@
 #include "common.hpp"
 #include "internal.hpp"
 #include "coarse_score.hpp"
+#include "exact_select.hpp"
+#include "group_select.hpp"
 
 namespace a2ats {
 
-constexpr int kExactThreads = 1024;
 constexpr int kStreamThreads = 512;
 constexpr int kStreamWaves = kStreamThreads / 64;
 constexpr int kSampleThreads = 512;
 constexpr int kSegMeta = 8;          // words of a segment header: rows, 4 per-head counts, padding
 constexpr int kSampleRows = 1024;    // smallest sample of a problem; a sampling workgroup scores up to 8 of these
-constexpr int kSmallList = 1024;     // members of the K-th key's bin ranked by brute force
 
 TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink) {
   TopkPlan p{};
@@ -130,92 +132,6 @@ TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink) 
   return p;
 }
 
-// ------------------------------------------------------------------------------------------
-// Scoring primitives
-// ------------------------------------------------------------------------------------------
-
-// Exact score of one token for one head.  The head's table sits in LDS with one 256-byte row per
-// centroid id c; the 4-byte entry of subspace m is at byte m << 2 of the row (M = 32), or, for
-// M = 16, twice: at m << 2 and at 64 + (m << 2).  LDS serves a 4-byte read 32 lanes at a time.
-// Lane L visits the subspaces of its row in the order m = t ^ (L & 15) within a 16-byte half row,
-// and lanes 16..31 of each half-wave use the second copy (M = 16) or take the two half rows in the
-// other order (M = 32): the 32 lanes served together then touch 32 different banks whatever the
-// code bytes are (a [m][c] table would spread them at random: ~3.5 lanes on the busiest bank).
-// The visiting order does not change the result because the scores are integer sums.
-constexpr int kExactLdsBytes = kCentroids * 256;
-
-template <int M, int NT>
-__device__ __forceinline__ void load_exact_table(const int32_t* __restrict__ head_table, unsigned char* tbl) {
-  const int4* src = (const int4*)head_table;   // [256 c][M] int32
-#pragma unroll 4
-  for (int e = threadIdx.x; e < kCentroids * M / 4; e += NT) {
-    const int c = e / (M / 4), mq = e % (M / 4);
-    const int4 v = src[e];
-    *(int4*)(tbl + (c << 8) + (mq << 4)) = v;
-    if (M == 16) *(int4*)(tbl + (c << 8) + 64 + (mq << 4)) = v;
-  }
-}
-
-template <int M>
-struct ExactSwizzle {
-  uint32_t mc[M / 4];   // byte t&3 of mc[t>>2]: low address byte for step t of this lane
-  uint32_t sel[4];      // v_perm selectors: address byte 1 <- code byte (k ^ b), byte 0 <- mc byte k
-  bool swap1, swap2;    // dword index inside a half row is XORed with (rho >> 2)
-  bool swaph;           // M = 32: this lane takes the two half rows in the other order
-  __device__ __forceinline__ void init(int lane) {
-    const uint32_t rho = lane & 15, b = rho & 3, hi = (lane >> 4) & 1;
-#pragma unroll
-    for (int d = 0; d < M / 4; ++d) {
-      uint32_t v = 0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const uint32_t t = 4 * d + k;
-        const uint32_t m_low = (t ^ rho) & 15u, half = t >> 4;
-        const uint32_t byte = M == 16 ? ((hi << 6) | (m_low << 2)) : ((((half ^ hi) << 4) | m_low) << 2);
-        v |= byte << (8 * k);
-      }
-      mc[d] = v;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) sel[k] = 0x0c0c0000u | ((4u + ((uint32_t)k ^ b)) << 8) | (uint32_t)k;
-    swap1 = (rho >> 2) & 1;
-    swap2 = (rho >> 3) & 1;
-    swaph = M == 32 && hi;
-  }
-};
-
-template <int M>
-__device__ __forceinline__ int32_t score_exact(const uint4 (&w)[M / 16], const unsigned char* tbl,
-                                               const ExactSwizzle<M>& sw) {
-  int32_t s = 0;
-#pragma unroll
-  for (int qd = 0; qd < M / 16; ++qd) {
-    uint4 h = w[qd];
-    if (M == 32) {
-      const uint4 o = w[(M / 16 - 1) - qd];
-      h = make_uint4(sw.swaph ? o.x : h.x, sw.swaph ? o.y : h.y, sw.swaph ? o.z : h.z, sw.swaph ? o.w : h.w);
-    }
-    const uint32_t x0 = sw.swap1 ? h.y : h.x, x1 = sw.swap1 ? h.x : h.y;
-    const uint32_t x2 = sw.swap1 ? h.w : h.z, x3 = sw.swap1 ? h.z : h.w;
-    const uint32_t z[4] = {sw.swap2 ? x2 : x0, sw.swap2 ? x3 : x1, sw.swap2 ? x0 : x2, sw.swap2 ? x1 : x3};
-#pragma unroll
-    for (int t = 0; t < 16; ++t) {
-      const uint32_t off = __builtin_amdgcn_perm(z[t >> 2], sw.mc[qd * 4 + (t >> 2)], sw.sel[t & 3]);
-      s += *(const int32_t*)(tbl + off);
-    }
-  }
-  return s;
-}
-
-template <int M>
-__device__ __forceinline__ int32_t score_exact_row(const uint8_t* row, const unsigned char* tbl,
-                                                   const ExactSwizzle<M>& sw) {
-  uint4 w[M / 16];
-#pragma unroll
-  for (int qd = 0; qd < M / 16; ++qd) w[qd] = *(const uint4*)(row + qd * 16);
-  return score_exact<M>(w, tbl, sw);
-}
-
 // The P0 sampling workgroups of a problem each estimate a head's threshold from their share of the
 // sample; the streaming and final kernels use the mean of the estimates (rounded down), which is
 // close to what one rank search over the merged sample would give.  INT32_MIN ("take every row")
@@ -257,209 +173,6 @@ __host__ __device__ __forceinline__ size_t segment_words(int row_cap) {
 __device__ __forceinline__ uint32_t entry_pos(uint32_t w0) { return w0 & 0xfffffu; }
 __device__ __forceinline__ bool entry_wanted(uint32_t w0, int r) { return (w0 >> (20 + r)) & 1u; }
 
-// ------------------------------------------------------------------------------------------
-// Exact route (also the fallback of the fast route)
-// ------------------------------------------------------------------------------------------
-constexpr int kKeepRows = 16;   // rows per thread the exact route keeps in registers (16384 candidates)
-struct ExactLds {
-  uint32_t hist[kHistBins];
-  uint32_t wave_a[kExactThreads / 64];
-  uint32_t wave_b[kExactThreads / 64];
-  uint32_t res[2];
-  // emission with resident keys: packed (above, equal) counts per round and wave, their exclusive
-  // prefixes over the waves of a round, and the rounds' totals
-  uint32_t round_wave[kKeepRows][kExactThreads / 64];
-  uint32_t round_pre[kKeepRows][kExactThreads / 64];
-  uint32_t round_tot[kKeepRows];
-  // the keys of the K-th key's bin after a select level, when they are few enough to rank by counting
-  uint32_t small_n;
-  uint32_t small_key[kSmallList];
-};
-
-// Exact top-K for one head by the whole workgroup.  `head_table` is the head's [c][m] table in
-// global memory, `meta` its four table constants, `tbl` kExactLdsBytes of LDS.  Writes
-// out_idx[0..kk) ascending (and out_score); the caller has written the count and the -1 padding.
-// Requires sr.kk >= 1.
-template <int M>
-__device__ void exact_select_block(const SeqCodes& seq_codes,
-                                   const int32_t* __restrict__ head_table,
-                                   const int32_t* __restrict__ meta, float scale,
-                                   const SeqRange& sr, int32_t* __restrict__ out_idx,
-                                   float* __restrict__ out_score, unsigned char* tbl, ExactLds& L) {
-  constexpr int NT = kExactThreads;
-  const int tid = threadIdx.x;
-  const int32_t s_lo = meta[0], s_hi = meta[2];   // bounds of any score
-  ExactSwizzle<M> sw;
-  sw.init(tid & 63);
-  __syncthreads();   // tbl may alias LDS the caller was still reading
-  load_exact_table<M, NT>(head_table, tbl);
-  __syncthreads();
-
-  const int lo = sr.sink_end, hi = sr.win_start;
-  uint32_t kth = 0, k_rem = (uint32_t)sr.kk;
-  // Radix digits are taken from key - key(lower bound of any score), so that the histogram bins
-  // spread over the occupied range instead of all keys sharing their leading bits.
-  const uint32_t k_lo = score_key(s_lo);
-  // Up to kKeep rows per thread (16384 candidates: every shape that takes this route for its length)
-  // are scored once and their relative keys kept in registers; the select levels and the emission
-  // then work on those instead of streaming and scoring the rows again (4 passes at 4096 tokens:
-  // 23 us).  Thread t owns rows lo + t + i NT, the order of the streaming loops below.
-  constexpr int kKeep = kKeepRows;
-  const bool resident = hi - lo <= kKeep * NT;   // (uniform)
-  uint32_t keys[kKeep];
-  if (resident) {
-#pragma unroll
-    for (int i = 0; i < kKeep; ++i) {
-      const int j = lo + tid + i * NT;
-      keys[i] = j < hi ? score_key(score_exact_row<M>(row_ptr<M>(seq_codes, j), tbl, sw)) - k_lo : 0u;
-    }
-  }
-  if (sr.kk < sr.ncand) {
-    int remaining = 32 - __clz(score_key(s_hi) - k_lo);   // significant bits of a relative key
-    uint32_t prefix = 0, mask = 0;
-#pragma unroll 1
-    while (remaining > 0) {
-      const int bits = remaining < 11 ? remaining : 11;
-      const int shift = remaining - bits;
-      const uint32_t dmask = (1u << bits) - 1u;
-      for (int i = tid; i < kHistBins; i += NT) L.hist[i] = 0;
-      __syncthreads();
-      if (resident) {
-#pragma unroll
-        for (int i = 0; i < kKeep; ++i)
-          if (lo + tid + i * NT < hi && (keys[i] & mask) == prefix) atomicAdd(&L.hist[(keys[i] >> shift) & dmask], 1u);
-      } else {
-        for (int j = lo + tid; j < hi; j += NT) {
-          const uint32_t key = score_key(score_exact_row<M>(row_ptr<M>(seq_codes, j), tbl, sw)) - k_lo;
-          if ((key & mask) == prefix) atomicAdd(&L.hist[(key >> shift) & dmask], 1u);
-        }
-      }
-      __syncthreads();
-      block_find_rank_desc<NT, kHistBins>([&](int i) { return L.hist[i]; }, k_rem, L.wave_a, L.res);
-      const uint32_t bin = L.res[0], above = L.res[1], m_bin = L.hist[bin];
-      k_rem -= above;
-      prefix |= bin << shift;
-      mask |= dmask << shift;
-      remaining = shift;
-      if (tid == 0) L.small_n = 0;
-      __syncthreads();
-      if (resident && remaining > 0 && m_bin <= (uint32_t)kSmallList) {   // (uniform)
-        // The bin of the K-th key usually holds a handful of keys: they are listed and each member
-        // counts the members above and at its own key -- the member whose range contains k_rem is the
-        // K-th key.  (A crowded bin, heavy ties, goes on with the next radix level.)
-#pragma unroll
-        for (int i = 0; i < kKeep; ++i)
-          if (lo + tid + i * NT < hi && (keys[i] & mask) == prefix) L.small_key[atomicAdd(&L.small_n, 1u)] = keys[i];
-        __syncthreads();
-        if ((uint32_t)tid < m_bin) {
-          const uint32_t key = L.small_key[tid];
-          uint32_t gt = 0, eq = 0;
-          for (uint32_t u = 0; u < m_bin; ++u) {
-            const uint32_t ku = L.small_key[u];
-            gt += ku > key ? 1u : 0u;
-            eq += ku == key ? 1u : 0u;
-          }
-          if (gt < k_rem && k_rem <= gt + eq) {   // every member at the K-th key writes the same two words
-            L.res[0] = key;
-            L.res[1] = k_rem - gt;
-          }
-        }
-        __syncthreads();
-        prefix = L.res[0];
-        k_rem = L.res[1];
-        remaining = 0;
-        __syncthreads();   // L.res is rewritten by the caller's next use
-      }
-    }
-    kth = prefix + k_lo;
-  }
-
-  // Ordered emission: keys above the K-th, plus the first k_rem positions that equal it.
-  uint32_t eq_seen = 0, out_n = 0;
-  const bool take_all = sr.kk >= sr.ncand;
-  auto emit_round = [&](int base, bool have_key, uint32_t rel_key, bool& done) {
-    const int j = base + tid;
-    int32_t s = 0;
-    uint32_t gt = 0, eq = 0;
-    if (j < hi) {
-      s = have_key ? key_score(rel_key + k_lo) : score_exact_row<M>(row_ptr<M>(seq_codes, j), tbl, sw);
-      const uint32_t key = score_key(s);
-      gt = take_all ? 1u : (key > kth ? 1u : 0u);
-      eq = take_all ? 0u : (key == kth ? 1u : 0u);
-    }
-    uint32_t tot_eq, tot_sel;
-    const uint32_t ex_eq = block_exclusive_scan<NT>(eq, L.wave_a, tot_eq);
-    const uint32_t sel = gt | ((eq && (eq_seen + ex_eq < k_rem)) ? 1u : 0u);
-    const uint32_t ex_sel = block_exclusive_scan<NT>(sel, L.wave_b, tot_sel);
-    if (sel) {
-      const uint32_t pos = out_n + ex_sel;
-      out_idx[pos] = j;
-      if (out_score) out_score[pos] = (float)s * scale;
-    }
-    eq_seen += tot_eq;
-    out_n += tot_sel;
-    done = out_n >= (uint32_t)sr.kk;   // (uniform)
-  };
-  bool done = false;
-  if (resident) {
-    // All rounds at once: a wave scan of the packed (above, equal) flags per round, one scan over the
-    // waves of every round (16 lanes per round), then each thread places its winners -- two barriers
-    // instead of four per round.  A winner's slot is the number of keys above the K-th before it plus
-    // the number of equal keys before it that still fit (both counts grow with the position).
-    constexpr int NW = NT / 64;
-    static_assert(kKeep * NW <= NT && NW == 16, "one lane per (round, wave), 16 waves per round");
-    const int lane = tid & 63, wave = tid >> 6;
-    uint32_t flags = 0;        // bit 2 i: above the K-th key, bit 2 i + 1: equal to it
-    uint32_t pre[kKeep];
-#pragma unroll
-    for (int i = 0; i < kKeep; ++i) {
-      uint32_t own = 0;
-      if (lo + tid + i * NT < hi) {
-        const uint32_t key = keys[i] + k_lo;
-        own = take_all ? 1u : (key > kth ? 1u : (key == kth ? 0x10000u : 0u));
-      }
-      flags |= ((own & 1u) | ((own >> 16) << 1)) << (2 * i);
-      const uint32_t v = wave_inclusive_scan(own);
-      pre[i] = v - own;
-      if (lane == 63) L.round_wave[i][wave] = v;
-    }
-    __syncthreads();
-    if (tid < kKeep * NW) {
-      const int i = tid / NW, w = tid % NW;
-      const uint32_t own = L.round_wave[i][w];
-      uint32_t v = own;
-#pragma unroll
-      for (int off = 1; off < NW; off <<= 1) {
-        const uint32_t n = __shfl_up(v, off, NW);
-        if (w >= off) v += n;
-      }
-      L.round_pre[i][w] = v - own;
-      if (w == NW - 1) L.round_tot[i] = v;
-    }
-    __syncthreads();
-    uint32_t gt_base = 0, eq_base = 0;
-#pragma unroll
-    for (int i = 0; i < kKeep; ++i) {
-      const uint32_t f = (flags >> (2 * i)) & 3u;
-      if (f) {
-        const uint32_t p = pre[i] + L.round_pre[i][wave];
-        const uint32_t gt_before = gt_base + (p & 0xffffu), eq_before = eq_base + (p >> 16);
-        if ((f & 1u) || eq_before < k_rem) {
-          const uint32_t slot = gt_before + min(eq_before, k_rem);
-          out_idx[slot] = lo + tid + i * NT;
-          if (out_score) out_score[slot] = (float)key_score(keys[i] + k_lo) * scale;
-        }
-      }
-      const uint32_t tot = L.round_tot[i];
-      gt_base += tot & 0xffffu;
-      eq_base += tot >> 16;
-    }
-  } else {
-#pragma unroll 1
-    for (int base = lo; base < hi && !done; base += NT) emit_round(base, false, 0u, done);
-  }
-}
-
 template <int M>
 __global__ __launch_bounds__(kExactThreads) void select_exact_kernel(
     const uint8_t* __restrict__ codes, const int32_t* __restrict__ lut,
@@ -484,6 +197,23 @@ __global__ __launch_bounds__(kExactThreads) void select_exact_kernel(
   exact_select_block<M>(seq_codes_of<M>(codes, pg, b, kv, Hkv, ctx_stride),
                         lut + lay.off_exact + (size_t)bh * (kCentroids * M), lut + lay.off_meta + (size_t)bh * 4,
                         lut_scale[bh], sr, oi, os, dyn_lds, L);
+}
+
+// ------------------------------------------------------------------------------------------
+// Short contexts: one workgroup per problem
+// ------------------------------------------------------------------------------------------
+template <int M>
+__global__ __launch_bounds__(kGroupThreads) void group_select_kernel(
+    const uint8_t* __restrict__ codes, const int32_t* __restrict__ lut, const float* __restrict__ lut_scale,
+    const int32_t* __restrict__ seq_lens, int32_t* __restrict__ topk_idx, int32_t* __restrict__ topk_count,
+    float* __restrict__ topk_score, GridMap gm, CodePages pg, int B, int Hq, int Hkv, int ctx_len, int64_t ctx_stride,
+    int top_k, int window, int n_sink) {
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
+  int prob, part, b, kv, g4;
+  map_block(blockIdx.x, gm, prob, part);
+  split_problem(prob, gm, b, kv, g4);
+  group_select_body<M, false>(b, kv, g4, prob, codes, pg, lut, lut_scale, seq_lens, topk_idx, topk_count, topk_score, B,
+                              Hq, Hkv, ctx_len, ctx_stride, top_k, window, n_sink, dyn_lds);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1013,7 +743,7 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
   const size_t coarse_bytes = (size_t)kCoarseLdsBytes;
   const size_t lut1_bytes = kExactLdsBytes;
   hipError_t err;
-  static LdsSlot s_dense[16], s_exact[16], s_sample[16], s_stream[16], s_stream_r[16], s_stream_p[16], s_final[16];
+  static LdsSlot s_dense[16], s_exact[16], s_sample[16], s_stream[16], s_stream_r[16], s_stream_p[16], s_final[16], s_group[16];
   if (heads == 0) return hipSuccess;
 
   if (scores_out) {
@@ -1025,7 +755,15 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
     if ((err = hipGetLastError()) != hipSuccess) return err;
   }
 
-  if (!plan.fast && !(plan.wide && ws)) {
+  const bool streams = plan.fast || (plan.wide && ws);
+  if (!streams && (long)d.ctx_len - window - n_sink <= kGroupMaxCand) {
+    if ((err = allow_dynamic_lds(group_select_kernel<M>, kGroupLdsBytes, s_group)) != hipSuccess) return err;
+    hipLaunchKernelGGL((group_select_kernel<M>), dim3(problems), dim3(kGroupThreads), kGroupLdsBytes, stream, codes, lut,
+                       lut_scale, seq_lens, topk_idx, topk_count, topk_score, make_grid_map(1, problems, NG, Hkv), pg, B,
+                       Hq, Hkv, d.ctx_len, d.ctx_stride, top_k, window, n_sink);
+    return hipGetLastError();
+  }
+  if (!streams) {
     if ((err = allow_dynamic_lds(select_exact_kernel<M>, lut1_bytes, s_exact)) != hipSuccess) return err;
     hipLaunchKernelGGL((select_exact_kernel<M>), dim3(heads), dim3(kExactThreads), lut1_bytes, stream,
                        codes, lut, lut_scale, seq_lens, topk_idx, topk_count, topk_score, pg, B, Hq, Hkv,

@@ -43,3 +43,89 @@ def test_wide_selection_equals_the_exact_route(Bn, G, M, N, K, w, n_sink, lens, 
     assert B.workspace_bytes(H.dims_of(wl), B.OP_SCORE_TOPK, K, w) > 0
     for a, b in zip(_select(wl, xd, lens, True), _select(wl, xd, lens, False)):
         assert torch.equal(a, b)
+
+
+def _full_sort(wl, xd, st, seq_lens):
+    """Indices, counts and scores of a full sort of the table's exact integer scores (ties by position)."""
+    N, M, G, K, dev = wl.ctx_len, wl.n_sub, wl.group, wl.top_k, "cuda"
+    table = st.lut[:wl.batch * wl.n_q_heads * 256 * M].reshape(wl.batch, wl.n_q_heads, 256 * M).long()
+    idx = torch.full((wl.batch, wl.n_q_heads, K), -1, dtype=torch.int32, device=dev)
+    cnt = torch.zeros(wl.batch, wl.n_q_heads, dtype=torch.int32, device=dev)
+    score = torch.zeros(wl.batch, wl.n_q_heads, K, dtype=torch.float32, device=dev)
+    for b in range(wl.batch):
+        n = N if seq_lens is None else seq_lens[b]
+        end = max(n - wl.window, 0)
+        first = min(wl.n_sink, end)
+        pos = torch.arange(first, end, device=dev)
+        for h in range(wl.n_q_heads):
+            at = xd["codes"][b, h // G, first:end].long() * M + torch.arange(M, device=dev)
+            s = table[b, h][at].sum(1)
+            best = torch.sort(s * (1 << 20) + ((1 << 20) - 1 - pos), descending=True).indices[:K]
+            best = torch.sort(best).values
+            k = best.numel()
+            idx[b, h, :k], cnt[b, h] = (pos[best]).to(torch.int32), k
+            score[b, h, :k] = s[best].to(torch.float32) * st.lut_scale[b, h]
+    return idx, cnt, score.view(torch.int32)
+
+
+@pytest.mark.parametrize("Bn,G,M,N,K,w,n_sink,lens,rows", [
+    (2, 4, 16, 16384 + 63, 491, 63, 0, None, None),                      # the most candidates of the short route
+    (1, 7, 32, 16383, 4096, 0, 4, None, None),                           # two head groups, the largest K, M = 32
+    (3, 1, 16, 1025, 32, 0, 0, [1025, 1, 0], None),                      # one row past a round of the threads; one row; none
+    (2, 2, 16, 3000, 3000, 16, 0, [3000, 700], None),                    # K above the candidates: all of them
+    (1, 8, 16, 9000, 1, 64, 17, None, None),
+    (1, 3, 16, 5000, 900, 64, 4, None, "patterns"),                      # ~125 equal scores: ties inside the band
+    (2, 4, 32, 12000, 300, 64, 4, None, "equal"),                        # the band overflows: the exact route
+])
+def test_short_contexts_equal_a_full_sort(Bn, G, M, N, K, w, n_sink, lens, rows):
+    """The short-context route (one workgroup for the heads of a group) against a full sort."""
+    wl = synth.Workload("short", Bn, 2 * G, 2, 128, M, N, K, w, n_sink=n_sink, seed=N + K)
+    xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
+    if rows == "patterns":
+        xd["codes"][:] = xd["codes"][:, :, torch.randint(0, 40, (N,), device="cuda")]
+    if rows == "equal":
+        xd["codes"][:] = xd["codes"][:, :, :1]
+    got = _select(wl, xd, lens, True)
+    st = B.DecodeState(H.dims_of(wl), K, w, n_sink, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
+    B.build_lut(st.dims, xd["q"], st.cos_b, st.sin_b, xd["codebook"], st.q_rot, st.lut, st.lut_scale)
+    for a, b in zip(got, _full_sort(wl, xd, st, lens)):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("Bn,Hkv,G,M,N,K,w,n_sink,n_new,lens,shared", [
+    (2, 2, 7, 32, 9001, 300, 64, 4, 1, [9001, 2000], False),
+    (40, 8, 4, 16, 1500, 45, 64, 0, 2, None, False),                     # 320 table workgroups: they encode the append
+    (1, 1, 8, 32, 16384 + 128, 4096, 128, 0, 32, None, False),
+    (3, 2, 8, 32, 5000, 200, 64, 4, 1, [5000, 64, 0], True),
+    (2, 2, 4, 16, 6000, 0, 64, 0, 1, None, False),                       # nothing to select
+    (2, 2, 4, 16, 6000, 100, 1, 0, 3, None, False),                      # two of the three appended rows are candidates
+])
+def test_short_decode_select_equals_the_separate_calls(Bn, Hkv, G, M, N, K, w, n_sink, n_new, lens, shared):
+    """Append, tables and selection of a short context in one launch against the calls one after the other."""
+    wl = synth.Workload("one", Bn, Hkv * G, Hkv, 128, M, N, K, w, n_sink=n_sink, seed=N)
+    xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
+    keys = synth.make_encode_keys(wl, n_new, device="cuda", stress=True)
+    weights = synth.make_query_second_moment(wl)["h_diag"].cuda()
+    dims, sel = H.dims_of(wl), H.dims_of(wl.replace(n_q_heads=Hkv) if shared else wl)
+    sl = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
+    res = []
+    for fused in (True, False):
+        st = B.DecodeState(dims, K, w, n_sink, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
+        sk = B.DecodeState(sel, K, w, n_sink, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
+        codes = xd["codes"].clone()
+        for t in (st.q_rot, sk.lut, sk.lut_scale, sk.topk_idx, sk.topk_count, sk.topk_score):
+            t.fill_(-7)
+        tables = (xd["q"], st.cos_b, st.sin_b, xd["codebook"], st.q_rot, sk.lut, sk.lut_scale)
+        pick = (K, w, n_sink, sl, sk.topk_idx, sk.topk_count, sk.topk_score)
+        if fused:
+            call = B.decode_select_shared if shared else B.decode_select
+            call(dims, keys, n_new, N - n_new, xd["codebook"], weights, B.W_DIAG, codes, xd["q"], st.cos_b, st.sin_b,
+                 st.q_rot, sk.lut, sk.lut_scale, *pick, sk.ws)
+        else:
+            B.encode_keys(dims, keys, n_new, N - n_new, xd["codebook"], weights, B.W_DIAG, codes, st.ws)
+            (B.build_lut_shared if shared else B.build_lut)(dims, *tables)
+            B.score_topk(sel, codes, sk.lut, sk.lut_scale, *pick, None, sk.ws)
+        torch.cuda.synchronize()
+        res.append((codes, st.q_rot, sk.lut, sk.lut_scale, sk.topk_idx, sk.topk_count, sk.topk_score))
+    for a, b in zip(*res):
+        assert torch.equal(a.contiguous().view(torch.uint8), b.contiguous().view(torch.uint8))

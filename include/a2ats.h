@@ -120,9 +120,9 @@ int a2ats_rope_tables(int32_t head_dim, const double* inv_freq, int32_t b, int32
  *   keys     [dev, f32  B*Hkv*n_new*D]     pre-RoPE keys, dense (no stride)
  *   codebook [dev, f32  Hkv*M*256*ds]
  *   codes    [dev, u8   B*Hkv*ctx_stride*M] rows pos0 .. pos0+n_new-1 are written
- * Distances are evaluated in float32 and re-evaluated in float64 from the definition
- * whenever the two smallest are closer than 1e-4 relative, so codes equal the float64
- * argmin.  The weighted modes need a2ats_workspace_bytes(dims, A2ATS_OP_ENCODE, 0, 0) bytes
+ * Distances are formed on the matrix cores from f16 hi/lo splits of both operands (22 bits) and
+ * re-evaluated in float64 from the definition whenever the two smallest are closer than that
+ * arithmetic can tell apart, so codes equal the float64 argmin.  The weighted modes need a2ats_workspace_bytes(dims, A2ATS_OP_ENCODE, 0, 0) bytes
  * of workspace (transformed centroids); A2ATS_W_NONE needs none.  n_new == 0 is a no-op.
  * Single codebook: H is the full D x D matrix (A2ATS_W_BLOCK: weights [dev, f32 Hkv*D*D], the
  * lower triangle is read) and the argmin is over 4096 codewords of all 128 dimensions:

@@ -1,0 +1,95 @@
+"""The product-quantiser encoder against the float64 argmin of the definition, at the sizes and values where its
+matrix-core filter could go wrong."""
+import pytest
+import torch
+
+from paper_2502_12665_amd import binding as B
+from paper_2502_12665_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _distortions(keys, codebook, weights, mode):
+    """float64 (k - c) H (k - c)^T of every key, subspace and centroid: [B, Hkv, n, M, 256]."""
+    kv, m, _, ds = codebook.shape
+    k = keys.double().reshape(*keys.shape[:3], m, 1, ds)
+    e = k - codebook.double()[None, :, None]
+    if mode == B.W_DIAG:
+        return (e * e * weights.double().reshape(kv, m, ds)[None, :, None, :, None]).sum(-1)
+    if mode == B.W_BLOCK:
+        out = torch.empty(e.shape[:-1], dtype=torch.float64, device=keys.device)
+        for h in range(kv):
+            for s in range(m):
+                x = e[:, h, :, s].contiguous()
+                out[:, h, :, s] = ((x @ weights[h, s].double()) * x).sum(-1)
+        return out
+    return (e * e).sum(-1)
+
+
+def _encode(dims, keys, codebook, weights, mode, stride, m, offset=0):
+    flat = torch.full((keys.shape[0] * keys.shape[1] * stride * m + 8,), 0xEE, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(max(B.workspace_bytes(dims, B.OP_ENCODE), 16), dtype=torch.uint8, device="cuda")
+    codes = flat[offset:offset + flat.numel() - 8].view(keys.shape[0], keys.shape[1], stride, m)
+    B.encode_keys(dims, keys, keys.shape[2], 3, codebook, weights, mode, codes, ws)
+    torch.cuda.synchronize()
+    assert (flat[:offset] == 0xEE).all() and (flat[flat.numel() - 8 + offset:] == 0xEE).all()
+    assert (codes[:, :, :3] == 0xEE).all() and (codes[:, :, 3 + keys.shape[2]:] == 0xEE).all()
+    return codes[:, :, 3:3 + keys.shape[2]].long()
+
+
+@pytest.mark.parametrize("m,mode", [(16, "none"), (16, "diag"), (16, "block"), (32, "none"), (32, "diag"), (32, "block")])
+@pytest.mark.parametrize("n_new,batch,kv", [(33, 1, 1), (64, 2, 3), (65, 1, 2), (1024, 1, 1), (1087, 2, 1), (5000, 1, 2)])
+def test_codes_are_the_float64_argmin(m, mode, n_new, batch, kv):
+    wl = synth.Workload("enc", batch, kv, kv, 128, m, n_new + 8, 16, 16, seed=n_new + m)
+    hm = synth.make_query_second_moment(wl)
+    code = {"none": B.W_NONE, "diag": B.W_DIAG, "block": B.W_BLOCK}[mode]
+    weights = {"none": None, "diag": hm["h_diag"].cuda(), "block": hm["h_block"].cuda()}[mode]
+    codebook = synth.make_codebook(wl, "cuda")
+    ds = 128 // m
+    dims = B.make_dims(batch, kv, kv, 128, m, n_new + 8)
+    keys = synth.make_encode_keys(wl, n_new, device="cuda", stress=n_new % 2 == 0)
+    keys[:, :, 5] *= 40.0                                     # far outside the codebook
+    keys[:, :, 6] *= 1e4
+    keys[:, :, 7] = 0.0
+    keys[:, :, 8] *= 1e-6
+    midpoint = 0.5 * (codebook[:, :, 17] + codebook[:, :, 201]).reshape(kv, 128)
+    keys[:, :, 9] = midpoint                                  # two centroids about equally far
+    for scale in (1.0, 3e-9, 1e12):                           # (a power of two apart or not, small or large)
+        cb, ks = codebook * scale, keys * scale
+        got = _encode(dims, ks, cb, weights, code, n_new + 8, m)
+        dist = _distortions(ks, cb, weights, code)
+        best = dist.min(-1).values
+        mine = dist.gather(-1, got[..., None])[..., 0]
+        # the definition's own float64 rounding, relative to the terms that cancel in k - c
+        norm = ks.double().reshape(*ks.shape[:3], m, ds).pow(2).sum(-1) + cb.double().pow(2).sum(-1).amax(-1)[None, :, None]
+        wmax = 1.0 if weights is None else float(weights.abs().max()) * ds
+        assert ((mine - best) <= 1e-13 * wmax * norm).all(), float(((mine - best) / norm).max())
+
+
+@pytest.mark.parametrize("m", [16, 32])
+def test_ties_go_to_the_lower_code_and_values_that_are_not_finite_to_code_0(m):
+    ds, n = 128 // m, 200
+    wl = synth.Workload("enc_ties", 1, 1, 1, 128, m, n + 8, 16, 16, seed=m)
+    codebook = synth.make_codebook(wl, "cuda")
+    codebook[:, :, 128:] = codebook[:, :, :128]               # every centroid twice
+    keys = synth.make_encode_keys(wl, n, device="cuda")
+    keys[0, 0, 10] = float("nan")
+    keys[0, 0, 11] = float("inf")
+    dims = B.make_dims(1, 1, 1, 128, m, n + 8)
+    for offset in (0, 1):                                     # (codes may start at any byte)
+        got = _encode(dims, keys, codebook, None, B.W_NONE, n + 8, m, offset)
+        assert (got < 128).all()
+        assert (got[0, 0, 10:12] == 0).all()
+        dist = _distortions(keys, codebook, None, B.W_NONE)
+        ok = torch.ones(n, dtype=torch.bool, device="cuda")
+        ok[10:12] = False
+        first = (dist == dist.min(-1, keepdim=True).values).int().argmax(-1)
+        assert torch.equal(got[0, 0][ok], first[0, 0][ok])
+    broken = codebook.clone()
+    broken[0, 3, 5] = float("nan")                            # a centroid that is never the nearest
+    broken[0, 4] = 0.0                                        # a subspace that cannot tell its centroids apart
+    keys[0, 0, 10:12] = 0.0
+    got = _encode(dims, keys, broken, None, B.W_NONE, n + 8, m)
+    dist = _distortions(keys, broken, None, B.W_NONE).nan_to_num(nan=float("inf"))
+    first = (dist == dist.min(-1, keepdim=True).values).int().argmax(-1)
+    assert torch.equal(got, first)

@@ -311,7 +311,7 @@ int a2ats_decode_select(const a2ats_dims* d, const float* keys, int32_t n_new, i
   const long n_sample = (long)d->batch * d->n_kv_heads * plan.NG * plan.P0;
   const bool appended_rows_compete = n_new > 0 && (int64_t)pos0 < (int64_t)d->ctx_len - window;
   // (short contexts have a launch of their own for the whole call, under the same condition)
-  const bool in_one = !streams && a2ats::decode_select_group_fits(*d, window, n_sink);
+  const bool in_one = !streams && a2ats::takes_group_route(*d, window, n_sink);
   if (a2ats::single_codebook(*d) || appended_rows_compete || (!in_one && (!streams || n_sample > 256))) {   // the two calls, with their own checks
     rc = a2ats_decode_prologue(d, keys, n_new, pos0, codebook, weights, weight_mode, codes, q, q_dtype, cos_b,
                                sin_b, q_rot, lut, lut_scale, ws, ws_bytes, stream);
@@ -380,7 +380,7 @@ int a2ats_decode_select_shared(const a2ats_dims* d, const float* keys, int32_t n
   const long n_sample = (long)d->batch * d->n_kv_heads * plan.P0;
   const bool appended_rows_compete = n_new > 0 && (int64_t)pos0 < (int64_t)d->ctx_len - window;
   hipError_t e;
-  if (!streams && !appended_rows_compete && a2ats::decode_select_group_fits(dk, window, n_sink)) {
+  if (!streams && !appended_rows_compete && a2ats::takes_group_route(dk, window, n_sink)) {
     e = a2ats::launch_decode_select_group(*d, keys, n_new, pos0, codebook, weights, mode, codes, q, q_dtype, cos_b, sin_b,
                                           q_rot, lut, lut_scale, seq_lens, top_k, window, n_sink, topk_idx, topk_count,
                                           topk_score, true, (hipStream_t)stream);

@@ -387,10 +387,6 @@ static AppendPlan append_plan(long n_pairs, int n_lut) {
   return p;
 }
 
-bool decode_select_group_fits(const a2ats_dims& d, int window, int n_sink) {
-  return !single_codebook(d) && (long)d.ctx_len - window - n_sink <= kGroupMaxCand;
-}
-
 hipError_t launch_decode_select_group(const a2ats_dims& d, const float* keys, int n_new, int pos0,
                                       const float* codebook, const float* weights, int mode, uint8_t* codes,
                                       const void* q, int q_dtype, const float* cos_b, const float* sin_b, float* q_rot,

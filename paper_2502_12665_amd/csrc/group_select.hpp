@@ -1,5 +1,5 @@
 // The top-K of the (up to) four query heads of a group by one workgroup, for sequences whose candidates fit
-// its registers (at most 16384): the short-context route of a2ats_score_topk.
+// its registers (at most 16384): the group route of a2ats_score_topk.
 //
 // Every row is scored once for the four heads (one 8-byte LDS read per code byte, coarse_score.hpp) and the
 // coarse scores stay in registers.  A histogram over them gives, per head, the 32-wide bin of the K-th largest

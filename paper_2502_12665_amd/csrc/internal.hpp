@@ -76,9 +76,10 @@ hipError_t launch_decode_select_prologue(const a2ats_dims& d, const float* keys,
                                          float* q_rot, int32_t* lut, float* lut_scale, const int32_t* seq_lens,
                                          int32_t* thr, int P0, int sample_rows, int top_k, int window, int n_sink,
                                          bool shared, hipStream_t stream);
-// The whole of a2ats_decode_select (shared: a2ats_decode_select_shared) in one launch, for contexts whose
-// candidates fit one workgroup (decode_select_group_fits) and no appended row among the candidates.
-bool decode_select_group_fits(const a2ats_dims& d, int window, int n_sink);
+// Whether a selection (of these dims: shared, one head per KV head) that does not stream takes the group route.
+bool takes_group_route(const a2ats_dims& d, int window, int n_sink);
+// The whole of a2ats_decode_select (shared: a2ats_decode_select_shared) in one launch, where the selection takes
+// the group route and no appended row is among the candidates.
 hipError_t launch_decode_select_group(const a2ats_dims& d, const float* keys, int n_new, int pos0,
                                       const float* codebook, const float* weights, int mode, uint8_t* codes,
                                       const void* q, int q_dtype, const float* cos_b, const float* sin_b, float* q_rot,

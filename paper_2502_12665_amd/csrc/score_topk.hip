@@ -3,9 +3,10 @@
 //
 // Three routes, chosen on the host from the shape:
 //
-//  group route (at most 16384 candidates): one workgroup for the four heads of a group, group_select.hpp.
+//  group route (at most 16384 candidates, see takes_group_route): one workgroup for the four heads of a group,
+//  group_select.hpp.
 //
-//  exact route (the in-kernel fallback of the others, and more than 2048 winners without a workspace):
+//  exact route (the other short contexts, more than 2048 winners without a workspace, and the in-kernel fallback):
 //  one workgroup per query head runs an MSB-first radix select over the 32-bit score keys by
 //  re-streaming its sequence (<= 3 histogram passes), then one ordered pass that emits the
 //  winners in ascending position, equal scores going to the lower position.
@@ -130,6 +131,22 @@ TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink) 
     p.bytes = (p.off_cand + segs * (size_t)p.row_cap * entry_bytes + 255) / 256 * 256;
   }
   return p;
+}
+
+// The exact route spreads the heads of a group over as many CUs; the group route scores a row once for all of
+// them.  So it is taken where the heads need more rounds of the 256 CUs than the groups do, and otherwise for
+// short contexts, where what it saves is the launch of the tables.  Steps, exact -> group route, 32 query and 8
+// KV heads: 16 sequences (two rounds) M = 16, 4096 and 16384 tokens 48.7 -> 36.1 and 78.2 -> 61.9 us, M = 32 60.1
+// -> 49.4 and 104.2 -> 91.4; 4 sequences (one round) M = 16, 4096, 8228, 16384 tokens 31.6 -> 30.0, 35.6 -> 35.2,
+// 43.9 -> 46.1, M = 32, 1500, 4096, 16384 tokens 35.1 -> 32.5, 38.9 -> 38.4, 56.2 -> 74.6.  One head per group,
+// 16 sequences: M = 16, 16384 tokens 53.5 -> 48.3, M = 32, 8228 tokens 54.2 -> 48.6.
+bool takes_group_route(const a2ats_dims& d, int window, int n_sink) {
+  const long ncand = (long)d.ctx_len - window - n_sink;
+  if (single_codebook(d) || ncand > kGroupMaxCand) return false;
+  const int G = d.n_q_heads / d.n_kv_heads;
+  const long groups = (long)d.batch * d.n_kv_heads * ((G + kHeadsPerGroup - 1) / kHeadsPerGroup);
+  if (((long)d.batch * d.n_q_heads + 255) / 256 > (groups + 255) / 256) return true;
+  return ncand * std::min(G, kHeadsPerGroup) <= (d.n_sub == 16 ? 32768 : 8192);
 }
 
 // The P0 sampling workgroups of a problem each estimate a head's threshold from their share of the
@@ -756,7 +773,7 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
   }
 
   const bool streams = plan.fast || (plan.wide && ws);
-  if (!streams && (long)d.ctx_len - window - n_sink <= kGroupMaxCand) {
+  if (!streams && takes_group_route(d, window, n_sink)) {
     if ((err = allow_dynamic_lds(group_select_kernel<M>, kGroupLdsBytes, s_group)) != hipSuccess) return err;
     hipLaunchKernelGGL((group_select_kernel<M>), dim3(problems), dim3(kGroupThreads), kGroupLdsBytes, stream, codes, lut,
                        lut_scale, seq_lens, topk_idx, topk_count, topk_score, make_grid_map(1, problems, NG, Hkv), pg, B,

@@ -75,7 +75,10 @@ def _full_sort(wl, xd, st, seq_lens):
     (2, 2, 16, 3000, 3000, 16, 0, [3000, 700], None),                    # K above the candidates: all of them
     (1, 8, 16, 9000, 1, 64, 17, None, None),
     (1, 3, 16, 5000, 900, 64, 4, None, "patterns"),                      # ~125 equal scores: ties inside the band
-    (2, 4, 32, 12000, 300, 64, 4, None, "equal"),                        # the band overflows: the exact route
+    (2, 4, 32, 12000, 300, 64, 4, None, "equal"),
+    (33, 4, 16, 16384 + 63, 491, 63, 0, None, None),                     # more heads than CUs: long ones by groups too
+    (19, 7, 32, 16383, 4096, 0, 4, None, "patterns"),
+    (33, 4, 32, 12000, 300, 64, 4, None, "equal"),                       # the band overflows: the exact route
 ])
 def test_short_contexts_equal_a_full_sort(Bn, G, M, N, K, w, n_sink, lens, rows):
     """The short-context route (one workgroup for the heads of a group) against a full sort."""

@@ -127,12 +127,12 @@ int a2ats_rope_tables(int32_t head_dim, const double* inv_freq, int32_t b, int32
  * Single codebook: H is the full D x D matrix (A2ATS_W_BLOCK: weights [dev, f32 Hkv*D*D], the
  * lower triangle is read) and the argmin is over 4096 codewords of all 128 dimensions:
  * codes [dev, u16 B*Hkv*ctx_stride].  With the Cholesky factor of section 4.2 (H = L L^T,
- * z = k L, c^z = c L) the distortion is ||z - c^z||^2; the scores 1/2||c^z||^2 - z.c^z are
- * formed on the matrix cores from bf16 hi/lo splits of both operands (about 2^-18 relative),
- * and every key whose two best scores are closer than that arithmetic can tell apart is decided
- * again in float64, so codes equal the float64 argmin.  Every weight mode needs the workspace
- * (L, c^z in three forms and w = c (L L^T), 10.8 MB per KV head; a buffer of transformed keys for
- * up to 16384 rows per sequence and KV head; 8 bytes per key that ctx_stride allows); each call
+ * c^z = c L, w = c (L L^T)) the scores 1/2||c^z||^2 - k.w are formed on the matrix cores from f16
+ * roundings of both operands; keys whose two best scores are closer than the rounding can account
+ * for are scored again from bf16 hi/lo splits (about 2^-17 relative), and those still too close in
+ * float64, so codes equal the float64 argmin.  Every weight mode needs the workspace (L, c^z and w
+ * in their forms, 11.9 MB per KV head, 2.1 MB for short lists of such keys; 12 bytes per key that
+ * ctx_stride allows); each call
  * derives them again unless weight_mode carries A2ATS_W_PREPARED (see a2ats_encode_prepare).  Up
  * to 8 keys per sequence and KV head (the decode-time append) are decided by one float64 sweep
  * each, over the expanded form 1/2||c^z||^2 - k.w of the same distortion.

@@ -4,22 +4,26 @@
 //
 // With the Cholesky factor of section 4.2 (H = L L^T, z = k L, c^z = c L) the distortion is the
 // plain squared distance ||z - c^z||^2, and minimising it over c is minimising
-//     s_c = 1/2 ||c^z||^2 - z . c^z ,
+//     s_c = 1/2 ||c^z||^2 - k . w_c ,   w_c = c (L L^T) ,
 // a dense [keys x 128] . [128 x 4096] contraction: 1 Mflop per key, the one matrix-core shape of
 // this library.  The kernels:
 //
 //   encode_single_factor_kernel    per KV head: L in float64 (Cholesky in LDS, or the identity /
 //                                  a diagonal for the unweighted / per-dimension modes)
-//   encode_single_codewords_kernel c^z = c L in float64; kept transposed in float64 for the exact
-//                                  re-check, and split into two bf16 terms (hi + lo, 16 significant
-//                                  bits) laid out in matrix-core operand order, with 1/2 ||c^z||^2
-//   encode_single_transform_kernel z = k L in float64, rounded once to float32 (full-matrix mode only;
-//                                  a few k keys at a time, into a buffer the main pass reads as keys)
-//   encode_single_kernel           256 keys per workgroup: z is split the same way and kept in
-//                                  registers as the B operands; the codewords stream through LDS
-//                                  32 at a time as the A operand; three bf16 products per term
+//   encode_single_heff_kernel      L L^T (full-matrix mode)
+//   encode_single_codewords_kernel c^z and w_c in float64, kept transposed for the exact decisions,
+//                                  1/2 ||c^z||^2, and the largest norms
+//   encode_single_operands_kernel  w_c in matrix-core operand order: rounded to f16, and as two bf16
+//                                  terms (hi + lo, 16 significant bits)
+//   encode_single_filter_kernel    every key: scores from one f16 product (11 significant bits per
+//                                  operand) with the two smallest and the code of the first kept per
+//                                  key.  Where they are further apart than the rounding of the
+//                                  operands can account for -- its norm is known for every key and
+//                                  bounded for the codewords -- the code is decided; the other keys
+//                                  are listed.
+//   encode_single_kernel           the listed keys, 256 at a time: three bf16 products per term
 //                                  (hi.hi + hi.lo + lo.hi, float32 accumulate) give the scores to
-//                                  about 2^-18 relative.  Every lane owns one key column of the
+//                                  about 2^-17 relative.  Every lane owns one key column of the
 //                                  32 x 32 result tile, so the running smallest three scores (and
 //                                  the codes of the first two) are per-lane registers; nothing
 //                                  crosses lanes until the end.
@@ -27,11 +31,10 @@
 //                                  of the bf16 products are decided in float64 between those two
 //                                  codewords; keys with three that close by a float64 sweep over all
 //                                  4096.  So the emitted code is the float64 argmin.
-//   encode_single_heff_kernel      L L^T (full-matrix mode), for w = c (L L^T) kept beside c^z
-//   encode_single_sweep_kernel     the few-key (decode-time append) route: the distortion expanded as
-//                                  |z|^2 - 2 k . w_c + |c^z|^2, so one float64 pass of dot products
-//                                  over w decides the key; 16 workgroups per key, then
+//   encode_single_sweep_kernel     the few-key (decode-time append) route: one float64 pass of dot
+//                                  products k . w_c decides the key; 16 workgroups per key, then
 //                                  encode_single_sweep_pick_kernel
+//   encode_single_transform_kernel z = k L in float64, rounded once to float32 (seeding only)
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -49,16 +52,32 @@ constexpr int kBlocks = kCW / 32;       // streamed 32-codeword blocks
 static_assert(kFragBytes / 16 / kEncThreads == 4, "a thread stages four 16-byte pieces of a block");
 constexpr int kFewSingle = kFewSingleKeys;   // at most this many keys per (sequence, KV head): float64 sweep only
 constexpr int kSlices = kEncodeSlices;  // workgroups sharing the codewords of one such key
-constexpr float kReach = 1.5e-5f;       // rounding reach of a score, relative to |z| max|c^z|
-constexpr int kChunk = 16384;           // keys per (sequence, KV head) transformed at a time
+constexpr float kReach = 2.5e-5f;       // rounding reach of two scores of the bf16 products, relative to |k| max|w|
+constexpr int kF16Bytes = 8 * 64 * 16;  // 8 k-steps x 64 lanes x 16 bytes: 32 codewords of 128 dims in f16
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
+// Of a KV head, over its codewords (float bits, which order like the values).
+struct CodewordStat {
+  uint32_t w_max, c_max, bias_max;   // largest |w|, |c| and 1/2 |c^z|^2, rounded up
+  uint32_t w_err;                    // largest |w - f16(w)|, in the scaled units of the f16 operands
+};
+
+// Smallest three scores of a listed key over a slice of the codewords, and the codes of the first two.
+struct NearPart {
+  float s1, s2, s3;
+  uint32_t codes;
+};
+constexpr int kMaxSlices = 16;
+// Workgroups per KV head that work on its list.
+inline long near_groups(const a2ats_dims& d) { return d.n_kv_heads < 512 ? 512 / d.n_kv_heads : 1; }
+
 struct EncWs {
-  size_t off_L, off_sd, off_heff, off_czT, off_wT, off_chalf, off_cfrag, off_cbias, off_cstat, off_z, off_count, off_list,
-      off_part, bytes;
-  int chunk;   // keys per (sequence, KV head) the transform buffer holds
+  size_t off_L, off_sd, off_heff, off_czT, off_wT, off_chalf, off_cfrag, off_cbias, off_f16, off_fbias, off_cstat, off_count,
+      off_list, off_near, off_near_part, off_part, bytes;
+  size_t near_cap;   // keys of a KV head
 };
 
 EncWs enc_single_ws(const a2ats_dims& d) {
@@ -79,43 +98,42 @@ EncWs enc_single_ws(const a2ats_dims& d) {
   w.off_chalf = take(Hkv * kCW * sizeof(double));
   w.off_cfrag = take(Hkv * kBlocks * (size_t)kFragBytes);
   w.off_cbias = take(Hkv * kCW * sizeof(float));
-  w.off_cstat = take(Hkv * 4 * sizeof(float));
-  w.chunk = (int)(d.ctx_stride < kChunk ? d.ctx_stride : kChunk);
-  w.off_z = take((size_t)d.batch * Hkv * w.chunk * kD * sizeof(float));
-  w.off_count = take(sizeof(uint32_t));
+  w.off_f16 = take(Hkv * kBlocks * (size_t)kF16Bytes);
+  w.off_fbias = take(Hkv * kCW * sizeof(float));
+  w.off_cstat = take(Hkv * sizeof(CodewordStat));
+  // keys for float64, listed keys per KV head, arrivals per KV head and chunk of its list
+  w.off_count = take((1 + Hkv + Hkv * (size_t)near_groups(d)) * sizeof(uint32_t));
   w.off_list = take(keys_max * 2 * sizeof(uint32_t));
+  w.near_cap = (size_t)d.batch * (size_t)d.ctx_stride;
+  w.off_near = take(keys_max * sizeof(uint32_t));
+  w.off_near_part = take(Hkv * (size_t)near_groups(d) * kKeysPerWG * sizeof(NearPart));
   w.off_part = take((size_t)d.batch * Hkv * kFewSingle * kSlices * 2 * sizeof(double));
   w.bytes = o;
   return w;
 }
 
-// Position of dimension t inside a 16-dimension k-step of an operand fragment: lane half g holds
-// dims {4g .. 4g+3} and {8+4g .. 8+4g+3}.  This is the order in which the transform's result tile
-// leaves the matrix core (row 8(v/4) + 4g + v%4 in register v), so z needs no shuffling to become
-// an operand; the codewords are stored in the same order.
-__device__ __forceinline__ void frag_slot(int t, int& kt, int& g, int& i) {
-  kt = t >> 4;
-  const int u = t & 15;
-  g = (u >> 2) & 1;
-  i = ((u >> 3) << 2) | (u & 3);
+// Scales of the f16 operands: powers of two that bring the largest |c| into [4, 8) -- keys up to 8000 times as
+// long then fit f16 -- and the largest |w| into [64, 128).  False: out of reach of such a scale.
+__device__ __forceinline__ bool f16_scales(const CodewordStat& st, float& key_scale, float& w_scale) {
+  const int ec = (int)(st.c_max >> 23) - 127, ew = (int)(st.w_max >> 23) - 127;   // (inf and NaN: 128)
+  const bool ok = ec > -60 && ec < 60 && ew > -60 && ew < 60;
+  key_scale = ok ? __uint_as_float((uint32_t)(127 + 2 - ec) << 23) : 1.f;
+  w_scale = ok ? __uint_as_float((uint32_t)(127 + 6 - ew) << 23) : 1.f;
+  return ok;
 }
 
 // ------------------------------------------------------------------------------------------
-// Per KV head: the factor L (H = L L^T) and its Frobenius norm.
+// Per KV head: the factor L (H = L L^T).
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void encode_single_factor_kernel(
     const float* __restrict__ weights, int mode, double* __restrict__ Lmat, double* __restrict__ sd,
-    float* __restrict__ cstat) {
+    CodewordStat* __restrict__ cstat) {
   extern __shared__ double s_A[];   // 128 x 128, lower triangle in use
-  __shared__ double s_red[256];
   const int kv = blockIdx.x, tid = threadIdx.x;
   double* L = Lmat + (size_t)kv * kD * kD;
+  if (tid == 0) cstat[kv] = CodewordStat{0u, 0u, 0u, 0u};
   if (mode != A2ATS_W_BLOCK) {
     if (tid < kD) sd[(size_t)kv * kD + tid] = mode == A2ATS_W_DIAG ? sqrt((double)weights[(size_t)kv * kD + tid]) : 1.0;
-    if (tid == 0) {
-      cstat[kv * 4 + 0] = 0.f;
-      cstat[kv * 4 + 1] = 0.f;
-    }
     return;
   }
   const float* H = weights + (size_t)kv * kD * kD;
@@ -137,22 +155,7 @@ __global__ __launch_bounds__(256) void encode_single_factor_kernel(
     }
     __syncthreads();
   }
-  double f2 = 0.0;
-  for (int e = tid; e < kD * kD; e += 256) {
-    const double v = s_A[e];
-    L[e] = v;
-    f2 += v * v;
-  }
-  s_red[tid] = f2;
-  __syncthreads();
-  for (int s = 128; s >= 1; s >>= 1) {
-    if (tid < s) s_red[tid] += s_red[tid + s];
-    __syncthreads();
-  }
-  if (tid == 0) {
-    cstat[kv * 4 + 0] = 0.f;
-    cstat[kv * 4 + 1] = __double2float_ru(sqrt(s_red[0]));
-  }
+  for (int e = tid; e < kD * kD; e += 256) L[e] = s_A[e];
 }
 
 // ------------------------------------------------------------------------------------------
@@ -176,15 +179,14 @@ __global__ __launch_bounds__(kD) void encode_single_heff_kernel(const double* __
 }
 
 // ------------------------------------------------------------------------------------------
-// c^z = c L for 64 codewords per workgroup (float64), in the three forms the other kernels read,
-// and w = c (L L^T) with 1/2 |c^z|^2 in float64 for the few-key route.
+// c^z = c L and w = c (L L^T) for 64 codewords per workgroup (float64), and the largest norms.
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void encode_single_codewords_kernel(
     const float* __restrict__ codebook, int mode, const double* __restrict__ Lmat, const double* __restrict__ sd,
     const double* __restrict__ heff, double* __restrict__ czT, double* __restrict__ wT, double* __restrict__ chalf,
-    uint16_t* __restrict__ cfrag, float* __restrict__ cbias, float* __restrict__ cstat) {
+    float* __restrict__ cbias, CodewordStat* __restrict__ cstat) {
   __shared__ float s_c[64][kD + 1];
-  __shared__ double s_n[4][64];
+  __shared__ double s_n[3][4][64];   // |c^z|^2, |w|^2, |c|^2 of a quarter of the dimensions
   const int kv = blockIdx.y, c0 = blockIdx.x * 64, tid = threadIdx.x;
   const int c = tid & 63, tq = __builtin_amdgcn_readfirstlane(tid >> 6);
   const float* cw = codebook + ((size_t)kv * kCW + c0) * kD;
@@ -204,33 +206,17 @@ __global__ __launch_bounds__(256) void encode_single_codewords_kernel(
 #pragma unroll
     for (int u = 0; u < 32; ++u) acc[u] = (double)s_c[c][32 * tq + u] * sd[(size_t)kv * kD + 32 * tq + u];
   }
-  double n2 = 0.0;
-#pragma unroll
-  for (int u = 0; u < 32; ++u) n2 += acc[u] * acc[u];
-  s_n[tq][c] = n2;
-  const int cg = c0 + c, cb = cg >> 5, row = cg & 31;
-  uint16_t* blk = cfrag + ((size_t)kv * kBlocks + cb) * (kFragBytes / 2);
+  double z2 = 0.0, w2 = 0.0, c2 = 0.0;
 #pragma unroll
   for (int u = 0; u < 32; ++u) {
-    const int t = 32 * tq + u;
-    czT[((size_t)kv * kD + t) * kCW + cg] = acc[u];
-    int kt, g, i;
-    frag_slot(t, kt, g, i);
-    const double neg = -acc[u];   // the operand is -c^z: the matrix core then leaves 1/2 |c^z|^2 - z . c^z
-    const uint16_t hi = f32_to_bf16((float)neg);
-    const uint16_t lo = f32_to_bf16((float)(neg - (double)bf16_to_f32(hi)));
-    blk[((0 * 8 + kt) * 64 + row + 32 * g) * 8 + i] = hi;
-    blk[((1 * 8 + kt) * 64 + row + 32 * g) * 8 + i] = lo;
+    const double cu = (double)s_c[c][32 * tq + u];
+    z2 += acc[u] * acc[u];
+    c2 += cu * cu;
   }
-  __syncthreads();
-  if (tq == 0) {
-    const double n = s_n[0][c] + s_n[1][c] + s_n[2][c] + s_n[3][c];
-    cbias[(size_t)kv * kCW + cg] = (float)(0.5 * n);
-    chalf[(size_t)kv * kCW + cg] = 0.5 * n;
-    // max over the codewords of |c^z|, rounded up (a non-negative float orders like its bits)
-    atomicMax((uint32_t*)&cstat[kv * 4 + 0], __float_as_uint(__double2float_ru(sqrt(n))));
-  }
-  // w = c (L L^T): the distortion is |z|^2 - 2 k . w + |c^z|^2, so the few-key route needs no z
+  const int cg = c0 + c;
+#pragma unroll
+  for (int u = 0; u < 32; ++u) czT[((size_t)kv * kD + 32 * tq + u) * kCW + cg] = acc[u];
+  // the distortion is |z|^2 - 2 k . w + |c^z|^2, so scores need no z
   if (mode == A2ATS_W_BLOCK) {
 #pragma unroll
     for (int u = 0; u < 32; ++u) acc[u] = 0.0;
@@ -248,25 +234,90 @@ __global__ __launch_bounds__(256) void encode_single_codewords_kernel(
     }
   }
 #pragma unroll
-  for (int u = 0; u < 32; ++u) wT[((size_t)kv * kD + 32 * tq + u) * kCW + cg] = acc[u];
+  for (int u = 0; u < 32; ++u) {
+    wT[((size_t)kv * kD + 32 * tq + u) * kCW + cg] = acc[u];
+    w2 += acc[u] * acc[u];
+  }
+  s_n[0][tq][c] = z2;
+  s_n[1][tq][c] = w2;
+  s_n[2][tq][c] = c2;
+  __syncthreads();
+  if (tq < 3) {
+    const double n = s_n[tq][0][c] + s_n[tq][1][c] + s_n[tq][2][c] + s_n[tq][3][c];
+    if (tq == 0) {
+      cbias[(size_t)kv * kCW + cg] = (float)(0.5 * n);
+      chalf[(size_t)kv * kCW + cg] = 0.5 * n;
+    }
+    // rounded up; a float that is not negative orders like its bits
+    uint32_t most = __float_as_uint(__double2float_ru(tq == 0 ? 0.5 * n : sqrt(n)));
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) most = max(most, (uint32_t)__shfl_xor((int)most, off));
+    if (c == 0) atomicMax(tq == 0 ? &cstat[kv].bias_max : (tq == 1 ? &cstat[kv].w_max : &cstat[kv].c_max), most);
+  }
 }
 
 // ------------------------------------------------------------------------------------------
-// z = k L for rows j0 .. j0 + n_part - 1 of every sequence, float64 accumulation, one rounding.
+// The matrix-core operands of 32 codewords, all -w (the matrix core then leaves 1/2 |c^z|^2 - k . w).
+// Lane (row, g) of k-step kt holds dimensions 16 kt + 8 g .. + 8 of its codeword.
+// ------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(512) void encode_single_operands_kernel(const double* __restrict__ wT,
+                                                                     const float* __restrict__ cbias,
+                                                                     uint16_t* __restrict__ cfrag,
+                                                                     _Float16* __restrict__ f16,
+                                                                     float* __restrict__ fbias,
+                                                                     CodewordStat* __restrict__ cstat) {
+  __shared__ float s_e[16][32];
+  const int kv = blockIdx.y, cb = blockIdx.x, tid = threadIdx.x;
+  const int row = tid & 31, kt = tid >> 6, g = (tid >> 5) & 1;
+  float key_scale, w_scale;
+  const bool ok = f16_scales(cstat[kv], key_scale, w_scale);
+  bf16x8 hi, lo;
+  f16x8 h;
+  float err = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const double neg = -wT[((size_t)kv * kD + 16 * kt + 8 * g + i) * kCW + 32 * cb + row];
+    const uint16_t b = f32_to_bf16((float)neg);
+    hi[i] = __builtin_bit_cast(__bf16, b);
+    lo[i] = __builtin_bit_cast(__bf16, f32_to_bf16((float)(neg - (double)bf16_to_f32(b))));
+    const double x = neg * (double)w_scale;
+    h[i] = (_Float16)(float)x;
+    const float r = (float)(x - (double)(float)h[i]);
+    err += r * r;
+  }
+  uint16_t* blk = cfrag + ((size_t)kv * kBlocks + cb) * (kFragBytes / 2) + (kt * 64 + row + 32 * g) * 8;
+  *(bf16x8*)blk = hi;
+  *(bf16x8*)(blk + 8 * 64 * 8) = lo;
+  *(f16x8*)(f16 + ((size_t)kv * kBlocks + cb) * (kF16Bytes / 2) + (kt * 64 + row + 32 * g) * 8) = h;
+  s_e[2 * kt + g][row] = err;
+  __syncthreads();
+  if (tid < 32) {
+    float e2 = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) e2 += s_e[i][tid];
+    fbias[(size_t)kv * kCW + 32 * cb + tid] = cbias[(size_t)kv * kCW + 32 * cb + tid] * (key_scale * w_scale);
+    uint32_t most = __float_as_uint(ok ? 1.00001f * sqrtf(e2) : NAN);   // NaN: no key is decided by the filter
+#pragma unroll
+    for (int off = 16; off >= 1; off >>= 1) most = max(most, (uint32_t)__shfl_xor((int)most, off));
+    if (tid == 0) atomicMax(&cstat[kv].w_err, most);
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// z = k L for all rows (seeding), float64 accumulation, one rounding.
 // A thread owns one key and 32 consecutive output dimensions; the rows of L it needs are the same
 // for the whole wave.
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void encode_single_transform_kernel(
-    const float* __restrict__ keys, const double* __restrict__ Lmat, float* __restrict__ z, int Hkv, int n_new,
-    int j0, int n_part, int chunk) {
+    const float* __restrict__ keys, const double* __restrict__ Lmat, float* __restrict__ z, int Hkv, int n_new) {
   __shared__ float s_k[64][kD + 1];
   const int bkv = blockIdx.y, kv = bkv % Hkv, tid = threadIdx.x;
   const int key = tid & 63, og = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int first = blockIdx.x * 64;
-  const float* src = keys + ((size_t)bkv * n_new + j0) * kD;
+  const float* src = keys + (size_t)bkv * n_new * kD;
   for (int e = tid; e < 64 * (kD / 4); e += 256) {
     const int row = e / (kD / 4), c4 = e % (kD / 4);
-    const float4 f = *(const float4*)(src + (size_t)min(first + row, n_part - 1) * kD + 4 * c4);
+    const float4 f = *(const float4*)(src + (size_t)min(first + row, n_new - 1) * kD + 4 * c4);
     s_k[row][4 * c4] = f.x, s_k[row][4 * c4 + 1] = f.y, s_k[row][4 * c4 + 2] = f.z, s_k[row][4 * c4 + 3] = f.w;
   }
   __syncthreads();
@@ -279,8 +330,8 @@ __global__ __launch_bounds__(256) void encode_single_transform_kernel(
 #pragma unroll
     for (int u = 0; u < 32; ++u) acc[u] += kr * L[(size_t)r * kD + u];
   }
-  if (first + key < n_part) {
-    float* dst = z + ((size_t)bkv * chunk + first + key) * kD + 32 * og;
+  if (first + key < n_new) {
+    float* dst = z + ((size_t)bkv * n_new + first + key) * kD + 32 * og;
 #pragma unroll
     for (int u = 0; u < 32; u += 4)
       *(float4*)(dst + u) = make_float4((float)acc[u], (float)acc[u + 1], (float)acc[u + 2], (float)acc[u + 3]);
@@ -288,7 +339,173 @@ __global__ __launch_bounds__(256) void encode_single_transform_kernel(
 }
 
 // ------------------------------------------------------------------------------------------
-// Main pass
+// The filter
+// ------------------------------------------------------------------------------------------
+// 32 NT keys per wave (B operands in registers, rounded to f16), 4 waves; the codewords stream through LDS 32 at
+// a time as the A operand.  The accumulators start at 1/2 |c^z|^2 and the stored operands are -w, so the matrix
+// core leaves the scores.  Ranking has no branch: the codeword's number within the lane goes into the low 11
+// mantissa bits, and the two smallest are kept (2.25 vector instructions per score).
+//
+// With e_k = |k - f16(k)|, e_w = max |w - f16(w)| and float32 sums, a score is off by at most
+//   e_k max|w| + |k| e_w + 4e-6 (|k| max|w| + max 1/2 |c^z|^2)
+// and by 2^-12 of itself for the number; the two smallest are told apart where they differ by more than that
+// counted twice.  Of keys drawn like the codewords (normal, nothing in common with them) 2 % are not.
+//
+// What bounds it: the matrix cores (one product of f16; three of bf16 for every key before, and a float64 pass z = k L
+// over the keys ahead of them): 96001 keys x 8 heads, full matrix: the whole call 694 us (2420 before), 1.26 PFLOP/s;
+// 16 keys of one head 64 us (193), whatever the matrix.
+__device__ __forceinline__ void filter_insert(float a, float b, float c, float d, float& k1, float& k2) {
+  // two at a time: the median of (smallest so far, two new) is the only candidate they add for second place
+  float m0, m1;
+  asm("v_med3_f32 %0, %1, %2, %3" : "=v"(m0) : "v"(k1), "v"(a), "v"(b));
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(k1) : "v"(k1), "v"(a), "v"(b));
+  asm("v_med3_f32 %0, %1, %2, %3" : "=v"(m1) : "v"(k1), "v"(c), "v"(d));
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(k1) : "v"(k1), "v"(c), "v"(d));
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(k2) : "v"(k2), "v"(m0), "v"(m1));
+}
+
+template <int NT>
+__global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void encode_single_filter_kernel(
+    const float* __restrict__ keys, const uint8_t* __restrict__ f16, const float* __restrict__ fbias,
+    const CodewordStat* __restrict__ cstat, uint16_t* __restrict__ codes, uint32_t* __restrict__ near_count,
+    uint32_t* __restrict__ near, int64_t near_cap, int Hkv, int n_new, int pos0, int64_t ctx_stride) {
+  constexpr int kBuf = kF16Bytes + 128, kPieces = kF16Bytes / 16 / kEncThreads;
+  __shared__ __align__(16) uint8_t s_mem[2 * kBuf];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, g = lane >> 5;
+  const int bkv = blockIdx.y, kv = bkv % Hkv, seq = bkv / Hkv;
+  const long key_first = ((long)blockIdx.x * kEncWaves + wave) * (32 * NT);
+  const float* seq_keys = keys + (size_t)bkv * n_new * kD;
+  const CodewordStat st = cstat[kv];
+  float key_scale, w_scale;
+  f16_scales(st, key_scale, w_scale);
+
+  f16x8 kh[NT][8];
+  float n2[NT], e2[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const float* kp = seq_keys + (size_t)min(key_first + 32 * t + col, (long)n_new - 1) * kD + 8 * g;
+    n2[t] = e2[t] = 0.f;
+#pragma unroll
+    for (int k4 = 0; k4 < 8; k4 += 4) {   // four k-steps of loads in flight at a time
+      float4 a[4], b[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        a[u] = *(const float4*)(kp + 16 * (k4 + u));
+        b[u] = *(const float4*)(kp + 16 * (k4 + u) + 4);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        typedef __attribute__((ext_vector_type(8))) float f32x8;
+        const f32x8 x = {a[u].x, a[u].y, a[u].z, a[u].w, b[u].x, b[u].y, b[u].z, b[u].w};
+        const f32x8 v = x * key_scale;
+        kh[t][k4 + u] = __builtin_convertvector(v, f16x8);
+        const f32x8 r = v - __builtin_convertvector(kh[t][k4 + u], f32x8);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          n2[t] += v[i] * v[i];
+          e2[t] += r[i] * r[i];
+        }
+        asm volatile("" : "+v"(kh[t][k4 + u]), "+v"(n2[t]), "+v"(e2[t]));   // (in this order: else all of v and r stay live)
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+
+  const uint8_t* gblk = f16 + (size_t)kv * kBlocks * kF16Bytes + tid * 16;
+  const float* gbias = fbias + (size_t)kv * kCW + (tid & 31);
+  static_assert(kPieces == 2, "a thread stages two 16-byte pieces of a block");
+  uint4 p0, p1;
+  float pb;
+  auto request = [&](int cb) {
+    cb = min(cb, kBlocks - 1);   // the step of the last block loads it once more, unused
+    p0 = *(const uint4*)(gblk + (size_t)cb * kF16Bytes);
+    p1 = *(const uint4*)(gblk + (size_t)cb * kF16Bytes + kEncThreads * 16);
+    pb = gbias[cb * 32];
+  };
+  auto stage = [&](int cb) {
+    uint8_t* dst = s_mem + (cb & 1) * kBuf;
+    *(uint4*)(dst + tid * 16) = p0;
+    *(uint4*)(dst + (kEncThreads + tid) * 16) = p1;
+    *(float*)(dst + kF16Bytes + (tid & 31) * 4) = pb;   // several threads write each word, all the same
+  };
+  float k1[NT], k2[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) k1[t] = k2[t] = INFINITY;
+  const uint32_t keep = ~2047u;
+  request(0);
+  stage(0);
+  __syncthreads();
+#pragma unroll 1
+  for (int cb = 0; cb < kBlocks; ++cb) {
+    // The next block is requested first, and the operand of k-step kt + 1 before the products of k-step kt (the
+    // fences keep that order), so neither latency is waited for in the open.
+    request(cb + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    const uint8_t* blk = s_mem + (cb & 1) * kBuf;
+    const uint8_t* fr = blk + lane * 16;
+    // register v of a tile: codeword 32 cb + 8 (v/4) + 4 g + v%4
+    f32x16 bias, acc[NT];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 f = *(const float4*)(blk + kF16Bytes + (8 * q + 4 * g) * 4);
+      bias[4 * q] = f.x, bias[4 * q + 1] = f.y, bias[4 * q + 2] = f.z, bias[4 * q + 3] = f.w;
+    }
+    f16x8 a = *(const f16x8*)fr;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int kt = 0; kt < 8; ++kt) {
+      f16x8 next = a;
+      if (kt < 7) next = *(const f16x8*)(fr + (kt + 1) * 1024);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, kh[t][kt], kt == 0 ? bias : acc[t], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      a = next;
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int v = 0; v < 16; v += 4) {
+        float key[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const uint32_t number = (uint32_t)(cb * 16 + v + u);   // (scalar, shared by the tiles)
+          key[u] = __uint_as_float((__float_as_uint(acc[t][v + u]) & keep) | number);
+        }
+        filter_insert(key[0], key[1], key[2], key[3], k1[t], k2[t]);
+      }
+    stage(cb + 1);
+    __syncthreads();
+  }
+
+  // The two lane halves of a key column hold disjoint codewords.
+  const float w_max = __uint_as_float(st.w_max) * w_scale, w_err = __uint_as_float(st.w_err);
+  const float bias_max = __uint_as_float(st.bias_max) * (key_scale * w_scale);
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const float o1 = __shfl_xor(k1[t], 32), o2 = __shfl_xor(k2[t], 32);
+    const float kn = sqrtf(n2[t] + __shfl_xor(n2[t], 32)), ke = sqrtf(e2[t] + __shfl_xor(e2[t], 32));
+    const bool own = k1[t] <= o1;
+    const float m1 = own ? k1[t] : o1, m2 = fminf(fmaxf(k1[t], o1), fminf(k2[t], o2));
+    const uint32_t number = __float_as_uint(m1) & 2047u;
+    const uint32_t code = (number >> 4) * 32 + ((number >> 2) & 3) * 8 + (own ? g : 1 - g) * 4 + (number & 3);
+    const long j = key_first + 32 * t + col;
+    if (g == 0 && j < n_new) {
+      const float reach = 2.f * (1.00001f * (ke * w_max + kn * w_err) + 4e-6f * (kn * w_max + bias_max)) +
+                          2.5e-4f * (fabsf(m1) + fabsf(m2));
+      codes[(size_t)bkv * ctx_stride + pos0 + j] = (uint16_t)code;
+      if (!(m2 - m1 > reach)) {   // (also where anything is not a number)
+        const uint32_t at = atomicAdd(near_count + kv, 1u);
+        near[(size_t)kv * near_cap + at] = (uint32_t)((size_t)seq * n_new + j);
+      }
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// The keys the filter left open
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ void split8(const float (&z)[8], bf16x8& hi, bf16x8& lo, float& n2) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -315,194 +532,223 @@ __device__ __forceinline__ void top3_insert(float s, int c, float& s1, float& s2
   s1 = fminf(s1, s);
 }
 
-template <int MODE>
 __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void encode_single_kernel(
-    const float* __restrict__ keys, const double* __restrict__ sd, const uint8_t* __restrict__ cfrag,
-    const float* __restrict__ cbias, const float* __restrict__ cstat, uint16_t* __restrict__ codes,
-    uint32_t* __restrict__ counter, uint32_t* __restrict__ list, int Hkv, int n_new, int pos0,
-    int64_t ctx_stride, int j0, int n_part, int64_t seq_stride) {
-  // `keys` holds rows j0 .. j0 + n_part - 1 of every sequence, seq_stride floats apart (the
-  // caller's keys themselves, or the transformed copy of one part of them).
+    const float* __restrict__ keys, const uint8_t* __restrict__ cfrag,
+    const float* __restrict__ cbias, const CodewordStat* __restrict__ cstat, uint16_t* __restrict__ codes,
+    const uint32_t* __restrict__ near_count, const uint32_t* __restrict__ near, int64_t near_cap,
+    uint32_t* __restrict__ counter, uint32_t* __restrict__ list, uint32_t* __restrict__ arrived, NearPart* parts, int Hkv,
+    int n_new, int pos0, int64_t ctx_stride) {
   __shared__ __align__(16) uint8_t s_mem[2 * (kFragBytes + 128)];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, g = lane >> 5;
-  const int bkv = blockIdx.y, kv = bkv % Hkv;
-  const long key_first = (long)blockIdx.x * kKeysPerWG + wave * kKeysPerWave;
-  const float* seq_keys = keys + (size_t)bkv * seq_stride;
-
-  bf16x8 zh[2][8], zl[2][8];
-  float zn2[2] = {0.f, 0.f};
-  {
-    // (four k-steps of loads in flight at a time: with all sixteen the registers they land in
-    // and the 128 the operands need do not fit, and the spills cost far more than the latency)
-#pragma unroll
-    for (int tile = 0; tile < 2; ++tile) {
-      const long jr = min(key_first + 32 * tile + col, (long)n_part - 1);
-      const float* kp = seq_keys + (size_t)jr * kD;
-#pragma unroll
-      for (int k4 = 0; k4 < 8; k4 += 4) {
-        float4 a[4], b[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {   // operand element i <-> dimension 16 kt + 8 (i/4) + 4 g + i%4
-          a[u] = *(const float4*)(kp + 16 * (k4 + u) + 4 * g);
-          b[u] = *(const float4*)(kp + 16 * (k4 + u) + 4 * g + 8);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int kt = k4 + u, t0 = 16 * kt + 4 * g;
-          float x[8] = {a[u].x, a[u].y, a[u].z, a[u].w, b[u].x, b[u].y, b[u].z, b[u].w};
-          if (MODE == A2ATS_W_DIAG) {
-            const double* s = sd + (size_t)kv * kD;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              x[i] *= (float)s[t0 + i];
-              x[4 + i] *= (float)s[t0 + 8 + i];
-            }
-          }
-          split8(x, zh[tile][kt], zl[tile][kt], zn2[tile]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  }
-
-  // Main loop: blocks of 32 codewords (operands + their 1/2 |c^z|^2) through a double buffer in
-  // LDS.  The accumulators start at 1/2 |c^z|^2 and the stored operands are -c^z, so the matrix
-  // core leaves the score itself.  Ranking: a score only matters if it is below the lane's third
-  // smallest so far, which after the first blocks is rare, so four scores at a time are tested by
-  // their minimum and the insertion is skipped by the whole wave when no lane needs it.  (The
-  // vector ALU issues one instruction per four cycles per SIMD and a product takes 32: ten
-  // instructions per score would cost more than the products.)  Two workgroups share a CU, one wave
-  // of each per SIMD, so one computes while the other waits at its barrier.
-  const uint8_t* gblk = cfrag + (size_t)kv * kBlocks * kFragBytes;
-  const float* gbias = cbias + (size_t)kv * kCW;
-  constexpr int kBuf = kFragBytes + 128;
-  float s1[2], s2[2], s3[2];
-  int c1[2] = {0, 0}, c2[2] = {0, 0};
-#pragma unroll
-  for (int tile = 0; tile < 2; ++tile) s1[tile] = s2[tile] = s3[tile] = INFINITY;
-
-  // The loads of the next block are written as asm statements: as ordinary loads the compiler
-  // sinks them past the ranking branches down to their only use, the LDS store before the barrier,
-  // and every step then waits for global memory in the open.  The matching wait is explicit
-  // (loads the compiler does not know of only make its own, counted waits stricter).
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  auto prefetch = [&](int bi, u32x4 (&p)[kFragBytes / 16 / kEncThreads], float& pb) {
-    bi = min(bi, kBlocks - 1);   // the step of the last block loads it once more, unused
-    const uint8_t* src = gblk + (size_t)bi * kFragBytes + tid * 16;
-#pragma unroll
-    for (int i = 0; i < kFragBytes / 16 / kEncThreads; ++i)
-      asm volatile("global_load_dwordx4 %0, %1, off" : "=&v"(p[i]) : "v"(src + i * kEncThreads * 16) : "memory");
-    const float* bsrc = gbias + bi * 32 + (tid & 31);
-    asm volatile("global_load_dword %0, %1, off" : "=&v"(pb) : "v"(bsrc) : "memory");
-  };
-  auto stage = [&](int bi, u32x4 (&p)[kFragBytes / 16 / kEncThreads], float& pb) {
-    asm volatile("s_waitcnt vmcnt(0)" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]), "+v"(pb)::"memory");
-    uint8_t* dst = s_mem + (bi & 1) * kBuf;
-#pragma unroll
-    for (int i = 0; i < kFragBytes / 16 / kEncThreads; ++i) *(u32x4*)(dst + tid * 16 + i * kEncThreads * 16) = p[i];
-    *(float*)(dst + kFragBytes + (tid & 31) * 4) = pb;   // several threads write each word, all the same
-  };
-  {
-    u32x4 p[kFragBytes / 16 / kEncThreads];
-    float pb;
-    prefetch(0, p, pb);
-    stage(0, p, pb);
-  }
-  __syncthreads();
+  const int kv = blockIdx.y;
+  const long n_near = (long)near_count[kv];
+  __shared__ uint32_t s_last;
+  // A short list is spread over the workgroups by slices of the codewords too (a multiple of two blocks each): one
+  // workgroup takes 165 us for all of them (2000 normal keys x 8 heads: 285 -> 143 us).
+  const long n_chunks = (n_near + kKeysPerWG - 1) / kKeysPerWG;
+  int slices = 1;
+  while (slices < kMaxSlices && n_chunks * slices * 2 <= (long)gridDim.x) slices *= 2;
 #pragma unroll 1
-  for (int cb = 0; cb < kBlocks; ++cb) {
-    // The order of the memory operations is pinned (nothing crosses a fence): the next block is
-    // requested from global memory first, and the operands of k-step kt + 1 are requested from
-    // LDS before the six products of k-step kt, so neither latency is waited for in the open.
-    u32x4 p[kFragBytes / 16 / kEncThreads];
-    float pb;
-    prefetch(cb + 1, p, pb);
-    __builtin_amdgcn_sched_barrier(0);
-    const uint8_t* blk = s_mem + (cb & 1) * kBuf;
-    const uint8_t* fr = blk + lane * 16;
-    bf16x8 a_hi = *(const bf16x8*)fr, a_lo = *(const bf16x8*)(fr + 8 * 1024);
-    // register v of a tile: codeword 32 cb + 8 (v/4) + 4 g + v%4 (the 4 g is added at the end)
-    f32x16 acc0, acc1;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float4 f = *(const float4*)(blk + kFragBytes + (8 * q + 4 * g) * 4);
-      acc0[4 * q] = acc1[4 * q] = f.x;
-      acc0[4 * q + 1] = acc1[4 * q + 1] = f.y;
-      acc0[4 * q + 2] = acc1[4 * q + 2] = f.z;
-      acc0[4 * q + 3] = acc1[4 * q + 3] = f.w;
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int kt = 0; kt < 8; ++kt) {
-      bf16x8 n_hi = a_hi, n_lo = a_lo;
-      if (kt < 7) {
-        n_hi = *(const bf16x8*)(fr + (kt + 1) * 1024);
-        n_lo = *(const bf16x8*)(fr + (8 + kt + 1) * 1024);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_hi, zh[0][kt], acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_hi, zh[1][kt], acc1, 0, 0, 0);
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_hi, zl[0][kt], acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_hi, zl[1][kt], acc1, 0, 0, 0);
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_lo, zh[0][kt], acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_lo, zh[1][kt], acc1, 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      a_hi = n_hi;
-      a_lo = n_lo;
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float m0 = fminf(fminf(acc0[4 * q], acc0[4 * q + 1]), fminf(acc0[4 * q + 2], acc0[4 * q + 3]));
-      if (m0 < s3[0]) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) top3_insert(acc0[4 * q + r], cb * 32 + 8 * q + r, s1[0], s2[0], s3[0], c1[0], c2[0]);
-      }
-      const float m1 = fminf(fminf(acc1[4 * q], acc1[4 * q + 1]), fminf(acc1[4 * q + 2], acc1[4 * q + 3]));
-      if (m1 < s3[1]) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) top3_insert(acc1[4 * q + r], cb * 32 + 8 * q + r, s1[1], s2[1], s3[1], c1[1], c2[1]);
-      }
-    }
-    stage(cb + 1, p, pb);
-    __syncthreads();
-  }
+  for (long item = blockIdx.x; item < n_chunks * slices; item += gridDim.x) {
+    const long chunk = item / slices, base = chunk * kKeysPerWG;
+    const int cb0 = (int)(item % slices) * (kBlocks / slices), cb1 = cb0 + kBlocks / slices;
+    const long key_first = base + wave * kKeysPerWave;
+    auto row_of = [&](int tile) {   // of the listed key: its row in `keys`
+      const uint32_t e = near[(size_t)kv * near_cap + min(key_first + 32 * tile + col, n_near - 1)];
+      return ((size_t)(e / (uint32_t)n_new) * Hkv + kv) * n_new + e % (uint32_t)n_new;
+    };
 
-  // The two lane halves of a key column hold disjoint codewords: merge them, decide, flag.
-  const float cmax = cstat[kv * 4 + 0];
+    bf16x8 zh[2][8], zl[2][8];
+    float zn2[2] = {0.f, 0.f};
+    {
+      // (four k-steps of loads in flight at a time: with all sixteen the registers they land in
+      // and the 128 the operands need do not fit, and the spills cost far more than the latency)
 #pragma unroll
-  for (int tile = 0; tile < 2; ++tile) {
-    const int a1 = c1[tile] + 4 * g, a2 = c2[tile] + 4 * g;
-    const float o1 = __shfl_xor(s1[tile], 32), o2 = __shfl_xor(s2[tile], 32), o3 = __shfl_xor(s3[tile], 32);
-    const int b1 = __shfl_xor(a1, 32), b2 = __shfl_xor(a2, 32);
-    const float zn = zn2[tile] + __shfl_xor(zn2[tile], 32);
-    // smallest three of the six, with the codes of the first two (equal scores: lower code first)
-    float m1 = s1[tile], m2 = s2[tile], m3 = s3[tile];
-    int d1 = a1, d2 = a2;
-    const float os[3] = {o1, o2, o3};
-    const int oc[3] = {b1, b2, 0x7fffffff};   // the third one's code is not tracked and never wins a tie
+      for (int tile = 0; tile < 2; ++tile) {
+        const float* kp = keys + row_of(tile) * kD + 8 * g;
 #pragma unroll
-    for (int e = 0; e < 3; ++e) {
-      const float s = os[e];
-      const int c = oc[e];
+        for (int k4 = 0; k4 < 8; k4 += 4) {
+          float4 a[4], b[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            a[u] = *(const float4*)(kp + 16 * (k4 + u));
+            b[u] = *(const float4*)(kp + 16 * (k4 + u) + 4);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const float x[8] = {a[u].x, a[u].y, a[u].z, a[u].w, b[u].x, b[u].y, b[u].z, b[u].w};
+            split8(x, zh[tile][k4 + u], zl[tile][k4 + u], zn2[tile]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+
+    // Main loop: blocks of 32 codewords (operands + their 1/2 |c^z|^2) through a double buffer in
+    // LDS.  The accumulators start at 1/2 |c^z|^2 and the stored operands are -w, so the matrix
+    // core leaves the score itself.  Ranking: a score only matters if it is below the lane's third
+    // smallest so far, which after the first blocks is rare, so four scores at a time are tested by
+    // their minimum and the insertion is skipped by the whole wave when no lane needs it.  (The
+    // vector ALU issues one instruction per four cycles per SIMD and a product takes 32: ten
+    // instructions per score would cost more than the products.)  Two workgroups share a CU, one wave
+    // of each per SIMD, so one computes while the other waits at its barrier.
+    const uint8_t* gblk = cfrag + (size_t)kv * kBlocks * kFragBytes;
+    const float* gbias = cbias + (size_t)kv * kCW;
+    constexpr int kBuf = kFragBytes + 128;
+    float s1[2], s2[2], s3[2];
+    int c1[2] = {0, 0}, c2[2] = {0, 0};
+#pragma unroll
+    for (int tile = 0; tile < 2; ++tile) s1[tile] = s2[tile] = s3[tile] = INFINITY;
+
+    // The loads of the next block are written as asm statements: as ordinary loads the compiler
+    // sinks them past the ranking branches down to their only use, the LDS store before the barrier,
+    // and every step then waits for global memory in the open.  The matching wait is explicit
+    // (loads the compiler does not know of only make its own, counted waits stricter).
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    auto prefetch = [&](int bi, u32x4 (&p)[kFragBytes / 16 / kEncThreads], float& pb) {
+      bi = min(bi, kBlocks - 1);   // the step of the last block loads it once more, unused
+      const uint8_t* src = gblk + (size_t)bi * kFragBytes + tid * 16;
+#pragma unroll
+      for (int i = 0; i < kFragBytes / 16 / kEncThreads; ++i)
+        asm volatile("global_load_dwordx4 %0, %1, off" : "=&v"(p[i]) : "v"(src + i * kEncThreads * 16) : "memory");
+      const float* bsrc = gbias + bi * 32 + (tid & 31);
+      asm volatile("global_load_dword %0, %1, off" : "=&v"(pb) : "v"(bsrc) : "memory");
+    };
+    auto stage = [&](int bi, u32x4 (&p)[kFragBytes / 16 / kEncThreads], float& pb) {
+      asm volatile("s_waitcnt vmcnt(0)" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]), "+v"(pb)::"memory");
+      uint8_t* dst = s_mem + (bi & 1) * kBuf;
+#pragma unroll
+      for (int i = 0; i < kFragBytes / 16 / kEncThreads; ++i) *(u32x4*)(dst + tid * 16 + i * kEncThreads * 16) = p[i];
+      *(float*)(dst + kFragBytes + (tid & 31) * 4) = pb;   // several threads write each word, all the same
+    };
+    {
+      u32x4 p[kFragBytes / 16 / kEncThreads];
+      float pb;
+      prefetch(cb0, p, pb);
+      stage(cb0, p, pb);
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int cb = cb0; cb < cb1; ++cb) {
+      // The order of the memory operations is pinned (nothing crosses a fence): the next block is
+      // requested from global memory first, and the operands of k-step kt + 1 are requested from
+      // LDS before the six products of k-step kt, so neither latency is waited for in the open.
+      u32x4 p[kFragBytes / 16 / kEncThreads];
+      float pb;
+      prefetch(cb + 1, p, pb);
+      __builtin_amdgcn_sched_barrier(0);
+      const uint8_t* blk = s_mem + (cb & 1) * kBuf;
+      const uint8_t* fr = blk + lane * 16;
+      bf16x8 a_hi = *(const bf16x8*)fr, a_lo = *(const bf16x8*)(fr + 8 * 1024);
+      // register v of a tile: codeword 32 cb + 8 (v/4) + 4 g + v%4 (the 4 g is added at the end)
+      f32x16 acc0, acc1;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float4 f = *(const float4*)(blk + kFragBytes + (8 * q + 4 * g) * 4);
+        acc0[4 * q] = acc1[4 * q] = f.x;
+        acc0[4 * q + 1] = acc1[4 * q + 1] = f.y;
+        acc0[4 * q + 2] = acc1[4 * q + 2] = f.z;
+        acc0[4 * q + 3] = acc1[4 * q + 3] = f.w;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int kt = 0; kt < 8; ++kt) {
+        bf16x8 n_hi = a_hi, n_lo = a_lo;
+        if (kt < 7) {
+          n_hi = *(const bf16x8*)(fr + (kt + 1) * 1024);
+          n_lo = *(const bf16x8*)(fr + (8 + kt + 1) * 1024);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_hi, zh[0][kt], acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_hi, zh[1][kt], acc1, 0, 0, 0);
+        acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_hi, zl[0][kt], acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_hi, zl[1][kt], acc1, 0, 0, 0);
+        acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_lo, zh[0][kt], acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_lo, zh[1][kt], acc1, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        a_hi = n_hi;
+        a_lo = n_lo;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float m0 = fminf(fminf(acc0[4 * q], acc0[4 * q + 1]), fminf(acc0[4 * q + 2], acc0[4 * q + 3]));
+        if (m0 < s3[0]) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) top3_insert(acc0[4 * q + r], cb * 32 + 8 * q + r, s1[0], s2[0], s3[0], c1[0], c2[0]);
+        }
+        const float m1 = fminf(fminf(acc1[4 * q], acc1[4 * q + 1]), fminf(acc1[4 * q + 2], acc1[4 * q + 3]));
+        if (m1 < s3[1]) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) top3_insert(acc1[4 * q + r], cb * 32 + 8 * q + r, s1[1], s2[1], s3[1], c1[1], c2[1]);
+        }
+      }
+      stage(cb + 1, p, pb);
+      __syncthreads();
+    }
+
+    // The two lane halves of a key column hold disjoint codewords: merge them, then the slices, decide, flag.
+    const float wmax = __uint_as_float(cstat[kv].w_max);
+    // score s of code c (not tracked: 0x7fffffff, never wins a tie) into the smallest three (equal scores: lower code first)
+    auto insert = [](float s, int c, float& m1, float& m2, float& m3, int& d1, int& d2) {
       const bool lt1 = s < m1 || (s == m1 && c < d1), lt2 = s < m2 || (s == m2 && c < d2);
       m3 = lt2 ? m2 : fminf(m3, s);
       d2 = lt1 ? d1 : (lt2 ? c : d2);
       m2 = lt1 ? m1 : (lt2 ? s : m2);
       d1 = lt1 ? c : d1;
       m1 = lt1 ? s : m1;
+    };
+    int d1[2], d2[2];
+#pragma unroll
+    for (int tile = 0; tile < 2; ++tile) {
+      d1[tile] = c1[tile] + 4 * g;
+      d2[tile] = c2[tile] + 4 * g;
+      const float o1 = __shfl_xor(s1[tile], 32), o2 = __shfl_xor(s2[tile], 32), o3 = __shfl_xor(s3[tile], 32);
+      const int b1 = __shfl_xor(d1[tile], 32), b2 = __shfl_xor(d2[tile], 32);
+      zn2[tile] += __shfl_xor(zn2[tile], 32);
+      insert(o1, b1, s1[tile], s2[tile], s3[tile], d1[tile], d2[tile]);
+      insert(o2, b2, s1[tile], s2[tile], s3[tile], d1[tile], d2[tile]);
+      insert(o3, 0x7fffffff, s1[tile], s2[tile], s3[tile], d1[tile], d2[tile]);
     }
-    const long j = key_first + 32 * tile + col;
-    if (g == 0 && j < n_part) {
-      const float reach = kReach * sqrtf(zn) * cmax;
-      codes[(size_t)bkv * ctx_stride + pos0 + j0 + j] = (uint16_t)d1;
-      if (!(m2 - m1 > reach)) {
-        const uint32_t at = atomicAdd(counter, 1u);
-        const uint32_t full = !(m3 - m1 > reach) ? 0x80000000u : 0u;
-        list[2 * (size_t)at] = (uint32_t)((size_t)bkv * n_new + j0 + j) | full;
-        list[2 * (size_t)at + 1] = (uint32_t)d1 | ((uint32_t)d2 << 16);
+    if (slices > 1) {   // (uniform) the workgroup that is last to finish a chunk decides it
+      NearPart* mine = parts + ((size_t)kv * gridDim.x + item) * kKeysPerWG + wave * kKeysPerWave + col;
+      if (g == 0) {
+#pragma unroll
+        for (int tile = 0; tile < 2; ++tile)
+          mine[32 * tile] = NearPart{s1[tile], s2[tile], s3[tile], (uint32_t)d1[tile] | ((uint32_t)d2[tile] << 16)};
+      }
+      __threadfence();
+      __syncthreads();
+      if (tid == 0) s_last = atomicAdd(arrived + (size_t)kv * gridDim.x + chunk, 1u) == (uint32_t)slices - 1 ? 1u : 0u;
+      __syncthreads();
+      if (!s_last) continue;
+      __threadfence();
+      const NearPart* all = mine - (size_t)(item % slices) * kKeysPerWG;
+#pragma unroll
+      for (int tile = 0; tile < 2; ++tile) {
+        s1[tile] = s2[tile] = s3[tile] = INFINITY;
+        d1[tile] = d2[tile] = 0;
+        for (int i = 0; i < slices; ++i) {
+          const NearPart o = all[(size_t)i * kKeysPerWG + 32 * tile];
+          insert(o.s1, (int)(o.codes & 0xffffu), s1[tile], s2[tile], s3[tile], d1[tile], d2[tile]);
+          insert(o.s2, (int)(o.codes >> 16), s1[tile], s2[tile], s3[tile], d1[tile], d2[tile]);
+          insert(o.s3, 0x7fffffff, s1[tile], s2[tile], s3[tile], d1[tile], d2[tile]);
+        }
       }
     }
+#pragma unroll
+    for (int tile = 0; tile < 2; ++tile)
+      if (g == 0 && key_first + 32 * tile + col < n_near) {
+        const size_t row = row_of(tile);
+        const float reach = kReach * sqrtf(zn2[tile]) * wmax;
+        codes[row / n_new * ctx_stride + pos0 + row % n_new] = (uint16_t)d1[tile];
+        if (!(s2[tile] - s1[tile] > reach)) {
+          const uint32_t at = atomicAdd(counter, 1u);
+          const uint32_t full = !(s3[tile] - s1[tile] > reach) ? 0x80000000u : 0u;
+          list[2 * (size_t)at] = (uint32_t)row | full;
+          list[2 * (size_t)at + 1] = (uint32_t)d1[tile] | ((uint32_t)d2[tile] << 16);
+        }
+      }
   }
 }
 
@@ -603,7 +849,9 @@ __global__ __launch_bounds__(256) void encode_single_recheck_kernel(
   }
 }
 
-__global__ void encode_single_clear_kernel(uint32_t* counter) { *counter = 0; }
+__global__ void encode_single_clear_kernel(uint32_t* counter, int n) {
+  for (int i = threadIdx.x; i < n; i += blockDim.x) counter[i] = 0;
+}
 
 // The few-key (append) route: every key is decided by a float64 sweep, its 4096 codewords split
 // over kSlices workgroups (one workgroup would read 4 MB by itself).  With w_c = c (L L^T) the
@@ -855,7 +1103,7 @@ hipError_t launch_encode_single_prepare(const a2ats_dims& d, const float* codebo
   uint8_t* base = (uint8_t*)ws;
   double* Lmat = (double*)(base + w.off_L);
   double* sd = (double*)(base + w.off_sd);
-  float* cstat = (float*)(base + w.off_cstat);
+  CodewordStat* cstat = (CodewordStat*)(base + w.off_cstat);
   const size_t factor_lds = (size_t)kD * kD * sizeof(double);
   hipError_t err = allow_dynamic_lds(encode_single_factor_kernel, factor_lds, g_factor_lds);
   if (err != hipSuccess) return err;
@@ -869,8 +1117,11 @@ hipError_t launch_encode_single_prepare(const a2ats_dims& d, const float* codebo
   }
   hipLaunchKernelGGL(encode_single_codewords_kernel, dim3(kCW / 64, d.n_kv_heads), dim3(256), 0, stream, codebook,
                      mode, Lmat, sd, heff, (double*)(base + w.off_czT), (double*)(base + w.off_wT),
-                     (double*)(base + w.off_chalf), (uint16_t*)(base + w.off_cfrag), (float*)(base + w.off_cbias),
-                     cstat);
+                     (double*)(base + w.off_chalf), (float*)(base + w.off_cbias), cstat);
+  if ((err = hipGetLastError()) != hipSuccess) return err;
+  hipLaunchKernelGGL(encode_single_operands_kernel, dim3(kBlocks, d.n_kv_heads), dim3(512), 0, stream,
+                     (const double*)(base + w.off_wT), (const float*)(base + w.off_cbias), (uint16_t*)(base + w.off_cfrag),
+                     (_Float16*)(base + w.off_f16), (float*)(base + w.off_fbias), cstat);
   return hipGetLastError();
 }
 
@@ -902,9 +1153,9 @@ hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_ne
   double* czT = (double*)(base + w.off_czT);
   uint8_t* cfrag = base + w.off_cfrag;
   float* cbias = (float*)(base + w.off_cbias);
-  float* cstat = (float*)(base + w.off_cstat);
-  float* zbuf = (float*)(base + w.off_z);
+  CodewordStat* cstat = (CodewordStat*)(base + w.off_cstat);
   uint32_t* counter = (uint32_t*)(base + w.off_count);
+  uint32_t* near = (uint32_t*)(base + w.off_near);
   uint32_t* list = (uint32_t*)(base + w.off_list);
   double* part = (double*)(base + w.off_part);
   const int Hkv = d.n_kv_heads, bkv = d.batch * Hkv;
@@ -921,28 +1172,26 @@ hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_ne
                        (uint16_t*)codes, n_all, n_new, pos0, d.ctx_stride);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(encode_single_clear_kernel, dim3(1), dim3(1), 0, stream, counter);
+  hipLaunchKernelGGL(encode_single_clear_kernel, dim3(1), dim3(1024), 0, stream, counter,
+                     (int)(1 + Hkv + Hkv * near_groups(d)));
   if ((err = hipGetLastError()) != hipSuccess) return err;
-  if (mode == A2ATS_W_BLOCK) {   // part by part: transform into the buffer, then the plain pass over it
-    for (int j0 = 0; j0 < n_new; j0 += w.chunk) {
-      const int n_part = n_new - j0 < w.chunk ? n_new - j0 : w.chunk;
-      hipLaunchKernelGGL(encode_single_transform_kernel, dim3((n_part + 63) / 64, bkv), dim3(256), 0, stream, keys,
-                         Lmat, zbuf, Hkv, n_new, j0, n_part, w.chunk);
-      if ((err = hipGetLastError()) != hipSuccess) return err;
-      hipLaunchKernelGGL((encode_single_kernel<A2ATS_W_NONE>), dim3((n_part + kKeysPerWG - 1) / kKeysPerWG, bkv),
-                         dim3(kEncThreads), 0, stream, zbuf, sd, cfrag, cbias, cstat, (uint16_t*)codes, counter, list,
-                         Hkv, n_new, pos0, d.ctx_stride, j0, n_part, (int64_t)w.chunk * kD);
-      if ((err = hipGetLastError()) != hipSuccess) return err;
-    }
-  } else {
-    const dim3 grid((n_new + kKeysPerWG - 1) / kKeysPerWG, bkv), block(kEncThreads);
-    if (mode == A2ATS_W_NONE)
-      hipLaunchKernelGGL((encode_single_kernel<A2ATS_W_NONE>), grid, block, 0, stream, keys, sd, cfrag, cbias, cstat,
-                         (uint16_t*)codes, counter, list, Hkv, n_new, pos0, d.ctx_stride, 0, n_new, (int64_t)n_new * kD);
-    else
-      hipLaunchKernelGGL((encode_single_kernel<A2ATS_W_DIAG>), grid, block, 0, stream, keys, sd, cfrag, cbias, cstat,
-                         (uint16_t*)codes, counter, list, Hkv, n_new, pos0, d.ctx_stride, 0, n_new, (int64_t)n_new * kD);
-  }
+  // Keys per wave: a workgroup reads all codewords whatever its keys, so 128 where that gives about the 512
+  // workgroups that are resident at once, else 64 or 32.
+  const long waves = (long)bkv * (((long)n_new + 31) / 32);   // (of 32 keys)
+  const int nt = waves >= 4L * kEncWaves * 400 ? 4 : (waves >= 2L * kEncWaves * 400 ? 2 : 1);
+  const dim3 grid((n_new + 32 * nt * kEncWaves - 1) / (32 * nt * kEncWaves), bkv), block(kEncThreads);
+#define A2ATS_LAUNCH_FILTER(NT)                                                                                      \
+  hipLaunchKernelGGL(encode_single_filter_kernel<NT>, grid, block, 0, stream, keys, (const uint8_t*)(base + w.off_f16), \
+                     (const float*)(base + w.off_fbias), cstat, (uint16_t*)codes, counter + 1, near,                 \
+                     (int64_t)w.near_cap, Hkv, n_new, pos0, d.ctx_stride)
+  if (nt == 4) A2ATS_LAUNCH_FILTER(4);
+  else if (nt == 2) A2ATS_LAUNCH_FILTER(2);
+  else A2ATS_LAUNCH_FILTER(1);
+#undef A2ATS_LAUNCH_FILTER
+  if ((err = hipGetLastError()) != hipSuccess) return err;
+  hipLaunchKernelGGL(encode_single_kernel, dim3((unsigned)near_groups(d), Hkv), block, 0, stream, keys, cfrag, cbias,
+                     cstat, (uint16_t*)codes, counter + 1, near, (int64_t)w.near_cap, counter, list, counter + 1 + Hkv,
+                     (NearPart*)(base + w.off_near_part), Hkv, n_new, pos0, d.ctx_stride);
   if ((err = hipGetLastError()) != hipSuccess) return err;
   const uint32_t re_grid = n_all < 2048u ? n_all : 2048u;
   hipLaunchKernelGGL(encode_single_recheck_kernel, dim3(re_grid), dim3(256), 0, stream, keys, mode, Lmat, sd, czT,
@@ -980,7 +1229,7 @@ hipError_t launch_kmeanspp_seed(const a2ats_dims& d, const float* keys, int n_ne
   uint8_t* base = (uint8_t*)ws;
   double* Lmat = (double*)(base + w.off_L);
   double* sd = (double*)(base + w.off_sd);
-  float* cstat = (float*)(base + w.off_cstat);
+  CodewordStat* cstat = (CodewordStat*)(base + w.off_cstat);
   float* z = (float*)(base + sw.off_z);
   double* dmin = (double*)(base + sw.off_d);
   double* partial = (double*)(base + sw.off_partial);
@@ -994,7 +1243,7 @@ hipError_t launch_kmeanspp_seed(const a2ats_dims& d, const float* keys, int n_ne
   if ((err = hipGetLastError()) != hipSuccess) return err;
   if (mode == A2ATS_W_BLOCK)
     hipLaunchKernelGGL(encode_single_transform_kernel, dim3((n_new + 63) / 64, bkv), dim3(256), 0, stream, keys, Lmat,
-                       z, Hkv, n_new, 0, n_new, n_new);
+                       z, Hkv, n_new);
   else
     hipLaunchKernelGGL(scale_keys_kernel, dim3((unsigned)(((size_t)n_new * kD + 255) / 256), bkv), dim3(256), 0,
                        stream, keys, sd, z, Hkv, (size_t)n_new);

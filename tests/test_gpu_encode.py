@@ -93,3 +93,68 @@ def test_ties_go_to_the_lower_code_and_values_that_are_not_finite_to_code_0(m):
     dist = _distortions(keys, broken, None, B.W_NONE).nan_to_num(nan=float("inf"))
     first = (dist == dist.min(-1, keepdim=True).values).int().argmax(-1)
     assert torch.equal(got, first)
+
+
+def _single(dims, keys, codebook, weights, mode, stride, prepared=False):
+    codes = torch.full((keys.shape[0], keys.shape[1], stride), -2, dtype=torch.int16, device="cuda")
+    ws = torch.empty(B.workspace_bytes(dims, B.OP_ENCODE), dtype=torch.uint8, device="cuda").fill_(0xA5)
+    if prepared:
+        B.encode_prepare(dims, codebook, weights, mode, ws)
+        mode |= B.W_PREPARED
+    B.encode_keys(dims, keys, keys.shape[2], 3, codebook, weights, mode, codes, ws)
+    torch.cuda.synchronize()
+    assert (codes[:, :, :3] == -2).all() and (codes[:, :, 3 + keys.shape[2]:] == -2).all()
+    return codes[:, :, 3:3 + keys.shape[2]].long()
+
+
+@pytest.mark.parametrize("mode", ["none", "diag", "block"])
+@pytest.mark.parametrize("n_new,batch,kv", [(9, 1, 1), (129, 2, 3), (1025, 1, 8), (8200, 2, 4), (66000, 2, 2)])
+def test_single_codebook_codes_are_the_float64_argmin(mode, n_new, batch, kv):
+    """The sizes take the filter's 32, 64 and 128 keys per wave; keys drawn like the codewords leave some open."""
+    wl = synth.Workload("enc1", batch, kv, kv, 128, 1, n_new + 8, 16, 16, seed=n_new, n_centroids=4096)
+    hm = synth.make_query_second_moment(wl)
+    code = {"none": B.W_NONE, "diag": B.W_DIAG, "block": B.W_BLOCK}[mode]
+    weights = {"none": None, "diag": hm["h_diag"].cuda(), "block": hm["h_block"].cuda()}[mode]
+    codebook = synth.make_codebook(wl, "cuda")
+    dims = B.make_dims(batch, kv, kv, 128, 1, n_new + 8, n_centroids=4096)
+    keys = synth.make_encode_keys(wl, n_new, device="cuda", stress=n_new % 2 == 1)
+    keys[:, :, 2] *= 1e5                                      # beyond f16
+    keys[:, :, 3] = 0.0
+    keys[:, :, 4] *= 1e-6
+    keys[:, :, 5] = 0.5 * (codebook[:, 0, 17] + codebook[:, 0, 2001])
+    h64 = {"none": torch.eye(128, dtype=torch.float64, device="cuda").expand(kv, 128, 128)}.get(mode)
+    if h64 is None:
+        h64 = torch.diag_embed(weights.double()) if mode == "diag" else weights.double().reshape(kv, 128, 128)
+    for scale in (1.0, 3e-7):
+        cb, ks = codebook * scale, keys * scale
+        got = _single(dims, ks, cb, weights, code, n_new + 8, prepared=scale == 1.0)
+        for h in range(kv):
+            c = cb[h, 0].double()
+            w = c @ h64[h]
+            half = 0.5 * (w * c).sum(-1)
+            for b in range(batch):
+                k = ks[b, h].double()
+                score = half - k @ w.t()
+                lost = score.gather(1, got[b, h][:, None])[:, 0] - score.min(1).values
+                norm = half.max() + k.norm(dim=1) * w.norm(dim=1).max()
+                assert (lost <= 1e-13 * norm).all(), float((lost / norm).max())
+
+
+def test_single_codebook_ties_and_values_that_are_not_finite():
+    n = 700
+    wl = synth.Workload("enc1_ties", 1, 2, 2, 128, 1, n + 8, 16, 16, seed=5, n_centroids=4096)
+    codebook = synth.make_codebook(wl, "cuda")
+    codebook[:, :, 2048:] = codebook[:, :, :2048]             # every codeword twice: float64 decides every key
+    keys = synth.make_encode_keys(wl, n, device="cuda")
+    keys[0, 1, 10], keys[0, 1, 11] = float("nan"), float("inf")
+    dims = B.make_dims(1, 2, 2, 128, 1, n + 8, n_centroids=4096)
+    got = _single(dims, keys, codebook, None, B.W_NONE, n + 8)
+    want = synth.make_encode_keys(wl, n, device="cuda")
+    for h in range(2):
+        score = 0.5 * codebook[h, 0].double().pow(2).sum(-1) - want[0, h].double() @ codebook[h, 0].double().t()
+        first = score[:, :2048].argmin(1)
+        ok = torch.ones(n, dtype=torch.bool, device="cuda")
+        if h == 1:
+            ok[10:12] = False
+            assert (got[0, 1, 10:12] == 0).all()
+        assert torch.equal(got[0, h][ok], first[ok])

@@ -6,13 +6,18 @@
 // (k - c) H (k - c)^T) followed by a2ats_codebook_update.  Both geometries: codewords are
 // [Hkv][M][L][ds], and a key contributes its subvector m to codeword codes[j][m] of subspace m.
 //
-//   second_moment_kernel     a workgroup accumulates the 128 x 128 outer-product sum of its share of
-//                            the samples in float64 (an 8 x 8 block per thread), one partial each
+//   second_moment_kernel     a workgroup accumulates the outer-product sum of its share of the samples
+//                            on the float64 matrix cores, the upper triangle of 16 x 16 tiles
 //   second_moment_sum_kernel adds the partials in a fixed order, divides, rounds once to float32
 //   update_clear_kernel      zeroes the float64 sums and the counts
-//   update_add_kernel        one thread per (key, dimension): hardware float64 atomic adds into the
-//                            sums (the order of the additions, and so the last bits, vary from run
-//                            to run), one count per (key, subspace)
+//   update_few_kernel        few keys: one thread per (key, dimension), float64 atomic adds into the sums
+//                            (the order of the additions, and so the last bits, vary from run to run)
+//   update_add_kernel        product quantiser: the sums of a subspace stay in LDS while a workgroup
+//                            walks over its share of the keys, then go to memory by float64 atomic adds
+//   update_count_kernel, update_scan_kernel, update_place_kernel
+//                            single codebook: the keys of a KV head in the order of their codes
+//   update_sorted_kernel     a wave adds up 64 consecutive keys of that order, one float64 atomic add
+//                            per run of equal codes
 //   update_mean_kernel       sum / count, rounded once; codewords without keys keep their value
 #include "common.hpp"
 #include "internal.hpp"
@@ -21,53 +26,145 @@ namespace a2ats {
 namespace {
 
 constexpr int kFD = 128;
-constexpr int kMomentParts = 64;   // partial sums per KV head
-constexpr int kMomentRows = 32;    // sample rows staged per step
+constexpr int kMomentTiles = 36;   // 16 x 16 tiles on and above the diagonal of 128 x 128
+constexpr int kMomentRows = 16;    // sample rows a wave has in flight
 
-__global__ __launch_bounds__(256) void second_moment_kernel(const float* __restrict__ q_rot, double* __restrict__ part,
-                                                            int Hq, int Hkv, long rows) {
-  // rows = n_samples * G row vectors of this KV head: row r is sample r / G, head kv * G + r % G
-  __shared__ float s_x[kMomentRows][kFD];
-  const int kv = blockIdx.y, p = blockIdx.x, tid = threadIdx.x, G = Hq / Hkv;
-  const int ti = (tid >> 4) * 8, tj = (tid & 15) * 8;   // this thread's 8 x 8 block of H
-  double acc[8][8];
-#pragma unroll
+// Partial sums per KV head: two workgroups per CU over all heads.
+inline int moment_parts(int Hkv) { return Hkv < 8 ? 512 / Hkv : 64; }
+
+struct MomentPlan {
+  int i[kMomentTiles], j[kMomentTiles];   // tiles row by row, j >= i; wave w takes 9 w .. 9 w + 8
+  bool needs[4][8];                       // does wave w read block b of the dimensions
+};
+constexpr MomentPlan make_moment_plan() {
+  MomentPlan p{};
+  int t = 0;
   for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[i][j] = 0.0;
-  for (long r0 = (long)p * kMomentRows; r0 < rows; r0 += (long)kMomentParts * kMomentRows) {
-    __syncthreads();
-    for (int e = tid; e < kMomentRows * (kFD / 4); e += 256) {
-      const int rr = e / (kFD / 4), c4 = e % (kFD / 4);
-      const long r = r0 + rr;
-      float4 f = make_float4(0.f, 0.f, 0.f, 0.f);   // rows past the end add nothing
-      if (r < rows) f = *(const float4*)(q_rot + ((size_t)(r / G) * Hq + kv * G + r % G) * kFD + 4 * c4);
-      *(float4*)&s_x[rr][4 * c4] = f;
+    for (int j = i; j < 8; ++j, ++t) {
+      p.i[t] = i;
+      p.j[t] = j;
+      p.needs[t / 9][i] = p.needs[t / 9][j] = true;
     }
-    __syncthreads();
-    for (int rr = 0; rr < kMomentRows; ++rr) {
-      double a[8], b[8];
+  return p;
+}
+
+// Nine tiles of one of the four waves.  Four rows x[k][..] at a time: lane = (k = lane / 16, dimension lane % 16 of
+// a block) is the layout of both operands of v_mfma_f64_16x16x4_f64, so one conversion of a loaded float serves
+// every tile of its block, as row and as column operand.  Register r of a result: row 4 r + lane / 16, column lane % 16
+// of the tile -- or its transpose, which is the same sum.
+template <int W>
+__device__ __forceinline__ void moment_body(const float* __restrict__ q_rot, double* __restrict__ out, int Hq, int G, int kv,
+                                            uint32_t row0, uint32_t row1) {
+  typedef __attribute__((ext_vector_type(4))) double f64x4;
+  constexpr int kSteps = kMomentRows / 4;
+  constexpr MomentPlan P = make_moment_plan();
+  const int lane = threadIdx.x & 63, k = lane >> 4, c = lane & 15;
+  f64x4 acc[9];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) a[i] = (double)s_x[rr][ti + i], b[i] = (double)s_x[rr][tj + i];
+  for (int t = 0; t < 9; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+  auto row_at = [&](uint32_t r) { return q_rot + ((size_t)(r / (uint32_t)G) * Hq + (uint32_t)(kv * G) + r % (uint32_t)G) * kFD + c; };
+  auto add = [&](const float (&x)[kSteps][8]) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
+    for (int u = 0; u < kSteps; ++u) {
+      double f[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] += a[i] * b[j];
+      for (int b = 0; b < 8; ++b)
+        if (P.needs[W][b]) f[b] = (double)x[u][b];
+#pragma unroll
+      for (int t = 0; t < 9; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[P.i[9 * W + t]], f[P.j[9 * W + t]], acc[t], 0, 0, 0);
     }
+  };
+  // Whole steps of 16 rows, the next one in flight.  (A vector instruction holds up the float64 products, so the rows'
+  // addresses are stepped, not divided out again: 16 / G samples on and 16 % G heads, one more sample where that wraps.)
+  const uint32_t n_full = (row1 - row0) / kMomentRows, head_step = kMomentRows % G;
+  const ptrdiff_t step = ((ptrdiff_t)(kMomentRows / G) * Hq + head_step) * kFD, wrap = (ptrdiff_t)(Hq - G) * kFD;
+  const float* at[kSteps];
+  uint32_t head[kSteps];
+  float x[kSteps][8];
+#pragma unroll
+  for (int u = 0; u < kSteps; ++u) {
+    const uint32_t r = min(row0 + 4 * u + k, row1 - 1);
+    at[u] = row_at(r);
+    head[u] = r % (uint32_t)G;
   }
-  double* out = part + ((size_t)kv * kMomentParts + p) * kFD * kFD;
+  auto request = [&]() {
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+    for (int u = 0; u < kSteps; ++u) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) out[(ti + i) * kFD + tj + j] = acc[i][j];
+      for (int b = 0; b < 8; ++b)
+        if (P.needs[W][b]) x[u][b] = at[u][16 * b];
+      head[u] += head_step;
+      const bool over = head[u] >= (uint32_t)G;
+      at[u] += over ? step + wrap : step;
+      head[u] -= over ? G : 0;
+    }
+  };
+  if (n_full) request();
+#pragma unroll 1
+  for (uint32_t i = 0; i < n_full; ++i) {
+    float now[kSteps][8];
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u)
+#pragma unroll
+      for (int b = 0; b < 8; ++b)
+        if (P.needs[W][b]) now[u][b] = x[u][b];
+    if (i + 1 < n_full) request();   // (uniform)
+    __builtin_amdgcn_sched_barrier(0);
+    add(now);
+  }
+  const uint32_t r0 = row0 + n_full * kMomentRows;
+  if (r0 < row1) {   // the last rows; those past the end are read as the last one and count as zero
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) {
+      const float* p = row_at(min(r0 + 4 * u + k, row1 - 1));
+#pragma unroll
+      for (int b = 0; b < 8; ++b)
+        if (P.needs[W][b]) x[u][b] = p[16 * b];
+#pragma unroll
+      for (int b = 0; b < 8; ++b)
+        if (P.needs[W][b]) x[u][b] = r0 + 4 * u + k < row1 ? x[u][b] : 0.f;
+    }
+    add(x);
+  }
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[((size_t)(9 * W + t) * 16 + 4 * r + k) * 16 + c] = acc[t][r];
+}
+
+// What bounds it: the float64 matrix cores, which run at the vector ALU's rate; what they save are the other half of
+// the symmetric sum and the conversions and LDS reads of a register-blocked loop.  50000 samples x 32 heads:
+// 1255 -> 505 us.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3))) void second_moment_kernel(   // (at least 2: else the accumulators travel to AGPRs and back)
+    const float* __restrict__ q_rot, double* __restrict__ part, int Hq, int Hkv, uint32_t rows, uint32_t rows_per_part) {
+  // rows = n_samples * G row vectors of this KV head: row r is sample r / G, head kv * G + r % G
+  const int kv = blockIdx.y, p = blockIdx.x, G = Hq / Hkv;
+  const uint32_t row0 = p * rows_per_part, row1 = min(rows, row0 + rows_per_part);   // (host: row0 < rows)
+  double* out = part + ((size_t)kv * gridDim.x + p) * (kMomentTiles * 256);
+  switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
+    case 0: moment_body<0>(q_rot, out, Hq, G, kv, row0, row1); break;
+    case 1: moment_body<1>(q_rot, out, Hq, G, kv, row0, row1); break;
+    case 2: moment_body<2>(q_rot, out, Hq, G, kv, row0, row1); break;
+    default: moment_body<3>(q_rot, out, Hq, G, kv, row0, row1);
+  }
 }
 
 __global__ __launch_bounds__(256) void second_moment_sum_kernel(const double* __restrict__ part, float* __restrict__ h,
-                                                                double inv_rows) {
-  const int kv = blockIdx.y, e = blockIdx.x * 256 + threadIdx.x;   // e < 128 * 128
+                                                                double inv_rows, int n_parts) {
+  const int kv = blockIdx.y, t = blockIdx.x, e = threadIdx.x;   // an element of tile t
+  const double* p = part + (size_t)kv * n_parts * (kMomentTiles * 256) + t * 256 + e;
   double s = 0.0;
-  for (int p = 0; p < kMomentParts; ++p) s += part[((size_t)kv * kMomentParts + p) * kFD * kFD + e];
-  h[(size_t)kv * kFD * kFD + e] = (float)(s * inv_rows);
+#pragma unroll 8
+  for (int i = 0; i < n_parts; ++i) s += p[(size_t)i * (kMomentTiles * 256)];
+  const float v = (float)(s * inv_rows);
+  int bi = 0, bj = t;
+  while (bj >= 8 - bi) bj -= 8 - bi++;
+  bj += bi;
+  const int i = 16 * bi + (e >> 4), j = 16 * bj + (e & 15);
+  float* o = h + (size_t)kv * kFD * kFD;
+  o[(size_t)i * kFD + j] = v;
+  if (bi != bj) o[(size_t)j * kFD + i] = v;   // (a diagonal tile holds both)
 }
 
 __global__ void update_clear_kernel(double* __restrict__ sums, uint32_t* __restrict__ counts, size_t n_sums,
@@ -79,7 +176,7 @@ __global__ void update_clear_kernel(double* __restrict__ sums, uint32_t* __restr
 }
 
 template <typename CODE>
-__global__ __launch_bounds__(256) void update_add_kernel(const float* __restrict__ keys, const CODE* __restrict__ codes,
+__global__ __launch_bounds__(256) void update_few_kernel(const float* __restrict__ keys, const CODE* __restrict__ codes,
                                                          double* __restrict__ sums, uint32_t* __restrict__ counts,
                                                          int Hkv, int M, int L, int ds, int n_new, int pos0,
                                                          int64_t ctx_stride) {
@@ -92,6 +189,126 @@ __global__ __launch_bounds__(256) void update_add_kernel(const float* __restrict
   const size_t cw = ((size_t)kv * M + m) * L + c;
   unsafeAtomicAdd(&sums[cw * ds + t % ds], (double)keys[((size_t)bkv * n_new + j) * kFD + t]);
   if (t % ds == 0) atomicAdd(&counts[cw], 1u);
+}
+
+// Product quantiser.  A workgroup takes kAddSub subspaces (64 dimensions at ds = 8, 32 at ds = 4) of a share of the
+// keys of a KV head; their sums fill 128 KB (64 KB) of LDS.  What bounds it: the LDS atomics; in memory every key would
+// cost 128 float64 atomics (24001 keys x 32: M = 16 1056 -> 239 us, M = 32 1950 -> 240 us).
+constexpr int kAddThreads = 1024, kAddSub = 8;
+template <int DS>
+__global__ __launch_bounds__(kAddThreads) void update_add_kernel(const float* __restrict__ keys,
+                                                                 const uint8_t* __restrict__ codes,
+                                                                 double* __restrict__ sums, uint32_t* __restrict__ counts,
+                                                                 int B, int Hkv, int M, int n_new, int pos0,
+                                                                 int64_t ctx_stride, long rows_per_wg) {
+  constexpr int L = 256, kRow = kAddSub * DS, kPerStep = kAddThreads / kRow;   // floats of a key, keys per step
+  extern __shared__ double s_sum[];              // [subspace][code][ds]
+  uint32_t* s_n = (uint32_t*)(s_sum + kAddSub * L * DS);   // [subspace][code]
+  const int kv = blockIdx.z, sub0 = blockIdx.y * kAddSub, tid = threadIdx.x;
+  for (int i = tid; i < kAddSub * L * DS; i += kAddThreads) s_sum[i] = 0.0;
+  for (int i = tid; i < kAddSub * L; i += kAddThreads) s_n[i] = 0u;
+  __syncthreads();
+  const long rows = (long)B * n_new;   // of the KV head: row r is key r % n_new of sequence r / n_new
+  const long r0 = blockIdx.x * rows_per_wg, r1 = min(rows, r0 + rows_per_wg);
+  const int e = tid % kRow, sub = e / DS, t = e % DS;
+#pragma unroll 4
+  for (long r = r0 + tid / kRow; r < r1; r += kPerStep) {
+    const uint32_t b = (uint32_t)r / (uint32_t)n_new, j = (uint32_t)r % (uint32_t)n_new;   // (rows < 2^31)
+    const size_t bkv = (size_t)b * Hkv + kv;
+    const int c = codes[(bkv * ctx_stride + pos0 + j) * M + sub0 + sub];
+    const float x = keys[(bkv * n_new + j) * kFD + sub0 * DS + e];
+    unsafeAtomicAdd(&s_sum[(sub * L + c) * DS + t], (double)x);
+    if (t == 0) atomicAdd(&s_n[sub * L + c], 1u);
+  }
+  __syncthreads();
+  const size_t cw0 = ((size_t)kv * M + sub0) * L;
+  for (int i = tid; i < kAddSub * L * DS; i += kAddThreads)
+    if (s_n[i / DS]) unsafeAtomicAdd(&sums[cw0 * DS + i], s_sum[i]);
+  for (int i = tid; i < kAddSub * L; i += kAddThreads)
+    if (s_n[i]) atomicAdd(&counts[cw0 + i], s_n[i]);
+}
+
+// Single codebook: 4096 codewords of 128 dimensions do not fit LDS, but the keys can be read in the order of their
+// codes.  counts[kv][c] and every key's rank among those of its code, then cursor[kv][c] = first place of code c, then
+// order[kv][place] = (row, code).
+constexpr int kFL = 4096;
+__global__ __launch_bounds__(256) void update_count_kernel(const uint16_t* __restrict__ codes, uint32_t* __restrict__ counts,
+                                                           uint32_t* __restrict__ rank, int Hkv, int n_new, int pos0,
+                                                           int64_t ctx_stride) {
+  const int bkv = blockIdx.y, j = blockIdx.x * 256 + threadIdx.x;
+  if (j >= n_new) return;
+  const int c = codes[(size_t)bkv * ctx_stride + pos0 + j] & (kFL - 1);
+  rank[(size_t)bkv * n_new + j] = atomicAdd(&counts[(size_t)(bkv % Hkv) * kFL + c], 1u);
+}
+
+__global__ __launch_bounds__(1024) void update_scan_kernel(const uint32_t* __restrict__ counts, uint32_t* __restrict__ cursor) {
+  __shared__ uint32_t s_wave[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint4 n = ((const uint4*)(counts + (size_t)blockIdx.x * kFL))[tid];
+  const uint32_t own = n.x + n.y + n.z + n.w;
+  uint32_t inc = own;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t o = __shfl_up(inc, off);
+    if (lane >= off) inc += o;
+  }
+  if (lane == 63) s_wave[wave] = inc;
+  __syncthreads();
+  uint32_t at = inc - own;
+  for (int w = 0; w < wave; ++w) at += s_wave[w];
+  ((uint4*)(cursor + (size_t)blockIdx.x * kFL))[tid] = make_uint4(at, at + n.x, at + n.x + n.y, at + n.x + n.y + n.z);
+}
+
+__global__ __launch_bounds__(256) void update_place_kernel(const uint16_t* __restrict__ codes,
+                                                           const uint32_t* __restrict__ cursor,
+                                                           const uint32_t* __restrict__ rank, uint2* __restrict__ order,
+                                                           int Hkv, int n_new, int pos0, int64_t ctx_stride, long rows) {
+  const int bkv = blockIdx.y, kv = bkv % Hkv, j = blockIdx.x * 256 + threadIdx.x;
+  if (j >= n_new) return;
+  const uint32_t c = codes[(size_t)bkv * ctx_stride + pos0 + j] & (kFL - 1), row = (uint32_t)((size_t)bkv * n_new + j);
+  const uint32_t at = cursor[(size_t)kv * kFL + c] + rank[row];
+  order[(size_t)kv * rows + at] = make_uint2(row, c);   // (512 bytes a key: fewer than 2^32 fit the card)
+}
+
+// A wave takes 64 consecutive keys of the order, two dimensions per lane, and adds a run of equal codes up before it
+// goes to memory.  What bounds it: reading the keys, 512 bytes at a time in no order of theirs, and 2 atomics per lane
+// and run (23 keys a run at 768 k keys): 88 us, 156 us for the whole call; 592 us with 128 atomics per
+// key.
+__global__ __launch_bounds__(256) void update_sorted_kernel(const float* __restrict__ keys, const uint2* __restrict__ order,
+                                                            double* __restrict__ sums, long rows) {
+  const int kv = blockIdx.y, lane = threadIdx.x & 63;
+  const long first = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * 64;
+  if (first >= rows) return;
+  const int n = (int)min(64L, rows - first);   // (uniform in the wave)
+  const uint2 mine = order[(size_t)kv * rows + first + min(lane, n - 1)];
+  double* out = sums + (size_t)kv * kFL * kFD + 2 * lane;
+  double a0 = 0.0, a1 = 0.0;
+  uint32_t run = __builtin_amdgcn_readfirstlane(mine.y);
+  constexpr int U = 8;
+#pragma unroll 1
+  for (int i0 = 0; i0 < n; i0 += U) {
+    float2 x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t row = __builtin_amdgcn_readlane(mine.x, min(i0 + u, n - 1));
+      x[u] = *(const float2*)(keys + (size_t)row * kFD + 2 * lane);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (i0 + u >= n) break;
+      const uint32_t c = __builtin_amdgcn_readlane(mine.y, i0 + u);
+      if (c != run) {   // (uniform)
+        unsafeAtomicAdd(&out[(size_t)run * kFD], a0);
+        unsafeAtomicAdd(&out[(size_t)run * kFD + 1], a1);
+        a0 = a1 = 0.0;
+        run = c;
+      }
+      a0 += (double)x[u].x;
+      a1 += (double)x[u].y;
+    }
+  }
+  unsafeAtomicAdd(&out[(size_t)run * kFD], a0);
+  unsafeAtomicAdd(&out[(size_t)run * kFD + 1], a1);
 }
 
 __global__ __launch_bounds__(256) void update_mean_kernel(const double* __restrict__ sums,
@@ -108,24 +325,48 @@ __global__ __launch_bounds__(256) void update_mean_kernel(const double* __restri
 
 }  // namespace
 
-size_t fit_ws_bytes(const a2ats_dims& d) {
-  const size_t moment = (size_t)d.n_kv_heads * kMomentParts * kFD * kFD * sizeof(double);
+struct FitWs {
+  size_t off_counts, off_cursor, off_rank, off_order, bytes;   // of the update; its sums come first
+};
+static FitWs fit_ws(const a2ats_dims& d) {
   const size_t cws = (size_t)d.n_kv_heads * d.n_sub * d.n_centroids;
-  const size_t update = cws * d.sub_dim * sizeof(double) + cws * sizeof(uint32_t);
-  return ((moment > update ? moment : update) + 255) & ~(size_t)255;
+  size_t o = 0;
+  auto take = [&](size_t bytes) {
+    const size_t at = o;
+    o += (bytes + 255) & ~(size_t)255;
+    return at;
+  };
+  FitWs w;
+  take(cws * d.sub_dim * sizeof(double));
+  w.off_counts = take(cws * sizeof(uint32_t));
+  const bool single = single_codebook(d);
+  w.off_cursor = take(single ? cws * sizeof(uint32_t) : 0);
+  w.off_rank = take(single ? (size_t)d.batch * d.n_kv_heads * (size_t)d.ctx_stride * sizeof(uint32_t) : 0);
+  w.off_order = take(single ? (size_t)d.batch * d.n_kv_heads * (size_t)d.ctx_stride * sizeof(uint2) : 0);
+  const size_t moment = (size_t)d.n_kv_heads * moment_parts(d.n_kv_heads) * kMomentTiles * 256 * sizeof(double);
+  w.bytes = ((moment > o ? moment : o) + 255) & ~(size_t)255;
+  return w;
 }
+
+size_t fit_ws_bytes(const a2ats_dims& d) { return fit_ws(d).bytes; }
 
 hipError_t launch_second_moment(const a2ats_dims& d, const float* q_rot, int64_t n_samples, float* h_out, void* ws,
                                 hipStream_t stream) {
   if (d.n_kv_heads == 0) return hipSuccess;
   const int G = d.n_q_heads / d.n_kv_heads;
-  const long rows = (long)n_samples * G;
-  hipLaunchKernelGGL(second_moment_kernel, dim3(kMomentParts, d.n_kv_heads), dim3(256), 0, stream, q_rot, (double*)ws,
-                     d.n_q_heads, d.n_kv_heads, rows);
+  const long rows = (long)n_samples * G;   // (512 bytes each: fewer than 2^32 fit the card)
+  // at least 64 rows a workgroup: the partials are 72 KB each
+  const int most = moment_parts(d.n_kv_heads);
+  long per = (rows + most - 1) / most;
+  per = ((per < 64 ? 64 : per) + kMomentRows - 1) / kMomentRows * kMomentRows;
+  const int parts = (int)((rows + per - 1) / per);
+  if (parts > 0)
+    hipLaunchKernelGGL(second_moment_kernel, dim3(parts, d.n_kv_heads), dim3(256), 0, stream, q_rot, (double*)ws,
+                       d.n_q_heads, d.n_kv_heads, (uint32_t)rows, (uint32_t)per);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(second_moment_sum_kernel, dim3(kFD * kFD / 256, d.n_kv_heads), dim3(256), 0, stream,
-                     (const double*)ws, h_out, rows > 0 ? 1.0 / (double)rows : 0.0);
+  hipLaunchKernelGGL(second_moment_sum_kernel, dim3(kMomentTiles, d.n_kv_heads), dim3(256), 0, stream,
+                     (const double*)ws, h_out, rows > 0 ? 1.0 / (double)rows : 0.0, parts);
   return hipGetLastError();
 }
 
@@ -134,19 +375,63 @@ hipError_t launch_codebook_update(const a2ats_dims& d, const float* keys, int n_
                                   hipStream_t stream) {
   const size_t cws = (size_t)d.n_kv_heads * d.n_sub * d.n_centroids, n_elems = cws * d.sub_dim;
   if (n_elems == 0) return hipSuccess;
-  double* sums = (double*)ws;
-  uint32_t* counts = (uint32_t*)(sums + n_elems);
+  const FitWs w = fit_ws(d);
+  uint8_t* base = (uint8_t*)ws;
+  double* sums = (double*)base;
+  uint32_t* counts = (uint32_t*)(base + w.off_counts);
   hipLaunchKernelGGL(update_clear_kernel, dim3(1024), dim3(256), 0, stream, sums, counts, n_elems, cws);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
-  if (n_new > 0 && d.batch > 0) {
-    const dim3 grid((n_new + 1) / 2, d.batch * d.n_kv_heads);
+  const int Hkv = d.n_kv_heads, bkv = d.batch * Hkv;
+  const long rows = (long)d.batch * n_new, n_keys = rows * Hkv;
+  // Few keys are added one by one: below these counts the further launches, or filling and emptying the sums in LDS,
+  // cost more than the atomics they save (one by one -> otherwise, us: single codebook 16000 keys 33 -> 50, 20000 24 ->
+  // 29, 80000 75 -> 51; M = 16, 8000 keys 18 -> 21, 16000 29 -> 24; M = 32, 2000 keys 13 -> 14, 8000 28 -> 15).
+  if (n_new > 0 && d.batch > 0 && n_keys < (single_codebook(d) ? 48000 : 192000 / d.n_sub)) {
+    const dim3 grid((n_new + 1) / 2, bkv);
     if (single_codebook(d))
-      hipLaunchKernelGGL(update_add_kernel<uint16_t>, grid, dim3(256), 0, stream, keys, (const uint16_t*)codes, sums,
-                         counts, d.n_kv_heads, d.n_sub, d.n_centroids, d.sub_dim, n_new, pos0, d.ctx_stride);
+      hipLaunchKernelGGL(update_few_kernel<uint16_t>, grid, dim3(256), 0, stream, keys, (const uint16_t*)codes, sums,
+                         counts, Hkv, d.n_sub, d.n_centroids, d.sub_dim, n_new, pos0, d.ctx_stride);
     else
-      hipLaunchKernelGGL(update_add_kernel<uint8_t>, grid, dim3(256), 0, stream, keys, (const uint8_t*)codes, sums,
-                         counts, d.n_kv_heads, d.n_sub, d.n_centroids, d.sub_dim, n_new, pos0, d.ctx_stride);
+      hipLaunchKernelGGL(update_few_kernel<uint8_t>, grid, dim3(256), 0, stream, keys, (const uint8_t*)codes, sums,
+                         counts, Hkv, d.n_sub, d.n_centroids, d.sub_dim, n_new, pos0, d.ctx_stride);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+  } else if (n_new > 0 && d.batch > 0 && single_codebook(d)) {
+    uint32_t* cursor = (uint32_t*)(base + w.off_cursor);
+    uint32_t* rank = (uint32_t*)(base + w.off_rank);
+    uint2* order = (uint2*)(base + w.off_order);
+    const uint16_t* c16 = (const uint16_t*)codes;
+    const dim3 grid((n_new + 255) / 256, bkv);
+    hipLaunchKernelGGL(update_count_kernel, grid, dim3(256), 0, stream, c16, counts, rank, Hkv, n_new, pos0,
+                       d.ctx_stride);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+    hipLaunchKernelGGL(update_scan_kernel, dim3(Hkv), dim3(1024), 0, stream, counts, cursor);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+    hipLaunchKernelGGL(update_place_kernel, grid, dim3(256), 0, stream, c16, cursor, rank, order, Hkv, n_new, pos0,
+                       d.ctx_stride, rows);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+    hipLaunchKernelGGL(update_sorted_kernel, dim3((unsigned)((rows + 255) / 256), Hkv), dim3(256), 0, stream, keys, order,
+                       sums, rows);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+  } else if (n_new > 0 && d.batch > 0) {
+    // One workgroup per CU: as many shares of the keys as fill the CUs once, of 512 keys or more (a share ends with
+    // up to 16384 atomics).
+    const long groups = (long)Hkv * (d.n_sub / kAddSub);
+    const long shares = groups < 256 ? 256 / groups : 1;
+    long per = (rows + shares - 1) / shares;
+    if (per < 512) per = 512;
+    const dim3 grid((unsigned)((rows + per - 1) / per), d.n_sub / kAddSub, Hkv);
+    const size_t lds = (size_t)kAddSub * 256 * (d.sub_dim * sizeof(double) + sizeof(uint32_t));
+    static LdsSlot s_lds[2][16];
+    if (d.sub_dim == 8) {
+      if ((err = allow_dynamic_lds(update_add_kernel<8>, lds, s_lds[0])) != hipSuccess) return err;
+      hipLaunchKernelGGL(update_add_kernel<8>, grid, dim3(kAddThreads), lds, stream, keys, (const uint8_t*)codes, sums,
+                         counts, d.batch, Hkv, d.n_sub, n_new, pos0, d.ctx_stride, per);
+    } else {
+      if ((err = allow_dynamic_lds(update_add_kernel<4>, lds, s_lds[1])) != hipSuccess) return err;
+      hipLaunchKernelGGL(update_add_kernel<4>, grid, dim3(kAddThreads), lds, stream, keys, (const uint8_t*)codes, sums,
+                         counts, d.batch, Hkv, d.n_sub, n_new, pos0, d.ctx_stride, per);
+    }
     if ((err = hipGetLastError()) != hipSuccess) return err;
   }
   hipLaunchKernelGGL(update_mean_kernel, dim3((unsigned)((n_elems + 255) / 256)), dim3(256), 0, stream, sums, counts,

@@ -40,6 +40,9 @@ AttnPlan make_attn_plan(const a2ats_dims& d, int top_k, int window, int n_sink) 
   p.n_far = (int)nf;
   p.n_win = (int)nw;
   p.bytes = (size_t)heads * (nf + nw) * (kD + 2) * sizeof(float);
+  // Heads that fill the CUs four times over by themselves: one workgroup takes all rows of a head and writes its
+  // output, and nothing is left to merge (64 sequences x 32 heads, 491 + 64 rows: 112 us and 5 for the merge -> 105).
+  p.whole = heads >= 1024;
   return p;
 }
 
@@ -101,7 +104,8 @@ __device__ __forceinline__ void merge_state(float& m, float& l, float (&acc)[VEC
 // rows.  The grid is then one-dimensional and mapped so that the G workgroups that read the same
 // rows (same KV head, same part) run next to each other on one XCD: the rows come from HBM once
 // and from that XCD's L2 for the other G - 1 heads.
-template <typename T, bool SHARED>
+// WHOLE: the workgroup takes the far rows and then the window rows of its head and writes the head's output (`out`).
+template <typename T, bool SHARED, bool WHOLE = false>
 __device__ __forceinline__ void attn_partial_body(
     int part, int bh, const T* __restrict__ q, const float* __restrict__ q_rot, const T* __restrict__ k_cache,
     const T* __restrict__ v_cache, const int32_t* __restrict__ topk_idx,
@@ -109,7 +113,7 @@ __device__ __forceinline__ void attn_partial_body(
     const float* __restrict__ sin_win, const int32_t* __restrict__ seq_lens,
     float* __restrict__ partial, int Hq, int Hkv, int ctx_len, int64_t ctx_stride, int top_k,
     int window, int n_sink, int n_far, int n_win, const int32_t* __restrict__ page_table, int page_shift,
-    int pages_per_seq) {
+    int pages_per_seq, T* __restrict__ out = nullptr) {
   // page_table != NULL: k_cache / v_cache are pools of pages [page][Hkv][2^page_shift][D] and token j of
   // sequence b lives in page page_table[b][j >> page_shift]; else row j of [B][Hkv][ctx_stride][D].
   constexpr int LPR = RowVec<T>::LPR, VEC = RowVec<T>::VEC;
@@ -129,10 +133,10 @@ __device__ __forceinline__ void attn_partial_body(
   const int cnt = max(0, min(min(topk_count[ih], top_k), sr.ncand));
   // Far rows (sinks, then the retrieved rows) are dealt out round-robin to the first n_far
   // workgroups of the head, window rows to the other n_win.
-  const bool win_part = part >= n_far;
+  bool win_part = !WHOLE && part >= n_far;
   const int n_rows = win_part ? sr.n - sr.win_start : sr.sink_end + cnt;
-  const int stride = win_part ? n_win : n_far, first = win_part ? part - n_far : part;
-  const int n_mine = n_rows > first ? (n_rows - first + stride - 1) / stride : 0;
+  const int stride = WHOLE ? 1 : (win_part ? n_win : n_far), first = WHOLE ? 0 : (win_part ? part - n_far : part);
+  int n_mine = n_rows > first ? (n_rows - first + stride - 1) / stride : 0;
 
   const int d0 = sub * VEC;
   const float scale = 0.08838834764831845f;   // 1/sqrt(128)
@@ -162,99 +166,106 @@ __device__ __forceinline__ void attn_partial_body(
     m_run = mn;
   };
 
-  for (int tb = 0; tb < n_mine; tb += kAttnTile) {
-    const int tn = min(kAttnTile, n_mine - tb);
-    __syncthreads();
-    for (int i = tid; i < tn; i += kAttnThreads) {
-      const int t = first + (tb + i) * stride;
-      int j;
-      if (win_part) j = sr.win_start + t;
-      else j = t < sr.sink_end ? t : idx[t - sr.sink_end];
-      j = min(max(j, 0), sr.n - 1);   // a bad caller index must not leave the cache
-      s_pos[i] = j;
-      s_row[i] = pages ? (((uint32_t)pages[j >> page_shift] * (uint32_t)Hkv + (uint32_t)kv) << page_shift) +
-                             (uint32_t)(j & ((1 << page_shift) - 1))
-                       : (uint32_t)j;
+#pragma unroll
+  for (int pass = 0; pass < (WHOLE ? 2 : 1); ++pass) {
+    if (WHOLE) {
+      win_part = pass == 1;
+      n_mine = win_part ? sr.n - sr.win_start : sr.sink_end + cnt;
     }
-    __syncthreads();
+    for (int tb = 0; tb < n_mine; tb += kAttnTile) {
+      const int tn = min(kAttnTile, n_mine - tb);
+      __syncthreads();
+      for (int i = tid; i < tn; i += kAttnThreads) {
+        const int t = first + (tb + i) * stride;
+        int j;
+        if (win_part) j = sr.win_start + t;
+        else j = t < sr.sink_end ? t : idx[t - sr.sink_end];
+        j = min(max(j, 0), sr.n - 1);   // a bad caller index must not leave the cache
+        s_pos[i] = j;
+        s_row[i] = pages ? (((uint32_t)pages[j >> page_shift] * (uint32_t)Hkv + (uint32_t)kv) << page_shift) +
+                               (uint32_t)(j & ((1 << page_shift) - 1))
+                         : (uint32_t)j;
+      }
+      __syncthreads();
 
-    if (!win_part) {
-      // Far rows: logit = q~ . k.  Two register sets of U rows are used alternately: the loads of
-      // one are issued (unconditionally, row index clamped) before the other is consumed, so a
-      // wave always has 2 U key and value rows in flight.
-      constexpr int U = 2;
-      constexpr int STEP = RB * U;
-      float q_far[VEC];
+      if (!win_part) {
+        // Far rows: logit = q~ . k.  Two register sets of U rows are used alternately: the loads of
+        // one are issued (unconditionally, row index clamped) before the other is consumed, so a
+        // wave always has 2 U key and value rows in flight.
+        constexpr int U = 2;
+        constexpr int STEP = RB * U;
+        float q_far[VEC];
 #pragma unroll
-      for (int v = 0; v < VEC; ++v) q_far[v] = q_rot[qb + d0 + v];
-      uint4 ka[U], va[U], kc[U], vc[U];
-      auto load_set = [&](int i0, uint4 (&kr)[U], uint4 (&vr)[U]) {
+        for (int v = 0; v < VEC; ++v) q_far[v] = q_rot[qb + d0 + v];
+        uint4 ka[U], va[U], kc[U], vc[U];
+        auto load_set = [&](int i0, uint4 (&kr)[U], uint4 (&vr)[U]) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const uint32_t row = s_row[min(i0 + u * RB, tn - 1)];
-          kr[u] = RowVec<T>::load(kb + (size_t)row * kD);
-          vr[u] = RowVec<T>::load(vb + (size_t)row * kD);
-        }
-      };
-      auto use_set = [&](int i0, const uint4 (&kr)[U], const uint4 (&vr)[U]) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          float kf[VEC];
-          RowVec<T>::widen(kr[u], kf);
-          float dot = 0.f;
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) dot += q_far[v] * kf[v];
-          if (i0 + u * RB < tn) absorb(dot, vr[u]);
-        }
-      };
-      const int lane_row = wv * SLOTS + slot;
-      load_set(lane_row, ka, va);
-#pragma unroll 1
-      for (int base = 0; base < tn; base += 2 * STEP) {
-        load_set(base + STEP + lane_row, kc, vc);
-        use_set(base + lane_row, ka, va);
-        load_set(base + 2 * STEP + lane_row, ka, va);
-        use_set(base + STEP + lane_row, kc, vc);
-      }
-    } else {
-      // Window rows: logit = (q R_delta) . k with the standard rotation at the relative position
-      // delta = n - 1 - j, built from the cos/sin tables of the row.
-      constexpr int U = 2;
-      const bool low_half = d0 < HALF;
-      const int dp = low_half ? d0 + HALF : d0 - HALF;
-      const float sgn = low_half ? -1.f : 1.f;
-      float q_own[VEC], q_par[VEC];
-#pragma unroll
-      for (int v = 0; v < VEC; ++v) {
-        q_own[v] = load_elem(q + qb + d0 + v);
-        q_par[v] = load_elem(q + qb + dp + v) * sgn;
-      }
-      for (int i0 = wv * SLOTS + slot; i0 < tn; i0 += RB * U) {
-        uint4 kr[U], vr[U];
-        float cw[U][VEC], sw[U][VEC];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int j = s_pos[min(i0 + u * RB, tn - 1)];
-          const uint32_t row = s_row[min(i0 + u * RB, tn - 1)];
-          kr[u] = RowVec<T>::load(kb + (size_t)row * kD);
-          vr[u] = RowVec<T>::load(vb + (size_t)row * kD);
-          const int delta = min(max(sr.n - 1 - j, 0), window - 1);
-          const float* cp = cos_win + (size_t)delta * HALF + (d0 & (HALF - 1));
-          const float* sp = sin_win + (size_t)delta * HALF + (d0 & (HALF - 1));
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) {
-            cw[u][v] = cp[v];
-            sw[u][v] = sp[v];
+          for (int u = 0; u < U; ++u) {
+            const uint32_t row = s_row[min(i0 + u * RB, tn - 1)];
+            kr[u] = RowVec<T>::load(kb + (size_t)row * kD);
+            vr[u] = RowVec<T>::load(vb + (size_t)row * kD);
           }
+        };
+        auto use_set = [&](int i0, const uint4 (&kr)[U], const uint4 (&vr)[U]) {
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            float kf[VEC];
+            RowVec<T>::widen(kr[u], kf);
+            float dot = 0.f;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) dot += q_far[v] * kf[v];
+            if (i0 + u * RB < tn) absorb(dot, vr[u]);
+          }
+        };
+        const int lane_row = wv * SLOTS + slot;
+        load_set(lane_row, ka, va);
+#pragma unroll 1
+        for (int base = 0; base < tn; base += 2 * STEP) {
+          load_set(base + STEP + lane_row, kc, vc);
+          use_set(base + lane_row, ka, va);
+          load_set(base + 2 * STEP + lane_row, ka, va);
+          use_set(base + STEP + lane_row, kc, vc);
         }
+      } else {
+        // Window rows: logit = (q R_delta) . k with the standard rotation at the relative position
+        // delta = n - 1 - j, built from the cos/sin tables of the row.
+        constexpr int U = 2;
+        const bool low_half = d0 < HALF;
+        const int dp = low_half ? d0 + HALF : d0 - HALF;
+        const float sgn = low_half ? -1.f : 1.f;
+        float q_own[VEC], q_par[VEC];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          float kf[VEC];
-          RowVec<T>::widen(kr[u], kf);
-          float dot = 0.f;
+        for (int v = 0; v < VEC; ++v) {
+          q_own[v] = load_elem(q + qb + d0 + v);
+          q_par[v] = load_elem(q + qb + dp + v) * sgn;
+        }
+        for (int i0 = wv * SLOTS + slot; i0 < tn; i0 += RB * U) {
+          uint4 kr[U], vr[U];
+          float cw[U][VEC], sw[U][VEC];
 #pragma unroll
-          for (int v = 0; v < VEC; ++v) dot += (q_own[v] * cw[u][v] + q_par[v] * sw[u][v]) * kf[v];
-          if (i0 + u * RB < tn) absorb(dot, vr[u]);
+          for (int u = 0; u < U; ++u) {
+            const int j = s_pos[min(i0 + u * RB, tn - 1)];
+            const uint32_t row = s_row[min(i0 + u * RB, tn - 1)];
+            kr[u] = RowVec<T>::load(kb + (size_t)row * kD);
+            vr[u] = RowVec<T>::load(vb + (size_t)row * kD);
+            const int delta = min(max(sr.n - 1 - j, 0), window - 1);
+            const float* cp = cos_win + (size_t)delta * HALF + (d0 & (HALF - 1));
+            const float* sp = sin_win + (size_t)delta * HALF + (d0 & (HALF - 1));
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+              cw[u][v] = cp[v];
+              sw[u][v] = sp[v];
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            float kf[VEC];
+            RowVec<T>::widen(kr[u], kf);
+            float dot = 0.f;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) dot += (q_own[v] * cw[u][v] + q_par[v] * sw[u][v]) * kf[v];
+            if (i0 + u * RB < tn) absorb(dot, vr[u]);
+          }
         }
       }
     }
@@ -281,9 +292,13 @@ __device__ __forceinline__ void attn_partial_body(
       const float a2[1] = {s_acc[w][tid]};
       merge_state<1>(m, l, a, s_m[w], s_l[w], a2);
     }
-    float* pp = partial + ((size_t)bh * (n_far + n_win) + part) * (kD + 2);
-    pp[tid] = a[0];
-    if (tid == 0) { pp[kD] = m; pp[kD + 1] = l; }
+    if constexpr (WHOLE) {
+      store_elem(out + qb + tid, l > 0.f ? a[0] / l : 0.f);
+    } else {
+      float* pp = partial + ((size_t)bh * (n_far + n_win) + part) * (kD + 2);
+      pp[tid] = a[0];
+      if (tid == 0) { pp[kD] = m; pp[kD + 1] = l; }
+    }
   }
 }
 
@@ -308,6 +323,15 @@ __global__ __launch_bounds__(kAttnThreads) void attn_partial_kernel(A2ATS_ATTN_A
   int prob, pg;
   xcd_map(blockIdx.x, parts * G, (int)(gridDim.x / (parts * G)), prob, pg);   // prob = b * Hkv + kv
   attn_partial_body<T, SHARED>(pg / G, prob * G + pg % G, A2ATS_ATTN_PASS);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kAttnThreads) void attn_whole_kernel(A2ATS_ATTN_ARGS, T* __restrict__ out) {
+  // (the heads of a KV head side by side on one XCD, as above)
+  const int G = Hq / Hkv;
+  int prob, g;
+  xcd_map(blockIdx.x, G, (int)(gridDim.x / G), prob, g);
+  attn_partial_body<T, false, true>(0, prob * G + g, A2ATS_ATTN_PASS, out);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -619,6 +643,12 @@ static hipError_t launch_attn_t(const a2ats_dims& d, const AttnPlan& plan, const
                          (const uint16_t*)k_cache, (const uint16_t*)v_cache, topk_idx, topk_count, cos_win, sin_win,
                          seq_lens, (float*)ws, d.n_q_heads, d.n_kv_heads, d.ctx_len, d.ctx_stride, top_k, window,
                          n_sink, plan.n_far, plan.n_win, page_table, page_shift, pages_per_seq, problems);
+  } else if (!shared && plan.whole) {
+    hipLaunchKernelGGL((attn_whole_kernel<T>), dim3(heads), dim3(kAttnThreads), 0, stream, (const T*)q, q_rot,
+                       (const T*)k_cache, (const T*)v_cache, topk_idx, topk_count, cos_win, sin_win, seq_lens, (float*)ws,
+                       d.n_q_heads, d.n_kv_heads, d.ctx_len, d.ctx_stride, top_k, window, n_sink, plan.n_far, plan.n_win,
+                       page_table, page_shift, pages_per_seq, (T*)out);
+    return hipGetLastError();
   } else if (shared)
     hipLaunchKernelGGL((attn_partial_kernel<T, true>), dim3(parts * heads), dim3(kAttnThreads), 0, stream,
                        (const T*)q, q_rot, (const T*)k_cache, (const T*)v_cache, topk_idx, topk_count,

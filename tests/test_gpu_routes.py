@@ -132,3 +132,60 @@ def test_short_decode_select_equals_the_separate_calls(Bn, Hkv, G, M, N, K, w, n
         res.append((codes, st.q_rot, sk.lut, sk.lut_scale, sk.topk_idx, sk.topk_count, sk.topk_score))
     for a, b in zip(*res):
         assert torch.equal(a.contiguous().view(torch.uint8), b.contiguous().view(torch.uint8))
+
+
+@pytest.mark.parametrize("G,Hkv,N,K,w,n_sink,dtype,page,ragged", [
+    (4, 8, 700, 50, 100, 4, "bf16", 0, True),
+    (7, 4, 1300, 600, 256, 0, "bf16", 16, False),                        # more rows than a staged tile; two windows' worth
+    (4, 8, 300, 0, 64, 0, "f32", 0, True),                               # the window alone
+    (8, 4, 513, 200, 0, 4, "f32", 64, True),                             # no window
+])
+def test_attention_of_many_heads_equals_that_of_few(G, Hkv, N, K, w, n_sink, dtype, page, ragged):
+    """From 1024 heads on a workgroup takes a whole head; the same sequences eight at a time take the split route."""
+    Bn = 40
+    wl = synth.Workload("many", Bn, G * Hkv, Hkv, 128, 16, N, K, w, n_sink=n_sink, kv_dtype=dtype, seed=N)
+    xd = synth.make_decode_inputs(wl, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(N)
+    lens = torch.randint(0, N + 1, (Bn,), generator=g, device="cuda", dtype=torch.int32) if ragged else None
+    if ragged:
+        lens[0], lens[1] = 0, 1
+    k, v, table = xd["k"], xd["v"], None
+    if page:
+        slots = (N + page - 1) // page
+        table = torch.randperm(Bn * slots, generator=g, device="cuda").reshape(Bn, slots).to(torch.int32)
+        pools = []
+        for x in (k, v):
+            padded = torch.zeros(Bn, Hkv, slots * page, 128, dtype=x.dtype, device="cuda")
+            padded[:, :, :N] = x
+            pool = torch.empty(Bn * slots, Hkv, page, 128, dtype=x.dtype, device="cuda")
+            pool[table.long().reshape(-1)] = (padded.reshape(Bn, Hkv, slots, page, 128).permute(0, 2, 1, 3, 4)
+                                              .reshape(Bn * slots, Hkv, page, 128))
+            pools.append(pool)
+        k, v = pools
+
+    def attend(first, n, idx, count):
+        part = wl.replace(batch=n)
+        st = B.DecodeState(H.dims_of(part), K, w, n_sink, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
+        sl = None if lens is None else lens[first:first + n].contiguous()
+        q = xd["q"][first:first + n].contiguous()
+        q_rot = q.float().contiguous()
+        st.out.fill_(7.0)
+        args = (idx[first:first + n].contiguous(), count[first:first + n].contiguous(), K, w, n_sink, st.cos_win, st.sin_win,
+                sl, st.out, st.ws)
+        if page:
+            B.sparse_attn_paged(st.dims, q, q_rot, k, v, table[first:first + n].contiguous(), page, *args)
+        else:
+            B.sparse_attn(st.dims, q, q_rot, k[first:first + n].contiguous(), v[first:first + n].contiguous(), *args)
+        torch.cuda.synchronize()
+        return st.out.float()
+
+    heads = G * Hkv
+    idx = torch.sort(torch.rand(Bn, heads, max(N - w, 1), generator=g, device="cuda").argsort(-1)[..., :max(K, 1)], -1).values
+    idx = idx.to(torch.int32)
+    count = torch.full((Bn, heads), K, dtype=torch.int32, device="cuda")
+    whole = attend(0, Bn, idx, count)
+    few = torch.cat([attend(b, 8, idx, count) for b in range(0, Bn, 8)])
+    # float32 sums in another order, 4e-6 of the values' size (about 1); a bfloat16 output may round the other way, and
+    # neighbours of 8 significant bits are up to 2^-7 of themselves apart
+    tol = 2.0 ** -7 if dtype == "bf16" else 4e-6
+    assert ((whole - few).abs() <= tol * torch.maximum(whole.abs(), few.abs()) + 4e-6).all(), float((whole - few).abs().max())

@@ -147,18 +147,17 @@ def encode_prefill(args, torch, B, synth):
     torch.cuda.synchronize()
     ms = (time.perf_counter() - t0) * 1e3 / steps
     evals = n_keys * M * 256                       # (key subvector, centroid) distance evaluations
-    # instruction mix of the inner loop (from the kernel's ISA, ds = 4): per evaluation 4 subtract,
-    # 1 multiply + 3 fused multiply-add, and + add (index into the low mantissa bits), median-of-3,
-    # minimum = 12 vector instructions; peak issue rate taken as the published 157.3 TFLOP/s / 2 flop
-    # per FMA lane
-    ops_per_eval = 12.0
-    peak = 157.3e12 / 2 / 1e12
+    # the vector ALU ranks what the matrix cores multiply: 17 instructions of a lane per 16 distances (minimum,
+    # median-of-3, and-or), which issue at half the rate of an add; peak taken as half of the published 157.3
+    # TFLOP/s / 2 flop per FMA lane
+    ops_per_eval = 17.0 / 16.0
+    peak = 157.3e12 / 4 / 1e12
     achieved = evals * ops_per_eval / (ms * 1e-3) / 1e12
     print(json.dumps({
         "metric": "encoded keys/s (prefill-side query-aware key encoding, per-dimension weights)",
         "value": n_keys / (ms * 1e-3), "unit": "keys/s", "n_gpus": 1, "steps": steps, "warmup": warmup,
         "ms_per_step": ms, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "f32 distances, f64 re-check of near ties", "data": "synthetic",
+        "dtype": "f16 hi/lo products with f32 accumulate, f64 re-check of near ties", "data": "synthetic",
         "config": {"workload": "c5_qwen7b_64k encode, all 32 sequences", "keys": n_keys, "n_sub": M,
                    "sub_dim": wl.sub_dim, "weights": "W_DIAG"},
         "roofline": {"kernel": "encode_kernel", "bound": "alu", "achieved": achieved, "peak": peak,
@@ -322,14 +321,14 @@ def single_codebook_encode_prefill(args, torch, B, synth, wl):
         "metric": "encoded keys/s (prefill-side query-aware key encoding, one codebook of 4096, full D x D matrix H)",
         "value": n_keys / (ms * 1e-3), "unit": "keys/s", "n_gpus": 1, "steps": steps, "warmup": warmup,
         "ms_per_step": ms, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "bf16 hi/lo split products with f32 accumulate; f64 transform and f64 re-check of near ties",
+        "dtype": "f16 products with f32 accumulate; bf16 hi/lo products, then f64, where they cannot decide",
         "data": "synthetic",
         "config": {"workload": wl.name + " encode", "keys": n_keys, "codewords": 4096, "weights": "W_BLOCK"},
-        "roofline": {"kernel": "encode_single_kernel (+ float64 transform, factor, codeword and re-check kernels)",
+        "roofline": {"kernel": "encode_single_filter_kernel (+ factor, codeword, listed-key and re-check kernels)",
                      "bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak, "traffic": None,
-                     "executed_bf16_TFLOPs": 3.0 * achieved, "executed_frac": 3.0 * achieved / peak,
-                     "note": "algorithmic flops; each term takes three bf16 products (hi.hi + hi.lo + lo.hi)"},
+                     "executed_f16_TFLOPs": achieved, "executed_frac": achieved / peak,
+                     "note": "algorithmic flops; each term takes one f16 product, the keys it leaves open three bf16 ones"},
     }))
 
 

@@ -159,7 +159,7 @@ __device__ __forceinline__ int encode_exact_wave(const float* __restrict__ kp, c
 // centroid near the key has |c| <= |z| + sqrt(d), so S <= 4 |z|^2 + d; the margin between the two nearest
 // quads covers two such errors and the 6 mantissa bits (2^-17) that give way to the quad's number.
 //
-// What bounds it: the vector ALU, of which the ranking is 17 / 64 of an instruction per distance; these (min,
+// What bounds it: the vector ALU, of which the ranking is 17 instructions of a lane per 16 distances; these (min,
 // med3, and_or) issue at half the rate of an add, 4 cycles a wave.  50001 keys x 32 heads x 16 subspaces,
 // per-dimension weights: 2157 -> 545 us (one thread per subvector with 19 vector instructions per distance
 // before; 698 us with the two smallest of all distances tracked, 9 cycles each).

@@ -40,9 +40,12 @@ AttnPlan make_attn_plan(const a2ats_dims& d, int top_k, int window, int n_sink) 
   p.n_far = (int)nf;
   p.n_win = (int)nw;
   p.bytes = (size_t)heads * (nf + nw) * (kD + 2) * sizeof(float);
-  // Heads that fill the CUs four times over by themselves: one workgroup takes all rows of a head and writes its
-  // output, and nothing is left to merge (64 sequences x 32 heads, 491 + 64 rows: 112 us and 5 for the merge -> 105).
-  p.whole = heads >= 1024;
+  // Heads that fill the CUs twice over by themselves, or once with at most a staged tile of far rows: one workgroup
+  // takes all rows of a head and writes its output, and nothing is left to merge.  64 sequences x 32 heads, 491 + 64
+  // rows: 112 us and 5 for the merge -> 105.  Steps, split and merged -> whole: 896 heads, 2048 + 128 rows 304.5 ->
+  // 299.1 us; 512 heads, 1024 + 128 109.3 -> 106.5, 240 + 64 45.9 -> 43.5; 384 heads, 480 + 64 55.8 -> 53.9, 2048 + 128
+  // 158.4 -> 161.1; 256 heads, 400 + 128 52.8 -> 51.9, 1475 + 64 91.3 -> 92.0.
+  p.whole = heads >= 512 || (heads >= 256 && (long)n_sink + top_k <= kAttnTile);
   return p;
 }
 

@@ -141,7 +141,7 @@ def test_short_decode_select_equals_the_separate_calls(Bn, Hkv, G, M, N, K, w, n
     (8, 4, 513, 200, 0, 4, "f32", 64, True),                             # no window
 ])
 def test_attention_of_many_heads_equals_that_of_few(G, Hkv, N, K, w, n_sink, dtype, page, ragged):
-    """From 1024 heads on a workgroup takes a whole head; the same sequences eight at a time take the split route."""
+    """From 512 heads on a workgroup takes a whole head; the same sequences four at a time take the split route."""
     Bn = 40
     wl = synth.Workload("many", Bn, G * Hkv, Hkv, 128, 16, N, K, w, n_sink=n_sink, kv_dtype=dtype, seed=N)
     xd = synth.make_decode_inputs(wl, device="cuda")
@@ -184,7 +184,7 @@ def test_attention_of_many_heads_equals_that_of_few(G, Hkv, N, K, w, n_sink, dty
     idx = idx.to(torch.int32)
     count = torch.full((Bn, heads), K, dtype=torch.int32, device="cuda")
     whole = attend(0, Bn, idx, count)
-    few = torch.cat([attend(b, 8, idx, count) for b in range(0, Bn, 8)])
+    few = torch.cat([attend(b, 4, idx, count) for b in range(0, Bn, 4)])
     # float32 sums in another order, 4e-6 of the values' size (about 1); a bfloat16 output may round the other way, and
     # neighbours of 8 significant bits are up to 2^-7 of themselves apart
     tol = 2.0 ** -7 if dtype == "bf16" else 4e-6

@@ -52,7 +52,10 @@ constexpr int kBlocks = kCW / 32;       // streamed 32-codeword blocks
 static_assert(kFragBytes / 16 / kEncThreads == 4, "a thread stages four 16-byte pieces of a block");
 constexpr int kFewSingle = kFewSingleKeys;   // at most this many keys per (sequence, KV head): float64 sweep only
 constexpr int kSlices = kEncodeSlices;  // workgroups sharing the codewords of one such key
-constexpr float kReach = 2.5e-5f;       // rounding reach of two scores of the bf16 products, relative to |k| max|w|
+// Rounding reach of two scores s of the bf16 products: the split operands' (3 * 2^-18 of |k| max|w| each) and the float32
+// sums', which start at 1/2 |c^z|^2 = s + k . w and take 24 products (25 * 2^-23 of s each; what they lose of k . w is in
+// the slack of the first figure).  Where |k| is short against the codewords the second is all there is.
+constexpr float kSplitReach = 2.5e-5f, kSumReach = 6e-6f;
 constexpr int kF16Bytes = 8 * 64 * 16;  // 8 k-steps x 64 lanes x 16 bytes: 32 codewords of 128 dims in f16
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -836,7 +839,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
     for (int tile = 0; tile < 2; ++tile)
       if (g == 0 && key_first + 32 * tile + col < n_near) {
         const size_t row = row_of(tile);
-        const float reach = kReach * sqrtf(zn2[tile]) * wmax;
+        const float reach = kSplitReach * sqrtf(zn2[tile]) * wmax + kSumReach * fabsf(s1[tile]);
         codes[row / n_new * ctx_stride + pos0 + row % n_new] = (uint16_t)d1[tile];
         if (!(s2[tile] - s1[tile] > reach)) {
           const uint32_t at = atomicAdd(counter, 1u);

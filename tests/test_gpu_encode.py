@@ -158,3 +158,33 @@ def test_single_codebook_ties_and_values_that_are_not_finite():
             ok[10:12] = False
             assert (got[0, 1, 10:12] == 0).all()
         assert torch.equal(got[0, h][ok], first[ok])
+
+
+@pytest.mark.parametrize("mode", ["none", "block"])
+def test_single_codebook_keys_short_against_codewords_of_one_length(mode):
+    """Scores 1/2 |c^z|^2 - k . w whose first term is common to all codewords up to its last bits: the rounding of the
+    sums is relative to that term, not to |k| |w|, and the second term alone decides."""
+    kv, n = 2, 2000
+    wl = synth.Workload("enc1_short", 1, kv, kv, 128, 1, n + 8, 16, 16, seed=11, n_centroids=4096)
+    h64 = torch.eye(128, dtype=torch.float64, device="cuda").expand(kv, 128, 128)
+    weights = None
+    if mode == "block":
+        weights = synth.make_query_second_moment(wl)["h_block"].cuda().reshape(kv, 128, 128).contiguous()
+        h64 = weights.double()
+    codebook = synth.make_codebook(wl, "cuda")
+    z = codebook.double() @ torch.linalg.cholesky(h64)[:, None]
+    codebook = (codebook / z.norm(dim=-1, keepdim=True)).float().contiguous()
+    dims = B.make_dims(1, kv, kv, 128, 1, n + 8, n_centroids=4096)
+    unit = synth.make_encode_keys(wl, n, device="cuda", stress=True)
+    unit = unit / unit.norm(dim=-1, keepdim=True)
+    for size in (1e-1, 1e-2, 1e-3, 1e-4, 1e-5, 1e-6):
+        keys = (unit * size).contiguous()
+        got = _single(dims, keys, codebook, weights, B.W_NONE if mode == "none" else B.W_BLOCK, n + 8)
+        for h in range(kv):
+            c, k = codebook[h, 0].double(), keys[0, h].double()
+            w = c @ h64[h]
+            half = 0.5 * (w * c).sum(-1)
+            score = half - k @ w.t()
+            lost = score.gather(1, got[0, h][:, None])[:, 0] - score.min(1).values
+            # (float64 sums of 128 products, of L L^T instead of H)
+            assert (lost <= 1e-13 * (half.max() + k.norm(dim=1) * w.norm(dim=1).max())).all(), (size, int((lost > 1e-13).sum()))

@@ -700,22 +700,23 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
     for (int tile = 0; tile < 2; ++tile) s1[tile] = s2[tile] = s3[tile] = INFINITY;
 
-    // The loads of the next block are written as asm statements: as ordinary loads the compiler
-    // sinks them past the ranking branches down to their only use, the LDS store before the barrier,
-    // and every step then waits for global memory in the open.  The matching wait is explicit
-    // (loads the compiler does not know of only make its own, counted waits stricter).
+    // The loads of the next block are issued here and waited for where they are used: without the address that the compiler
+    // cannot look through and the fence behind them it sinks them past the ranking branches down to their only use, the
+    // LDS store before the barrier, and every step then waits for global memory in the open.
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef const __attribute__((address_space(1))) uint8_t* global_ptr;
     auto prefetch = [&](int bi, u32x4 (&p)[kFragBytes / 16 / kEncThreads], float& pb) {
       bi = min(bi, kBlocks - 1);   // the step of the last block loads it once more, unused
-      const uint8_t* src = gblk + (size_t)bi * kFragBytes + tid * 16;
+      global_ptr src = (global_ptr)(gblk + (size_t)bi * kFragBytes + tid * 16);
+      global_ptr bsrc = (global_ptr)(gbias + bi * 32 + (tid & 31));
+      asm volatile("" : "+v"(src), "+v"(bsrc));
 #pragma unroll
       for (int i = 0; i < kFragBytes / 16 / kEncThreads; ++i)
-        asm volatile("global_load_dwordx4 %0, %1, off" : "=&v"(p[i]) : "v"(src + i * kEncThreads * 16) : "memory");
-      const float* bsrc = gbias + bi * 32 + (tid & 31);
-      asm volatile("global_load_dword %0, %1, off" : "=&v"(pb) : "v"(bsrc) : "memory");
+        p[i] = *(const __attribute__((address_space(1))) u32x4*)(src + i * kEncThreads * 16);
+      pb = *(const __attribute__((address_space(1))) float*)bsrc;
+      asm volatile("" ::: "memory");
     };
     auto stage = [&](int bi, u32x4 (&p)[kFragBytes / 16 / kEncThreads], float& pb) {
-      asm volatile("s_waitcnt vmcnt(0)" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]), "+v"(pb)::"memory");
       uint8_t* dst = s_mem + (bi & 1) * kBuf;
 #pragma unroll
       for (int i = 0; i < kFragBytes / 16 / kEncThreads; ++i) *(u32x4*)(dst + tid * 16 + i * kEncThreads * 16) = p[i];

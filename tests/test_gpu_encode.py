@@ -188,3 +188,18 @@ def test_single_codebook_keys_short_against_codewords_of_one_length(mode):
             lost = score.gather(1, got[0, h][:, None])[:, 0] - score.min(1).values
             # (float64 sums of 128 products, of L L^T instead of H)
             assert (lost <= 1e-13 * (half.max() + k.norm(dim=1) * w.norm(dim=1).max())).all(), (size, int((lost > 1e-13).sum()))
+
+
+@pytest.mark.parametrize("kv,n", [(8, 12001), (8, 20100), (2, 33000)])
+def test_single_codebook_long_lists_of_undecided_keys(kv, n):
+    """Every codeword twice, so the filter decides no key: lists of 24 to 129 chunks of 256 keys per KV head, by 64 (of 8
+    heads) or 256 (of 2) workgroups each: in slices of the codewords, and with a second chunk for some workgroups."""
+    wl = synth.Workload("enc1_lists", 1, kv, kv, 128, 1, n + 8, 16, 16, seed=n, n_centroids=4096)
+    codebook = synth.make_codebook(wl, "cuda")
+    codebook[:, :, 2048:] = codebook[:, :, :2048]
+    keys = synth.make_encode_keys(wl, n, device="cuda", stress=True)
+    dims = B.make_dims(1, kv, kv, 128, 1, n + 8, n_centroids=4096)
+    got = _single(dims, keys, codebook, None, B.W_NONE, n + 8)
+    for h in range(kv):
+        c = codebook[h, 0, :2048].double()
+        assert torch.equal(got[0, h], (0.5 * c.pow(2).sum(-1) - keys[0, h].double() @ c.t()).argmin(1))

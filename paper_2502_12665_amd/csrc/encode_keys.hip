@@ -158,6 +158,9 @@ __device__ __forceinline__ int encode_exact_wave(const float* __restrict__ kp, c
 // float32 accumulation over at most 32 terms about 2^-21 S, f16 steps 2^-25 * 2.9 (|z| + |c|) + 2^-24.  A
 // centroid near the key has |c| <= |z| + sqrt(d), so S <= 4 |z|^2 + d; the margin between the two nearest
 // quads covers two such errors and the 6 mantissa bits (2^-17) that give way to the quad's number.
+// With a matrix, z = k L itself is off by e = (ds + 1) 2^-24 |k| |L|, which is no small part of a short z where the key lies
+// along a direction that the block hardly weighs.  It moves |z - a|^2 - |z - b|^2 by 2 e |a - b|, and |a - b| is at most
+// the sum of the two distances: 4 e sqrt(d) of a difference, half of it between halves.
 //
 // What bounds it: the vector ALU, of which the ranking is 17 instructions of a lane per 16 distances; these (min,
 // med3, and_or) issue at half the rate of an add, 4 cycles a wave.  50001 keys x 32 heads x 16 subspaces,
@@ -253,11 +256,19 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
   }
 
   const float* T = MODE == A2ATS_W_NONE ? nullptr : tmat + (size_t)blk * DS * DS;
+  float t_err2 = 0.f;   // e^2 of a key of length 1
+  if (MODE == A2ATS_W_BLOCK) {
+#pragma unroll
+    for (int r = 0; r < DS; ++r)
+#pragma unroll
+      for (int t = 0; t <= r; ++t) t_err2 += T[r * DS + t] * T[r * DS + t];
+    t_err2 *= (DS + 1) * 6e-8f * scale * ((DS + 1) * 6e-8f * scale);
+  }
   const int steps = (n_mine + 63) / 64;
   const uint32_t keep = ~63u;
 #pragma unroll 1
   for (int step = 0; step < steps; ++step) {
-    float z[DS], zz = 0.f;
+    float z[DS], zz = 0.f, kk = 0.f;
     {
       const float* kp = my_keys + (size_t)min(step * 64 + lane, n_mine - 1) * D;
       float ks[DS];
@@ -279,6 +290,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
         }
         z[t] *= scale;
         zz += z[t] * z[t];
+        if (MODE == A2ATS_W_BLOCK) kk += ks[t] * ks[t];
       }
     }
     // Operands of the lane's key, then of keys 0 .. 31 (b1a, b2a) and 32 .. 63 (b1b, b2b) in both halves.
@@ -367,9 +379,14 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
       c1 = min(c1, key);
     }
     const float d1 = __uint_as_float((uint32_t)c1 & ~3u), d2 = __uint_as_float((uint32_t)c2 & ~3u);
+    float between = 3.5e-5f * q2 + 2e-5f * zz + 1e-6f, within = 1e-5f * d2 + 4e-6f * zz + 1e-30f;
+    if (MODE == A2ATS_W_BLOCK) {
+      const float e2 = t_err2 * kk;   // (the bare instruction is good to an ulp; the library's root takes as long as half a tile)
+      between += __builtin_amdgcn_sqrtf(8.f * e2 * fmaxf(q2, 0.f));
+      within += __builtin_amdgcn_sqrtf(16.f * e2 * d2);
+    }
     // (NaN anywhere: not decided)
-    const bool decided = q2 - q1 > 3.5e-5f * q2 + 2e-5f * zz + 1e-6f && d2 - d1 > 1e-5f * d2 + 4e-6f * zz + 1e-30f &&
-                         zz <= 1.2e5f && !all_near;
+    const bool decided = q2 - q1 > between && d2 - d1 > within && zz <= 1.2e5f && !all_near;
     const uint64_t near = __builtin_amdgcn_ballot_w64(!decided);
     s_code[step * 64 + lane][wave] = (uint8_t)(4 * quad + (c1 & 3));
     if (lane == 0) s_near[wave][step] = near;

@@ -203,3 +203,40 @@ def test_single_codebook_long_lists_of_undecided_keys(kv, n):
     for h in range(kv):
         c = codebook[h, 0, :2048].double()
         assert torch.equal(got[0, h], (0.5 * c.pow(2).sum(-1) - keys[0, h].double() @ c.t()).argmin(1))
+
+
+@pytest.mark.parametrize("m", [16, 32])
+@pytest.mark.parametrize("smallest", [1e-2, 1e-4, 1e-6])
+def test_codes_under_blocks_that_are_far_from_round(m, smallest):
+    """Keys about midway between two centroids, all far out along the direction that a block of H weighs least: z = k L is
+    short, but its rounding is that of |k| |L|."""
+    ds, n = 128 // m, 20000
+    g = torch.Generator(device="cuda").manual_seed(m)
+    rand = lambda *shape: torch.randn(*shape, generator=g, device="cuda", dtype=torch.float64)
+    basis = torch.linalg.qr(rand(m, ds, ds)).Q
+    weigh = torch.ones(ds, dtype=torch.float64, device="cuda")
+    weigh[0] = smallest
+    weights = (basis * weigh @ basis.transpose(-1, -2)).float()
+    weights = (0.5 * (weights + weights.transpose(-1, -2))).contiguous()
+    back = torch.linalg.inv(torch.linalg.cholesky(weights.double()))
+    # in z: clusters of four centroids (consecutive ones, and ones far apart in the codebook)
+    z = (4.0 * rand(m, 64, 1, ds) + 0.7 * rand(m, 64, 4, ds)).reshape(m, 256, ds)
+    z[:, 128:] = z[:, 128:].reshape(m, 32, 4, ds).transpose(1, 2).reshape(m, 128, ds)
+    codebook = (z @ back).float()[None].contiguous()
+    dims = B.make_dims(1, 1, 1, 128, m, n + 8)
+    at = torch.randint(0, 256, (n,), generator=g, device="cuda")
+    cluster, member = torch.where(at < 128, at // 4, at % 32), torch.where(at < 128, at % 4, (at - 128) // 32)
+    other = torch.where(at < 128, cluster * 4 + (member + 1) % 4, 128 + cluster + 32 * ((member + 1) % 4))
+    keys = 0.5 * (codebook[0][:, at].double() + codebook[0][:, other].double()) + 1e-4 * rand(m, n, ds) @ back
+    keys = keys.float().permute(1, 0, 2).reshape(1, 1, n, 128).contiguous()
+    got = _encode(dims, keys, codebook, weights[None].contiguous(), B.W_BLOCK, n + 8, m)
+    wrong = 0
+    for first in range(0, n, 5000):
+        part = keys[:, :, first:first + 5000]
+        dist = _distortions(part, codebook, weights[None], B.W_BLOCK)
+        best = dist.min(-1).values
+        mine = dist.gather(-1, got[:, :, first:first + 5000, :, None])[..., 0]
+        # (the definition's own rounding: terms of |k - c|^2)
+        far = (part.double().reshape(1, 1, -1, m, ds) - codebook[0].double()[torch.arange(m, device="cuda"), got[:, :, first:first + 5000]]).pow(2).sum(-1)
+        wrong += int((mine - best > 1e-13 * ds * far).sum())
+    assert wrong == 0

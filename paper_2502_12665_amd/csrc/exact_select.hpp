@@ -133,10 +133,17 @@ __device__ void exact_select_block(const SeqCodes& seq_codes,
   __syncthreads();
 
   const int lo = sr.sink_end, hi = sr.win_start;
-  uint32_t kth = 0, k_rem = (uint32_t)sr.kk;
+  uint32_t kth = 0, k_rem = (uint32_t)sr.kk;   // kth: relative
   // Radix digits are taken from key - key(lower bound of any score), so that the histogram bins
   // spread over the occupied range instead of all keys sharing their leading bits.
-  const uint32_t k_lo = score_key(s_lo);
+  // Relative keys are compared in the bits that the histograms look at.  For a table of finite numbers those are all that
+  // they have; with an infinite query the entries saturate and their sums wrap, and then this is what makes every level
+  // and the emission agree on one order, so that exactly kk winners are written whatever it is worth.
+  const uint32_t k_lo = score_key(s_lo), range = score_key(s_hi) - k_lo;
+  const uint32_t in_range = range == 0u ? 0u : ~0u >> __clz(range);
+  auto relative_key = [&](int j) {
+    return (score_key(score_exact_row<M>(row_ptr<M>(seq_codes, j), tbl, sw)) - k_lo) & in_range;
+  };
   // Up to kKeep rows per thread (16384 candidates: every shape that takes this route for its length)
   // are scored once and their relative keys kept in registers; the select levels and the emission
   // then work on those instead of streaming and scoring the rows again (4 passes at 4096 tokens:
@@ -148,11 +155,11 @@ __device__ void exact_select_block(const SeqCodes& seq_codes,
 #pragma unroll
     for (int i = 0; i < kKeep; ++i) {
       const int j = lo + tid + i * NT;
-      keys[i] = j < hi ? score_key(score_exact_row<M>(row_ptr<M>(seq_codes, j), tbl, sw)) - k_lo : 0u;
+      keys[i] = j < hi ? relative_key(j) : 0u;
     }
   }
   if (sr.kk < sr.ncand) {
-    int remaining = 32 - __clz(score_key(s_hi) - k_lo);   // significant bits of a relative key
+    int remaining = 32 - __clz(range);   // significant bits of a relative key
     uint32_t prefix = 0, mask = 0;
 #pragma unroll 1
     while (remaining > 0) {
@@ -167,7 +174,7 @@ __device__ void exact_select_block(const SeqCodes& seq_codes,
           if (lo + tid + i * NT < hi && (keys[i] & mask) == prefix) atomicAdd(&L.hist[(keys[i] >> shift) & dmask], 1u);
       } else {
         for (int j = lo + tid; j < hi; j += NT) {
-          const uint32_t key = score_key(score_exact_row<M>(row_ptr<M>(seq_codes, j), tbl, sw)) - k_lo;
+          const uint32_t key = relative_key(j);
           if ((key & mask) == prefix) atomicAdd(&L.hist[(key >> shift) & dmask], 1u);
         }
       }
@@ -208,19 +215,17 @@ __device__ void exact_select_block(const SeqCodes& seq_codes,
         __syncthreads();   // L.res is rewritten by the caller's next use
       }
     }
-    kth = prefix + k_lo;
+    kth = prefix;
   }
 
   // Ordered emission: keys above the K-th, plus the first k_rem positions that equal it.
   uint32_t eq_seen = 0, out_n = 0;
   const bool take_all = sr.kk >= sr.ncand;
-  auto emit_round = [&](int base, bool have_key, uint32_t rel_key, bool& done) {
+  auto emit_round = [&](int base, bool& done) {
     const int j = base + tid;
-    int32_t s = 0;
-    uint32_t gt = 0, eq = 0;
+    uint32_t key = 0, gt = 0, eq = 0;
     if (j < hi) {
-      s = have_key ? key_score(rel_key + k_lo) : score_exact_row<M>(row_ptr<M>(seq_codes, j), tbl, sw);
-      const uint32_t key = score_key(s);
+      key = relative_key(j);
       gt = take_all ? 1u : (key > kth ? 1u : 0u);
       eq = take_all ? 0u : (key == kth ? 1u : 0u);
     }
@@ -231,7 +236,7 @@ __device__ void exact_select_block(const SeqCodes& seq_codes,
     if (sel) {
       const uint32_t pos = out_n + ex_sel;
       out_idx[pos] = j;
-      if (out_score) out_score[pos] = (float)s * scale;
+      if (out_score) out_score[pos] = (float)key_score(key + k_lo) * scale;
     }
     eq_seen += tot_eq;
     out_n += tot_sel;
@@ -252,7 +257,7 @@ __device__ void exact_select_block(const SeqCodes& seq_codes,
     for (int i = 0; i < kKeep; ++i) {
       uint32_t own = 0;
       if (lo + tid + i * NT < hi) {
-        const uint32_t key = keys[i] + k_lo;
+        const uint32_t key = keys[i];
         own = take_all ? 1u : (key > kth ? 1u : (key == kth ? 0x10000u : 0u));
       }
       flags |= ((own & 1u) | ((own >> 16) << 1)) << (2 * i);
@@ -293,7 +298,7 @@ __device__ void exact_select_block(const SeqCodes& seq_codes,
     }
   } else {
 #pragma unroll 1
-    for (int base = lo; base < hi && !done; base += NT) emit_round(base, false, 0u, done);
+    for (int base = lo; base < hi && !done; base += NT) emit_round(base, done);
   }
 }
 

@@ -616,9 +616,10 @@ __global__ __launch_bounds__(kExactThreads) void final_select_kernel(
       uint4 w[M / 16];
 #pragma unroll
       for (int qd = 0; qd < M / 16; ++qd) w[qd] = e[qd];
-      const uint32_t key = max(score_key(score_exact<M>(w, tbl, sw)), klo) - klo;
+      // (no finite table has a key above khi: an infinite query's does, and the bins have to hold every key in its place)
+      const uint32_t key = min(max(score_key(score_exact<M>(w, tbl, sw)), klo), khi) - klo;
       c_key[i] = key;
-      atomicAdd(&L.hist[min(key >> shift1, (uint32_t)kHistBins - 1)], 1u);
+      atomicAdd(&L.hist[key >> shift1], 1u);
     }
   }
   const uint32_t kmin = klo;

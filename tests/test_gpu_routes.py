@@ -189,3 +189,38 @@ def test_attention_of_many_heads_equals_that_of_few(G, Hkv, N, K, w, n_sink, dty
     # neighbours of 8 significant bits are up to 2^-7 of themselves apart
     tol = 2.0 ** -7 if dtype == "bf16" else 4e-6
     assert ((whole - few).abs() <= tol * torch.maximum(whole.abs(), few.abs()) + 4e-6).all(), float((whole - few).abs().max())
+
+
+@pytest.mark.parametrize("Bn,G,M,N,K,n_sink", [
+    (2, 4, 16, 12000, 300, 4),        # the exact route, its keys in registers
+    (1, 4, 32, 12000, 300, 0),
+    (2, 4, 16, 40000, 4000, 4),       # without a workspace the exact route, its keys scored again and again
+    (40, 4, 16, 12000, 300, 4),       # a workgroup per group
+    (2, 4, 16, 60000, 1500, 4),       # the streaming route
+])
+@pytest.mark.parametrize("bad", ["inf", "nan", "huge"])
+def test_queries_that_are_not_finite_select_within_their_rows(Bn, G, M, N, K, n_sink, bad):
+    """Table entries of an infinite query saturate and their sums wrap.  What is selected then means nothing, but it is K'
+    ascending candidates per head, and nothing is written anywhere else."""
+    wl = synth.Workload("bad", Bn, 2 * G, 2, 128, M, N, K, 64, n_sink=n_sink, seed=N + K)
+    xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
+    q = xd["q"].float()
+    if bad == "huge":
+        q *= 3e38
+    else:
+        q[:, ::2, 5] = float(bad)
+        q[:, 1, 64:] = -float(bad)
+        q[-1, -1, ::3] = float(bad)
+    dims = H.dims_of(wl)
+    st = B.DecodeState(dims, K, 64, n_sink, torch.float32, xd["inv_freq"], wl.wrope_b)
+    heads = Bn * 2 * G
+    idx = torch.full((heads * K + N,), -7, dtype=torch.int32, device="cuda")
+    score = torch.full((heads * K + N,), -7.0, device="cuda")
+    B.build_lut(dims, q, st.cos_b, st.sin_b, xd["codebook"], st.q_rot, st.lut, st.lut_scale)
+    for ws in (st.ws, None) if K > 2048 else (st.ws,):
+        B.score_topk(dims, xd["codes"], st.lut, st.lut_scale, K, 64, n_sink, None, idx, st.topk_count, score, None, ws)
+        torch.cuda.synchronize()
+        assert (idx[heads * K:] == -7).all() and (score[heads * K:] == -7.0).all()
+        assert (st.topk_count == K).all()
+        got = idx[:heads * K].view(heads, K)
+        assert (got[:, 1:] > got[:, :-1]).all() and (got >= n_sink).all() and (got < N - 64).all()

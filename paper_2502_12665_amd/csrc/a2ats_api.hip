@@ -195,8 +195,8 @@ int a2ats_second_moment(const a2ats_dims* d, const float* q_rot, int64_t n_sampl
   if (rc != A2ATS_OK) return rc;
   if (n_samples < 0 || !h_out || (n_samples > 0 && !q_rot)) return A2ATS_ERR_INVALID_ARG;
   if (misaligned16(q_rot)) return A2ATS_ERR_INVALID_ARG;
-  if (!ws || misaligned16(ws) || ws_bytes < a2ats::fit_ws_bytes(*d)) return A2ATS_ERR_WORKSPACE;
-  const hipError_t e = a2ats::launch_second_moment(*d, q_rot, n_samples, h_out, ws, (hipStream_t)stream);
+  if (!ws || misaligned16(ws) || ws_bytes < a2ats::fit_ws_least_bytes(*d)) return A2ATS_ERR_WORKSPACE;
+  const hipError_t e = a2ats::launch_second_moment(*d, q_rot, n_samples, h_out, ws, ws_bytes, (hipStream_t)stream);
   return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
 }
 
@@ -208,9 +208,9 @@ int a2ats_codebook_update(const a2ats_dims* d, const float* keys, int32_t n_new,
   if (n_new < 0 || pos0 < 0 || (int64_t)pos0 + n_new > d->ctx_stride) return A2ATS_ERR_INVALID_ARG;
   if (!codebook || !codebook_out || (n_new > 0 && (!keys || !codes))) return A2ATS_ERR_INVALID_ARG;
   if (misaligned16(keys)) return A2ATS_ERR_INVALID_ARG;
-  if (!ws || misaligned16(ws) || ws_bytes < a2ats::fit_ws_bytes(*d)) return A2ATS_ERR_WORKSPACE;
+  if (!ws || misaligned16(ws) || ws_bytes < a2ats::fit_ws_least_bytes(*d)) return A2ATS_ERR_WORKSPACE;
   const hipError_t e = a2ats::launch_codebook_update(*d, keys, n_new, pos0, codes, codebook, codebook_out, counts,
-                                                     ws, (hipStream_t)stream);
+                                                     ws, ws_bytes, (hipStream_t)stream);
   return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
 }
 

@@ -29,7 +29,7 @@ constexpr int kFD = 128;
 constexpr int kMomentTiles = 36;   // 16 x 16 tiles on and above the diagonal of 128 x 128
 constexpr int kMomentRows = 16;    // sample rows a wave has in flight
 
-// Partial sums per KV head: two workgroups per CU over all heads.
+// Partial sums per KV head: two workgroups per CU over all heads, as far as the workspace holds them.
 inline int moment_parts(int Hkv) { return Hkv < 8 ? 512 / Hkv : 64; }
 
 struct MomentPlan {
@@ -326,8 +326,10 @@ __global__ __launch_bounds__(256) void update_mean_kernel(const double* __restri
 }  // namespace
 
 struct FitWs {
-  size_t off_counts, off_cursor, off_rank, off_order, bytes;   // of the update; its sums come first
+  size_t off_counts, off_cursor, off_rank, off_order, update_bytes;   // of the update; its sums come first
+  size_t bytes;
 };
+constexpr size_t kMomentPart = kMomentTiles * 256 * sizeof(double);   // a partial sum of the second moment
 static FitWs fit_ws(const a2ats_dims& d) {
   const size_t cws = (size_t)d.n_kv_heads * d.n_sub * d.n_centroids;
   size_t o = 0;
@@ -343,20 +345,28 @@ static FitWs fit_ws(const a2ats_dims& d) {
   w.off_cursor = take(single ? cws * sizeof(uint32_t) : 0);
   w.off_rank = take(single ? (size_t)d.batch * d.n_kv_heads * (size_t)d.ctx_stride * sizeof(uint32_t) : 0);
   w.off_order = take(single ? (size_t)d.batch * d.n_kv_heads * (size_t)d.ctx_stride * sizeof(uint2) : 0);
-  const size_t moment = (size_t)d.n_kv_heads * moment_parts(d.n_kv_heads) * kMomentTiles * 256 * sizeof(double);
+  w.update_bytes = o;
+  const size_t moment = (size_t)d.n_kv_heads * moment_parts(d.n_kv_heads) * kMomentPart;
   w.bytes = ((moment > o ? moment : o) + 255) & ~(size_t)255;
   return w;
 }
 
 size_t fit_ws_bytes(const a2ats_dims& d) { return fit_ws(d).bytes; }
 
+// What either call can do with: 113 partial sums per KV head, or the sums and counts of the update (4.3 MB at most).
+size_t fit_ws_least_bytes(const a2ats_dims& d) {
+  const size_t least = (size_t)d.n_kv_heads << 23, all = fit_ws(d).bytes;
+  return least < all ? least : all;
+}
+
 hipError_t launch_second_moment(const a2ats_dims& d, const float* q_rot, int64_t n_samples, float* h_out, void* ws,
-                                hipStream_t stream) {
+                                size_t ws_bytes, hipStream_t stream) {
   if (d.n_kv_heads == 0) return hipSuccess;
   const int G = d.n_q_heads / d.n_kv_heads;
   const long rows = (long)n_samples * G;   // (512 bytes each: fewer than 2^32 fit the card)
   // at least 64 rows a workgroup: the partials are 72 KB each
-  const int most = moment_parts(d.n_kv_heads);
+  const long held = (long)(ws_bytes / kMomentPart) / d.n_kv_heads, wanted = moment_parts(d.n_kv_heads);
+  const long most = held < wanted ? held : wanted;
   long per = (rows + most - 1) / most;
   per = ((per < 64 ? 64 : per) + kMomentRows - 1) / kMomentRows * kMomentRows;
   const int parts = (int)((rows + per - 1) / per);
@@ -372,7 +382,7 @@ hipError_t launch_second_moment(const a2ats_dims& d, const float* q_rot, int64_t
 
 hipError_t launch_codebook_update(const a2ats_dims& d, const float* keys, int n_new, int pos0, const void* codes,
                                   const float* codebook, float* codebook_out, int32_t* counts_out, void* ws,
-                                  hipStream_t stream) {
+                                  size_t ws_bytes, hipStream_t stream) {
   const size_t cws = (size_t)d.n_kv_heads * d.n_sub * d.n_centroids, n_elems = cws * d.sub_dim;
   if (n_elems == 0) return hipSuccess;
   const FitWs w = fit_ws(d);
@@ -387,7 +397,9 @@ hipError_t launch_codebook_update(const a2ats_dims& d, const float* keys, int n_
   // Few keys are added one by one: below these counts the further launches, or filling and emptying the sums in LDS,
   // cost more than the atomics they save (one by one -> otherwise, us: single codebook 16000 keys 33 -> 50, 20000 24 ->
   // 29, 80000 75 -> 51; M = 16, 8000 keys 18 -> 21, 16000 29 -> 24; M = 32, 2000 keys 13 -> 14, 8000 28 -> 15).
-  if (n_new > 0 && d.batch > 0 && n_keys < (single_codebook(d) ? 48000 : 192000 / d.n_sub)) {
+  // So are those of a single codebook whose order the workspace has no room for.
+  const bool one_by_one = n_keys < (single_codebook(d) ? 48000 : 192000 / d.n_sub) || (single_codebook(d) && ws_bytes < w.update_bytes);
+  if (n_new > 0 && d.batch > 0 && one_by_one) {
     const dim3 grid((n_new + 1) / 2, bkv);
     if (single_codebook(d))
       hipLaunchKernelGGL(update_few_kernel<uint16_t>, grid, dim3(256), 0, stream, keys, (const uint16_t*)codes, sums,

@@ -138,12 +138,13 @@ hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_ne
 size_t kmeanspp_ws_bytes(const a2ats_dims& d);
 hipError_t launch_kmeanspp_seed(const a2ats_dims& d, const float* keys, int n_new, const float* weights, int mode,
                                 const double* u, float* codebook_out, int32_t* picks, void* ws, hipStream_t stream);
-size_t fit_ws_bytes(const a2ats_dims& d);
+size_t fit_ws_bytes(const a2ats_dims& d);         // what the fastest forms of the two calls use,
+size_t fit_ws_least_bytes(const a2ats_dims& d);   // and what they need
 hipError_t launch_second_moment(const a2ats_dims& d, const float* q_rot, int64_t n_samples, float* h_out, void* ws,
-                                hipStream_t stream);
+                                size_t ws_bytes, hipStream_t stream);
 hipError_t launch_codebook_update(const a2ats_dims& d, const float* keys, int n_new, int pos0, const void* codes,
                                   const float* codebook, float* codebook_out, int32_t* counts_out, void* ws,
-                                  hipStream_t stream);
+                                  size_t ws_bytes, hipStream_t stream);
 
 // Copy freshly encoded code rows [B][Hkv][n_new][row_bytes] to tokens pos0 .. pos0 + n_new - 1 of a paged pool.
 hipError_t launch_codes_to_pages(const a2ats_dims& d, const uint8_t* rows, int n_new, int pos0, int row_bytes,

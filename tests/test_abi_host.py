@@ -76,6 +76,10 @@ def test_dims_validation_and_plans(binding):
     assert rc == -1                                                     # weighted mode without weights
     rc = L.a2ats_encode_keys(ctypes.byref(small), one, 4, 0, one, one, 2, one, null, 0, null)
     assert rc == -3
+    fit = binding.make_dims(4, 32, 8, 128, 1, 100000, n_centroids=4096)   # 8 MiB per KV head are enough, a byte less is not
+    assert binding.workspace_bytes(fit, binding.OP_FIT) > 8 << 23
+    assert L.a2ats_second_moment(ctypes.byref(fit), one, 10, one, one, (8 << 23) - 1, null) == -3
+    assert L.a2ats_codebook_update(ctypes.byref(fit), one, 10, 0, one, one, one, null, one, (8 << 23) - 1, null) == -3
     rc = L.a2ats_sparse_attn(ctypes.byref(small), one, one, one, one, 3, one, one, 8, 4, 0, one, one, null,
                              one, null, 0, null)
     assert rc == -1                                                     # unknown dtype

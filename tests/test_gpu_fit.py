@@ -7,10 +7,17 @@ from paper_2502_12665_amd import binding as B
 pytestmark = pytest.mark.gpu
 
 
+def _workspace(dims, least):
+    """What the fastest forms ask for, or no more than the 8 MiB per KV head that any size of call can do with."""
+    n = B.workspace_bytes(dims, B.OP_FIT)
+    return torch.empty(min(n, dims.n_kv_heads << 23) if least else n, dtype=torch.uint8, device="cuda")
+
+
 @pytest.mark.parametrize("m", [1, 16, 32])
+@pytest.mark.parametrize("least", [False, True])
 @pytest.mark.parametrize("batch,kv,n,skew", [(1, 1, 1, False), (2, 3, 63, False), (1, 2, 4097, True), (3, 8, 2050, False),
-                                             (1, 1, 50001, True)])
-def test_codebook_update(m, batch, kv, n, skew):
+                                             (1, 1, 50001, True), (12, 1, 60000, False)])
+def test_codebook_update(m, least, batch, kv, n, skew):
     L, ds, stride, pos0 = (4096, 128, n + 9, 5) if m == 1 else (256, 128 // m, n + 9, 5)
     g = torch.Generator(device="cuda").manual_seed(n + m)
     keys = torch.randn(batch, kv, n, 128, generator=g, device="cuda")
@@ -22,7 +29,7 @@ def test_codebook_update(m, batch, kv, n, skew):
     out = torch.full_like(codebook, float("nan"))
     counts = torch.full((kv, m, L), -1, dtype=torch.int32, device="cuda")
     dims = B.make_dims(batch, kv, kv, 128, m, stride, n_centroids=L)
-    ws = torch.empty(B.workspace_bytes(dims, B.OP_FIT), dtype=torch.uint8, device="cuda").fill_(0xA5)
+    ws = _workspace(dims, least).fill_(0xA5)
     B.codebook_update(dims, keys, n, pos0, codes.to(torch.int16 if m == 1 else torch.uint8), codebook, out, counts, ws)
     torch.cuda.synchronize()
     used = codes[:, :, pos0:pos0 + n]
@@ -40,12 +47,13 @@ def test_codebook_update(m, batch, kv, n, skew):
     assert ((out.double() - want).abs() <= 1.2e-7 * want.abs() + 1e-12).all()
 
 
-@pytest.mark.parametrize("heads,kv,n", [(8, 1, 1), (5, 1, 13), (6, 2, 1025), (7, 1, 4800), (24, 3, 3001), (64, 64, 40)])
-def test_second_moment_shares(heads, kv, n):
+@pytest.mark.parametrize("heads,kv,n", [(8, 1, 1), (5, 1, 13), (6, 2, 1025), (7, 1, 4800), (24, 3, 3001), (64, 64, 40), (8, 1, 4096)])
+@pytest.mark.parametrize("least", [False, True])
+def test_second_moment_shares(heads, kv, n, least):
     g = torch.Generator(device="cuda").manual_seed(n)
     q = torch.randn(n, heads, 128, generator=g, device="cuda") * torch.linspace(0.1, 4.0, 128, device="cuda")
     dims = B.make_dims(1, heads, kv, 128, 16, 64)
-    ws = torch.empty(B.workspace_bytes(dims, B.OP_FIT), dtype=torch.uint8, device="cuda").fill_(0xFF)   # (NaN)
+    ws = _workspace(dims, least).fill_(0xFF)   # (NaN)
     out = torch.full((kv, 128, 128), float("nan"), device="cuda")
     B.second_moment(dims, q, n, out, ws)
     torch.cuda.synchronize()

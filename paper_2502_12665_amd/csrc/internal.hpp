@@ -32,7 +32,6 @@ struct TopkPlan {
 struct AttnPlan {
   int n_far;            // workgroups sharing the sinks and retrieved rows of one head
   int n_win;            // workgroups sharing its window rows
-  bool whole;           // one workgroup takes all rows of a head (per-head selections)
   size_t bytes;
 };
 

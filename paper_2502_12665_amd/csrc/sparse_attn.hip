@@ -11,6 +11,7 @@
 // triples a second small kernel merges.  With one selection per KV head (the shared variant) the
 // far rows are the same for the G heads of a KV head and q~ K^T is a thin matrix product: that case
 // (bf16 caches) goes through the matrix cores, see attn_shared_mfma_kernel.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -40,13 +41,28 @@ AttnPlan make_attn_plan(const a2ats_dims& d, int top_k, int window, int n_sink) 
   p.n_far = (int)nf;
   p.n_win = (int)nw;
   p.bytes = (size_t)heads * (nf + nw) * (kD + 2) * sizeof(float);
-  // Heads that fill the CUs twice over by themselves, or once with at most a staged tile of far rows: one workgroup
-  // takes all rows of a head and writes its output, and nothing is left to merge.  64 sequences x 32 heads, 491 + 64
-  // rows: 112 us and 5 for the merge -> 105.  Steps, split and merged -> whole: 896 heads, 2048 + 128 rows 304.5 ->
-  // 299.1 us; 512 heads, 1024 + 128 109.3 -> 106.5, 240 + 64 45.9 -> 43.5; 384 heads, 480 + 64 55.8 -> 53.9, 2048 + 128
-  // 158.4 -> 161.1; 256 heads, 400 + 128 52.8 -> 51.9, 1475 + 64 91.3 -> 92.0.
-  p.whole = heads >= 512 || (heads >= 256 && (long)n_sink + top_k <= kAttnTile);
   return p;
+}
+
+// Whether one workgroup takes all rows of a head and writes its output, so that nothing is left to merge: a launch less, but
+// rows that are not shared out.  Per-head selections of 256 heads or more; us, split and merged -> whole:
+//   - few rows a head, where the launch is what counts: 256 heads, bf16, 128 + 64 rows 12.8 -> 10.3, 384 + 128 16.0 -> 14.8,
+//     but 128 + 512 17.9 -> 21.9 (a window row costs a rotation, and the split shares them out the most); 512 heads, 192 +
+//     256 rows 22.0 -> 19.4, 128 + 512 26.8 -> 25.4; float32, 384 heads, 256 + 128 rows 26.9 -> 23.9, 896 heads, 256 + 64 39.4
+//     -> 41.1;
+//   - so many heads that they even out among the CUs: 1152 heads, bf16, 2048 + 64 rows 167 -> 151, 508 + 256 66 -> 64, but
+//     256 + 256 3 to 7 % slower; from 1280 on the window hardly matters;
+//   - fewer, where they fill the rounds of the CUs and the window is a small part: 512 heads, bf16, 2048 + 64 rows 72.6 ->
+//     64.4, 896 heads 127 -> 122, but 576 heads 85.0 -> 87.3, and 832 heads with 508 + 128 rows 37.0 -> 41.6.
+static bool attn_whole(const a2ats_dims& d, int top_k, int window, int n_sink, bool bf16) {
+  const long heads = (long)d.batch * d.n_q_heads;
+  if (heads < 256) return false;
+  const long far_rows = std::min<long>((long)n_sink + top_k, d.ctx_len), rows = far_rows + std::min(window, d.ctx_len);
+  if (heads < 512) return (window <= 128 && rows <= (bf16 ? 512 : 384)) || (bf16 && rows <= 320);
+  if (bf16 ? (window <= 256 && rows <= 448) || (window <= 512 && far_rows <= 128) : window <= 128 && rows <= 192) return true;
+  if (heads >= 1000) return window <= (heads < 1280 ? 128 : (bf16 ? 512 : 256)) || far_rows >= std::max(768, window);
+  const long full = heads * 100 / ((heads + 255) / 256 * 256);   // of the rounds, in percent
+  return heads >= (bf16 ? 512 : 768) && full >= 87 && window <= std::max<long>(64, far_rows / (full >= 90 ? 4 : 16));
 }
 
 // A lane's 16-byte piece of a row, kept as loaded (so that rows in flight cost four registers
@@ -646,7 +662,7 @@ static hipError_t launch_attn_t(const a2ats_dims& d, const AttnPlan& plan, const
                          (const uint16_t*)k_cache, (const uint16_t*)v_cache, topk_idx, topk_count, cos_win, sin_win,
                          seq_lens, (float*)ws, d.n_q_heads, d.n_kv_heads, d.ctx_len, d.ctx_stride, top_k, window,
                          n_sink, plan.n_far, plan.n_win, page_table, page_shift, pages_per_seq, problems);
-  } else if (!shared && plan.whole) {
+  } else if (!shared && attn_whole(d, top_k, window, n_sink, std::is_same<T, uint16_t>::value)) {
     hipLaunchKernelGGL((attn_whole_kernel<T>), dim3(heads), dim3(kAttnThreads), 0, stream, (const T*)q, q_rot,
                        (const T*)k_cache, (const T*)v_cache, topk_idx, topk_count, cos_win, sin_win, seq_lens, (float*)ws,
                        d.n_q_heads, d.n_kv_heads, d.ctx_len, d.ctx_stride, top_k, window, n_sink, plan.n_far, plan.n_win,

@@ -139,9 +139,12 @@ def test_short_decode_select_equals_the_separate_calls(Bn, Hkv, G, M, N, K, w, n
     (7, 4, 1300, 600, 256, 0, "bf16", 16, False),                        # more rows than a staged tile; two windows' worth
     (4, 8, 300, 0, 64, 0, "f32", 0, True),                               # the window alone
     (8, 4, 513, 200, 0, 4, "f32", 64, True),                             # no window
+    (8, 4, 1300, 600, 128, 0, "bf16", 16, True),
+    (8, 4, 1300, 600, 128, 4, "f32", 0, False),
 ])
 def test_attention_of_many_heads_equals_that_of_few(G, Hkv, N, K, w, n_sink, dtype, page, ragged):
-    """From 512 heads on a workgroup takes a whole head; the same sequences four at a time take the split route."""
+    """Of many heads a workgroup takes a whole one (all cases but that with 256 window rows); the same sequences four at a
+    time take the split route."""
     Bn = 40
     wl = synth.Workload("many", Bn, G * Hkv, Hkv, 128, 16, N, K, w, n_sink=n_sink, kv_dtype=dtype, seed=N)
     xd = synth.make_decode_inputs(wl, device="cuda")

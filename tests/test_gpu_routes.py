@@ -227,3 +227,39 @@ def test_queries_that_are_not_finite_select_within_their_rows(Bn, G, M, N, K, n_
         assert (st.topk_count == K).all()
         got = idx[:heads * K].view(heads, K)
         assert (got[:, 1:] > got[:, :-1]).all() and (got >= n_sink).all() and (got < N - 64).all()
+
+
+@pytest.mark.parametrize("N,K,w,n_sink", [(700, 100, 64, 4), (700, 508, 100, 0), (5000, 4096, 64, 4), (1500, 1000, 0, 0), (900, 0, 230, 0)])
+def test_float32_attention_of_many_heads_is_as_exact_as_that_of_few(N, K, w, n_sink):
+    """The same four sequences among 40 (a workgroup takes a whole head) and alone (its rows are shared out), against
+    float64: errors of rounding only, and of the same size."""
+    Bn, Hkv, G, n = 40, 4, 8, 4
+    wl = synth.Workload("exact", Bn, Hkv * G, Hkv, 128, 16, N, K, w, n_sink=n_sink, kv_dtype="f32", seed=N)
+    xd = synth.make_decode_inputs(wl, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(N)
+    idx = torch.rand(Bn, Hkv * G, N - w - n_sink, generator=g, device="cuda").topk(max(K, 1), -1).indices
+    idx = (torch.sort(idx, -1).values + n_sink).to(torch.int32).contiguous()
+    count = torch.full((Bn, Hkv * G), K, dtype=torch.int32, device="cuda")
+    outs = []
+    for take in (Bn, n):
+        st = B.DecodeState(H.dims_of(wl.replace(batch=take)), K, w, n_sink, torch.float32, xd["inv_freq"], wl.wrope_b)
+        B.sparse_attn(st.dims, xd["q"][:take], xd["q"][:take], xd["k"][:take], xd["v"][:take], idx[:take], count[:take], K, w,
+                      n_sink, st.cos_win, st.sin_win, None, st.out, st.ws)
+        torch.cuda.synchronize()
+        outs.append(st.out[:n].double())
+    back = torch.arange(w - 1, -1, -1, device="cuda")
+    cos, sin = st.cos_win.double()[back], st.sin_win.double()[back]
+    err, size = [0.0, 0.0], 0.0
+    for b in range(n):
+        for h in range(Hkv * G):
+            k, v, q = xd["k"][b, h // G].double(), xd["v"][b, h // G].double(), xd["q"][b, h].double()
+            far = torch.cat([torch.arange(n_sink, device="cuda"), idx[b, h, :K].long()])
+            turned = torch.cat([q[:64] * cos - q[64:] * sin, q[64:] * cos + q[:64] * sin], 1)
+            logit = torch.cat([k[far] @ q, (turned * k[N - w:]).sum(1)]) * 128 ** -0.5
+            want = torch.softmax(logit, 0) @ torch.cat([v[far], v[N - w:]])
+            size += float(want.pow(2).sum())
+            for i, o in enumerate(outs):
+                err[i] += float((o[b, h] - want).pow(2).sum())
+    whole, few = (err[0] / size) ** 0.5, (err[1] / size) ** 0.5
+    H.log(f"float32 attention, {K} + {w} rows: error {whole:.3e} whole, {few:.3e} shared out")
+    assert whole <= 1.1 * few and few < 4e-7

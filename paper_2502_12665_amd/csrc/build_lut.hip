@@ -9,6 +9,8 @@
 // a2ats.h): the exact 32-bit fixed-point table [c][m], a 16-bit coarse copy of it interleaved
 // over the four heads of the group [c][m][4] for the streaming kernel, and the numbers that
 // relate them (sum of the per-subspace minima, shift, sum of the per-subspace maxima).
+#include <algorithm>
+
 #include "common.hpp"
 #include "internal.hpp"
 #include "encode_few.hpp"
@@ -18,6 +20,7 @@
 namespace a2ats {
 
 constexpr int kLutThreads = 1024;
+constexpr uint32_t kWriteCommon = 1u << kHeadsPerGroup, kWriteAll = 2 * kWriteCommon - 1;
 
 // SHARED: one table per KV head, built from the sum of the rotated queries of its G heads (the
 // group's summed score sum_g q~_g . c equals (sum_g q~_g) . c); the rotated queries themselves
@@ -27,9 +30,9 @@ __device__ __forceinline__ void build_lut_body(
     int prob, const void* __restrict__ q_in, const float* __restrict__ cos_b,
     const float* __restrict__ sin_b, const float* __restrict__ codebook, float* __restrict__ q_rot,
     int32_t* __restrict__ lut, float* __restrict__ lut_scale, int B, int Hq, int Hkv, int NG,
-    bool write_out = true, unsigned char* coarse_lds = nullptr) {
-  // write_out false: the tables are computed but nothing is written to global memory (another
-  // workgroup does that); coarse_lds: the group's coarse table is also put there, in the layout the
+    uint32_t write = kWriteAll, unsigned char* coarse_lds = nullptr) {
+  // write: what goes to global memory, where other workgroups write the rest: bit r the exact table of head r of the
+  // group, its constants and its scale, kWriteCommon the coarse table and the rotated queries; coarse_lds: the group's coarse table is also put there, in the layout the
   // scoring kernels read (one 256-byte row per centroid id).
   constexpr int D = 128, HALF = 64, M = D / DS;
   constexpr int ENTRIES = kCentroids * M;
@@ -87,7 +90,7 @@ __device__ __forceinline__ void build_lut_body(
       const double c = (double)cos_b[t], s = (double)sin_b[t];
       o1 = (float)(x1 * c - x2 * s);
       o2 = (float)(x2 * c + x1 * s);
-      if (write_out) {
+      if (write & kWriteCommon) {
         q_rot[base + t] = o1;
         q_rot[base + t + HALF] = o2;
       }
@@ -169,7 +172,7 @@ __device__ __forceinline__ void build_lut_body(
   }
   if (tid < kHeadsPerGroup) {
     const int hg = g4 * kHeadsPerGroup + tid;
-    if (hg < G && write_out) lut_scale[(size_t)b * Hq + kv * G + hg] = (float)ldexp(1.0, -s_exp[tid]);
+    if (hg < G && ((write >> tid) & 1u)) lut_scale[(size_t)b * Hq + kv * G + hg] = (float)ldexp(1.0, -s_exp[tid]);
   }
 
   // --- exact fixed-point entries; per-(subspace, head) minimum and maximum over the centroids
@@ -207,7 +210,7 @@ __device__ __forceinline__ void build_lut_body(
     while ((range >> sh) > (uint32_t)MAXQ) ++sh;
     s_shift[r] = sh;
     const int hg = g4 * kHeadsPerGroup + r;
-    if (hg < G && write_out) {
+    if (hg < G && ((write >> r) & 1u)) {
       int32_t* meta = lut + lay.off_meta + ((size_t)b * Hq + kv * G + hg) * 4;
       meta[0] = base;   // sum over subspaces of the smallest entry
       meta[1] = sh;     // coarse entry = (exact entry - subspace minimum) >> sh
@@ -219,7 +222,7 @@ __device__ __forceinline__ void build_lut_body(
 #pragma unroll
   for (int r = 0; r < kHeadsPerGroup; ++r) {
     const int hg = g4 * kHeadsPerGroup + r;
-    if (hg < G && write_out) {
+    if (hg < G && ((write >> r) & 1u)) {
       int32_t* ex = lut + lay.off_exact + ((size_t)b * Hq + kv * G + hg) * ENTRIES;
 #pragma unroll
       for (int k = 0; k < EPT; ++k) ex[tid + k * kLutThreads] = iv[k][r];
@@ -238,7 +241,7 @@ __device__ __forceinline__ void build_lut_body(
       const uint32_t q0 = (uint32_t)(iv[k][0] - mn0) >> sh0, q1 = (uint32_t)(iv[k][1] - mn1) >> sh1;
       const uint32_t q2 = (uint32_t)(iv[k][2] - mn2) >> sh2, q3 = (uint32_t)(iv[k][3] - mn3) >> sh3;
       const uint2 entry = make_uint2(q0 | (q1 << 16), q2 | (q3 << 16));
-      if (write_out) coarse[(m >> 4) * (kCentroids * 16) + c * 16 + (m & 15)] = entry;
+      if (write & kWriteCommon) coarse[(m >> 4) * (kCentroids * 16) + c * 16 + (m & 15)] = entry;
       if (coarse_lds) store_coarse_lds<M>(coarse_lds, c, m, entry);
     }
   }
@@ -326,7 +329,7 @@ __global__ __launch_bounds__(kLutThreads) void decode_select_prologue_kernel(
     int prob, p;
     xcd_map_sets(blockIdx.x, P0, n_sample / P0, NG, prob, p);
     build_lut_body<DS, QBF16, SHARED>(prob, q_in, cos_b, sin_b, codebook, q_rot, lut, lut_scale, B, Hq, Hkv, NG,
-                                      p == 0, dyn_lds);
+                                      p == 0 ? kWriteAll : 0u, dyn_lds);
     __syncthreads();
     sample_threshold_body<M, kLutThreads, true>(prob, p, codes, CodePages{nullptr, 0, 0}, lut, seq_lens, thr, B,
                                                 SHARED ? Hkv : Hq, Hkv, NG, P0, sample_rows, ctx_len, ctx_stride,
@@ -339,13 +342,14 @@ __global__ __launch_bounds__(kLutThreads) void decode_select_prologue_kernel(
 
 // A whole a2ats_decode_select for short contexts (group_select.hpp) in one launch: a workgroup builds its
 // problem's tables, keeps the coarse one in LDS and selects from it at once.  Against the prologue and the
-// selection as two launches this saves a launch and the copy of the table.  The appended keys are encoded as in
+// selection as two launches this saves a launch and the copy of the table.  Of the `split` workgroups of a problem each
+// writes the exact tables of the heads that it selects for (it reads them back).  The appended keys are encoded as in
 // decode_prologue_kernel.
 template <int DS, bool QBF16, bool SHARED>
 __global__ __launch_bounds__(kLutThreads) void decode_select_group_kernel(
     const void* __restrict__ q_in, const float* __restrict__ cos_b, const float* __restrict__ sin_b,
     const float* __restrict__ codebook, float* __restrict__ q_rot, int32_t* __restrict__ lut,
-    float* __restrict__ lut_scale, int B, int Hq, int Hkv, int NG, int n_lut, GridMap gm,
+    float* __restrict__ lut_scale, int B, int Hq, int Hkv, int NG, int n_lut, GridMap gm, int split,
     const float* __restrict__ keys, const float* __restrict__ weights, int mode,
     uint8_t* __restrict__ codes, int n_new, int pos0, int64_t ctx_stride, int sweeps, int folded,
     const int32_t* __restrict__ seq_lens, int32_t* __restrict__ topk_idx, int32_t* __restrict__ topk_count,
@@ -357,9 +361,11 @@ __global__ __launch_bounds__(kLutThreads) void decode_select_group_kernel(
     int prob, part, b, kv, g4;
     map_block(blockIdx.x, gm, prob, part);
     split_problem(prob, gm, b, kv, g4);
-    build_lut_body<DS, QBF16, SHARED>(prob, q_in, cos_b, sin_b, codebook, q_rot, lut, lut_scale, B, Hq, Hkv, NG, true,
-                                      dyn_lds);
-    group_select_body<M, true>(b, kv, g4, prob, codes, CodePages{nullptr, 0, 0}, lut, lut_scale, seq_lens, topk_idx,
+    const int G = SHARED ? 1 : Hq / Hkv;
+    const uint32_t mine = group_part(part, split, min(G, kHeadsPerGroup), min(kHeadsPerGroup, G - g4 * kHeadsPerGroup));
+    build_lut_body<DS, QBF16, SHARED>(prob, q_in, cos_b, sin_b, codebook, q_rot, lut, lut_scale, B, Hq, Hkv, NG,
+                                      part == 0 ? mine | kWriteCommon : mine, dyn_lds);
+    group_select_body<M, true>(b, kv, g4, prob, mine, codes, CodePages{nullptr, 0, 0}, lut, lut_scale, seq_lens, topk_idx,
                                topk_count, topk_score, B, SHARED ? Hkv : Hq, Hkv, ctx_len, ctx_stride, top_k, window,
                                n_sink, dyn_lds);
     if (folded)
@@ -395,8 +401,10 @@ hipError_t launch_decode_select_group(const a2ats_dims& d, const float* keys, in
                                       bool shared, hipStream_t stream) {
   const int G = d.n_q_heads / d.n_kv_heads;
   const int NG = shared ? 1 : (G + kHeadsPerGroup - 1) / kHeadsPerGroup;
-  const int n_lut = d.batch * d.n_kv_heads * NG;
-  const AppendPlan ap = append_plan((long)d.batch * d.n_kv_heads * n_new * d.n_sub, n_lut);
+  const int groups = d.batch * d.n_kv_heads * NG;
+  const AppendPlan ap = append_plan((long)d.batch * d.n_kv_heads * n_new * d.n_sub, groups);
+  const int split = ap.folded ? 1 : group_split(groups, shared ? 1 : std::min(G, kHeadsPerGroup), ap.n_enc);
+  const int n_lut = groups * split;
   const dim3 grid(n_lut + ap.n_enc), block(kLutThreads);
   if (grid.x == 0) return hipSuccess;
   static LdsSlot s_lds[8][16];
@@ -408,7 +416,7 @@ hipError_t launch_decode_select_group(const a2ats_dims& d, const float* keys, in
       return err;                                                                                               \
     hipLaunchKernelGGL((decode_select_group_kernel<DS, BF, SH>), grid, block, kGroupLdsBytes, stream, q, cos_b, \
                        sin_b, codebook, q_rot, lut, lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, NG, n_lut,   \
-                       make_grid_map(1, n_lut, NG, d.n_kv_heads), keys, weights, mode, codes, n_new, pos0,      \
+                       make_grid_map(split, groups, NG, d.n_kv_heads), split, keys, weights, mode, codes, n_new, pos0, \
                        d.ctx_stride, ap.sweeps, ap.folded, seq_lens, topk_idx, topk_count, topk_score, d.ctx_len, \
                        top_k, window, n_sink);                                                                  \
   } while (0)

@@ -113,19 +113,41 @@ struct ExactLds {
   uint32_t small_key[kSmallList];
 };
 
+// One count more in hist[bin] for every lane that is `in`, where few bins hold most of a wave (what lies below the bounds,
+// above them, and the tied scores): the lanes of three bins are added up, as atomics of a wave on one address take their
+// turns.
+__device__ __forceinline__ void count_shared_bins(uint32_t* hist, uint32_t bin, bool in) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const uint64_t left = __builtin_amdgcn_ballot_w64(in);
+    if (!left) return;
+    const int leader = (int)__builtin_ctzll(left);
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)bin, leader);
+    const bool same = in && bin == first;
+    const uint32_t n = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(same));
+    if (lane_id() == leader) atomicAdd(&hist[first], n);
+    in = in && !same;
+  }
+  if (in) atomicAdd(&hist[bin], 1u);
+}
+
 // Exact top-K for one head by the whole workgroup.  `head_table` is the head's [c][m] table in
-// global memory, `meta` its four table constants, `tbl` kExactLdsBytes of LDS.  Writes
+// global memory, s_lo and s_hi bounds of any score, `tbl` kExactLdsBytes of LDS.  Writes
 // out_idx[0..kk) ascending (and out_score); the caller has written the count and the -1 padding.
 // Requires sr.kk >= 1.
-template <int M>
+// TIES: many rows are expected to have one score, and s_lo and s_hi are bounds of the K-th; out_score is not written.
+template <int M, bool TIES = false>
 __device__ void exact_select_block(const SeqCodes& seq_codes,
                                    const int32_t* __restrict__ head_table,
-                                   const int32_t* __restrict__ meta, float scale,
+                                   int32_t s_lo, int32_t s_hi, float scale,
                                    const SeqRange& sr, int32_t* __restrict__ out_idx,
                                    float* __restrict__ out_score, unsigned char* tbl, ExactLds& L) {
   constexpr int NT = kExactThreads;
   const int tid = threadIdx.x;
-  const int32_t s_lo = meta[0], s_hi = meta[2];   // bounds of any score
+  if (TIES) {   // one to either side for what lies beyond
+    s_lo = (int32_t)((uint32_t)s_lo - 1u);
+    s_hi = (int32_t)((uint32_t)s_hi + 1u);
+  }
   ExactSwizzle<M> sw;
   sw.init(tid & 63);
   __syncthreads();   // tbl may alias LDS the caller was still reading
@@ -142,7 +164,8 @@ __device__ void exact_select_block(const SeqCodes& seq_codes,
   const uint32_t k_lo = score_key(s_lo), range = score_key(s_hi) - k_lo;
   const uint32_t in_range = range == 0u ? 0u : ~0u >> __clz(range);
   auto relative_key = [&](int j) {
-    return (score_key(score_exact_row<M>(row_ptr<M>(seq_codes, j), tbl, sw)) - k_lo) & in_range;
+    const int32_t score = score_exact_row<M>(row_ptr<M>(seq_codes, j), tbl, sw);
+    return (score_key(TIES ? min(max(score, s_lo), s_hi) : score) - k_lo) & in_range;
   };
   // Up to kKeep rows per thread (16384 candidates: every shape that takes this route for its length)
   // are scored once and their relative keys kept in registers; the select levels and the emission
@@ -170,8 +193,11 @@ __device__ void exact_select_block(const SeqCodes& seq_codes,
       __syncthreads();
       if (resident) {
 #pragma unroll
-        for (int i = 0; i < kKeep; ++i)
-          if (lo + tid + i * NT < hi && (keys[i] & mask) == prefix) atomicAdd(&L.hist[(keys[i] >> shift) & dmask], 1u);
+        for (int i = 0; i < kKeep; ++i) {
+          const bool in = lo + tid + i * NT < hi && (keys[i] & mask) == prefix;
+          if (TIES) count_shared_bins(L.hist, (keys[i] >> shift) & dmask, in);
+          else if (in) atomicAdd(&L.hist[(keys[i] >> shift) & dmask], 1u);
+        }
       } else {
         for (int j = lo + tid; j < hi; j += NT) {
           const uint32_t key = relative_key(j);
@@ -187,7 +213,8 @@ __device__ void exact_select_block(const SeqCodes& seq_codes,
       remaining = shift;
       if (tid == 0) L.small_n = 0;
       __syncthreads();
-      if (resident && remaining > 0 && m_bin <= (uint32_t)kSmallList) {   // (uniform)
+      // (counting takes about 0.1 us per member, a further level 3 us)
+      if (resident && remaining > 0 && m_bin <= (uint32_t)(TIES ? 32 : kSmallList)) {   // (uniform)
         // The bin of the K-th key usually holds a handful of keys: they are listed and each member
         // counts the members above and at its own key -- the member whose range contains k_rem is the
         // K-th key.  (A crowded bin, heavy ties, goes on with the next radix level.)
@@ -236,7 +263,7 @@ __device__ void exact_select_block(const SeqCodes& seq_codes,
     if (sel) {
       const uint32_t pos = out_n + ex_sel;
       out_idx[pos] = j;
-      if (out_score) out_score[pos] = (float)key_score(key + k_lo) * scale;
+      if (!TIES && out_score) out_score[pos] = (float)key_score(key + k_lo) * scale;
     }
     eq_seen += tot_eq;
     out_n += tot_sel;
@@ -289,7 +316,7 @@ __device__ void exact_select_block(const SeqCodes& seq_codes,
         if ((f & 1u) || eq_before < k_rem) {
           const uint32_t slot = gt_before + min(eq_before, k_rem);
           out_idx[slot] = lo + tid + i * NT;
-          if (out_score) out_score[slot] = (float)key_score(keys[i] + k_lo) * scale;
+          if (!TIES && out_score) out_score[slot] = (float)key_score(keys[i] + k_lo) * scale;
         }
       }
       const uint32_t tot = L.round_tot[i];

@@ -12,15 +12,24 @@
 //     ranked among themselves, by (score, position).
 // Winners are marked in a bitmap over the positions, from which they are written in ascending order.
 //
+// Where the groups leave CUs idle, two or four workgroups share one: each scores all rows and selects for a part of the
+// heads.
+//
 // What bounds it: one workgroup per CU (the tables and 108 registers a thread), its phases one after the other.
 // At 16384 tokens, K 491: table and first rows 1.7 us (5 with all CUs asking at once), scores and histogram 12.3
 // (LDS: 16 gathers and four atomics a row), bin 0.8, winners and band 4.6, exact band 3.1, ranks 1.4, output 1.2.
 // The exact route, which served these contexts before, scores every row once per head (four times the LDS reads)
 // and needs a workgroup per head: 64 sequences of 16384 tokens, 32 heads: 187 us, and 34 us for the tables before
 // it, against 99 us for tables and selection in one launch (build_lut.hip); one sequence of 4096 tokens, 4 heads:
-// 21 us in two launches against 20 us in one.
+// 21 us in two launches against 18.5 in one.
 // Counting only rows above a floor taken from a sample, to save atomics, was slower (15.8 us for scores and
 // histogram): the branches cost more than the atomics.
+//
+// Many equal scores overflow the band's list, and such heads are redone, by the exact route between the bounds that the bin
+// gives, one after the other in their workgroup.  32 heads, M = 16, tables and selection, the exact route of earlier -> this:
+// all rows equal, one sequence of 8228 tokens 45 -> 45 us (186 with all four heads of a group in one workgroup), 16
+// sequences of 16384 132 -> 173, 64 of them 508 -> 363; 50 different rows 30 -> 31, 78 -> 104, 277 -> 170; 8 different
+// rows 58 -> 55, 66 -> 147, 238 -> 302.
 #pragma once
 #include "common.hpp"
 #include "coarse_score.hpp"
@@ -50,11 +59,24 @@ constexpr size_t kGroupWorkBytes = sizeof(GroupLds) > sizeof(ExactLds) ? sizeof(
 constexpr size_t kGroupLdsBytes = kCoarseLdsBytes + (kGroupWorkBytes + 15) / 16 * 16;
 static_assert(kExactLdsBytes <= kCoarseLdsBytes, "the exact table of a redone head takes the coarse table's place");
 
-// Called by all kGroupThreads threads of a workgroup.  dyn_lds: kGroupLdsBytes.  TABLE_IN_LDS: the caller has
+// Workgroups that share a group where CUs would be idle otherwise, a part of its heads each: all score the rows, but what
+// follows is done for fewer heads, above all where a head has to be redone.
+inline int group_split(long groups, int heads, long others) {   // heads: of a full group; others: workgroups of the launch
+  int split = 1;
+  while (split < 4 && 2 * split <= heads && groups * split * 2 + others <= 256) split *= 2;
+  return split;
+}
+// The heads (a bit each) of part `part`; n_real: how many the group has.
+__device__ __forceinline__ uint32_t group_part(int part, int split, int heads, int n_real) {
+  const int per = (heads + split - 1) / split;
+  return ((1u << per) - 1u) << (part * per) & ((1u << n_real) - 1u);
+}
+
+// Called by all kGroupThreads threads of a workgroup for the heads `mine` of its group.  dyn_lds: kGroupLdsBytes.  TABLE_IN_LDS: the caller has
 // put the group's coarse table at its start (a barrier follows here), otherwise it is copied from `lut`.
 template <int M, bool TABLE_IN_LDS>
 __device__ __forceinline__ void group_select_body(
-    int b, int kv, int g4, int prob, const uint8_t* __restrict__ codes, const CodePages& pg,
+    int b, int kv, int g4, int prob, uint32_t mine, const uint8_t* __restrict__ codes, const CodePages& pg,
     const int32_t* __restrict__ lut, const float* __restrict__ lut_scale, const int32_t* __restrict__ seq_lens,
     int32_t* __restrict__ topk_idx, int32_t* __restrict__ topk_count, float* __restrict__ topk_score, int B, int Hq,
     int Hkv, int ctx_len, int64_t ctx_stride, int top_k, int window, int n_sink, unsigned char* dyn_lds) {
@@ -64,18 +86,18 @@ __device__ __forceinline__ void group_select_body(
   GroupLds& L = *(GroupLds*)(dyn_lds + kCoarseLdsBytes);
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int G = Hq / Hkv, head0 = b * Hq + kv * G + g4 * kHeadsPerGroup;
-  const int n_real = min(kHeadsPerGroup, G - g4 * kHeadsPerGroup);   // heads of this group that exist
   const SeqRange sr = seq_range(ctx_len, seq_lens, b, window, n_sink, top_k);
   const SeqCodes seq_codes = seq_codes_of<M>(codes, pg, b, kv, Hkv, ctx_stride);
   const LutLayout lay = lut_layout(B, Hq, Hkv, M);
 
-  if (tid < n_real) topk_count[head0 + tid] = sr.kk;
-  for (int r = 0; r < n_real; ++r)
-    for (int t = sr.kk + tid; t < top_k; t += NT) {
-      topk_idx[(size_t)(head0 + r) * top_k + t] = -1;
-      if (topk_score) topk_score[(size_t)(head0 + r) * top_k + t] = 0.f;
-    }
-  if (sr.kk == 0) return;   // (uniform)
+  if (tid < kHeadsPerGroup && ((mine >> tid) & 1u)) topk_count[head0 + tid] = sr.kk;
+  for (int r = 0; r < kHeadsPerGroup; ++r)
+    if ((mine >> r) & 1u)
+      for (int t = sr.kk + tid; t < top_k; t += NT) {
+        topk_idx[(size_t)(head0 + r) * top_k + t] = -1;
+        if (topk_score) topk_score[(size_t)(head0 + r) * top_k + t] = 0.f;
+      }
+  if (sr.kk == 0 || mine == 0) return;   // (uniform)
 
   // Wave w owns chunks w n_i .. w n_i + n_i - 1 of 64 consecutive rows, so the chunks of a wave, and the waves,
   // follow each other in position.
@@ -116,30 +138,33 @@ __device__ __forceinline__ void group_select_body(
         score_coarse<M, false>(rows[q & 1][u], tbl, sw, a01[i0 + u], a23[i0 + u]);
         if (!take_all && row0 + (i0 + u) * 64 < hi) {
           const uint32_t w01 = a01[i0 + u], w23 = a23[i0 + u];
-          atomicAdd(&L.hist[0][(w01 & 0xffffu) >> 5], 1u);
-          if (n_real > 1) atomicAdd(&L.hist[0][w01 >> 21], 1u << 16);
-          if (n_real > 2) atomicAdd(&L.hist[1][(w23 & 0xffffu) >> 5], 1u);
-          if (n_real > 3) atomicAdd(&L.hist[1][w23 >> 21], 1u << 16);
+          if (mine & 1u) atomicAdd(&L.hist[0][(w01 & 0xffffu) >> 5], 1u);
+          if (mine & 2u) atomicAdd(&L.hist[0][w01 >> 21], 1u << 16);
+          if (mine & 4u) atomicAdd(&L.hist[1][(w23 & 0xffffu) >> 5], 1u);
+          if (mine & 8u) atomicAdd(&L.hist[1][w23 >> 21], 1u << 16);
         }
         if ((u & 1) || M == 32) __builtin_amdgcn_sched_barrier(0);   // 32 gathers at a time: bounds live registers
       }
     }
   }
   __syncthreads();
-  if (wv < n_real && !take_all) {
+  if (wv < kHeadsPerGroup && ((mine >> wv) & 1u) && !take_all) {
     const int bin = wave_find_bin(L.hist[wv >> 1], 16 * (wv & 1), (uint32_t)sr.kk, lane);
     if (lane == 0) L.bin[wv] = bin;
   }
   __syncthreads();
 
   // --- winners and band rows.  Lane r 16 + i collects the winners of head r in chunk i.
-  // (No coarse score is above 65520: 0xffff keeps the slots past the group's last head empty.)
+  // (No coarse score is above 65520: 0xffff keeps the slots of the other heads empty.)
   uint32_t t_lo[kHeadsPerGroup], t_hi[kHeadsPerGroup];
+  int kth_bin[kHeadsPerGroup];
 #pragma unroll
   for (int r = 0; r < kHeadsPerGroup; ++r) {
-    const int bin = take_all ? 0 : __builtin_amdgcn_readfirstlane(L.bin[min(r, n_real - 1)]);
-    t_lo[r] = r >= n_real ? 0xffffu : (take_all ? 0u : (uint32_t)max(0, (bin << 5) - M + 1));
-    t_hi[r] = r >= n_real ? 0xffffu : (take_all ? 0u : (uint32_t)min(0xffff, (bin << 5) + 32 + M));
+    const bool is_mine = (mine >> r) & 1u;
+    const int bin = take_all ? 0 : __builtin_amdgcn_readfirstlane(L.bin[r]);   // (of another head: not looked at)
+    kth_bin[r] = bin;
+    t_lo[r] = !is_mine ? 0xffffu : (take_all ? 0u : (uint32_t)max(0, (bin << 5) - M + 1));
+    t_hi[r] = !is_mine ? 0xffffu : (take_all ? 0u : (uint32_t)min(0xffff, (bin << 5) + 32 + M));
   }
   // The low half of a word is compared as 16 bits, the high half as the whole word against the threshold
   // shifted up: no extraction.
@@ -236,7 +261,7 @@ __device__ __forceinline__ void group_select_body(
   // --- winners in ascending position: head tid / 256, 64 positions per thread
   {
     const int r = tid >> 8, q = tid & 255;
-    uint64_t word = (q < kGroupWaves * n_i && r < n_real && !((redo >> r) & 1u)) ? L.won[r][q] : 0ull;
+    uint64_t word = (q < kGroupWaves * n_i && ((mine & ~redo) >> r & 1u)) ? L.won[r][q] : 0ull;
     const uint32_t n = (uint32_t)__popcll(word);
     const uint32_t inc = wave_inclusive_scan(n);
     if (lane == 63) L.wave_tot[wv] = inc;
@@ -250,27 +275,31 @@ __device__ __forceinline__ void group_select_body(
       word &= word - 1;
     }
   }
-  if (topk_score) {
-    __syncthreads();
-    for (int r = 0; r < n_real; ++r)
-      if (!((redo >> r) & 1u))
-        for (int t = tid; t < sr.kk; t += NT)
-          topk_score[(size_t)(head0 + r) * top_k + t] =
-              (float)exact_at(r, topk_idx[(size_t)(head0 + r) * top_k + t]) * lut_scale[head0 + r];
-  }
-  // --- heads with more band rows than the list holds (many equal scores): the exact route
+  // --- heads with more band rows than the list holds (many equal scores): the exact route.  The K-th coarse score is in the
+  // bin, hence the K-th score is at least the bin's lower edge, and its own row's is below the upper edge.
 #pragma unroll 1
-  for (int r = 0; r < n_real; ++r)
+  for (int r = 0; r < kHeadsPerGroup; ++r)
     if ((redo >> r) & 1u) {
       const size_t bh = (size_t)(head0 + r);
+      const int32_t* meta = lut + lay.off_meta + bh * 4;
+      const uint32_t bin = (uint32_t)(r == 0 ? kth_bin[0] : (r == 1 ? kth_bin[1] : (r == 2 ? kth_bin[2] : kth_bin[3])));
+      const int32_t base = meta[0], shift = meta[1];
       SeqCodes rows = seq_codes;
       SeqRange range = sr;
       // (else the addresses of all rows are formed before the loop, and spilled)
       asm volatile("" : "+s"(rows.base), "+s"(range.sink_end));
-      exact_select_block<M>(rows, lut + lay.off_exact + bh * (kCentroids * M), lut + lay.off_meta + bh * 4,
-                            lut_scale[bh], range, topk_idx + bh * top_k, topk_score ? topk_score + bh * top_k : nullptr,
-                            tbl, *(ExactLds*)(dyn_lds + kCoarseLdsBytes));
+      exact_select_block<M, true>(rows, lut + lay.off_exact + bh * (kCentroids * M),
+                                  (int32_t)((uint32_t)base + ((bin << 5) << shift)),
+                                  (int32_t)((uint32_t)base + (((bin << 5) + 32u + 2u * M) << shift)), 0.f, range,
+                                  topk_idx + bh * top_k, nullptr, tbl, *(ExactLds*)(dyn_lds + kCoarseLdsBytes));
     }
+  if (topk_score) {
+    __syncthreads();
+    for (int r = 0; r < kHeadsPerGroup; ++r)
+      for (int t = ((mine >> r) & 1u) ? tid : sr.kk; t < sr.kk; t += NT)
+        topk_score[(size_t)(head0 + r) * top_k + t] =
+            (float)exact_at(r, topk_idx[(size_t)(head0 + r) * top_k + t]) * lut_scale[head0 + r];
+  }
 }
 
 }  // namespace a2ats

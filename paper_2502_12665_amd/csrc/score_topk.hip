@@ -211,9 +211,10 @@ __global__ __launch_bounds__(kExactThreads) void select_exact_kernel(
   }
   if (sr.kk == 0) return;
   const LutLayout lay = lut_layout(B, Hq, Hkv, M);
+  const int32_t* meta = lut + lay.off_meta + (size_t)bh * 4;
   exact_select_block<M>(seq_codes_of<M>(codes, pg, b, kv, Hkv, ctx_stride),
-                        lut + lay.off_exact + (size_t)bh * (kCentroids * M), lut + lay.off_meta + (size_t)bh * 4,
-                        lut_scale[bh], sr, oi, os, dyn_lds, L);
+                        lut + lay.off_exact + (size_t)bh * (kCentroids * M), meta[0], meta[2], lut_scale[bh], sr, oi, os,
+                        dyn_lds, L);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -224,12 +225,14 @@ __global__ __launch_bounds__(kGroupThreads) void group_select_kernel(
     const uint8_t* __restrict__ codes, const int32_t* __restrict__ lut, const float* __restrict__ lut_scale,
     const int32_t* __restrict__ seq_lens, int32_t* __restrict__ topk_idx, int32_t* __restrict__ topk_count,
     float* __restrict__ topk_score, GridMap gm, CodePages pg, int B, int Hq, int Hkv, int ctx_len, int64_t ctx_stride,
-    int top_k, int window, int n_sink) {
+    int top_k, int window, int n_sink, int split) {
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   int prob, part, b, kv, g4;
   map_block(blockIdx.x, gm, prob, part);
   split_problem(prob, gm, b, kv, g4);
-  group_select_body<M, false>(b, kv, g4, prob, codes, pg, lut, lut_scale, seq_lens, topk_idx, topk_count, topk_score, B,
+  const int G = Hq / Hkv;
+  const uint32_t mine = group_part(part, split, min(G, kHeadsPerGroup), min(kHeadsPerGroup, G - g4 * kHeadsPerGroup));
+  group_select_body<M, false>(b, kv, g4, prob, mine, codes, pg, lut, lut_scale, seq_lens, topk_idx, topk_count, topk_score, B,
                               Hq, Hkv, ctx_len, ctx_stride, top_k, window, n_sink, dyn_lds);
 }
 
@@ -549,7 +552,7 @@ __global__ __launch_bounds__(kExactThreads) void final_select_kernel(
   __syncthreads();
   if (s_overflow || n_c > (uint32_t)cap || n_c < (uint32_t)sr.kk) {
     if (tid == 0) route[bh] = s_overflow ? 3u : (n_c > (uint32_t)cap ? 2u : 1u);   // diagnostics only
-    exact_select_block<M>(seq_codes, head_table, meta, scale, sr, oi, os, tbl, L);
+    exact_select_block<M>(seq_codes, head_table, m_base, m_top, scale, sr, oi, os, tbl, L);
     return;
   }
 
@@ -681,7 +684,7 @@ __global__ __launch_bounds__(kExactThreads) void final_select_kernel(
     const long kth_score = (long)key_score(kth + kmin);
     if (tc != INT32_MIN && kth_score < proof_bound) {
       if (tid == 0) route[bh] = 4u;
-      exact_select_block<M>(seq_codes, head_table, meta, scale, sr, oi, os, tbl, L);
+      exact_select_block<M>(seq_codes, head_table, m_base, m_top, scale, sr, oi, os, tbl, L);
       return;
     }
     if (tid == 0) route[bh] = 0u;
@@ -776,9 +779,10 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
   const bool streams = plan.fast || (plan.wide && ws);
   if (!streams && takes_group_route(d, window, n_sink)) {
     if ((err = allow_dynamic_lds(group_select_kernel<M>, kGroupLdsBytes, s_group)) != hipSuccess) return err;
-    hipLaunchKernelGGL((group_select_kernel<M>), dim3(problems), dim3(kGroupThreads), kGroupLdsBytes, stream, codes, lut,
-                       lut_scale, seq_lens, topk_idx, topk_count, topk_score, make_grid_map(1, problems, NG, Hkv), pg, B,
-                       Hq, Hkv, d.ctx_len, d.ctx_stride, top_k, window, n_sink);
+    const int split = group_split(problems, std::min(Hq / Hkv, kHeadsPerGroup), 0);
+    hipLaunchKernelGGL((group_select_kernel<M>), dim3(problems * split), dim3(kGroupThreads), kGroupLdsBytes, stream, codes,
+                       lut, lut_scale, seq_lens, topk_idx, topk_count, topk_score, make_grid_map(split, problems, NG, Hkv),
+                       pg, B, Hq, Hkv, d.ctx_len, d.ctx_stride, top_k, window, n_sink, split);
     return hipGetLastError();
   }
   if (!streams) {

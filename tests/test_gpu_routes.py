@@ -75,6 +75,10 @@ def _full_sort(wl, xd, st, seq_lens):
     (2, 2, 16, 3000, 3000, 16, 0, [3000, 700], None),                    # K above the candidates: all of them
     (1, 8, 16, 9000, 1, 64, 17, None, None),
     (1, 3, 16, 5000, 900, 64, 4, None, "patterns"),                      # ~125 equal scores: ties inside the band
+    (2, 4, 16, 8000, 1200, 64, 4, None, "few"),                          # ~2650 equal scores: more than the band's list holds
+    (33, 4, 16, 16384 + 64, 2000, 64, 0, None, "few"),
+    (9, 7, 32, 5000, 4096, 0, 4, None, "few"),
+    (3, 8, 16, 7001, 512, 0, 0, [7001, 2100, 1030], "few"),
     (2, 4, 32, 12000, 300, 64, 4, None, "equal"),
     (33, 4, 16, 16384 + 63, 491, 63, 0, None, None),                     # more heads than CUs: long ones by groups too
     (19, 7, 32, 16383, 4096, 0, 4, None, "patterns"),
@@ -86,8 +90,8 @@ def test_short_contexts_equal_a_full_sort(Bn, G, M, N, K, w, n_sink, lens, rows)
     xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
     if rows == "patterns":
         xd["codes"][:] = xd["codes"][:, :, torch.randint(0, 40, (N,), device="cuda")]
-    if rows == "equal":
-        xd["codes"][:] = xd["codes"][:, :, :1]
+    if rows in ("equal", "few"):
+        xd["codes"][:] = xd["codes"][:, :, torch.randint(0, 3 if rows == "few" else 1, (N,), device="cuda")]
     got = _select(wl, xd, lens, True)
     st = B.DecodeState(H.dims_of(wl), K, w, n_sink, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
     B.build_lut(st.dims, xd["q"], st.cos_b, st.sin_b, xd["codebook"], st.q_rot, st.lut, st.lut_scale)
@@ -103,10 +107,13 @@ def test_short_contexts_equal_a_full_sort(Bn, G, M, N, K, w, n_sink, lens, rows)
     (2, 2, 4, 16, 6000, 0, 64, 0, 1, None, False),                       # nothing to select
     (2, 2, 4, 16, 6000, 100, 1, 0, 3, None, False),                      # two of the three appended rows are candidates
 ])
-def test_short_decode_select_equals_the_separate_calls(Bn, Hkv, G, M, N, K, w, n_sink, n_new, lens, shared):
+@pytest.mark.parametrize("rows", ["random", "few", "equal"])             # (the band overflows: tables read back by their writers)
+def test_short_decode_select_equals_the_separate_calls(Bn, Hkv, G, M, N, K, w, n_sink, n_new, lens, shared, rows):
     """Append, tables and selection of a short context in one launch against the calls one after the other."""
     wl = synth.Workload("one", Bn, Hkv * G, Hkv, 128, M, N, K, w, n_sink=n_sink, seed=N)
     xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
+    if rows != "random":
+        xd["codes"][:] = xd["codes"][:, :, torch.randint(0, 3 if rows == "few" else 1, (N,), device="cuda")]
     keys = synth.make_encode_keys(wl, n_new, device="cuda", stress=True)
     weights = synth.make_query_second_moment(wl)["h_diag"].cuda()
     dims, sel = H.dims_of(wl), H.dims_of(wl.replace(n_q_heads=Hkv) if shared else wl)

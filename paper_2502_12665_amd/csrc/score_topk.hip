@@ -138,15 +138,19 @@ TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink) 
 // short contexts, where what it saves is the launch of the tables.  Steps, exact -> group route, 32 query and 8
 // KV heads: 16 sequences (two rounds) M = 16, 4096 and 16384 tokens 48.7 -> 36.1 and 78.2 -> 61.9 us, M = 32 60.1
 // -> 49.4 and 104.2 -> 91.4; 4 sequences (one round) M = 16, 4096, 8228, 16384 tokens 31.6 -> 30.0, 35.6 -> 35.2,
-// 43.9 -> 46.1, M = 32, 1500, 4096, 16384 tokens 35.1 -> 32.5, 38.9 -> 38.4, 56.2 -> 74.6.  One head per group,
-// 16 sequences: M = 16, 16384 tokens 53.5 -> 48.3, M = 32, 8228 tokens 54.2 -> 48.6.
+// 43.9 -> 46.1, M = 32, 1500, 4096, 16384 tokens 35.1 -> 32.5, 38.9 -> 38.4, 56.2 -> 74.6.  A group of one head saves
+// nothing but the launch, so the line does not move with the heads of a group (tables and selection of 16 sequences of 16
+// heads, one a group, M = 16, 16384 tokens 35.6 -> 42.1, 24 of 8 34.6 -> 37.5, M = 32, 8228 tokens 29.6 -> 30.9).  In more than one round it is lower: 64 of 8 heads, M = 16, 4096, 8228, 16384 tokens 49.4 ->
+// 45.1, 55.0 -> 56.8, 66.5 -> 77.8, M = 32, 1500, 4096, 8228 tokens 60.9 -> 59.6, 67.3 -> 69.0, 76.9 -> 84.6.
 bool takes_group_route(const a2ats_dims& d, int window, int n_sink) {
   const long ncand = (long)d.ctx_len - window - n_sink;
   if (single_codebook(d) || ncand > kGroupMaxCand) return false;
   const int G = d.n_q_heads / d.n_kv_heads;
   const long groups = (long)d.batch * d.n_kv_heads * ((G + kHeadsPerGroup - 1) / kHeadsPerGroup);
-  if (((long)d.batch * d.n_q_heads + 255) / 256 > (groups + 255) / 256) return true;
-  return ncand * std::min(G, kHeadsPerGroup) <= (d.n_sub == 16 ? 32768 : 8192);
+  const long head_rounds = ((long)d.batch * d.n_q_heads + 255) / 256, group_rounds = (groups + 255) / 256;
+  if (head_rounds > group_rounds) return true;
+  const long line = d.n_sub == 16 ? 8192 : 2048;
+  return ncand <= (head_rounds > 1 ? line * 3 / 4 : line);
 }
 
 // The P0 sampling workgroups of a problem each estimate a head's threshold from their share of the

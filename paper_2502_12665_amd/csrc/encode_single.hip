@@ -527,7 +527,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
   // same step (742 us instead of 697 for 768032 keys).
   f32x16 acc[2];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) acc[1][v] = 3e38f;   // (ranked before the first tile)
+  for (int v = 0; v < 16; ++v) acc[1][v] = 3e38f;   // (ranked before the first tile, as numbers of block 0: above any score)
 #pragma unroll 1
   for (int cb = 0; cb < kBlocks; ++cb) {
     request(cb + 1);
@@ -537,7 +537,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
       constexpr int kOne = NT == 1 ? 0 : 1;   // (a single tile is ranked after its own products)
       f32x16& now = acc[kOne * (t & 1)];
       const f32x16& done = acc[kOne * ((t + 1) & 1)];
-      const int prev = (t + NT - 1) % NT, prev_cb = t == 0 && NT > 1 ? cb - 1 : cb;
+      const int prev = (t + NT - 1) % NT, prev_cb = t == 0 && NT > 1 ? max(cb - 1, 0) : cb;
       float key[4];
 #pragma unroll
       for (int kt = 0; kt < 8; ++kt) {

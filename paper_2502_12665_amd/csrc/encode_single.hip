@@ -8,8 +8,15 @@
 // a dense [keys x 128] . [128 x 4096] contraction: 1 Mflop per key, the one matrix-core shape of
 // this library.  The kernels:
 //
+// Distortions do not change when keys and codewords are moved together, but products, whose rounding goes with |k| |w|, are
+// the larger the more all of them have in common.  So everything below is about keys and codewords less a centre of the
+// codewords, and the matrix-core operands are balanced per dimension by powers of two t: k t . w / t.  160000 keys in all,
+// 8 KV heads, all of them around 16 in every dimension: 8045 -> 381 us (nearly every key went to the float64 sweep before);
+// variances 1 and 1e4 by dimension: 1297 -> 549; around the origin 375 -> 377.
+//
 //   encode_single_factor_kernel    per KV head: L in float64 (Cholesky in LDS, or the identity /
-//                                  a diagonal for the unweighted / per-dimension modes)
+//                                  a diagonal for the unweighted / per-dimension modes); in other
+//                                  workgroups the means that the centre is taken from
 //   encode_single_heff_kernel      L L^T (full-matrix mode)
 //   encode_single_codewords_kernel c^z and w_c in float64, kept transposed for the exact decisions,
 //                                  1/2 ||c^z||^2, and the largest norms
@@ -64,9 +71,16 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 // Of a KV head, over its codewords (float bits, which order like the values).
 struct alignas(128) CodewordStat {   // (a cache line each: they are filled by atomics)
-  uint32_t w_max, c_max, bias_max;   // largest |w|, |c| and 1/2 |c^z|^2, rounded up
+  uint32_t w_max, c_max, bias_max;   // largest |w / t|, |c t| and 1/2 |c^z|^2, rounded up
   uint32_t w_err;                    // largest |w - f16(w)|, in the scaled units of the f16 operands
 };
+
+// What is subtracted from every key and codeword of a KV head, and the powers of two t.
+struct alignas(32) Center {
+  float mu[kD], key[kD], t[kD];   // (key: t by the scale of the f16 operands)
+};
+__device__ __forceinline__ float inverse_of_power(float t) { return __uint_as_float((254u << 23) - __float_as_uint(t)); }
+constexpr int kMeans = 16;   // shares of the codewords whose means the centre is the median of
 
 // Smallest three scores of a listed key over a slice of the codewords, and the codes of the first two.
 struct NearPart {
@@ -78,8 +92,8 @@ constexpr int kMaxSlices = 16;
 inline long near_groups(const a2ats_dims& d) { return d.n_kv_heads < 512 ? 512 / d.n_kv_heads : 1; }
 
 struct EncWs {
-  size_t off_L, off_sd, off_heff, off_czT, off_wT, off_chalf, off_cfrag, off_cbias, off_f16, off_fbias, off_cstat, off_count,
-      off_list, off_near, off_near_part, off_part, bytes;
+  size_t off_L, off_sd, off_heff, off_means, off_center, off_czT, off_wT, off_chalf, off_cfrag, off_cbias, off_f16,
+      off_fbias, off_cstat, off_count, off_list, off_near, off_near_part, off_part, bytes;
   size_t near_cap;   // keys of a KV head
 };
 
@@ -96,6 +110,8 @@ EncWs enc_single_ws(const a2ats_dims& d) {
   w.off_L = take(Hkv * kD * kD * sizeof(double));
   w.off_sd = take(Hkv * kD * sizeof(double));
   w.off_heff = take(Hkv * kD * kD * sizeof(double));
+  w.off_means = take(Hkv * kMeans * kD * sizeof(double));
+  w.off_center = take(Hkv * sizeof(Center));
   w.off_czT = take(Hkv * kD * kCW * sizeof(double));
   w.off_wT = take(Hkv * kD * kCW * sizeof(double));
   w.off_chalf = take(Hkv * kCW * sizeof(double));
@@ -143,8 +159,20 @@ __device__ __forceinline__ double lane_value(double v, int src_lane) {   // src_
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void encode_single_factor_kernel(
     const float* __restrict__ weights, int mode, double* __restrict__ Lmat, double* __restrict__ sd,
-    CodewordStat* __restrict__ cstat) {
+    CodewordStat* __restrict__ cstat, const float* __restrict__ codebook, double* __restrict__ means) {
   extern __shared__ double s_A[];   // 128 rows, lower triangle in use
+  if (blockIdx.y > 0) {             // the mean of one share of the codewords
+    constexpr int kRows = kCW / kMeans;
+    const int t = threadIdx.x & (kD - 1), half = threadIdx.x / kD;
+    const float* c = codebook + ((size_t)blockIdx.x * kCW + (blockIdx.y - 1) * kRows + half * (kRows / 2)) * kD + t;
+    double sum = 0.0;
+#pragma unroll 16
+    for (int r = 0; r < kRows / 2; ++r) sum += (double)c[(size_t)r * kD];
+    if (half) s_A[t] = sum;
+    __syncthreads();
+    if (!half) means[((size_t)blockIdx.x * kMeans + blockIdx.y - 1) * kD + t] = (sum + s_A[t]) * (1.0 / kRows);
+    return;
+  }
   const int kv = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   double* L = Lmat + (size_t)kv * kD * kD;
   if (tid == 0) cstat[kv] = CodewordStat{0u, 0u, 0u, 0u};
@@ -201,10 +229,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // ------------------------------------------------------------------------------------------
 // L L^T, the matrix the factor stands for (equal to H up to rounding when H is positive definite;
 // the few-key route weighs with it so that both routes minimise the same distortion).
-// One workgroup per row i: thread j sums L[i][m] L[j][m] over m.
+// One workgroup per row i: thread j sums L[i][m] L[j][m] over m.  And the norm of the row.
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kD) void encode_single_heff_kernel(const double* __restrict__ Lmat,
-                                                                double* __restrict__ heff) {
+__global__ __launch_bounds__(kD) void encode_single_heff_kernel(const double* __restrict__ Lmat, double* __restrict__ heff,
+                                                                double* __restrict__ row_norm) {
+  __shared__ double s_n[kD / 64];
   const int kv = blockIdx.y, i = blockIdx.x, j = threadIdx.x;
   const double* L = Lmat + (size_t)kv * kD * kD;
   double s0 = 0.0, s1 = 0.0;
@@ -216,28 +245,71 @@ __global__ __launch_bounds__(kD) void encode_single_heff_kernel(const double* __
   }
   if (m < m_end) s0 += L[(size_t)i * kD + m] * L[(size_t)j * kD + m];
   heff[((size_t)kv * kD + i) * kD + j] = s0 + s1;
+  double n = (s0 + s1) * (s0 + s1);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) n += __shfl_xor(n, off);
+  if ((j & 63) == 0) s_n[j >> 6] = n;
+  __syncthreads();
+  if (j == 0) row_norm[(size_t)kv * kD + i] = sqrt(s_n[0] + s_n[1]);
 }
 
 // ------------------------------------------------------------------------------------------
-// c^z = c L and w = c (L L^T) in float64, and the largest norms.  A wave takes 16 codewords and all dimensions, on the
-// float64 matrix cores: the matrix is the first operand (a row of the result is a dimension), the codewords the second
+// c^z = c L and w = c (L L^T) in float64, c less the centre, and the largest norms.  A wave takes 16 codewords and all
+// dimensions, on the float64 matrix cores: the matrix is the first operand (a row of the result is a dimension), the codewords the second
 // (a column is a codeword), so a lane's results belong to one codeword and are written to consecutive addresses.
-// 8 KV heads, full matrix: 99 -> 44 us (a thread per codeword and 32 dimensions before).
+// 8 KV heads, full matrix: 99 -> 44 us (a thread per codeword and 32 dimensions before); with the centre 51: every workgroup
+// finds it again from the 16 means, which is less than one more launch takes.
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void encode_single_codewords_kernel(
     const float* __restrict__ codebook, int mode, const double* __restrict__ Lmat, const double* __restrict__ sd,
-    const double* __restrict__ heff, double* __restrict__ czT, double* __restrict__ wT, double* __restrict__ chalf,
-    float* __restrict__ cbias, CodewordStat* __restrict__ cstat) {
+    const double* __restrict__ heff, const double* __restrict__ means, Center* __restrict__ center,
+    double* __restrict__ czT, double* __restrict__ wT, double* __restrict__ chalf, float* __restrict__ cbias,
+    CodewordStat* __restrict__ cstat) {
+  __shared__ float s_mu[kD], s_t[kD];
   const int kv = blockIdx.y, lane = threadIdx.x & 63, c = lane & 15, k = lane >> 4;
   const int cg = blockIdx.x * 64 + (threadIdx.x >> 6) * 16 + c;
   const float* cw = codebook + ((size_t)kv * kCW + cg) * kD + k;
   float cv[kD / 4];   // dimensions k, 4 + k, ... of codeword cg
+#pragma unroll
+  for (int u = 0; u < kD / 4; ++u) cv[u] = cw[4 * u];
+  if (threadIdx.x < kD) {
+    // The centre of a dimension is the median of the means of the shares, so that a few codewords far out (or not finite) do
+    // not draw it away from the others, whose last bits it would cost.  t: the power of two next to the square root of the
+    // norm of the matrix's row, which is by how much w is longer than c in this dimension, so that k t and w / t are evenly
+    // long.
+    const int d = threadIdx.x;
+    float m[kMeans], mu = 0.f;
+#pragma unroll
+    for (int i = 0; i < kMeans; ++i) {
+      m[i] = (float)means[((size_t)kv * kMeans + i) * kD + d];
+      if (!(fabsf(m[i]) < INFINITY)) m[i] = INFINITY;
+    }
+#pragma unroll
+    for (int i = 0; i < kMeans; ++i) {
+      int below = 0;
+#pragma unroll
+      for (int j = 0; j < kMeans; ++j) below += m[j] < m[i] || (m[j] == m[i] && j < i) ? 1 : 0;
+      if (below == kMeans / 2) mu = m[i];
+    }
+    if (!(fabsf(mu) < INFINITY)) mu = 0.f;
+    const double sd_d = sd[(size_t)kv * kD + d], h = mode == A2ATS_W_BLOCK ? sd_d : sd_d * sd_d;
+    const int e = (int)(__float_as_uint((float)h) >> 23) - 127;   // (negative, infinite, not a number: above 100)
+    const float t = e > -80 && e < 80 ? __uint_as_float((uint32_t)(127 + ((e + 1) >> 1)) << 23) : 1.f;
+    s_mu[d] = mu;
+    s_t[d] = t;
+    if (blockIdx.x == 0) {
+      center[kv].mu[d] = mu;
+      center[kv].t[d] = t;
+    }
+  }
+  __syncthreads();
   double c2 = 0.0;
 #pragma unroll
   for (int u = 0; u < kD / 4; ++u) {
-    cv[u] = cw[4 * u];
-    c2 += (double)cv[u] * (double)cv[u];
+    const double x = ((double)cv[u] - (double)s_mu[4 * u + k]) * (double)s_t[4 * u + k];
+    c2 += x * x;
   }
+  auto centred = [&](int u) { return (double)cv[u] - (double)s_mu[4 * u + k]; };
   // register r of tile t: dimension 16 t + 4 r + k of codeword cg
   f64x4 acc[8];
   auto times = [&](const double* m, bool lower) {   // acc = (c m)^T, m row-major, its rows above column blocks zero if lower
@@ -255,21 +327,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int u = 0; u < kD / 4; ++u) {
       if (u + 2 < kD / 4) request(u + 2);
       __builtin_amdgcn_sched_barrier(0);
-      const double b = (double)cv[u];
+      const double b = centred(u);
 #pragma unroll
       for (int t = 0; t < 8; ++t)
         if (!lower || u >= 4 * t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(row[u % 3][t], b, acc[t], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  auto put = [&](double* out) {   // and the squared norm of the codeword's column
+  auto put = [&](double* out, bool balanced) {   // and the squared norm of the codeword's column
     double n = 0.0;
 #pragma unroll
     for (int t = 0; t < 8; ++t)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         out[((size_t)kv * kD + 16 * t + 4 * r + k) * kCW + cg] = acc[t][r];
-        n += acc[t][r] * acc[t][r];
+        const double x = balanced ? acc[t][r] * (double)inverse_of_power(s_t[16 * t + 4 * r + k]) : acc[t][r];
+        n += x * x;
       }
     n += __shfl_xor(n, 16);
     return n + __shfl_xor(n, 32);
@@ -279,20 +352,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   double z2, w2;
   if (mode == A2ATS_W_BLOCK) {
     times(Lmat + (size_t)kv * kD * kD, true);
-    z2 = put(czT);
+    z2 = put(czT, false);
     // the distortion is |z|^2 - 2 k . w + |c^z|^2, so scores need no z
     times(heff + (size_t)kv * kD * kD, false);
-    w2 = put(wT);
+    w2 = put(wT, true);
   } else {
     double s[kD / 4];
 #pragma unroll
     for (int u = 0; u < kD / 4; ++u) s[u] = sd[(size_t)kv * kD + 4 * u + k];
 #pragma unroll
-    for (int u = 0; u < kD / 4; ++u) acc[u / 4][u % 4] = (double)cv[u] * s[u];
-    z2 = put(czT);
+    for (int u = 0; u < kD / 4; ++u) acc[u / 4][u % 4] = centred(u) * s[u];
+    z2 = put(czT, false);
 #pragma unroll
     for (int u = 0; u < kD / 4; ++u) acc[u / 4][u % 4] *= s[u];
-    w2 = put(wT);
+    w2 = put(wT, true);
   }
   if (k == 0) {
     cbias[(size_t)kv * kCW + cg] = (float)(0.5 * z2);
@@ -317,10 +390,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 
 // ------------------------------------------------------------------------------------------
-// The matrix-core operands of 32 codewords, all -w (the matrix core then leaves 1/2 |c^z|^2 - k . w).
+// The matrix-core operands of 32 codewords, all -w / t (the matrix core then leaves 1/2 |c^z|^2 - k . w).
 // Lane (row, g) of k-step kt holds dimensions 16 kt + 8 g .. + 8 of its codeword.
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(512) void encode_single_operands_kernel(const double* __restrict__ wT,
+                                                                     Center* __restrict__ center,
                                                                      const float* __restrict__ cbias,
                                                                      uint16_t* __restrict__ cfrag,
                                                                      _Float16* __restrict__ f16,
@@ -331,12 +405,14 @@ __global__ __launch_bounds__(512) void encode_single_operands_kernel(const doubl
   const int row = tid & 31, kt = tid >> 6, g = (tid >> 5) & 1;
   float key_scale, w_scale;
   const bool ok = f16_scales(cstat[kv], key_scale, w_scale);
+  if (cb == 0 && tid < kD) center[kv].key[tid] = center[kv].t[tid] * key_scale;
   bf16x8 hi, lo;
   f16x8 h;
   float err = 0.f;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const double neg = -wT[((size_t)kv * kD + 16 * kt + 8 * g + i) * kCW + 32 * cb + row];
+    const int d = 16 * kt + 8 * g + i;
+    const double neg = -wT[((size_t)kv * kD + d) * kCW + 32 * cb + row] * (double)inverse_of_power(center[kv].t[d]);
     const uint16_t b = f32_to_bf16((float)neg);
     hi[i] = __builtin_bit_cast(__bf16, b);
     lo[i] = __builtin_bit_cast(__bf16, f32_to_bf16((float)(neg - (double)bf16_to_f32(b))));
@@ -406,7 +482,8 @@ __global__ __launch_bounds__(256) void encode_single_transform_kernel(
 // core leaves the scores.  Ranking has no branch: the codeword's number within the lane goes into the low 11
 // mantissa bits, and the two smallest are kept (2.25 vector instructions per score).
 //
-// With e_k = |k - f16(k)|, e_w = max |w - f16(w)| and float32 sums, a score is off by at most
+// With k and w now less the centre and balanced, e_k = |k - f16(k)|, e_w = max |w - f16(w)| and float32 sums, a score is off
+// by at most
 //   e_k max|w| + |k| e_w + 4e-6 (|k| max|w| + max 1/2 |c^z|^2)
 // and by 2^-12 of itself for the number; the two smallest are told apart where they differ by more than that
 // counted twice.  Of keys drawn like the codewords (normal, nothing in common with them) 2 % are not.
@@ -427,8 +504,8 @@ __device__ __forceinline__ void filter_insert(float a, float b, float c, float d
 
 template <int NT>
 __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void encode_single_filter_kernel(
-    const float* __restrict__ keys, const uint8_t* __restrict__ f16, const float* __restrict__ fbias,
-    const CodewordStat* __restrict__ cstat, uint16_t* __restrict__ codes, uint32_t* __restrict__ near_count,
+    const float* __restrict__ keys, const Center* __restrict__ center, const uint8_t* __restrict__ f16,
+    const float* __restrict__ fbias, const CodewordStat* __restrict__ cstat, uint16_t* __restrict__ codes, uint32_t* __restrict__ near_count,
     uint32_t* __restrict__ near, int64_t near_cap, int Hkv, int n_new, int pos0, int64_t ctx_stride) {
   constexpr int kBuf = kF16Bytes + 128, kPieces = kF16Bytes / 16 / kEncThreads;
   __shared__ __align__(16) uint8_t s_mem[2 * kBuf];
@@ -441,6 +518,12 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
   f16_scales(st, key_scale, w_scale);
 
   __shared__ float s_n2[NT][kEncThreads], s_e2[NT][kEncThreads];   // (kept out of the registers for the main loop)
+  __shared__ __align__(32) float s_mu[kD], s_key[kD];
+  if (tid < kD) {
+    s_mu[tid] = center[kv].mu[tid];
+    s_key[tid] = center[kv].key[tid];
+  }
+  __syncthreads();
   f16x8 kh[NT][8];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
@@ -448,18 +531,19 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
     float n2 = 0.f, e2 = 0.f;
 #pragma unroll
     for (int k4 = 0; k4 < 8; k4 += 4) {   // four k-steps of loads in flight at a time
-      float4 a[4], b[4];
+      float4 lo[4], hi[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        a[u] = *(const float4*)(kp + 16 * (k4 + u));
-        b[u] = *(const float4*)(kp + 16 * (k4 + u) + 4);
+        lo[u] = *(const float4*)(kp + 16 * (k4 + u));
+        hi[u] = *(const float4*)(kp + 16 * (k4 + u) + 4);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         typedef __attribute__((ext_vector_type(8))) float f32x8;
-        const f32x8 x = {a[u].x, a[u].y, a[u].z, a[u].w, b[u].x, b[u].y, b[u].z, b[u].w};
-        const f32x8 v = x * key_scale;
+        const f32x8 x = {lo[u].x, lo[u].y, lo[u].z, lo[u].w, hi[u].x, hi[u].y, hi[u].z, hi[u].w};
+        const int d = 16 * (k4 + u) + 8 * g;
+        const f32x8 v = (x - *(const f32x8*)&s_mu[d]) * *(const f32x8*)&s_key[d];
         kh[t][k4 + u] = __builtin_convertvector(v, f16x8);
         const f32x8 r = v - __builtin_convertvector(kh[t][k4 + u], f32x8);
 #pragma unroll
@@ -632,7 +716,7 @@ __device__ __forceinline__ void top3_insert(float s, int c, float& s1, float& s2
 }
 
 __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void encode_single_kernel(
-    const float* __restrict__ keys, const uint8_t* __restrict__ cfrag,
+    const float* __restrict__ keys, const Center* __restrict__ center, const uint8_t* __restrict__ cfrag,
     const float* __restrict__ cbias, const CodewordStat* __restrict__ cstat, uint16_t* __restrict__ codes,
     const uint32_t* __restrict__ near_count, const uint32_t* __restrict__ near, int64_t near_cap,
     uint32_t* __restrict__ counter, uint32_t* __restrict__ list, uint32_t* __restrict__ arrived, NearPart* parts, int Hkv,
@@ -642,6 +726,13 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
   const int kv = blockIdx.y;
   const long n_near = (long)near_count[kv];
   __shared__ uint32_t s_last;
+  __shared__ float s_mu[kD], s_t[kD];
+  if (n_near == 0) return;   // (uniform)
+  if (tid < kD) {
+    s_mu[tid] = center[kv].mu[tid];
+    s_t[tid] = center[kv].t[tid];
+  }
+  __syncthreads();
   // A short list is spread over the workgroups by slices of the codewords too (a multiple of two blocks each): one
   // workgroup takes 165 us for all of them (2000 normal keys x 8 heads: 285 -> 143 us).
   const long n_chunks = (n_near + kKeysPerWG - 1) / kKeysPerWG;
@@ -676,7 +767,10 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            const float x[8] = {a[u].x, a[u].y, a[u].z, a[u].w, b[u].x, b[u].y, b[u].z, b[u].w};
+            float x[8] = {a[u].x, a[u].y, a[u].z, a[u].w, b[u].x, b[u].y, b[u].z, b[u].w};
+            const int d = 16 * (k4 + u) + 8 * g;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] = (x[i] - s_mu[d + i]) * s_t[d + i];
             split8(x, zh[tile][k4 + u], zl[tile][k4 + u], zn2[tile]);
           }
           __builtin_amdgcn_sched_barrier(0);
@@ -856,8 +950,8 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
 // Exact decisions in float64
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void encode_single_recheck_kernel(
-    const float* __restrict__ keys, int mode, const double* __restrict__ Lmat, const double* __restrict__ sd,
-    const double* __restrict__ czT, uint16_t* __restrict__ codes, const uint32_t* __restrict__ counter,
+    const float* __restrict__ keys, const Center* __restrict__ center, int mode, const double* __restrict__ Lmat,
+    const double* __restrict__ sd, const double* __restrict__ czT, uint16_t* __restrict__ codes, const uint32_t* __restrict__ counter,
     const uint32_t* __restrict__ list, int Hkv, int n_new, int pos0, int64_t ctx_stride) {
   __shared__ double s_k[kD], s_z[kD], s_d[256];
   __shared__ int s_i[256];
@@ -868,7 +962,7 @@ __global__ __launch_bounds__(256) void encode_single_recheck_kernel(
     const bool full = (list[2 * (size_t)it] >> 31) != 0;
     const int bkv = (int)(key / (uint32_t)n_new), j = (int)(key % (uint32_t)n_new), kv = bkv % Hkv;
     __syncthreads();   // the arrays of the key before are still being read
-    if (tid < kD) s_k[tid] = (double)keys[((size_t)bkv * n_new + j) * kD + tid];
+    if (tid < kD) s_k[tid] = (double)keys[((size_t)bkv * n_new + j) * kD + tid] - (double)center[kv].mu[tid];
     __syncthreads();
     if (tid < kD) {
       double z;
@@ -962,8 +1056,8 @@ __global__ void encode_single_clear_kernel(uint32_t* counter, int n) {
 // decode batch (32 keys x 16 slices on 256 CUs) are resident together.
 constexpr int kSweepThreads = 512;
 __global__ __launch_bounds__(kSweepThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void encode_single_sweep_kernel(
-    const float* __restrict__ keys, const double* __restrict__ wT, const double* __restrict__ chalf,
-    double* __restrict__ part, int Hkv, int n_new) {
+    const float* __restrict__ keys, const Center* __restrict__ center, const double* __restrict__ wT,
+    const double* __restrict__ chalf, double* __restrict__ part, int Hkv, int n_new) {
   constexpr int PER = kCW / kSlices;   // codewords per slice
   static_assert(PER == 256 && kSweepThreads == 2 * PER, "a thread owns one codeword and half of the dimensions");
   __shared__ double s_k[kD], s_p[2][PER];
@@ -979,7 +1073,7 @@ __global__ __launch_bounds__(kSweepThreads) __attribute__((amdgpu_waves_per_eu(4
 #pragma unroll
   for (int t = 0; t < 32; ++t) wv[t] = w[(size_t)t * kCW];
   const double half = chalf[(size_t)kv * kCW + c];
-  if (tid < kD) s_k[tid] = (double)keys[(size_t)key * kD + tid];
+  if (tid < kD) s_k[tid] = (double)keys[(size_t)key * kD + tid] - (double)center[kv].mu[tid];
   __builtin_amdgcn_sched_barrier(0);
   __syncthreads();
   double d0 = 0.0, d1 = 0.0;
@@ -1207,20 +1301,22 @@ hipError_t launch_encode_single_prepare(const a2ats_dims& d, const float* codebo
   const size_t factor_lds = (size_t)kD * kFactorStride * sizeof(double);
   hipError_t err = allow_dynamic_lds(encode_single_factor_kernel, factor_lds, g_factor_lds);
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(encode_single_factor_kernel, dim3(d.n_kv_heads), dim3(256), factor_lds, stream, weights, mode,
-                     Lmat, sd, cstat);
+  double* means = (double*)(base + w.off_means);
+  Center* center = (Center*)(base + w.off_center);
+  hipLaunchKernelGGL(encode_single_factor_kernel, dim3(d.n_kv_heads, 1 + kMeans), dim3(256), factor_lds, stream, weights,
+                     mode, Lmat, sd, cstat, codebook, means);
   if ((err = hipGetLastError()) != hipSuccess) return err;
   double* heff = (double*)(base + w.off_heff);
   if (mode == A2ATS_W_BLOCK) {
-    hipLaunchKernelGGL(encode_single_heff_kernel, dim3(kD, d.n_kv_heads), dim3(kD), 0, stream, Lmat, heff);
+    hipLaunchKernelGGL(encode_single_heff_kernel, dim3(kD, d.n_kv_heads), dim3(kD), 0, stream, Lmat, heff, sd);
     if ((err = hipGetLastError()) != hipSuccess) return err;
   }
   hipLaunchKernelGGL(encode_single_codewords_kernel, dim3(kCW / 64, d.n_kv_heads), dim3(256), 0, stream, codebook,
-                     mode, Lmat, sd, heff, (double*)(base + w.off_czT), (double*)(base + w.off_wT),
+                     mode, Lmat, sd, heff, means, center, (double*)(base + w.off_czT), (double*)(base + w.off_wT),
                      (double*)(base + w.off_chalf), (float*)(base + w.off_cbias), cstat);
   if ((err = hipGetLastError()) != hipSuccess) return err;
   hipLaunchKernelGGL(encode_single_operands_kernel, dim3(kBlocks, d.n_kv_heads), dim3(512), 0, stream,
-                     (const double*)(base + w.off_wT), (const float*)(base + w.off_cbias), (uint16_t*)(base + w.off_cfrag),
+                     (const double*)(base + w.off_wT), center, (const float*)(base + w.off_cbias), (uint16_t*)(base + w.off_cfrag),
                      (_Float16*)(base + w.off_f16), (float*)(base + w.off_fbias), cstat);
   return hipGetLastError();
 }
@@ -1237,7 +1333,8 @@ hipError_t launch_encode_single_sweep(const a2ats_dims& d, const float* keys, in
     return err;
   const uint32_t n_all = (uint32_t)((size_t)d.batch * d.n_kv_heads * n_new);
   hipLaunchKernelGGL(encode_single_sweep_kernel, dim3(n_all, kSlices), dim3(kSweepThreads), 0, stream, keys,
-                     (const double*)(base + w.off_wT), (const double*)(base + w.off_chalf), part, d.n_kv_heads,
+                     (const Center*)(base + w.off_center), (const double*)(base + w.off_wT),
+                     (const double*)(base + w.off_chalf), part, d.n_kv_heads,
                      n_new);
   return hipGetLastError();
 }
@@ -1250,6 +1347,7 @@ hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_ne
   uint8_t* base = (uint8_t*)ws;
   double* Lmat = (double*)(base + w.off_L);
   double* sd = (double*)(base + w.off_sd);
+  const Center* center = (const Center*)(base + w.off_center);
   double* czT = (double*)(base + w.off_czT);
   uint8_t* cfrag = base + w.off_cfrag;
   float* cbias = (float*)(base + w.off_cbias);
@@ -1265,7 +1363,7 @@ hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_ne
 
   const uint32_t n_all = (uint32_t)((size_t)bkv * n_new);
   if (n_new <= kFewSingle) {
-    hipLaunchKernelGGL(encode_single_sweep_kernel, dim3(n_all, kSlices), dim3(kSweepThreads), 0, stream, keys,
+    hipLaunchKernelGGL(encode_single_sweep_kernel, dim3(n_all, kSlices), dim3(kSweepThreads), 0, stream, keys, center,
                        (const double*)(base + w.off_wT), (const double*)(base + w.off_chalf), part, Hkv, n_new);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     hipLaunchKernelGGL(encode_single_sweep_pick_kernel, dim3((n_all + 63) / 64), dim3(64), 0, stream, part,
@@ -1281,7 +1379,7 @@ hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_ne
   const int nt = waves >= 4L * kEncWaves * 400 ? 4 : (waves >= 2L * kEncWaves * 400 ? 2 : 1);
   const dim3 grid((n_new + 32 * nt * kEncWaves - 1) / (32 * nt * kEncWaves), bkv), block(kEncThreads);
 #define A2ATS_LAUNCH_FILTER(NT)                                                                                      \
-  hipLaunchKernelGGL(encode_single_filter_kernel<NT>, grid, block, 0, stream, keys, (const uint8_t*)(base + w.off_f16), \
+  hipLaunchKernelGGL(encode_single_filter_kernel<NT>, grid, block, 0, stream, keys, center, (const uint8_t*)(base + w.off_f16), \
                      (const float*)(base + w.off_fbias), cstat, (uint16_t*)codes, counter + 1, near,                 \
                      (int64_t)w.near_cap, Hkv, n_new, pos0, d.ctx_stride)
   if (nt == 4) A2ATS_LAUNCH_FILTER(4);
@@ -1289,12 +1387,12 @@ hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_ne
   else A2ATS_LAUNCH_FILTER(1);
 #undef A2ATS_LAUNCH_FILTER
   if ((err = hipGetLastError()) != hipSuccess) return err;
-  hipLaunchKernelGGL(encode_single_kernel, dim3((unsigned)near_groups(d), Hkv), block, 0, stream, keys, cfrag, cbias,
+  hipLaunchKernelGGL(encode_single_kernel, dim3((unsigned)near_groups(d), Hkv), block, 0, stream, keys, center, cfrag, cbias,
                      cstat, (uint16_t*)codes, counter + 1, near, (int64_t)w.near_cap, counter, list, counter + 1 + Hkv,
                      (NearPart*)(base + w.off_near_part), Hkv, n_new, pos0, d.ctx_stride);
   if ((err = hipGetLastError()) != hipSuccess) return err;
   const uint32_t re_grid = n_all < 2048u ? n_all : 2048u;
-  hipLaunchKernelGGL(encode_single_recheck_kernel, dim3(re_grid), dim3(256), 0, stream, keys, mode, Lmat, sd, czT,
+  hipLaunchKernelGGL(encode_single_recheck_kernel, dim3(re_grid), dim3(256), 0, stream, keys, center, mode, Lmat, sd, czT,
                      (uint16_t*)codes, counter, (const uint32_t*)list, Hkv, n_new, pos0, d.ctx_stride);
   return hipGetLastError();
 }
@@ -1339,7 +1437,7 @@ hipError_t launch_kmeanspp_seed(const a2ats_dims& d, const float* keys, int n_ne
   hipError_t err = allow_dynamic_lds(encode_single_factor_kernel, factor_lds, g_factor_lds);
   if (err != hipSuccess) return err;
   hipLaunchKernelGGL(encode_single_factor_kernel, dim3(Hkv), dim3(256), factor_lds, stream, weights, mode, Lmat, sd,
-                     cstat);
+                     cstat, (const float*)nullptr, (double*)nullptr);
   if ((err = hipGetLastError()) != hipSuccess) return err;
   if (mode == A2ATS_W_BLOCK)
     hipLaunchKernelGGL(encode_single_transform_kernel, dim3((n_new + 63) / 64, bkv), dim3(256), 0, stream, keys, Lmat,

@@ -240,3 +240,41 @@ def test_codes_under_blocks_that_are_far_from_round(m, smallest):
         far = (part.double().reshape(1, 1, -1, m, ds) - codebook[0].double()[torch.arange(m, device="cuda"), got[:, :, first:first + 5000]]).pow(2).sum(-1)
         wrong += int((mine - best > 1e-13 * ds * far).sum())
     assert wrong == 0
+
+
+@pytest.mark.parametrize("mode", ["none", "diag", "block"])
+@pytest.mark.parametrize("n_new,data", [(8, "shifted"), (3000, "shifted"), (3000, "uneven"), (3000, "outliers")])
+def test_single_codebook_away_from_the_origin_and_under_uneven_weights(mode, n_new, data):
+    """Keys and codewords with much in common, weights over six orders of magnitude, and a few codewords far out, infinite or
+    not a number among many, which must not move the centre that all are taken relative to."""
+    kv = 2
+    wl = synth.Workload("enc1_shift", 1, kv, kv, 128, 1, n_new + 8, 16, 16, seed=n_new + len(data), n_centroids=4096)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    h64 = synth.make_query_second_moment(wl)["H"].cuda()
+    if data == "uneven":
+        scale = torch.logspace(-1.5, 1.5, 128, dtype=torch.float64, device="cuda")[torch.randperm(128, generator=g, device="cuda")]
+        h64 = scale[:, None] * h64 * scale[None, :]
+    weights, code = {"none": (None, B.W_NONE), "diag": (torch.diagonal(h64, dim1=1, dim2=2).float().contiguous(), B.W_DIAG),
+                     "block": (h64.float().contiguous(), B.W_BLOCK)}[mode]
+    h64 = {"none": lambda: torch.eye(128, dtype=torch.float64, device="cuda").expand(kv, 128, 128),
+           "diag": lambda: torch.diag_embed(weights.double()), "block": lambda: weights.double()}[mode]()
+    h64 = 0.5 * (h64 + h64.transpose(1, 2))
+    codebook = synth.make_codebook(wl, "cuda")
+    keys = synth.make_encode_keys(wl, n_new, device="cuda", stress=True)
+    if data == "shifted":
+        shift = 40.0 * torch.randn(kv, 128, generator=g, device="cuda")
+        codebook += shift[:, None, None]
+        keys += shift[None, :, None]
+    if data == "outliers":
+        codebook[0, 0, 7], codebook[0, 0, 300, 5], codebook[1, 0, 4000, 100], codebook[1, 0, 9] = 1e12, float("nan"), float("inf"), -1e18
+    dims = B.make_dims(1, kv, kv, 128, 1, n_new + 8, n_centroids=4096)
+    got = _single(dims, keys, codebook, weights, code, n_new + 8, prepared=True)
+    for h in range(kv):
+        c, k = codebook[h, 0].double(), keys[0, h].double()
+        middle = c[1000:2000].mean(0)
+        c, k = c - middle, k - middle
+        w = c @ h64[h]
+        score = (0.5 * (w * c).sum(-1) - k @ w.t()).nan_to_num(nan=float("inf"), posinf=float("inf"), neginf=float("inf"))
+        lost = score.gather(1, got[0, h][:, None])[:, 0] - score.min(1).values
+        ordinary = w[1000:2000].norm(dim=1).max()
+        assert (lost <= 1e-12 * ((0.5 * (w * c).sum(-1))[1000:2000].max() + k.norm(dim=1) * ordinary)).all(), float(lost.max())

@@ -587,14 +587,16 @@ def codebook_fit(args, torch, B, synth, wl):
                   "step; plus one second-moment accumulation)",
         "value": n_keys / (ms * 1e-3), "unit": "keys/s", "n_gpus": 1, "steps": steps, "warmup": warmup,
         "ms_per_step": ms, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "bf16 split products / f64 re-check for the assignment; f64 sums for means and moments",
+        "dtype": "assignment: f16 products, bf16 hi/lo products, then f64, where they cannot decide; f64 sums for means "
+                 "and moments",
         "data": "synthetic",
         "config": {"workload": wl.name + " codebook construction", "keys": n_keys, "codewords": wl.n_centroids,
                    "query_rows": N * wl.n_q_heads},
         "phase_ms_median": {"assign": ph[0], "centroid_step": ph[1], "second_moment": ph[2]},
         "kmeanspp_seed_ms": {"keys_per_kv_head": wl.batch * n_seed, "ms": seed_ms},
-        "roofline": {"kernel": "encode_single_kernel", "bound": "mfma", "achieved": flop / (ph[0] * 1e-3) / 1e12,
-                     "peak": 2500.0, "unit": "TFLOP/s", "frac": flop / (ph[0] * 1e-3) / 1e12 / 2500.0,
+        "roofline": {"kernel": "encode_single_filter_kernel (+ factor, codeword, listed-key and re-check kernels)",
+                     "bound": "mfma", "achieved": flop / (ph[0] * 1e-3) / 1e12, "peak": 2500.0, "unit": "TFLOP/s",
+                     "frac": flop / (ph[0] * 1e-3) / 1e12 / 2500.0,
                      "traffic": None, "note": "algorithmic flops of the assignment over its whole call"},
     }))
 

@@ -122,20 +122,23 @@ int a2ats_rope_tables(int32_t head_dim, const double* inv_freq, int32_t b, int32
  *   codes    [dev, u8   B*Hkv*ctx_stride*M] rows pos0 .. pos0+n_new-1 are written
  * Distances are formed on the matrix cores from f16 hi/lo splits of both operands (22 bits) and
  * re-evaluated in float64 from the definition whenever the two smallest are closer than that
- * arithmetic can tell apart, so codes equal the float64 argmin.  The weighted modes need a2ats_workspace_bytes(dims, A2ATS_OP_ENCODE, 0, 0) bytes
- * of workspace (transformed centroids); A2ATS_W_NONE needs none.  n_new == 0 is a no-op.
+ * arithmetic can tell apart, so codes equal the float64 argmin.  The weighted modes need
+ * a2ats_workspace_bytes(dims, A2ATS_OP_ENCODE, 0, 0) bytes of workspace (transformed centroids);
+ * A2ATS_W_NONE needs none.  n_new == 0 is a no-op.
  * Single codebook: H is the full D x D matrix (A2ATS_W_BLOCK: weights [dev, f32 Hkv*D*D], the
  * lower triangle is read) and the argmin is over 4096 codewords of all 128 dimensions:
  * codes [dev, u16 B*Hkv*ctx_stride].  With the Cholesky factor of section 4.2 (H = L L^T,
  * c^z = c L, w = c (L L^T)) the scores 1/2||c^z||^2 - k.w are formed on the matrix cores from f16
- * roundings of both operands; keys whose two best scores are closer than the rounding can account
+ * roundings of both operands, with a centre of the codewords subtracted from keys and codewords
+ * (which leaves the distances as they are) and the dimensions of k and w balanced by powers of two;
+ * keys whose two best scores are closer than the rounding can account
  * for are scored again from bf16 hi/lo splits (about 2^-17 relative), and those still too close in
  * float64, so codes equal the float64 argmin.  Every weight mode needs the workspace (L, c^z and w
- * in their forms, 11.9 MB per KV head, 2.1 MB for short lists of such keys; 12 bytes per key that
- * ctx_stride allows); each call
+ * in their forms and the centre, 11.9 MB per KV head, 2.1 MB for short lists of such keys; 12 bytes
+ * per key that ctx_stride allows); each call
  * derives them again unless weight_mode carries A2ATS_W_PREPARED (see a2ats_encode_prepare).  Up
  * to 8 keys per sequence and KV head (the decode-time append) are decided by one float64 sweep
- * each, over the expanded form 1/2||c^z||^2 - k.w of the same distortion.
+ * each, over the expanded form 1/2||c^z||^2 - k.w of the same distortion (less the centre, too).
  * B*Hkv*n_new must stay below 2^31.
  */
 int a2ats_encode_keys(const a2ats_dims* dims, const float* keys, int32_t n_new, int32_t pos0,
@@ -193,13 +196,15 @@ int a2ats_decode_prologue(const a2ats_dims* dims, const float* keys, int32_t n_n
  * a2ats_decode_prologue followed by a2ats_score_topk (without its debug output) as one call: steps
  * 1-3 of a decode step plus the append of the current token's key (paper sections 4.1-4.3).  Where
  * a2ats_score_topk takes its streaming route (product quantisation, at least 16384 candidates,
- * 1 <= top_k, 4 top_k <= candidates) the call needs one launch less than the two: the
+ * 1 <= top_k <= 4096, 4 top_k <= candidates; from top_k 2049 on with the workspace that
+ * a2ats_workspace_bytes asks for) the call needs one launch less than the two: the
  * workgroups that sample the thresholds build their problem's tables themselves and keep the coarse
  * copy in LDS.  That is done while (a) those workgroups, batch * n_kv_heads * head groups * sampling
  * parts, number at most 256, one per CU, and (b) no appended row can be a candidate of any sequence,
  * pos0 >= ctx_len - window (the usual append of the current token; the sampling workgroups read
- * candidate rows while others write the appended ones).  With at most 16384 candidates, and (b), the whole
- * call is one launch.  Elsewhere it simply makes the two calls.
+ * candidate rows while others write the appended ones).  With fewer candidates, (b), and the group
+ * route (see a2ats_score_topk) the whole call is one launch.
+ * Elsewhere it simply makes the two calls.
  * Arguments are the union of theirs and are all checked before anything is enqueued; every output
  * (codes, q_rot, lut, lut_scale, topk_*) is bit for bit what the two calls write.
  * `ws`: a2ats_workspace_bytes(dims, A2ATS_OP_SCORE_TOPK, top_k, window) bytes for product
@@ -230,6 +235,15 @@ int a2ats_decode_select(const a2ats_dims* dims, const float* keys, int32_t n_new
  *   scores_out [dev, out, nullable, f32 B*Hq*ctx_stride] debug: every token's score
  *              (positions >= n are not written)
  * top_k == 0 is allowed.  window >= 0, n_sink >= 0.
+ * Routes (product quantisation; the results are the same bit for bit): from 16384 candidates on, with
+ * 1 <= top_k <= 4096 and 4 top_k <= candidates, the codes are streamed once.  Of the others, those with
+ * at most 16384 candidates take the group route, up to four heads of a KV head together, where the
+ * query heads need more rounds of 256 workgroups than the head groups do, and else while there are at
+ * most 8192 candidates (M = 16; M = 32: 2048; three quarters of that with more than 256 query heads in
+ * all).  What is left has one workgroup per query head.
+ * Workspace: a2ats_workspace_bytes(dims, A2ATS_OP_SCORE_TOPK, top_k, window).  A streaming call of up to
+ * 2048 tokens is refused without it; one of 2049 to 4096 tokens then takes the slower last route, which
+ * needs none.
  * Single codebook: codes [dev, u16 B*Hkv*ctx_stride]; a score is the table entry of the token's
  * code, there are at most 4096 distinct scores per head and ties (by position) decide most
  * selections; needs no workspace (a2ats_workspace_bytes returns 0) and lut_scale is not read.

@@ -417,9 +417,13 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4, 
   }
 }
 
-// Append-time shape (a few new keys per sequence, e.g. one per decode step): the prefill kernel
-// would run one thread per key with 256 serial distance evaluations; here a workgroup of 256
-// threads takes one (key, subspace) pair (see encode_few.hpp).
+// Append-time shape (a few new keys per sequence, e.g. one per decode step): a workgroup of 256 threads takes one (key,
+// subspace) pair, a thread per centroid, in float64 from the definition (see encode_few.hpp), so nothing is prepared and the
+// weighted modes too are one launch; the matrix-core kernel has 64 rows of keys in a step whatever the number of keys, and the
+// weighted modes a launch before it.  Bound by float64 arithmetic, a time that grows with the pairs: M = 16, weights per
+// dimension, a whole call: 8 us up to 4096 pairs (one key of 32 sequences x 8 KV heads), 126 at 131072 (32 keys of them),
+// where the other kernel takes 19 (33 keys; 8 KV heads of one sequence: 8 here, 13 there).  The line at 32 keys is
+// a2ats_decode_prologue's, which takes as many and has no workspace; by time alone it would lie near 8192 pairs.
 template <int DS>
 __global__ __launch_bounds__(kCentroids) void encode_few_kernel(
     const float* __restrict__ keys, const float* __restrict__ codebook,

@@ -6,7 +6,7 @@
 // plain squared distance ||z - c^z||^2, and minimising it over c is minimising
 //     s_c = 1/2 ||c^z||^2 - k . w_c ,   w_c = c (L L^T) ,
 // a dense [keys x 128] . [128 x 4096] contraction: 1 Mflop per key, the one matrix-core shape of
-// this library.  The kernels:
+// this library.
 //
 // Distortions do not change when keys and codewords are moved together, but products, whose rounding goes with |k| |w|, are
 // the larger the more all of them have in common.  So everything below is about keys and codewords less a centre of the
@@ -14,11 +14,13 @@
 // 8 KV heads, all of them around 16 in every dimension: 8045 -> 381 us (nearly every key went to the float64 sweep before);
 // variances 1 and 1e4 by dimension: 1297 -> 549; around the origin 375 -> 377.
 //
+// The kernels:
+//
 //   encode_single_factor_kernel    per KV head: L in float64 (Cholesky in LDS, or the identity /
 //                                  a diagonal for the unweighted / per-dimension modes); in other
 //                                  workgroups the means that the centre is taken from
-//   encode_single_heff_kernel      L L^T (full-matrix mode)
-//   encode_single_codewords_kernel c^z and w_c in float64, kept transposed for the exact decisions,
+//   encode_single_heff_kernel      L L^T and the norms of its rows (full-matrix mode)
+//   encode_single_codewords_kernel the centre and t; c^z and w_c in float64, kept transposed for the exact decisions,
 //                                  1/2 ||c^z||^2, and the largest norms
 //   encode_single_operands_kernel  w_c in matrix-core operand order: rounded to f16, and as two bf16
 //                                  terms (hi + lo, 16 significant bits)

@@ -191,7 +191,7 @@ constexpr int kSmallSel = 128;                      // a K-th-key bin of at most
 
 struct SelLds {
   int32_t table[kCodewords];    // the head's scores as order-preserving keys
-  uint32_t count[kCodewords + 1];   // candidate tokens per codeword (+ a spare bin)
+  uint32_t count[kCodewords];   // candidate tokens per codeword
   uint32_t hist[kHistBins];
   uint32_t wave_tot[kSpan][kSelWaves];   // packed (above, equal) counts per round and wave
   uint32_t wave_pre[kSpan][kSelWaves];   // ... exclusive over the waves of a round
@@ -310,11 +310,11 @@ __global__ __launch_bounds__(kSelThreads) void select_single_kernel(
         if (jw >= lo && jw + 64 * kPerThread <= hi) {   // (wave-uniform) every token is a candidate
 #pragma unroll
           for (int i = 0; i < kPerThread; ++i) atomicAdd(&L.count[code_of(cv[r], i)], 1u);
-        } else {
+        } else if (jw < hi) {   // (a spare bin for the others is one address for all that lies past the end: 122 us, not 18, at 4096 tokens)
           const uint32_t vm = valid_mask8(s0 + r * kRound + tid * kPerThread, lo, hi);
 #pragma unroll
-          for (int i = 0; i < kPerThread; ++i)   // tokens outside the candidate range count in a spare bin
-            atomicAdd(&L.count[(vm >> i) & 1u ? code_of(cv[r], i) : (uint32_t)kCodewords], 1u);
+          for (int i = 0; i < kPerThread; ++i)
+            if ((vm >> i) & 1u) atomicAdd(&L.count[code_of(cv[r], i)], 1u);
         }
       }
     }

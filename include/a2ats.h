@@ -182,8 +182,8 @@ int a2ats_build_lut(const a2ats_dims* dims, const void* q, int q_dtype, const fl
  * at positions pos0 .. pos0 + n_new - 1.  Arguments, layouts and results are exactly those of the
  * two calls; n_new > 32 returns A2ATS_ERR_UNSUPPORTED, n_new == 0 builds the tables only (keys /
  * codes may then be NULL).  Product quantisation needs no workspace (ws may be NULL).
- * Single codebook: at most 8 keys per sequence and KV head; two launches (the float64 sweep of
- * a2ats_encode_keys' few-key route, then the table build, which also picks the codes); `ws` as for
+ * Single codebook: at most 8 keys per sequence and KV head; two launches (a float64 sweep of the codewords
+ * for the keys and the table build, one with the other or one after the other); `ws` as for
  * a2ats_encode_keys, and weight_mode may carry A2ATS_W_PREPARED in the same way.
  */
 int a2ats_decode_prologue(const a2ats_dims* dims, const float* keys, int32_t n_new, int32_t pos0,
@@ -204,12 +204,15 @@ int a2ats_decode_prologue(const a2ats_dims* dims, const float* keys, int32_t n_n
  * pos0 >= ctx_len - window (the usual append of the current token; the sampling workgroups read
  * candidate rows while others write the appended ones).  With fewer candidates, (b), and the group
  * route (see a2ats_score_topk) the whole call is one launch.
+ * Single codebook: with a key to append and (b) the call is two launches -- tables, keys and the number of
+ * candidates per codeword, then the selection -- instead of three; the counts lie in `ws`, behind the part that
+ * a2ats_encode_prepare fills.
  * Elsewhere it simply makes the two calls.
  * Arguments are the union of theirs and are all checked before anything is enqueued; every output
  * (codes, q_rot, lut, lut_scale, topk_*) is bit for bit what the two calls write.
  * `ws`: a2ats_workspace_bytes(dims, A2ATS_OP_SCORE_TOPK, top_k, window) bytes for product
  * quantisation (the prologue needs none there), a2ats_workspace_bytes(dims, A2ATS_OP_ENCODE, 0, 0)
- * for the single codebook (its selection needs none).
+ * for the single codebook (n_new == 0: none).
  */
 int a2ats_decode_select(const a2ats_dims* dims, const float* keys, int32_t n_new, int32_t pos0,
                         const float* codebook, const float* weights, int weight_mode, uint8_t* codes,

@@ -224,7 +224,7 @@ int a2ats_build_lut(const a2ats_dims* d, const void* q, int q_dtype, const float
   const hipError_t e =
       a2ats::single_codebook(*d)
           ? a2ats::launch_build_lut_single(*d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale, false,
-                                           a2ats::FewKeyPick{nullptr, nullptr, 0, 0},
+                                           a2ats::FewKeys{}, a2ats::FewKeyPick{},
                                            (hipStream_t)stream)
           : a2ats::launch_build_lut(*d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale,
                                     (hipStream_t)stream);
@@ -242,7 +242,7 @@ int a2ats_build_lut_shared(const a2ats_dims* d, const void* q, int q_dtype, cons
   const hipError_t e =
       a2ats::single_codebook(*d)
           ? a2ats::launch_build_lut_single(*d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale, true,
-                                           a2ats::FewKeyPick{nullptr, nullptr, 0, 0},
+                                           a2ats::FewKeys{}, a2ats::FewKeyPick{},
                                            (hipStream_t)stream)
           : a2ats::launch_build_lut_shared(*d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale,
                                            (hipStream_t)stream);
@@ -268,17 +268,15 @@ int a2ats_decode_prologue(const a2ats_dims* d, const float* keys, int32_t n_new,
     return A2ATS_ERR_INVALID_ARG;
   if (n_new > 32) return A2ATS_ERR_UNSUPPORTED;   // prefill-sized batches go through a2ats_encode_keys
   if (a2ats::single_codebook(*d)) {
-    // the float64 sweep for the appended keys, then the table build, which also picks their codes
     if (n_new > a2ats::kFewSingleKeys) return A2ATS_ERR_UNSUPPORTED;
-    a2ats::FewKeyPick pick{nullptr, (uint16_t*)codes, n_new, pos0};
-    if (n_new > 0 && d->batch > 0) {
-      if (!ws || misaligned16(ws) || ws_bytes < a2ats::encode_single_ws_bytes(*d)) return A2ATS_ERR_WORKSPACE;
-      if (a2ats::launch_encode_single_sweep(*d, keys, n_new, codebook, weights, weight_mode, prepared, ws,
-                                            &pick.part, (hipStream_t)stream) != hipSuccess)
-        return A2ATS_ERR_HIP;
-    }
-    const hipError_t e = a2ats::launch_build_lut_single(*d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut,
-                                                        lut_scale, false, pick, (hipStream_t)stream);
+    if (n_new > 0 && d->batch > 0 && (!ws || misaligned16(ws) || ws_bytes < a2ats::encode_single_ws_bytes(*d)))
+      return A2ATS_ERR_WORKSPACE;
+    const hipError_t e =
+        n_new > 0 && d->batch > 0
+            ? a2ats::launch_decode_prologue_single(*d, keys, n_new, pos0, codebook, weights, weight_mode, prepared, codes, q,
+                                                   q_dtype, cos_b, sin_b, q_rot, lut, lut_scale, ws, (hipStream_t)stream)
+            : a2ats::launch_build_lut_single(*d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale, false,
+                                             a2ats::FewKeys{}, a2ats::FewKeyPick{}, (hipStream_t)stream);
     return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
   }
   const hipError_t e = a2ats::launch_decode_prologue(*d, keys, n_new, pos0, codebook, weights, weight_mode,
@@ -312,6 +310,30 @@ int a2ats_decode_select(const a2ats_dims* d, const float* keys, int32_t n_new, i
   const bool appended_rows_compete = n_new > 0 && (int64_t)pos0 < (int64_t)d->ctx_len - window;
   // (short contexts have a launch of their own for the whole call, under the same condition)
   const bool in_one = !streams && a2ats::takes_group_route(*d, window, n_sink);
+  // Single codebook, under the same condition: tables, appended keys and counts of the codewords in one launch, the selection
+  // in another.  The counts lie in the workspace, which a call without keys to append may come without.
+  if (a2ats::single_codebook(*d) && n_new > 0 && n_new <= a2ats::kFewSingleKeys && !appended_rows_compete && ws &&
+      !misaligned16(ws) && ws_bytes >= a2ats::encode_single_ws_bytes(*d) &&
+      a2ats::select_chunks_single_fits(*d, window, n_sink, a2ats::encode_single_scratch_bytes(*d))) {
+    if (pos0 < 0 || (int64_t)pos0 + n_new > d->ctx_stride) return A2ATS_ERR_INVALID_ARG;
+    const int mode = weight_mode & ~A2ATS_W_PREPARED;
+    if (mode != A2ATS_W_NONE && mode != A2ATS_W_DIAG && mode != A2ATS_W_BLOCK) return A2ATS_ERR_INVALID_ARG;
+    if (q_dtype != A2ATS_F32 && q_dtype != A2ATS_BF16) return A2ATS_ERR_INVALID_ARG;
+    if (!codebook || !q || !cos_b || !sin_b || !q_rot || !keys) return A2ATS_ERR_INVALID_ARG;
+    if (mode != A2ATS_W_NONE && !weights) return A2ATS_ERR_INVALID_ARG;
+    if (misaligned16(codebook) || misaligned16(lut) || misaligned16(keys)) return A2ATS_ERR_INVALID_ARG;
+    if (d->batch == 0) return A2ATS_OK;
+    a2ats::FewKeys few{};
+    void* scratch = nullptr;
+    hipError_t e = a2ats::launch_encode_single_few(*d, keys, n_new, codebook, weights, mode,
+                                                   (weight_mode & A2ATS_W_PREPARED) != 0, ws, &few, &scratch,
+                                                   (hipStream_t)stream);
+    if (e == hipSuccess)
+      e = a2ats::launch_decode_select_single(*d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale, few, pos0, codes,
+                                             top_k, window, n_sink, seq_lens, topk_idx, topk_count, topk_score, scratch,
+                                             (hipStream_t)stream);
+    return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
+  }
   if (a2ats::single_codebook(*d) || appended_rows_compete || (!in_one && (!streams || n_sample > 256))) {   // the two calls, with their own checks
     rc = a2ats_decode_prologue(d, keys, n_new, pos0, codebook, weights, weight_mode, codes, q, q_dtype, cos_b,
                                sin_b, q_rot, lut, lut_scale, ws, ws_bytes, stream);

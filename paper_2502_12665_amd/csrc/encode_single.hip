@@ -42,7 +42,8 @@
 //                                  4096.  So the emitted code is the float64 argmin.
 //   encode_single_sweep_kernel     the few-key (decode-time append) route: one float64 pass of dot
 //                                  products k . w_c decides the key; 16 workgroups per key, then
-//                                  encode_single_sweep_pick_kernel
+//                                  encode_single_sweep_pick_kernel.  More keys, and those of a decode
+//                                  step's first launch, are swept in single_codebook.hip
 //   encode_single_transform_kernel z = k L in float64, rounded once to float32 (seeding only)
 #include "common.hpp"
 #include "internal.hpp"
@@ -1049,7 +1050,7 @@ __global__ void encode_single_clear_kernel(uint32_t* counter, int n) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) counter[i] = 0;
 }
 
-// The few-key (append) route: every key is decided by a float64 sweep, its 4096 codewords split
+// The few-key (append) route of a few keys in all: every key is decided by a float64 sweep, its 4096 codewords split
 // over kSlices workgroups (one workgroup would read 4 MB by itself).  With w_c = c (L L^T) the
 // distortion of codeword c is |z|^2 - 2 k . w_c + |c^z|^2, so the sweep minimises
 // 1/2 |c^z|^2 - k . w_c and needs neither z nor L: one pass of dot products over wT.
@@ -1323,28 +1324,82 @@ hipError_t launch_encode_single_prepare(const a2ats_dims& d, const float* codebo
   return hipGetLastError();
 }
 
-hipError_t launch_encode_single_sweep(const a2ats_dims& d, const float* keys, int n_new, const float* codebook,
-                                      const float* weights, int mode, bool prepared, void* ws,
-                                      const double** part_out, hipStream_t stream) {
+size_t encode_single_scratch_bytes(const a2ats_dims& d) {
+  const EncWs w = enc_single_ws(d);
+  return w.off_near_part - w.off_list;   // the lists of a call with more keys
+}
+
+hipError_t launch_encode_single_few(const a2ats_dims& d, const float* keys, int n_new, const float* codebook,
+                                    const float* weights, int mode, bool prepared, void* ws, FewKeys* few, void** scratch,
+                                    hipStream_t stream) {
   const EncWs w = enc_single_ws(d);
   uint8_t* base = (uint8_t*)ws;
-  double* part = (double*)(base + w.off_part);
-  *part_out = part;
-  hipError_t err;
-  if (!prepared && (err = launch_encode_single_prepare(d, codebook, weights, mode, ws, stream)) != hipSuccess)
-    return err;
-  const uint32_t n_all = (uint32_t)((size_t)d.batch * d.n_kv_heads * n_new);
-  hipLaunchKernelGGL(encode_single_sweep_kernel, dim3(n_all, kSlices), dim3(kSweepThreads), 0, stream, keys,
-                     (const Center*)(base + w.off_center), (const double*)(base + w.off_wT),
-                     (const double*)(base + w.off_chalf), part, d.n_kv_heads,
-                     n_new);
+  few->keys = keys;
+  few->mu = ((const Center*)(base + w.off_center))->mu;
+  few->mu_stride = sizeof(Center) / sizeof(float);
+  few->heff = (const double*)(base + w.off_heff);
+  few->sd = (const double*)(base + w.off_sd);
+  few->chalf = (const double*)(base + w.off_chalf);
+  few->part = (double*)(base + w.off_part);
+  few->mode = mode;
+  few->n_new = n_new;
+  *scratch = base + w.off_list;
+  return prepared ? hipSuccess : launch_encode_single_prepare(d, codebook, weights, mode, ws, stream);
+}
+
+// The sweep of a key at a time, whose results are in few.part.
+static hipError_t launch_sweep_by_key(const a2ats_dims& d, const FewKeys& few, const void* ws, hipStream_t stream) {
+  const EncWs w = enc_single_ws(d);
+  const uint8_t* base = (const uint8_t*)ws;
+  hipLaunchKernelGGL(encode_single_sweep_kernel, dim3((unsigned)((size_t)d.batch * d.n_kv_heads * few.n_new), kSlices),
+                     dim3(kSweepThreads), 0, stream, few.keys, (const Center*)(base + w.off_center),
+                     (const double*)(base + w.off_wT), (const double*)(base + w.off_chalf), few.part, d.n_kv_heads, few.n_new);
   return hipGetLastError();
+}
+
+static hipError_t launch_pick(const a2ats_dims& d, const FewKeys& few, void* codes, int pos0, hipStream_t stream) {
+  const uint32_t n_all = (uint32_t)((size_t)d.batch * d.n_kv_heads * few.n_new);
+  hipLaunchKernelGGL(encode_single_sweep_pick_kernel, dim3((n_all + 63) / 64), dim3(64), 0, stream, few.part,
+                     (uint16_t*)codes, n_all, few.n_new, pos0, d.ctx_stride);
+  return hipGetLastError();
+}
+
+// The keys swept with the tables and picked by a launch of their own, or swept one by one before the tables, whose
+// launch picks: one key of 8 KV heads 15.4 us the second way, 16.5 the first; of 4 sequences 21.7 and 17.2.
+hipError_t launch_decode_prologue_single(const a2ats_dims& d, const float* keys, int n_new, int pos0, const float* codebook,
+                                         const float* weights, int mode, bool prepared, void* codes, const void* q,
+                                         int q_dtype, const float* cos_b, const float* sin_b, float* q_rot, int32_t* lut,
+                                         float* lut_scale, void* ws, hipStream_t stream) {
+  FewKeys few{};
+  void* scratch;
+  hipError_t err = launch_encode_single_few(d, keys, n_new, codebook, weights, mode, prepared, ws, &few, &scratch, stream);
+  if (err != hipSuccess) return err;
+  if ((long)d.batch * d.n_kv_heads * n_new <= 8) {
+    if ((err = launch_sweep_by_key(d, few, ws, stream)) != hipSuccess) return err;
+    return launch_build_lut_single(d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale, false, FewKeys{},
+                                   FewKeyPick{few.part, (uint16_t*)codes, n_new, pos0}, stream);
+  }
+  err = launch_build_lut_single(d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale, false, few, FewKeyPick{},
+                                stream);
+  return err == hipSuccess ? launch_pick(d, few, codes, pos0, stream) : err;
 }
 
 hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_new, int pos0,
                                 const float* codebook, const float* weights, int mode, bool prepared, void* codes,
                                 void* ws, hipStream_t stream) {
   if (n_new == 0 || d.batch == 0) return hipSuccess;
+  if (n_new <= kFewSingle) {
+    FewKeys few{};
+    void* scratch;
+    hipError_t err = launch_encode_single_few(d, keys, n_new, codebook, weights, mode, prepared, ws, &few, &scratch, stream);
+    if (err != hipSuccess) return err;
+    // The sweep of prepared rows takes a key at a time, the other one 16 at a time, with a product more ahead: one key of 8 KV
+    // heads 10.9 us against 16.1, of 4 sequences 12.8 against 16.7, but 8 keys of these 70 against 19.5.  The line is where
+    // the first has more workgroups than two a CU.
+    err = (long)d.batch * d.n_kv_heads * n_new * kSlices <= 512 ? launch_sweep_by_key(d, few, ws, stream)
+                                                                : launch_sweep_single(d, codebook, few, stream);
+    return err == hipSuccess ? launch_pick(d, few, codes, pos0, stream) : err;
+  }
   const EncWs w = enc_single_ws(d);
   uint8_t* base = (uint8_t*)ws;
   double* Lmat = (double*)(base + w.off_L);
@@ -1357,21 +1412,12 @@ hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_ne
   uint32_t* counter = (uint32_t*)(base + w.off_count);
   uint32_t* near = (uint32_t*)(base + w.off_near);
   uint32_t* list = (uint32_t*)(base + w.off_list);
-  double* part = (double*)(base + w.off_part);
   const int Hkv = d.n_kv_heads, bkv = d.batch * Hkv;
   hipError_t err;
   if (!prepared && (err = launch_encode_single_prepare(d, codebook, weights, mode, ws, stream)) != hipSuccess)
     return err;
 
   const uint32_t n_all = (uint32_t)((size_t)bkv * n_new);
-  if (n_new <= kFewSingle) {
-    hipLaunchKernelGGL(encode_single_sweep_kernel, dim3(n_all, kSlices), dim3(kSweepThreads), 0, stream, keys, center,
-                       (const double*)(base + w.off_wT), (const double*)(base + w.off_chalf), part, Hkv, n_new);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    hipLaunchKernelGGL(encode_single_sweep_pick_kernel, dim3((n_all + 63) / 64), dim3(64), 0, stream, part,
-                       (uint16_t*)codes, n_all, n_new, pos0, d.ctx_stride);
-    return hipGetLastError();
-  }
   hipLaunchKernelGGL(encode_single_clear_kernel, dim3(1), dim3(1024), 0, stream, counter,
                      (int)(1 + Hkv + Hkv * near_groups(d)));
   if ((err = hipGetLastError()) != hipSuccess) return err;

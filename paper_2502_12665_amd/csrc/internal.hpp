@@ -105,10 +105,27 @@ inline bool single_codebook(const a2ats_dims& d) {
 }
 // The few-key route of the single-codebook encoder decides a key in two steps: kEncodeSlices
 // workgroups each find the best codeword of their slice ("sweep": part[key][slice] = {value, code}),
-// then the smallest of the slices is picked.  `pick` hands the second step to the table-build
-// kernel, which follows the sweep in the fused decode prologue.
+// then the smallest of the slices is picked.
 constexpr int kEncodeSlices = 16;
 constexpr int kFewSingleKeys = 8;   // at most this many keys per (sequence, KV head) take that route
+// The keys appended in a decode step, for the launch that builds the tables: it sweeps the same codewords.  The pointers
+// are into the prepared part of the encoder's workspace, and `part`.
+struct FewKeys {
+  const float* keys;    // [B * Hkv][n_new][128]; nullptr: none
+  const float* mu;      // centre of the codewords of a KV head
+  const double* heff;   // L L^T
+  const double* sd;     // (without a matrix) square roots of the weights
+  const double* chalf;  // 1/2 |c^z|^2
+  double* part;
+  int mu_stride;        // floats from a KV head's centre to the next
+  int mode, n_new;
+};
+// Prepares the codewords if they are not, and says where FewKeys' inputs are; *scratch: memory behind the prepared part.
+hipError_t launch_encode_single_few(const a2ats_dims& d, const float* keys, int n_new, const float* codebook,
+                                    const float* weights, int mode, bool prepared, void* ws, FewKeys* few, void** scratch,
+                                    hipStream_t stream);
+size_t encode_single_scratch_bytes(const a2ats_dims& d);   // of *scratch
+// The second step as part of the table build, after a launch that has swept the keys.
 struct FewKeyPick {
   const double* part;   // nullptr: nothing to pick
   uint16_t* codes;
@@ -116,11 +133,23 @@ struct FewKeyPick {
 };
 hipError_t launch_build_lut_single(const a2ats_dims& d, const void* q, int q_dtype, const float* cos_b,
                                    const float* sin_b, const float* codebook, float* q_rot, int32_t* lut,
-                                   float* lut_scale, bool shared, FewKeyPick pick, hipStream_t stream);
-// The sweep alone (n_new <= kFewSingleKeys); returns where its results are in *part.
-hipError_t launch_encode_single_sweep(const a2ats_dims& d, const float* keys, int n_new, const float* codebook,
-                                      const float* weights, int mode, bool prepared, void* ws,
-                                      const double** part, hipStream_t stream);
+                                   float* lut_scale, bool shared, const FewKeys& few, const FewKeyPick& pick,
+                                   hipStream_t stream);
+// a2ats_decode_prologue of n_new >= 1 keys.
+hipError_t launch_decode_prologue_single(const a2ats_dims& d, const float* keys, int n_new, int pos0, const float* codebook,
+                                         const float* weights, int mode, bool prepared, void* codes, const void* q,
+                                         int q_dtype, const float* cos_b, const float* sin_b, float* q_rot, int32_t* lut,
+                                         float* lut_scale, void* ws, hipStream_t stream);
+// The sweep alone.
+hipError_t launch_sweep_single(const a2ats_dims& d, const float* codebook, const FewKeys& few, hipStream_t stream);
+// Tables, appended keys and selection in two launches; no appended row may be a candidate.  scratch holds the counts of
+// the sequences' chunks.
+bool select_chunks_single_fits(const a2ats_dims& d, int window, int n_sink, size_t scratch_bytes);
+hipError_t launch_decode_select_single(const a2ats_dims& d, const void* q, int q_dtype, const float* cos_b,
+                                       const float* sin_b, const float* codebook, float* q_rot, int32_t* lut,
+                                       float* lut_scale, const FewKeys& few, int pos0, void* codes, int top_k, int window,
+                                       int n_sink, const int32_t* seq_lens, int32_t* topk_idx, int32_t* topk_count,
+                                       float* topk_score, void* scratch, hipStream_t stream);
 hipError_t launch_score_topk_single(const a2ats_dims& d, const void* codes, const int32_t* lut, int top_k,
                                     int window, int n_sink, const int32_t* seq_lens, int32_t* topk_idx,
                                     int32_t* topk_count, float* topk_score, float* scores_out,

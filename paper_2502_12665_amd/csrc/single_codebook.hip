@@ -6,11 +6,17 @@
 //
 //   build_lut_single_kernel    q~ = q R_b and the 4096 scores q~ . c per head, float64 inner
 //                              products rounded once to float32 and stored as order-preserving
-//                              32-bit keys (no fixed-point scale is needed: a score is one entry)
-//   select_single_kernel       exact top-K per head: candidates counted per codeword, a weighted
-//                              selection over the 4096 codewords, then one ordered pass that emits
-//                              the winners in ascending position, equal scores to the lower position
+//                              32-bit keys (no fixed-point scale is needed: a score is one entry);
+//                              in other workgroups the same sweep for a few appended keys, and the
+//                              candidates per codeword
+//   select_chunks_single_kernel  exact top-K of a head from those counts, by a workgroup per chunk of
+//                              the sequence (a2ats_decode_select)
+//   select_single_kernel       exact top-K per head without them: candidates counted per codeword, a
+//                              weighted selection over the 4096 codewords, then one ordered pass that
+//                              emits the winners in ascending position, equal scores to the lower position
 // (the key encoder of this geometry lives in encode_single.hip)
+#include <algorithm>
+
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -18,6 +24,16 @@ namespace a2ats {
 
 constexpr int kCodewords = 4096;
 constexpr int kSD = 128;   // head dimension = subspace dimension
+constexpr int kLutChunk = kCodewords / kEncodeSlices;   // codewords of a table workgroup
+static_assert(kLutChunk == 256, "a thread per codeword of the chunk writes the entries");
+constexpr int kMaxChunk = 16384;   // tokens of a chunk of a sequence whose codewords are counted, at most (16-bit counts)
+struct CodeCount {
+  uint16_t* counts;   // [B * Hkv][chunks][codeword]
+  uint2* ranges;      // [B * Hq][table workgroup]: the largest of the complements of the keys, and of the keys
+  GridMap gm;         // of (sequence and KV head, chunk)
+  int tokens;         // of a chunk: a power of two, 4096 .. kMaxChunk
+  int aligned;        // the codes of every (sequence, KV head) start on 16 bytes
+};
 
 // float32 score <-> signed 32-bit key with the same order (so that the integer selection
 // machinery of the product-quantised path applies unchanged).
@@ -30,179 +46,10 @@ __device__ __forceinline__ float key_to_float(int32_t k) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Tables
+// Candidates per codeword
 // ------------------------------------------------------------------------------------------
-// float64 sum over aligned groups of 8 lanes, the same value in every lane of the group.
-template <int CTRL>
-__device__ __forceinline__ double add_dpp_f64(double x) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, false);
-  return x + __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double group8_sum_f64(double v) {
-  v = add_dpp_f64<0xB1>(v);      // quad_perm [1,0,3,2]
-  v = add_dpp_f64<0x4E>(v);      // quad_perm [2,3,0,1]
-  return add_dpp_f64<0x141>(v);  // row_half_mirror
-}
-
-constexpr int kLutChunk = 256;   // codewords per workgroup
-
-// `shared`: one table per KV head, from the float32 sum of its heads' rotated queries (selection
-// shared by the query heads of a KV head); the table array is then laid out for Hq = Hkv.
-template <bool QBF16>
-__global__ __launch_bounds__(kLutChunk) void build_lut_single_kernel(
-    const void* __restrict__ q_in, const float* __restrict__ cos_b, const float* __restrict__ sin_b,
-    const float* __restrict__ codebook, float* __restrict__ q_rot, int32_t* __restrict__ lut,
-    float* __restrict__ lut_scale, int Hq, int Hkv, int shared, FewKeyPick pick, int64_t ctx_stride) {
-  constexpr int HALF = kSD / 2;
-  __shared__ __align__(16) float s_q[8][kSD];   // q~ of the (up to) 8 query heads of this KV head
-  __shared__ int32_t s_out[8][kLutChunk];       // the chunk's table entries, written out in one coalesced pass
-  const int chunk = blockIdx.x, bkv = blockIdx.y, b = bkv / Hkv, kv = bkv % Hkv;
-  const int G = Hq / Hkv, tid = threadIdx.x;
-  for (int i = tid; i < G * HALF; i += kLutChunk) {
-    const int g = i / HALF, t = i % HALF;
-    const size_t base = ((size_t)b * Hq + kv * G + g) * kSD;
-    double x1, x2;
-    if (QBF16) {
-      const uint16_t* qp = (const uint16_t*)q_in;
-      x1 = (double)bf16_to_f32(qp[base + t]);
-      x2 = (double)bf16_to_f32(qp[base + t + HALF]);
-    } else {
-      const float* qp = (const float*)q_in;
-      x1 = (double)qp[base + t];
-      x2 = (double)qp[base + t + HALF];
-    }
-    const double c = (double)cos_b[t], s = (double)sin_b[t];
-    const float o1 = (float)(x1 * c - x2 * s), o2 = (float)(x2 * c + x1 * s);
-    s_q[g][t] = o1;
-    s_q[g][t + HALF] = o2;
-    if (chunk == 0) {
-      q_rot[base + t] = o1;
-      q_rot[base + t + HALF] = o2;
-      if (t == 0 && !shared) lut_scale[(size_t)b * Hq + kv * G + g] = 1.f;
-    }
-  }
-  __syncthreads();
-  if (shared) {
-    double sum = 0.0;
-    if (tid < kSD)
-      for (int g = 0; g < G; ++g) sum += (double)s_q[g][tid];
-    __syncthreads();
-    if (tid < kSD) s_q[0][tid] = (float)sum;
-    if (chunk == 0 && tid == 0) lut_scale[(size_t)b * Hkv + kv] = 1.f;
-    __syncthreads();
-  }
-  const int Gt = shared ? 1 : G, Ht = shared ? Hkv : Hq;   // table heads
-  // Eight lanes share a codeword: lane part p holds dimensions {32 i + 4 p .. + 3}, i < 4, so that one
-  // load instruction of a wave reads eight whole 128-byte lines (a lane reading its own 512-byte row
-  // touches 64 lines per instruction and the rows of the waves of a CU evict each other from the
-  // vector cache).  A lane row handles 8 consecutive codewords, one per pass; the query (as float64,
-  // four heads at a time) stays in registers across the passes.
-  const int lane = tid & 63, wave = tid >> 6, p = lane & 7, r = lane >> 3;
-  const int cl0 = wave * 64 + r * 8;   // first of this lane row's codewords, within the chunk
-  const float* cw0 = codebook + ((size_t)kv * kCodewords + chunk * kLutChunk + cl0) * kSD + 4 * p;
-#pragma unroll 1
-  for (int g0 = 0; g0 < Gt; g0 += 4) {
-    double qd[4][16];
-#pragma unroll
-    for (int gg = 0; gg < 4; ++gg) {
-      const int g = g0 + gg < Gt ? g0 + gg : g0;   // a head past the end repeats the first; its result is dropped
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float4 f = *(const float4*)&s_q[g][32 * i + 4 * p];
-        qd[gg][4 * i] = (double)f.x;
-        qd[gg][4 * i + 1] = (double)f.y;
-        qd[gg][4 * i + 2] = (double)f.z;
-        qd[gg][4 * i + 3] = (double)f.w;
-      }
-    }
-#pragma unroll 1
-    for (int half = 0; half < 2; ++half) {
-      float4 row[4][4];
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) row[jj][i] = *(const float4*)(cw0 + (size_t)(4 * half + jj) * kSD + 32 * i);
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const double c0 = (double)row[jj][i].x, c1 = (double)row[jj][i].y, c2 = (double)row[jj][i].z,
-                       c3 = (double)row[jj][i].w;
-#pragma unroll
-          for (int gg = 0; gg < 4; ++gg)
-            acc[gg] += qd[gg][4 * i] * c0 + qd[gg][4 * i + 1] * c1 + qd[gg][4 * i + 2] * c2 + qd[gg][4 * i + 3] * c3;
-        }
-#pragma unroll
-        for (int gg = 0; gg < 4; ++gg) {
-          const double tot = group8_sum_f64(acc[gg]);
-          if (p == gg && g0 + gg < Gt) s_out[g0 + gg][cl0 + 4 * half + jj] = float_to_key((float)tot);
-        }
-      }
-    }
-  }
-  __syncthreads();
-  for (int g = 0; g < Gt; ++g)
-    lut[((size_t)b * Ht + kv * Gt + g) * kCodewords + chunk * kLutChunk + tid] = s_out[g][tid];
-  // Fused decode prologue: the launch before this one swept the codewords for the keys appended in
-  // this step; the first workgroup of a (sequence, KV head) picks the smallest of the slices for each
-  // of its keys (slices hold ascending codes: strict < keeps the lower code on equal values).
-  if (pick.part && chunk == 0 && tid < pick.n_new) {
-    const double* mine = pick.part + ((size_t)bkv * pick.n_new + tid) * kEncodeSlices * 2;
-    double best = mine[0];
-    int arg = (int)mine[1];
-    for (int sl = 1; sl < kEncodeSlices; ++sl) {
-      const double dv = mine[2 * sl];
-      if (dv < best) {
-        best = dv;
-        arg = (int)mine[2 * sl + 1];
-      }
-    }
-    pick.codes[(size_t)bkv * ctx_stride + pick.pos0 + tid] = (uint16_t)arg;
-  }
-}
-
-hipError_t launch_build_lut_single(const a2ats_dims& d, const void* q, int q_dtype, const float* cos_b,
-                                   const float* sin_b, const float* codebook, float* q_rot, int32_t* lut,
-                                   float* lut_scale, bool shared, FewKeyPick pick, hipStream_t stream) {
-  const dim3 grid(kCodewords / kLutChunk, d.batch * d.n_kv_heads), block(kLutChunk);
-  if (grid.y == 0) return hipSuccess;
-  if (q_dtype == A2ATS_BF16)
-    hipLaunchKernelGGL((build_lut_single_kernel<true>), grid, block, 0, stream, q, cos_b, sin_b, codebook,
-                       q_rot, lut, lut_scale, d.n_q_heads, d.n_kv_heads, shared ? 1 : 0, pick, d.ctx_stride);
-  else
-    hipLaunchKernelGGL((build_lut_single_kernel<false>), grid, block, 0, stream, q, cos_b, sin_b, codebook,
-                       q_rot, lut, lut_scale, d.n_q_heads, d.n_kv_heads, shared ? 1 : 0, pick, d.ctx_stride);
-  return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------------
-// Selection
-// ------------------------------------------------------------------------------------------
-constexpr int kSelThreads = 512;
-constexpr int kPerThread = 8;                       // consecutive tokens per thread and round
-constexpr int kRound = kSelThreads * kPerThread;    // tokens per round
-
-constexpr int kSpan = 32;                           // rounds a thread keeps in registers
-constexpr int kSpanTokens = kSpan * kRound;         // 131072
-constexpr int kSelWaves = kSelThreads / 64;
-constexpr int kSmallSel = 128;                      // a K-th-key bin of at most this many codewords is finished by counting
-
-struct SelLds {
-  int32_t table[kCodewords];    // the head's scores as order-preserving keys
-  uint32_t count[kCodewords];   // candidate tokens per codeword
-  uint32_t hist[kHistBins];
-  uint32_t wave_tot[kSpan][kSelWaves];   // packed (above, equal) counts per round and wave
-  uint32_t wave_pre[kSpan][kSelWaves];   // ... exclusive over the waves of a round
-  uint32_t round_tot[kSpan];
-  uint32_t wave_a[kSelWaves];
-  uint32_t res[2];
-  uint32_t kmin, kmax;
-  uint32_t small_n;                 // codewords in the bin of the K-th key after a radix level
-  uint32_t small_key[kSmallSel], small_w[kSmallSel];
-  uint8_t cls[kCodewords];          // per codeword: 1 = above the K-th key, 2 = equal to it, 0 = below
-};
+constexpr int kPerThread = 8;                       // consecutive tokens of one load
+constexpr int kCountThreads = 512;
 
 // The codes of tokens [j0, j0 + 8) of a sequence.  Branch-free: a start beyond the row is moved
 // back into it (the caller masks such tokens by position), so every load is unconditional and a
@@ -225,6 +72,412 @@ __device__ __forceinline__ uint32_t valid_mask8(int j0, int lo, int hi) {
   const int a = min(max(lo - j0, 0), kPerThread), e = min(max(hi - j0, 0), kPerThread);
   return ((1u << e) - 1u) & ~((1u << a) - 1u);
 }
+
+// Whether every load of 8 codes may be one of 16 bytes.
+static bool codes_aligned(const a2ats_dims& d, const void* codes) {
+  return (((uintptr_t)codes) & 15u) == 0 && d.ctx_stride % kPerThread == 0 && d.ctx_stride >= kPerThread;
+}
+
+// Where the candidates of a sequence start being counted: rounds start on a multiple of 8 tokens.
+__device__ __forceinline__ int first_token(const SeqRange& sr) { return sr.sink_end & ~(kPerThread - 1); }
+
+// The sequence of a KV head in chunks of cc.tokens tokens, one workgroup (kCountThreads threads) each: counts[bkv][chunk][codeword].
+// Chunks past the candidates and those of sequences that select everything are left out.
+__device__ __forceinline__ void count_codes_body(int block, const CodeCount& cc, uint32_t* s_count,
+                                                 const uint16_t* __restrict__ codes, const int32_t* __restrict__ seq_lens,
+                                                 int Hkv, int ctx_len, int64_t ctx_stride, int top_k, int window,
+                                                 int n_sink) {
+  constexpr int NT = kCountThreads, kRounds = kMaxChunk / (NT * kPerThread);
+  int bkv, chunk;
+  map_block((uint32_t)block, cc.gm, bkv, chunk);
+  const int tid = threadIdx.x, b = bkv / Hkv;
+  const SeqRange sr = seq_range(ctx_len, seq_lens, b, window, n_sink, top_k);
+  const int lo = sr.sink_end, hi = sr.win_start, s0 = first_token(sr) + chunk * cc.tokens;
+  if (s0 >= hi || sr.kk == 0 || sr.kk >= sr.ncand) return;
+  const uint16_t* seq_codes = codes + (size_t)bkv * ctx_stride;
+  const int row_len = (int)ctx_stride, rounds = cc.tokens / (NT * kPerThread);
+  uint4 cv[kRounds];
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const int j0 = s0 + (min(r, rounds - 1) * NT + tid) * kPerThread;
+    cv[r] = cc.aligned ? load_codes8<true>(seq_codes, j0, row_len) : load_codes8<false>(seq_codes, j0, row_len);
+  }
+  for (int i = tid; i < kCodewords / 4; i += NT) ((uint4*)s_count)[i] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    if (r >= rounds) break;   // (uniform)
+    const uint32_t vm = valid_mask8(s0 + (r * NT + tid) * kPerThread, lo, hi);
+#pragma unroll
+    for (int i = 0; i < kPerThread; ++i)
+      if ((vm >> i) & 1u) atomicAdd(&s_count[code_of(cv[r], i)], 1u);
+  }
+  __syncthreads();
+  uint4* out = (uint4*)(cc.counts + ((size_t)bkv * cc.gm.parts.d + chunk) * kCodewords);
+  for (int i = tid; i < kCodewords / 8; i += NT) {   // (at most kMaxChunk tokens: 16 bits)
+    const uint4 x = ((const uint4*)s_count)[2 * i], y = ((const uint4*)s_count)[2 * i + 1];
+    out[i] = make_uint4(x.x | x.y << 16, x.z | x.w << 16, y.x | y.y << 16, y.z | y.w << 16);
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// Tables
+// ------------------------------------------------------------------------------------------
+// The sweep of 256 codewords against up to 16 vectors on the float64 matrix cores (16 x 16 x 4): a row of the product is a
+// vector, from LDS, a column a codeword, from memory.  The inner dimension is taken in the order 16 i + 4 k + e (lane quarter
+// k, step 4 i + e), so that a lane's share of a codeword is eight 16-byte loads; a wave takes two tiles of 16 codewords.
+//
+// Tables: the vectors are rotated queries, of any sequences (they have the codebook in common); `shared`: one table per KV
+// head, from the float32 sum of its heads' rotated queries (the table array is then laid out for Hq = Hkv).
+// Appended keys: up to a constant of the key, the distortion of codeword c is 1/2 |c^z|^2 - (k - mu) H (c - mu)^T, so a key is
+// the vector u = (k - mu) H, a product by itself (128 KB of H for 16 keys).  part[key][chunk] = {smallest value, its code}.
+// Counts: candidates per codeword of the chunks of the sequences.
+// The three kinds of workgroup have nothing to do with each other.
+//
+// What bounds it: latency.  4 sequences of 131072 tokens, 8 KV heads, one key each, tables, keys and counts: 16.8 us (a launch
+// for the keys 11.5 and one for the tables 11.0 before, the counting in the selection), of which u takes 3.3, a sweep 4.6
+// (64 products of a wave, two waves a SIMD; a thread's dimensions on the vector ALU, eight lanes a codeword, took 10), the
+// first loads 2.5 to 3.8.  Tables alone: 32 sequences of 32 heads 52 -> 28 us, one sequence of 4 heads 8.3 -> 8.9.
+constexpr int kTabThreads = 512, kTabTiles = kLutChunk / (16 * kTabThreads / 64);
+static_assert(kTabTiles == 2, "a wave's codewords");
+typedef __attribute__((ext_vector_type(4))) double f64x4;
+
+struct TabLds {
+  union {
+    double v[kSD * 16];               // [dimension][vector], see tab_slot
+    uint32_t count[kCodewords];
+  };
+  double mu[kSD];
+  uint32_t range[2][16];            // of the vectors
+  uint64_t best[16];                // of the keys: the smallest value, and the lowest code that has it
+  int32_t arg[16];
+};
+// Where dimension d of vector `row` lies: the dimensions that the quarters of a wave read together are on different halves of
+// the banks.
+__device__ __forceinline__ int tab_slot(int d, int row) { return ((d ^ ((d >> 2) & 1)) << 4) | row; }
+
+// acc[t]: rows 4 r + k (register r), column lane & 15 of tile t.  CENTRED: the codewords less L.mu.
+template <bool CENTRED>
+__device__ __forceinline__ void tab_product(const float* __restrict__ cw, const TabLds& L, f64x4 (&acc)[kTabTiles]) {
+  const int lane = threadIdx.x & 63, j = lane & 15, k = lane >> 4, wave = threadIdx.x >> 6;
+  float4 c[kTabTiles][8];
+#pragma unroll
+  for (int t = 0; t < kTabTiles; ++t)
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      c[t][i] = *(const float4*)(cw + (size_t)((wave * kTabTiles + t) * 16 + j) * kSD + 16 * i + 4 * k);
+#pragma unroll
+  for (int t = 0; t < kTabTiles; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int d = 16 * i + 4 * k + e;
+      const double a = L.v[tab_slot(d, j)];
+#pragma unroll
+      for (int t = 0; t < kTabTiles; ++t) {
+        const float4 f = c[t][i];
+        double x = (double)(e == 0 ? f.x : (e == 1 ? f.y : (e == 2 ? f.z : f.w)));
+        if (CENTRED) x -= L.mu[d];
+        acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, x, acc[t], 0, 0, 0);
+      }
+    }
+}
+
+// A number that is not a NaN as an unsigned integer of the same order (0 and -0 are one).
+__device__ __forceinline__ uint64_t ordered_bits(double x) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x + 0.0);
+  return b ^ ((uint64_t)((int64_t)b >> 63) | 0x8000000000000000ull);
+}
+// The largest of 16 lanes, in all of them.
+__device__ __forceinline__ uint32_t row16_most(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, false));
+  return v;
+}
+
+// Workgroups of build_lut_single_kernel: those of the appended keys, the tables, the counts, in this order.
+struct TabPlan {
+  int n_key, n_table;        // workgroups
+  FastDiv key_groups, table_groups;   // of 16 vectors, of a KV head
+  int per_seq;               // table heads of a sequence and KV head
+  FastDiv per_seq_div, n_new_div;
+  FewKeyPick pick;
+};
+
+// The code of key `key` of all: the smallest of its slices (they hold ascending codes: strict < keeps the lower code on equal
+// values).
+__device__ __forceinline__ uint16_t pick_code(const double* __restrict__ part, size_t key) {
+  const double* mine = part + key * kEncodeSlices * 2;
+  double best = mine[0];
+  int arg = (int)mine[1];
+#pragma unroll
+  for (int sl = 1; sl < kEncodeSlices; ++sl) {
+    const double dv = mine[2 * sl];
+    const int code = (int)mine[2 * sl + 1];
+    arg = dv < best ? code : arg;
+    best = dv < best ? dv : best;
+  }
+  return (uint16_t)arg;
+}
+
+template <bool QBF16>
+__global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void build_lut_single_kernel(
+    const void* __restrict__ q_in, const float* __restrict__ cos_b, const float* __restrict__ sin_b,
+    const float* __restrict__ codebook, float* __restrict__ q_rot, int32_t* __restrict__ lut,
+    float* __restrict__ lut_scale, int B, int Hq, int Hkv, int shared, TabPlan tp, FewKeys few, CodeCount cc,
+    const uint16_t* __restrict__ codes, const int32_t* __restrict__ seq_lens, int ctx_len, int64_t ctx_stride, int top_k,
+    int window, int n_sink) {
+  constexpr int HALF = kSD / 2, NT = kTabThreads;
+  __shared__ __align__(16) TabLds L;
+  const int tid = threadIdx.x, lane = tid & 63, j = lane & 15, k = lane >> 4, wave = tid >> 6;
+  int block = blockIdx.x;
+  if (block >= tp.n_key + tp.n_table) {
+    if (tp.pick.part) {   // (one workgroup, beside the tables: at the end of one of theirs it takes 1.5 us more)
+      for (int i = tid; i < B * Hkv * tp.pick.n_new; i += NT) {
+        const int bkv = i / tp.pick.n_new, t = i % tp.pick.n_new;
+        tp.pick.codes[(size_t)bkv * ctx_stride + tp.pick.pos0 + t] = pick_code(tp.pick.part, (size_t)i);
+      }
+      return;
+    }
+    count_codes_body(block - tp.n_key - tp.n_table, cc, L.count, codes, seq_lens, Hkv, ctx_len, ctx_stride, top_k, window,
+                     n_sink);
+    return;
+  }
+  const bool is_key = block < tp.n_key;
+  if (!is_key) block -= tp.n_key;
+  const int chunk = block % kEncodeSlices, unit = block / kEncodeSlices;
+  const FastDiv& groups = is_key ? tp.key_groups : tp.table_groups;
+  const int kv = (int)fast_div((uint32_t)unit, groups), v0 = (unit - kv * (int)groups.d) * 16;   // first vector of the group
+  const float* cw = codebook + ((size_t)kv * kCodewords + chunk * kLutChunk) * kSD;
+  f64x4 acc[kTabTiles];
+
+  if (!is_key) {
+    const int G = Hq / Hkv, per = tp.per_seq, n_vec = B * per;
+    for (int i = tid; i < 16 * HALF; i += NT) {
+      const int row = i / HALF, t = i % HALF, vec = v0 + row;
+      double s1 = 0.0, s2 = 0.0;
+      if (vec < n_vec) {
+        const int b = (int)fast_div((uint32_t)vec, tp.per_seq_div), g0 = vec - b * per;
+        const double c = (double)cos_b[t], s = (double)sin_b[t];
+        for (int g = shared ? 0 : g0; g < (shared ? G : g0 + 1); ++g) {
+          const size_t base = ((size_t)b * Hq + kv * G + g) * kSD;
+          double x1, x2;
+          if (QBF16) {
+            const uint16_t* qp = (const uint16_t*)q_in;
+            x1 = (double)bf16_to_f32(qp[base + t]);
+            x2 = (double)bf16_to_f32(qp[base + t + HALF]);
+          } else {
+            const float* qp = (const float*)q_in;
+            x1 = (double)qp[base + t];
+            x2 = (double)qp[base + t + HALF];
+          }
+          const float o1 = (float)(x1 * c - x2 * s), o2 = (float)(x2 * c + x1 * s);
+          s1 += (double)o1;
+          s2 += (double)o2;
+          if (chunk == 0) {
+            q_rot[base + t] = o1;
+            q_rot[base + t + HALF] = o2;
+          }
+        }
+        if (chunk == 0 && t == 0) lut_scale[((size_t)b * Hkv + kv) * per + g0] = 1.f;
+      }
+      L.v[tab_slot(t, row)] = (double)(float)s1;
+      L.v[tab_slot(t + HALF, row)] = (double)(float)s2;
+    }
+    __syncthreads();
+    if (cc.ranges && tid < 32) L.range[tid >> 4][tid & 15] = 0u;
+    tab_product<false>(cw, L, acc);
+    if (cc.ranges) __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int vec = v0 + 4 * r + k;
+      uint32_t key[kTabTiles];
+#pragma unroll
+      for (int t = 0; t < kTabTiles; ++t) key[t] = (uint32_t)float_to_key((float)acc[t][r]);
+      if (vec < n_vec) {   // (uniform over 16 lanes)
+        const int b = (int)fast_div((uint32_t)vec, tp.per_seq_div), g = vec - b * per;
+        int32_t* out = lut + (((size_t)b * Hkv + kv) * per + g) * kCodewords + chunk * kLutChunk + wave * kTabTiles * 16 + j;
+#pragma unroll
+        for (int t = 0; t < kTabTiles; ++t) out[16 * t] = (int32_t)key[t];
+      }
+      if (cc.ranges) {
+        uint32_t least = 0, most = 0;
+#pragma unroll
+        for (int t = 0; t < kTabTiles; ++t) {
+          least = max(least, ~score_key((int32_t)key[t]));
+          most = max(most, score_key((int32_t)key[t]));
+        }
+        least = row16_most(least);
+        most = row16_most(most);
+        if (j == 0) {
+          atomicMax(&L.range[0][4 * r + k], least);
+          atomicMax(&L.range[1][4 * r + k], most);
+        }
+      }
+    }
+    if (cc.ranges) {
+      __syncthreads();
+      const int vec = v0 + tid;
+      if (tid < 16 && vec < n_vec) {
+        const int b = (int)fast_div((uint32_t)vec, tp.per_seq_div), g = vec - b * per;
+        cc.ranges[(((size_t)b * Hkv + kv) * per + g) * kEncodeSlices + chunk] = make_uint2(L.range[0][tid], L.range[1][tid]);
+      }
+    }
+    return;
+  }
+
+  // --- appended keys
+  const int n_vec = B * few.n_new;
+  const float* mu = few.mu + (size_t)kv * few.mu_stride;
+  auto key_index = [&](int vec) {   // among all keys
+    const int b = (int)fast_div((uint32_t)vec, tp.n_new_div);
+    return (size_t)(b * Hkv + kv) * few.n_new + (vec - b * few.n_new);
+  };
+  const bool full_matrix = few.mode == A2ATS_W_BLOCK;
+  const double* h = few.heff + (size_t)kv * kSD * kSD + 16 * wave + j;
+  double hv[32];
+  if (full_matrix) {
+#pragma unroll
+    for (int i = 0; i < 32; ++i) hv[i] = h[(size_t)(16 * (i / 4) + 4 * k + i % 4) * kSD];
+  }
+  for (int i = tid; i < 16 * kSD; i += NT) {
+    const int row = i / kSD, d = i % kSD, vec = v0 + row;
+    double x = vec < n_vec ? (double)few.keys[key_index(vec) * kSD + d] - (double)mu[d] : 0.0;
+    if (!full_matrix) {
+      const double sd = few.sd[(size_t)kv * kSD + d];
+      x = x * sd * sd;
+    }
+    L.v[tab_slot(d, row)] = x;
+  }
+  if (tid < kSD) L.mu[tid] = (double)mu[tid];
+  if (tid < 16) {
+    L.best[tid] = ~0ull;
+    L.arg[tid] = kLutChunk;
+  }
+  const double* ch = few.chalf + (size_t)kv * kCodewords + chunk * kLutChunk + wave * kTabTiles * 16 + j;
+  double chalf[kTabTiles];
+#pragma unroll
+  for (int t = 0; t < kTabTiles; ++t) chalf[t] = ch[16 * t];
+  __syncthreads();
+  if (full_matrix) {   // u: a wave takes 16 of its dimensions
+    f64x4 u = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < 32; ++i)
+      u = __builtin_amdgcn_mfma_f64_16x16x4f64(L.v[tab_slot(16 * (i / 4) + 4 * k + i % 4, j)], hv[i], u, 0, 0, 0);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) L.v[tab_slot(16 * wave + j, 4 * r + k)] = u[r];
+    __syncthreads();
+  }
+  tab_product<true>(cw, L, acc);
+  // the smallest of a key's values, the lower code on equal ones (a value that is not a number is never smaller)
+  double best[4];
+  int arg[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    best[r] = INFINITY;
+    arg[r] = 0;
+#pragma unroll
+    for (int t = 0; t < kTabTiles; ++t) {
+      const double s = chalf[t] - acc[t][r];
+      if (s < best[r]) {
+        best[r] = s;
+        arg[r] = (wave * kTabTiles + t) * 16 + j;
+      }
+    }
+  }
+  uint64_t mine[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    mine[r] = ordered_bits(best[r]);
+    atomicMin((unsigned long long*)&L.best[4 * r + k], (unsigned long long)mine[r]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (mine[r] == L.best[4 * r + k]) atomicMin(&L.arg[4 * r + k], arg[r]);
+  __syncthreads();
+  if (tid < 16 && v0 + tid < n_vec) {
+    double* out = few.part + (key_index(v0 + tid) * kEncodeSlices + chunk) * 2;
+    const uint64_t o = L.best[tid];
+    out[0] = __builtin_bit_cast(double, o ^ (o >> 63 ? 0x8000000000000000ull : ~0ull));
+    out[1] = (double)(chunk * kLutChunk + L.arg[tid]);
+  }
+}
+
+// Tables (q), appended keys (few.keys) and counts (n_count workgroups), any of them or all.
+static hipError_t launch_tables_single(const a2ats_dims& d, const void* q, int q_dtype, const float* cos_b,
+                                       const float* sin_b, const float* codebook, float* q_rot, int32_t* lut,
+                                       float* lut_scale, bool shared, const FewKeys& few, const FewKeyPick& pick,
+                                       const CodeCount& cc, int n_count,
+                                       const void* codes, const int32_t* seq_lens, int top_k, int window, int n_sink,
+                                       hipStream_t stream) {
+  if (d.batch == 0) return hipSuccess;
+  TabPlan tp;
+  const int n_new = few.keys ? few.n_new : 0;
+  tp.pick = pick;
+  tp.per_seq = shared ? 1 : d.n_q_heads / d.n_kv_heads;
+  tp.per_seq_div = make_fastdiv((uint32_t)tp.per_seq);
+  tp.n_new_div = make_fastdiv((uint32_t)n_new);
+  const int key_groups = (d.batch * n_new + 15) / 16, table_groups = q ? (d.batch * tp.per_seq + 15) / 16 : 0;
+  tp.key_groups = make_fastdiv((uint32_t)key_groups);
+  tp.table_groups = make_fastdiv((uint32_t)table_groups);
+  tp.n_key = key_groups * d.n_kv_heads * kEncodeSlices;
+  tp.n_table = table_groups * d.n_kv_heads * kEncodeSlices;
+  const dim3 grid(tp.n_key + tp.n_table + n_count), block(kTabThreads);
+  if (grid.x == 0) return hipSuccess;
+  if (q_dtype == A2ATS_BF16)
+    hipLaunchKernelGGL((build_lut_single_kernel<true>), grid, block, 0, stream, q, cos_b, sin_b, codebook, q_rot, lut,
+                       lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, shared ? 1 : 0, tp, few, cc, (const uint16_t*)codes,
+                       seq_lens, d.ctx_len, d.ctx_stride, top_k, window, n_sink);
+  else
+    hipLaunchKernelGGL((build_lut_single_kernel<false>), grid, block, 0, stream, q, cos_b, sin_b, codebook, q_rot, lut,
+                       lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, shared ? 1 : 0, tp, few, cc, (const uint16_t*)codes,
+                       seq_lens, d.ctx_len, d.ctx_stride, top_k, window, n_sink);
+  return hipGetLastError();
+}
+
+hipError_t launch_build_lut_single(const a2ats_dims& d, const void* q, int q_dtype, const float* cos_b,
+                                   const float* sin_b, const float* codebook, float* q_rot, int32_t* lut,
+                                   float* lut_scale, bool shared, const FewKeys& few, const FewKeyPick& pick,
+                                   hipStream_t stream) {
+  return launch_tables_single(d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale, shared, few, pick, CodeCount{},
+                              pick.part ? 1 : 0, nullptr, nullptr, 0, 0, 0, stream);
+}
+
+hipError_t launch_sweep_single(const a2ats_dims& d, const float* codebook, const FewKeys& few, hipStream_t stream) {
+  return launch_tables_single(d, nullptr, A2ATS_F32, nullptr, nullptr, codebook, nullptr, nullptr, nullptr, false, few,
+                              FewKeyPick{}, CodeCount{}, 0, nullptr, nullptr, 0, 0, 0, stream);
+}
+
+// ------------------------------------------------------------------------------------------
+// Selection
+// ------------------------------------------------------------------------------------------
+constexpr int kSelThreads = 512;
+constexpr int kRound = kSelThreads * kPerThread;    // tokens per round
+
+constexpr int kSpan = 32;                           // rounds a thread keeps in registers
+constexpr int kSpanTokens = kSpan * kRound;         // 131072
+constexpr int kSelWaves = kSelThreads / 64;
+constexpr int kSmallSel = 128;                      // a K-th-key bin of at most this many codewords is finished by counting
+
+struct SelLds {
+  int32_t table[kCodewords];    // the head's scores as order-preserving keys
+  uint32_t count[kCodewords];   // candidate tokens per codeword
+  uint32_t hist[kHistBins];
+  uint32_t wave_tot[kSpan][kSelWaves];   // packed (above, equal) counts per round and wave
+  uint32_t wave_pre[kSpan][kSelWaves];   // ... exclusive over the waves of a round
+  uint32_t round_tot[kSpan];
+  uint32_t wave_a[kSelWaves];
+  uint32_t res[2];
+  uint32_t kmin, kmax;
+  uint32_t small_n;                 // codewords in the bin of the K-th key after a radix level
+  uint32_t small_key[kSmallSel], small_w[kSmallSel];
+  uint8_t cls[kCodewords];          // per codeword: 1 = above the K-th key, 2 = equal to it, 0 = below
+};
 
 // Bit 2i set when bit i of an 8-bit mask is.
 __device__ __forceinline__ uint32_t spread8(uint32_t m) {
@@ -515,6 +768,411 @@ __global__ __launch_bounds__(kSelThreads) void select_single_kernel(
   }
 }
 
+// ------------------------------------------------------------------------------------------
+// Selection from counts that an earlier launch has made (a2ats_decode_select)
+// ------------------------------------------------------------------------------------------
+// One workgroup per chunk of a sequence and H query heads of a KV head.  Every workgroup adds up the chunks' counts (8 KB
+// each) and finds the K-th key of its heads by itself; what the chunks before its own hold above that key and at it gives
+// the place of its first winner, so the workgroups of a head need nothing from each other.
+//
+// What bounds it: its phases one after the other; 4 sequences of 131072 tokens, 32 heads: 14.5 us, of which counts, keys and
+// codes take 4.5 to arrive, bins and K-th keys 4.5, flags and places 3.  A workgroup a head, which counts by itself and holds
+// the codes meanwhile (select_single_kernel), takes 32.5.  Steps: 90.1 -> 63.9 us.
+constexpr int kCsThreads = 512, kCsWaves = kCsThreads / 64;
+constexpr int kCsPer = kCodewords / kCsThreads;                       // codewords of a thread
+static_assert(kCsPer == 8, "a thread's counts are one 16-byte load");
+template <int H>
+struct ChunkLds {
+  uint32_t hist[H][kHistBins];
+  uint32_t flags[kCodewords];   // bit (16 / H) h: above the K-th key of head h, 16 bits further: equal to it
+  uint32_t small_key[H][kSmallSel], small_w[H][kSmallSel];
+  uint32_t bin[H], kth[H], k_rem[H], small_n[H];
+  uint32_t before_gt[H], before_eq[H];
+  uint32_t wave_tot[H][kCsWaves];
+  uint32_t wave_a[kCsWaves], res[2];
+};
+
+// The bin that holds the k-th largest of the values counted in a 2048-bin histogram, and how many lie above it, by one wave.
+__device__ __forceinline__ void wave_rank(const uint32_t* hist, uint32_t k, int lane, uint32_t& bin, uint32_t& above) {
+  uint32_t sum = 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {   // (rotated: the lanes of a read hit different banks)
+    const uint4 v = *(const uint4*)(hist + 32 * lane + 4 * ((i + lane) & 7));
+    sum += v.x + v.y + v.z + v.w;
+  }
+  const uint32_t pre = wave_inclusive_scan(sum);
+  const uint32_t inc = (uint32_t)__builtin_amdgcn_readlane((int)pre, 63) - pre + sum, higher = inc - sum;
+  const uint64_t owner = __builtin_amdgcn_ballot_w64(higher < k && k <= inc);
+  const int src = owner ? (int)__builtin_ctzll(owner) : 0;
+  const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)higher, src);
+  const uint32_t c = lane < 32 ? hist[32 * src + 31 - lane] : 0u;
+  const uint32_t incl = wave_inclusive_scan(c);
+  const uint64_t reach = __builtin_amdgcn_ballot_w64(lane < 32 && base + incl >= k);
+  const int at = reach ? (int)__builtin_ctzll(reach) : 31;
+  bin = (uint32_t)(32 * src + 31 - at);
+  above = base + (uint32_t)__builtin_amdgcn_readlane((int)(incl - c), at);
+}
+
+template <int H>
+__global__ __launch_bounds__(kCsThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void select_chunks_single_kernel(
+    uint16_t* __restrict__ codes, const int32_t* __restrict__ lut, const int32_t* __restrict__ seq_lens,
+    int32_t* __restrict__ topk_idx, int32_t* __restrict__ topk_count, float* __restrict__ topk_score, CodeCount cc,
+    GridMap gm, const double* __restrict__ part, int n_new, int pos0, int Hq, int Hkv, int ctx_len,
+    int64_t ctx_stride, int top_k, int window, int n_sink) {
+  constexpr int NT = kCsThreads, kLoads = kMaxChunk / (kCsThreads * kPerThread);
+  constexpr int kBits = 16 / H, kAcc = kLoads * kPerThread / kBits, kWords = kLoads * kPerThread / 32;   // tokens of a word of flags
+  __shared__ ChunkLds<H> L;
+  int prob, chunk, b, kv, g4;
+  map_block(blockIdx.x, gm, prob, chunk);
+  split_problem(prob, gm, b, kv, g4);
+  const int G = Hq / Hkv, n_real = min(H, G - g4 * H), bkv = b * Hkv + kv, head0 = b * Hq + kv * G + g4 * H;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const SeqRange sr = seq_range(ctx_len, seq_lens, b, window, n_sink, top_k);
+  if (chunk == 0) {
+    if (tid < n_real) topk_count[head0 + tid] = sr.kk;
+    for (int h = 0; h < n_real; ++h)
+      for (int t = sr.kk + tid; t < top_k; t += NT) {
+        topk_idx[(size_t)(head0 + h) * top_k + t] = -1;
+        if (topk_score) topk_score[(size_t)(head0 + h) * top_k + t] = 0.f;
+      }
+    // The codes of the keys appended in this step, which the launch before has swept.  No candidate is among them.
+    if (g4 == 0 && tid < n_new)
+      codes[(size_t)bkv * ctx_stride + pos0 + tid] = pick_code(part, (size_t)bkv * n_new + tid);
+  }
+  const int lo = sr.sink_end, hi = sr.win_start, first = first_token(sr), s0 = first + chunk * cc.tokens;
+  if (sr.kk == 0 || s0 >= hi) return;
+  const uint16_t* seq_codes = codes + (size_t)bkv * ctx_stride;
+  const int row_len = (int)ctx_stride, loads = cc.tokens / (NT * kPerThread);   // 1 .. kLoads
+  const int j0 = s0 + tid * loads * kPerThread;   // this thread's tokens follow each other
+  const bool take_all = sr.kk >= sr.ncand;
+  uint4 cv[kLoads];
+  uint32_t k_rem[H], acc[kAcc];
+#pragma unroll
+  for (int q = 0; q < kAcc; ++q) acc[q] = 0u;
+#pragma unroll
+  for (int h = 0; h < H; ++h) k_rem[h] = 0u;
+
+  if (!take_all) {   // (uniform, as the conditions on n_real and n_part below)
+    // --- this thread's 8 codewords: their counts in all chunks and in those before this one, and their keys
+    const int n_part = (hi - first + cc.tokens - 1) / cc.tokens;
+    const uint4* cnt = (const uint4*)(cc.counts + (size_t)bkv * cc.gm.parts.d * kCodewords) + tid;
+    int32_t tv[H][kCsPer];
+    uint2 range[H];
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      if (h >= n_real) break;
+      range[h] = cc.ranges[(size_t)(head0 + h) * kEncodeSlices + (lane & (kEncodeSlices - 1))];
+      const int4* t = (const int4*)(lut + (size_t)(head0 + h) * kCodewords) + 2 * tid;
+      const int4 x = t[0], y = t[1];
+      tv[h][0] = x.x, tv[h][1] = x.y, tv[h][2] = x.z, tv[h][3] = x.w;
+      tv[h][4] = y.x, tv[h][5] = y.y, tv[h][6] = y.z, tv[h][7] = y.w;
+    }
+    uint32_t tot[kCsPer], before[kCsPer];
+#pragma unroll
+    for (int i = 0; i < kCsPer; ++i) tot[i] = before[i] = 0u;
+#pragma unroll 1
+    for (int p0 = 0; p0 < n_part; p0 += 4) {
+      uint4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = cnt[(size_t)min(p0 + u, n_part - 1) * (kCodewords / 8)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+        const uint32_t in = p0 + u < n_part ? 0xffffu : 0u, pre = p0 + u < chunk ? 0xffffu : 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          tot[2 * i] += w[i] & in;
+          tot[2 * i + 1] += (w[i] >> 16) & in;
+          before[2 * i] += w[i] & pre;
+          before[2 * i + 1] += (w[i] >> 16) & pre;
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kLoads; ++r)
+      if (r < loads)
+        cv[r] = cc.aligned ? load_codes8<true>(seq_codes, j0 + r * kPerThread, row_len)
+                           : load_codes8<false>(seq_codes, j0 + r * kPerThread, row_len);
+    for (int i = tid; i < H * kHistBins / 4; i += NT) ((uint4*)&L.hist[0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid < H) {
+      L.small_n[tid] = 0u;
+      L.before_gt[tid] = 0u;
+      L.before_eq[tid] = 0u;
+    }
+    __syncthreads();
+    // --- a level of 2048 bins linear in the score, as in select_single_kernel
+    float s_lo[H], lin_scale[H];
+    uint32_t use_lin = 0, k_lo[H], k_hi[H];
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      if (h >= n_real) break;
+      const uint2 mine = range[h];
+      k_lo[h] = ~(uint32_t)__builtin_amdgcn_readfirstlane((int)row16_most(mine.x));
+      k_hi[h] = (uint32_t)__builtin_amdgcn_readfirstlane((int)row16_most(mine.y));
+      s_lo[h] = key_to_float(key_score(k_lo[h]));
+      const float span = key_to_float(key_score(k_hi[h])) - s_lo[h];
+      const bool ok = span >= 1e-30f && span < INFINITY;
+      lin_scale[h] = ok ? (float)kHistBins / span : 0.f;
+      use_lin |= ok ? 1u << h : 0u;
+    }
+    auto lin_bin = [&](int h, int i) {
+      return (uint32_t)min((int)((key_to_float(tv[h][i]) - s_lo[h]) * lin_scale[h]), kHistBins - 1);
+    };
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      if (h >= n_real) break;
+      if ((use_lin >> h) & 1u) {
+#pragma unroll
+        for (int i = 0; i < kCsPer; ++i)
+          if (tot[i]) atomicAdd(&L.hist[h][lin_bin(h, i)], tot[i]);
+      }
+    }
+    __syncthreads();
+    if (wave < n_real && ((use_lin >> wave) & 1u)) {
+      uint32_t bin, above;
+      wave_rank(L.hist[wave], (uint32_t)sr.kk, lane, bin, above);
+      if (lane == 0) {
+        L.bin[wave] = bin;
+        L.k_rem[wave] = (uint32_t)sr.kk - above;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      if (h >= n_real) break;
+      if ((use_lin >> h) & 1u) {
+        const uint32_t bin = L.bin[h];
+#pragma unroll
+        for (int i = 0; i < kCsPer; ++i)
+          if (tot[i] && lin_bin(h, i) == bin) {
+            const uint32_t at = atomicAdd(&L.small_n[h], 1u);
+            if (at < (uint32_t)kSmallSel) {
+              L.small_key[h][at] = score_key(tv[h][i]);
+              L.small_w[h][at] = tot[i];
+            }
+          }
+      }
+    }
+    __syncthreads();
+    if (wave < n_real && ((use_lin >> wave) & 1u)) {
+      const uint32_t n_small = L.small_n[wave], rem = L.k_rem[wave];
+      if (n_small <= (uint32_t)kSmallSel) {
+        for (uint32_t m = lane; m < n_small; m += 64) {
+          const uint32_t key = L.small_key[wave][m];
+          uint32_t gt = 0, eq = 0;
+          for (uint32_t u = 0; u < n_small; ++u) {
+            const uint32_t ku = L.small_key[wave][u], wu = L.small_w[wave][u];
+            gt += ku > key ? wu : 0u;
+            eq += ku == key ? wu : 0u;
+          }
+          if (gt < rem && rem <= gt + eq) {   // every member at the K-th key writes the same two words
+            L.kth[wave] = key;
+            L.k_rem[wave] = rem - gt;   // (read by all lanes above)
+          }
+        }
+      }
+    }
+    __syncthreads();
+    // --- a crowded bin, or a table whose range is empty or not finite: an MSB-first radix select on the keys
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      if (h >= n_real) break;
+      const bool lin = (use_lin >> h) & 1u;
+      if (lin && L.small_n[h] <= (uint32_t)kSmallSel) continue;   // (uniform)
+      const uint32_t bin1 = lin ? L.bin[h] : 0u;
+      uint32_t rem = lin ? L.k_rem[h] : (uint32_t)sr.kk, prefix = 0, mask = 0;
+      int remaining = 32 - __clz(k_hi[h] - k_lo[h]);
+#pragma unroll 1
+      while (remaining > 0) {
+        const int bits = remaining < 11 ? remaining : 11, shift = remaining - bits;
+        const uint32_t dmask = (1u << bits) - 1u;
+        __syncthreads();   // the histogram may still be read
+        for (int i = tid; i < kHistBins; i += NT) L.hist[h][i] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kCsPer; ++i) {
+          const uint32_t rel = score_key(tv[h][i]) - k_lo[h];
+          if (tot[i] && (!lin || lin_bin(h, i) == bin1) && (rel & mask) == prefix)
+            atomicAdd(&L.hist[h][(rel >> shift) & dmask], tot[i]);
+        }
+        __syncthreads();
+        block_find_rank_desc<NT, kHistBins>([&](int i) { return L.hist[h][i]; }, rem, L.wave_a, L.res);
+        rem -= L.res[1];
+        prefix |= L.res[0] << shift;
+        mask |= dmask << shift;
+        remaining = shift;
+      }
+      __syncthreads();
+      if (tid == 0) {
+        L.kth[h] = prefix + k_lo[h];
+        L.k_rem[h] = rem;
+      }
+      __syncthreads();
+    }
+    // --- flags of the codewords, and the candidates above and at the K-th key in the chunks before
+    uint32_t fl[kCsPer];
+#pragma unroll
+    for (int i = 0; i < kCsPer; ++i) fl[i] = 0u;
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      if (h >= n_real) break;
+      const uint32_t kth = L.kth[h];
+      k_rem[h] = L.k_rem[h];
+      uint32_t gt = 0, eq = 0;
+#pragma unroll
+      for (int i = 0; i < kCsPer; ++i) {
+        const uint32_t key = score_key(tv[h][i]);
+        fl[i] |= key > kth ? 1u << (kBits * h) : (key == kth ? 0x10000u << (kBits * h) : 0u);
+        gt += key > kth ? before[i] : 0u;
+        eq += key == kth ? before[i] : 0u;
+      }
+      if (chunk > 0) {
+        gt = wave_inclusive_scan(gt);
+        eq = wave_inclusive_scan(eq);
+        if (lane == 63) {
+          if (gt) atomicAdd(&L.before_gt[h], gt);
+          if (eq) atomicAdd(&L.before_eq[h], eq);
+        }
+      }
+    }
+    ((uint4*)L.flags)[2 * tid] = make_uint4(fl[0], fl[1], fl[2], fl[3]);
+    ((uint4*)L.flags)[2 * tid + 1] = make_uint4(fl[4], fl[5], fl[6], fl[7]);
+    __syncthreads();
+    // --- flags of this thread's tokens, kBits of them to a word
+#pragma unroll
+    for (int r = 0; r < kLoads; ++r)
+      if (r < loads) {
+#pragma unroll
+        for (int i = 0; i < kPerThread; ++i)
+          acc[(r * kPerThread + i) / kBits] |= L.flags[code_of(cv[r], i)] << ((r * kPerThread + i) % kBits);
+      }
+  }
+  // which of them are candidates, above the K-th key, equal to it: 32 tokens a word
+  uint32_t above[H][kWords], equal[H][kWords], pre[H];
+#pragma unroll
+  for (int w = 0; w < kWords; ++w) {
+    const int a = min(max(lo - j0 - 32 * w, 0), 32), e = min(max(min(hi - j0, loads * kPerThread) - 32 * w, 0), 32);
+    const uint32_t valid = e > a ? (uint32_t)((1ull << e) - (1ull << a)) : 0u;
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      uint32_t g = 0, q_ = 0;
+#pragma unroll
+      for (int q = 0; q < 32 / kBits; ++q) {
+        const uint32_t word = acc[w * (32 / kBits) + q];
+        g |= ((word >> (kBits * h)) & ((1u << kBits) - 1u)) << (kBits * q);
+        q_ |= ((word >> (16 + kBits * h)) & ((1u << kBits) - 1u)) << (kBits * q);
+      }
+      above[h][w] = take_all ? valid : g & valid;
+      equal[h][w] = take_all ? 0u : q_ & valid;
+    }
+  }
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    if (h >= n_real) break;
+    uint32_t own = 0;
+#pragma unroll
+    for (int w = 0; w < kWords; ++w) own += (uint32_t)__popc(above[h][w]) | (uint32_t)__popc(equal[h][w]) << 16;
+    const uint32_t inc = wave_inclusive_scan(own);   // (a chunk's counts fit 16 bits)
+    pre[h] = inc - own;
+    if (lane == 63) L.wave_tot[h][wave] = inc;
+  }
+  __syncthreads();
+  // --- the winners of this chunk in ascending position
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    if (h >= n_real) break;
+    uint32_t p = pre[h];
+    for (int w = 0; w < wave; ++w) p += L.wave_tot[h][w];
+    uint32_t gt_before = (take_all ? (uint32_t)max(s0 - lo, 0) : L.before_gt[h]) + (p & 0xffffu);
+    uint32_t eq_before = (take_all ? 0u : L.before_eq[h]) + (p >> 16);
+    int32_t* oi = topk_idx + (size_t)(head0 + h) * top_k;
+#pragma unroll
+    for (int w = 0; w < kWords; ++w) {
+      uint32_t e_take = 0;
+      if (equal[h][w] && eq_before < k_rem[h]) {
+        const uint32_t room = k_rem[h] - eq_before;
+        e_take = equal[h][w];
+        if ((uint32_t)__popc(e_take) > room) {   // keep the lowest `room` set bits
+#pragma unroll 1
+          for (uint32_t drop = (uint32_t)__popc(e_take) - room; drop; --drop) e_take &= ~(0x80000000u >> __clz(e_take));
+        }
+      }
+      uint32_t m = above[h][w] | e_take, slot = gt_before + min(eq_before, k_rem[h]);
+#pragma unroll 1
+      for (; m; m &= m - 1, ++slot) {
+        const int at = j0 + 32 * w + __ffs(m) - 1;
+        if (slot < (uint32_t)sr.kk) {   // (always, of consistent counts)
+          oi[slot] = at;
+          if (topk_score)
+            topk_score[(size_t)(head0 + h) * top_k + slot] =
+                key_to_float(lut[(size_t)(head0 + h) * kCodewords + (seq_codes[at] & (kCodewords - 1))]);
+        }
+      }
+      gt_before += (uint32_t)__popc(above[h][w]);
+      eq_before += (uint32_t)__popc(equal[h][w]);
+    }
+  }
+}
+
+// How many heads a workgroup of the selection takes and how long the chunks are.  What a workgroup does whatever its chunk
+// (adding up the counts, the K-th keys) costs more than the chunk's own tokens, but less for a further head than for a first
+// one.  So the chunks are long and the heads of a workgroup few, while there are CUs for all, and shorter only where CUs
+// would be idle.  Steps of 32 query and 8 KV heads, us, heads / tokens of a workgroup: 4 sequences of 131072 tokens 1 / 8192
+// 86, 1 / 16384 69.5, 2 / 16384 64.7, 4 / 16384 66.7; one of 131072 1 / 8192 43.4, 1 / 16384 39.7, 2 / 16384 42.3; one of
+// 32768 1 / 4096 38.7, 1 / 16384 61; 64 of 16384 1 / 16384 232, 2 / 16384 228, 4 / 16384 224.
+struct ChunkPlan {
+  int heads, tokens, n;
+  size_t off_ranges, bytes;   // of the counts; of counts and ranges
+};
+static ChunkPlan plan_chunks(const a2ats_dims& d, int window, int n_sink) {
+  const int G = d.n_q_heads / d.n_kv_heads;
+  const long rows = (long)d.batch * d.n_kv_heads, win = d.ctx_len > window ? d.ctx_len - window : 0;
+  const long span = std::max<long>(1, win - (std::min<long>(n_sink, win) & ~(long)(kPerThread - 1)));
+  ChunkPlan p;
+  auto groups = [&](int heads, int tokens) { return rows * ((G + heads - 1) / heads) * ((span + tokens - 1) / tokens); };
+  p.heads = groups(1, kMaxChunk) <= 256 ? 1 : (groups(2, kMaxChunk) <= 512 ? 2 : 4);
+  p.tokens = kMaxChunk / 4;
+  while (p.tokens < kMaxChunk && groups(p.heads, p.tokens) > 256) p.tokens *= 2;
+  p.n = (int)((span + p.tokens - 1) / p.tokens);
+  p.off_ranges = (size_t)rows * p.n * kCodewords * sizeof(uint16_t);
+  p.bytes = p.off_ranges + (size_t)d.batch * d.n_q_heads * kEncodeSlices * sizeof(uint2);
+  return p;
+}
+
+bool select_chunks_single_fits(const a2ats_dims& d, int window, int n_sink, size_t scratch_bytes) {
+  return plan_chunks(d, window, n_sink).bytes <= scratch_bytes;
+}
+
+hipError_t launch_decode_select_single(const a2ats_dims& d, const void* q, int q_dtype, const float* cos_b,
+                                       const float* sin_b, const float* codebook, float* q_rot, int32_t* lut,
+                                       float* lut_scale, const FewKeys& few, int pos0, void* codes, int top_k, int window,
+                                       int n_sink, const int32_t* seq_lens, int32_t* topk_idx, int32_t* topk_count,
+                                       float* topk_score, void* scratch, hipStream_t stream) {
+  const int G = d.n_q_heads / d.n_kv_heads, rows = d.batch * d.n_kv_heads;
+  if (rows == 0) return hipSuccess;
+  const ChunkPlan p = plan_chunks(d, window, n_sink);
+  CodeCount cc;
+  cc.counts = (uint16_t*)scratch;
+  cc.ranges = (uint2*)((unsigned char*)scratch + p.off_ranges);
+  cc.gm = make_grid_map(p.n, rows, 1, d.n_kv_heads);
+  cc.tokens = p.tokens;
+  cc.aligned = codes_aligned(d, codes);
+  const hipError_t err = launch_tables_single(d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale, false, few,
+                                              FewKeyPick{}, cc, rows * p.n, codes, seq_lens, top_k, window, n_sink, stream);
+  if (err != hipSuccess) return err;
+  const int groups = (G + p.heads - 1) / p.heads;
+#define A2ATS_LAUNCH_CHUNKS(H)                                                                                          \
+  hipLaunchKernelGGL(select_chunks_single_kernel<H>, dim3(rows * groups * p.n), dim3(kCsThreads), 0, stream,            \
+                     (uint16_t*)codes, lut, seq_lens, topk_idx, topk_count, topk_score, cc,                             \
+                     make_grid_map(p.n, rows * groups, groups, d.n_kv_heads), few.part, few.keys ? few.n_new : 0, pos0, \
+                     d.n_q_heads, d.n_kv_heads, d.ctx_len, d.ctx_stride, top_k, window, n_sink)
+  if (p.heads == 1) A2ATS_LAUNCH_CHUNKS(1);
+  else if (p.heads == 2) A2ATS_LAUNCH_CHUNKS(2);
+  else A2ATS_LAUNCH_CHUNKS(4);
+#undef A2ATS_LAUNCH_CHUNKS
+  return hipGetLastError();
+}
+
 // Debug / parity: every token's score as float.
 __global__ __launch_bounds__(256) void score_dense_single_kernel(
     const uint16_t* __restrict__ codes, const int32_t* __restrict__ lut, const int32_t* __restrict__ seq_lens,
@@ -543,7 +1201,7 @@ hipError_t launch_score_topk_single(const a2ats_dims& d, const void* codes, cons
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
   }
-  const bool aligned = (((uintptr_t)codes) & 15u) == 0 && d.ctx_stride % kPerThread == 0 && d.ctx_stride >= kPerThread;
+  const bool aligned = codes_aligned(d, codes);
   if (aligned)
     hipLaunchKernelGGL(select_single_kernel<true>, dim3(heads), dim3(kSelThreads), 0, stream,
                        (const uint16_t*)codes, lut, seq_lens, topk_idx, topk_count, topk_score, d.n_q_heads,

@@ -270,3 +270,64 @@ def test_float32_attention_of_many_heads_is_as_exact_as_that_of_few(N, K, w, n_s
     whole, few = (err[0] / size) ** 0.5, (err[1] / size) ** 0.5
     H.log(f"float32 attention, {K} + {w} rows: error {whole:.3e} whole, {few:.3e} shared out")
     assert whole <= 1.1 * few and few < 4e-7
+
+
+@pytest.mark.parametrize("Bn,G,Hkv,N,K,w,n_sink,n_new,lens,stride,data", [
+    (1, 4, 1, 4096 + 16, 100, 16, 0, 1, None, 0, None),          # one head a workgroup, exactly one chunk of 4096
+    (1, 4, 1, 4097 + 16, 100, 16, 0, 2, None, 8, None),          # and one token more
+    (2, 7, 2, 9000, 777, 32, 4, 1, [9000, 4104], 5, None),       # rows that do not start on 16 bytes; an odd group
+    (2, 8, 2, 50000, 4096, 64, 3, 8, None, 0, "patterns"),       # the K-th score is shared by many tokens
+    (3, 4, 8, 70001, 1500, 128, 4, 1, [70001, 1, 33000], 7, None),   # two heads a workgroup, sequences without candidates
+    (33, 4, 8, 17000, 600, 64, 0, 1, None, 0, None),             # four heads a workgroup, two chunks of 16384
+    (17, 7, 8, 16500, 300, 64, 1, 1, [16500] * 16 + [360], 0, "patterns"),   # of which the last has three; everything selected
+    (1, 1, 2, 20000, 3000, 64, 0, 1, None, 0, "equal"),          # a table of equal scores: radix levels, lowest positions
+    (4, 4, 2, 12000, 3999, 64, 4, 3, None, 0, "crowded"),        # nearly equal scores: a crowded bin
+    (2, 4, 1, 700, 636, 64, 0, 1, None, 0, None),                # few tokens: the counts do not fit, the two calls
+    (1, 2, 1, 6000, 0, 64, 0, 1, None, 0, None),
+])
+@pytest.mark.parametrize("mode", ["none", "block"])
+def test_single_codebook_decode_select_equals_the_two_calls(Bn, G, Hkv, N, K, w, n_sink, n_new, lens, stride, data, mode):
+    """Tables, appended keys and selection from counts in two launches against prologue and selection as calls of their own:
+    every output bit for bit; no memory behind the outputs is written."""
+    wl = synth.Workload("single_select", Bn, G * Hkv, Hkv, 128, 1, N, K, w, n_sink=n_sink, n_centroids=4096, seed=N + K)
+    xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
+    if data == "patterns":
+        xd["codes"][:] = xd["codes"][:, :, torch.randint(0, 60, (N,), device="cuda")]
+    if data == "equal":
+        xd["codebook"][:] = xd["codebook"][:, :, :1]
+    if data == "crowded":
+        xd["codebook"][:, :, 1:3000] = xd["codebook"][:, :, :1] * (1 + 1e-6 * torch.rand(2999, 1, device="cuda"))
+        xd["codebook"][:, :, 500:900] = xd["codebook"][:, :, :1]
+    weights = None if mode == "none" else synth.make_query_second_moment(wl)["h_block"].cuda()
+    wmode = B.W_NONE if mode == "none" else B.W_BLOCK
+    keys = synth.make_encode_keys(wl, n_new, device="cuda", stress=True)
+    dims = H.dims_of(wl, N + stride)
+    full = torch.zeros(Bn, Hkv, N + stride, 1, dtype=xd["codes"].dtype, device="cuda")
+    full[:, :, :N] = xd["codes"]
+    sl = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
+    ws = torch.empty(B.workspace_bytes(dims, B.OP_ENCODE), dtype=torch.uint8, device="cuda")
+    res = []
+    for how in ("two calls", "one", "one, prepared"):
+        st = B.DecodeState(dims, max(K, 1), w, n_sink, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
+        st.lut.fill_(-1)
+        idx = torch.full((Bn * Hkv * G * K + 8,), -7, dtype=torch.int32, device="cuda")
+        score = torch.full((Bn * Hkv * G * K + 8,), -7.0, device="cuda")
+        codes = full.clone()
+        ws.fill_(255)
+        flag = 0
+        if how == "one, prepared":
+            B.encode_prepare(dims, xd["codebook"], weights, wmode, ws)
+            flag = B.W_PREPARED
+        args = (dims, keys, n_new, N - n_new, xd["codebook"], weights, wmode | flag, codes, xd["q"], st.cos_b, st.sin_b,
+                st.q_rot, st.lut, st.lut_scale)
+        if how == "two calls":
+            B.decode_prologue(*args, ws)
+            B.score_topk(dims, codes, st.lut, st.lut_scale, K, w, n_sink, sl, idx, st.topk_count, score, None, None)
+        else:
+            B.decode_select(*args, K, w, n_sink, sl, idx, st.topk_count, score, ws)
+        torch.cuda.synchronize()
+        res.append((codes, st.lut, st.lut_scale, st.q_rot, idx, st.topk_count, score.view(torch.int32)))
+    for other in res[1:]:
+        for a, b in zip(res[0], other):
+            assert torch.equal(a, b)
+    assert (res[1][4][-8:] == -7).all() and (res[1][0][:, :, N:] == 0).all()

@@ -63,3 +63,66 @@ def test_second_moment_shares(heads, kv, n, least):
         scale = torch.sqrt(torch.diagonal(want)[:, None] * torch.diagonal(want)[None])
         assert ((out[h].double() - want).abs() <= 6e-8 * want.abs() + 1e-13 * scale).all()
         assert torch.equal(out[h], out[h].t())
+
+
+def _moment(q, kv, least=False):
+    heads = q.shape[1]
+    dims = B.make_dims(1, heads, kv, 128, 16, 64)
+    ws = _workspace(dims, least).fill_(0xFF)
+    out = torch.full((kv, 128, 128), float("nan"), device="cuda")
+    B.second_moment(dims, q, q.shape[0], out, ws)
+    torch.cuda.synchronize()
+    for h in range(kv):
+        x = q[:, h * (heads // kv):(h + 1) * (heads // kv)].reshape(-1, 128).double()
+        yield out[h].double(), x
+
+
+@pytest.mark.parametrize("heads,kv,n,data", [
+    (5, 1, 411, "normal"), (5, 1, 410, "normal"),      # 2055 rows by digits, 2050 too; not multiples of a step of 64
+    (7, 1, 1000, "normal"), (6, 2, 5001, "normal"),    # heads that do not divide a step
+    (16, 2, 2049, "steps"),                            # values that grow by 2^10 three times: larger units
+    (4, 4, 3000, "late"),                              # dimensions that are zero in the first rows, tiny, or huge
+    (8, 1, 2000, "correlated"),                        # equal and opposite dimensions
+])
+def test_second_moment_by_digits(heads, kv, n, data):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q = torch.randn(n, heads, 128, generator=g, device="cuda")
+    if data == "steps":
+        q *= 1024.0 ** torch.arange(n, device="cuda").mul(4).div(n, rounding_mode="floor")[:, None, None]
+    if data == "late":
+        q[:n // 2, :, :20] = 0
+        q[..., 20:40] *= 1e-17
+        q[..., 40:50] *= 1e15
+        q[..., 50] = 0
+    if data == "correlated":
+        q[..., 1], q[..., 2] = q[..., 0], -q[..., 0]
+    for got, x in _moment(q, kv):
+        want = x.t() @ x / x.shape[0]
+        most = x.abs().amax(0)
+        # half an ulp of float32, and of each row's entry two roundings to a unit of 2^-42 of the dimension's largest value
+        # and what is left of the products, 5 x 2^14 of 2^46 units squared: 2^-40 of the largest entry in all
+        assert ((got - want).abs() <= 6e-8 * want.abs() + 2.0 ** -40 * most[:, None] * most[None] + 1e-45).all()
+        assert torch.equal(got, got.t())
+
+
+def test_second_moment_of_values_that_are_not_finite():
+    q = torch.randn(3000, 4, 128, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    q[2999, 0, 3] = float("nan")      # head 0: the last row
+    q[0, 1, 5] = float("inf")         # head 1: the first
+    q[1500, 1, 9] = float("-inf")
+    q[1500, 2, 77] = float("inf")     # head 2: in the middle; head 3: none
+    for got, x in _moment(q, 4):
+        want = x.t() @ x / x.shape[0]
+        assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got.isinf(), want.isinf())
+        ok = want.isfinite()
+        assert torch.equal(got[want.isinf()], want[want.isinf()])
+        assert ((got - want).abs()[ok] <= 6e-8 * want.abs()[ok] + 1e-11).all()
+
+
+def test_second_moment_of_long_shares():
+    """More rows to a workgroup than its 32-bit sums hold, in the least workspace."""
+    q = torch.randn(1900000, 1, 128, generator=torch.Generator(device="cuda").manual_seed(2), device="cuda")
+    q[..., 7] = 3.0                                    # the digits' products all of one sign
+    for got, x in _moment(q, 1, least=True):
+        want = x.t() @ x / x.shape[0]
+        assert ((got - want).abs() <= 6e-8 * want.abs() + 1e-13).all()

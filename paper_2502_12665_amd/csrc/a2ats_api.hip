@@ -309,7 +309,8 @@ int a2ats_decode_select(const a2ats_dims* d, const float* keys, int32_t n_new, i
   const long n_sample = (long)d->batch * d->n_kv_heads * plan.NG * plan.P0;
   const bool appended_rows_compete = n_new > 0 && (int64_t)pos0 < (int64_t)d->ctx_len - window;
   // (short contexts have a launch of their own for the whole call, under the same condition)
-  const bool in_one = !streams && a2ats::takes_group_route(*d, window, n_sink);
+  const bool by_head = !streams && a2ats::takes_head_route(*d, n_new, window, n_sink, false);
+  const bool in_one = by_head || (!streams && a2ats::takes_group_route(*d, window, n_sink));
   // Single codebook, under the same condition: tables, appended keys and counts of the codewords in one launch, the selection
   // in another.  The counts lie in the workspace, which a call without keys to append may come without.
   if (a2ats::single_codebook(*d) && n_new > 0 && n_new <= a2ats::kFewSingleKeys && !appended_rows_compete && ws &&
@@ -354,6 +355,12 @@ int a2ats_decode_select(const a2ats_dims* d, const float* keys, int32_t n_new, i
     return A2ATS_ERR_INVALID_ARG;
   if (n_new > 32) return A2ATS_ERR_UNSUPPORTED;
   hipError_t e;
+  if (by_head) {
+    e = a2ats::launch_decode_select_head(*d, keys, n_new, pos0, codebook, weights, weight_mode, codes, q, q_dtype, cos_b, sin_b,
+                                         q_rot, lut, lut_scale, seq_lens, top_k, window, n_sink, topk_idx, topk_count,
+                                         topk_score, false, (hipStream_t)stream);
+    return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
+  }
   if (in_one) {
     e = a2ats::launch_decode_select_group(*d, keys, n_new, pos0, codebook, weights, weight_mode, codes, q, q_dtype, cos_b,
                                           sin_b, q_rot, lut, lut_scale, seq_lens, top_k, window, n_sink, topk_idx,
@@ -402,6 +409,12 @@ int a2ats_decode_select_shared(const a2ats_dims* d, const float* keys, int32_t n
   const long n_sample = (long)d->batch * d->n_kv_heads * plan.P0;
   const bool appended_rows_compete = n_new > 0 && (int64_t)pos0 < (int64_t)d->ctx_len - window;
   hipError_t e;
+  if (!streams && !appended_rows_compete && a2ats::takes_head_route(*d, n_new, window, n_sink, true)) {
+    e = a2ats::launch_decode_select_head(*d, keys, n_new, pos0, codebook, weights, mode, codes, q, q_dtype, cos_b, sin_b, q_rot,
+                                         lut, lut_scale, seq_lens, top_k, window, n_sink, topk_idx, topk_count, topk_score,
+                                         true, (hipStream_t)stream);
+    return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
+  }
   if (!streams && !appended_rows_compete && a2ats::takes_group_route(dk, window, n_sink)) {
     e = a2ats::launch_decode_select_group(*d, keys, n_new, pos0, codebook, weights, mode, codes, q, q_dtype, cos_b, sin_b,
                                           q_rot, lut, lut_scale, seq_lens, top_k, window, n_sink, topk_idx, topk_count,

@@ -15,6 +15,7 @@
 #include "internal.hpp"
 #include "encode_few.hpp"
 #include "coarse_score.hpp"
+#include "exact_select.hpp"
 #include "group_select.hpp"
 
 namespace a2ats {
@@ -377,6 +378,194 @@ __global__ __launch_bounds__(kLutThreads) void decode_select_group_kernel(
                        ctx_stride);
 }
 
+// A whole a2ats_decode_select for short contexts by one workgroup per head: it builds the head's exact table, keeps it in
+// LDS and selects from it at once (exact_select.hpp).  Per head the tables are a quarter of the work that they are for a
+// group, and no coarse scores and no band stand between the table and the selection; so this is the faster way as long as
+// every head has a CU.  The table, its coarse copy (the head's 16 bits of every entry), constants, scale and rotated query
+// also go to global memory, bit for bit as build_lut_body writes them.
+template <int DS, bool QBF16, bool SHARED>
+__global__ __launch_bounds__(kLutThreads) void decode_select_head_kernel(
+    const void* __restrict__ q_in, const float* __restrict__ cos_b, const float* __restrict__ sin_b,
+    const float* __restrict__ codebook, float* __restrict__ q_rot, int32_t* __restrict__ lut,
+    float* __restrict__ lut_scale, int B, int Hq, int Hkv, int n_heads, GridMap gm, const float* __restrict__ keys,
+    const float* __restrict__ weights, int mode, uint8_t* __restrict__ codes, int n_new, int pos0, int64_t ctx_stride,
+    int sweeps, int folded, const int32_t* __restrict__ seq_lens, int32_t* __restrict__ topk_idx,
+    int32_t* __restrict__ topk_count, float* __restrict__ topk_score, int ctx_len, int top_k, int window, int n_sink) {
+  constexpr int D = 128, HALF = 64, M = D / DS, ENTRIES = kCentroids * M, EPT = ENTRIES / kLutThreads;
+  constexpr int MAXQ = 65535 / M, LOG2M = M == 16 ? 4 : 5;
+  static_assert(kExactThreads == kLutThreads, "one workgroup does both");
+  extern __shared__ __align__(16) unsigned char tbl[];   // kExactLdsBytes
+  __shared__ ExactLds L;
+  __shared__ float s_q[D];
+  __shared__ float s_all[SHARED ? 8 : 1][SHARED ? D : 1];
+  __shared__ uint32_t s_maxbits;
+  __shared__ int32_t s_min[M], s_max[M], s_const[3];   // sum of minima, shift, sum of maxima
+  if ((int)blockIdx.x >= n_heads) {
+    encode_few_block<DS>((int)blockIdx.x - n_heads, sweeps, keys, codebook, weights, mode, codes, B, Hkv, n_new, pos0,
+                         ctx_stride);
+    return;
+  }
+  int prob, r, b, kv, g4;
+  map_block(blockIdx.x, gm, prob, r);   // r: the head of the KV head (SHARED: 0)
+  split_problem(prob, gm, b, kv, g4);
+  const int Gq = Hq / Hkv, G = SHARED ? 1 : Gq, Ht = SHARED ? Hkv : Hq, tid = threadIdx.x;
+  const int bh = b * Ht + kv * G + r;
+  const LutLayout lay = lut_layout(B, Ht, Hkv, M);
+  const int m = tid % M;
+  float cv[EPT][DS];
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {
+    const int c = (tid + k * kLutThreads) / M;
+    const float* cw = codebook + (((size_t)kv * M + m) * kCentroids + c) * DS;
+#pragma unroll
+    for (int t = 0; t < DS; t += 4) {
+      const float4 f = *(const float4*)(cw + t);
+      cv[k][t] = f.x; cv[k][t + 1] = f.y; cv[k][t + 2] = f.z; cv[k][t + 3] = f.w;
+    }
+  }
+  if (tid < (SHARED ? 8 : 1) * HALF) {
+    const int g = tid / HALF, t = tid % HALF;
+    float o1 = 0.f, o2 = 0.f;
+    if (!SHARED || g < Gq) {
+      const size_t base = ((size_t)b * Hq + kv * Gq + (SHARED ? g : r)) * D;
+      double x1, x2;
+      if (QBF16) {
+        const uint16_t* qp = (const uint16_t*)q_in;
+        x1 = (double)bf16_to_f32(qp[base + t]);
+        x2 = (double)bf16_to_f32(qp[base + t + HALF]);
+      } else {
+        const float* qp = (const float*)q_in;
+        x1 = (double)qp[base + t];
+        x2 = (double)qp[base + t + HALF];
+      }
+      const double c = (double)cos_b[t], s = (double)sin_b[t];
+      o1 = (float)(x1 * c - x2 * s);
+      o2 = (float)(x2 * c + x1 * s);
+      q_rot[base + t] = o1;
+      q_rot[base + t + HALF] = o2;
+    }
+    if (SHARED) {
+      s_all[g][t] = o1;
+      s_all[g][t + HALF] = o2;
+    } else {
+      s_q[t] = o1;
+      s_q[t + HALF] = o2;
+    }
+  }
+  if (SHARED) {
+    __syncthreads();
+    if (tid < D) {
+      double sum = 0.0;
+      for (int g = 0; g < 8; ++g) sum += (double)s_all[g][tid];   // heads past G hold zeros
+      s_q[tid] = (float)sum;
+    }
+  }
+  if (tid == 0) s_maxbits = 0u;
+  if (tid < M) {
+    s_min[tid] = INT32_MAX;
+    s_max[tid] = INT32_MIN;
+  }
+  __syncthreads();
+  // (the steps of build_lut_body, for one head)
+  double val[EPT], most = 0.0;
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {
+    double acc = 0.0;
+#pragma unroll
+    for (int t = 0; t < DS; ++t) acc += (double)s_q[m * DS + t] * (double)cv[k][t];
+    val[k] = acc;
+    most = fmax(most, fabs(acc));
+  }
+  const uint32_t wave_most = wave_max_to_last_lane(__float_as_uint(__double2float_ru(most)));
+  if ((tid & 63) == 63) atomicMax(&s_maxbits, wave_most);
+  __syncthreads();
+  int e = 0;
+  {
+    const uint32_t bits = s_maxbits;
+    if (bits != 0u) {
+      int x;   // largest entry * M < 2^x
+      if ((bits >> 23) != 0u) x = (int)(bits >> 23) - 126 + LOG2M;
+      else frexp((double)__uint_as_float(bits) * (double)M, &x);
+      e = 30 - x;
+      e = e > 100 ? 100 : (e < -100 ? -100 : e);
+    }
+  }
+  const float scale = (float)ldexp(1.0, -e);
+  if (tid == 0) lut_scale[bh] = scale;
+  int32_t iv[EPT], mn = INT32_MAX, mx = INT32_MIN;
+  int32_t* ex = lut + lay.off_exact + (size_t)bh * ENTRIES;
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {
+    iv[k] = (int32_t)rint(ldexp(val[k], e));
+    mn = min(mn, iv[k]);
+    mx = max(mx, iv[k]);
+    const int c = (tid + k * kLutThreads) / M;
+    *(int32_t*)(tbl + (c << 8) + (m << 2)) = iv[k];
+    if (M == 16) *(int32_t*)(tbl + (c << 8) + 64 + (m << 2)) = iv[k];
+    ex[tid + k * kLutThreads] = iv[k];
+  }
+  // the lanes of a wave that share a subspace, then the waves
+#pragma unroll
+  for (int off = M; off < 64; off <<= 1) {
+    mn = min(mn, __shfl_xor(mn, off));
+    mx = max(mx, __shfl_xor(mx, off));
+  }
+  if ((tid & 63) < M) {
+    atomicMin(&s_min[m], mn);
+    atomicMax(&s_max[m], mx);
+  }
+  __syncthreads();
+  if (tid < 64) {
+    int32_t base = tid < M ? s_min[tid & (M - 1)] : 0, top = tid < M ? s_max[tid & (M - 1)] : 0;
+    uint32_t range = (uint32_t)(top - base);
+#pragma unroll
+    for (int off = M / 2; off >= 1; off >>= 1) {
+      base += __shfl_xor(base, off);
+      top += __shfl_xor(top, off);
+      range = max(range, (uint32_t)__shfl_xor((int)range, off));
+    }
+    if (tid == 0) {
+      int sh = 0;
+      while ((range >> sh) > (uint32_t)MAXQ) ++sh;
+      s_const[0] = base;
+      s_const[1] = sh;
+      s_const[2] = top;
+      *(int4*)(lut + lay.off_meta + (size_t)bh * 4) = make_int4(base, sh, top, 0);
+    }
+  }
+  __syncthreads();
+  const int32_t base = s_const[0], sh = s_const[1], top = s_const[2];
+  {
+    // this head's 16 bits of the coarse entries; the last head of a group also fills the places of those that there are none
+    // of
+    const int slot = r % kHeadsPerGroup, NG = (G + kHeadsPerGroup - 1) / kHeadsPerGroup;
+    const int n_real = min(kHeadsPerGroup, G - (r / kHeadsPerGroup) * kHeadsPerGroup), last = slot == n_real - 1 ? kHeadsPerGroup : slot + 1;
+    uint16_t* coarse = (uint16_t*)(lut + lay.off_coarse) +
+                       (size_t)((b * Hkv + kv) * NG + r / kHeadsPerGroup) * ENTRIES * kHeadsPerGroup;
+    const int32_t least = s_min[m];
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+      const int c = (tid + k * kLutThreads) / M;
+      uint16_t* at = coarse + ((m >> 4) * (kCentroids * 16) + c * 16 + (m & 15)) * kHeadsPerGroup;
+      at[slot] = (uint16_t)((uint32_t)(iv[k] - least) >> sh);
+      for (int i = slot + 1; i < last; ++i) at[i] = 0;
+    }
+  }
+  const SeqRange sr = seq_range(ctx_len, seq_lens, b, window, n_sink, top_k);
+  int32_t* oi = topk_idx + (size_t)bh * top_k;
+  float* os = topk_score ? topk_score + (size_t)bh * top_k : nullptr;
+  if (tid == 0) topk_count[bh] = sr.kk;
+  for (int t = sr.kk + tid; t < top_k; t += kLutThreads) {
+    oi[t] = -1;
+    if (os) os[t] = 0.f;
+  }
+  if (sr.kk > 0)   // (uniform)
+    exact_select_block<M, false, true>(seq_codes_of<M>(codes, CodePages{nullptr, 0, 0}, b, kv, Hkv, ctx_stride), nullptr, base,
+                                       top, scale, sr, oi, os, tbl, L);
+  if (folded)   // (see decode_prologue_kernel)
+    encode_few_block<DS>((int)blockIdx.x, sweeps, keys, codebook, weights, mode, codes, B, Hkv, n_new, pos0, ctx_stride);
+}
+
 // How the append-time encoding shares a launch with n_lut table workgroups: workgroups of its own, or
 // (folded) the table workgroups, where both kinds would not fit one round of the CUs.
 struct AppendPlan {
@@ -391,6 +580,59 @@ static AppendPlan append_plan(long n_pairs, int n_lut) {
   if (p.folded) p.sweeps = (int)((n_pairs + (long)kFewPairsPerSweep * n_lut - 1) / ((long)kFewPairsPerSweep * n_lut));
   p.n_enc = p.folded ? 0u : (unsigned)n_enc;
   return p;
+}
+
+// Whether a selection that does not stream is taken by a workgroup per head: where every head has a CU, beside the workgroups
+// that encode; where it has one only without those (folded), the group route is the faster one for few rows and M = 16.
+// Steps, us, group or exact route -> a workgroup per head, one sequence of 32 query and 8 KV heads, M = 16, 1600, 4096, 8300,
+// 16384 tokens 24.8 -> 23.8, 26.6 -> 24.3, 32.2 -> 26.8, 36.6 -> 31.3, M = 32 30.3 -> 24.4, 34.3 -> 26.9, 38.5 -> 31.1, 49.4
+// -> 38.8; 8 sequences (folded) M = 16 24.7 -> 26.4, 28.3 -> 29.2, 38.7 -> 36.3, 48.9 -> 45.9, M = 32 34.0 -> 28.6, 41.3 -> 32.4,
+// 49.1 -> 40.9, 63.0 -> 52.9; 9 sequences (two rounds) 25.3 -> 37.2 and 70.6 -> 80.6.  With one head to a group nothing is shared
+// that a second round could lose: 64 sequences of 8 KV heads, one selection each, 4096, 8192, 16000 tokens 81.0 -> 80.6, 97.3 ->
+// 88.0, 107.8 -> 98.9.
+bool takes_head_route(const a2ats_dims& d, int n_new, int window, int n_sink, bool shared) {
+  const long ncand = (long)d.ctx_len - window - n_sink, heads = (long)d.batch * (shared ? d.n_kv_heads : d.n_q_heads);
+  const bool one_a_group = shared || d.n_q_heads == d.n_kv_heads;
+  if (single_codebook(d) || ncand > kKeepRows * kExactThreads || heads > (one_a_group ? 512 : 256)) return false;
+  return d.n_sub == 32 || ncand > 8192 || !append_plan((long)d.batch * d.n_kv_heads * n_new * d.n_sub, (int)heads).folded;
+}
+
+// Heads that select by themselves (SHARED: KV heads) and the append in one launch, where takes_head_route.
+hipError_t launch_decode_select_head(const a2ats_dims& d, const float* keys, int n_new, int pos0, const float* codebook,
+                                     const float* weights, int mode, uint8_t* codes, const void* q, int q_dtype,
+                                     const float* cos_b, const float* sin_b, float* q_rot, int32_t* lut, float* lut_scale,
+                                     const int32_t* seq_lens, int top_k, int window, int n_sink, int32_t* topk_idx,
+                                     int32_t* topk_count, float* topk_score, bool shared, hipStream_t stream) {
+  const int per = shared ? 1 : d.n_q_heads / d.n_kv_heads, problems = d.batch * d.n_kv_heads, n_heads = problems * per;
+  const AppendPlan ap = append_plan((long)problems * n_new * d.n_sub, n_heads);
+  const dim3 grid(n_heads + ap.n_enc), block(kLutThreads);
+  if (grid.x == 0) return hipSuccess;
+  static LdsSlot s_lds[8][16];
+  hipError_t err;
+#define A2ATS_LAUNCH_HEAD(DS, BF, SH, SLOT)                                                                       \
+  do {                                                                                                            \
+    if ((err = allow_dynamic_lds(decode_select_head_kernel<DS, BF, SH>, (size_t)kExactLdsBytes, s_lds[SLOT])) !=  \
+        hipSuccess)                                                                                               \
+      return err;                                                                                                 \
+    hipLaunchKernelGGL((decode_select_head_kernel<DS, BF, SH>), grid, block, kExactLdsBytes, stream, q, cos_b,    \
+                       sin_b, codebook, q_rot, lut, lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, n_heads,       \
+                       make_grid_map(per, problems, 1, d.n_kv_heads), keys, weights, mode, codes, n_new, pos0,    \
+                       d.ctx_stride, ap.sweeps, ap.folded, seq_lens, topk_idx, topk_count, topk_score, d.ctx_len, top_k,        \
+                       window, n_sink);                                                                           \
+  } while (0)
+#define A2ATS_LAUNCH_HEAD2(DS, BF, SLOT)                   \
+  do {                                                     \
+    if (shared) A2ATS_LAUNCH_HEAD(DS, BF, true, SLOT + 4); \
+    else A2ATS_LAUNCH_HEAD(DS, BF, false, SLOT);           \
+  } while (0)
+  if (d.sub_dim == 8) {
+    if (q_dtype == A2ATS_BF16) A2ATS_LAUNCH_HEAD2(8, true, 0); else A2ATS_LAUNCH_HEAD2(8, false, 1);
+  } else {
+    if (q_dtype == A2ATS_BF16) A2ATS_LAUNCH_HEAD2(4, true, 2); else A2ATS_LAUNCH_HEAD2(4, false, 3);
+  }
+#undef A2ATS_LAUNCH_HEAD2
+#undef A2ATS_LAUNCH_HEAD
+  return hipGetLastError();
 }
 
 hipError_t launch_decode_select_group(const a2ats_dims& d, const float* keys, int n_new, int pos0,

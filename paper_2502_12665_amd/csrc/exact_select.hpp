@@ -136,7 +136,8 @@ __device__ __forceinline__ void count_shared_bins(uint32_t* hist, uint32_t bin, 
 // out_idx[0..kk) ascending (and out_score); the caller has written the count and the -1 padding.
 // Requires sr.kk >= 1.
 // TIES: many rows are expected to have one score, and s_lo and s_hi are bounds of the K-th; out_score is not written.
-template <int M, bool TIES = false>
+// TABLE_IN_LDS: the caller has put the head's table at `tbl` (a barrier follows here).
+template <int M, bool TIES = false, bool TABLE_IN_LDS = false>
 __device__ void exact_select_block(const SeqCodes& seq_codes,
                                    const int32_t* __restrict__ head_table,
                                    int32_t s_lo, int32_t s_hi, float scale,
@@ -151,8 +152,10 @@ __device__ void exact_select_block(const SeqCodes& seq_codes,
   ExactSwizzle<M> sw;
   sw.init(tid & 63);
   __syncthreads();   // tbl may alias LDS the caller was still reading
-  load_exact_table<M, NT>(head_table, tbl);
-  __syncthreads();
+  if (!TABLE_IN_LDS) {
+    load_exact_table<M, NT>(head_table, tbl);
+    __syncthreads();
+  }
 
   const int lo = sr.sink_end, hi = sr.win_start;
   uint32_t kth = 0, k_rem = (uint32_t)sr.kk;   // kth: relative

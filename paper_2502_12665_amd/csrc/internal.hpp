@@ -86,6 +86,13 @@ hipError_t launch_decode_select_group(const a2ats_dims& d, const float* keys, in
                                       int32_t* lut, float* lut_scale, const int32_t* seq_lens, int top_k, int window,
                                       int n_sink, int32_t* topk_idx, int32_t* topk_count, float* topk_score,
                                       bool shared, hipStream_t stream);
+// The same with a workgroup per head (of `d` and shared as above), where every head has a CU.
+bool takes_head_route(const a2ats_dims& d, int n_new, int window, int n_sink, bool shared);
+hipError_t launch_decode_select_head(const a2ats_dims& d, const float* keys, int n_new, int pos0, const float* codebook,
+                                     const float* weights, int mode, uint8_t* codes, const void* q, int q_dtype,
+                                     const float* cos_b, const float* sin_b, float* q_rot, int32_t* lut, float* lut_scale,
+                                     const int32_t* seq_lens, int top_k, int window, int n_sink, int32_t* topk_idx,
+                                     int32_t* topk_count, float* topk_score, bool shared, hipStream_t stream);
 hipError_t launch_sparse_attn(const a2ats_dims& d, const void* q, const float* q_rot, const void* k_cache,
                               const void* v_cache, int kv_dtype, const int32_t* topk_idx,
                               const int32_t* topk_count, int top_k, int window, int n_sink,

@@ -617,8 +617,8 @@ hipError_t launch_decode_select_head(const a2ats_dims& d, const float* keys, int
     hipLaunchKernelGGL((decode_select_head_kernel<DS, BF, SH>), grid, block, kExactLdsBytes, stream, q, cos_b,    \
                        sin_b, codebook, q_rot, lut, lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, n_heads,       \
                        make_grid_map(per, problems, 1, d.n_kv_heads), keys, weights, mode, codes, n_new, pos0,    \
-                       d.ctx_stride, ap.sweeps, ap.folded, seq_lens, topk_idx, topk_count, topk_score, d.ctx_len, top_k,        \
-                       window, n_sink);                                                                           \
+                       d.ctx_stride, ap.sweeps, ap.folded, seq_lens, topk_idx, topk_count, topk_score, d.ctx_len,         \
+                       top_k, window, n_sink);                                                                    \
   } while (0)
 #define A2ATS_LAUNCH_HEAD2(DS, BF, SLOT)                   \
   do {                                                     \

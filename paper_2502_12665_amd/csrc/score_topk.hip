@@ -142,7 +142,8 @@ TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink) 
 // nothing but the launch, so the line does not move with the heads of a group (tables and selection of 16 sequences of 16
 // heads, one a group, M = 16, 16384 tokens 35.6 -> 42.1, 24 of 8 34.6 -> 37.5, M = 32, 8228 tokens 29.6 -> 30.9).  In more
 // than one round it is lower: 64 of 8 heads, M = 16, 4096, 8228, 16384 tokens 49.4 -> 45.1, 55.0 -> 56.8, 66.5 -> 77.8, M =
-// 32, 1500, 4096, 8228 tokens 60.9 -> 59.6, 67.3 -> 69.0, 76.9 -> 84.6.
+// 32, 1500, 4096, 8228 tokens 60.9 -> 59.6, 67.3 -> 69.0, 76.9 -> 84.6.  This is the line of the selection by itself; a step
+// with up to 256 heads (one round) mostly goes by head, tables included (takes_head_route).
 bool takes_group_route(const a2ats_dims& d, int window, int n_sink) {
   const long ncand = (long)d.ctx_len - window - n_sink;
   if (single_codebook(d) || ncand > kGroupMaxCand) return false;

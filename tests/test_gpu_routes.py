@@ -380,254 +380,6 @@ def test_selection_by_head_equals_the_calls(Bn, G, Hkv, M, N, K, w, n_sink, n_ne
         else:
             B.encode_keys(dims, keys, n_new, N - n_new, xd["codebook"], weights, B.W_DIAG, codes,
                           torch.empty(B.workspace_bytes(dims, B.OP_ENCODE), dtype=torch.uint8, device="cuda"))
-            (B.build_lut_shared if shared else B.build_lut)(dims, *tables)
-            B.score_topk(sel, codes, sk.lut, sk.lut_scale, *pick, None, sk.ws)
-        torch.cuda.synchronize()
-        res.append((codes, st.q_rot, sk.lut, sk.lut_scale, sk.topk_idx, sk.topk_count, sk.topk_score))
-    for a, b in zip(*res):
-        assert torch.equal(a.contiguous().view(torch.uint8), b.contiguous().view(torch.uint8))
-
-
-@pytest.mark.parametrize("G,Hkv,N,K,w,n_sink,dtype,page,ragged", [
-    (4, 8, 700, 50, 100, 4, "bf16", 0, True),
-    (7, 4, 1300, 600, 256, 0, "bf16", 16, False),                        # more rows than a staged tile; two windows' worth
-    (4, 8, 300, 0, 64, 0, "f32", 0, True),                               # the window alone
-    (8, 4, 513, 200, 0, 4, "f32", 64, True),                             # no window
-    (8, 4, 1300, 600, 128, 0, "bf16", 16, True),
-    (8, 4, 1300, 600, 128, 4, "f32", 0, False),
-])
-def test_attention_of_many_heads_equals_that_of_few(G, Hkv, N, K, w, n_sink, dtype, page, ragged):
-    """Of many heads a workgroup takes a whole one (all cases but that with 256 window rows); the same sequences four at a
-    time take the split route."""
-    Bn = 40
-    wl = synth.Workload("many", Bn, G * Hkv, Hkv, 128, 16, N, K, w, n_sink=n_sink, kv_dtype=dtype, seed=N)
-    xd = synth.make_decode_inputs(wl, device="cuda")
-    g = torch.Generator(device="cuda").manual_seed(N)
-    lens = torch.randint(0, N + 1, (Bn,), generator=g, device="cuda", dtype=torch.int32) if ragged else None
-    if ragged:
-        lens[0], lens[1] = 0, 1
-    k, v, table = xd["k"], xd["v"], None
-    if page:
-        slots = (N + page - 1) // page
-        table = torch.randperm(Bn * slots, generator=g, device="cuda").reshape(Bn, slots).to(torch.int32)
-        pools = []
-        for x in (k, v):
-            padded = torch.zeros(Bn, Hkv, slots * page, 128, dtype=x.dtype, device="cuda")
-            padded[:, :, :N] = x
-            pool = torch.empty(Bn * slots, Hkv, page, 128, dtype=x.dtype, device="cuda")
-            pool[table.long().reshape(-1)] = (padded.reshape(Bn, Hkv, slots, page, 128).permute(0, 2, 1, 3, 4)
-                                              .reshape(Bn * slots, Hkv, page, 128))
-            pools.append(pool)
-        k, v = pools
-
-    def attend(first, n, idx, count):
-        part = wl.replace(batch=n)
-        st = B.DecodeState(H.dims_of(part), K, w, n_sink, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
-        sl = None if lens is None else lens[first:first + n].contiguous()
-        q = xd["q"][first:first + n].contiguous()
-        q_rot = q.float().contiguous()
-        st.out.fill_(7.0)
-        args = (idx[first:first + n].contiguous(), count[first:first + n].contiguous(), K, w, n_sink, st.cos_win, st.sin_win,
-                sl, st.out, st.ws)
-        if page:
-            B.sparse_attn_paged(st.dims, q, q_rot, k, v, table[first:first + n].contiguous(), page, *args)
-        else:
-            B.sparse_attn(st.dims, q, q_rot, k[first:first + n].contiguous(), v[first:first + n].contiguous(), *args)
-        torch.cuda.synchronize()
-        return st.out.float()
-
-    heads = G * Hkv
-    idx = torch.sort(torch.rand(Bn, heads, max(N - w, 1), generator=g, device="cuda").argsort(-1)[..., :max(K, 1)], -1).values
-    idx = idx.to(torch.int32)
-    count = torch.full((Bn, heads), K, dtype=torch.int32, device="cuda")
-    whole = attend(0, Bn, idx, count)
-    few = torch.cat([attend(b, 4, idx, count) for b in range(0, Bn, 4)])
-    # float32 sums in another order, 4e-6 of the values' size (about 1); a bfloat16 output may round the other way, and
-    # neighbours of 8 significant bits are up to 2^-7 of themselves apart
-    tol = 2.0 ** -7 if dtype == "bf16" else 4e-6
-    assert ((whole - few).abs() <= tol * torch.maximum(whole.abs(), few.abs()) + 4e-6).all(), float((whole - few).abs().max())
-
-
-@pytest.mark.parametrize("Bn,G,M,N,K,n_sink", [
-    (2, 4, 16, 12000, 300, 4),        # the exact route, its keys in registers
-    (1, 4, 32, 12000, 300, 0),
-    (2, 4, 16, 40000, 4000, 4),       # without a workspace the exact route, its keys scored again and again
-    (40, 4, 16, 12000, 300, 4),       # a workgroup per group
-    (2, 4, 16, 60000, 1500, 4),       # the streaming route
-])
-@pytest.mark.parametrize("bad", ["inf", "nan", "huge"])
-def test_queries_that_are_not_finite_select_within_their_rows(Bn, G, M, N, K, n_sink, bad):
-    """Table entries of an infinite query saturate and their sums wrap.  What is selected then means nothing, but it is K'
-    ascending candidates per head, and nothing is written anywhere else."""
-    wl = synth.Workload("bad", Bn, 2 * G, 2, 128, M, N, K, 64, n_sink=n_sink, seed=N + K)
-    xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
-    q = xd["q"].float()
-    if bad == "huge":
-        q *= 3e38
-    else:
-        q[:, ::2, 5] = float(bad)
-        q[:, 1, 64:] = -float(bad)
-        q[-1, -1, ::3] = float(bad)
-    dims = H.dims_of(wl)
-    st = B.DecodeState(dims, K, 64, n_sink, torch.float32, xd["inv_freq"], wl.wrope_b)
-    heads = Bn * 2 * G
-    idx = torch.full((heads * K + N,), -7, dtype=torch.int32, device="cuda")
-    score = torch.full((heads * K + N,), -7.0, device="cuda")
-    B.build_lut(dims, q, st.cos_b, st.sin_b, xd["codebook"], st.q_rot, st.lut, st.lut_scale)
-    for ws in (st.ws, None) if K > 2048 else (st.ws,):
-        B.score_topk(dims, xd["codes"], st.lut, st.lut_scale, K, 64, n_sink, None, idx, st.topk_count, score, None, ws)
-        torch.cuda.synchronize()
-        assert (idx[heads * K:] == -7).all() and (score[heads * K:] == -7.0).all()
-        assert (st.topk_count == K).all()
-        got = idx[:heads * K].view(heads, K)
-        assert (got[:, 1:] > got[:, :-1]).all() and (got >= n_sink).all() and (got < N - 64).all()
-
-
-@pytest.mark.parametrize("N,K,w,n_sink", [(700, 100, 64, 4), (700, 508, 100, 0), (5000, 4096, 64, 4), (1500, 1000, 0, 0), (900, 0, 230, 0)])
-def test_float32_attention_of_many_heads_is_as_exact_as_that_of_few(N, K, w, n_sink):
-    """The same four sequences among 40 (a workgroup takes a whole head) and alone (its rows are shared out), against
-    float64: errors of rounding only, and of the same size."""
-    Bn, Hkv, G, n = 40, 4, 8, 4
-    wl = synth.Workload("exact", Bn, Hkv * G, Hkv, 128, 16, N, K, w, n_sink=n_sink, kv_dtype="f32", seed=N)
-    xd = synth.make_decode_inputs(wl, device="cuda")
-    g = torch.Generator(device="cuda").manual_seed(N)
-    idx = torch.rand(Bn, Hkv * G, N - w - n_sink, generator=g, device="cuda").topk(max(K, 1), -1).indices
-    idx = (torch.sort(idx, -1).values + n_sink).to(torch.int32).contiguous()
-    count = torch.full((Bn, Hkv * G), K, dtype=torch.int32, device="cuda")
-    outs = []
-    for take in (Bn, n):
-        st = B.DecodeState(H.dims_of(wl.replace(batch=take)), K, w, n_sink, torch.float32, xd["inv_freq"], wl.wrope_b)
-        B.sparse_attn(st.dims, xd["q"][:take], xd["q"][:take], xd["k"][:take], xd["v"][:take], idx[:take], count[:take], K, w,
-                      n_sink, st.cos_win, st.sin_win, None, st.out, st.ws)
-        torch.cuda.synchronize()
-        outs.append(st.out[:n].double())
-    back = torch.arange(w - 1, -1, -1, device="cuda")
-    cos, sin = st.cos_win.double()[back], st.sin_win.double()[back]
-    err, size = [0.0, 0.0], 0.0
-    for b in range(n):
-        for h in range(Hkv * G):
-            k, v, q = xd["k"][b, h // G].double(), xd["v"][b, h // G].double(), xd["q"][b, h].double()
-            far = torch.cat([torch.arange(n_sink, device="cuda"), idx[b, h, :K].long()])
-            turned = torch.cat([q[:64] * cos - q[64:] * sin, q[64:] * cos + q[:64] * sin], 1)
-            logit = torch.cat([k[far] @ q, (turned * k[N - w:]).sum(1)]) * 128 ** -0.5
-            want = torch.softmax(logit, 0) @ torch.cat([v[far], v[N - w:]])
-            size += float(want.pow(2).sum())
-            for i, o in enumerate(outs):
-                err[i] += float((o[b, h] - want).pow(2).sum())
-    whole, few = (err[0] / size) ** 0.5, (err[1] / size) ** 0.5
-    H.log(f"float32 attention, {K} + {w} rows: error {whole:.3e} whole, {few:.3e} shared out")
-    assert whole <= 1.1 * few and few < 4e-7
-
-
-@pytest.mark.parametrize("Bn,G,Hkv,N,K,w,n_sink,n_new,lens,stride,data", [
-    (1, 4, 1, 4096 + 16, 100, 16, 0, 1, None, 0, None),          # one head a workgroup, exactly one chunk of 4096
-    (1, 4, 1, 4097 + 16, 100, 16, 0, 2, None, 8, None),          # and one token more
-    (2, 7, 2, 9000, 777, 32, 4, 1, [9000, 4104], 5, None),       # rows that do not start on 16 bytes; an odd group
-    (2, 8, 2, 50000, 4096, 64, 3, 8, None, 0, "patterns"),       # the K-th score is shared by many tokens
-    (3, 4, 8, 70001, 1500, 128, 4, 1, [70001, 1, 33000], 7, None),   # two heads a workgroup, sequences without candidates
-    (33, 4, 8, 17000, 600, 64, 0, 1, None, 0, None),             # four heads a workgroup, two chunks of 16384
-    (17, 7, 8, 16500, 300, 64, 1, 1, [16500] * 16 + [360], 0, "patterns"),   # of which the last has three; everything selected
-    (1, 1, 2, 20000, 3000, 64, 0, 1, None, 0, "equal"),          # a table of equal scores: radix levels, lowest positions
-    (4, 4, 2, 12000, 3999, 64, 4, 3, None, 0, "crowded"),        # nearly equal scores: a crowded bin
-    (2, 4, 1, 700, 636, 64, 0, 1, None, 0, None),                # few tokens: the counts do not fit, the two calls
-    (1, 2, 1, 6000, 0, 64, 0, 1, None, 0, None),
-])
-@pytest.mark.parametrize("mode", ["none", "block"])
-def test_single_codebook_decode_select_equals_the_two_calls(Bn, G, Hkv, N, K, w, n_sink, n_new, lens, stride, data, mode):
-    """Tables, appended keys and selection from counts in two launches against prologue and selection as calls of their own:
-    every output bit for bit; no memory behind the outputs is written."""
-    wl = synth.Workload("single_select", Bn, G * Hkv, Hkv, 128, 1, N, K, w, n_sink=n_sink, n_centroids=4096, seed=N + K)
-    xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
-    if data == "patterns":
-        xd["codes"][:] = xd["codes"][:, :, torch.randint(0, 60, (N,), device="cuda")]
-    if data == "equal":
-        xd["codebook"][:] = xd["codebook"][:, :, :1]
-    if data == "crowded":
-        xd["codebook"][:, :, 1:3000] = xd["codebook"][:, :, :1] * (1 + 1e-6 * torch.rand(2999, 1, device="cuda"))
-        xd["codebook"][:, :, 500:900] = xd["codebook"][:, :, :1]
-    weights = None if mode == "none" else synth.make_query_second_moment(wl)["h_block"].cuda()
-    wmode = B.W_NONE if mode == "none" else B.W_BLOCK
-    keys = synth.make_encode_keys(wl, n_new, device="cuda", stress=True)
-    dims = H.dims_of(wl, N + stride)
-    full = torch.zeros(Bn, Hkv, N + stride, 1, dtype=xd["codes"].dtype, device="cuda")
-    full[:, :, :N] = xd["codes"]
-    sl = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
-    ws = torch.empty(B.workspace_bytes(dims, B.OP_ENCODE), dtype=torch.uint8, device="cuda")
-    res = []
-    for how in ("two calls", "one", "one, prepared"):
-        st = B.DecodeState(dims, max(K, 1), w, n_sink, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
-        st.lut.fill_(-1)
-        idx = torch.full((Bn * Hkv * G * K + 8,), -7, dtype=torch.int32, device="cuda")
-        score = torch.full((Bn * Hkv * G * K + 8,), -7.0, device="cuda")
-        codes = full.clone()
-        ws.fill_(255)
-        flag = 0
-        if how == "one, prepared":
-            B.encode_prepare(dims, xd["codebook"], weights, wmode, ws)
-            flag = B.W_PREPARED
-        args = (dims, keys, n_new, N - n_new, xd["codebook"], weights, wmode | flag, codes, xd["q"], st.cos_b, st.sin_b,
-                st.q_rot, st.lut, st.lut_scale)
-        if how == "two calls":
-            B.decode_prologue(*args, ws)
-            B.score_topk(dims, codes, st.lut, st.lut_scale, K, w, n_sink, sl, idx, st.topk_count, score, None, None)
-        else:
-            B.decode_select(*args, K, w, n_sink, sl, idx, st.topk_count, score, ws)
-        torch.cuda.synchronize()
-        res.append((codes, st.lut, st.lut_scale, st.q_rot, idx, st.topk_count, score.view(torch.int32)))
-    for other in res[1:]:
-        for a, b in zip(res[0], other):
-            assert torch.equal(a, b)
-    assert (res[1][4][-8:] == -7).all() and (res[1][0][:, :, N:] == 0).all()
-
-
-@pytest.mark.parametrize("Bn,G,Hkv,M,N,K,w,n_sink,n_new,lens,data", [
-    (1, 1, 1, 16, 40, 7, 32, 4, 1, None, None),                       # four candidates
-    (2, 3, 2, 32, 1024 + 64, 300, 64, 0, 1, None, None),              # one row a thread, exactly; a group of three
-    (2, 4, 2, 16, 1025 + 64, 300, 64, 0, 2, [1089, 64], None),        # and one row more; a sequence without candidates
-    (3, 7, 2, 32, 16384 + 68, 4096, 64, 4, 1, [16452, 0, 9000], None),   # the most candidates; a second group of three
-    (3, 7, 2, 16, 16383 + 64, 2000, 64, 0, 1, None, "patterns"),      # the K-th score is shared by many rows
-    (1, 8, 1, 16, 9000, 8000 // 2, 64, 0, 1, None, "equal"),          # every row equal
-    (2, 5, 1, 32, 700, 700, 64, 2, 3, None, None),                    # everything selected
-    (1, 4, 2, 16, 3000, 0, 64, 0, 1, None, None),                     # nothing
-    (8, 4, 8, 32, 2000, 100, 64, 0, 1, None, None),                   # 256 heads: they encode the keys as well
-    (8, 4, 8, 16, 9000, 500, 64, 4, 4, None, "zero"),                 # the same; queries of zero
-    (33, 1, 8, 16, 2500, 100, 64, 0, 1, None, None),                  # 264 groups of one head, in two rounds
-])
-@pytest.mark.parametrize("shared", [False, True])
-def test_selection_by_head_equals_the_calls(Bn, G, Hkv, M, N, K, w, n_sink, n_new, lens, data, shared):
-    """Append, tables and selection by a workgroup per head in one launch against the calls one after the other: every
-    output bit for bit, the padded heads of the coarse tables too."""
-    wl = synth.Workload("by_head", Bn, G * Hkv, Hkv, 128, M, N, K, w, n_sink=n_sink, seed=N + K + M)
-    xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
-    if data == "patterns":
-        xd["codes"][:] = xd["codes"][:, :, torch.randint(0, 60, (N,), device="cuda")]
-    if data == "equal":
-        xd["codes"][:] = xd["codes"][:, :, :1]
-    if data == "zero":
-        xd["q"][0] = 0
-    weights = synth.make_query_second_moment(wl)["h_diag"].cuda()
-    keys = synth.make_encode_keys(wl, n_new, device="cuda", stress=True)
-    dims = H.dims_of(wl)
-    sel = B.make_dims(Bn, Hkv, Hkv, 128, M, N) if shared else dims
-    heads = Hkv if shared else G * Hkv
-    sl = None if lens is None else torch.tensor(lens, dtype=torch.int32, device="cuda")
-    res = []
-    for one in (False, True):
-        st = B.DecodeState(dims, max(K, 1), w, n_sink, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
-        lut = torch.full((B.lut_elems(sel),), -1, dtype=torch.int32, device="cuda")
-        scale = torch.zeros(Bn, heads, device="cuda")
-        idx = torch.full((Bn * heads * K + 8,), -7, dtype=torch.int32, device="cuda")
-        score = torch.full((Bn * heads * K + 8,), -7.0, device="cuda")
-        count = torch.full((Bn, heads), -7, dtype=torch.int32, device="cuda")
-        codes = xd["codes"].clone()
-        call = (dims, keys, n_new, N - n_new, xd["codebook"], weights, B.W_DIAG, codes, xd["q"], st.cos_b, st.sin_b, st.q_rot,
-                lut, scale, K, w, n_sink, sl, idx, count, score, None)
-        if one:
-            (B.decode_select_shared if shared else B.decode_select)(*call)
-        else:
-            B.encode_keys(dims, keys, n_new, N - n_new, xd["codebook"], weights, B.W_DIAG, codes, None if n_new <= 32 else st.ws) \
-                if False else B.encode_keys(dims, keys, n_new, N - n_new, xd["codebook"], weights, B.W_DIAG, codes,
-                                            torch.empty(B.workspace_bytes(dims, B.OP_ENCODE), dtype=torch.uint8, device="cuda"))
             (B.build_lut_shared if shared else B.build_lut)(dims, xd["q"], st.cos_b, st.sin_b, xd["codebook"], st.q_rot, lut, scale)
             B.score_topk(sel, codes, lut, scale, K, w, n_sink, sl, idx, count, score, None, None)
         torch.cuda.synchronize()

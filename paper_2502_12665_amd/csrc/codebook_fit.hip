@@ -17,9 +17,10 @@
 //                            walks over its share of the keys, then go to memory by float64 atomic adds
 //   update_count_kernel, update_scan_kernel, update_place_kernel
 //                            single codebook: the keys of a KV head in the order of their codes
-//   update_sorted_kernel     a wave adds up 64 consecutive keys of that order, one float64 atomic add
-//                            per run of equal codes
-//   update_mean_kernel       sum / count, rounded once; codewords without keys keep their value
+//   update_sorted_kernel     a wave adds up consecutive keys of that order; a codeword all of whose keys it has becomes
+//                            their mean
+//   update_rest_kernel       the codewords whose keys are several waves', and those without keys
+//   update_mean_kernel       the other routes: sum / count, rounded once; codewords without keys keep their value
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -520,23 +521,62 @@ __global__ __launch_bounds__(kAddThreads) void update_add_kernel(const float* __
     if (s_n[i]) atomicAdd(&counts[cw0 + i], s_n[i]);
 }
 
-// Single codebook: 4096 codewords of 128 dimensions do not fit LDS, but the keys can be read in the order of their
-// codes.  counts[kv][c] and every key's rank among those of its code, then cursor[kv][c] = first place of code c, then
-// order[kv][place] = (row, code).
-constexpr int kFL = 4096;
-__global__ __launch_bounds__(256) void update_count_kernel(const uint16_t* __restrict__ codes, uint32_t* __restrict__ counts,
-                                                           uint32_t* __restrict__ rank, int Hkv, int n_new, int pos0,
-                                                           int64_t ctx_stride) {
-  const int bkv = blockIdx.y, j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= n_new) return;
-  const int c = codes[(size_t)bkv * ctx_stride + pos0 + j] & (kFL - 1);
-  rank[(size_t)bkv * n_new + j] = atomicAdd(&counts[(size_t)(bkv % Hkv) * kFL + c], 1u);
+// Single codebook: 4096 codewords of 128 dimensions do not fit LDS, but the keys can be read in the order of their codes.
+// The keys of a KV head are cut into slices, of which a workgroup counts the codes in LDS; from the counts
+// hist[kv][slice][c] follow the first place start[kv][c] of a code and, in the place of the counts, that of a slice's keys of
+// it; a workgroup then puts the keys of its slice there: order[kv][place] = (row, code).  768032 keys, 8 KV heads, all three
+// 28 us; 52 with a counter per codeword in memory, to be cleared first, whose atomics return a key's rank.  16 slices a KV
+// head: with 23 the scan takes 13.4 us instead of 9.8, and counting no less than 5.
+constexpr int kFL = 4096, kOrderThreads = 1024;
+struct OrderSlices {
+  int n;        // per KV head
+  long per;     // rows of one
+};
+inline OrderSlices order_slices(long rows) {   // (at most as many as a word per row holds counts of, but at least one)
+  OrderSlices s;
+  s.n = (int)(rows / kFL < 1 ? 1 : (rows / kFL > 16 ? 16 : rows / kFL));
+  s.per = (rows + s.n - 1) / s.n;
+  return s;
 }
 
-__global__ __launch_bounds__(1024) void update_scan_kernel(const uint32_t* __restrict__ counts, uint32_t* __restrict__ cursor) {
+// use(row, code) for every key of the workgroup's slice: row r of a KV head is key r % n_new of sequence r / n_new.
+template <typename USE>
+__device__ __forceinline__ void for_slice(const uint16_t* __restrict__ codes, int Hkv, int n_new, int pos0,
+                                          int64_t ctx_stride, long rows, long per, const USE& use) {
+  const int kv = blockIdx.y;
+  const long r0 = blockIdx.x * per, r1 = min(rows, r0 + per);
+#pragma unroll 4
+  for (long r = r0 + threadIdx.x; r < r1; r += kOrderThreads) {
+    const uint32_t b = (uint32_t)r / (uint32_t)n_new, j = (uint32_t)r % (uint32_t)n_new;
+    const size_t bkv = (size_t)b * Hkv + kv;
+    use((uint32_t)(bkv * n_new + j), codes[bkv * ctx_stride + pos0 + j] & (uint32_t)(kFL - 1));
+  }
+}
+
+__global__ __launch_bounds__(kOrderThreads) void update_count_kernel(const uint16_t* __restrict__ codes,
+                                                                     uint32_t* __restrict__ hist, int Hkv, int n_new,
+                                                                     int pos0, int64_t ctx_stride, long rows, long per) {
+  __shared__ uint32_t s_n[kFL];
+  for (int i = threadIdx.x; i < kFL; i += kOrderThreads) s_n[i] = 0u;
+  __syncthreads();
+  for_slice(codes, Hkv, n_new, pos0, ctx_stride, rows, per, [&](uint32_t, uint32_t c) { atomicAdd(&s_n[c], 1u); });
+  __syncthreads();
+  uint32_t* out = hist + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kFL;
+  for (int i = threadIdx.x; i < kFL; i += kOrderThreads) out[i] = s_n[i];
+}
+
+// With one slice `hist` is `counts`, and the slice's first places are `start`.
+__global__ __launch_bounds__(1024) void update_scan_kernel(uint32_t* hist, uint32_t* counts, uint32_t* __restrict__ start,
+                                                           int slices) {
   __shared__ uint32_t s_wave[16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const uint4 n = ((const uint4*)(counts + (size_t)blockIdx.x * kFL))[tid];
+  uint4* mine = (uint4*)(hist + (size_t)blockIdx.x * slices * kFL) + tid;   // four codes, kFL / 4 apart by slice
+  uint4 n = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll 8
+  for (int s = 0; s < slices; ++s) {
+    const uint4 h = mine[(size_t)s * (kFL / 4)];
+    n = make_uint4(n.x + h.x, n.y + h.y, n.z + h.z, n.w + h.w);
+  }
   const uint32_t own = n.x + n.y + n.z + n.w;
   uint32_t inc = own;
 #pragma unroll
@@ -546,61 +586,137 @@ __global__ __launch_bounds__(1024) void update_scan_kernel(const uint32_t* __res
   }
   if (lane == 63) s_wave[wave] = inc;
   __syncthreads();
-  uint32_t at = inc - own;
-  for (int w = 0; w < wave; ++w) at += s_wave[w];
-  ((uint4*)(cursor + (size_t)blockIdx.x * kFL))[tid] = make_uint4(at, at + n.x, at + n.x + n.y, at + n.x + n.y + n.z);
+  uint32_t before = inc - own;
+  for (int w = 0; w < wave; ++w) before += s_wave[w];
+  uint4 at = make_uint4(before, before + n.x, before + n.x + n.y, before + n.x + n.y + n.z);
+  ((uint4*)(counts + (size_t)blockIdx.x * kFL))[tid] = n;
+  ((uint4*)(start + (size_t)blockIdx.x * kFL))[tid] = at;
+  if (slices == 1) return;
+#pragma unroll 8
+  for (int s = 0; s < slices; ++s) {
+    const uint4 h = mine[(size_t)s * (kFL / 4)];
+    mine[(size_t)s * (kFL / 4)] = at;
+    at = make_uint4(at.x + h.x, at.y + h.y, at.z + h.z, at.w + h.w);
+  }
 }
 
-__global__ __launch_bounds__(256) void update_place_kernel(const uint16_t* __restrict__ codes,
-                                                           const uint32_t* __restrict__ cursor,
-                                                           const uint32_t* __restrict__ rank, uint2* __restrict__ order,
-                                                           int Hkv, int n_new, int pos0, int64_t ctx_stride, long rows) {
-  const int bkv = blockIdx.y, kv = bkv % Hkv, j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= n_new) return;
-  const uint32_t c = codes[(size_t)bkv * ctx_stride + pos0 + j] & (kFL - 1), row = (uint32_t)((size_t)bkv * n_new + j);
-  const uint32_t at = cursor[(size_t)kv * kFL + c] + rank[row];
-  order[(size_t)kv * rows + at] = make_uint2(row, c);   // (512 bytes a key: fewer than 2^32 fit the card)
+__global__ __launch_bounds__(kOrderThreads) void update_place_kernel(const uint16_t* __restrict__ codes,
+                                                                     const uint32_t* __restrict__ first,
+                                                                     uint2* __restrict__ order, int Hkv, int n_new,
+                                                                     int pos0, int64_t ctx_stride, long rows, long per) {
+  __shared__ uint32_t s_at[kFL];
+  const uint32_t* in = first + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kFL;
+  for (int i = threadIdx.x; i < kFL; i += kOrderThreads) s_at[i] = in[i];
+  __syncthreads();
+  uint2* out = order + (size_t)blockIdx.y * rows;
+  for_slice(codes, Hkv, n_new, pos0, ctx_stride, rows, per,
+            [&](uint32_t row, uint32_t c) { out[atomicAdd(&s_at[c], 1u)] = make_uint2(row, c); });   // (512 bytes a key: fewer than 2^32 rows fit the card)
 }
 
-// A wave takes 64 consecutive keys of the order, two dimensions per lane, and adds a run of equal codes up before it
-// goes to memory.  What bounds it: reading the keys, 512 bytes at a time in no order of theirs, and 2 atomics per lane
-// and run (23 keys a run at 768 k keys): 88 us, 156 us for the whole call; 592 us with 128 atomics per
-// key.
+// A wave takes `chunk` consecutive keys of the order, two dimensions per lane, and adds up every run of equal codes.  A run
+// that holds all keys of its codeword becomes the mean at once; of the others, the one that goes on from the wave before and
+// the one that goes on into the next, the sums are left in the wave's two places for update_rest_kernel.  So no sums are
+// cleared, added to or read again in memory.  What bounds it: reading the keys, 512 bytes at a time in no order of theirs
+// (768032 keys, 8 KV heads: 80 us, 4.9 TB/s, and 6 for the rest; 104 with atomics of every run and a division of all sums).
+// Chunks: 64 keys, and 128 where that still makes the waves that keep the memory busy (fewer runs are cut); longer only where
+// the places would not fit the sums' part of the workspace.
+constexpr int kPlaces = 2048;   // waves per KV head whose places fit there
+inline int sum_chunk(long rows, int Hkv) {
+  const long fits = (rows + 64L * kPlaces - 1) / (64L * kPlaces), busy = rows * Hkv >= 300000 ? 2 : 1;
+  return (int)(64 * (fits > busy ? fits : busy));
+}
+
 __global__ __launch_bounds__(256) void update_sorted_kernel(const float* __restrict__ keys, const uint2* __restrict__ order,
-                                                            double* __restrict__ sums, long rows) {
+                                                            double* __restrict__ sums, float* __restrict__ new_cb, long rows,
+                                                            int chunk) {
   const int kv = blockIdx.y, lane = threadIdx.x & 63;
-  const long first = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * 64;
+  const long w = (long)blockIdx.x * 4 + (threadIdx.x >> 6), first = w * chunk;
   if (first >= rows) return;
-  const int n = (int)min(64L, rows - first);   // (uniform in the wave)
-  const uint2 mine = order[(size_t)kv * rows + first + min(lane, n - 1)];
-  double* out = sums + (size_t)kv * kFL * kFD + 2 * lane;
+  const long last = min(rows, first + chunk);   // (uniform in the wave, as all that follows)
+  const uint2* ord = order + (size_t)kv * rows;
+  double* places = sums + ((size_t)kv * kPlaces + w) * 2 * kFD + 2 * lane;
+  float* out = new_cb + (size_t)kv * kFL * kFD + 2 * lane;
+  const uint32_t none = ~0u;
+  const uint32_t code_before = first > 0 ? __builtin_amdgcn_readfirstlane(ord[first - 1].y) : none;
+  const uint32_t code_after = last < rows ? __builtin_amdgcn_readfirstlane(ord[last].y) : none;
   double a0 = 0.0, a1 = 0.0;
-  uint32_t run = __builtin_amdgcn_readfirstlane(mine.y);
+  uint32_t run = __builtin_amdgcn_readfirstlane(ord[first].y), n_run = 0;
+  bool cut = run == code_before;   // the run has keys in the wave before
+  auto finish = [&](bool goes_on) {
+    if (cut || goes_on) {
+      *(double2*)(places + (cut ? 0 : kFD)) = make_double2(a0, a1);
+    } else {
+      out[(size_t)run * kFD] = (float)(a0 / (double)n_run);
+      out[(size_t)run * kFD + 1] = (float)(a1 / (double)n_run);
+    }
+  };
   constexpr int U = 8;
 #pragma unroll 1
-  for (int i0 = 0; i0 < n; i0 += U) {
-    float2 x[U];
+  for (long p = first; p < last; p += 64) {
+    const int n = (int)min(64L, last - p);
+    const uint2 mine = ord[p + min(lane, n - 1)];
+#pragma unroll 1
+    for (int i0 = 0; i0 < n; i0 += U) {
+      float2 x[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t row = __builtin_amdgcn_readlane(mine.x, min(i0 + u, n - 1));
-      x[u] = *(const float2*)(keys + (size_t)row * kFD + 2 * lane);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (i0 + u >= n) break;
-      const uint32_t c = __builtin_amdgcn_readlane(mine.y, i0 + u);
-      if (c != run) {   // (uniform)
-        unsafeAtomicAdd(&out[(size_t)run * kFD], a0);
-        unsafeAtomicAdd(&out[(size_t)run * kFD + 1], a1);
-        a0 = a1 = 0.0;
-        run = c;
+      for (int u = 0; u < U; ++u) {
+        const uint32_t row = __builtin_amdgcn_readlane(mine.x, min(i0 + u, n - 1));
+        x[u] = *(const float2*)(keys + (size_t)row * kFD + 2 * lane);
       }
-      a0 += (double)x[u].x;
-      a1 += (double)x[u].y;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (i0 + u >= n) break;
+        const uint32_t c = __builtin_amdgcn_readlane(mine.y, i0 + u);
+        if (c != run) {
+          finish(false);
+          a0 = a1 = 0.0;
+          run = c;
+          n_run = 0;
+          cut = false;
+        }
+        a0 += (double)x[u].x;
+        a1 += (double)x[u].y;
+        ++n_run;
+      }
     }
   }
-  unsafeAtomicAdd(&out[(size_t)run * kFD], a0);
-  unsafeAtomicAdd(&out[(size_t)run * kFD + 1], a1);
+  finish(run == code_after);
+}
+
+// The codewords whose keys more than one wave added up, those without keys, and the counts: 16 codewords a wave.
+constexpr int kRestPerWave = 16;
+__global__ __launch_bounds__(256) void update_rest_kernel(const double* __restrict__ sums, const uint32_t* __restrict__ counts,
+                                                          const uint32_t* __restrict__ start, const float* __restrict__ old_cb,
+                                                          float* __restrict__ new_cb, int32_t* __restrict__ counts_out,
+                                                          int chunk) {
+  const int kv = blockIdx.y, lane = threadIdx.x & 63;
+  const int c0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * kRestPerWave;
+  const size_t cw = (size_t)kv * kFL + c0 + lane % kRestPerWave;
+  const uint32_t n = counts[cw], at = start[cw];
+  if (counts_out && lane < kRestPerWave) counts_out[cw] = (int32_t)n;
+  const uint32_t w0 = at / (uint32_t)chunk, w1 = n ? (at + n - 1) / (uint32_t)chunk : w0;
+  uint64_t todo = __builtin_amdgcn_ballot_w64(lane < kRestPerWave && (n == 0 || w1 > w0));
+  while (todo) {   // (uniform)
+    const int i = (int)__builtin_ctzll(todo);
+    todo &= todo - 1;
+    const uint32_t ni = __builtin_amdgcn_readlane(n, i), a = __builtin_amdgcn_readlane(w0, i), z = __builtin_amdgcn_readlane(w1, i);
+    const size_t o = ((size_t)kv * kFL + c0 + i) * kFD + 2 * lane;
+    if (ni == 0) {
+      new_cb[o] = old_cb[o];   // (codebooks are aligned to their elements, no more)
+      new_cb[o + 1] = old_cb[o + 1];
+      continue;
+    }
+    const double* places = sums + (size_t)kv * kPlaces * 2 * kFD + 2 * lane;
+    double2 s = *(const double2*)(places + ((size_t)a * 2 + 1) * kFD);
+#pragma unroll 8
+    for (uint32_t w = a + 1; w <= z; ++w) {
+      const double2 x = *(const double2*)(places + (size_t)w * 2 * kFD);
+      s.x += x.x;
+      s.y += x.y;
+    }
+    new_cb[o] = (float)(s.x / (double)ni);
+    new_cb[o + 1] = (float)(s.y / (double)ni);
+  }
 }
 
 __global__ __launch_bounds__(256) void update_mean_kernel(const double* __restrict__ sums,
@@ -618,7 +734,7 @@ __global__ __launch_bounds__(256) void update_mean_kernel(const double* __restri
 }  // namespace
 
 struct FitWs {
-  size_t off_counts, off_cursor, off_rank, off_order, update_bytes;   // of the update; its sums come first
+  size_t off_counts, off_start, off_hist, off_order, update_bytes;   // of the update; its sums come first
   size_t bytes;
 };
 // Rows of a KV head from which the second moment is taken from digits: 100 samples of 32 heads and 8 KV heads 13.8 -> 13.5 us,
@@ -637,8 +753,8 @@ static FitWs fit_ws(const a2ats_dims& d) {
   take(cws * d.sub_dim * sizeof(double));
   w.off_counts = take(cws * sizeof(uint32_t));
   const bool single = single_codebook(d);
-  w.off_cursor = take(single ? cws * sizeof(uint32_t) : 0);
-  w.off_rank = take(single ? (size_t)d.batch * d.n_kv_heads * (size_t)d.ctx_stride * sizeof(uint32_t) : 0);
+  w.off_start = take(single ? cws * sizeof(uint32_t) : 0);
+  w.off_hist = take(single ? (size_t)d.batch * d.n_kv_heads * (size_t)d.ctx_stride * sizeof(uint32_t) : 0);
   w.off_order = take(single ? (size_t)d.batch * d.n_kv_heads * (size_t)d.ctx_stride * sizeof(uint2) : 0);
   w.update_bytes = o;
   const size_t moment = (size_t)d.n_kv_heads * moment_parts(d.n_kv_heads) * kMomentPart;
@@ -694,9 +810,6 @@ hipError_t launch_codebook_update(const a2ats_dims& d, const float* keys, int n_
   uint8_t* base = (uint8_t*)ws;
   double* sums = (double*)base;
   uint32_t* counts = (uint32_t*)(base + w.off_counts);
-  hipLaunchKernelGGL(update_clear_kernel, dim3(1024), dim3(256), 0, stream, sums, counts, n_elems, cws);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
   const int Hkv = d.n_kv_heads, bkv = d.batch * Hkv;
   const long rows = (long)d.batch * n_new, n_keys = rows * Hkv;
   // Few keys are added one by one: below these counts the further launches, or filling and emptying the sums in LDS,
@@ -704,6 +817,32 @@ hipError_t launch_codebook_update(const a2ats_dims& d, const float* keys, int n_
   // 29, 80000 75 -> 51; M = 16, 8000 keys 18 -> 21, 16000 29 -> 24; M = 32, 2000 keys 13 -> 14, 8000 28 -> 15).
   // So are those of a single codebook whose order the workspace has no room for.
   const bool one_by_one = n_keys < (single_codebook(d) ? 48000 : 192000 / d.n_sub) || (single_codebook(d) && ws_bytes < w.update_bytes);
+  hipError_t err;
+  if (n_keys > 0 && single_codebook(d) && !one_by_one) {
+    uint32_t* start = (uint32_t*)(base + w.off_start);
+    uint2* order = (uint2*)(base + w.off_order);
+    const uint16_t* c16 = (const uint16_t*)codes;
+    const OrderSlices sl = order_slices(rows);
+    uint32_t* hist = sl.n > 1 ? (uint32_t*)(base + w.off_hist) : counts;
+    const int chunk = sum_chunk(rows, Hkv);
+    const long waves = (rows + chunk - 1) / chunk;
+    hipLaunchKernelGGL(update_count_kernel, dim3(sl.n, Hkv), dim3(kOrderThreads), 0, stream, c16, hist, Hkv, n_new, pos0,
+                       d.ctx_stride, rows, sl.per);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+    hipLaunchKernelGGL(update_scan_kernel, dim3(Hkv), dim3(1024), 0, stream, hist, counts, start, sl.n);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+    hipLaunchKernelGGL(update_place_kernel, dim3(sl.n, Hkv), dim3(kOrderThreads), 0, stream, c16, sl.n > 1 ? hist : start, order,
+                       Hkv, n_new, pos0, d.ctx_stride, rows, sl.per);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+    hipLaunchKernelGGL(update_sorted_kernel, dim3((unsigned)((waves + 3) / 4), Hkv), dim3(256), 0, stream, keys, order, sums,
+                       codebook_out, rows, chunk);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+    hipLaunchKernelGGL(update_rest_kernel, dim3(kFL / (4 * kRestPerWave), Hkv), dim3(256), 0, stream, sums, counts, start,
+                       codebook, codebook_out, counts_out, chunk);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(update_clear_kernel, dim3(1024), dim3(256), 0, stream, sums, counts, n_elems, cws);
+  if ((err = hipGetLastError()) != hipSuccess) return err;
   if (n_new > 0 && d.batch > 0 && one_by_one) {
     const dim3 grid((n_new + 1) / 2, bkv);
     if (single_codebook(d))
@@ -712,23 +851,6 @@ hipError_t launch_codebook_update(const a2ats_dims& d, const float* keys, int n_
     else
       hipLaunchKernelGGL(update_few_kernel<uint8_t>, grid, dim3(256), 0, stream, keys, (const uint8_t*)codes, sums,
                          counts, Hkv, d.n_sub, d.n_centroids, d.sub_dim, n_new, pos0, d.ctx_stride);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-  } else if (n_new > 0 && d.batch > 0 && single_codebook(d)) {
-    uint32_t* cursor = (uint32_t*)(base + w.off_cursor);
-    uint32_t* rank = (uint32_t*)(base + w.off_rank);
-    uint2* order = (uint2*)(base + w.off_order);
-    const uint16_t* c16 = (const uint16_t*)codes;
-    const dim3 grid((n_new + 255) / 256, bkv);
-    hipLaunchKernelGGL(update_count_kernel, grid, dim3(256), 0, stream, c16, counts, rank, Hkv, n_new, pos0,
-                       d.ctx_stride);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    hipLaunchKernelGGL(update_scan_kernel, dim3(Hkv), dim3(1024), 0, stream, counts, cursor);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    hipLaunchKernelGGL(update_place_kernel, grid, dim3(256), 0, stream, c16, cursor, rank, order, Hkv, n_new, pos0,
-                       d.ctx_stride, rows);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    hipLaunchKernelGGL(update_sorted_kernel, dim3((unsigned)((rows + 255) / 256), Hkv), dim3(256), 0, stream, keys, order,
-                       sums, rows);
     if ((err = hipGetLastError()) != hipSuccess) return err;
   } else if (n_new > 0 && d.batch > 0) {
     // One workgroup per CU: as many shares of the keys as fill the CUs once, of 512 keys or more (a share ends with

@@ -47,6 +47,39 @@ def test_codebook_update(m, least, batch, kv, n, skew):
     assert ((out.double() - want).abs() <= 1.2e-7 * want.abs() + 1e-12).all()
 
 
+@pytest.mark.parametrize("run", [0, 1, 63, 64, 65, 128, 1000])
+@pytest.mark.parametrize("batch,kv,n", [(1, 2, 24577), (7, 3, 14301), (1, 1, 131137), (1, 1, 48000)])
+def test_codebook_update_of_runs_across_waves(batch, kv, n, run):
+    """Codewords with exactly `run` keys (the last one what is left, 0: all keys one codeword's), so that runs begin and end
+    with the waves' shares, span several of them or fill one, and most codewords have no keys."""
+    rows = batch * n
+    g = torch.Generator(device="cuda").manual_seed(rows + run)
+    keys = torch.randn(batch, kv, n, 128, generator=g, device="cuda")
+    by_row = torch.zeros(kv, rows, dtype=torch.int64, device="cuda")
+    for h in range(kv):
+        if run:
+            at = torch.arange(rows, device="cuda") // run
+            by_row[h] = torch.clamp(at, max=4095 - 2 * h)[torch.randperm(rows, generator=g, device="cuda")]
+        else:
+            by_row[h] = 4095 - h
+    codes = by_row.reshape(kv, batch, n).permute(1, 0, 2).contiguous()
+    codebook = torch.randn(kv, 1, 4096, 128, generator=g, device="cuda")
+    out = torch.full_like(codebook, float("nan"))
+    counts = torch.full((kv, 1, 4096), -1, dtype=torch.int32, device="cuda")
+    dims = B.make_dims(batch, kv, kv, 128, 1, n, n_centroids=4096)
+    ws = _workspace(dims, False).fill_(0xA5)
+    B.codebook_update(dims, keys, n, 0, codes.to(torch.int16).unsqueeze(-1).contiguous(), codebook, out, counts, ws)
+    torch.cuda.synchronize()
+    for h in range(kv):
+        x = keys[:, h].reshape(rows, 128).double()
+        sums = torch.zeros(4096, 128, dtype=torch.float64, device="cuda").index_add_(0, by_row[h], x)
+        want_n = torch.bincount(by_row[h], minlength=4096)
+        assert torch.equal(counts[h, 0].long(), want_n)
+        want = torch.where(want_n[:, None] > 0, sums / want_n.clamp(min=1)[:, None], codebook[h, 0].double())
+        # one rounding to float32 of sums whose order differs: an ulp where float64 lands next to a midpoint
+        assert ((out[h, 0].double() - want).abs() <= 1.2e-7 * want.abs() + 1e-12).all()
+
+
 @pytest.mark.parametrize("heads,kv,n", [(8, 1, 1), (5, 1, 13), (6, 2, 1025), (7, 1, 4800), (24, 3, 3001), (64, 64, 40), (8, 1, 4096)])
 @pytest.mark.parametrize("least", [False, True])
 def test_second_moment_shares(heads, kv, n, least):

@@ -55,6 +55,18 @@ bool holds(const a2ats::TopkPlan& plan, const void* ws, size_t ws_bytes) {
   return ws && !misaligned16(ws) && ws_bytes >= plan.bytes;
 }
 
+// Where tables and sampling are one launch and the parts of a problem's sample would need more than one round of the CUs,
+// one workgroup takes the whole sample, as far as its 16-bit counts go: a launch, the copies of the tables and, where table
+// workgroups fill the CUs, the queue of the encoding ones are saved, for a sample that its workgroup takes longer over.
+// Steps, two launches -> one: 256 groups of 65536 tokens, M = 32 368 -> 359 us, 256 of 32768, M = 16 211 -> 207, 320 of 24000
+// 213 -> 210, 512 of 17000 232 -> 228, 160 of 50000, M = 32 211 -> 200; one selection per KV head, 384 of 20000 170 -> 166,
+// 256 of 32768, M = 32 189 -> 185.
+void sample_in_one_part(a2ats::TopkPlan& plan, long problems) {
+  if (problems * plan.P0 <= 256 || (long)plan.P0 * plan.sample_rows > a2ats::kSampleMost) return;
+  plan.sample_rows *= plan.P0;
+  plan.P0 = 1;
+}
+
 }  // namespace
 
 extern "C" {
@@ -298,15 +310,16 @@ int a2ats_decode_select(const a2ats_dims* d, const float* keys, int32_t n_new, i
   if (top_k > 4096) return A2ATS_ERR_UNSUPPORTED;
   if (!codes || !lut || !lut_scale || !topk_count || (top_k > 0 && !topk_idx)) return A2ATS_ERR_INVALID_ARG;
   if (misaligned16(codes)) return A2ATS_ERR_INVALID_ARG;
-  const a2ats::TopkPlan plan = a2ats::make_topk_plan(*d, top_k, window, n_sink);
+  a2ats::TopkPlan plan = a2ats::make_topk_plan(*d, top_k, window, n_sink);
   if (!a2ats::single_codebook(*d) && plan.fast && !holds(plan, ws, ws_bytes)) return A2ATS_ERR_WORKSPACE;
   const bool streams = plan.fast || (plan.wide && holds(plan, ws, ws_bytes));
+  if (streams) sample_in_one_part(plan, (long)d->batch * d->n_kv_heads * plan.NG);
   // The fused launch has every sampling workgroup build its problem's tables: worth it while those
-  // workgroups fit the 256 CUs in one round, a loss when they queue up behind each other.  Its
+  // workgroups fit the 256 CUs in one round or a problem has only one, a loss when they queue up behind each other.  Its
   // sampling workgroups read candidate rows while others write the appended rows, so it is only
   // taken when no appended row can be a candidate of any sequence (pos0 >= ctx_len - window: the
   // usual append of the current token); otherwise the two calls run one after the other.
-  const long n_sample = (long)d->batch * d->n_kv_heads * plan.NG * plan.P0;
+  const bool sample_apart = plan.P0 > 1 && (long)d->batch * d->n_kv_heads * plan.NG * plan.P0 > 256;
   const bool appended_rows_compete = n_new > 0 && (int64_t)pos0 < (int64_t)d->ctx_len - window;
   // (short contexts have a launch of their own for the whole call, under the same condition)
   const bool by_head = !streams && a2ats::takes_head_route(*d, n_new, window, n_sink, false);
@@ -335,7 +348,7 @@ int a2ats_decode_select(const a2ats_dims* d, const float* keys, int32_t n_new, i
                                              (hipStream_t)stream);
     return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
   }
-  if (a2ats::single_codebook(*d) || appended_rows_compete || (!in_one && (!streams || n_sample > 256))) {   // the two calls, with their own checks
+  if (a2ats::single_codebook(*d) || appended_rows_compete || (!in_one && (!streams || sample_apart))) {   // the two calls, with their own checks
     rc = a2ats_decode_prologue(d, keys, n_new, pos0, codebook, weights, weight_mode, codes, q, q_dtype, cos_b,
                                sin_b, q_rot, lut, lut_scale, ws, ws_bytes, stream);
     if (rc != A2ATS_OK) return rc;
@@ -373,7 +386,7 @@ int a2ats_decode_select(const a2ats_dims* d, const float* keys, int32_t n_new, i
       false, (hipStream_t)stream);
   if (e != hipSuccess) return A2ATS_ERR_HIP;
   e = a2ats::launch_score_topk(*d, codes, a2ats::CodePages{nullptr, 0, 0}, lut, lut_scale, top_k, window, n_sink,
-                               seq_lens, topk_idx, topk_count, topk_score, nullptr, ws, true, (hipStream_t)stream);
+                               seq_lens, topk_idx, topk_count, topk_score, nullptr, ws, plan.P0, (hipStream_t)stream);
   return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
 }
 
@@ -402,11 +415,12 @@ int a2ats_decode_select_shared(const a2ats_dims* d, const float* keys, int32_t n
     return A2ATS_ERR_INVALID_ARG;
   a2ats_dims dk = *d;   // the score/top-K side sees one table head per KV head
   dk.n_q_heads = d->n_kv_heads;
-  const a2ats::TopkPlan plan = a2ats::make_topk_plan(dk, top_k, window, n_sink);
+  a2ats::TopkPlan plan = a2ats::make_topk_plan(dk, top_k, window, n_sink);
   if (plan.fast && !holds(plan, ws, ws_bytes)) return A2ATS_ERR_WORKSPACE;
   if (plan.wide && !holds(plan, ws, ws_bytes)) ws = nullptr;   // the exact route
   const bool streams = plan.fast || (plan.wide && ws);
-  const long n_sample = (long)d->batch * d->n_kv_heads * plan.P0;
+  if (streams) sample_in_one_part(plan, (long)d->batch * d->n_kv_heads);
+  const bool sample_apart = plan.P0 > 1 && (long)d->batch * d->n_kv_heads * plan.P0 > 256;
   const bool appended_rows_compete = n_new > 0 && (int64_t)pos0 < (int64_t)d->ctx_len - window;
   hipError_t e;
   if (!streams && !appended_rows_compete && a2ats::takes_head_route(*d, n_new, window, n_sink, true)) {
@@ -421,7 +435,7 @@ int a2ats_decode_select_shared(const a2ats_dims* d, const float* keys, int32_t n
                                           topk_score, true, (hipStream_t)stream);
     return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
   }
-  if (!streams || n_sample > 256 || appended_rows_compete) {   // the three launches one after the other
+  if (!streams || sample_apart || appended_rows_compete) {   // the three launches one after the other
     // (at most 32 keys per sequence: the append-time encoder, which needs no workspace)
     if ((e = a2ats::launch_encode(*d, keys, n_new, pos0, codebook, weights, mode, codes, nullptr,
                                   (hipStream_t)stream)) != hipSuccess)
@@ -430,7 +444,7 @@ int a2ats_decode_select_shared(const a2ats_dims* d, const float* keys, int32_t n
                                             (hipStream_t)stream)) != hipSuccess)
       return A2ATS_ERR_HIP;
     e = a2ats::launch_score_topk(dk, codes, a2ats::CodePages{nullptr, 0, 0}, lut, lut_scale, top_k, window, n_sink,
-                                 seq_lens, topk_idx, topk_count, topk_score, nullptr, ws, false,
+                                 seq_lens, topk_idx, topk_count, topk_score, nullptr, ws, 0,
                                  (hipStream_t)stream);
     return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
   }
@@ -440,7 +454,7 @@ int a2ats_decode_select_shared(const a2ats_dims* d, const float* keys, int32_t n
                                            top_k, window, n_sink, true, (hipStream_t)stream);
   if (e != hipSuccess) return A2ATS_ERR_HIP;
   e = a2ats::launch_score_topk(dk, codes, a2ats::CodePages{nullptr, 0, 0}, lut, lut_scale, top_k, window, n_sink,
-                               seq_lens, topk_idx, topk_count, topk_score, nullptr, ws, true, (hipStream_t)stream);
+                               seq_lens, topk_idx, topk_count, topk_score, nullptr, ws, plan.P0, (hipStream_t)stream);
   return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
 }
 

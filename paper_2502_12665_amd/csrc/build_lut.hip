@@ -311,7 +311,7 @@ __global__ __launch_bounds__(kLutThreads) void decode_prologue_kernel(
 // sampling workgroup (P0 per problem) builds its problem's tables itself -- the arithmetic is a few
 // microseconds and identical in all of them -- keeps the coarse table in LDS and scores its share of
 // the sample against it; part 0 of a problem also writes the tables out for the launches that
-// follow.  The remaining workgroups encode the appended keys.  Saves one launch and the copy of the
+// follow.  The remaining workgroups encode the appended keys, or (folded, as in decode_prologue_kernel) these do.  Saves one launch and the copy of the
 // table from global memory per step; every result is bit for bit that of the separate calls.
 // SHARED: one table per KV head from the summed rotated queries of its heads (build_lut_body<.., true>);
 // the thresholds are then per KV head (NG is 1 and the sampling sees Hkv table heads).
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(kLutThreads) void decode_select_prologue_kernel(
     const float* __restrict__ keys, const float* __restrict__ weights, int mode,
     uint8_t* __restrict__ codes, int n_new, int pos0, int64_t ctx_stride,
     const int32_t* __restrict__ seq_lens, int32_t* __restrict__ thr, int P0, int sample_rows, int ctx_len,
-    int top_k, int window, int n_sink, int sweeps) {
+    int top_k, int window, int n_sink, int sweeps, int folded) {
   constexpr int M = 128 / DS;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   if ((int)blockIdx.x < n_sample) {
@@ -335,6 +335,8 @@ __global__ __launch_bounds__(kLutThreads) void decode_select_prologue_kernel(
     sample_threshold_body<M, kLutThreads, true>(prob, p, codes, CodePages{nullptr, 0, 0}, lut, seq_lens, thr, B,
                                                 SHARED ? Hkv : Hq, Hkv, NG, P0, sample_rows, ctx_len, ctx_stride,
                                                 top_k, window, n_sink, dyn_lds);
+    if (folded)   // (see decode_prologue_kernel)
+      encode_few_block<DS>((int)blockIdx.x, sweeps, keys, codebook, weights, mode, codes, B, Hkv, n_new, pos0, ctx_stride);
     return;
   }
   encode_few_block<DS>((int)blockIdx.x - n_sample, sweeps, keys, codebook, weights, mode, codes, B, Hkv, n_new, pos0,
@@ -686,10 +688,8 @@ hipError_t launch_decode_select_prologue(const a2ats_dims& d, const float* keys,
   const int G = d.n_q_heads / d.n_kv_heads;
   const int NG = shared ? 1 : (G + kHeadsPerGroup - 1) / kHeadsPerGroup;
   const int n_sample = d.batch * d.n_kv_heads * NG * P0;
-  const long n_pairs = (long)d.batch * d.n_kv_heads * n_new * d.n_sub;
-  const int sweeps = encode_few_sweeps(n_pairs);
-  const long per_wg = (long)kFewPairsPerSweep * sweeps;
-  const dim3 grid(n_sample + (unsigned)((n_pairs + per_wg - 1) / per_wg)), block(kLutThreads);
+  const AppendPlan ap = append_plan((long)d.batch * d.n_kv_heads * n_new * d.n_sub, n_sample);
+  const dim3 grid(n_sample + ap.n_enc), block(kLutThreads);
   if (grid.x == 0) return hipSuccess;
   static LdsSlot s_lds[8][16];
   hipError_t err;
@@ -701,7 +701,7 @@ hipError_t launch_decode_select_prologue(const a2ats_dims& d, const float* keys,
     hipLaunchKernelGGL((decode_select_prologue_kernel<DS, BF, SH>), grid, block, kCoarseLdsBytes, stream, q, \
                        cos_b, sin_b, codebook, q_rot, lut, lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, NG, \
                        n_sample, keys, weights, mode, codes, n_new, pos0, d.ctx_stride, seq_lens, thr, P0,   \
-                       sample_rows, d.ctx_len, top_k, window, n_sink, sweeps);                               \
+                       sample_rows, d.ctx_len, top_k, window, n_sink, ap.sweeps, ap.folded);                               \
   } while (0)
 #define A2ATS_LAUNCH_SEL2(DS, BF, SLOT)                                    \
   do {                                                                     \

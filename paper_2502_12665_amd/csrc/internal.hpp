@@ -14,6 +14,7 @@
 namespace a2ats {
 
 // How a2ats_score_topk runs for a shape, and how it carves its workspace.
+constexpr int kSampleMost = 8192;   // sampled rows of a workgroup: its counts are 16 bits wide
 struct TopkPlan {
   bool fast;            // sampled threshold + one streaming pass, up to 2048 winners
   bool wide;            // the same for more winners; without a workspace it falls back to the exact route
@@ -64,10 +65,10 @@ hipError_t launch_build_lut(const a2ats_dims& d, const void* q, int q_dtype, con
 hipError_t launch_score_topk(const a2ats_dims& d, const uint8_t* codes, const CodePages& pg, const int32_t* lut,
                              const float* lut_scale, int top_k, int window, int n_sink,
                              const int32_t* seq_lens, int32_t* topk_idx, int32_t* topk_count,
-                             float* topk_score, float* scores_out, void* ws, bool presampled, hipStream_t stream,
+                             float* topk_score, float* scores_out, void* ws, int presampled, hipStream_t stream,
                              hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 // Decode prologue (append-time encode + tables) and the threshold sampling of the streaming route in
-// one launch; launch_score_topk(..., presampled = true) then skips its sampling launch.  shared: one table
+// one launch; launch_score_topk(..., presampled = P0) then skips its sampling launch.  shared: one table
 // and one set of thresholds per KV head (d has the real head counts; the score/top-K launches that follow
 // take dims with n_q_heads = n_kv_heads).
 hipError_t launch_decode_select_prologue(const a2ats_dims& d, const float* keys, int n_new, int pos0,

@@ -73,8 +73,8 @@ TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink) 
     // the table build) whatever it samples.  So the number of parts is what keeps the sampling
     // launch in one round of the 256 CUs beside the workgroups that encode a one-key append
     // (batch * n_kv_heads * M / 16), with about 2048 rows per part where that leaves a choice; a
-    // batch whose problems alone exceed one round (the sampling is then a launch of its own) takes
-    // parts of up to 4096 rows.  Measured steps (one-key append, 1/16 in 1024-row parts before):
+    // batch whose problems alone exceed one round takes parts of up to 4096 rows where the sampling is a
+    // launch of its own, and only one where it shares one with the tables (sample_in_one_part).  Measured steps (one-key append, 1/16 in 1024-row parts before):
     // batch 4 x 131072 tokens 82.4 -> 81.3 us, batch 16 x 32768 tokens 122.2 -> 117.6 us, batch 32 x
     // 65536 tokens with 7 heads per KV head 390.7 -> 382.5 us.
     long s_tot = ncand / 8 / 512 * 512;
@@ -763,7 +763,7 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
                                       const CodePages& pg, const int32_t* lut, const float* lut_scale, int top_k, int window,
                                       int n_sink, const int32_t* seq_lens, int32_t* topk_idx,
                                       int32_t* topk_count, float* topk_score, float* scores_out,
-                                      void* ws, bool presampled, hipStream_t stream, hipEvent_t ev_start,
+                                      void* ws, int presampled, hipStream_t stream, hipEvent_t ev_start,
                                       hipEvent_t ev_stop) {
   const int B = d.batch, Hq = d.n_q_heads, Hkv = d.n_kv_heads, NG = plan.NG;
   const int heads = B * Hq, problems = B * Hkv * NG;
@@ -873,9 +873,10 @@ hipError_t launch_codes_to_pages(const a2ats_dims& d, const uint8_t* rows, int n
 hipError_t launch_score_topk(const a2ats_dims& d, const uint8_t* codes, const CodePages& pg, const int32_t* lut,
                              const float* lut_scale, int top_k, int window, int n_sink,
                              const int32_t* seq_lens, int32_t* topk_idx, int32_t* topk_count,
-                             float* topk_score, float* scores_out, void* ws, bool presampled,
+                             float* topk_score, float* scores_out, void* ws, int presampled,
                              hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  const TopkPlan plan = make_topk_plan(d, top_k, window, n_sink);
+  TopkPlan plan = make_topk_plan(d, top_k, window, n_sink);
+  if (presampled) plan.P0 = presampled;
   if (d.n_sub == 16)
     return launch_score_topk_m<16>(d, plan, codes, pg, lut, lut_scale, top_k, window, n_sink, seq_lens,
                                    topk_idx, topk_count, topk_score, scores_out, ws, presampled, stream,

@@ -386,3 +386,52 @@ def test_selection_by_head_equals_the_calls(Bn, G, Hkv, M, N, K, w, n_sink, n_ne
         res.append((codes, lut, scale, st.q_rot, idx, count, score.view(torch.int32)))
     for i, (a, b) in enumerate(zip(*res)):
         assert torch.equal(a, b), f"output {i} differs"
+
+
+@pytest.mark.parametrize("Bn,G,Hkv,M,N,K,w,n_sink,n_new,lens", [
+    (40, 4, 8, 16, 16500, 400, 64, 4, 1, None),      # 320 groups, two rounds: they sample and encode
+    (34, 7, 4, 32, 18000, 300, 64, 0, 2, True),      # 272, every other of three heads; ragged lengths
+    (24, 4, 8, 16, 60000, 700, 64, 0, 1, None),      # 192 groups, the sample of two parts taken by one workgroup
+    (24, 4, 8, 16, 70000, 700, 64, 0, 1, None),      # too many rows for one: the sampling stays a launch of its own
+    (17, 4, 8, 32, 40000, 2300, 64, 4, 1, True),     # a wide selection
+    (40, 4, 8, 16, 16500, 400, 64, 0, 0, None),      # nothing appended
+])
+@pytest.mark.parametrize("shared", [False, True])
+def test_decode_select_of_many_sequences_equals_the_calls(Bn, G, Hkv, M, N, K, w, n_sink, n_new, lens, shared):
+    """Tables, sampling and append by the same workgroups, where they are more than one round of the CUs, against the calls
+    one after the other, whose samples have other parts: every output bit for bit, twice in the same workspace."""
+    wl = synth.Workload("many", Bn, G * Hkv, Hkv, 128, M, N, K, w, n_sink=n_sink, seed=N + K + M)
+    xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
+    weights = synth.make_query_second_moment(wl)["h_diag"].cuda()
+    keys = synth.make_encode_keys(wl, n_new, device="cuda", stress=True) if n_new else None
+    dims = H.dims_of(wl)
+    sel = B.make_dims(Bn, Hkv, Hkv, 128, M, N) if shared else dims
+    heads = Hkv if shared else G * Hkv
+    sl = None
+    if lens:
+        sl = torch.randint(0, N + 1, (Bn,), generator=torch.Generator().manual_seed(N), dtype=torch.int32).cuda()
+    ws = torch.full((B.workspace_bytes(sel, B.OP_SCORE_TOPK, K, w),), 0xA5, dtype=torch.uint8, device="cuda")
+    res = []
+    for one in (False, True, True):
+        st = B.DecodeState(dims, K, w, n_sink, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
+        lut = torch.full((B.lut_elems(sel),), -1, dtype=torch.int32, device="cuda")
+        scale = torch.zeros(Bn, heads, device="cuda")
+        idx = torch.full((Bn * heads * K + 8,), -7, dtype=torch.int32, device="cuda")
+        score = torch.full((Bn * heads * K + 8,), -7.0, device="cuda")
+        count = torch.full((Bn, heads), -7, dtype=torch.int32, device="cuda")
+        codes = xd["codes"].clone()
+        if one:
+            (B.decode_select_shared if shared else B.decode_select)(
+                dims, keys, n_new, N - n_new, xd["codebook"], weights, B.W_DIAG, codes, xd["q"], st.cos_b, st.sin_b, st.q_rot,
+                lut, scale, K, w, n_sink, sl, idx, count, score, ws)
+        else:
+            if n_new:
+                B.encode_keys(dims, keys, n_new, N - n_new, xd["codebook"], weights, B.W_DIAG, codes,
+                              torch.empty(B.workspace_bytes(dims, B.OP_ENCODE), dtype=torch.uint8, device="cuda"))
+            (B.build_lut_shared if shared else B.build_lut)(dims, xd["q"], st.cos_b, st.sin_b, xd["codebook"], st.q_rot, lut, scale)
+            B.score_topk(sel, codes, lut, scale, K, w, n_sink, sl, idx, count, score, None, ws)
+        torch.cuda.synchronize()
+        res.append((codes, lut, scale, st.q_rot, idx, count, score.view(torch.int32)))
+    for other in res[1:]:
+        for i, (a, b) in enumerate(zip(res[0], other)):
+            assert torch.equal(a, b), f"output {i} differs"

@@ -422,7 +422,7 @@ int a2ats_decode_select_shared(const a2ats_dims* dims, const float* keys, int32_
  *   codebook_out  [dev, out, f32 Hkv*M*L*ds]  means in float64, rounded once; a codeword without keys
  *                                             keeps its value (may alias `codebook`)
  *   counts        [dev, out, nullable, int32 Hkv*M*L]  keys per codeword
- * The sums are float64 hardware atomics: the last bits of a mean can differ from run to run.
+ * The sums are float64, in an order that varies: the last bits of a mean can differ from run to run.
  * Workspace of both calls: a2ats_workspace_bytes(dims, A2ATS_OP_FIT, 0, 0) is what their fastest forms use.  For a single
  * codebook it has 12 bytes per key that batch and ctx_stride allow (the order of the keys), and below 8 KV heads more partial
  * sums of the second moment than above.  Where that is more than 8 MiB per KV head, these are enough: same results, later.

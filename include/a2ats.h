@@ -410,7 +410,10 @@ int a2ats_decode_select_shared(const a2ats_dims* dims, const float* keys, int32_
  * a2ats_second_moment: H = E[q~^T q~], one D x D matrix per KV head, from n_samples rotated query
  * rows; the G query heads of a KV head are pooled.
  *   q_rot  [dev, f32 n_samples*Hq*D]   rotated queries (e.g. the q_rot output of a2ats_build_lut)
- *   h_out  [dev, out, f32 Hkv*D*D]     accumulated in float64, rounded once; zeros if n_samples == 0
+ *   h_out  [dev, out, f32 Hkv*D*D]     accumulated in float64, rounded once; zeros if n_samples == 0.
+ *                                      (From 2048 rows of a KV head on, with more than 16384 rows in all, stretches of rows are
+ *                                      summed exactly from 48-bit fixed-point forms of the entries where that is off by less than
+ *                                      2^-26 of their sum of |q_i q_j|, a quarter of a float32 ulp of it, and usually 2^-34.)
  * H (or its diagonal / diagonal blocks) is the `weights` argument of a2ats_encode_keys.
  *
  * a2ats_codebook_update: the centroid step of k-means under the query-aware distortion.  The paper

@@ -54,14 +54,13 @@ constexpr MomentPlan make_moment_plan() {
 // a block) is the layout of both operands of v_mfma_f64_16x16x4_f64, so one conversion of a loaded float serves
 // every tile of its block, as row and as column operand.  Register r of a result: row 4 r + lane / 16, column lane % 16
 // of the tile -- or its transpose, which is the same sum.
+typedef __attribute__((ext_vector_type(4))) double f64x4;
 template <int W>
-__device__ __forceinline__ void moment_body(const float* __restrict__ q_rot, double* __restrict__ out, int Hq, int G, int kv,
-                                            uint32_t row0, uint32_t row1) {
-  typedef __attribute__((ext_vector_type(4))) double f64x4;
+__device__ __forceinline__ void moment_body(const float* __restrict__ q_rot, int Hq, int G, int kv, uint32_t row0,
+                                            uint32_t row1, f64x4 (&acc)[9]) {
   constexpr int kSteps = kMomentRows / 4;
   constexpr MomentPlan P = make_moment_plan();
   const int lane = threadIdx.x & 63, k = lane >> 4, c = lane & 15;
-  f64x4 acc[9];
 #pragma unroll
   for (int t = 0; t < 9; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
   auto row_at = [&](uint32_t r) { return q_rot + ((size_t)(r / (uint32_t)G) * Hq + (uint32_t)(kv * G) + r % (uint32_t)G) * kFD + c; };
@@ -129,10 +128,16 @@ __device__ __forceinline__ void moment_body(const float* __restrict__ q_rot, dou
     }
     add(x);
   }
+}
+
+// use(place in a partial sum, sum) for each of a lane's.
+template <int W, typename USE>
+__device__ __forceinline__ void for_moments(const f64x4 (&acc)[9], const USE& use) {
+  const int lane = threadIdx.x & 63, k = lane >> 4, c = lane & 15;
 #pragma unroll
   for (int t = 0; t < 9; ++t)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) out[((size_t)(9 * W + t) * 16 + 4 * r + k) * 16 + c] = acc[t][r];
+    for (int r = 0; r < 4; ++r) use(((9 * W + t) * 16 + 4 * r + k) * 16 + c, acc[t][r]);
 }
 
 // What bounds it: the float64 matrix cores, which run at the vector ALU's rate; what they save are the other half of
@@ -144,12 +149,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3))) voi
   const int kv = blockIdx.y, p = blockIdx.x, G = Hq / Hkv;
   const uint32_t row0 = p * rows_per_part, row1 = min(rows, row0 + rows_per_part);   // (host: row0 < rows)
   double* out = part + ((size_t)kv * gridDim.x + p) * (kMomentTiles * 256);
+  f64x4 acc[9];
+#define A2ATS_WAVE(W)                                                          \
+  moment_body<W>(q_rot, Hq, G, kv, row0, row1, acc);                           \
+  for_moments<W>(acc, [&](int at, double v) { out[at] = v; })
   switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
-    case 0: moment_body<0>(q_rot, out, Hq, G, kv, row0, row1); break;
-    case 1: moment_body<1>(q_rot, out, Hq, G, kv, row0, row1); break;
-    case 2: moment_body<2>(q_rot, out, Hq, G, kv, row0, row1); break;
-    default: moment_body<3>(q_rot, out, Hq, G, kv, row0, row1);
+    case 0: A2ATS_WAVE(0); break;
+    case 1: A2ATS_WAVE(1); break;
+    case 2: A2ATS_WAVE(2); break;
+    default: A2ATS_WAVE(3);
   }
+#undef A2ATS_WAVE
 }
 
 // The same sums by 8-bit integer products, for many samples.  A dimension of a workgroup's rows is taken in units of a power
@@ -157,23 +167,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3))) voi
 // digits' products that have a weight in common in one sum, and from time to time the six sums go to the float64 partial sum.
 // Products of digits a and b with a + b > 5 are left out.
 //
-// Error: the unit is at most 2^-43 of the largest value of the first 64 rows (they get two to three bits of headroom; where a
-// later row does not fit, the sums go to memory and the unit grows), and a row's entry is off by about that twice, times
-// the values, and by what is left out, 2^-48 of the squared range: against float64 some 1e-14 of sqrt(H_ii H_jj) over
-// thousands of rows, where a float32 result is off by 6e-8 of itself.
-// Values that are not finite send the workgroup through the float64 products.
+// Error: with V a value in units of its upper three digits, |V| <= 2^22 (the first 64 rows get two to three bits of headroom;
+// where a later row does not fit, the sums go to memory and the unit grows), V is off by at most 2^-24 and a row's product by
+// at most 0.5 from that and 1.26 from what is left out (five pairs of weight 2^-16, of digits up to 2^7).  Usually 0.2, of
+// either sign: for normal values 1e-14 of sqrt(H_ii H_jj) over thousands of rows.  That is fine beside products that are
+// large against it, and nothing where a few rows are so large that those of all others have no upper digits; so
+// the workgroup also adds up the products of the magnitudes of the upper digits, of every fourth step: a quarter of that, times
+// 2^32, is no more than the sum of |V_i V_j| over all rows.  Where it shows for every i, j that a stretch of rows (in the same
+// units) is off by at most 2^-26 of the sum of |x_i x_j|, half of half an ulp of a float32 result of one sign, the digits' sums
+// are taken; else, and where values are not finite, the rows from the first of that stretch on go through the float64 products.
+// 4096 rows, a row of 1000 times the usual size for i and another one for j: off by 7e-9 of H_ij without this, 1e6 times: 1e-3.
 //
 // A wave's tiles of 16 x 16 are those of two blocks of rows and two of columns, so that a digit read from LDS serves two
 // products; the waves of a SIMD (w, w + 4) have nine tiles together.  One of them turns the next rows into digits before its
 // products, the other after them: so one's vector instructions run beside the other's products.
 //
 // What bounds it: the matrix cores (756 products of 16 cycles for 64 rows, a wave by itself issues one in 36) and beside
-// them, not quite hidden, the rows: 50000 samples x 32 heads 532 us by float64 products, 328 by digits; without the
-// products, reading and conversion take 186.  8000 samples x 64 KV heads 266 -> 116.  The vector instructions of the conversion
+// them, not quite hidden, the rows: 50000 samples x 32 heads 524 us by float64 products, 324 by digits (312 without the upper
+// digits' products); without the products, reading and conversion take 186.  8000 samples x 64 KV heads 253 -> 112.  A sample
+// 1e5 times the usual size in the middle: 549 and 364.  The vector instructions of the conversion
 // between the products, one by one, changed nothing (347), nor did addresses prepared once (325).
 constexpr int kDigits = 6, kDigitRows = 64, kDigitThreads = 512;
 constexpr int kDigitFrag = 16 * kDigitRows;                      // bytes of one digit of a block of 16 dimensions
 constexpr int kDigitBuf = 8 * kDigits * kDigitFrag;
+constexpr int kTopEvery = 4, kTopFirst = 8;                      // steps whose upper digits are looked at; after which first
+constexpr int kTopMags = 8 * kDigitFrag, kTopSums = kMomentTiles * 256 * 4;   // bytes of their magnitudes, and of the sums
+constexpr int kDigitLds = 2 * kDigitBuf + kTopMags + kTopSums;
+static_assert(kMomentTiles * 256 * sizeof(double) <= 2 * kDigitBuf, "float64 sums in the digits' place");
 constexpr float kDigitLimit = 4194302.f;                         // of a value in units of its upper three digits
 constexpr uint32_t kDigitFlushRows = 16384;                      // 6 x 2^14 a row: fits 31 bits
 typedef __attribute__((ext_vector_type(4))) int i32x4;
@@ -212,6 +232,7 @@ struct DigitLds {
   uint32_t most[kFD];      // largest magnitude of a dimension so far (float bits)
   double unit[kFD];
   int32_t flagged, not_finite;   // the step whose rows do not fit; whether any value is not finite
+  int32_t coarse;                // whether the digits are too coarse for the products of some i, j
 };
 
 template <int W>
@@ -254,6 +275,44 @@ __device__ __forceinline__ void digit_products(const uint8_t* buf, i32x4 (&acc)[
   }
 }
 
+constexpr int tile_index(int i, int j) { return i * 8 - i * (i - 1) / 2 + j - i; }
+
+// Adds the products of a step's magnitudes to this lane's sums.
+template <int W>
+__device__ __forceinline__ void top_products(const uint8_t* mags, i32x4* sums) {
+  constexpr DigitTiles T = digit_tiles(W);
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int t = 0; t < kDigitTiles; ++t)
+    if (t < T.n) {
+      const i32x4 row = *(const i32x4*)(mags + T.i[t] * kDigitFrag + lane * 16);
+      const i32x4 col = *(const i32x4*)(mags + T.j[t] * kDigitFrag + lane * 16);
+      i32x4& s = sums[tile_index(T.i[t], T.j[t]) * 64 + lane];
+      s = __builtin_amdgcn_mfma_i32_16x16x64_i8(row, col, s, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);   // (registers)
+    }
+}
+
+// Whether this lane's sums are large enough for `rows` rows.  (A dimension that has been zero so far has exact products.)
+template <int W>
+__device__ __forceinline__ bool top_suffices(const i32x4* sums, const DigitLds& L, uint32_t rows) {
+  constexpr DigitTiles T = digit_tiles(W);
+  const int lane = threadIdx.x & 63;
+  bool ok = true;
+#pragma unroll
+  for (int t = 0; t < kDigitTiles; ++t)
+    if (t < T.n) {
+      const int i = T.i[t], j = T.j[t];
+      const i32x4 s = sums[tile_index(i, j) * 64 + lane];
+      const uint4 m = *(const uint4*)&L.most[16 * i + 4 * (lane >> 4)];
+      const uint32_t most[4] = {m.x, m.y, m.z, m.w}, col = L.most[16 * j + (lane & 15)];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) ok &= 8u * (uint32_t)s[r] >= rows || col == 0u || most[r] == 0u;
+      __builtin_amdgcn_sched_barrier(0);   // (registers)
+    }
+  return ok;
+}
+
 // The sums to the partial sum in memory (`first`: which holds nothing yet).
 template <int W>
 __device__ __forceinline__ void digit_flush(const i32x4 (&acc)[kDigitTiles][kDigits], const DigitLds& L, double* __restrict__ out,
@@ -264,7 +323,7 @@ __device__ __forceinline__ void digit_flush(const i32x4 (&acc)[kDigitTiles][kDig
 #pragma unroll
   for (int t = 0; t < kDigitTiles; ++t) {
     if (t < T.n) {
-      const int i = T.i[t], j = T.j[t], tile = i * 8 - i * (i - 1) / 2 + j - i;
+      const int i = T.i[t], j = T.j[t], tile = tile_index(i, j);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = 4 * (lane >> 4) + r, c = lane & 15;
@@ -280,9 +339,9 @@ __device__ __forceinline__ void digit_flush(const i32x4 (&acc)[kDigitTiles][kDig
   }
 }
 
-// Wave W of a workgroup (every wave passes the same barriers).  False: a value is not finite, and the partial sum unfinished.
+// Wave W of a workgroup (every wave passes the same barriers).
 template <int W>
-__device__ __forceinline__ bool digit_body(const float* __restrict__ q_rot, double* __restrict__ out, int Hq, int kv,
+__device__ __forceinline__ void digit_body(const float* __restrict__ q_rot, double* __restrict__ out, int Hq, int kv,
                                            const FastDiv& G, uint32_t row0, uint32_t row1, uint8_t* s_buf, DigitLds& L) {
   const int tid = threadIdx.x;
   // this thread's dimension, and its 16 rows of a step (the same for the wave)
@@ -326,7 +385,10 @@ __device__ __forceinline__ bool digit_body(const float* __restrict__ q_rot, doub
   // Six digits of each of 16 values.  Value times scale = hi + lo 2^-24, hi its nearest integer (23 bits), lo the nearest even
   // one (25 bits): adding 1.5 2^23 (2^24) leaves them in the mantissa.  With 128 added at every digit but the first, digits are
   // bytes, the carry of lo's first goes to hi, and the top bit of those bytes turned makes them signed.
-  auto convert = [&](const float (&x)[16], uint8_t* buf) {
+  uint8_t* mags = s_buf + 2 * kDigitBuf;
+  i32x4* top_sums = (i32x4*)(mags + kTopMags);   // (a lane's own, as is what it reads of them)
+  // top: also the magnitudes of the upper digits, one less for those below zero.
+  auto convert = [&](const float (&x)[16], uint8_t* buf, bool top) {
     uint32_t w[kDigits][4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -352,12 +414,32 @@ __device__ __forceinline__ bool digit_body(const float* __restrict__ q_rot, doub
     uint8_t* dst = buf + (d >> 4) * (kDigits * kDigitFrag) + ((d & 15) + 16 * rg) * 16;
 #pragma unroll
     for (int a = 0; a < kDigits; ++a) *(uint4*)(dst + a * kDigitFrag) = make_uint4(w[a][0], w[a][1], w[a][2], w[a][3]);
+    if (top) {   // (uniform)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint32_t below = w[0][q] & 0x80808080u;
+        w[0][q] ^= (below << 1) - (below >> 7);   // (all bits of those bytes)
+      }
+      *(uint4*)(mags + (d >> 4) * kDigitFrag + ((d & 15) + 16 * rg) * 16) = make_uint4(w[0][0], w[0][1], w[0][2], w[0][3]);
+    }
+  };
+  auto clear_top = [&]() {
+    constexpr DigitTiles T = digit_tiles(W);
+#pragma unroll
+    for (int t = 0; t < kDigitTiles; ++t)
+      if (t < T.n) top_sums[tile_index(T.i[t], T.j[t]) * 64 + (tid & 63)] = i32x4{0, 0, 0, 0};
+  };
+  auto fine_enough = [&](int steps) {
+    if (!top_suffices<W>(top_sums, L, (uint32_t)steps * kDigitRows)) L.coarse = 1;
+    __syncthreads();
+    return L.coarse == 0;
   };
   float x[16], most;
   if (tid < kFD) L.most[tid] = 0u;
   if (tid == 0) {
     L.flagged = -1;
     L.not_finite = 0;
+    L.coarse = 0;
   }
   load(0, x);
   drop_past_end(0, x);
@@ -365,18 +447,19 @@ __device__ __forceinline__ bool digit_body(const float* __restrict__ q_rot, doub
   atomicMax(&L.most[d], __float_as_uint(most_of(x)) & 0x7fffffffu);
   __syncthreads();
   set_scale();
-  convert(x, s_buf);
+  convert(x, s_buf, true);
   load(min(1, n_steps - 1), x);
   __syncthreads();
-  bool finite = L.not_finite == 0, first = true;
-  int step = 0;
+  bool good = L.not_finite == 0, first = true;
+  int step = 0, start = 0;   // what comes before row `start` is in the partial sum
 #pragma unroll 1
-  while (finite && step < n_steps) {   // (uniform, as the conditions below) a stretch of rows in the same units
+  while (good && step < n_steps) {   // (uniform, as the conditions below) a stretch of rows in the same units
     i32x4 acc[kDigitTiles][kDigits];
 #pragma unroll
     for (int t = 0; t < kDigitTiles; ++t)
 #pragma unroll
       for (int l = 0; l < kDigits; ++l) acc[t][l] = i32x4{0, 0, 0, 0};
+    clear_top();
     const int stop = min(n_steps, step + (int)(kDigitFlushRows / kDigitRows));
     bool fits = true;
 #pragma unroll 1
@@ -387,19 +470,23 @@ __device__ __forceinline__ bool digit_body(const float* __restrict__ q_rot, doub
       auto prepare_next = [&]() {
         drop_past_end(step + 1, x);
         most = most_of(x);
-        convert(x, next);
+        convert(x, next, (step + 1 - start) % kTopEvery == 0);
         if (!(most * scale <= kDigitLimit)) L.flagged = step + 1;
         load(min(step + 2, n_steps - 1), x);
       };
       if (W < 4 && more) prepare_next();
       digit_products<W>(now, acc);
+      if ((step - start) % kTopEvery == 0) top_products<W>(mags, top_sums);
       if (W >= 4 && more) prepare_next();
       __syncthreads();
       ++step;
       fits = L.flagged != step;
-    } while (fits && step < stop);
+      if (fits && step < stop && step - start == kTopFirst) good = fine_enough(kTopFirst);
+    } while (fits && good && step < stop);
+    if (!good || !(good = fine_enough(step - start))) break;
     digit_flush<W>(acc, L, out, first);
     first = false;
+    start = step;
     if (!fits) {   // a larger unit from here on
       __syncthreads();   // (the units have been read)
       atomicMax(&L.most[d], __float_as_uint(most) & 0x7fffffffu);
@@ -408,27 +495,36 @@ __device__ __forceinline__ bool digit_body(const float* __restrict__ q_rot, doub
       float again[16];
       load(step, again);
       drop_past_end(step, again);
-      convert(again, s_buf + (step & 1) * kDigitBuf);
+      convert(again, s_buf + (step & 1) * kDigitBuf, true);
       __syncthreads();
-      finite = L.not_finite == 0;
+      good = L.not_finite == 0;
     }
   }
-  return finite;
+  if (start == n_steps) return;
+  // what is left, by float64 products: one half of the rows each for waves 0 to 3 and 4 to 7
+  const uint32_t from = row0 + (uint32_t)(start * kDigitRows), mid = from + (row1 - from + 1) / 2;
+  f64x4 sums[9];
+  moment_body<W & 3>(q_rot, Hq, (int)G.d, kv, W < 4 ? from : mid, W < 4 ? mid : row1, sums);
+  double* other = (double*)s_buf;
+  if (W >= 4) for_moments<W & 3>(sums, [&](int at, double v) { other[at] = v; });
+  __syncthreads();
+  if (W < 4)
+    for_moments<W & 3>(sums, [&](int at, double v) {
+      v += other[at];
+      out[at] = first ? v : out[at] + v;
+    });
 }
 
 __global__ __launch_bounds__(kDigitThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void second_moment_digits_kernel(
     const float* __restrict__ q_rot, double* __restrict__ part, int Hq, int Hkv, FastDiv G, uint32_t rows,
     uint32_t rows_per_part) {
-  extern __shared__ __align__(16) uint8_t s_buf[];   // two buffers of digits, then DigitLds
-  DigitLds& L = *(DigitLds*)(s_buf + 2 * kDigitBuf);
-  const int kv = blockIdx.y, p = blockIdx.x, g = (int)G.d;
+  extern __shared__ __align__(16) uint8_t s_buf[];   // two buffers of digits, the upper digits' magnitudes and sums, DigitLds
+  DigitLds& L = *(DigitLds*)(s_buf + kDigitLds);
+  const int kv = blockIdx.y, p = blockIdx.x;
   const uint32_t row0 = p * rows_per_part, row1 = min(rows, row0 + rows_per_part);   // (host: row0 < rows)
   double* out = part + ((size_t)kv * gridDim.x + p) * (kMomentTiles * 256);
-#define A2ATS_WAVE(W)                                                              \
-  case W:                                                                          \
-    if (!digit_body<W>(q_rot, out, Hq, kv, G, row0, row1, s_buf, L) && W < 4)      \
-      moment_body<W & 3>(q_rot, out, Hq, g, kv, row0, row1);                       \
-    break
+#define A2ATS_WAVE(W) \
+  case W: digit_body<W>(q_rot, out, Hq, kv, G, row0, row1, s_buf, L); break
   switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
     A2ATS_WAVE(0);
     A2ATS_WAVE(1);
@@ -737,9 +833,11 @@ struct FitWs {
   size_t off_counts, off_start, off_hist, off_order, update_bytes;   // of the update; its sums come first
   size_t bytes;
 };
-// Rows of a KV head from which the second moment is taken from digits: 100 samples of 32 heads and 8 KV heads 13.8 -> 13.5 us,
-// 500 21.5 -> 20.8, 1000 29.7 -> 23.4, 2000 41.3 -> 26.4.  Fewer leave more of a digit sum's error in the mean.
-constexpr long kDigitLeast = 2048;
+// The second moment is taken from digits where the rows are more than a step for each CU (its look at the upper digits pays
+// from the second on): float64 -> digits, 16500 rows of one KV head 41.9 -> 30.9 us, 8000 26.9 -> 28.8; 8 KV heads, 2400 rows each
+// 27.6 -> 22.6, 2048 22.2 -> 24.5; 4 of 4200 28.7 -> 22.1.  And from 2048 rows of a KV head: fewer leave more of a digit sum's
+// error in the mean.
+inline bool moment_by_digits(long rows, int Hkv) { return rows >= 2048 && rows * Hkv > 256L * kDigitRows; }
 constexpr size_t kMomentPart = kMomentTiles * 256 * sizeof(double);   // a partial sum of the second moment
 static FitWs fit_ws(const a2ats_dims& d) {
   const size_t cws = (size_t)d.n_kv_heads * d.n_sub * d.n_centroids;
@@ -778,14 +876,14 @@ hipError_t launch_second_moment(const a2ats_dims& d, const float* q_rot, int64_t
   // at least 64 rows a workgroup: the partials are 72 KB each
   const long held = (long)(ws_bytes / kMomentPart) / d.n_kv_heads, wanted = moment_parts(d.n_kv_heads);
   long most = held < wanted ? held : wanted;
-  const bool digits = rows >= kDigitLeast;
+  const bool digits = moment_by_digits(rows, d.n_kv_heads);
   if (digits && most > 256 / d.n_kv_heads && d.n_kv_heads <= 256) most = 256 / d.n_kv_heads;   // one workgroup a CU
   long per = (rows + most - 1) / most;
   per = ((per < 64 ? 64 : per) + kDigitRows - 1) / kDigitRows * kDigitRows;
   const int parts = (int)((rows + per - 1) / per);
   hipError_t e;
   if (digits) {
-    const size_t lds = 2 * kDigitBuf + sizeof(DigitLds);
+    const size_t lds = kDigitLds + sizeof(DigitLds);
     static LdsSlot s_lds[16];
     if ((e = allow_dynamic_lds(second_moment_digits_kernel, lds, s_lds)) != hipSuccess) return e;
     hipLaunchKernelGGL(second_moment_digits_kernel, dim3(parts, d.n_kv_heads), dim3(kDigitThreads), lds, stream, q_rot,

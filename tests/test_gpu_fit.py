@@ -111,11 +111,13 @@ def _moment(q, kv, least=False):
 
 
 @pytest.mark.parametrize("heads,kv,n,data", [
-    (5, 1, 411, "normal"), (5, 1, 410, "normal"),      # 2055 rows by digits, 2050 too; not multiples of a step of 64
-    (7, 1, 1000, "normal"), (6, 2, 5001, "normal"),    # heads that do not divide a step
+    (5, 1, 411, "normal"), (5, 1, 410, "normal"),      # few rows: float64 products
+    (5, 1, 3277, "normal"), (5, 1, 3276, "normal"),    # 16385 rows are by digits, 16380 not
+    (8, 8, 2049, "normal"), (8, 8, 2047, "normal"),    # 2049 rows of a KV head, 2047
+    (7, 1, 1000, "normal"), (7, 1, 3001, "normal"), (6, 2, 5001, "normal"),   # heads that do not divide a step
     (16, 2, 2049, "steps"),                            # values that grow by 2^10 three times: larger units
-    (4, 4, 3000, "late"),                              # dimensions that are zero in the first rows, tiny, or huge
-    (8, 1, 2000, "correlated"),                        # equal and opposite dimensions
+    (4, 4, 3000, "late"), (4, 4, 9000, "late"),        # dimensions that are zero in the first rows, tiny, or huge
+    (8, 1, 2000, "correlated"), (8, 1, 2100, "correlated"),   # equal and opposite dimensions
 ])
 def test_second_moment_by_digits(heads, kv, n, data):
     g = torch.Generator(device="cuda").manual_seed(n)
@@ -131,19 +133,55 @@ def test_second_moment_by_digits(heads, kv, n, data):
         q[..., 1], q[..., 2] = q[..., 0], -q[..., 0]
     for got, x in _moment(q, kv):
         want = x.t() @ x / x.shape[0]
-        most = x.abs().amax(0)
-        # half an ulp of float32, and of each row's entry two roundings to a unit of 2^-42 of the dimension's largest value
-        # and what is left of the products, 5 x 2^14 of 2^46 units squared: 2^-40 of the largest entry in all
-        assert ((got - want).abs() <= 6e-8 * want.abs() + 2.0 ** -40 * most[:, None] * most[None] + 1e-45).all()
+        # half an ulp of float32, and of the sum of magnitudes what the digits may leave out (see the next test)
+        assert ((got - want).abs() <= 6e-8 * want.abs() + 2e-10 * (x.abs().t() @ x.abs()) / x.shape[0] + 1e-45).all()
         assert torch.equal(got, got.t())
 
 
-def test_second_moment_of_values_that_are_not_finite():
-    q = torch.randn(3000, 4, 128, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
-    q[2999, 0, 3] = float("nan")      # head 0: the last row
+@pytest.mark.parametrize("factor", [30.0, 1e3, 1e4, 1e6, 1e12])
+@pytest.mark.parametrize("heads,kv,n,data", [
+    (4, 1, 4097, "one row each"), (8, 2, 3073, "one row each"), (4, 1, 20000, "last"), (4, 4, 60000, "first"),
+    (5, 1, 30011, "tenth"), (8, 1, 9000, "heads"), (4, 1, 9000, "heavy")])
+def test_second_moment_of_a_few_large_values(factor, heads, kv, n, data):
+    """Rows that are large in one dimension where another is not: H_ij comes from the many small products, which float64
+    sums keep."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q = torch.randn(n, heads, 128, generator=g, device="cuda")
+    q[..., 90] += 0.5 * q[..., 3]
+    if data == "one row each":
+        q[n // 3, 0, 3] *= factor
+        q[n // 2, -1, 90] *= factor
+        q[n - 1, :, 17] *= factor
+    if data == "last":                               # at the end of the workgroups' shares
+        q[n // 8 - 1::n // 8, :, 3] *= factor
+        q[n // 8 - 2::n // 8, :, 90] *= factor
+    if data == "first":
+        q[::n // 32, :, 3:60] *= factor
+        q[1::n // 32, :, 60:] *= factor
+    if data == "tenth":                              # large in one dimension or in the other, not in both
+        rows = torch.rand(n, 1, generator=g, device="cuda")
+        q[..., 3] *= torch.where(rows < 0.1, factor, 1.0)
+        q[..., 90] *= torch.where(rows > 0.9, factor, 1.0)
+    if data == "heads":
+        q[:, 1::2, ::2] *= factor
+        q[:, ::2, 1::2] *= factor
+    if data == "heavy":                              # no variance at all
+        q /= torch.randn(n, heads, 128, generator=g, device="cuda").abs() + 1.0 / factor
+    for got, x in _moment(q, kv):
+        want = x.t() @ x / x.shape[0]
+        # Half an ulp of float32, and what the digits leave out: 0.2 a row, of either sign, where the rows' |V_i V_j| are 2^27
+        # or more on average: 1.5e-9 / sqrt(rows) of their sum, five times that from 2048 rows on.
+        assert ((got - want).abs() <= 6e-8 * want.abs() + 2e-10 * (x.abs().t() @ x.abs()) / x.shape[0]).all()
+        assert torch.equal(got, got.t())
+
+
+@pytest.mark.parametrize("n", [3000, 9000])   # float64 products, digits
+def test_second_moment_of_values_that_are_not_finite(n):
+    q = torch.randn(n, 4, 128, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    q[n - 1, 0, 3] = float("nan")     # head 0: the last row
     q[0, 1, 5] = float("inf")         # head 1: the first
-    q[1500, 1, 9] = float("-inf")
-    q[1500, 2, 77] = float("inf")     # head 2: in the middle; head 3: none
+    q[n // 2, 1, 9] = float("-inf")
+    q[n // 2, 2, 77] = float("inf")   # head 2: in the middle; head 3: none
     for got, x in _moment(q, 4):
         want = x.t() @ x / x.shape[0]
         assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got.isinf(), want.isinf())

@@ -137,10 +137,14 @@ __device__ __forceinline__ void count_codes_body(int block, const CodeCount& cc,
 // What bounds it: latency.  4 sequences of 131072 tokens, 8 KV heads, one key each, tables, keys and counts: 16.8 us (a launch
 // for the keys 11.5 and one for the tables 11.0 before, the counting in the selection), of which u takes 3.3, a sweep 4.6
 // (64 products of a wave, two waves a SIMD; a thread's dimensions on the vector ALU, eight lanes a codeword, took 10), the
-// first loads 2.5 to 3.8.  Tables alone: 32 sequences of 32 heads 52 -> 28 us, one sequence of 4 heads 8.3 -> 8.9.
+// first loads 2.5 to 3.8.  Tables alone: 32 sequences of 32 heads 52 -> 28 us.  Up to four vectors of a KV head: products of four
+// rows, and without keys and counts a wave takes one tile, twice as many workgroups: 4 heads 8.1 -> 5.1 us (eight lanes a
+// codeword: 6.4), 8 KV heads of 4 8.6 -> 5.6, and with one key each, tables and key, 15.6 -> 13.0.
 constexpr int kTabThreads = 512, kTabTiles = kLutChunk / (16 * kTabThreads / 64);
 static_assert(kTabTiles == 2, "a wave's codewords");
 typedef __attribute__((ext_vector_type(4))) double f64x4;
+
+constexpr int kFewVectors = 4;   // of a KV head: see add_product
 
 struct TabLds {
   union {
@@ -156,30 +160,39 @@ struct TabLds {
 // the banks.
 __device__ __forceinline__ int tab_slot(int d, int row) { return ((d ^ ((d >> 2) & 1)) << 4) | row; }
 
-// acc[t]: rows 4 r + k (register r), column lane & 15 of tile t.  CENTRED: the codewords less L.mu.
-template <bool CENTRED>
-__device__ __forceinline__ void tab_product(const float* __restrict__ cw, const TabLds& L, f64x4 (&acc)[kTabTiles]) {
+// Adds a step of the product to acc: rows 4 r + k (register r), column lane & 15; a: of row lane & 15.  FEW: there are no rows
+// but the first four (four products of 4 x 4 x 4, of the same rows; a is of row lane & 3).  Their sums are the same bit for bit:
+// either form adds the dimensions one after the other, without rounding the products.
+template <bool FEW>
+__device__ __forceinline__ void add_product(double a, double b, f64x4& acc) {
+  if (FEW) acc[0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, acc[0], 0, 0, 0);
+  else acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+}
+
+// acc[t]: as above, of tile t.  CENTRED: the codewords less L.mu.
+template <bool CENTRED, bool FEW, int TILES>
+__device__ __forceinline__ void tab_product(const float* __restrict__ cw, const TabLds& L, f64x4 (&acc)[TILES]) {
   const int lane = threadIdx.x & 63, j = lane & 15, k = lane >> 4, wave = threadIdx.x >> 6;
-  float4 c[kTabTiles][8];
+  float4 c[TILES][8];
 #pragma unroll
-  for (int t = 0; t < kTabTiles; ++t)
+  for (int t = 0; t < TILES; ++t)
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      c[t][i] = *(const float4*)(cw + (size_t)((wave * kTabTiles + t) * 16 + j) * kSD + 16 * i + 4 * k);
+      c[t][i] = *(const float4*)(cw + (size_t)((wave * TILES + t) * 16 + j) * kSD + 16 * i + 4 * k);
 #pragma unroll
-  for (int t = 0; t < kTabTiles; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+  for (int t = 0; t < TILES; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
   for (int i = 0; i < 8; ++i)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int d = 16 * i + 4 * k + e;
-      const double a = L.v[tab_slot(d, j)];
+      const double a = L.v[tab_slot(d, FEW ? j & 3 : j)];
 #pragma unroll
-      for (int t = 0; t < kTabTiles; ++t) {
+      for (int t = 0; t < TILES; ++t) {
         const float4 f = c[t][i];
         double x = (double)(e == 0 ? f.x : (e == 1 ? f.y : (e == 2 ? f.z : f.w)));
         if (CENTRED) x -= L.mu[d];
-        acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, x, acc[t], 0, 0, 0);
+        add_product<FEW>(a, x, acc[t]);
       }
     }
 }
@@ -223,14 +236,16 @@ __device__ __forceinline__ uint16_t pick_code(const double* __restrict__ part, s
   return (uint16_t)arg;
 }
 
-template <bool QBF16>
+// TILES 1: no more than kFewVectors tables of a KV head, and neither keys nor counts.
+template <bool QBF16, int TILES>
 __global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void build_lut_single_kernel(
     const void* __restrict__ q_in, const float* __restrict__ cos_b, const float* __restrict__ sin_b,
     const float* __restrict__ codebook, float* __restrict__ q_rot, int32_t* __restrict__ lut,
     float* __restrict__ lut_scale, int B, int Hq, int Hkv, int shared, TabPlan tp, FewKeys few, CodeCount cc,
     const uint16_t* __restrict__ codes, const int32_t* __restrict__ seq_lens, int ctx_len, int64_t ctx_stride, int top_k,
     int window, int n_sink) {
-  constexpr int HALF = kSD / 2, NT = kTabThreads;
+  constexpr int HALF = kSD / 2, NT = kTabThreads, CHUNK = 16 * (NT / 64) * TILES, CHUNKS = kCodewords / CHUNK;
+  static_assert(TILES == 1 || CHUNKS == kEncodeSlices, "the slices of the keys, and those of the ranges");
   __shared__ __align__(16) TabLds L;
   const int tid = threadIdx.x, lane = tid & 63, j = lane & 15, k = lane >> 4, wave = tid >> 6;
   int block = blockIdx.x;
@@ -248,11 +263,11 @@ __global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(4, 
   }
   const bool is_key = block < tp.n_key;
   if (!is_key) block -= tp.n_key;
-  const int chunk = block % kEncodeSlices, unit = block / kEncodeSlices;
+  const int chunk = block % CHUNKS, unit = block / CHUNKS;
   const FastDiv& groups = is_key ? tp.key_groups : tp.table_groups;
   const int kv = (int)fast_div((uint32_t)unit, groups), v0 = (unit - kv * (int)groups.d) * 16;   // first vector of the group
-  const float* cw = codebook + ((size_t)kv * kCodewords + chunk * kLutChunk) * kSD;
-  f64x4 acc[kTabTiles];
+  const float* cw = codebook + ((size_t)kv * kCodewords + chunk * CHUNK) * kSD;
+  f64x4 acc[TILES];
 
   if (!is_key) {
     const int G = Hq / Hkv, per = tp.per_seq, n_vec = B * per;
@@ -289,24 +304,25 @@ __global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(4, 
     }
     __syncthreads();
     if (cc.ranges && tid < 32) L.range[tid >> 4][tid & 15] = 0u;
-    tab_product<false>(cw, L, acc);
+    if (TILES == 1 || n_vec <= kFewVectors) tab_product<false, true>(cw, L, acc);
+    else tab_product<false, false>(cw, L, acc);
     if (cc.ranges) __syncthreads();
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int vec = v0 + 4 * r + k;
-      uint32_t key[kTabTiles];
+      uint32_t key[TILES];
 #pragma unroll
-      for (int t = 0; t < kTabTiles; ++t) key[t] = (uint32_t)float_to_key((float)acc[t][r]);
+      for (int t = 0; t < TILES; ++t) key[t] = (uint32_t)float_to_key((float)acc[t][r]);
       if (vec < n_vec) {   // (uniform over 16 lanes)
         const int b = (int)fast_div((uint32_t)vec, tp.per_seq_div), g = vec - b * per;
-        int32_t* out = lut + (((size_t)b * Hkv + kv) * per + g) * kCodewords + chunk * kLutChunk + wave * kTabTiles * 16 + j;
+        int32_t* out = lut + (((size_t)b * Hkv + kv) * per + g) * kCodewords + chunk * CHUNK + wave * TILES * 16 + j;
 #pragma unroll
-        for (int t = 0; t < kTabTiles; ++t) out[16 * t] = (int32_t)key[t];
+        for (int t = 0; t < TILES; ++t) out[16 * t] = (int32_t)key[t];
       }
       if (cc.ranges) {
         uint32_t least = 0, most = 0;
 #pragma unroll
-        for (int t = 0; t < kTabTiles; ++t) {
+        for (int t = 0; t < TILES; ++t) {
           least = max(least, ~score_key((int32_t)key[t]));
           most = max(most, score_key((int32_t)key[t]));
         }
@@ -330,6 +346,7 @@ __global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(4, 
   }
 
   // --- appended keys
+  if (TILES == 1) return;
   const int n_vec = B * few.n_new;
   const float* mu = few.mu + (size_t)kv * few.mu_stride;
   auto key_index = [&](int vec) {   // among all keys
@@ -355,24 +372,29 @@ __global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(4, 
   if (tid < kSD) L.mu[tid] = (double)mu[tid];
   if (tid < 16) {
     L.best[tid] = ~0ull;
-    L.arg[tid] = kLutChunk;
+    L.arg[tid] = CHUNK;
   }
-  const double* ch = few.chalf + (size_t)kv * kCodewords + chunk * kLutChunk + wave * kTabTiles * 16 + j;
-  double chalf[kTabTiles];
+  const double* ch = few.chalf + (size_t)kv * kCodewords + chunk * CHUNK + wave * TILES * 16 + j;
+  double chalf[TILES];
 #pragma unroll
-  for (int t = 0; t < kTabTiles; ++t) chalf[t] = ch[16 * t];
+  for (int t = 0; t < TILES; ++t) chalf[t] = ch[16 * t];
   __syncthreads();
   if (full_matrix) {   // u: a wave takes 16 of its dimensions
     f64x4 u = {0.0, 0.0, 0.0, 0.0};
+    if (n_vec <= kFewVectors) {
 #pragma unroll
-    for (int i = 0; i < 32; ++i)
-      u = __builtin_amdgcn_mfma_f64_16x16x4f64(L.v[tab_slot(16 * (i / 4) + 4 * k + i % 4, j)], hv[i], u, 0, 0, 0);
+      for (int i = 0; i < 32; ++i) add_product<true>(L.v[tab_slot(16 * (i / 4) + 4 * k + i % 4, j & 3)], hv[i], u);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 32; ++i) add_product<false>(L.v[tab_slot(16 * (i / 4) + 4 * k + i % 4, j)], hv[i], u);
+    }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < 4; ++r) L.v[tab_slot(16 * wave + j, 4 * r + k)] = u[r];
     __syncthreads();
   }
-  tab_product<true>(cw, L, acc);
+  if (n_vec <= kFewVectors) tab_product<true, true>(cw, L, acc);
+  else tab_product<true, false>(cw, L, acc);
   // the smallest of a key's values, the lower code on equal ones (a value that is not a number is never smaller)
   double best[4];
   int arg[4];
@@ -381,11 +403,11 @@ __global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(4, 
     best[r] = INFINITY;
     arg[r] = 0;
 #pragma unroll
-    for (int t = 0; t < kTabTiles; ++t) {
+    for (int t = 0; t < TILES; ++t) {
       const double s = chalf[t] - acc[t][r];
       if (s < best[r]) {
         best[r] = s;
-        arg[r] = (wave * kTabTiles + t) * 16 + j;
+        arg[r] = (wave * TILES + t) * 16 + j;
       }
     }
   }
@@ -404,7 +426,7 @@ __global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(4, 
     double* out = few.part + (key_index(v0 + tid) * kEncodeSlices + chunk) * 2;
     const uint64_t o = L.best[tid];
     out[0] = __builtin_bit_cast(double, o ^ (o >> 63 ? 0x8000000000000000ull : ~0ull));
-    out[1] = (double)(chunk * kLutChunk + L.arg[tid]);
+    out[1] = (double)(chunk * CHUNK + L.arg[tid]);
   }
 }
 
@@ -426,17 +448,20 @@ static hipError_t launch_tables_single(const a2ats_dims& d, const void* q, int q
   tp.key_groups = make_fastdiv((uint32_t)key_groups);
   tp.table_groups = make_fastdiv((uint32_t)table_groups);
   tp.n_key = key_groups * d.n_kv_heads * kEncodeSlices;
-  tp.n_table = table_groups * d.n_kv_heads * kEncodeSlices;
+  const bool small = n_new == 0 && !cc.counts && d.batch * tp.per_seq <= kFewVectors;
+  tp.n_table = table_groups * d.n_kv_heads * kEncodeSlices * (small ? kTabTiles : 1);
   const dim3 grid(tp.n_key + tp.n_table + n_count), block(kTabThreads);
   if (grid.x == 0) return hipSuccess;
-  if (q_dtype == A2ATS_BF16)
-    hipLaunchKernelGGL((build_lut_single_kernel<true>), grid, block, 0, stream, q, cos_b, sin_b, codebook, q_rot, lut,
-                       lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, shared ? 1 : 0, tp, few, cc, (const uint16_t*)codes,
-                       seq_lens, d.ctx_len, d.ctx_stride, top_k, window, n_sink);
-  else
-    hipLaunchKernelGGL((build_lut_single_kernel<false>), grid, block, 0, stream, q, cos_b, sin_b, codebook, q_rot, lut,
-                       lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, shared ? 1 : 0, tp, few, cc, (const uint16_t*)codes,
-                       seq_lens, d.ctx_len, d.ctx_stride, top_k, window, n_sink);
+#define A2ATS_LAUNCH_TABLES(BF, TILES)                                                                                    \
+  hipLaunchKernelGGL((build_lut_single_kernel<BF, TILES>), grid, block, 0, stream, q, cos_b, sin_b, codebook, q_rot, lut, \
+                     lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, shared ? 1 : 0, tp, few, cc, (const uint16_t*)codes,   \
+                     seq_lens, d.ctx_len, d.ctx_stride, top_k, window, n_sink)
+  if (q_dtype == A2ATS_BF16) {
+    if (small) A2ATS_LAUNCH_TABLES(true, 1); else A2ATS_LAUNCH_TABLES(true, kTabTiles);
+  } else {
+    if (small) A2ATS_LAUNCH_TABLES(false, 1); else A2ATS_LAUNCH_TABLES(false, kTabTiles);
+  }
+#undef A2ATS_LAUNCH_TABLES
   return hipGetLastError();
 }
 

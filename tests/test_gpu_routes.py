@@ -333,6 +333,41 @@ def test_single_codebook_decode_select_equals_the_two_calls(Bn, G, Hkv, N, K, w,
     assert (res[1][4][-8:] == -7).all() and (res[1][0][:, :, N:] == 0).all()
 
 
+@pytest.mark.parametrize("Bn,G,Hkv", [(5, 1, 2), (4, 2, 1), (3, 4, 3), (2, 7, 1), (17, 1, 1), (1, 8, 1)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("shared", [False, True])
+def test_single_codebook_tables_of_few_heads_equal_those_of_many(Bn, G, Hkv, dtype, shared):
+    """One to four vectors of a KV head take smaller products in more workgroups: the same tables bit for bit, and those
+    of float64 sums rounded once."""
+    g = torch.Generator(device="cuda").manual_seed(Bn * 8 + G)
+    codebook = torch.randn(Hkv, 1, 4096, 128, generator=g, device="cuda")
+    q = torch.randn(Bn, Hkv * G, 128, generator=g, device="cuda").to(dtype)
+    cos, sin, _, _ = B.rope_tables(128, torch.tensor([1e4 ** (-i / 64) for i in range(64)], dtype=torch.float64), 33, 4, "cuda")
+    heads = Hkv if shared else Hkv * G
+
+    def tables(q):
+        n = q.shape[0]
+        dims = B.make_dims(n, Hkv * G, Hkv, 128, 1, 64, n_centroids=4096)
+        lut = torch.full((n * heads * 4096 + 64,), -7, dtype=torch.int32, device="cuda")
+        q_rot, scale = torch.empty(n, Hkv * G, 128, device="cuda"), torch.zeros(n, heads, device="cuda")
+        (B.build_lut_shared if shared else B.build_lut)(dims, q.contiguous(), cos, sin, codebook, q_rot, lut, scale)
+        torch.cuda.synchronize()
+        assert (lut[n * heads * 4096:] == -7).all() and (scale == 1).all()
+        return lut[:n * heads * 4096].reshape(n, heads, 4096), q_rot
+
+    lut, q_rot = tables(q)
+    for b in range(Bn):
+        one = tables(q[b:b + 1])
+        assert torch.equal(one[0][0], lut[b]) and torch.equal(one[1][0], q_rot[b])
+    v = q_rot.double().reshape(Bn, Hkv, G, 128)
+    if shared:
+        v = v.sum(2, keepdim=True).float().double()
+    want = torch.matmul(v, codebook.double().reshape(1, Hkv, 4096, 128).transpose(2, 3).contiguous()).reshape(Bn, heads, 4096)
+    got = torch.where(lut < 0, lut ^ 0x7FFFFFFF, lut).view(torch.float32).double()
+    # half an ulp of float32; float64 sums of 128 products in two orders, of magnitudes that add up to some 80
+    assert ((got - want).abs() <= 6e-8 * want.abs() + 1e-12).all()
+
+
 @pytest.mark.parametrize("Bn,G,Hkv,M,N,K,w,n_sink,n_new,lens,data", [
     (1, 1, 1, 16, 40, 7, 32, 4, 1, None, None),                       # four candidates
     (2, 3, 2, 32, 1024 + 64, 300, 64, 0, 1, None, None),              # one row a thread, exactly; a group of three

@@ -182,8 +182,8 @@ int a2ats_build_lut(const a2ats_dims* dims, const void* q, int q_dtype, const fl
  * at positions pos0 .. pos0 + n_new - 1.  Arguments, layouts and results are exactly those of the
  * two calls; n_new > 32 returns A2ATS_ERR_UNSUPPORTED, n_new == 0 builds the tables only (keys /
  * codes may then be NULL).  Product quantisation needs no workspace (ws may be NULL).
- * Single codebook: at most 8 keys per sequence and KV head; two launches (a float64 sweep of the codewords
- * for the keys and the table build, one with the other or one after the other); `ws` as for
+ * Single codebook: at most 8 keys per sequence and KV head; two launches (the float64 sweep of the codewords
+ * for the keys with the table build, and one that picks the keys' codes); `ws` as for
  * a2ats_encode_keys, and weight_mode may carry A2ATS_W_PREPARED in the same way.
  */
 int a2ats_decode_prologue(const a2ats_dims* dims, const float* keys, int32_t n_new, int32_t pos0,

@@ -236,8 +236,7 @@ int a2ats_build_lut(const a2ats_dims* d, const void* q, int q_dtype, const float
   const hipError_t e =
       a2ats::single_codebook(*d)
           ? a2ats::launch_build_lut_single(*d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale, false,
-                                           a2ats::FewKeys{}, a2ats::FewKeyPick{},
-                                           (hipStream_t)stream)
+                                           a2ats::FewKeys{}, (hipStream_t)stream)
           : a2ats::launch_build_lut(*d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale,
                                     (hipStream_t)stream);
   return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
@@ -254,8 +253,7 @@ int a2ats_build_lut_shared(const a2ats_dims* d, const void* q, int q_dtype, cons
   const hipError_t e =
       a2ats::single_codebook(*d)
           ? a2ats::launch_build_lut_single(*d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale, true,
-                                           a2ats::FewKeys{}, a2ats::FewKeyPick{},
-                                           (hipStream_t)stream)
+                                           a2ats::FewKeys{}, (hipStream_t)stream)
           : a2ats::launch_build_lut_shared(*d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale,
                                            (hipStream_t)stream);
   return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
@@ -288,7 +286,7 @@ int a2ats_decode_prologue(const a2ats_dims* d, const float* keys, int32_t n_new,
             ? a2ats::launch_decode_prologue_single(*d, keys, n_new, pos0, codebook, weights, weight_mode, prepared, codes, q,
                                                    q_dtype, cos_b, sin_b, q_rot, lut, lut_scale, ws, (hipStream_t)stream)
             : a2ats::launch_build_lut_single(*d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale, false,
-                                             a2ats::FewKeys{}, a2ats::FewKeyPick{}, (hipStream_t)stream);
+                                             a2ats::FewKeys{}, (hipStream_t)stream);
     return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
   }
   const hipError_t e = a2ats::launch_decode_prologue(*d, keys, n_new, pos0, codebook, weights, weight_mode,

@@ -1055,11 +1055,11 @@ __global__ void encode_single_clear_kernel(uint32_t* counter, int n) {
 // distortion of codeword c is |z|^2 - 2 k . w_c + |c^z|^2, so the sweep minimises
 // 1/2 |c^z|^2 - k . w_c and needs neither z nor L: one pass of dot products over wT.
 // part[key][slice] = {smallest value of the slice, its code as a double}.
-// 512 threads and at most 128 registers each, so that the two workgroups per CU of the usual
-// decode batch (32 keys x 16 slices on 256 CUs) are resident together.
+// Each half of the dimensions is added one after the other without rounding the products, as the float64 matrix cores add them
+// (build_lut_single_kernel): the codes do not depend on which of the two a call takes, whatever the rounding.
 constexpr int kSweepThreads = 512;
 __global__ __launch_bounds__(kSweepThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void encode_single_sweep_kernel(
-    const float* __restrict__ keys, const Center* __restrict__ center, const double* __restrict__ wT,
+    const float* __restrict__ keys, const float* __restrict__ mu, int mu_stride, const double* __restrict__ wT,
     const double* __restrict__ chalf, double* __restrict__ part, int Hkv, int n_new) {
   constexpr int PER = kCW / kSlices;   // codewords per slice
   static_assert(PER == 256 && kSweepThreads == 2 * PER, "a thread owns one codeword and half of the dimensions");
@@ -1076,27 +1076,25 @@ __global__ __launch_bounds__(kSweepThreads) __attribute__((amdgpu_waves_per_eu(4
 #pragma unroll
   for (int t = 0; t < 32; ++t) wv[t] = w[(size_t)t * kCW];
   const double half = chalf[(size_t)kv * kCW + c];
-  if (tid < kD) s_k[tid] = (double)keys[(size_t)key * kD + tid] - (double)center[kv].mu[tid];
+  if (tid < kD) s_k[tid] = (double)keys[(size_t)key * kD + tid] - (double)mu[(size_t)kv * mu_stride + tid];
   __builtin_amdgcn_sched_barrier(0);
   __syncthreads();
-  double d0 = 0.0, d1 = 0.0;
+  double dot = 0.0;
 #pragma unroll
   for (int t = 0; t < 32; t += 2) {
-    d0 += s_k[64 * th + t] * wv[t];
-    d1 += s_k[64 * th + t + 1] * wv[t + 1];
+    dot = __builtin_fma(s_k[64 * th + t], wv[t], dot);
+    dot = __builtin_fma(s_k[64 * th + t + 1], wv[t + 1], dot);
     wv[t] = w[(size_t)(32 + t) * kCW];
     wv[t + 1] = w[(size_t)(32 + t + 1) * kCW];
     __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
-  for (int t = 0; t < 32; t += 2) {
-    d0 += s_k[64 * th + 32 + t] * wv[t];
-    d1 += s_k[64 * th + 32 + t + 1] * wv[t + 1];
-  }
-  s_p[th][cl] = d0 + d1;
+  for (int t = 0; t < 32; ++t) dot = __builtin_fma(s_k[64 * th + 32 + t], wv[t], dot);
+  s_p[th][cl] = dot;
   __syncthreads();
-  if (tid < PER) {
-    s_p[0][tid] = half - (s_p[0][tid] + s_p[1][tid]);
+  if (tid < PER) {   // (a value that is not a number is never the smallest, as there)
+    const double value = half - (s_p[0][tid] + s_p[1][tid]);
+    s_p[0][tid] = value < INFINITY ? value : INFINITY;
     s_i[tid] = c;
   }
   __syncthreads();
@@ -1337,23 +1335,19 @@ hipError_t launch_encode_single_few(const a2ats_dims& d, const float* keys, int 
   few->keys = keys;
   few->mu = ((const Center*)(base + w.off_center))->mu;
   few->mu_stride = sizeof(Center) / sizeof(float);
-  few->heff = (const double*)(base + w.off_heff);
-  few->sd = (const double*)(base + w.off_sd);
+  few->wT = (const double*)(base + w.off_wT);
   few->chalf = (const double*)(base + w.off_chalf);
   few->part = (double*)(base + w.off_part);
-  few->mode = mode;
   few->n_new = n_new;
   *scratch = base + w.off_list;
   return prepared ? hipSuccess : launch_encode_single_prepare(d, codebook, weights, mode, ws, stream);
 }
 
 // The sweep of a key at a time, whose results are in few.part.
-static hipError_t launch_sweep_by_key(const a2ats_dims& d, const FewKeys& few, const void* ws, hipStream_t stream) {
-  const EncWs w = enc_single_ws(d);
-  const uint8_t* base = (const uint8_t*)ws;
+static hipError_t launch_sweep_by_key(const a2ats_dims& d, const FewKeys& few, hipStream_t stream) {
   hipLaunchKernelGGL(encode_single_sweep_kernel, dim3((unsigned)((size_t)d.batch * d.n_kv_heads * few.n_new), kSlices),
-                     dim3(kSweepThreads), 0, stream, few.keys, (const Center*)(base + w.off_center),
-                     (const double*)(base + w.off_wT), (const double*)(base + w.off_chalf), few.part, d.n_kv_heads, few.n_new);
+                     dim3(kSweepThreads), 0, stream, few.keys, few.mu, few.mu_stride, few.wT, few.chalf, few.part, d.n_kv_heads,
+                     few.n_new);
   return hipGetLastError();
 }
 
@@ -1364,8 +1358,7 @@ static hipError_t launch_pick(const a2ats_dims& d, const FewKeys& few, void* cod
   return hipGetLastError();
 }
 
-// The keys swept with the tables and picked by a launch of their own, or swept one by one before the tables, whose
-// launch picks: one key of 8 KV heads 15.4 us the second way, 16.5 the first; of 4 sequences 21.7 and 17.2.
+// The keys are swept with the tables, and picked by a launch of their own.
 hipError_t launch_decode_prologue_single(const a2ats_dims& d, const float* keys, int n_new, int pos0, const float* codebook,
                                          const float* weights, int mode, bool prepared, void* codes, const void* q,
                                          int q_dtype, const float* cos_b, const float* sin_b, float* q_rot, int32_t* lut,
@@ -1374,13 +1367,7 @@ hipError_t launch_decode_prologue_single(const a2ats_dims& d, const float* keys,
   void* scratch;
   hipError_t err = launch_encode_single_few(d, keys, n_new, codebook, weights, mode, prepared, ws, &few, &scratch, stream);
   if (err != hipSuccess) return err;
-  if ((long)d.batch * d.n_kv_heads * n_new <= 8) {
-    if ((err = launch_sweep_by_key(d, few, ws, stream)) != hipSuccess) return err;
-    return launch_build_lut_single(d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale, false, FewKeys{},
-                                   FewKeyPick{few.part, (uint16_t*)codes, n_new, pos0}, stream);
-  }
-  err = launch_build_lut_single(d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale, false, few, FewKeyPick{},
-                                stream);
+  err = launch_build_lut_single(d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale, false, few, stream);
   return err == hipSuccess ? launch_pick(d, few, codes, pos0, stream) : err;
 }
 
@@ -1393,11 +1380,11 @@ hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_ne
     void* scratch;
     hipError_t err = launch_encode_single_few(d, keys, n_new, codebook, weights, mode, prepared, ws, &few, &scratch, stream);
     if (err != hipSuccess) return err;
-    // The sweep of prepared rows takes a key at a time, the other one 16 at a time, with a product more ahead: one key of 8 KV
-    // heads 10.9 us against 16.1, of 4 sequences 12.8 against 16.7, but 8 keys of these 70 against 19.5.  The line is where
-    // the first has more workgroups than two a CU.
-    err = (long)d.batch * d.n_kv_heads * n_new * kSlices <= 512 ? launch_sweep_by_key(d, few, ws, stream)
-                                                                : launch_sweep_single(d, codebook, few, stream);
+    // One sweep takes a key at a time, the other one 16 of a KV head on the matrix cores: one key of 8 KV heads 8.7 us against
+    // 10.6, of 2 sequences 8.8 against 11.1, of 3 12.4 against 10.6, 8 keys of 4 sequences 70 against 13.1.  The line is where
+    // the first has more workgroups than there are CUs.
+    err = (long)d.batch * d.n_kv_heads * n_new * kSlices <= 256 ? launch_sweep_by_key(d, few, stream)
+                                                                : launch_sweep_single(d, few, stream);
     return err == hipSuccess ? launch_pick(d, few, codes, pos0, stream) : err;
   }
   const EncWs w = enc_single_ws(d);

@@ -121,35 +121,27 @@ constexpr int kFewSingleKeys = 8;   // at most this many keys per (sequence, KV 
 struct FewKeys {
   const float* keys;    // [B * Hkv][n_new][128]; nullptr: none
   const float* mu;      // centre of the codewords of a KV head
-  const double* heff;   // L L^T
-  const double* sd;     // (without a matrix) square roots of the weights
+  const double* wT;     // (c - mu) H by dimension, then codeword
   const double* chalf;  // 1/2 |c^z|^2
   double* part;
   int mu_stride;        // floats from a KV head's centre to the next
-  int mode, n_new;
+  int n_new;
 };
 // Prepares the codewords if they are not, and says where FewKeys' inputs are; *scratch: memory behind the prepared part.
 hipError_t launch_encode_single_few(const a2ats_dims& d, const float* keys, int n_new, const float* codebook,
                                     const float* weights, int mode, bool prepared, void* ws, FewKeys* few, void** scratch,
                                     hipStream_t stream);
 size_t encode_single_scratch_bytes(const a2ats_dims& d);   // of *scratch
-// The second step as part of the table build, after a launch that has swept the keys.
-struct FewKeyPick {
-  const double* part;   // nullptr: nothing to pick
-  uint16_t* codes;
-  int n_new, pos0;
-};
 hipError_t launch_build_lut_single(const a2ats_dims& d, const void* q, int q_dtype, const float* cos_b,
                                    const float* sin_b, const float* codebook, float* q_rot, int32_t* lut,
-                                   float* lut_scale, bool shared, const FewKeys& few, const FewKeyPick& pick,
-                                   hipStream_t stream);
+                                   float* lut_scale, bool shared, const FewKeys& few, hipStream_t stream);
 // a2ats_decode_prologue of n_new >= 1 keys.
 hipError_t launch_decode_prologue_single(const a2ats_dims& d, const float* keys, int n_new, int pos0, const float* codebook,
                                          const float* weights, int mode, bool prepared, void* codes, const void* q,
                                          int q_dtype, const float* cos_b, const float* sin_b, float* q_rot, int32_t* lut,
                                          float* lut_scale, void* ws, hipStream_t stream);
 // The sweep alone.
-hipError_t launch_sweep_single(const a2ats_dims& d, const float* codebook, const FewKeys& few, hipStream_t stream);
+hipError_t launch_sweep_single(const a2ats_dims& d, const FewKeys& few, hipStream_t stream);
 // Tables, appended keys and selection in two launches; no appended row may be a candidate.  scratch holds the counts of
 // the sequences' chunks.
 bool select_chunks_single_fits(const a2ats_dims& d, int window, int n_sink, size_t scratch_bytes);

@@ -129,17 +129,19 @@ __device__ __forceinline__ void count_codes_body(int block, const CodeCount& cc,
 //
 // Tables: the vectors are rotated queries, of any sequences (they have the codebook in common); `shared`: one table per KV
 // head, from the float32 sum of its heads' rotated queries (the table array is then laid out for Hq = Hkv).
-// Appended keys: up to a constant of the key, the distortion of codeword c is 1/2 |c^z|^2 - (k - mu) H (c - mu)^T, so a key is
-// the vector u = (k - mu) H, a product by itself (128 KB of H for 16 keys).  part[key][chunk] = {smallest value, its code}.
+// Appended keys: up to a constant of the key, the distortion of codeword c is 1/2 |c^z|^2 - (k - mu) . w_c, so a key is the vector
+// k - mu and the columns are the prepared w_c = (c - mu) H; each half of the dimensions one after the other, as
+// encode_single_sweep_kernel has them, so that either finds the same code.  part[key][chunk] = {smallest value, its code}.
 // Counts: candidates per codeword of the chunks of the sequences.
 // The three kinds of workgroup have nothing to do with each other.
 //
-// What bounds it: latency.  4 sequences of 131072 tokens, 8 KV heads, one key each, tables, keys and counts: 16.8 us (a launch
-// for the keys 11.5 and one for the tables 11.0 before, the counting in the selection), of which u takes 3.3, a sweep 4.6
+// What bounds it: latency.  4 sequences of 131072 tokens, 8 KV heads, one key each, tables, keys and counts: 16 us (a launch
+// for the keys 11.5 and one for the tables 11.0 before, the counting in the selection), of which a sweep of 16 vectors takes 4.6
 // (64 products of a wave, two waves a SIMD; a thread's dimensions on the vector ALU, eight lanes a codeword, took 10), the
 // first loads 2.5 to 3.8.  Tables alone: 32 sequences of 32 heads 52 -> 28 us.  Up to four vectors of a KV head: products of four
 // rows, and without keys and counts a wave takes one tile, twice as many workgroups: 4 heads 8.1 -> 5.1 us (eight lanes a
-// codeword: 6.4), 8 KV heads of 4 8.6 -> 5.6, and with one key each, tables and key, 15.6 -> 13.0.
+// codeword: 6.4), 8 KV heads of 4 8.6 -> 5.6.  Keys from the prepared columns instead of (k - mu) H, a product more, and the
+// codewords: 8 keys of 4 sequences, a launch to pick them included, 18.2 -> 13.1 us.
 constexpr int kTabThreads = 512, kTabTiles = kLutChunk / (16 * kTabThreads / 64);
 static_assert(kTabTiles == 2, "a wave's codewords");
 typedef __attribute__((ext_vector_type(4))) double f64x4;
@@ -151,7 +153,6 @@ struct TabLds {
     double v[kSD * 16];               // [dimension][vector], see tab_slot
     uint32_t count[kCodewords];
   };
-  double mu[kSD];
   uint32_t range[2][16];            // of the vectors
   uint64_t best[16];                // of the keys: the smallest value, and the lowest code that has it
   int32_t arg[16];
@@ -169,8 +170,8 @@ __device__ __forceinline__ void add_product(double a, double b, f64x4& acc) {
   else acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
 }
 
-// acc[t]: as above, of tile t.  CENTRED: the codewords less L.mu.
-template <bool CENTRED, bool FEW, int TILES>
+// acc[t]: as above, of tile t.
+template <bool FEW, int TILES>
 __device__ __forceinline__ void tab_product(const float* __restrict__ cw, const TabLds& L, f64x4 (&acc)[TILES]) {
   const int lane = threadIdx.x & 63, j = lane & 15, k = lane >> 4, wave = threadIdx.x >> 6;
   float4 c[TILES][8];
@@ -190,11 +191,39 @@ __device__ __forceinline__ void tab_product(const float* __restrict__ cw, const 
 #pragma unroll
       for (int t = 0; t < TILES; ++t) {
         const float4 f = c[t][i];
-        double x = (double)(e == 0 ? f.x : (e == 1 ? f.y : (e == 2 ? f.z : f.w)));
-        if (CENTRED) x -= L.mu[d];
-        add_product<FEW>(a, x, acc[t]);
+        add_product<FEW>(a, (double)(e == 0 ? f.x : (e == 1 ? f.y : (e == 2 ? f.z : f.w))), acc[t]);
       }
     }
+}
+
+// The same with the prepared columns of a KV head, the first half of which is in wv; each is replaced by its successor as it is
+// used.  `at`: bytes to this lane's column and quarter of a step's dimensions.  (By descriptor: the steps are 128 KB apart, and
+// an address in registers for each would not fit.)
+constexpr int kKeySteps = kSD / 4;
+__device__ __forceinline__ double load_column(__amdgpu_buffer_rsrc_t w, int at, int step, int tile) {
+  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(w, at + tile * 16 * (int)sizeof(double),
+                                                                         step * 4 * kCodewords * (int)sizeof(double), 0));
+}
+template <bool FEW, int TILES>
+__device__ __forceinline__ void key_product(__amdgpu_buffer_rsrc_t w, int at, double (&wv)[TILES][kKeySteps / 2], const TabLds& L,
+                                            f64x4 (&acc)[TILES]) {
+  const int lane = threadIdx.x & 63, j = lane & 15, k = lane >> 4;
+  f64x4 second[TILES];
+#pragma unroll
+  for (int t = 0; t < TILES; ++t) acc[t] = second[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int i = 0; i < kKeySteps; ++i) {
+    const double a = L.v[tab_slot(4 * i + k, FEW ? j & 3 : j)];
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) {
+      double& x = wv[t][i % (kKeySteps / 2)];
+      add_product<FEW>(a, x, i < kKeySteps / 2 ? acc[t] : second[t]);
+      if (i < kKeySteps / 2) x = load_column(w, at, i + kKeySteps / 2, t);
+    }
+    __builtin_amdgcn_sched_barrier(0);   // (else the second half is requested before the first has been used: registers)
+  }
+#pragma unroll
+  for (int t = 0; t < TILES; ++t) acc[t] += second[t];
 }
 
 // A number that is not a NaN as an unsigned integer of the same order (0 and -0 are one).
@@ -217,7 +246,6 @@ struct TabPlan {
   FastDiv key_groups, table_groups;   // of 16 vectors, of a KV head
   int per_seq;               // table heads of a sequence and KV head
   FastDiv per_seq_div, n_new_div;
-  FewKeyPick pick;
 };
 
 // The code of key `key` of all: the smallest of its slices (they hold ascending codes: strict < keeps the lower code on equal
@@ -236,8 +264,8 @@ __device__ __forceinline__ uint16_t pick_code(const double* __restrict__ part, s
   return (uint16_t)arg;
 }
 
-// TILES 1: no more than kFewVectors tables of a KV head, and neither keys nor counts.
-template <bool QBF16, int TILES>
+// TILES 1: no more than kFewVectors tables of a KV head, and neither keys nor counts.  FEW_KEYS: no more than that many keys.
+template <bool QBF16, int TILES, bool FEW_KEYS>
 __global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void build_lut_single_kernel(
     const void* __restrict__ q_in, const float* __restrict__ cos_b, const float* __restrict__ sin_b,
     const float* __restrict__ codebook, float* __restrict__ q_rot, int32_t* __restrict__ lut,
@@ -250,13 +278,6 @@ __global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(4, 
   const int tid = threadIdx.x, lane = tid & 63, j = lane & 15, k = lane >> 4, wave = tid >> 6;
   int block = blockIdx.x;
   if (block >= tp.n_key + tp.n_table) {
-    if (tp.pick.part) {   // (one workgroup, beside the tables: at the end of one of theirs it takes 1.5 us more)
-      for (int i = tid; i < B * Hkv * tp.pick.n_new; i += NT) {
-        const int bkv = i / tp.pick.n_new, t = i % tp.pick.n_new;
-        tp.pick.codes[(size_t)bkv * ctx_stride + tp.pick.pos0 + t] = pick_code(tp.pick.part, (size_t)i);
-      }
-      return;
-    }
     count_codes_body(block - tp.n_key - tp.n_table, cc, L.count, codes, seq_lens, Hkv, ctx_len, ctx_stride, top_k, window,
                      n_sink);
     return;
@@ -266,7 +287,6 @@ __global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(4, 
   const int chunk = block % CHUNKS, unit = block / CHUNKS;
   const FastDiv& groups = is_key ? tp.key_groups : tp.table_groups;
   const int kv = (int)fast_div((uint32_t)unit, groups), v0 = (unit - kv * (int)groups.d) * 16;   // first vector of the group
-  const float* cw = codebook + ((size_t)kv * kCodewords + chunk * CHUNK) * kSD;
   f64x4 acc[TILES];
 
   if (!is_key) {
@@ -303,9 +323,10 @@ __global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(4, 
       L.v[tab_slot(t + HALF, row)] = (double)(float)s2;
     }
     __syncthreads();
+    const float* cw = codebook + ((size_t)kv * kCodewords + chunk * CHUNK) * kSD;
     if (cc.ranges && tid < 32) L.range[tid >> 4][tid & 15] = 0u;
-    if (TILES == 1 || n_vec <= kFewVectors) tab_product<false, true>(cw, L, acc);
-    else tab_product<false, false>(cw, L, acc);
+    if (TILES == 1 || n_vec <= kFewVectors) tab_product<true>(cw, L, acc);
+    else tab_product<false>(cw, L, acc);
     if (cc.ranges) __syncthreads();
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -353,48 +374,36 @@ __global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(4, 
     const int b = (int)fast_div((uint32_t)vec, tp.n_new_div);
     return (size_t)(b * Hkv + kv) * few.n_new + (vec - b * few.n_new);
   };
-  const bool full_matrix = few.mode == A2ATS_W_BLOCK;
-  const double* h = few.heff + (size_t)kv * kSD * kSD + 16 * wave + j;
-  double hv[32];
-  if (full_matrix) {
+  constexpr int PER = 16 * kSD / NT;   // of the vectors' entries
+  float x[PER], m[PER];
 #pragma unroll
-    for (int i = 0; i < 32; ++i) hv[i] = h[(size_t)(16 * (i / 4) + 4 * k + i % 4) * kSD];
+  for (int i = 0; i < PER; ++i) {
+    const int row = (tid + i * NT) / kSD, d = tid % kSD, vec = min(v0 + row, n_vec - 1);
+    x[i] = few.keys[key_index(vec) * kSD + d];
+    m[i] = mu[d];
   }
-  for (int i = tid; i < 16 * kSD; i += NT) {
-    const int row = i / kSD, d = i % kSD, vec = v0 + row;
-    double x = vec < n_vec ? (double)few.keys[key_index(vec) * kSD + d] - (double)mu[d] : 0.0;
-    if (!full_matrix) {
-      const double sd = few.sd[(size_t)kv * kSD + d];
-      x = x * sd * sd;
-    }
-    L.v[tab_slot(d, row)] = x;
+  const int col = chunk * CHUNK + wave * TILES * 16 + j, at = (k * kCodewords + col) * (int)sizeof(double);
+  const auto w = __builtin_amdgcn_make_buffer_rsrc((void*)(few.wT + (size_t)kv * kSD * kCodewords), 0,
+                                                   kSD * kCodewords * (int)sizeof(double), 0x00027000);
+  double wv[TILES][kKeySteps / 2], chalf[TILES];
+#pragma unroll
+  for (int i = 0; i < kKeySteps / 2; ++i)
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) wv[t][i] = load_column(w, at, i, t);
+#pragma unroll
+  for (int t = 0; t < TILES; ++t) chalf[t] = few.chalf[(size_t)kv * kCodewords + col + 16 * t];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int row = (tid + i * NT) / kSD, d = tid % kSD;
+    L.v[tab_slot(d, row)] = v0 + row < n_vec ? (double)x[i] - (double)m[i] : 0.0;
   }
-  if (tid < kSD) L.mu[tid] = (double)mu[tid];
   if (tid < 16) {
     L.best[tid] = ~0ull;
     L.arg[tid] = CHUNK;
   }
-  const double* ch = few.chalf + (size_t)kv * kCodewords + chunk * CHUNK + wave * TILES * 16 + j;
-  double chalf[TILES];
-#pragma unroll
-  for (int t = 0; t < TILES; ++t) chalf[t] = ch[16 * t];
   __syncthreads();
-  if (full_matrix) {   // u: a wave takes 16 of its dimensions
-    f64x4 u = {0.0, 0.0, 0.0, 0.0};
-    if (n_vec <= kFewVectors) {
-#pragma unroll
-      for (int i = 0; i < 32; ++i) add_product<true>(L.v[tab_slot(16 * (i / 4) + 4 * k + i % 4, j & 3)], hv[i], u);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 32; ++i) add_product<false>(L.v[tab_slot(16 * (i / 4) + 4 * k + i % 4, j)], hv[i], u);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < 4; ++r) L.v[tab_slot(16 * wave + j, 4 * r + k)] = u[r];
-    __syncthreads();
-  }
-  if (n_vec <= kFewVectors) tab_product<true, true>(cw, L, acc);
-  else tab_product<true, false>(cw, L, acc);
+  key_product<FEW_KEYS>(w, at, wv, L, acc);
   // the smallest of a key's values, the lower code on equal ones (a value that is not a number is never smaller)
   double best[4];
   int arg[4];
@@ -433,14 +442,12 @@ __global__ __launch_bounds__(kTabThreads) __attribute__((amdgpu_waves_per_eu(4, 
 // Tables (q), appended keys (few.keys) and counts (n_count workgroups), any of them or all.
 static hipError_t launch_tables_single(const a2ats_dims& d, const void* q, int q_dtype, const float* cos_b,
                                        const float* sin_b, const float* codebook, float* q_rot, int32_t* lut,
-                                       float* lut_scale, bool shared, const FewKeys& few, const FewKeyPick& pick,
-                                       const CodeCount& cc, int n_count,
+                                       float* lut_scale, bool shared, const FewKeys& few, const CodeCount& cc, int n_count,
                                        const void* codes, const int32_t* seq_lens, int top_k, int window, int n_sink,
                                        hipStream_t stream) {
   if (d.batch == 0) return hipSuccess;
   TabPlan tp;
   const int n_new = few.keys ? few.n_new : 0;
-  tp.pick = pick;
   tp.per_seq = shared ? 1 : d.n_q_heads / d.n_kv_heads;
   tp.per_seq_div = make_fastdiv((uint32_t)tp.per_seq);
   tp.n_new_div = make_fastdiv((uint32_t)n_new);
@@ -452,30 +459,33 @@ static hipError_t launch_tables_single(const a2ats_dims& d, const void* q, int q
   tp.n_table = table_groups * d.n_kv_heads * kEncodeSlices * (small ? kTabTiles : 1);
   const dim3 grid(tp.n_key + tp.n_table + n_count), block(kTabThreads);
   if (grid.x == 0) return hipSuccess;
-#define A2ATS_LAUNCH_TABLES(BF, TILES)                                                                                    \
-  hipLaunchKernelGGL((build_lut_single_kernel<BF, TILES>), grid, block, 0, stream, q, cos_b, sin_b, codebook, q_rot, lut, \
-                     lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, shared ? 1 : 0, tp, few, cc, (const uint16_t*)codes,   \
-                     seq_lens, d.ctx_len, d.ctx_stride, top_k, window, n_sink)
-  if (q_dtype == A2ATS_BF16) {
-    if (small) A2ATS_LAUNCH_TABLES(true, 1); else A2ATS_LAUNCH_TABLES(true, kTabTiles);
-  } else {
-    if (small) A2ATS_LAUNCH_TABLES(false, 1); else A2ATS_LAUNCH_TABLES(false, kTabTiles);
-  }
+#define A2ATS_LAUNCH_TABLES(BF, TILES, FEW_KEYS)                                                                          \
+  hipLaunchKernelGGL((build_lut_single_kernel<BF, TILES, FEW_KEYS>), grid, block, 0, stream, q, cos_b, sin_b, codebook,  \
+                     q_rot, lut, lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, shared ? 1 : 0, tp, few, cc,             \
+                     (const uint16_t*)codes, seq_lens, d.ctx_len, d.ctx_stride, top_k, window, n_sink)
+#define A2ATS_LAUNCH_TABLES2(BF)                                                          \
+  do {                                                                                    \
+    if (small) A2ATS_LAUNCH_TABLES(BF, 1, true);                                          \
+    else if (d.batch * n_new <= kFewVectors) A2ATS_LAUNCH_TABLES(BF, kTabTiles, true);    \
+    else A2ATS_LAUNCH_TABLES(BF, kTabTiles, false);                                       \
+  } while (0)
+  if (q_dtype == A2ATS_BF16) A2ATS_LAUNCH_TABLES2(true);
+  else A2ATS_LAUNCH_TABLES2(false);
+#undef A2ATS_LAUNCH_TABLES2
 #undef A2ATS_LAUNCH_TABLES
   return hipGetLastError();
 }
 
 hipError_t launch_build_lut_single(const a2ats_dims& d, const void* q, int q_dtype, const float* cos_b,
                                    const float* sin_b, const float* codebook, float* q_rot, int32_t* lut,
-                                   float* lut_scale, bool shared, const FewKeys& few, const FewKeyPick& pick,
-                                   hipStream_t stream) {
-  return launch_tables_single(d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale, shared, few, pick, CodeCount{},
-                              pick.part ? 1 : 0, nullptr, nullptr, 0, 0, 0, stream);
+                                   float* lut_scale, bool shared, const FewKeys& few, hipStream_t stream) {
+  return launch_tables_single(d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale, shared, few, CodeCount{}, 0,
+                              nullptr, nullptr, 0, 0, 0, stream);
 }
 
-hipError_t launch_sweep_single(const a2ats_dims& d, const float* codebook, const FewKeys& few, hipStream_t stream) {
-  return launch_tables_single(d, nullptr, A2ATS_F32, nullptr, nullptr, codebook, nullptr, nullptr, nullptr, false, few,
-                              FewKeyPick{}, CodeCount{}, 0, nullptr, nullptr, 0, 0, 0, stream);
+hipError_t launch_sweep_single(const a2ats_dims& d, const FewKeys& few, hipStream_t stream) {
+  return launch_tables_single(d, nullptr, A2ATS_F32, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, false, few,
+                              CodeCount{}, 0, nullptr, nullptr, 0, 0, 0, stream);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1183,7 +1193,7 @@ hipError_t launch_decode_select_single(const a2ats_dims& d, const void* q, int q
   cc.tokens = p.tokens;
   cc.aligned = codes_aligned(d, codes);
   const hipError_t err = launch_tables_single(d, q, q_dtype, cos_b, sin_b, codebook, q_rot, lut, lut_scale, false, few,
-                                              FewKeyPick{}, cc, rows * p.n, codes, seq_lens, top_k, window, n_sink, stream);
+                                              cc, rows * p.n, codes, seq_lens, top_k, window, n_sink, stream);
   if (err != hipSuccess) return err;
   const int groups = (G + p.heads - 1) / p.heads;
 #define A2ATS_LAUNCH_CHUNKS(H)                                                                                          \

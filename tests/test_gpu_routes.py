@@ -333,6 +333,57 @@ def test_single_codebook_decode_select_equals_the_two_calls(Bn, G, Hkv, N, K, w,
     assert (res[1][4][-8:] == -7).all() and (res[1][0][:, :, N:] == 0).all()
 
 
+@pytest.mark.parametrize("Bn,Hkv,n_new", [(1, 1, 1), (1, 8, 1), (1, 4, 4), (1, 2, 5), (4, 8, 1), (5, 3, 1), (3, 2, 8), (17, 1, 1)])
+@pytest.mark.parametrize("mode", ["none", "diag", "block"])
+def test_single_codebook_keys_between_two_codewords_get_one_code_from_every_call(Bn, Hkv, n_new, mode):
+    """Keys half way between their two nearest codewords, so that only the rounding of the distortions tells these apart:
+    the calls that append keys agree, whatever the number of keys and whichever sweep that takes."""
+    g = torch.Generator(device="cuda").manual_seed(Bn * 64 + Hkv * 8 + n_new)
+    N, n = 4096 + 100, Bn * n_new
+    keys = torch.round(torch.randn(Bn, Hkv, n_new, 128, generator=g, device="cuda") * 512) / 512
+    codebook = torch.randn(Hkv, 4096, 128, generator=g, device="cuda") * 8
+    at = torch.stack([torch.randperm(4096, generator=g, device="cuda")[:2 * n] for _ in range(Hkv)])
+    for h in range(Hkv):
+        k = keys[:, h].reshape(n, 128)
+        off = torch.round(torch.randn(n, 128, generator=g, device="cuda") * 64) / 512   # (sums exact in float32)
+        codebook[h, at[h, :n]], codebook[h, at[h, n:]] = k + off, k - off
+    codebook = codebook.reshape(Hkv, 1, 4096, 128).contiguous()
+    a = torch.randn(Hkv, 128, 128, generator=g, device="cuda")
+    weights = {"none": None, "diag": torch.rand(Hkv, 128, generator=g, device="cuda") + 0.5,
+               "block": (torch.matmul(a, a.transpose(1, 2).contiguous()) / 128 + torch.eye(128, device="cuda")).contiguous()}[mode]
+    wmode = {"none": B.W_NONE, "diag": B.W_DIAG, "block": B.W_BLOCK}[mode]
+    q = torch.randn(Bn, 2 * Hkv, 128, generator=g, device="cuda")
+    inv = torch.tensor([1e4 ** (-i / 64) for i in range(64)], dtype=torch.float64)
+    res = []
+    for how in ("encode", "prologue", "select", "one sequence at a time", "one key at a time"):
+        codes = torch.zeros(Bn, Hkv, N, 1, dtype=torch.int16, device="cuda")
+        step = 1 if how == "one sequence at a time" else Bn
+        for b in range(0, Bn, step):
+            dims = B.make_dims(step, 2 * Hkv, Hkv, 128, 1, N, n_centroids=4096)
+            st = B.DecodeState(dims, 64, 64, 0, torch.float32, inv, 100)
+            ws = torch.empty(B.workspace_bytes(dims, B.OP_ENCODE), dtype=torch.uint8, device="cuda")
+            part = codes[b:b + step]
+            args = (part, q[b:b + step], st.cos_b, st.sin_b, st.q_rot, st.lut, st.lut_scale)
+            new = keys[b:b + step].contiguous()
+            if how in ("encode", "one sequence at a time"):
+                B.encode_keys(dims, new, n_new, N - n_new, codebook, weights, wmode, part, ws)
+            elif how == "one key at a time":
+                for j in range(n_new):
+                    B.encode_keys(dims, new[:, :, j:j + 1].contiguous(), 1, N - n_new + j, codebook, weights, wmode, part, ws)
+            elif how == "prologue":
+                B.decode_prologue(dims, new, n_new, N - n_new, codebook, weights, wmode, *args, ws)
+            else:
+                B.decode_select(dims, new, n_new, N - n_new, codebook, weights, wmode, *args, 64, 64, 0, None, st.topk_idx,
+                                st.topk_count, None, ws)
+            torch.cuda.synchronize()
+        res.append(codes)
+    got = res[0][:, :, N - n_new:, 0].long()
+    pair = at.reshape(Hkv, 2, Bn, n_new)
+    assert ((got == pair[:, 0].transpose(0, 1)) | (got == pair[:, 1].transpose(0, 1))).all()
+    for other in res[1:]:
+        assert torch.equal(res[0], other)
+
+
 @pytest.mark.parametrize("Bn,G,Hkv", [(5, 1, 2), (4, 2, 1), (3, 4, 3), (2, 7, 1), (17, 1, 1), (1, 8, 1)])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("shared", [False, True])

@@ -622,7 +622,9 @@ __global__ __launch_bounds__(kAddThreads) void update_add_kernel(const float* __
 // hist[kv][slice][c] follow the first place start[kv][c] of a code and, in the place of the counts, that of a slice's keys of
 // it; a workgroup then puts the keys of its slice there: order[kv][place] = (row, code).  768032 keys, 8 KV heads, all three
 // 28 us; 52 with a counter per codeword in memory, to be cleared first, whose atomics return a key's rank.  16 slices a KV
-// head: with 23 the scan takes 13.4 us instead of 9.8, and counting no less than 5.
+// head, which the scan reads at once, and 32 where they are long, whatever the number of heads: the whole update with 16, 24,
+// 32, 48, one KV head, 300000 keys 66 us, 67, 67, 72, 800000 169, 159, 153, 153 (163 with the counters in memory); 2 heads of
+// 400000 144, 142, 142, 145; 4 of 200000 132, 133, 136, 141; 8 of 200000 226, 230, 233, 240.
 constexpr int kFL = 4096, kOrderThreads = 1024;
 struct OrderSlices {
   int n;        // per KV head
@@ -630,7 +632,8 @@ struct OrderSlices {
 };
 inline OrderSlices order_slices(long rows) {   // (at most as many as a word per row holds counts of, but at least one)
   OrderSlices s;
-  s.n = (int)(rows / kFL < 1 ? 1 : (rows / kFL > 16 ? 16 : rows / kFL));
+  const long most = rows >= 400000 ? 32 : 16;
+  s.n = (int)(rows / kFL < 1 ? 1 : (rows / kFL > most ? most : rows / kFL));
   s.per = (rows + s.n - 1) / s.n;
   return s;
 }
@@ -661,17 +664,24 @@ __global__ __launch_bounds__(kOrderThreads) void update_count_kernel(const uint1
   for (int i = threadIdx.x; i < kFL; i += kOrderThreads) out[i] = s_n[i];
 }
 
+constexpr int kScanAhead = 16;   // slices whose counts are on their way together
 // With one slice `hist` is `counts`, and the slice's first places are `start`.
 __global__ __launch_bounds__(1024) void update_scan_kernel(uint32_t* hist, uint32_t* counts, uint32_t* __restrict__ start,
                                                            int slices) {
   __shared__ uint32_t s_wave[16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   uint4* mine = (uint4*)(hist + (size_t)blockIdx.x * slices * kFL) + tid;   // four codes, kFL / 4 apart by slice
-  uint4 n = make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll 8
-  for (int s = 0; s < slices; ++s) {
-    const uint4 h = mine[(size_t)s * (kFL / 4)];
-    n = make_uint4(n.x + h.x, n.y + h.y, n.z + h.z, n.w + h.w);
+  uint4 n = make_uint4(0u, 0u, 0u, 0u), h[kScanAhead];
+  auto request = [&](int s0) {   // (conditions on slices are uniform)
+#pragma unroll
+    for (int u = 0; u < kScanAhead; ++u)
+      if (s0 + u < slices) h[u] = mine[(size_t)(s0 + u) * (kFL / 4)];
+  };
+  for (int s0 = 0; s0 < slices; s0 += kScanAhead) {
+    request(s0);
+#pragma unroll
+    for (int u = 0; u < kScanAhead; ++u)
+      if (s0 + u < slices) n = make_uint4(n.x + h[u].x, n.y + h[u].y, n.z + h[u].z, n.w + h[u].w);
   }
   const uint32_t own = n.x + n.y + n.z + n.w;
   uint32_t inc = own;
@@ -688,11 +698,14 @@ __global__ __launch_bounds__(1024) void update_scan_kernel(uint32_t* hist, uint3
   ((uint4*)(counts + (size_t)blockIdx.x * kFL))[tid] = n;
   ((uint4*)(start + (size_t)blockIdx.x * kFL))[tid] = at;
   if (slices == 1) return;
-#pragma unroll 8
-  for (int s = 0; s < slices; ++s) {
-    const uint4 h = mine[(size_t)s * (kFL / 4)];
-    mine[(size_t)s * (kFL / 4)] = at;
-    at = make_uint4(at.x + h.x, at.y + h.y, at.z + h.z, at.w + h.w);
+  for (int s0 = 0; s0 < slices; s0 += kScanAhead) {
+    if (slices > kScanAhead) request(s0);   // (else they are still there)
+#pragma unroll
+    for (int u = 0; u < kScanAhead; ++u)
+      if (s0 + u < slices) {
+        mine[(size_t)(s0 + u) * (kFL / 4)] = at;
+        at = make_uint4(at.x + h[u].x, at.y + h[u].y, at.z + h[u].z, at.w + h[u].w);
+      }
   }
 }
 
@@ -779,8 +792,9 @@ __global__ __launch_bounds__(256) void update_sorted_kernel(const float* __restr
   finish(run == code_after);
 }
 
-// The codewords whose keys more than one wave added up, those without keys, and the counts: 16 codewords a wave.
-constexpr int kRestPerWave = 16;
+// The codewords whose keys more than one wave added up, those without keys, and the counts: four codewords a wave, one after the
+// other (48000 keys of one KV head 31.3 -> 29.9 us against 16 a wave, 800000 152.9 -> 150.4).
+constexpr int kRestPerWave = 4;
 __global__ __launch_bounds__(256) void update_rest_kernel(const double* __restrict__ sums, const uint32_t* __restrict__ counts,
                                                           const uint32_t* __restrict__ start, const float* __restrict__ old_cb,
                                                           float* __restrict__ new_cb, int32_t* __restrict__ counts_out,

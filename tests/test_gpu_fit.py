@@ -16,7 +16,7 @@ def _workspace(dims, least):
 @pytest.mark.parametrize("m", [1, 16, 32])
 @pytest.mark.parametrize("least", [False, True])
 @pytest.mark.parametrize("batch,kv,n,skew", [(1, 1, 1, False), (2, 3, 63, False), (1, 2, 4097, True), (3, 8, 2050, False),
-                                             (1, 1, 50001, True), (12, 1, 60000, False)])
+                                             (1, 1, 50001, True), (12, 1, 60000, False)])   # (of the last: more slices than the scan reads at once)
 def test_codebook_update(m, least, batch, kv, n, skew):
     L, ds, stride, pos0 = (4096, 128, n + 9, 5) if m == 1 else (256, 128 // m, n + 9, 5)
     g = torch.Generator(device="cuda").manual_seed(n + m)

@@ -592,11 +592,20 @@ static AppendPlan append_plan(long n_pairs, int n_lut) {
 // 49.1 -> 40.9, 63.0 -> 52.9; 9 sequences (two rounds) 25.3 -> 37.2 and 70.6 -> 80.6.  With one head to a group nothing is shared
 // that a second round could lose: 64 sequences of 8 KV heads, one selection each, 4096, 8192, 16000 tokens 81.0 -> 80.6, 97.3 ->
 // 88.0, 107.8 -> 98.9.
+// Several keys to append are more than the heads should take besides (three sweeps or more), while the groups leave room for
+// workgroups that do: 8 sequences, M = 32, 1500 tokens (without the attention), 4 keys 25.7 -> 23.3, 8 25.6 -> 27.7; 16, which
+// neither leaves room for, 42.9 -> 36.7.
 bool takes_head_route(const a2ats_dims& d, int n_new, int window, int n_sink, bool shared) {
   const long ncand = (long)d.ctx_len - window - n_sink, heads = (long)d.batch * (shared ? d.n_kv_heads : d.n_q_heads);
   const bool one_a_group = shared || d.n_q_heads == d.n_kv_heads;
   if (single_codebook(d) || ncand > kKeepRows * kExactThreads || heads > (one_a_group ? 512 : 256)) return false;
-  return d.n_sub == 32 || ncand > 8192 || !append_plan((long)d.batch * d.n_kv_heads * n_new * d.n_sub, (int)heads).folded;
+  const long pairs = (long)d.batch * d.n_kv_heads * n_new * d.n_sub;
+  const AppendPlan ap = append_plan(pairs, (int)heads);
+  if (!ap.folded || ncand > 8192) return true;
+  if (d.n_sub == 16) return false;
+  const int per = shared ? 1 : d.n_q_heads / d.n_kv_heads;
+  const long groups = (long)d.batch * d.n_kv_heads * ((per + kHeadsPerGroup - 1) / kHeadsPerGroup);
+  return ap.sweeps < 3 || !takes_group_route(d, window, n_sink) || append_plan(pairs, (int)groups).folded;
 }
 
 // Heads that select by themselves (SHARED: KV heads) and the append in one launch, where takes_head_route.

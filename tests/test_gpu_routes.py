@@ -429,6 +429,8 @@ def test_single_codebook_tables_of_few_heads_equal_those_of_many(Bn, G, Hkv, dty
     (2, 5, 1, 32, 700, 700, 64, 2, 3, None, None),                    # everything selected
     (1, 4, 2, 16, 3000, 0, 64, 0, 1, None, None),                     # nothing
     (8, 4, 8, 32, 2000, 100, 64, 0, 1, None, None),                   # 256 heads: they encode the keys as well
+    (8, 4, 8, 32, 2000, 100, 64, 0, 8, None, None),                   # too many keys for that: by group
+    (8, 4, 8, 32, 2000, 100, 64, 0, 16, None, None),                  # neither leaves room for workgroups that encode
     (8, 4, 8, 16, 9000, 500, 64, 4, 4, None, "zero"),                 # the same; queries of zero
     (33, 1, 8, 16, 2500, 100, 64, 0, 1, None, None),                  # 264 groups of one head, in two rounds
 ])

@@ -236,6 +236,64 @@ def test_queries_that_are_not_finite_select_within_their_rows(Bn, G, M, N, K, n_
         assert (got[:, 1:] > got[:, :-1]).all() and (got >= n_sink).all() and (got < N - 64).all()
 
 
+@pytest.mark.parametrize("Bn,G,Hkv,M,N,K,w,n_sink", [
+    (1, 4, 2, 16, 3000, 300, 64, 4),      # a workgroup per head
+    (2, 3, 2, 32, 16384 + 64, 700, 64, 0),
+    (16, 4, 8, 16, 3000, 300, 64, 4),     # by group
+    (2, 4, 2, 16, 40000, 1200, 64, 4),    # the streaming route
+    (40, 8, 2, 32, 20000, 600, 64, 0),    # ... with one sampling workgroup a problem
+    (1, 4, 1, 1, 20000, 500, 64, 4),      # a single codebook: one head a workgroup
+    (5, 7, 2, 1, 9000, 4000, 64, 0),      # (and more than four vectors of a KV head)
+    (40, 4, 2, 1, 40000, 500, 64, 0),     # two heads, longer chunks
+])
+@pytest.mark.parametrize("bad", ["inf", "nan", "huge"])
+def test_decode_select_of_values_that_are_not_finite_equals_the_two_calls(Bn, G, Hkv, M, N, K, w, n_sink, bad):
+    """Queries and appended keys that are not finite through the one call: tables, codes and counts of the two calls, bit for bit,
+    K' ascending candidates per head, and nothing behind the outputs.  (Which candidates is told by the single codebook only,
+    whose scores are table entries; the sums of the others wrap, and the routes order them differently.)"""
+    wl = synth.Workload("bad", Bn, Hkv * G, Hkv, 128, M, N, K, w, n_sink=n_sink, seed=N + K,
+                        n_centroids=4096 if M == 1 else 256)
+    xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
+    q, keys = xd["q"].float(), synth.make_encode_keys(wl, 1, device="cuda")
+    if bad == "huge":
+        q *= 3e38
+        keys[::2] *= 1e38
+    else:
+        q[:, ::2, 5] = float(bad)
+        q[:, 1, 64:] = -float(bad)
+        q[-1, -1, ::3] = float(bad)
+        keys[0, :, :, 7] = float(bad)
+        keys[-1, -1, :, 70:] = -float(bad)
+    dims = H.dims_of(wl)
+    heads = Bn * Hkv * G
+    ws = torch.empty(max(B.workspace_bytes(dims, B.OP_ENCODE), B.workspace_bytes(dims, B.OP_SCORE_TOPK, K, w), 256),
+                     dtype=torch.uint8, device="cuda")
+    res = []
+    for one in (False, True):
+        st = B.DecodeState(dims, K, w, n_sink, torch.float32, xd["inv_freq"], wl.wrope_b)
+        st.lut.fill_(-1)
+        idx = torch.full((heads * K + N,), -7, dtype=torch.int32, device="cuda")
+        score = torch.full((heads * K + N,), -7.0, device="cuda")
+        codes = torch.cat([xd["codes"].reshape(-1), xd["codes"].reshape(-1)[:256]])
+        args = (dims, keys, 1, N - 1, xd["codebook"], None, B.W_NONE, codes, q, st.cos_b, st.sin_b, st.q_rot, st.lut,
+                st.lut_scale)
+        if one:
+            B.decode_select(*args, K, w, n_sink, None, idx, st.topk_count, score, ws)
+        else:
+            B.decode_prologue(*args, ws)
+            B.score_topk(dims, codes, st.lut, st.lut_scale, K, w, n_sink, None, idx, st.topk_count, score, None, ws)
+        torch.cuda.synchronize()
+        res.append([t.view(torch.int32) for t in (st.lut, st.lut_scale, st.q_rot, st.topk_count)] + [codes] +
+                   ([idx, score.view(torch.int32)] if M == 1 else []))
+        assert (idx[heads * K:] == -7).all() and (score[heads * K:] == -7.0).all()
+        assert torch.equal(codes[-256:], xd["codes"].reshape(-1)[:256])
+        got = idx[:heads * K].view(heads, K)
+        assert (st.topk_count == K).all()
+        assert (got[:, 1:] > got[:, :-1]).all() and (got >= n_sink).all() and (got < N - w).all()
+    for a, b in zip(*res):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("N,K,w,n_sink", [(700, 100, 64, 4), (700, 508, 100, 0), (5000, 4096, 64, 4), (1500, 1000, 0, 0), (900, 0, 230, 0)])
 def test_float32_attention_of_many_heads_is_as_exact_as_that_of_few(N, K, w, n_sink):
     """The same four sequences among 40 (a workgroup takes a whole head) and alone (its rows are shared out), against

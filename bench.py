@@ -355,7 +355,17 @@ def single_codebook_step(args, torch, B, synth, wl):
         B.encode_prepare(dims, x["codebook"], h_block, B.W_BLOCK, x["enc_ws"])
 
     def step(i, timed):
+        # the steps timed for `value` make two calls (a2ats_decode_select: tables, appended key and the candidates per
+        # codeword in one launch, the selection in another; a2ats_sparse_attn), unless --separate-prologue asks for
+        # single ones; the steps with events between the phases make separate calls
         x = reps[i % R]
+        if not timed and not args.separate_prologue:
+            B.decode_select(dims, x["new_key"], 1, N - 1, x["codebook"], h_block, B.W_BLOCK | B.W_PREPARED, x["codes"],
+                            x["q"], st.cos_b, st.sin_b, st.q_rot, st.lut, st.lut_scale, K, w, wl.n_sink, None,
+                            st.topk_idx, st.topk_count, None, x["enc_ws"])
+            B.sparse_attn(dims, x["q"], st.q_rot, x["k"], x["v"], st.topk_idx, st.topk_count, K, w, wl.n_sink,
+                          st.cos_win, st.sin_win, None, st.out, st.ws)
+            return
         if timed:
             ev[i][0].record()
         if args.separate_prologue:
@@ -364,7 +374,7 @@ def single_codebook_step(args, torch, B, synth, wl):
             if timed:
                 ev[i][1].record()
             B.build_lut(dims, x["q"], st.cos_b, st.sin_b, x["codebook"], st.q_rot, st.lut, st.lut_scale)
-        else:   # the sweep of the key encoder, then the table build that also picks the code
+        else:   # the table build with the key's sweep, then the pick of its code
             if timed:
                 ev[i][1].record()
             B.decode_prologue(dims, x["new_key"], 1, N - 1, x["codebook"], h_block, B.W_BLOCK | B.W_PREPARED,
@@ -405,14 +415,17 @@ def single_codebook_step(args, torch, B, synth, wl):
         "config": {"workload": wl.name, "batch": Bn, "n_q_heads": Hq, "n_kv_heads": Hkv, "head_dim": D, "n_sub": 1,
                    "codewords": 4096, "ctx_len": N, "top_k": K, "window": w, "replicas_cycled": R},
         "us_per_decode_step": ms * 1e3,
-        "prologue": "encode_keys + build_lut" if args.separate_prologue else "decode_prologue (two launches)",
+        "calls_per_step": "encode_keys, build_lut, score_topk, sparse_attn" if args.separate_prologue else
+                          "decode_select (tables, key and counts of the codewords, then the selection), sparse_attn",
         "phase_us_median": ({"encode_1key": ph[0], "wrope_lut": ph[1]} if args.separate_prologue else
-                            {"encode_1key_and_wrope_lut": ph[1]}) | {"score_topk": ph[2], "sparse_attn": ph[3]},
+                            {"encode_1key_and_wrope_lut": ph[1]}) | {
+                                 "score_topk": ph[2], "sparse_attn": ph[3],
+                                 "note": "from steps made of the separate calls with events between"},
         "roofline": {"kernel": "select_single_kernel", "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": None,
                      "algorithmic_bytes_per_launch": kernel_bytes,
                      "avg_launch_us": ph[2],
-                     "note": "duration = events around the a2ats_score_topk call (one kernel)"},
+                     "note": "duration = events around the a2ats_score_topk call (one kernel) of the separate calls"},
     }
     if not args.no_cpu_baseline:
         from oracle import oracle as orc

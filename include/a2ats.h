@@ -200,19 +200,23 @@ int a2ats_decode_prologue(const a2ats_dims* dims, const float* keys, int32_t n_n
  * a2ats_workspace_bytes asks for) the call needs one launch less than the two: the
  * workgroups that sample the thresholds build their problem's tables themselves and keep the coarse
  * copy in LDS.  That is done while (a) those workgroups, batch * n_kv_heads * head groups * sampling
- * parts, number at most 256, one per CU, and (b) no appended row can be a candidate of any sequence,
+ * parts, number at most 256, one per CU, or one of them can take a problem's whole sample (8192 rows
+ * or fewer), and (b) no appended row can be a candidate of any sequence,
  * pos0 >= ctx_len - window (the usual append of the current token; the sampling workgroups read
  * candidate rows while others write the appended ones).  With at most 16384 candidates and (b) the
  * whole call is one launch: by head, a workgroup each, while batch * n_q_heads is at most 256 (512
- * where every KV head has one query head) and n_sub is 32, or the candidates number more than 8192,
- * or there are too many appended keys for the heads' workgroups; else by group where a2ats_score_topk
- * takes its group route.
+ * where every KV head has one query head) and the candidates number more than 8192, or workgroups that
+ * encode the appended keys fit beside the heads' in one round of 256, or n_sub is 32 and the keys are
+ * few enough (or fit nowhere) for the heads' workgroups to encode them too; else by group where
+ * a2ats_score_topk takes its group route.
  * Single codebook: with a key to append and (b) the call is two launches -- tables, keys and the number of
  * candidates per codeword, then the selection -- instead of three; the counts lie in `ws`, behind the part that
  * a2ats_encode_prepare fills.
  * Elsewhere it simply makes the two calls.
  * Arguments are the union of theirs and are all checked before anything is enqueued; every output
- * (codes, q_rot, lut, lut_scale, topk_*) is bit for bit what the two calls write.
+ * (codes, q_rot, lut, lut_scale, topk_*) is bit for bit what the two calls write.  (With product quantisation and a
+ * query that is not finite the sums of table entries wrap: K' candidates are selected all the same, but which
+ * depends on the route.)
  * `ws`: a2ats_workspace_bytes(dims, A2ATS_OP_SCORE_TOPK, top_k, window) bytes for product
  * quantisation (the prologue needs none there), a2ats_workspace_bytes(dims, A2ATS_OP_ENCODE, 0, 0)
  * for the single codebook (n_new == 0: none).
@@ -379,9 +383,9 @@ int a2ats_sparse_attn_host(const a2ats_dims* dims, const void* q, const float* q
  *                            + a2ats_build_lut_shared + a2ats_score_topk with those dims, as one call
  *                            (what a2ats_decode_select is for the per-head selection: on the streaming
  *                            route, with at most 256 sampling workgroups = batch * n_kv_heads * sampling
- *                            parts and pos0 >= ctx_len - window, one launch does the append, the
- *                            tables and the threshold sampling; at most 16384 candidates: one launch for
- *                            all, as there; elsewhere the three launches follow each other).  `dims` are the real ones; lut, lut_scale, topk_* and `ws`
+ *                            parts, or samples of at most 8192 rows, and pos0 >= ctx_len - window, one launch
+ *                            does the append, the tables and the threshold sampling; at most 16384 candidates:
+ *                            one launch for all, as there; elsewhere the three launches follow each other).  `dims` are the real ones; lut, lut_scale, topk_* and `ws`
  *                            (a2ats_workspace_bytes(.., A2ATS_OP_SCORE_TOPK, ..)) are those of dims with
  *                            n_q_heads = n_kv_heads.  Every output is bit for bit what the three calls
  *                            write.  Product quantisation only (A2ATS_ERR_UNSUPPORTED otherwise).

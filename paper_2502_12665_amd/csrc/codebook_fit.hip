@@ -282,15 +282,20 @@ template <int W>
 __device__ __forceinline__ void top_products(const uint8_t* mags, i32x4* sums) {
   constexpr DigitTiles T = digit_tiles(W);
   const int lane = threadIdx.x & 63;
+  i32x4 s[kDigitTiles];   // (read ahead of the stores, which the compiler would not pass)
+#pragma unroll
+  for (int t = 0; t < kDigitTiles; ++t)
+    if (t < T.n) s[t] = sums[tile_index(T.i[t], T.j[t]) * 64 + lane];
 #pragma unroll
   for (int t = 0; t < kDigitTiles; ++t)
     if (t < T.n) {
       const i32x4 row = *(const i32x4*)(mags + T.i[t] * kDigitFrag + lane * 16);
       const i32x4 col = *(const i32x4*)(mags + T.j[t] * kDigitFrag + lane * 16);
-      i32x4& s = sums[tile_index(T.i[t], T.j[t]) * 64 + lane];
-      s = __builtin_amdgcn_mfma_i32_16x16x64_i8(row, col, s, 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);   // (registers)
+      s[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(row, col, s[t], 0, 0, 0);
     }
+#pragma unroll
+  for (int t = 0; t < kDigitTiles; ++t)
+    if (t < T.n) sums[tile_index(T.i[t], T.j[t]) * 64 + lane] = s[t];
 }
 
 // Whether this lane's sums are large enough for `rows` rows.  (A dimension that has been zero so far has exact products.)

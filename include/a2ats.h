@@ -210,8 +210,8 @@ int a2ats_decode_prologue(const a2ats_dims* dims, const float* keys, int32_t n_n
  * few enough (or fit nowhere) for the heads' workgroups to encode them too; else by group where
  * a2ats_score_topk takes its group route.
  * Single codebook: with a key to append and (b) the call is two launches -- tables, keys and the number of
- * candidates per codeword, then the selection -- instead of three; the counts lie in `ws`, behind the part that
- * a2ats_encode_prepare fills.
+ * candidates per codeword, then the selection -- instead of three, but for many heads at very long contexts; the counts lie in
+ * `ws`, behind the part that a2ats_encode_prepare fills.
  * Elsewhere it simply makes the two calls.
  * Arguments are the union of theirs and are all checked before anything is enqueued; every output
  * (codes, q_rot, lut, lut_scale, topk_*) is bit for bit what the two calls write.  (With product quantisation and a

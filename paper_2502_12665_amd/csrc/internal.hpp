@@ -143,7 +143,7 @@ hipError_t launch_decode_prologue_single(const a2ats_dims& d, const float* keys,
 // The sweep alone.
 hipError_t launch_sweep_single(const a2ats_dims& d, const FewKeys& few, hipStream_t stream);
 // Tables, appended keys and selection in two launches; no appended row may be a candidate.  scratch holds the counts of
-// the sequences' chunks.
+// the sequences' chunks.  fits: and whether that is the faster way.
 bool select_chunks_single_fits(const a2ats_dims& d, int window, int n_sink, size_t scratch_bytes);
 hipError_t launch_decode_select_single(const a2ats_dims& d, const void* q, int q_dtype, const float* cos_b,
                                        const float* sin_b, const float* codebook, float* q_rot, int32_t* lut,

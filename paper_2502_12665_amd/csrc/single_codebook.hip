@@ -1174,8 +1174,21 @@ static ChunkPlan plan_chunks(const a2ats_dims& d, int window, int n_sink) {
   return p;
 }
 
+// Every workgroup adds up the counts of all chunks, so the work grows with the square of the context, and with many heads at long
+// contexts a workgroup a head, which counts by itself, is the faster way (two calls).  Both times but for what they have in
+// common, us, from steps without the attention of 1 to 128 sequences, 8 to 1024 heads, 16384 to 1048576 tokens; a workgroup
+// by itself holds the codes of 131072 tokens and reads those of more again.  Two calls -> by chunk: 32 sequences of 8 KV heads
+// with one query head each, 65536 tokens 49.8 -> 45.2, 131072 59.2 -> 69.0, 1048576 259 -> 759; 128 of these 158 -> 151, 208 -> 263;
+// 16 of them 262144 tokens 74 -> 68, 524288 116 -> 138; four heads each, 16 sequences, 524288 256 -> 205, 1048576 457 -> 514;
+// one sequence 1048576 181 -> 47.
 bool select_chunks_single_fits(const a2ats_dims& d, int window, int n_sink, size_t scratch_bytes) {
-  return plan_chunks(d, window, n_sink).bytes <= scratch_bytes;
+  const ChunkPlan p = plan_chunks(d, window, n_sink);
+  const int G = d.n_q_heads / d.n_kv_heads;
+  const double wgs = (double)d.batch * d.n_kv_heads * ((G + p.heads - 1) / p.heads) * p.n;
+  const double by_chunk = wgs * (0.0215 + 0.004 * (std::min(G, p.heads) - 1) + 0.0003 * p.n);
+  const double heads = (double)d.batch * d.n_q_heads, n = (double)p.n * p.tokens / kMaxChunk;
+  const double by_head = 10 + 0.06 * heads + n * (n <= 8 ? 1.6 : 3.0) * std::max(1.0, heads / 256);
+  return p.bytes <= scratch_bytes && by_chunk <= by_head;
 }
 
 hipError_t launch_decode_select_single(const a2ats_dims& d, const void* q, int q_dtype, const float* cos_b,

@@ -342,6 +342,8 @@ def test_float32_attention_of_many_heads_is_as_exact_as_that_of_few(N, K, w, n_s
     (4, 4, 2, 12000, 3999, 64, 4, 3, None, 0, "crowded"),        # nearly equal scores: a crowded bin
     (2, 4, 1, 700, 636, 64, 0, 1, None, 0, None),                # few tokens: the counts do not fit, the two calls
     (1, 2, 1, 6000, 0, 64, 0, 1, None, 0, None),
+    (40, 1, 8, 140000, 1000, 64, 4, 1, None, 0, None),           # too many chunks of too many heads: the two calls
+    (36, 1, 8, 49152 + 68, 1000, 64, 4, 1, None, 0, None),       # the most that still go by chunk, exactly three of them
 ])
 @pytest.mark.parametrize("mode", ["none", "block"])
 def test_single_codebook_decode_select_equals_the_two_calls(Bn, G, Hkv, N, K, w, n_sink, n_new, lens, stride, data, mode):

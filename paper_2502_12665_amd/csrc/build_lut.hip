@@ -574,11 +574,12 @@ struct AppendPlan {
   int sweeps, folded;
   unsigned n_enc;
 };
-static AppendPlan append_plan(long n_pairs, int n_lut) {
+// may_wait: pairs for each CU that the table workgroups leave free, from which these take them, where there are more.
+static AppendPlan append_plan(long n_pairs, int n_lut, int may_wait = 0) {
   AppendPlan p;
   p.sweeps = encode_few_sweeps(n_pairs);
   const long per_wg = (long)kFewPairsPerSweep * p.sweeps, n_enc = (n_pairs + per_wg - 1) / per_wg;
-  p.folded = n_lut > 0 && n_lut + n_enc > 256;
+  p.folded = n_lut > 0 && n_lut + n_enc > 256 && n_pairs > (long)may_wait * (256 - n_lut);
   if (p.folded) p.sweeps = (int)((n_pairs + (long)kFewPairsPerSweep * n_lut - 1) / ((long)kFewPairsPerSweep * n_lut));
   p.n_enc = p.folded ? 0u : (unsigned)n_enc;
   return p;
@@ -697,7 +698,12 @@ hipError_t launch_decode_select_prologue(const a2ats_dims& d, const float* keys,
   const int G = d.n_q_heads / d.n_kv_heads;
   const int NG = shared ? 1 : (G + kHeadsPerGroup - 1) / kHeadsPerGroup;
   const int n_sample = d.batch * d.n_kv_heads * NG * P0;
-  const AppendPlan ap = append_plan((long)d.batch * d.n_kv_heads * n_new * d.n_sub, n_sample);
+  // The sampling takes longer than the encoding of a few keys, so workgroups that encode may wait for one another on the CUs that
+  // it leaves free, up to 48 pairs for each (M = 32: 108).  Sampling workgroups do it themselves -> others, one wait: 176 problems
+  // of 40000 tokens (35 pairs a CU) 92.5 -> 90.3 us, M = 32 (70) 147.1 -> 143.1, two keys (70, 141) 95.7 -> 97.1 and 151.7 ->
+  // 152.7; 160, M = 32, two keys (107) 137.5 -> 133.8, three (160) 142.7 -> 147.4; 200 (57, M = 32 114) 103.4 -> 106.8 and 161.7
+  // -> 166.3.
+  const AppendPlan ap = append_plan((long)d.batch * d.n_kv_heads * n_new * d.n_sub, n_sample, d.n_sub == 32 ? 108 : 48);
   const dim3 grid(n_sample + ap.n_enc), block(kLutThreads);
   if (grid.x == 0) return hipSuccess;
   static LdsSlot s_lds[8][16];

@@ -543,6 +543,8 @@ def test_selection_by_head_equals_the_calls(Bn, G, Hkv, M, N, K, w, n_sink, n_ne
     (24, 4, 8, 16, 70000, 700, 64, 0, 1, None),      # too many rows for one: the sampling stays a launch of its own
     (17, 4, 8, 32, 40000, 2300, 64, 4, 1, True),     # a wide selection
     (40, 4, 8, 16, 16500, 400, 64, 0, 0, None),      # nothing appended
+    (24, 4, 8, 16, 17000, 400, 64, 0, 1, None),      # 192 groups, workgroups that encode wait for each other on the free CUs
+    (22, 4, 8, 32, 17000, 400, 64, 0, 2, None),      # 176, too many keys for that
 ])
 @pytest.mark.parametrize("shared", [False, True])
 def test_decode_select_of_many_sequences_equals_the_calls(Bn, G, Hkv, M, N, K, w, n_sink, n_new, lens, shared):

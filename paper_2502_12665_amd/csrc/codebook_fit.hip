@@ -313,7 +313,6 @@ __device__ __forceinline__ bool top_suffices(const i32x4* sums, const DigitLds& 
       const uint32_t most[4] = {m.x, m.y, m.z, m.w}, col = L.most[16 * j + (lane & 15)];
 #pragma unroll
       for (int r = 0; r < 4; ++r) ok &= 8u * (uint32_t)s[r] >= rows || col == 0u || most[r] == 0u;
-      __builtin_amdgcn_sched_barrier(0);   // (registers)
     }
   return ok;
 }
@@ -486,7 +485,7 @@ __device__ __forceinline__ void digit_body(const float* __restrict__ q_rot, doub
       __syncthreads();
       ++step;
       fits = L.flagged != step;
-      if (fits && step < stop && step - start == kTopFirst) good = fine_enough(kTopFirst);
+      if (fits && step - start == kTopFirst && stop - step >= kTopFirst) good = fine_enough(kTopFirst);
     } while (fits && good && step < stop);
     if (!good || !(good = fine_enough(step - start))) break;
     digit_flush<W>(acc, L, out, first);

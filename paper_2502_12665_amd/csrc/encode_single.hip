@@ -24,12 +24,14 @@
 //                                  1/2 ||c^z||^2, and the largest norms
 //   encode_single_operands_kernel  w_c in matrix-core operand order: rounded to f16, and as two bf16
 //                                  terms (hi + lo, 16 significant bits)
-//   encode_single_filter_kernel    every key: scores from one f16 product (11 significant bits per
-//                                  operand) with the two smallest and the code of the first kept per
-//                                  key.  Where they are further apart than the rounding of the
-//                                  operands can account for -- its norm is known for every key and
-//                                  bounded for the codewords -- the code is decided; the other keys
-//                                  are listed.
+//   encode_single_sample_kernel, encode_single_choose_kernel
+//                                  128 keys of a KV head say which of the two filters it takes
+//   encode_single_filter8_kernel   every key: scores from one product of whole numbers of 8 bits; keys that their rounding
+//                                  leaves open are listed
+//   encode_single_filter_kernel    the same with scores from one f16 product (11 significant bits per operand): the two
+//                                  smallest and the code of the first are kept per key.  Where they are further apart than
+//                                  the rounding of the operands can account for -- its norm is known for every key and
+//                                  bounded for the codewords -- the code is decided; the other keys are listed.
 //   encode_single_kernel           the listed keys, 256 at a time: three bf16 products per term
 //                                  (hi.hi + hi.lo + lo.hi, float32 accumulate) give the scores to
 //                                  about 2^-17 relative.  Every lane owns one key column of the
@@ -67,20 +69,29 @@ constexpr int kSlices = kEncodeSlices;  // workgroups sharing the codewords of o
 // the slack of the first figure).  Where |k| is short against the codewords the second is all there is.
 constexpr float kSplitReach = 2.5e-5f, kSumReach = 6e-6f;
 constexpr int kF16Bytes = 8 * 64 * 16;  // 8 k-steps x 64 lanes x 16 bytes: 32 codewords of 128 dims in f16
+constexpr int kI8Bytes = 32 * kD;       // the same in i8, a codeword after the other
+constexpr int kSampleKeys = 128;        // keys of a KV head that say which filter it takes,
+constexpr int kSampleSlices = 16;       // against so many slices of the codewords
+constexpr int kSampleOpen = 4;          // and how many of them the i8 filter may leave open
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) int i32x4;
+typedef __attribute__((ext_vector_type(16))) int i32x16;
 
 // Of a KV head, over its codewords (float bits, which order like the values).
 struct alignas(128) CodewordStat {   // (a cache line each: they are filled by atomics)
   uint32_t w_max, c_max, bias_max;   // largest |w / t|, |c t| and 1/2 |c^z|^2, rounded up
   uint32_t w_err;                    // largest |w - f16(w)|, in the scaled units of the f16 operands
+  uint32_t w_elem, c_elem;           // largest magnitude of an element of w / t and of c t, rounded up
+  uint32_t w_err8;                   // largest |w - i8(w)|, in the scaled units of the i8 operands
 };
 
 // What is subtracted from every key and codeword of a KV head, and the powers of two t.
 struct alignas(32) Center {
   float mu[kD], key[kD], t[kD];   // (key: t by the scale of the f16 operands)
+  float key8[kD];                 // t by the scale of the i8 operands
 };
 __device__ __forceinline__ float inverse_of_power(float t) { return __uint_as_float((254u << 23) - __float_as_uint(t)); }
 constexpr int kMeans = 16;   // shares of the codewords whose means the centre is the median of
@@ -96,7 +107,7 @@ inline long near_groups(const a2ats_dims& d) { return d.n_kv_heads < 512 ? 512 /
 
 struct EncWs {
   size_t off_L, off_sd, off_heff, off_means, off_center, off_czT, off_wT, off_chalf, off_cfrag, off_cbias, off_f16,
-      off_fbias, off_cstat, off_count, off_list, off_near, off_near_part, off_part, bytes;
+      off_fbias, off_i8, off_bias8, off_cstat, off_sample, off_norms, off_eight, off_count, off_list, off_near, off_near_part, off_part, bytes;
   size_t near_cap;   // keys of a KV head
 };
 
@@ -122,7 +133,12 @@ EncWs enc_single_ws(const a2ats_dims& d) {
   w.off_cbias = take(Hkv * kCW * sizeof(float));
   w.off_f16 = take(Hkv * kBlocks * (size_t)kF16Bytes);
   w.off_fbias = take(Hkv * kCW * sizeof(float));
+  w.off_i8 = take(Hkv * kBlocks * (size_t)kI8Bytes);
+  w.off_bias8 = take(Hkv * kCW * sizeof(int));
   w.off_cstat = take(Hkv * sizeof(CodewordStat));
+  w.off_sample = take(Hkv * kSampleSlices * kSampleKeys * sizeof(int2));
+  w.off_norms = take(Hkv * kSampleKeys * sizeof(float2));
+  w.off_eight = take(Hkv * sizeof(uint32_t));
   // keys for float64, listed keys per KV head, arrivals per KV head and chunk of its list
   w.off_count = take((1 + Hkv + Hkv * (size_t)near_groups(d)) * sizeof(uint32_t));
   w.off_list = take(keys_max * 2 * sizeof(uint32_t));
@@ -142,6 +158,18 @@ __device__ __forceinline__ bool f16_scales(const CodewordStat& st, float& key_sc
   key_scale = ok ? __uint_as_float((uint32_t)(127 + 2 - ec) << 23) : 1.f;
   w_scale = ok ? __uint_as_float((uint32_t)(127 + 6 - ew) << 23) : 1.f;
   return ok;
+}
+
+// Scales of the i8 operands: the largest element of c becomes 100 (keys reach a little further out than their codewords; what
+// is beyond 127 is cut off and counted as an error), of w 127.  False: out of reach, or 1/2 |c^z|^2 is too large against the
+// products for a score of 22 bits.
+__device__ __forceinline__ bool i8_scales(const CodewordStat& st, float& key_scale, float& w_scale) {
+  const float c = __uint_as_float(st.c_elem), w = __uint_as_float(st.w_elem);
+  const int ec = (int)(st.c_max >> 23) - 127, ew = (int)(st.w_max >> 23) - 127;
+  const bool ok = ec > -60 && ec < 60 && ew > -60 && ew < 60;
+  key_scale = ok ? 100.f / c : 1.f;
+  w_scale = ok ? 127.f / w : 1.f;
+  return ok && __uint_as_float(st.bias_max) * (key_scale * w_scale) < 2e6f;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -178,7 +206,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
   const int kv = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   double* L = Lmat + (size_t)kv * kD * kD;
-  if (tid == 0) cstat[kv] = CodewordStat{0u, 0u, 0u, 0u};
+  if (tid == 0) cstat[kv] = CodewordStat{};
   if (mode != A2ATS_W_BLOCK) {
     if (tid < kD) sd[(size_t)kv * kD + tid] = mode == A2ATS_W_DIAG ? sqrt((double)weights[(size_t)kv * kD + tid]) : 1.0;
     return;
@@ -306,11 +334,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
   }
   __syncthreads();
-  double c2 = 0.0;
+  double c2 = 0.0, c_elem = 0.0, w_elem = 0.0;
 #pragma unroll
   for (int u = 0; u < kD / 4; ++u) {
     const double x = ((double)cv[u] - (double)s_mu[4 * u + k]) * (double)s_t[4 * u + k];
     c2 += x * x;
+    c_elem = fmax(c_elem, fabs(x));
   }
   auto centred = [&](int u) { return (double)cv[u] - (double)s_mu[4 * u + k]; };
   // register r of tile t: dimension 16 t + 4 r + k of codeword cg
@@ -346,6 +375,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         out[((size_t)kv * kD + 16 * t + 4 * r + k) * kCW + cg] = acc[t][r];
         const double x = balanced ? acc[t][r] * (double)inverse_of_power(s_t[16 * t + 4 * r + k]) : acc[t][r];
         n += x * x;
+        if (balanced) w_elem = fmax(w_elem, fabs(x));
       }
     n += __shfl_xor(n, 16);
     return n + __shfl_xor(n, 32);
@@ -375,20 +405,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     chalf[(size_t)kv * kCW + cg] = 0.5 * z2;
   }
   // rounded up; a float that is not negative orders like its bits
-  uint32_t most[3] = {__float_as_uint(__double2float_ru(0.5 * z2)), __float_as_uint(__double2float_ru(sqrt(w2))),
-                      __float_as_uint(__double2float_ru(sqrt(c2)))};
-  __shared__ uint32_t s_most[4][3];
+  uint32_t most[5] = {__float_as_uint(__double2float_ru(0.5 * z2)), __float_as_uint(__double2float_ru(sqrt(w2))),
+                      __float_as_uint(__double2float_ru(sqrt(c2))), __float_as_uint(__double2float_ru(w_elem)),
+                      __float_as_uint(__double2float_ru(c_elem))};
+  __shared__ uint32_t s_most[4][5];
 #pragma unroll
-  for (int i = 0; i < 3; ++i) {
+  for (int i = 0; i < 5; ++i) {
 #pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) most[i] = max(most[i], (uint32_t)__shfl_xor((int)most[i], off));
+    for (int off = i < 3 ? 8 : 32; off >= 1; off >>= 1) most[i] = max(most[i], (uint32_t)__shfl_xor((int)most[i], off));
     if (lane == 0) s_most[threadIdx.x >> 6][i] = most[i];
   }
   __syncthreads();
-  if (threadIdx.x < 3) {   // (one atomic per workgroup: one per wave, all heads in one cache line, took 100 us)
+  if (threadIdx.x < 5) {   // (one atomic per workgroup: one per wave, all heads in one cache line, took 100 us)
     const int i = threadIdx.x;
     const uint32_t v = max(max(s_most[0][i], s_most[1][i]), max(s_most[2][i], s_most[3][i]));
-    atomicMax(i == 0 ? &cstat[kv].bias_max : (i == 1 ? &cstat[kv].w_max : &cstat[kv].c_max), v);
+    uint32_t* at[5] = {&cstat[kv].bias_max, &cstat[kv].w_max, &cstat[kv].c_max, &cstat[kv].w_elem, &cstat[kv].c_elem};
+    atomicMax(at[i], v);
   }
 }
 
@@ -401,17 +433,24 @@ __global__ __launch_bounds__(512) void encode_single_operands_kernel(const doubl
                                                                      const float* __restrict__ cbias,
                                                                      uint16_t* __restrict__ cfrag,
                                                                      _Float16* __restrict__ f16,
-                                                                     float* __restrict__ fbias,
+                                                                     float* __restrict__ fbias, uint8_t* __restrict__ i8,
+                                                                     int* __restrict__ bias8,
                                                                      CodewordStat* __restrict__ cstat) {
-  __shared__ float s_e[16][32];
+  __shared__ float s_e[16][32], s_e8[16][32];
   const int kv = blockIdx.y, cb = blockIdx.x, tid = threadIdx.x;
   const int row = tid & 31, kt = tid >> 6, g = (tid >> 5) & 1;
   float key_scale, w_scale;
   const bool ok = f16_scales(cstat[kv], key_scale, w_scale);
-  if (cb == 0 && tid < kD) center[kv].key[tid] = center[kv].t[tid] * key_scale;
+  float key_scale8, w_scale8;
+  const bool ok8 = i8_scales(cstat[kv], key_scale8, w_scale8);
+  if (cb == 0 && tid < kD) {
+    center[kv].key[tid] = center[kv].t[tid] * key_scale;
+    center[kv].key8[tid] = center[kv].t[tid] * key_scale8;
+  }
   bf16x8 hi, lo;
   f16x8 h;
-  float err = 0.f;
+  float err = 0.f, err8 = 0.f;
+  uint32_t q8[2] = {0u, 0u};
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const int d = 16 * kt + 8 * g + i;
@@ -423,17 +462,31 @@ __global__ __launch_bounds__(512) void encode_single_operands_kernel(const doubl
     h[i] = (_Float16)(float)x;
     const float r = (float)(x - (double)(float)h[i]);
     err += r * r;
+    const double x8 = neg * (double)w_scale8, n8 = fmin(fmax(rint(x8), -127.0), 127.0);
+    q8[i / 4] |= ((uint32_t)(int)n8 & 255u) << (8 * (i % 4));
+    err8 += (float)(x8 - n8) * (float)(x8 - n8);
   }
   uint16_t* blk = cfrag + ((size_t)kv * kBlocks + cb) * (kFragBytes / 2) + (kt * 64 + row + 32 * g) * 8;
   *(bf16x8*)blk = hi;
   *(bf16x8*)(blk + 8 * 64 * 8) = lo;
   *(f16x8*)(f16 + ((size_t)kv * kBlocks + cb) * (kF16Bytes / 2) + (kt * 64 + row + 32 * g) * 8) = h;
+  *(uint2*)(i8 + ((size_t)kv * kCW + 32 * cb + row) * kD + 16 * kt + 8 * g) = make_uint2(q8[0], q8[1]);
   s_e[2 * kt + g][row] = err;
+  s_e8[2 * kt + g][row] = err8;
   __syncthreads();
   if (tid < 32) {
-    float e2 = 0.f;
+    float e2 = 0.f, e28 = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) e2 += s_e[i][tid];
+    for (int i = 0; i < 16; ++i) {
+      e2 += s_e[i][tid];
+      e28 += s_e8[i][tid];
+    }
+    bias8[(size_t)kv * kCW + 32 * cb + tid] =
+        ok8 ? (int)rint((double)cbias[(size_t)kv * kCW + 32 * cb + tid] * (double)(key_scale8 * w_scale8)) : 0;
+    uint32_t most8 = __float_as_uint(ok8 ? 1.00001f * sqrtf(e28) : NAN);
+#pragma unroll
+    for (int off = 16; off >= 1; off >>= 1) most8 = max(most8, (uint32_t)__shfl_xor((int)most8, off));
+    if (tid == 0) atomicMax(&cstat[kv].w_err8, most8);
     fbias[(size_t)kv * kCW + 32 * cb + tid] = cbias[(size_t)kv * kCW + 32 * cb + tid] * (key_scale * w_scale);
     uint32_t most = __float_as_uint(ok ? 1.00001f * sqrtf(e2) : NAN);   // NaN: no key is decided by the filter
 #pragma unroll
@@ -505,10 +558,307 @@ __device__ __forceinline__ void filter_insert(float a, float b, float c, float d
   asm("v_min3_f32 %0, %1, %2, %3" : "=v"(k2) : "v"(k2), "v"(m0), "v"(m1));
 }
 
+// ------------------------------------------------------------------------------------------
+// The filter in i8: whole numbers of 8 bits, keys and codewords, whose products are exact.  A score is off by at most
+//   e_k max|w| + |q_k| e_w + 3/4          (in units of the two scales; q_k the key's numbers, 3/4 for 1/2 |c^z|^2)
+// and about 50 times as many keys are left open as by the f16 one where keys have several codewords about equally near (of
+// normal keys nearly all), but hardly any where they lie close to one: so some keys of the call say which filter a KV head
+// takes (encode_single_sample_kernel).  The smallest of four scores goes on, with the number of the four in the 9 bits below
+// it; the four are multiplied again at the end, which gives the same whole numbers.
+//
+// A product takes half the time and power of the f16 one, the ranking 17 vector instructions a tile instead of 36.  96001 keys
+// x 8 heads, full matrix, codewords prepared: 713 -> 380 us (the products at 3.0 POP/s while they run, which is what this chip's
+// power leaves of 5; reading and rounding keys, and the four, a quarter of the time); 2000 keys 81 -> 48, 100 57 -> 42.  Keys
+// all of which are undecided pay for the sample: 12000 normal keys x 8 heads 397 -> 403.  With 2 % of the keys open both
+// filters, with their lists, take the same time at 3 to 6 % (0.02: 872 -> 671 us, 0.06: 879 -> 848); kSampleOpen is below that.
+// Tried: eight scores ranked together (13 instructions) and multiplied again 393; a wave of 32 NT keys with NT = 3 and its next
+// keys read and rounded during the products 418.
+// ------------------------------------------------------------------------------------------
+// A lane's 64 dimensions of a key (16 g + 32 kt .. + 16), |k - q|^2 and |q|^2 over them.
+__device__ __forceinline__ void quantise_key(const float* kp, const float* s_mu, const float* s_key, int g, i32x4 (&q)[4],
+                                             float& e2, int& n2) {
+#pragma unroll
+  for (int kt = 0; kt < 4; ++kt) {
+    float4 f[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) f[u] = *(const float4*)(kp + 32 * kt + 4 * u);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int d = 32 * kt + 16 * g + 4 * u;
+      const float4 mu = *(const float4*)&s_mu[d], sc = *(const float4*)&s_key[d];
+      const float v[4] = {(f[u].x - mu.x) * sc.x, (f[u].y - mu.y) * sc.y, (f[u].z - mu.z) * sc.z, (f[u].w - mu.w) * sc.w};
+      uint32_t b[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        constexpr float kRound = 12582912.f;   // 1.5 * 2^23: the sum's last bits are the whole number
+        const float r = __builtin_amdgcn_fmed3f(v[i], -127.f, 127.f) + kRound, e = v[i] - (r - kRound);
+        e2 += e * e;
+        b[i] = __float_as_uint(r);
+      }
+      const uint32_t lo = __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400), hi = __builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400);
+      q[kt][u] = (int)(lo | hi << 16);
+      n2 = __builtin_amdgcn_sdot4(q[kt][u], q[kt][u], n2, false);
+    }
+  }
+}
+
+// By how much two scores may be off together.
+__device__ __forceinline__ float reach8(const CodewordStat& st, float key_scale, float w_scale, float e2, float n2) {
+  const float w_max = __uint_as_float(st.w_max) * w_scale, w_err = __uint_as_float(st.w_err8), kn = sqrtf(n2), ke = sqrtf(e2);
+  return 2.f * (1.00001f * (ke * w_max + kn * w_err) +
+                4e-6f * ((kn + ke) * w_max + __uint_as_float(st.bias_max) * (key_scale * w_scale)) + 1.f);
+}
+
+__device__ __forceinline__ void insert8(int a, int b, int& k1, int& k2) {
+  int m;
+  asm("v_med3_i32 %0, %1, %2, %3" : "=v"(m) : "v"(k1), "v"(a), "v"(b));
+  asm("v_min3_i32 %0, %1, %2, %3" : "=v"(k1) : "v"(k1), "v"(a), "v"(b));
+  k2 = min(k2, m);
+}
+
+// 128 keys of a KV head, evenly spread, against a slice of its codewords: the two smallest scores.
+__global__ __launch_bounds__(kEncThreads) void encode_single_sample_kernel(
+    const float* __restrict__ keys, const Center* __restrict__ center, const uint8_t* __restrict__ i8,
+    const int* __restrict__ bias8, int2* __restrict__ sample, float2* __restrict__ norms, int Hkv, int n_new, long n_rows) {
+  static_assert(kSampleKeys == 32 * kEncWaves, "a wave takes 32 keys");
+  constexpr int kOwn = kBlocks / kSampleSlices;
+  __shared__ __align__(32) float s_mu[kD], s_key[kD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, g = lane >> 5;
+  const int slice = blockIdx.x, kv = blockIdx.y, at = wave * 32 + col;
+  if (tid < kD) {
+    s_mu[tid] = center[kv].mu[tid];
+    s_key[tid] = center[kv].key8[tid];
+  }
+  const uint8_t* blk = i8 + ((size_t)kv * kBlocks + slice * kOwn) * kI8Bytes + col * kD + 16 * g;
+  const int* bias = bias8 + (size_t)kv * kCW + slice * kOwn * 32 + 4 * g;
+  i32x4 a[kOwn][4];
+#pragma unroll
+  for (int i = 0; i < kOwn; ++i)
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) a[i][kt] = *(const i32x4*)(blk + i * kI8Bytes + 32 * kt);
+  __syncthreads();
+  const long row = (2 * at + 1) * n_rows / (2 * kSampleKeys);   // (rows of the KV head: sequence by sequence)
+  const float* kp = keys + (((size_t)(row / n_new) * Hkv + kv) * n_new + row % n_new) * kD + 16 * g;
+  i32x4 q[4];
+  float e2 = 0.f;
+  int n2 = 0, k1 = 0x7fffffff, k2 = 0x7fffffff;
+  quantise_key(kp, s_mu, s_key, g, q, e2, n2);
+#pragma unroll
+  for (int i = 0; i < kOwn; ++i) {
+    i32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int4 b = *(const int4*)(bias + i * 32 + 8 * v);
+      acc[4 * v] = b.x, acc[4 * v + 1] = b.y, acc[4 * v + 2] = b.z, acc[4 * v + 3] = b.w;
+    }
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i][kt], q[kt], acc, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 16; v += 2) insert8(acc[v], acc[v + 1], k1, k2);
+  }
+  const int o1 = __shfl_xor(k1, 32), o2 = __shfl_xor(k2, 32);
+  e2 += __shfl_xor(e2, 32);
+  n2 += __shfl_xor(n2, 32);
+  if (g == 0) {
+    sample[((size_t)kv * kSampleSlices + slice) * kSampleKeys + at] = make_int2(min(k1, o1), min(max(k1, o1), min(k2, o2)));
+    if (slice == 0) norms[(size_t)kv * kSampleKeys + at] = make_float2(e2, (float)n2);
+  }
+}
+
+// Whether the KV head takes the i8 filter; and no counts yet.
+__global__ __launch_bounds__(kSampleKeys) void encode_single_choose_kernel(const CodewordStat* __restrict__ cstat,
+                                                                           const int2* __restrict__ sample,
+                                                                           const float2* __restrict__ norms,
+                                                                           uint32_t* __restrict__ eight,
+                                                                           uint32_t* __restrict__ counter, int n_counter) {
+  const int kv = blockIdx.x, tid = threadIdx.x;
+  for (int i = kv * kSampleKeys + tid; i < n_counter; i += gridDim.x * kSampleKeys) counter[i] = 0;
+  int2 s[kSampleSlices];
+#pragma unroll
+  for (int i = 0; i < kSampleSlices; ++i) s[i] = sample[((size_t)kv * kSampleSlices + i) * kSampleKeys + tid];
+  const float2 n = norms[(size_t)kv * kSampleKeys + tid];
+  int k1 = 0x7fffffff, k2 = 0x7fffffff;
+#pragma unroll
+  for (int i = 0; i < kSampleSlices; ++i) insert8(s[i].x, s[i].y, k1, k2);
+  const CodewordStat st = cstat[kv];
+  float key_scale, w_scale;
+  i8_scales(st, key_scale, w_scale);
+  const int open = __syncthreads_count(!((float)(k2 - k1) > reach8(st, key_scale, w_scale, n.x, n.y)));
+  if (tid == 0) eight[kv] = open <= kSampleOpen ? 1u : 0u;
+}
+
+constexpr int kWaves8[5] = {0, 4, 3, 0, 2};   // per SIMD, of 32 NT keys each
+template <int NT>
+__global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(kWaves8[NT], kWaves8[NT]))) void encode_single_filter8_kernel(
+    const float* __restrict__ keys, const Center* __restrict__ center, const uint8_t* __restrict__ i8,
+    const int* __restrict__ bias8, const uint32_t* __restrict__ eight, const CodewordStat* __restrict__ cstat,
+    uint16_t* __restrict__ codes, uint32_t* __restrict__ near_count, uint32_t* __restrict__ near, int64_t near_cap, int Hkv,
+    int n_new, int pos0, int64_t ctx_stride) {
+  // The codewords go through LDS two blocks at a time (with one the loads are not back when they are wanted).
+  constexpr int kSect = 512 + 16;   // 16 bytes of 32 codewords; a codeword's eight on different banks
+  constexpr int kBlk = 8 * kSect + 128, kBuf = 2 * kBlk;
+  static_assert(kI8Bytes / 16 == kEncThreads, "a thread stages 16 bytes of a block");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, g = lane >> 5;
+  const int bkv = blockIdx.y, kv = bkv % Hkv, seq = bkv / Hkv;
+  const long key_first = ((long)blockIdx.x * kEncWaves + wave) * (32 * NT);
+  if (!eight[kv]) return;   // (uniform)
+  const CodewordStat st = cstat[kv];
+  __shared__ float s_n2[NT][kEncThreads], s_e2[NT][kEncThreads];   // (kept out of the registers for the main loop)
+  __shared__ __align__(32) float s_mu[kD], s_key[kD];
+  __shared__ __align__(16) uint8_t s_mem[2 * kBuf];
+  const float* seq_keys = keys + (size_t)bkv * n_new * kD;
+  if (tid < kD) {
+    s_mu[tid] = center[kv].mu[tid];
+    s_key[tid] = center[kv].key8[tid];
+  }
+  __syncthreads();
+  i32x4 kq[NT][4];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    float e2 = 0.f;
+    int n2 = 0;
+    quantise_key(seq_keys + (size_t)min(key_first + 32 * t + col, (long)n_new - 1) * kD + 16 * g, s_mu, s_key, g, kq[t], e2, n2);
+    s_n2[t][tid] = (float)n2;
+    s_e2[t][tid] = e2;
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  const uint8_t* all = i8 + (size_t)kv * kBlocks * kI8Bytes;
+  const uint8_t* gblk = all + tid * 16;
+  const int* gbias = bias8 + (size_t)kv * kCW + (tid & 63);
+  uint4 p0, p1;
+  int pb;
+  auto request = [&](int step) {
+    step = min(step, kBlocks / 2 - 1);   // the last step loads its blocks once more, unused
+    p0 = *(const uint4*)(gblk + (size_t)step * (2 * kI8Bytes));
+    p1 = *(const uint4*)(gblk + (size_t)step * (2 * kI8Bytes) + kI8Bytes);
+    pb = gbias[step * 64];
+  };
+  auto stage = [&](int step) {
+    uint8_t* dst = s_mem + (step & 1) * kBuf;
+    *(uint4*)(dst + (tid & 7) * kSect + (tid >> 3) * 16) = p0;   // (piece tid % 8 of codeword tid / 8)
+    *(uint4*)(dst + kBlk + (tid & 7) * kSect + (tid >> 3) * 16) = p1;
+    *(int*)(dst + ((tid >> 5) & 1) * kBlk + 8 * kSect + (tid & 31) * 4) = pb;   // several threads write each word, all the same
+  };
+  int k1[NT], k2[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) k1[t] = k2[t] = 0x7fffffff;
+  i32x4 a[4];
+  i32x16 bias;
+  auto read_bias = [&](int cb) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int4 f = *(const int4*)(s_mem + (cb & 3) * kBlk + 8 * kSect + (8 * q + 4 * g) * 4);
+      bias[4 * q] = f.x, bias[4 * q + 1] = f.y, bias[4 * q + 2] = f.z, bias[4 * q + 3] = f.w;
+    }
+  };
+  auto operand = [&](int cb, int kt) { return *(const i32x4*)(s_mem + (cb & 3) * kBlk + (2 * kt + g) * kSect + col * 16); };
+  // registers 4 q .. + 4 of a tile: codewords 32 cb + 8 q + 4 g .. + 4, number 4 cb + q
+  auto least_of = [&](const i32x16& acc, int q, int cb) {
+    uint32_t number = (uint32_t)(4 * cb + q);
+    asm("" : "+s"(number));   // (a scalar of its own, or it is put together on the vector ALU)
+    return (int)((uint32_t)min(min(acc[4 * q], acc[4 * q + 1]), min(acc[4 * q + 2], acc[4 * q + 3])) << 9 | number);
+  };
+  request(0);
+  stage(0);
+  request(1);
+  __syncthreads();
+  read_bias(0);
+#pragma unroll
+  for (int kt = 0; kt < 4; ++kt) a[kt] = operand(0, kt);
+  // (products and the ranking of the tile before in turns, as in the f16 filter)
+  i32x16 acc[2];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[1][v] = 0x3fffff;   // (ranked before the first tile: above any score)
+#pragma unroll 1
+  for (int step = 0; step < kBlocks / 2; ++step) {
+#pragma unroll
+    for (int tile = 0; tile < 2 * NT; ++tile) {
+      const int t = tile % NT, cb = 2 * step + tile / NT;
+      i32x16& now = acc[tile & 1];
+      const i32x16& done = acc[(tile + 1) & 1];
+      const int prev = (t + NT - 1) % NT, prev_cb = t == 0 ? max(cb - 1, 0) : cb;
+      int m0 = 0;
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt) {
+        now = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[kt], kq[t][kt], kt == 0 ? bias : now, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (kt == 1 || kt == 2) {
+          const int la = least_of(done, 2 * kt - 2, prev_cb), lb = least_of(done, 2 * kt - 1, prev_cb);
+          int m;
+          asm("v_med3_i32 %0, %1, %2, %3" : "=v"(m) : "v"(k1[prev]), "v"(la), "v"(lb));
+          asm("v_min3_i32 %0, %1, %2, %3" : "=v"(k1[prev]) : "v"(k1[prev]), "v"(la), "v"(lb));
+          if (kt == 1) m0 = m;
+          else k2[prev] = min(min(k2[prev], m0), m);
+        }
+        if (t == NT - 1) {   // the next block's operand, each part once the last tile has taken it
+          a[kt] = operand(cb + 1, kt);
+          if (kt == 0) {
+            asm volatile("" ::"v"(bias));   // (or the sums take the place of the bias, and both are moved about)
+            read_bias(cb + 1);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (tile == 3 * NT / 2 - 1) {
+        stage(step + 1);   // (its buffer was last read before the barrier of the step before)
+        request(step + 2);
+        __syncthreads();
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; i += 2)
+    insert8(least_of(acc[1], i, kBlocks - 1), least_of(acc[1], i + 1, kBlocks - 1), k1[NT - 1], k2[NT - 1]);
+
+  // The two lane halves of a key column hold disjoint codewords; both multiply the four of the smaller one again, over their
+  // dimensions.
+  float key_scale, w_scale;
+  i8_scales(st, key_scale, w_scale);
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int o1 = __shfl_xor(k1[t], 32), o2 = __shfl_xor(k2[t], 32);
+    const bool own = k1[t] < o1 || (k1[t] == o1 && g == 0);
+    const int m1 = own ? k1[t] : o1, other = min(max(k1[t], o1), min(k2[t], o2)) >> 9;
+    const int c0 = ((m1 & 511) >> 2) * 32 + (m1 & 3) * 8 + (own ? g : 1 - g) * 4;   // the first of the four
+    const uint8_t* src = all + (size_t)c0 * kD + 16 * g;
+    i32x4 w[4][4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt) w[r][kt] = *(const i32x4*)(src + r * kD + 32 * kt);
+    const int4 b = *(const int4*)(bias8 + (size_t)kv * kCW + c0);
+    const int half[4] = {b.x, b.y, b.z, b.w};
+    int best = 0x7fffffff, second = 0x7fffffff, code = c0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      int dot = 0;
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dot = __builtin_amdgcn_sdot4(kq[t][kt][i], w[r][kt][i], dot, false);
+      const int score = half[r] + dot + __shfl_xor(dot, 32);
+      second = min(second, max(best, score));
+      code = score < best ? c0 + r : code;
+      best = min(best, score);
+    }
+    second = min(second, other);
+    const float reach = reach8(st, key_scale, w_scale, s_e2[t][tid] + s_e2[t][tid ^ 32], s_n2[t][tid] + s_n2[t][tid ^ 32]);
+    const long j = key_first + 32 * t + col;
+    if (g == 0 && j < n_new) {
+      codes[(size_t)bkv * ctx_stride + pos0 + j] = (uint16_t)code;
+      if (!((float)(second - best) > reach)) {   // (also where anything is not a number)
+        const uint32_t place = atomicAdd(near_count + kv, 1u);
+        near[(size_t)kv * near_cap + place] = (uint32_t)((size_t)seq * n_new + j);
+      }
+    }
+  }
+}
+
 template <int NT>
 __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void encode_single_filter_kernel(
     const float* __restrict__ keys, const Center* __restrict__ center, const uint8_t* __restrict__ f16,
-    const float* __restrict__ fbias, const CodewordStat* __restrict__ cstat, uint16_t* __restrict__ codes, uint32_t* __restrict__ near_count,
+    const float* __restrict__ fbias, const uint32_t* __restrict__ eight, const CodewordStat* __restrict__ cstat, uint16_t* __restrict__ codes, uint32_t* __restrict__ near_count,
     uint32_t* __restrict__ near, int64_t near_cap, int Hkv, int n_new, int pos0, int64_t ctx_stride) {
   constexpr int kBuf = kF16Bytes + 128, kPieces = kF16Bytes / 16 / kEncThreads;
   __shared__ __align__(16) uint8_t s_mem[2 * kBuf];
@@ -517,11 +867,11 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
   const long key_first = ((long)blockIdx.x * kEncWaves + wave) * (32 * NT);
   const float* seq_keys = keys + (size_t)bkv * n_new * kD;
   const CodewordStat st = cstat[kv];
-  float key_scale, w_scale;
-  f16_scales(st, key_scale, w_scale);
-
   __shared__ float s_n2[NT][kEncThreads], s_e2[NT][kEncThreads];   // (kept out of the registers for the main loop)
   __shared__ __align__(32) float s_mu[kD], s_key[kD];
+  if (eight[kv]) return;   // (uniform)
+  float key_scale, w_scale;
+  f16_scales(st, key_scale, w_scale);
   if (tid < kD) {
     s_mu[tid] = center[kv].mu[tid];
     s_key[tid] = center[kv].key[tid];
@@ -1046,10 +1396,6 @@ __global__ __launch_bounds__(256) void encode_single_recheck_kernel(
   }
 }
 
-__global__ void encode_single_clear_kernel(uint32_t* counter, int n) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) counter[i] = 0;
-}
-
 // The few-key (append) route of a few keys in all: every key is decided by a float64 sweep, its 4096 codewords split
 // over kSlices workgroups (one workgroup would read 4 MB by itself).  With w_c = c (L L^T) the
 // distortion of codeword c is |z|^2 - 2 k . w_c + |c^z|^2, so the sweep minimises
@@ -1318,7 +1664,7 @@ hipError_t launch_encode_single_prepare(const a2ats_dims& d, const float* codebo
   if ((err = hipGetLastError()) != hipSuccess) return err;
   hipLaunchKernelGGL(encode_single_operands_kernel, dim3(kBlocks, d.n_kv_heads), dim3(512), 0, stream,
                      (const double*)(base + w.off_wT), center, (const float*)(base + w.off_cbias), (uint16_t*)(base + w.off_cfrag),
-                     (_Float16*)(base + w.off_f16), (float*)(base + w.off_fbias), cstat);
+                     (_Float16*)(base + w.off_f16), (float*)(base + w.off_fbias), base + w.off_i8, (int*)(base + w.off_bias8), cstat);
   return hipGetLastError();
 }
 
@@ -1405,18 +1751,37 @@ hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_ne
     return err;
 
   const uint32_t n_all = (uint32_t)((size_t)bkv * n_new);
-  hipLaunchKernelGGL(encode_single_clear_kernel, dim3(1), dim3(1024), 0, stream, counter,
-                     (int)(1 + Hkv + Hkv * near_groups(d)));
-  if ((err = hipGetLastError()) != hipSuccess) return err;
+  const int n_counter = (int)(1 + Hkv + Hkv * near_groups(d));
   // Keys per wave: a workgroup reads all codewords whatever its keys, so 128 where that gives about the 512
-  // workgroups that are resident at once, else 64 or 32.
+  // workgroups that are resident at once, else 64 or 32 (8 KV heads, 32 / 64 / 128 a wave, us: 2000 keys 47 / 59 / 87, 12000
+  // 83 / 85 / 89, 20000 122 / 119 / 134, 26000 156 / 152 / 140, 96001 479 / 415 / 395).
   const long waves = (long)bkv * (((long)n_new + 31) / 32);   // (of 32 keys)
   const int nt = waves >= 4L * kEncWaves * 400 ? 4 : (waves >= 2L * kEncWaves * 400 ? 2 : 1);
-  const dim3 grid((n_new + 32 * nt * kEncWaves - 1) / (32 * nt * kEncWaves), bkv), block(kEncThreads);
-#define A2ATS_LAUNCH_FILTER(NT)                                                                                      \
-  hipLaunchKernelGGL(encode_single_filter_kernel<NT>, grid, block, 0, stream, keys, center, (const uint8_t*)(base + w.off_f16), \
-                     (const float*)(base + w.off_fbias), cstat, (uint16_t*)codes, counter + 1, near,                 \
-                     (int64_t)w.near_cap, Hkv, n_new, pos0, d.ctx_stride)
+  const uint8_t *f16 = base + w.off_f16, *i8 = base + w.off_i8;
+  const float* fbias = (const float*)(base + w.off_fbias);
+  const int* bias8 = (const int*)(base + w.off_bias8);
+  uint32_t* eight = (uint32_t*)(base + w.off_eight);
+  int2* sample = (int2*)(base + w.off_sample);
+  float2* norms = (float2*)(base + w.off_norms);
+  hipLaunchKernelGGL(encode_single_sample_kernel, dim3(kSampleSlices, Hkv), dim3(kEncThreads), 0, stream, keys, center, i8,
+                     bias8, sample, norms, Hkv, n_new, (long)d.batch * n_new);
+  if ((err = hipGetLastError()) != hipSuccess) return err;
+  hipLaunchKernelGGL(encode_single_choose_kernel, dim3(Hkv), dim3(kSampleKeys), 0, stream, cstat, sample, norms, eight, counter,
+                     n_counter);
+  if ((err = hipGetLastError()) != hipSuccess) return err;
+  const dim3 block(kEncThreads);
+  auto grid = [&](int tiles) { return dim3((n_new + 32 * tiles * kEncWaves - 1) / (32 * tiles * kEncWaves), bkv); };
+#define A2ATS_LAUNCH_FILTER8(NT)                                                                                        \
+  hipLaunchKernelGGL(encode_single_filter8_kernel<NT>, grid(NT), block, 0, stream, keys, center, i8, bias8, eight, cstat, \
+                     (uint16_t*)codes, counter + 1, near, (int64_t)w.near_cap, Hkv, n_new, pos0, d.ctx_stride)
+  if (nt == 4) A2ATS_LAUNCH_FILTER8(4);
+  else if (nt == 2) A2ATS_LAUNCH_FILTER8(2);
+  else A2ATS_LAUNCH_FILTER8(1);
+#undef A2ATS_LAUNCH_FILTER8
+  if ((err = hipGetLastError()) != hipSuccess) return err;
+#define A2ATS_LAUNCH_FILTER(NT)                                                                                        \
+  hipLaunchKernelGGL(encode_single_filter_kernel<NT>, grid(NT), block, 0, stream, keys, center, f16, fbias, eight, cstat, \
+                     (uint16_t*)codes, counter + 1, near, (int64_t)w.near_cap, Hkv, n_new, pos0, d.ctx_stride)
   if (nt == 4) A2ATS_LAUNCH_FILTER(4);
   else if (nt == 2) A2ATS_LAUNCH_FILTER(2);
   else A2ATS_LAUNCH_FILTER(1);

@@ -140,6 +140,40 @@ def test_single_codebook_codes_are_the_float64_argmin(mode, n_new, batch, kv):
                 assert (lost <= 1e-13 * norm).all(), float((lost / norm).max())
 
 
+@pytest.mark.parametrize("mode", ["none", "block"])
+@pytest.mark.parametrize("n_new,batch,kv", [(10, 1, 1), (97, 2, 3), (13001, 1, 8), (25700, 1, 8)])
+def test_single_codebook_keys_near_their_codewords(n_new, batch, kv, mode):
+    """The i8 filter's 32, 64 and 128 keys a wave, whose last tiles are ragged; some keys halfway between two codewords of one
+    group of four, of one lane and of two, far out, and not finite."""
+    wl = synth.Workload("enc1_near", batch, kv, kv, 128, 1, n_new + 8, 16, 16, seed=n_new, n_centroids=4096)
+    weights, h64 = None, torch.eye(128, dtype=torch.float64, device="cuda").expand(kv, 128, 128)
+    if mode == "block":
+        weights = synth.make_query_second_moment(wl)["h_block"].cuda()
+        h64 = weights.double().reshape(kv, 128, 128)
+    codebook = synth.make_codebook(wl, "cuda")
+    keys = synth.make_encode_keys(wl, n_new, device="cuda")
+    for at, (c, d) in enumerate([(40, 42), (1000, 1016), (3, 4095)]):
+        keys[:, :, n_new - 1 - at] = 0.5 * (codebook[:, 0, c] + codebook[:, 0, d])
+    keys[:, :, 1] *= 300.0
+    keys[:, 0, 2], keys[:, 0, 3] = float("nan"), float("inf")
+    dims = B.make_dims(batch, kv, kv, 128, 1, n_new + 8, n_centroids=4096)
+    got = _single(dims, keys, codebook, weights, B.W_NONE if mode == "none" else B.W_BLOCK, n_new + 8)
+    assert (got[:, 0, 2:4] == 0).all()
+    keys[:, 0, 2:4] = 0.0
+    for h in range(kv):
+        c = codebook[h, 0].double()
+        w = c @ h64[h]
+        half = 0.5 * (w * c).sum(-1)
+        for b in range(batch):
+            k = keys[b, h].double()
+            score = half - k @ w.t()
+            lost = score.gather(1, got[b, h][:, None])[:, 0] - score.min(1).values
+            if h == 0:
+                lost[2:4] = 0.0
+            # (float64 sums of 128 products, of L L^T instead of H)
+            assert (lost <= 1e-13 * (half.max() + k.norm(dim=1) * w.norm(dim=1).max())).all(), float(lost.max())
+
+
 def test_single_codebook_ties_and_values_that_are_not_finite():
     n = 700
     wl = synth.Workload("enc1_ties", 1, 2, 2, 128, 1, n + 8, 16, 16, seed=5, n_centroids=4096)

@@ -84,7 +84,7 @@ typedef __attribute__((ext_vector_type(16))) int i32x16;
 struct alignas(128) CodewordStat {   // (a cache line each: they are filled by atomics)
   uint32_t w_max, c_max, bias_max;   // largest |w / t|, |c t| and 1/2 |c^z|^2, rounded up
   uint32_t w_err;                    // largest |w - f16(w)|, in the scaled units of the f16 operands
-  uint32_t w_elem, c_elem;           // largest magnitude of an element of w / t and of c t, rounded up
+  uint32_t w_elem, c_elem;           // largest magnitude of an element of w / t and of c t
   uint32_t w_err8;                   // largest |w - i8(w)|, in the scaled units of the i8 operands
 };
 
@@ -334,12 +334,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
   }
   __syncthreads();
-  double c2 = 0.0, c_elem = 0.0, w_elem = 0.0;
+  float c2 = 0.f, c_elem = 0.f, w_elem = 0.f;   // (of c only for scales; in float64 the differences would stay live)
 #pragma unroll
   for (int u = 0; u < kD / 4; ++u) {
-    const double x = ((double)cv[u] - (double)s_mu[4 * u + k]) * (double)s_t[4 * u + k];
+    const float x = (cv[u] - s_mu[4 * u + k]) * s_t[4 * u + k];
     c2 += x * x;
-    c_elem = fmax(c_elem, fabs(x));
+    c_elem = fmaxf(c_elem, fabsf(x));
   }
   auto centred = [&](int u) { return (double)cv[u] - (double)s_mu[4 * u + k]; };
   // register r of tile t: dimension 16 t + 4 r + k of codeword cg
@@ -375,7 +375,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         out[((size_t)kv * kD + 16 * t + 4 * r + k) * kCW + cg] = acc[t][r];
         const double x = balanced ? acc[t][r] * (double)inverse_of_power(s_t[16 * t + 4 * r + k]) : acc[t][r];
         n += x * x;
-        if (balanced) w_elem = fmax(w_elem, fabs(x));
+        if (balanced) w_elem = fmaxf(w_elem, fabsf((float)x));
       }
     n += __shfl_xor(n, 16);
     return n + __shfl_xor(n, 32);
@@ -386,6 +386,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   if (mode == A2ATS_W_BLOCK) {
     times(Lmat + (size_t)kv * kD * kD, true);
     z2 = put(czT, false);
+    // (the differences are taken again: kept in float64, they would spill)
+#pragma unroll
+    for (int u = 0; u < kD / 4; ++u) asm volatile("" : "+v"(cv[u]));
     // the distortion is |z|^2 - 2 k . w + |c^z|^2, so scores need no z
     times(heff + (size_t)kv * kD * kD, false);
     w2 = put(wT, true);
@@ -406,8 +409,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
   // rounded up; a float that is not negative orders like its bits
   uint32_t most[5] = {__float_as_uint(__double2float_ru(0.5 * z2)), __float_as_uint(__double2float_ru(sqrt(w2))),
-                      __float_as_uint(__double2float_ru(sqrt(c2))), __float_as_uint(__double2float_ru(w_elem)),
-                      __float_as_uint(__double2float_ru(c_elem))};
+                      __float_as_uint(sqrtf(c2)), __float_as_uint(w_elem), __float_as_uint(c_elem)};
   __shared__ uint32_t s_most[4][5];
 #pragma unroll
   for (int i = 0; i < 5; ++i) {
@@ -419,8 +421,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   if (threadIdx.x < 5) {   // (one atomic per workgroup: one per wave, all heads in one cache line, took 100 us)
     const int i = threadIdx.x;
     const uint32_t v = max(max(s_most[0][i], s_most[1][i]), max(s_most[2][i], s_most[3][i]));
-    uint32_t* at[5] = {&cstat[kv].bias_max, &cstat[kv].w_max, &cstat[kv].c_max, &cstat[kv].w_elem, &cstat[kv].c_elem};
-    atomicMax(at[i], v);
+    CodewordStat* c = cstat + kv;
+    atomicMax(i == 0 ? &c->bias_max : i == 1 ? &c->w_max : i == 2 ? &c->c_max : i == 3 ? &c->w_elem : &c->c_elem, v);
   }
 }
 

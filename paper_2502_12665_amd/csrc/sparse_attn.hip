@@ -65,6 +65,21 @@ static bool attn_whole(const a2ats_dims& d, int top_k, int window, int n_sink, b
   return heads >= (bf16 ? 512 : 768) && full >= 87 && window <= std::max<long>(64, far_rows / (full >= 90 ? 4 : 16));
 }
 
+// Whether a head is one workgroup of 16 waves (attn_block_kernel): every head has a CU, and so few rows that a CU fetches them
+// in about the time of the second launch that is saved.  us, split and merged (256 heads: one workgroup of four waves, where
+// that is what it would be) -> 16 waves:
+//   - bf16, 4 to 64 heads: 32 + 64 rows 7.0 -> 5.8, 128 + 64 7.2 -> 6.2, 256 + 128 8.6 -> 8.0, 128 + 256 8.5 -> 8.5, but
+//     512 + 64 8.0 -> 9.0; 128 heads: 256 + 128 rows 10.5 -> 8.4, 1024 + 128 18.3 -> 16.1; 256 heads: 128 + 64 7.1 -> 6.8,
+//     128 + 256 13.8 -> 9.4, 512 + 256 20.7 -> 17.2, 1024 + 128 24.9 -> 24.1, but 32 + 64 5.5 -> 6.1;
+//   - float32, 4 to 64 heads: 128 + 64 rows 7.8 -> 7.1, 256 + 128 10.4 -> 9.2, but 512 + 64 9.4 -> 11.6; 192 heads: 256 + 128
+//     rows 19.0 -> 14.1, 512 + 256 28.7 -> 22.8; 160 heads: 700 + 64 rows 22.0 -> 21.8, but 1024 + 128 28.5 -> 29.7.
+static bool attn_block(const a2ats_dims& d, int top_k, int window, int n_sink, bool bf16) {
+  const long heads = (long)d.batch * d.n_q_heads;
+  const long rows = (long)n_sink + top_k + window;
+  if (top_k == 0 || heads > 256 || (heads == 256 && rows <= 160)) return false;
+  return rows <= (heads < 96 ? 400 : (bf16 && heads <= 208 ? 1200 : 800));
+}
+
 // A lane's 16-byte piece of a row, kept as loaded (so that rows in flight cost four registers
 // each) and widened to float only when it is used.
 template <typename T> struct RowVec;
@@ -376,6 +391,225 @@ __global__ __launch_bounds__(kAttnThreads) void attn_whole_kernel(A2ATS_ATTN_ARG
   attn_partial_body<T, false, true>(0, prob * G + g, A2ATS_ATTN_PASS, out);
 }
 
+// A head by one workgroup of 16 waves, `win_waves` of which take its window rows and the others the far rows at the same time;
+// the waves are merged in LDS.  For few heads with few rows, which are bound by latency: one chain of loads (indices, rows) and
+// one launch, where the split form has a second one that merges.
+constexpr int kBlockThreads = 1024, kBlockWaves = kBlockThreads / 64;
+constexpr int kBlockRows = 2048;   // most far and window rows of a head (attn_block: 1200)
+
+template <typename T>
+__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void attn_block_kernel(
+    const T* __restrict__ q, const float* __restrict__ q_rot, const T* __restrict__ k_cache, const T* __restrict__ v_cache,
+    const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ topk_count, const float* __restrict__ cos_win,
+    const float* __restrict__ sin_win, const int32_t* __restrict__ seq_lens, int Hq, int Hkv, int ctx_len, int64_t ctx_stride,
+    int top_k, int window, int n_sink, int win_waves, const int32_t* __restrict__ page_table, int page_shift, int pages_per_seq,
+    T* __restrict__ out) {
+  constexpr int LPR = RowVec<T>::LPR, VEC = RowVec<T>::VEC, SLOTS = 64 / LPR, HALF = kD / 2;
+  __shared__ uint32_t s_row[kBlockRows];   // row numbers in the cache (or pool): far rows, then window rows
+  __shared__ float s_m[kBlockWaves], s_l[kBlockWaves], s_acc[kBlockWaves][kD];
+  const int G = Hq / Hkv;
+  int prob, hg;
+  xcd_map(blockIdx.x, G, (int)(gridDim.x / G), prob, hg);
+  const int bh = prob * G + hg, b = prob / Hkv, kv = prob % Hkv;
+  const int tid = threadIdx.x, lane = tid & 63, slot = lane / LPR, sub = lane % LPR;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // (all of the head's indices are requested before it is known how many count)
+  const int32_t* idx = topk_idx + (size_t)bh * top_k;
+  constexpr int PER = kBlockRows / kBlockThreads;
+  int32_t pos[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) pos[i] = idx[min(tid + i * kBlockThreads, top_k - 1)];
+  const int d0 = sub * VEC;
+  const size_t qb = (size_t)bh * kD;
+  const SeqRange sr = seq_range(ctx_len, seq_lens, b, window, n_sink, top_k);
+  const int cnt = max(0, min(min(topk_count[bh], top_k), sr.ncand));
+  const int n_far = sr.sink_end + cnt, n_win = sr.n - sr.win_start;
+  const int32_t* pages = page_table ? page_table + (size_t)b * pages_per_seq : nullptr;
+  auto put = [&](int at, int j) {
+    j = min(max(j, 0), sr.n - 1);   // a bad caller index must not leave the cache
+    s_row[at] = pages ? (((uint32_t)pages[j >> page_shift] * (uint32_t)Hkv + (uint32_t)kv) << page_shift) +
+                            (uint32_t)(j & ((1 << page_shift) - 1))
+                      : (uint32_t)j;
+  };
+  // (host: n_sink + top_k + window <= kBlockRows)
+  if (tid < sr.sink_end) put(tid, tid);
+  for (int i = tid + kBlockThreads; i < sr.sink_end; i += kBlockThreads) put(i, i);
+#pragma unroll
+  for (int i = 0; i < PER; ++i)
+    if (tid + i * kBlockThreads < cnt) put(sr.sink_end + tid + i * kBlockThreads, pos[i]);
+  for (int i = tid; i < n_win; i += kBlockThreads) put(n_far + i, sr.win_start + i);
+  __syncthreads();
+
+  // Logits are kept by log2 e, so that a weight is one exponential of a difference, without a product that is rounded once more.
+  const float scale = 0.12751743f;   // log2(e) / sqrt(128)
+  auto power = [](float x) { return __builtin_amdgcn_exp2f(x); };
+  auto merge = [&](float& m, float& l, float (&o)[VEC], float m2, float l2, const float (&o2)[VEC]) {
+    const float mm = fmaxf(m, m2);
+    if (mm == -INFINITY) return;
+    const float s1 = power(m - mm), s2 = power(m2 - mm);
+    l = l * s1 + l2 * s2;
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) o[v] = o[v] * s1 + o2[v] * s2;
+    m = mm;
+  };
+  const size_t seq_base = page_table ? 0 : (size_t)prob * ctx_stride * kD;
+  const T* kb = k_cache + seq_base + d0;
+  const T* vb = v_cache + seq_base + d0;
+  float m_run = -INFINITY, l_run = 0.f, acc[VEC];
+#pragma unroll
+  for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
+  // (float32: links of 8 rows, see attn_partial_body)
+  constexpr bool LINKS = VEC == 4;
+  float m_sum = -INFINITY, l_sum = 0.f, acc_sum[VEC];
+#pragma unroll
+  for (int v = 0; v < VEC; ++v) acc_sum[v] = 0.f;
+  auto end_link = [&]() {
+    merge(m_sum, l_sum, acc_sum, m_run, l_run, acc);
+    m_run = -INFINITY;
+    l_run = 0.f;
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
+  };
+  auto absorb = [&](float dot, const uint4& vraw) {
+    dot = row16_sum(dot);
+    if (LPR == 32) dot += __shfl_xor(dot, 16);
+    float vr[VEC];
+    RowVec<T>::widen(vraw, vr);
+    const float logit = dot * scale;
+    const float mn = fmaxf(m_run, logit);
+    const float alpha = power(m_run - mn), pr = power(logit - mn);
+    l_run = l_run * alpha + pr;
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) acc[v] = acc[v] * alpha + pr * vr[v];
+    m_run = mn;
+  };
+  const int far_waves = kBlockWaves - win_waves;
+  if (wv < far_waves) {
+    if (n_far > 0) {   // (uniform)
+      constexpr int U = 4;
+      const int rb = far_waves * SLOTS, step = rb * U, first = wv * SLOTS + slot;
+      float q_far[VEC];
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) q_far[v] = q_rot[qb + d0 + v];
+      uint4 ka[U], va[U], kc[U], vc[U];
+      auto load_set = [&](int i0, uint4 (&kr)[U], uint4 (&vr)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const uint32_t row = s_row[min(i0 + u * rb, n_far - 1)];
+          kr[u] = RowVec<T>::load(kb + (size_t)row * kD);
+          vr[u] = RowVec<T>::load(vb + (size_t)row * kD);
+        }
+      };
+      auto use_set = [&](int i0, const uint4 (&kr)[U], const uint4 (&vr)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          float kf[VEC];
+          RowVec<T>::widen(kr[u], kf);
+          float dot = 0.f;
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) dot += q_far[v] * kf[v];
+          if (i0 + u * rb < n_far) absorb(dot, vr[u]);
+        }
+      };
+      load_set(first, ka, va);
+#pragma unroll 1
+      for (int base = 0; base < n_far; base += 2 * step) {
+        load_set(base + step + first, kc, vc);
+        use_set(base + first, ka, va);
+        load_set(base + 2 * step + first, ka, va);
+        use_set(base + step + first, kc, vc);
+        if (LINKS) end_link();   // (eight rows of a slot each time)
+      }
+    }
+  } else if (n_win > 0) {
+    constexpr int U = 2;
+    const int rb = win_waves * SLOTS;
+    const bool low_half = d0 < HALF;
+    const int dp = low_half ? d0 + HALF : d0 - HALF;
+    const float sgn = low_half ? -1.f : 1.f;
+    float q_own[VEC], q_par[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+      q_own[v] = load_elem(q + qb + d0 + v);
+      q_par[v] = load_elem(q + qb + dp + v) * sgn;
+    }
+#pragma unroll 1
+    for (int i0 = (wv - far_waves) * SLOTS + slot, turn = 0; i0 - slot < n_win; i0 += rb * U, ++turn) {
+      uint4 kr[U], vr[U];
+      float cw[U][VEC], sw[U][VEC];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = min(i0 + u * rb, n_win - 1);
+        const uint32_t row = s_row[n_far + i];
+        kr[u] = RowVec<T>::load(kb + (size_t)row * kD);
+        vr[u] = RowVec<T>::load(vb + (size_t)row * kD);
+        const int delta = min(max(n_win - 1 - i, 0), window - 1);
+        const float* cp = cos_win + (size_t)delta * HALF + (d0 & (HALF - 1));
+        const float* sp = sin_win + (size_t)delta * HALF + (d0 & (HALF - 1));
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+          cw[u][v] = cp[v];
+          sw[u][v] = sp[v];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        float kf[VEC];
+        RowVec<T>::widen(kr[u], kf);
+        float dot = 0.f;
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) dot += (q_own[v] * cw[u][v] + q_par[v] * sw[u][v]) * kf[v];
+        if (i0 + u * rb < n_win) absorb(dot, vr[u]);
+      }
+      if (LINKS && turn % 4 == 3) end_link();   // (two rows of a slot each time)
+    }
+  }
+  if (LINKS) {
+    end_link();
+    m_run = m_sum;
+    l_run = l_sum;
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) acc[v] = acc_sum[v];
+  }
+#pragma unroll
+  for (int off = LPR; off < 64; off <<= 1) {
+    const float m2 = __shfl_xor(m_run, off), l2 = __shfl_xor(l_run, off);
+    float a2[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) a2[v] = __shfl_xor(acc[v], off);
+    merge(m_run, l_run, acc, m2, l2, a2);
+  }
+  // All waves take the head's maximum and scale what they have; then it is only added up.
+  if (lane == 0) s_m[wv] = m_run;
+  __syncthreads();
+  float mm = s_m[0];
+#pragma unroll
+  for (int w = 1; w < kBlockWaves; ++w) mm = fmaxf(mm, s_m[w]);
+  const float f = mm == -INFINITY ? 0.f : power(m_run - mm);   // (2^-inf = 0 for a wave without rows)
+  if (lane < LPR) {
+    if (lane == 0) s_l[wv] = l_run * f;
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) s_acc[wv][d0 + v] = acc[v] * f;
+  }
+  __syncthreads();
+  if (tid < kD) {
+    float l[kBlockWaves], o[kBlockWaves];
+#pragma unroll
+    for (int w = 0; w < kBlockWaves; ++w) {
+      l[w] = s_l[w];
+      o[w] = s_acc[w][tid];
+    }
+#pragma unroll
+    for (int n = kBlockWaves / 2; n >= 1; n /= 2)   // (pairs of pairs: 192 heads, 500 + 256 rows of float32 2.0 -> 1.73e-7 off; the split form 1.77)
+#pragma unroll
+      for (int w = 0; w < n; ++w) {
+        l[w] += l[w + n];
+        o[w] += o[w + n];
+      }
+    store_elem(out + qb + tid, l[0] > 0.f ? o[0] / l[0] : 0.f);
+  }
+}
+
 // ------------------------------------------------------------------------------------------
 // One selection per KV head, bf16 cache: the far rows (sinks + retrieved) of a KV head are the same
 // for its G query heads, so q~ K^T is a real (if thin) matrix product: G x 128 times 128 x rows.
@@ -685,6 +919,14 @@ static hipError_t launch_attn_t(const a2ats_dims& d, const AttnPlan& plan, const
                          (const uint16_t*)k_cache, (const uint16_t*)v_cache, topk_idx, topk_count, cos_win, sin_win,
                          seq_lens, (float*)ws, d.n_q_heads, d.n_kv_heads, d.ctx_len, d.ctx_stride, top_k, window,
                          n_sink, plan.n_far, plan.n_win, page_table, page_shift, pages_per_seq, problems);
+  } else if (!shared && attn_block(d, top_k, window, n_sink, std::is_same<T, uint16_t>::value)) {
+    const long far = std::min<long>((long)n_sink + top_k, d.ctx_len), win = 2l * std::min(window, d.ctx_len);
+    const int win_waves = std::min(kBlockWaves - 1, std::max(1, (int)((kBlockWaves * win + (far + win) / 2) / (far + win))));
+    hipLaunchKernelGGL((attn_block_kernel<T>), dim3(heads), dim3(kBlockThreads), 0, stream, (const T*)q, q_rot,
+                       (const T*)k_cache, (const T*)v_cache, topk_idx, topk_count, cos_win, sin_win, seq_lens, d.n_q_heads,
+                       d.n_kv_heads, d.ctx_len, d.ctx_stride, top_k, window, n_sink, win_waves, page_table, page_shift,
+                       pages_per_seq, (T*)out);
+    return hipGetLastError();
   } else if (!shared && attn_whole(d, top_k, window, n_sink, std::is_same<T, uint16_t>::value)) {
     hipLaunchKernelGGL((attn_whole_kernel<T>), dim3(heads), dim3(kAttnThreads), 0, stream, (const T*)q, q_rot,
                        (const T*)k_cache, (const T*)v_cache, topk_idx, topk_count, cos_win, sin_win, seq_lens, (float*)ws,

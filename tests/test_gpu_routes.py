@@ -330,6 +330,51 @@ def test_float32_attention_of_many_heads_is_as_exact_as_that_of_few(N, K, w, n_s
     assert whole <= 1.1 * few and few < 4e-7
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("Bn,G,Hkv,N,K,w,n_sink,lens", [
+    (1, 4, 1, 500, 1, 1, 0, None),                    # a row of each kind
+    (2, 7, 2, 900, 336, 60, 4, [900, 3]),             # the most rows of few heads; a sequence shorter than its window
+    (3, 8, 4, 2500, 680, 120, 0, [2500, 70, 1]),      # the most of 96 (float32); no candidates
+    (16, 4, 4, 1000, 30, 131, 4, None),               # 256 heads; window rows the most
+    (3, 8, 4, 2500, 1140, 56, 4, None),               # the most of bf16
+    (2, 4, 2, 600, 100, 0, 0, None),                  # no window
+])
+def test_attention_of_few_rows_by_one_workgroup(Bn, G, Hkv, N, K, w, n_sink, lens, dtype):
+    """Few rows a head: a workgroup of 16 waves takes them all.  Against float64; other sequences of the batch do not matter."""
+    wl = synth.Workload("block", Bn, Hkv * G, Hkv, 128, 16, N, K, w, n_sink=n_sink, kv_dtype=dtype, seed=N + K)
+    xd = synth.make_decode_inputs(wl, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(N)
+    lens = lens or [N] * Bn
+    idx = torch.zeros(Bn, Hkv * G, K, dtype=torch.int32, device="cuda")
+    count = torch.zeros(Bn, Hkv * G, dtype=torch.int32, device="cuda")
+    for b, n in enumerate(lens):
+        start = max(n - w, 0)
+        c = max(min(K, start - n_sink), 0)
+        if c:
+            pick = torch.rand(Hkv * G, start - n_sink, generator=g, device="cuda").topk(c, -1).indices
+            idx[b, :, :c] = (torch.sort(pick, -1).values + n_sink).to(torch.int32)
+        count[b] = c
+    st = B.DecodeState(H.dims_of(wl), K, w, n_sink, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
+    st.out.fill_(7.0)
+    B.sparse_attn(st.dims, xd["q"], xd["q"].float().contiguous(), xd["k"], xd["v"], idx, count, K, w, n_sink, st.cos_win,
+                  st.sin_win, torch.tensor(lens, dtype=torch.int32, device="cuda"), st.out, st.ws)
+    torch.cuda.synchronize()
+    # a bfloat16 output has 8 significant bits; float32: 1200 products and sums of values of size 1
+    tol = 2.0 ** -8 if dtype == "bf16" else 2e-6
+    for b, n in enumerate(lens):
+        start = max(n - w, 0)
+        back = torch.arange(n - start - 1, -1, -1, device="cuda")
+        cos, sin = st.cos_win.double()[back], st.sin_win.double()[back]
+        for h in range(Hkv * G):
+            k, v, q = xd["k"][b, h // G].double(), xd["v"][b, h // G].double(), xd["q"][b, h].double()
+            far = torch.cat([torch.arange(min(n_sink, start), device="cuda"), idx[b, h, :int(count[b, h])].long()])
+            turned = torch.cat([q[:64] * cos - q[64:] * sin, q[64:] * cos + q[:64] * sin], 1)
+            logit = torch.cat([k[far] @ q, (turned * k[start:n]).sum(1)]) * 128 ** -0.5
+            want = torch.softmax(logit, 0) @ torch.cat([v[far], v[start:n]])
+            got = st.out[b, h].double()
+            assert ((got - want).abs() <= tol * want.abs() + 2e-6).all(), (b, h, float((got - want).abs().max()))
+
+
 @pytest.mark.parametrize("Bn,G,Hkv,N,K,w,n_sink,n_new,lens,stride,data", [
     (1, 4, 1, 4096 + 16, 100, 16, 0, 1, None, 0, None),          # one head a workgroup, exactly one chunk of 4096
     (1, 4, 1, 4097 + 16, 100, 16, 0, 2, None, 8, None),          # and one token more

@@ -562,8 +562,8 @@ __global__ __launch_bounds__(kLutThreads) void decode_select_head_kernel(
     if (os) os[t] = 0.f;
   }
   if (sr.kk > 0)   // (uniform)
-    exact_select_block<M, false, true>(seq_codes_of<M>(codes, CodePages{nullptr, 0, 0}, b, kv, Hkv, ctx_stride), nullptr, base,
-                                       top, scale, sr, oi, os, tbl, L);
+    exact_select_sized<M, true>(seq_codes_of<M>(codes, CodePages{nullptr, 0, 0}, b, kv, Hkv, ctx_stride), nullptr, base, top,
+                                scale, sr, oi, os, tbl, L);
   if (folded)   // (see decode_prologue_kernel)
     encode_few_block<DS>((int)blockIdx.x, sweeps, keys, codebook, weights, mode, codes, B, Hkv, n_new, pos0, ctx_stride);
 }

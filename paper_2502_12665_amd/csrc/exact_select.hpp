@@ -137,7 +137,8 @@ __device__ __forceinline__ void count_shared_bins(uint32_t* hist, uint32_t bin, 
 // Requires sr.kk >= 1.
 // TIES: many rows are expected to have one score, and s_lo and s_hi are bounds of the K-th; out_score is not written.
 // TABLE_IN_LDS: the caller has put the head's table at `tbl` (a barrier follows here).
-template <int M, bool TIES = false, bool TABLE_IN_LDS = false>
+// ROWS: most rows per thread that stay in registers.
+template <int M, bool TIES = false, bool TABLE_IN_LDS = false, int ROWS = kKeepRows>
 __device__ void exact_select_block(const SeqCodes& seq_codes,
                                    const int32_t* __restrict__ head_table,
                                    int32_t s_lo, int32_t s_hi, float scale,
@@ -166,18 +167,30 @@ __device__ void exact_select_block(const SeqCodes& seq_codes,
   // and the emission agree on one order, so that exactly kk winners are written whatever it is worth.
   const uint32_t k_lo = score_key(s_lo), range = score_key(s_hi) - k_lo;
   const uint32_t in_range = range == 0u ? 0u : ~0u >> __clz(range);
-  auto relative_key = [&](int j) {
-    const int32_t score = score_exact_row<M>(row_ptr<M>(seq_codes, j), tbl, sw);
-    return (score_key(TIES ? min(max(score, s_lo), s_hi) : score) - k_lo) & in_range;
-  };
+  auto key_of = [&](int32_t score) { return (score_key(TIES ? min(max(score, s_lo), s_hi) : score) - k_lo) & in_range; };
+  auto relative_key = [&](int j) { return key_of(score_exact_row<M>(row_ptr<M>(seq_codes, j), tbl, sw)); };
   // Up to kKeep rows per thread (16384 candidates: every shape that takes this route for its length)
   // are scored once and their relative keys kept in registers; the select levels and the emission
   // then work on those instead of streaming and scoring the rows again (4 passes at 4096 tokens:
   // 23 us).  Thread t owns rows lo + t + i NT, the order of the streaming loops below.
-  constexpr int kKeep = kKeepRows;
+  constexpr int kKeep = ROWS;
   const bool resident = hi - lo <= kKeep * NT;   // (uniform)
   uint32_t keys[kKeep];
-  if (resident) {
+  if (resident && kKeep * M <= 128) {   // all rows are requested before the first is scored
+    uint4 w[kKeep][M / 16];
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i) {
+      const uint4* row = (const uint4*)row_ptr<M>(seq_codes, min(lo + tid + i * NT, hi - 1));
+#pragma unroll
+      for (int qd = 0; qd < M / 16; ++qd) w[i][qd] = row[qd];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i) {
+      const uint32_t key = key_of(score_exact<M>(w[i], tbl, sw));
+      keys[i] = lo + tid + i * NT < hi ? key : 0u;
+    }
+  } else if (resident) {
 #pragma unroll
     for (int i = 0; i < kKeep; ++i) {
       const int j = lo + tid + i * NT;
@@ -330,6 +343,21 @@ __device__ void exact_select_block(const SeqCodes& seq_codes,
 #pragma unroll 1
     for (int base = lo; base < hi && !done; base += NT) emit_round(base, done);
   }
+}
+
+// The same by as many rounds of rows as the sequence needs: rounds that hold none take their time all the same, in the scans
+// above all, and where there are few, all are requested at once (4 heads of 4096 candidates in decode_select_head_kernel 16.4
+// -> 12.7 us, 32 of 6370 with M = 32 21.9 -> 19.5).
+template <int M, bool TABLE_IN_LDS>
+__device__ __forceinline__ void exact_select_sized(const SeqCodes& seq_codes, const int32_t* head_table, int32_t s_lo,
+                                                   int32_t s_hi, float scale, const SeqRange& sr, int32_t* out_idx,
+                                                   float* out_score, unsigned char* tbl, ExactLds& L) {
+  if (sr.ncand <= 4 * kExactThreads)   // (uniform)
+    exact_select_block<M, false, TABLE_IN_LDS, 4>(seq_codes, head_table, s_lo, s_hi, scale, sr, out_idx, out_score, tbl, L);
+  else if (sr.ncand <= 8 * kExactThreads)
+    exact_select_block<M, false, TABLE_IN_LDS, 8>(seq_codes, head_table, s_lo, s_hi, scale, sr, out_idx, out_score, tbl, L);
+  else
+    exact_select_block<M, false, TABLE_IN_LDS>(seq_codes, head_table, s_lo, s_hi, scale, sr, out_idx, out_score, tbl, L);
 }
 
 }  // namespace a2ats

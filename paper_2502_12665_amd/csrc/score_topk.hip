@@ -218,9 +218,9 @@ __global__ __launch_bounds__(kExactThreads) void select_exact_kernel(
   if (sr.kk == 0) return;
   const LutLayout lay = lut_layout(B, Hq, Hkv, M);
   const int32_t* meta = lut + lay.off_meta + (size_t)bh * 4;
-  exact_select_block<M>(seq_codes_of<M>(codes, pg, b, kv, Hkv, ctx_stride),
-                        lut + lay.off_exact + (size_t)bh * (kCentroids * M), meta[0], meta[2], lut_scale[bh], sr, oi, os,
-                        dyn_lds, L);
+  exact_select_sized<M, false>(seq_codes_of<M>(codes, pg, b, kv, Hkv, ctx_stride),
+                               lut + lay.off_exact + (size_t)bh * (kCentroids * M), meta[0], meta[2], lut_scale[bh], sr, oi, os,
+                               dyn_lds, L);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -316,19 +316,19 @@ def single_codebook_encode_prefill(args, torch, B, synth, wl):
     ms = (time.perf_counter() - t0) * 1e3 / steps
     flop = n_keys * 4096.0 * 128.0 * 2.0           # the contraction [keys x 128] . [128 x 4096]
     achieved = flop / (ms * 1e-3) / 1e12
-    peak = 2500.0                                  # dense bf16 matrix-core peak, TFLOP/s
+    peak = 5000.0                                  # dense 8-bit matrix-core peak, Top/s (keys near their codewords take it)
     print(json.dumps({
         "metric": "encoded keys/s (prefill-side query-aware key encoding, one codebook of 4096, full D x D matrix H)",
         "value": n_keys / (ms * 1e-3), "unit": "keys/s", "n_gpus": 1, "steps": steps, "warmup": warmup,
         "ms_per_step": ms, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "f16 products with f32 accumulate; bf16 hi/lo products, then f64, where they cannot decide",
+        "dtype": "i8 products with i32 accumulate; bf16 hi/lo products, then f64, where they cannot decide",
         "data": "synthetic",
         "config": {"workload": wl.name + " encode", "keys": n_keys, "codewords": 4096, "weights": "W_BLOCK"},
-        "roofline": {"kernel": "encode_single_filter_kernel (+ factor, codeword, listed-key and re-check kernels)",
+        "roofline": {"kernel": "encode_single_filter8_kernel (+ factor, codeword, sample, listed-key and re-check kernels)",
                      "bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak, "traffic": None,
-                     "executed_f16_TFLOPs": achieved, "executed_frac": achieved / peak,
-                     "note": "algorithmic flops; each term takes one f16 product, the keys it leaves open three bf16 ones"},
+                     "executed_i8_TOPs": achieved, "executed_frac": achieved / peak,
+                     "note": "algorithmic operations; each term takes one 8-bit product, the keys it leaves open three bf16 ones"},
     }))
 
 
@@ -600,14 +600,15 @@ def codebook_fit(args, torch, B, synth, wl):
                   "step; plus one second-moment accumulation)",
         "value": n_keys / (ms * 1e-3), "unit": "keys/s", "n_gpus": 1, "steps": steps, "warmup": warmup,
         "ms_per_step": ms, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "assignment: f16 products, bf16 hi/lo products, then f64, where they cannot decide; f64 sums for means "
-                 "and moments",
+        "dtype": "assignment: i8 or f16 products, bf16 hi/lo products, then f64, where they cannot decide; f64 sums for "
+                 "means and moments",
         "data": "synthetic",
         "config": {"workload": wl.name + " codebook construction", "keys": n_keys, "codewords": wl.n_centroids,
                    "query_rows": N * wl.n_q_heads},
         "phase_ms_median": {"assign": ph[0], "centroid_step": ph[1], "second_moment": ph[2]},
         "kmeanspp_seed_ms": {"keys_per_kv_head": wl.batch * n_seed, "ms": seed_ms},
-        "roofline": {"kernel": "encode_single_filter_kernel (+ factor, codeword, listed-key and re-check kernels)",
+        "roofline": {"kernel": "encode_single_filter8_kernel or encode_single_filter_kernel (+ factor, codeword, sample, "
+                               "listed-key and re-check kernels)",
                      "bound": "mfma", "achieved": flop / (ph[0] * 1e-3) / 1e12, "peak": 2500.0, "unit": "TFLOP/s",
                      "frac": flop / (ph[0] * 1e-3) / 1e12 / 2500.0,
                      "traffic": None, "note": "algorithmic flops of the assignment over its whole call"},

@@ -569,8 +569,8 @@ __device__ __forceinline__ void filter_insert(float a, float b, float c, float d
 // it; the four are multiplied again at the end, which gives the same whole numbers.
 //
 // A product takes half the time and power of the f16 one, the ranking 17 vector instructions a tile instead of 36.  96001 keys
-// x 8 heads, full matrix, codewords prepared: 713 -> 380 us (the products at 3.0 POP/s while they run, which is what this chip's
-// power leaves of 5; reading and rounding keys, and the four, a quarter of the time); 2000 keys 81 -> 48, 100 57 -> 42.  Keys
+// x 8 heads, full matrix, codewords prepared: 707 -> 377 us (the products at 3.0 POP/s while they run, which is what this chip's
+// power leaves of 5; reading and rounding keys, and the four, a quarter of the time); 2000 keys 81 -> 45, 100 57 -> 39.  Keys
 // all of which are undecided pay for the sample: 12000 normal keys x 8 heads 397 -> 403.  With 2 % of the keys open both
 // filters, with their lists, take the same time at 3 to 6 % (0.02: 872 -> 671 us, 0.06: 879 -> 848); kSampleOpen is below that.
 // Tried: eight scores ranked together (13 instructions) and multiplied again 393; a wave of 32 NT keys with NT = 3 and its next

@@ -921,7 +921,8 @@ static hipError_t launch_attn_t(const a2ats_dims& d, const AttnPlan& plan, const
                          n_sink, plan.n_far, plan.n_win, page_table, page_shift, pages_per_seq, problems);
   } else if (!shared && attn_block(d, top_k, window, n_sink, std::is_same<T, uint16_t>::value)) {
     const long far = std::min<long>((long)n_sink + top_k, d.ctx_len), win = 2l * std::min(window, d.ctx_len);
-    const int win_waves = std::min(kBlockWaves - 1, std::max(1, (int)((kBlockWaves * win + (far + win) / 2) / (far + win))));
+    const long all = std::max(1l, far + win);   // (an empty context has no rows)
+    const int win_waves = std::min(kBlockWaves - 1, std::max(1, (int)((kBlockWaves * win + all / 2) / all)));
     hipLaunchKernelGGL((attn_block_kernel<T>), dim3(heads), dim3(kBlockThreads), 0, stream, (const T*)q, q_rot,
                        (const T*)k_cache, (const T*)v_cache, topk_idx, topk_count, cos_win, sin_win, seq_lens, d.n_q_heads,
                        d.n_kv_heads, d.ctx_len, d.ctx_stride, top_k, window, n_sink, win_waves, page_table, page_shift,

@@ -5,6 +5,8 @@ import itertools
 import math
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -303,6 +305,45 @@ def test_static_scratch_entry_point_refuses_what_does_not_fit(binding):
     assert call(huge, top_k=-1) == -1
     assert call(binding.make_dims(1, 4, 3, 128, 16, 64)) == -1
 
+
+
+def test_attention_over_an_empty_context_reaches_its_launches(binding, tmp_path):
+    """ctx_len = 0 is a valid context: the host's shares of rows must come out without one to divide by.  The launches go to
+    stubs that count them, in a process of its own, which a fault of the host arithmetic would end."""
+    stub = tmp_path / "launches.c"
+    stub.write_text("""
+typedef struct { unsigned x, y, z; } dim3_;
+int launches;
+int __hipPushCallConfiguration(dim3_ g, dim3_ b, unsigned long lds, void* s) { return 0; }
+int __hipPopCallConfiguration(dim3_* g, dim3_* b, unsigned long* lds, void** s) {
+  *g = *b = (dim3_){1, 1, 1}; *lds = 0; *s = 0; return 0;
+}
+int hipLaunchKernel(const void* f, dim3_ g, dim3_ b, void** args, unsigned long lds, void* s) { ++launches; return 0; }
+int hipGetLastError(void) { return 0; }
+""")
+    lib = tmp_path / "launches.so"
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", str(lib), str(stub)], check=True)
+    code = """
+import ctypes, sys
+stub = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)   # (before the library, whose calls go to what is found first)
+from paper_2502_12665_amd import binding as B
+L, one, null = B.lib(), ctypes.c_void_p(4096), ctypes.c_void_p(0)
+launches = ctypes.c_int.in_dll(stub, "launches")
+for heads, top_k, window, n_sink in ((4, 16, 16, 0), (4, 100, 100, 4), (128, 512, 128, 0), (256, 256, 128, 0), (4, 16, 0, 0),
+                                     (4, 0, 16, 0), (512, 64, 64, 4)):
+    for dtype in (0, 1):
+        for stride in (0, 64):
+            d = B.make_dims(1, heads, heads // 4, 128, 16, 0, stride)
+            tail = (one, one, top_k, window, n_sink, one, one, null, one, one, 1 << 30, null)
+            for call in (lambda: L.a2ats_sparse_attn(ctypes.byref(d), one, one, one, one, dtype, *tail),
+                         lambda: L.a2ats_sparse_attn_paged(ctypes.byref(d), one, one, one, one, dtype, one, 16, *tail),
+                         lambda: L.a2ats_sparse_attn_shared(ctypes.byref(d), one, one, one, one, dtype, *tail)):
+                before = launches.value
+                assert call() == 0 and launches.value > before
+print("reached")
+"""
+    run = subprocess.run([sys.executable, "-c", code, str(lib)], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert run.returncode == 0 and "reached" in run.stdout, (run.returncode, run.stderr[-2000:])
 
 
 def test_paged_code_entry_points_check_their_arguments(binding):

@@ -375,6 +375,30 @@ def test_attention_of_few_rows_by_one_workgroup(Bn, G, Hkv, N, K, w, n_sink, len
             assert ((got - want).abs() <= tol * want.abs() + 2e-6).all(), (b, h, float((got - want).abs().max()))
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("Hkv,K,w", [(1, 16, 16), (2, 0, 16), (64, 256, 100), (128, 64, 64)])
+def test_attention_over_an_empty_context_gives_zeros(Hkv, K, w, dtype):
+    """ctx_len = 0 in a cache that has room for more, through every per-head call."""
+    heads = 4 * Hkv
+    cache = torch.ones(1, Hkv, 32, 128, dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device="cuda")
+    dims = B.make_dims(1, heads, Hkv, 128, 16, 0, 32)
+    st = B.DecodeState(dims, K, w, 0, cache.dtype, synth.inv_freq(128, 10000.0), 1)
+    q = torch.ones(1, heads, 128, dtype=cache.dtype, device="cuda")
+    q_rot = q.float().contiguous()
+    idx = torch.zeros(1, heads, max(K, 1), dtype=torch.int32, device="cuda")
+    count = torch.full((1, heads), K, dtype=torch.int32, device="cuda")
+    pool, table = cache.reshape(1, Hkv, 2, 16, 128).transpose(1, 2).reshape(2, Hkv, 16, 128).contiguous(), torch.tensor(
+        [[0, 1]], dtype=torch.int32, device="cuda")
+    tail = (idx, count, K, w, 0, st.cos_win, st.sin_win, None, st.out)
+    for call in (lambda: B.sparse_attn(dims, q, q_rot, cache, cache, *tail, st.ws),
+                 lambda: B.sparse_attn_static(dims, q, q_rot, cache, cache, *tail),
+                 lambda: B.sparse_attn_paged(dims, q, q_rot, pool, pool, table, 16, *tail, st.ws)):
+        st.out.fill_(7.0)
+        call()
+        torch.cuda.synchronize()
+        assert (st.out == 0).all()
+
+
 @pytest.mark.parametrize("Bn,G,Hkv,N,K,w,n_sink,n_new,lens,stride,data", [
     (1, 4, 1, 4096 + 16, 100, 16, 0, 1, None, 0, None),          # one head a workgroup, exactly one chunk of 4096
     (1, 4, 1, 4097 + 16, 100, 16, 0, 2, None, 8, None),          # and one token more

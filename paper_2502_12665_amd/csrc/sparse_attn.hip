@@ -12,6 +12,7 @@
 // far rows are the same for the G heads of a KV head and q~ K^T is a thin matrix product: that case
 // (bf16 caches) goes through the matrix cores, see attn_shared_mfma_kernel.
 #include <algorithm>
+#include <cfloat>
 #include <type_traits>
 
 #include "common.hpp"
@@ -443,9 +444,10 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4
   // Logits are kept by log2 e, so that a weight is one exponential of a difference, without a product that is rounded once more.
   const float scale = 0.12751743f;   // log2(e) / sqrt(128)
   auto power = [](float x) { return __builtin_amdgcn_exp2f(x); };
+  // (a state without rows has the lowest finite logit: from -inf a row of logit -inf would not be a difference but NaN)
+  constexpr float kNone = -FLT_MAX;
   auto merge = [&](float& m, float& l, float (&o)[VEC], float m2, float l2, const float (&o2)[VEC]) {
     const float mm = fmaxf(m, m2);
-    if (mm == -INFINITY) return;
     const float s1 = power(m - mm), s2 = power(m2 - mm);
     l = l * s1 + l2 * s2;
 #pragma unroll
@@ -455,17 +457,17 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4
   const size_t seq_base = page_table ? 0 : (size_t)prob * ctx_stride * kD;
   const T* kb = k_cache + seq_base + d0;
   const T* vb = v_cache + seq_base + d0;
-  float m_run = -INFINITY, l_run = 0.f, acc[VEC];
+  float m_run = kNone, l_run = 0.f, acc[VEC];
 #pragma unroll
   for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
   // (float32: links of 8 rows, see attn_partial_body)
   constexpr bool LINKS = VEC == 4;
-  float m_sum = -INFINITY, l_sum = 0.f, acc_sum[VEC];
+  float m_sum = kNone, l_sum = 0.f, acc_sum[VEC];
 #pragma unroll
   for (int v = 0; v < VEC; ++v) acc_sum[v] = 0.f;
   auto end_link = [&]() {
     merge(m_sum, l_sum, acc_sum, m_run, l_run, acc);
-    m_run = -INFINITY;
+    m_run = kNone;
     l_run = 0.f;
 #pragma unroll
     for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
@@ -585,7 +587,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4
   float mm = s_m[0];
 #pragma unroll
   for (int w = 1; w < kBlockWaves; ++w) mm = fmaxf(mm, s_m[w]);
-  const float f = mm == -INFINITY ? 0.f : power(m_run - mm);   // (2^-inf = 0 for a wave without rows)
+  const float f = power(m_run - mm);   // (0 for a wave without rows, 1 if no wave has any)
   if (lane < LPR) {
     if (lane == 0) s_l[wv] = l_run * f;
 #pragma unroll

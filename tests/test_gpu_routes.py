@@ -376,6 +376,49 @@ def test_attention_of_few_rows_by_one_workgroup(Bn, G, Hkv, N, K, w, n_sink, len
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("Hkv,K,w", [(8, 100, 64), (32, 100, 66), (96, 100, 1), (48, 200, 100)])
+def test_attention_of_few_rows_by_one_workgroup_of_values_that_are_not_finite(Hkv, K, w, dtype):
+    """A row whose logit is -inf has no weight, wherever a wave meets it (alone, first, last, at both ends of a link); a logit
+    that is not a number empties its own head alone, and what is not finite among the values stays in its dimension."""
+    N = K + w
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(N)
+    k, v = (torch.randn(1, Hkv, N, 128, generator=g, device="cuda").to(dt) for _ in range(2))
+    q = torch.ones(1, Hkv, 128, dtype=dt, device="cuda")
+    dims = B.make_dims(1, Hkv, Hkv, 128, 16, N)
+    st = B.DecodeState(dims, K, w, 0, dt, synth.inv_freq(128, 10000.0), 1)
+    idx = torch.arange(K, dtype=torch.int32, device="cuda").expand(1, Hkv, K).contiguous()
+    count = torch.full((1, Hkv), K, dtype=torch.int32, device="cuda")
+    inf = float("inf")
+    # (dimension 63 turns the least: its factor is positive at every distance)
+    lost = torch.zeros(Hkv, N, dtype=torch.bool, device="cuda")
+    lost[0, N - 1] = lost[1, 0] = lost[2, K - 1] = True
+    lost[3, K:] = lost[4, :K] = True
+    lost[5, :64] = lost[5, K:K + w // 2] = True
+    lost[7] = torch.rand(N, generator=g, device="cuda") < 0.5
+    k[0, :, :, 63] = torch.where(lost, -inf, k[0, :, :, 63].float()).to(dt)
+    k[0, 6, 5, 63] = float("nan")
+    v[0, 7, int((~lost[7]).nonzero()[0]), 9] = inf
+    B.sparse_attn(dims, q, q.float().contiguous(), k, v, idx, count, K, w, 0, st.cos_win, st.sin_win, None, st.out, st.ws)
+    torch.cuda.synchronize()
+    back = torch.arange(w - 1, -1, -1, device="cuda")
+    cos, sin = st.cos_win.double()[back], st.sin_win.double()[back]
+    turn = torch.cat([torch.ones(K, 128, dtype=torch.float64, device="cuda"), torch.cat([cos - sin, cos + sin], 1)])
+    tol = 2.0 ** -8 if dtype == "bf16" else 2e-6   # (as above)
+    for h in range(Hkv):
+        if h == 6:
+            assert (st.out[0, h] == 0).all()
+            continue
+        logit = (turn * torch.where(lost[h][:, None], 0.0, k[0, h].double())).sum(1) * 128 ** -0.5
+        want = torch.softmax(torch.where(lost[h], -inf, logit), 0) @ torch.where(lost[h][:, None], 0.0, v[0, h].double())
+        got, fine = st.out[0, h].double(), torch.ones(128, dtype=torch.bool, device="cuda")
+        if h == 7:
+            fine[9] = False
+            assert got[9] == inf
+        assert ((got - want).abs() <= tol * want.abs() + 2e-6)[fine].all(), (h, float((got - want).abs()[fine].max()))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("Hkv,K,w", [(1, 16, 16), (2, 0, 16), (64, 256, 100), (128, 64, 64)])
 def test_attention_over_an_empty_context_gives_zeros(Hkv, K, w, dtype):
     """ctx_len = 0 in a cache that has room for more, through every per-head call."""

@@ -338,6 +338,12 @@ def test_float32_attention_of_many_heads_is_as_exact_as_that_of_few(N, K, w, n_s
     (16, 4, 4, 1000, 30, 131, 4, None),               # 256 heads; window rows the most
     (3, 8, 4, 2500, 1140, 56, 4, None),               # the most of bf16
     (2, 4, 2, 600, 100, 0, 0, None),                  # no window
+    (1, 4, 1, 500, 1, 70, 0, None),                   # (this and the next ones within attn_block's limits of their head counts)
+    (2, 7, 2, 900, 296, 100, 4, [900, 3]),
+    (18, 8, 1, 600, 100, 0, 0, None),
+    (24, 4, 1, 300, 1, 64, 0, None),
+    (5, 8, 4, 2500, 1140, 56, 4, [2500, 60, 1, 0, 1200]),
+    (5, 8, 4, 1000, 400, 236, 4, [1000, 700, 200, 0, 1]),
 ])
 def test_attention_of_few_rows_by_one_workgroup(Bn, G, Hkv, N, K, w, n_sink, lens, dtype):
     """Few rows a head: a workgroup of 16 waves takes them all.  Against float64; other sequences of the batch do not matter."""

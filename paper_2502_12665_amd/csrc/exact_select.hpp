@@ -347,17 +347,17 @@ __device__ void exact_select_block(const SeqCodes& seq_codes,
 
 // The same by as many rounds of rows as the sequence needs: rounds that hold none take their time all the same, in the scans
 // above all, and where there are few, all are requested at once (4 heads of 4096 candidates in decode_select_head_kernel 16.4
-// -> 12.7 us, 32 of 6370 with M = 32 21.9 -> 19.5).
+// -> 12.7 us, 32 of 6370 with M = 32 21.9 -> 19.5).  The longest come first in the code: behind the others they take 0.25 us more.
 template <int M, bool TABLE_IN_LDS>
 __device__ __forceinline__ void exact_select_sized(const SeqCodes& seq_codes, const int32_t* head_table, int32_t s_lo,
                                                    int32_t s_hi, float scale, const SeqRange& sr, int32_t* out_idx,
                                                    float* out_score, unsigned char* tbl, ExactLds& L) {
-  if (sr.ncand <= 4 * kExactThreads)   // (uniform)
-    exact_select_block<M, false, TABLE_IN_LDS, 4>(seq_codes, head_table, s_lo, s_hi, scale, sr, out_idx, out_score, tbl, L);
-  else if (sr.ncand <= 8 * kExactThreads)
+  if (__builtin_expect(sr.ncand > 8 * kExactThreads, 1))   // (uniform)
+    exact_select_block<M, false, TABLE_IN_LDS>(seq_codes, head_table, s_lo, s_hi, scale, sr, out_idx, out_score, tbl, L);
+  else if (sr.ncand > 4 * kExactThreads)
     exact_select_block<M, false, TABLE_IN_LDS, 8>(seq_codes, head_table, s_lo, s_hi, scale, sr, out_idx, out_score, tbl, L);
   else
-    exact_select_block<M, false, TABLE_IN_LDS>(seq_codes, head_table, s_lo, s_hi, scale, sr, out_idx, out_score, tbl, L);
+    exact_select_block<M, false, TABLE_IN_LDS, 4>(seq_codes, head_table, s_lo, s_hi, scale, sr, out_idx, out_score, tbl, L);
 }
 
 }  // namespace a2ats

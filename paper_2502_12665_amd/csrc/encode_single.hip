@@ -1127,6 +1127,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
             for (int i = 0; i < 8; ++i) x[i] = (x[i] - s_mu[d + i]) * s_t[d + i];
             split8(x, zh[tile][k4 + u], zl[tile][k4 + u], zn2[tile]);
+            asm volatile("" : "+v"(zn2[tile]));   // (now: else x is kept, in scratch memory, and summed up after the main loop)
           }
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -1266,8 +1267,10 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
         for (int tile = 0; tile < 2; ++tile)
           mine[32 * tile] = NearPart{s1[tile], s2[tile], s3[tile], (uint32_t)d1[tile] | ((uint32_t)d2[tile] << 16)};
       }
-      __threadfence();
+      // Each wave's parts have arrived before the barrier, so that one fence behind it covers them all (from every wave: 5 us more).
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
+      if (tid == 0) __threadfence();
       if (tid == 0) s_last = atomicAdd(arrived + (size_t)kv * gridDim.x + chunk, 1u) == (uint32_t)slices - 1 ? 1u : 0u;
       __syncthreads();
       if (!s_last) continue;
@@ -1277,11 +1280,19 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
       for (int tile = 0; tile < 2; ++tile) {
         s1[tile] = s2[tile] = s3[tile] = INFINITY;
         d1[tile] = d2[tile] = 0;
-        for (int i = 0; i < slices; ++i) {
-          const NearPart o = all[(size_t)i * kKeysPerWG + 32 * tile];
-          insert(o.s1, (int)(o.codes & 0xffffu), s1[tile], s2[tile], s3[tile], d1[tile], d2[tile]);
-          insert(o.s2, (int)(o.codes >> 16), s1[tile], s2[tile], s3[tile], d1[tile], d2[tile]);
-          insert(o.s3, 0x7fffffff, s1[tile], s2[tile], s3[tile], d1[tile], d2[tile]);
+#pragma unroll 1
+        for (int i = 0; i < slices; i += 4) {   // (four parts requested together; there are 2, 4, 8 or 16)
+          NearPart o[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) o[u] = all[(size_t)min(i + u, slices - 1) * kKeysPerWG + 32 * tile];
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            if (i + u >= slices) break;   // (uniform)
+            insert(o[u].s1, (int)(o[u].codes & 0xffffu), s1[tile], s2[tile], s3[tile], d1[tile], d2[tile]);
+            insert(o[u].s2, (int)(o[u].codes >> 16), s1[tile], s2[tile], s3[tile], d1[tile], d2[tile]);
+            insert(o[u].s3, 0x7fffffff, s1[tile], s2[tile], s3[tile], d1[tile], d2[tile]);
+          }
         }
       }
     }

@@ -24,11 +24,11 @@
 //                                  1/2 ||c^z||^2, and the largest norms
 //   encode_single_operands_kernel  w_c in matrix-core operand order: rounded to f16, and as two bf16
 //                                  terms (hi + lo, 16 significant bits)
-//   encode_single_sample_kernel, encode_single_choose_kernel
-//                                  128 keys of a KV head say which of the two filters it takes
-//   encode_single_filter8_kernel   every key: scores from one product of whole numbers of 8 bits; keys that their rounding
-//                                  leaves open are listed
-//   encode_single_filter_kernel    the same with scores from one f16 product (11 significant bits per operand): the two
+//   encode_single_sample_kernel    128 keys of a KV head, which say which of the two filters it takes
+//   encode_single_filter_kernel    every key, by one of two filters:
+//                                  - i8: scores from one product of whole numbers of 8 bits; keys that their rounding leaves
+//                                  open are listed
+//                                  - f16: the same with scores from one f16 product (11 significant bits per operand): the two
 //                                  smallest and the code of the first are kept per key.  Where they are further apart than
 //                                  the rounding of the operands can account for -- its norm is known for every key and
 //                                  bounded for the codewords -- the code is decided; the other keys are listed.
@@ -47,6 +47,8 @@
 //                                  encode_single_sweep_pick_kernel.  More keys, and those of a decode
 //                                  step's first launch, are swept in single_codebook.hip
 //   encode_single_transform_kernel z = k L in float64, rounded once to float32 (seeding only)
+#include <algorithm>
+
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -107,7 +109,8 @@ inline long near_groups(const a2ats_dims& d) { return d.n_kv_heads < 512 ? 512 /
 
 struct EncWs {
   size_t off_L, off_sd, off_heff, off_means, off_center, off_czT, off_wT, off_chalf, off_cfrag, off_cbias, off_f16,
-      off_fbias, off_i8, off_bias8, off_cstat, off_sample, off_norms, off_eight, off_count, off_list, off_near, off_near_part, off_part, bytes;
+      off_fbias, off_i8, off_bias8, off_cstat, off_sample, off_norms, off_eight, off_count, off_list, off_near,
+      off_near_part, off_part, bytes;
   size_t near_cap;   // keys of a KV head
 };
 
@@ -570,9 +573,8 @@ __device__ __forceinline__ void filter_insert(float a, float b, float c, float d
 //
 // A product takes half the time and power of the f16 one, the ranking 17 vector instructions a tile instead of 36.  96001 keys
 // x 8 heads, full matrix, codewords prepared: 707 -> 377 us (the products at 3.0 POP/s while they run, which is what this chip's
-// power leaves of 5; reading and rounding keys, and the four, a quarter of the time); 2000 keys 81 -> 45, 100 57 -> 39.  Keys
-// all of which are undecided pay for the sample: 12000 normal keys x 8 heads 397 -> 403.  With 2 % of the keys open both
-// filters, with their lists, take the same time at 3 to 6 % (0.02: 872 -> 671 us, 0.06: 879 -> 848); kSampleOpen is below that.
+// power leaves of 5; reading and rounding keys, and the four, a quarter of the time).  With 2 % of the keys open both filters, with
+// their lists, take the same time at 3 to 6 % (0.02: 872 -> 671 us, 0.06: 879 -> 848); kSampleOpen is below that.
 // Tried: eight scores ranked together (13 instructions) and multiplied again 393; a wave of 32 NT keys with NT = 3 and its next
 // keys read and rounded during the products 418.
 // ------------------------------------------------------------------------------------------
@@ -618,15 +620,18 @@ __device__ __forceinline__ void insert8(int a, int b, int& k1, int& k2) {
   k2 = min(k2, m);
 }
 
-// 128 keys of a KV head, evenly spread, against a slice of its codewords: the two smallest scores.
-__global__ __launch_bounds__(kEncThreads) void encode_single_sample_kernel(
+// 128 keys of a KV head, evenly spread, against a slice of its codewords: the two smallest scores.  (And no counts
+// yet.)
+__global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void encode_single_sample_kernel(
     const float* __restrict__ keys, const Center* __restrict__ center, const uint8_t* __restrict__ i8,
-    const int* __restrict__ bias8, int2* __restrict__ sample, float2* __restrict__ norms, int Hkv, int n_new, long n_rows) {
+    const int* __restrict__ bias8, int2* __restrict__ sample, float2* __restrict__ norms, uint32_t* __restrict__ counter,
+    int n_counter, int n_new, long n_rows) {
   static_assert(kSampleKeys == 32 * kEncWaves, "a wave takes 32 keys");
   constexpr int kOwn = kBlocks / kSampleSlices;
   __shared__ __align__(32) float s_mu[kD], s_key[kD];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, g = lane >> 5;
-  const int slice = blockIdx.x, kv = blockIdx.y, at = wave * 32 + col;
+  const int slice = blockIdx.x, kv = blockIdx.y, Hkv = gridDim.y, at = wave * 32 + col;
+  for (int i = (kv * kSampleSlices + slice) * kEncThreads + tid; i < n_counter; i += Hkv * kSampleSlices * kEncThreads) counter[i] = 0;
   if (tid < kD) {
     s_mu[tid] = center[kv].mu[tid];
     s_key[tid] = center[kv].key8[tid];
@@ -667,53 +672,61 @@ __global__ __launch_bounds__(kEncThreads) void encode_single_sample_kernel(
   }
 }
 
-// Whether the KV head takes the i8 filter; and no counts yet.
-__global__ __launch_bounds__(kSampleKeys) void encode_single_choose_kernel(const CodewordStat* __restrict__ cstat,
-                                                                           const int2* __restrict__ sample,
-                                                                           const float2* __restrict__ norms,
-                                                                           uint32_t* __restrict__ eight,
-                                                                           uint32_t* __restrict__ counter, int n_counter) {
-  const int kv = blockIdx.x, tid = threadIdx.x;
-  for (int i = kv * kSampleKeys + tid; i < n_counter; i += gridDim.x * kSampleKeys) counter[i] = 0;
-  int2 s[kSampleSlices];
+// Whether a KV head takes the i8 filter: every workgroup of the filter finds it from the sample (which costs less than a launch of
+// its own, or the fences with which the last workgroup of the sample could say it, 19 us).  Two threads take a key, each half of the
+// slices.
+__device__ __forceinline__ bool takes_filter8(const CodewordStat* cstat, const int2* __restrict__ sample,
+                                              const float2* __restrict__ norms, int kv, int2 (&s_half)[kSampleKeys]) {
+  static_assert(kEncThreads == 2 * kSampleKeys, "two threads a key");
+  const int at = threadIdx.x % kSampleKeys, half = threadIdx.x / kSampleKeys;
+  const float2 n = norms[(size_t)kv * kSampleKeys + at];
+  int2 s[kSampleSlices / 2];
 #pragma unroll
-  for (int i = 0; i < kSampleSlices; ++i) s[i] = sample[((size_t)kv * kSampleSlices + i) * kSampleKeys + tid];
-  const float2 n = norms[(size_t)kv * kSampleKeys + tid];
+  for (int i = 0; i < kSampleSlices / 2; ++i)
+    s[i] = sample[((size_t)kv * kSampleSlices + half * (kSampleSlices / 2) + i) * kSampleKeys + at];
   int k1 = 0x7fffffff, k2 = 0x7fffffff;
 #pragma unroll
-  for (int i = 0; i < kSampleSlices; ++i) insert8(s[i].x, s[i].y, k1, k2);
-  const CodewordStat st = cstat[kv];
-  float key_scale, w_scale;
-  i8_scales(st, key_scale, w_scale);
-  const int open = __syncthreads_count(!((float)(k2 - k1) > reach8(st, key_scale, w_scale, n.x, n.y)));
-  if (tid == 0) eight[kv] = open <= kSampleOpen ? 1u : 0u;
+  for (int i = 0; i < kSampleSlices / 2; ++i) insert8(s[i].x, s[i].y, k1, k2);
+  if (half == 1) s_half[at] = make_int2(k1, k2);
+  __syncthreads();
+  bool open = false;
+  if (half == 0) {
+    insert8(s_half[at].x, s_half[at].y, k1, k2);
+    const CodewordStat st = cstat[kv];
+    float key_scale, w_scale;
+    i8_scales(st, key_scale, w_scale);
+    open = !((float)(k2 - k1) > reach8(st, key_scale, w_scale, n.x, n.y));
+  }
+  return __syncthreads_count(open) <= kSampleOpen;
 }
 
-constexpr int kWaves8[5] = {0, 4, 3, 0, 2};   // per SIMD, of 32 NT keys each
+constexpr int kFilterWaves[2][5] = {{0, 2, 2, 0, 2}, {0, 4, 3, 0, 2}};   // per SIMD, of 32 NT keys each, without and with the i8 filter
+constexpr int kSect = 512 + 16;   // 16 bytes of 32 codewords; a codeword's eight on different banks
+constexpr int kBlk8 = 8 * kSect + 128, kBuf8 = 2 * kBlk8, kBuf16 = kF16Bytes + 128;
 template <int NT>
-__global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(kWaves8[NT], kWaves8[NT]))) void encode_single_filter8_kernel(
-    const float* __restrict__ keys, const Center* __restrict__ center, const uint8_t* __restrict__ i8,
-    const int* __restrict__ bias8, const uint32_t* __restrict__ eight, const CodewordStat* __restrict__ cstat,
-    uint16_t* __restrict__ codes, uint32_t* __restrict__ near_count, uint32_t* __restrict__ near, int64_t near_cap, int Hkv,
+struct FilterLds {
+  __align__(16) uint8_t mem[2 * (kBuf8 > kBuf16 ? kBuf8 : kBuf16)];
+  float n2[NT][kEncThreads], e2[NT][kEncThreads];   // (kept out of the registers for the main loop)
+  __align__(32) float mu[kD], key[2][kD];           // (of the f16 and of the i8 operands)
+  int2 half[kSampleKeys];
+};
+
+template <int NT>
+__device__ __forceinline__ void filter8_body(
+    FilterLds<NT>& lds, const float* __restrict__ keys, const uint8_t* __restrict__ i8, const int* __restrict__ bias8,
+    const CodewordStat* __restrict__ cstat, uint16_t* __restrict__ codes, uint32_t* __restrict__ near_count, uint32_t* __restrict__ near, int64_t near_cap, int Hkv,
     int n_new, int pos0, int64_t ctx_stride) {
   // The codewords go through LDS two blocks at a time (with one the loads are not back when they are wanted).
-  constexpr int kSect = 512 + 16;   // 16 bytes of 32 codewords; a codeword's eight on different banks
-  constexpr int kBlk = 8 * kSect + 128, kBuf = 2 * kBlk;
+  constexpr int kBlk = kBlk8, kBuf = kBuf8;
   static_assert(kI8Bytes / 16 == kEncThreads, "a thread stages 16 bytes of a block");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, g = lane >> 5;
   const int bkv = blockIdx.y, kv = bkv % Hkv, seq = bkv / Hkv;
   const long key_first = ((long)blockIdx.x * kEncWaves + wave) * (32 * NT);
-  if (!eight[kv]) return;   // (uniform)
   const CodewordStat st = cstat[kv];
-  __shared__ float s_n2[NT][kEncThreads], s_e2[NT][kEncThreads];   // (kept out of the registers for the main loop)
-  __shared__ __align__(32) float s_mu[kD], s_key[kD];
-  __shared__ __align__(16) uint8_t s_mem[2 * kBuf];
+  auto &s_n2 = lds.n2, &s_e2 = lds.e2;
+  auto &s_mu = lds.mu, &s_key = lds.key[1];
+  uint8_t* s_mem = lds.mem;
   const float* seq_keys = keys + (size_t)bkv * n_new * kD;
-  if (tid < kD) {
-    s_mu[tid] = center[kv].mu[tid];
-    s_key[tid] = center[kv].key8[tid];
-  }
-  __syncthreads();
   i32x4 kq[NT][4];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
@@ -858,27 +871,22 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(kWa
 }
 
 template <int NT>
-__global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void encode_single_filter_kernel(
-    const float* __restrict__ keys, const Center* __restrict__ center, const uint8_t* __restrict__ f16,
-    const float* __restrict__ fbias, const uint32_t* __restrict__ eight, const CodewordStat* __restrict__ cstat, uint16_t* __restrict__ codes, uint32_t* __restrict__ near_count,
-    uint32_t* __restrict__ near, int64_t near_cap, int Hkv, int n_new, int pos0, int64_t ctx_stride) {
-  constexpr int kBuf = kF16Bytes + 128, kPieces = kF16Bytes / 16 / kEncThreads;
-  __shared__ __align__(16) uint8_t s_mem[2 * kBuf];
+__device__ __forceinline__ void filter16_body(
+    FilterLds<NT>& lds, const float* __restrict__ keys, const uint8_t* __restrict__ f16, const float* __restrict__ fbias,
+    const CodewordStat* __restrict__ cstat, uint16_t* __restrict__ codes,
+    uint32_t* __restrict__ near_count, uint32_t* __restrict__ near, int64_t near_cap, int Hkv, int n_new, int pos0,
+    int64_t ctx_stride) {
+  constexpr int kBuf = kBuf16, kPieces = kF16Bytes / 16 / kEncThreads;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, g = lane >> 5;
   const int bkv = blockIdx.y, kv = bkv % Hkv, seq = bkv / Hkv;
   const long key_first = ((long)blockIdx.x * kEncWaves + wave) * (32 * NT);
   const float* seq_keys = keys + (size_t)bkv * n_new * kD;
   const CodewordStat st = cstat[kv];
-  __shared__ float s_n2[NT][kEncThreads], s_e2[NT][kEncThreads];   // (kept out of the registers for the main loop)
-  __shared__ __align__(32) float s_mu[kD], s_key[kD];
-  if (eight[kv]) return;   // (uniform)
+  auto &s_n2 = lds.n2, &s_e2 = lds.e2;
+  auto &s_mu = lds.mu, &s_key = lds.key[0];
+  uint8_t* s_mem = lds.mem;
   float key_scale, w_scale;
   f16_scales(st, key_scale, w_scale);
-  if (tid < kD) {
-    s_mu[tid] = center[kv].mu[tid];
-    s_key[tid] = center[kv].key[tid];
-  }
-  __syncthreads();
   f16x8 kh[NT][8];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
@@ -917,6 +925,9 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
   const uint8_t* gblk = f16 + (size_t)kv * kBlocks * kF16Bytes + tid * 16;
   const float* gbias = fbias + (size_t)kv * kCW + (tid & 31);
   static_assert(kPieces == 2, "a thread stages two 16-byte pieces of a block");
+  // A block is requested as soon as the one before is staged, where there are registers for that (otherwise at the top of its
+  // step, which with one tile is too late: 1100 normal keys x 8 heads 188 -> 173 us).
+  constexpr bool kEarly = NT <= 2;
   uint4 p0, p1;
   float pb;
   auto request = [&](int cb) {
@@ -957,6 +968,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
   auto operand = [&](int cb, int kt) { return *(const f16x8*)(s_mem + (cb & 1) * kBuf + kt * 1024 + lane * 16); };
   request(0);
   stage(0);
+  if (kEarly) request(1);
   __syncthreads();
   read_bias(0);
 #pragma unroll
@@ -969,7 +981,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
   for (int v = 0; v < 16; ++v) acc[1][v] = 3e38f;   // (ranked before the first tile, as numbers of block 0: above any score)
 #pragma unroll 1
   for (int cb = 0; cb < kBlocks; ++cb) {
-    request(cb + 1);
+    if (!kEarly) request(cb + 1);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -1000,6 +1012,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
           }
         }
         stage(cb + 1);   // (its buffer was last read before the barrier of block cb - 1)
+        if (kEarly) request(cb + 2);
         __syncthreads();
         if (NT == 1) {
           read_bias(cb + 1);
@@ -1040,6 +1053,35 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
       }
     }
   }
+}
+
+// I8, F16: the filters that the launch has.  Without the first, an earlier one has left its choice in `eight`.
+template <int NT, bool I8, bool F16>
+__global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(kFilterWaves[I8][NT], kFilterWaves[I8][NT]))) void encode_single_filter_kernel(
+    const float* __restrict__ keys, const Center* __restrict__ center, const uint8_t* __restrict__ f16,
+    const float* __restrict__ fbias, const uint8_t* __restrict__ i8, const int* __restrict__ bias8,
+    const int2* __restrict__ sample, const float2* __restrict__ norms, uint32_t* __restrict__ eight,
+    const CodewordStat* __restrict__ cstat, uint16_t* __restrict__ codes, uint32_t* __restrict__ near_count,
+    uint32_t* __restrict__ near, int64_t near_cap, int Hkv, int n_new, int pos0, int64_t ctx_stride) {
+  __shared__ FilterLds<NT> lds;
+  const int kv = blockIdx.y % Hkv, tid = threadIdx.x;
+  if (!I8 && eight[kv]) return;   // (uniform)
+  if (tid < kD) {
+    lds.mu[tid] = center[kv].mu[tid];
+    lds.key[0][tid] = center[kv].key[tid];
+    lds.key[1][tid] = center[kv].key8[tid];
+  }
+  bool eighth = false;
+  if (I8) {   // (has barriers)
+    eighth = takes_filter8(cstat, sample, norms, kv, lds.half);
+    if (blockIdx.x == 0 && (int)blockIdx.y < Hkv && tid == 0) eight[kv] = eighth ? 1u : 0u;
+  } else {
+    __syncthreads();
+  }
+  if (I8 && eighth)   // (uniform)
+    filter8_body<NT>(lds, keys, i8, bias8, cstat, codes, near_count, near, near_cap, Hkv, n_new, pos0, ctx_stride);
+  else if (F16)
+    filter16_body<NT>(lds, keys, f16, fbias, cstat, codes, near_count, near, near_cap, Hkv, n_new, pos0, ctx_stride);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1773,31 +1815,28 @@ hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_ne
   const uint8_t *f16 = base + w.off_f16, *i8 = base + w.off_i8;
   const float* fbias = (const float*)(base + w.off_fbias);
   const int* bias8 = (const int*)(base + w.off_bias8);
-  uint32_t* eight = (uint32_t*)(base + w.off_eight);
   int2* sample = (int2*)(base + w.off_sample);
   float2* norms = (float2*)(base + w.off_norms);
-  hipLaunchKernelGGL(encode_single_sample_kernel, dim3(kSampleSlices, Hkv), dim3(kEncThreads), 0, stream, keys, center, i8,
-                     bias8, sample, norms, Hkv, n_new, (long)d.batch * n_new);
-  if ((err = hipGetLastError()) != hipSuccess) return err;
-  hipLaunchKernelGGL(encode_single_choose_kernel, dim3(Hkv), dim3(kSampleKeys), 0, stream, cstat, sample, norms, eight, counter,
-                     n_counter);
-  if ((err = hipGetLastError()) != hipSuccess) return err;
+  uint32_t* eight = (uint32_t*)(base + w.off_eight);
   const dim3 block(kEncThreads);
-  auto grid = [&](int tiles) { return dim3((n_new + 32 * tiles * kEncWaves - 1) / (32 * tiles * kEncWaves), bkv); };
-#define A2ATS_LAUNCH_FILTER8(NT)                                                                                        \
-  hipLaunchKernelGGL(encode_single_filter8_kernel<NT>, grid(NT), block, 0, stream, keys, center, i8, bias8, eight, cstat, \
-                     (uint16_t*)codes, counter + 1, near, (int64_t)w.near_cap, Hkv, n_new, pos0, d.ctx_stride)
-  if (nt == 4) A2ATS_LAUNCH_FILTER8(4);
-  else if (nt == 2) A2ATS_LAUNCH_FILTER8(2);
-  else A2ATS_LAUNCH_FILTER8(1);
-#undef A2ATS_LAUNCH_FILTER8
+  hipLaunchKernelGGL(encode_single_sample_kernel, dim3(kSampleSlices, Hkv), block, 0, stream, keys, center, i8, bias8, sample, norms,
+                     counter, n_counter, n_new, (long)d.batch * n_new);
   if ((err = hipGetLastError()) != hipSuccess) return err;
-#define A2ATS_LAUNCH_FILTER(NT)                                                                                        \
-  hipLaunchKernelGGL(encode_single_filter_kernel<NT>, grid(NT), block, 0, stream, keys, center, f16, fbias, eight, cstat, \
-                     (uint16_t*)codes, counter + 1, near, (int64_t)w.near_cap, Hkv, n_new, pos0, d.ctx_stride)
-  if (nt == 4) A2ATS_LAUNCH_FILTER(4);
-  else if (nt == 2) A2ATS_LAUNCH_FILTER(2);
-  else A2ATS_LAUNCH_FILTER(1);
+  const dim3 grid((n_new + 32 * nt * kEncWaves - 1) / (32 * nt * kEncWaves), bkv);
+#define A2ATS_LAUNCH_FILTER(NT, I8, F16)                                                                                      \
+hipLaunchKernelGGL((encode_single_filter_kernel<NT, I8, F16>), grid, block, 0, stream, keys, center, f16, fbias, i8, bias8, sample, \
+                   norms, eight, cstat, (uint16_t*)codes, counter + 1, near, (int64_t)w.near_cap, Hkv, n_new, pos0, d.ctx_stride)
+  // One launch has both filters, except with 64 keys a wave: there the i8 one has three waves per SIMD, the f16 one the
+  // registers of two.
+  if (nt == 4) {
+    A2ATS_LAUNCH_FILTER(4, true, true);
+  } else if (nt == 2) {
+    A2ATS_LAUNCH_FILTER(2, true, false);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+    A2ATS_LAUNCH_FILTER(2, false, true);
+  } else {
+    A2ATS_LAUNCH_FILTER(1, true, true);
+  }
 #undef A2ATS_LAUNCH_FILTER
   if ((err = hipGetLastError()) != hipSuccess) return err;
   hipLaunchKernelGGL(encode_single_kernel, dim3((unsigned)near_groups(d), Hkv), block, 0, stream, keys, center, cfrag, cbias,

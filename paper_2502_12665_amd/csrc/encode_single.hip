@@ -24,8 +24,9 @@
 //                                  1/2 ||c^z||^2, and the largest norms
 //   encode_single_operands_kernel  w_c in matrix-core operand order: rounded to f16, and as two bf16
 //                                  terms (hi + lo, 16 significant bits)
-//   encode_single_sample_kernel    128 keys of a KV head, which say which of the two filters it takes
-//   encode_single_filter_kernel    every key, by one of two filters:
+//   encode_single_sample_kernel    128 keys of a KV head, which say which of the two filters it takes; of a short call all keys
+//   encode_single_decide_kernel    a short call's keys: decided by the sample's products, or listed
+//   encode_single_filter_kernel    every key of a longer one, by one of two filters:
 //                                  - i8: scores from one product of whole numbers of 8 bits; keys that their rounding leaves
 //                                  open are listed
 //                                  - f16: the same with scores from one f16 product (11 significant bits per operand): the two
@@ -47,8 +48,6 @@
 //                                  encode_single_sweep_pick_kernel.  More keys, and those of a decode
 //                                  step's first launch, are swept in single_codebook.hip
 //   encode_single_transform_kernel z = k L in float64, rounded once to float32 (seeding only)
-#include <algorithm>
-
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -620,17 +619,19 @@ __device__ __forceinline__ void insert8(int a, int b, int& k1, int& k2) {
   k2 = min(k2, m);
 }
 
-// 128 keys of a KV head, evenly spread, against a slice of its codewords: the two smallest scores.  (And no counts
-// yet.)
+// Keys of a KV head, 128 a workgroup, against a slice of its codewords: the two smallest scores, each with its number in the slice
+// in the 9 bits below it.  (And no counts yet.)  ALL: all `n_rows` keys, else 128 of them, evenly spread.
+template <bool ALL>
 __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void encode_single_sample_kernel(
     const float* __restrict__ keys, const Center* __restrict__ center, const uint8_t* __restrict__ i8,
     const int* __restrict__ bias8, int2* __restrict__ sample, float2* __restrict__ norms, uint32_t* __restrict__ counter,
     int n_counter, int n_new, long n_rows) {
   static_assert(kSampleKeys == 32 * kEncWaves, "a wave takes 32 keys");
   constexpr int kOwn = kBlocks / kSampleSlices;
+  static_assert(32 * kOwn <= 512, "a number has 9 bits");
   __shared__ __align__(32) float s_mu[kD], s_key[kD];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, g = lane >> 5;
-  const int slice = blockIdx.x, kv = blockIdx.y, Hkv = gridDim.y, at = wave * 32 + col;
+  const int slice = blockIdx.x, kv = blockIdx.y, Hkv = gridDim.y, at = blockIdx.z * kSampleKeys + wave * 32 + col;
   for (int i = (kv * kSampleSlices + slice) * kEncThreads + tid; i < n_counter; i += Hkv * kSampleSlices * kEncThreads) counter[i] = 0;
   if (tid < kD) {
     s_mu[tid] = center[kv].mu[tid];
@@ -644,7 +645,8 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
     for (int kt = 0; kt < 4; ++kt) a[i][kt] = *(const i32x4*)(blk + i * kI8Bytes + 32 * kt);
   __syncthreads();
-  const uint32_t row = (uint32_t)((2 * at + 1) * n_rows / (2 * kSampleKeys)), seq = row / (uint32_t)n_new;   // (sequence by sequence)
+  const uint32_t row = (uint32_t)(ALL ? min((long)at, n_rows - 1) : (2 * at + 1) * n_rows / (2 * kSampleKeys));
+  const uint32_t seq = row / (uint32_t)n_new;   // (sequence by sequence)
   const float* kp = keys + (((size_t)seq * Hkv + kv) * n_new + (row - seq * (uint32_t)n_new)) * kD + 16 * g;
   i32x4 q[4];
   float e2 = 0.f;
@@ -660,44 +662,87 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
     }
 #pragma unroll
     for (int kt = 0; kt < 4; ++kt) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i][kt], q[kt], acc, 0, 0, 0);
+    // register v: codeword 32 i + 8 (v / 4) + 4 g + v % 4 of the slice, number 32 i + 2 v + g
+    auto numbered = [&](int v) { return (int)((uint32_t)acc[v] << 9 | (uint32_t)(32 * i + 2 * v)); };
 #pragma unroll
-    for (int v = 0; v < 16; v += 2) insert8(acc[v], acc[v + 1], k1, k2);
+    for (int v = 0; v < 16; v += 2) insert8(numbered(v), numbered(v + 1), k1, k2);
   }
+  k1 |= g;
+  k2 |= g;
   const int o1 = __shfl_xor(k1, 32), o2 = __shfl_xor(k2, 32);
   e2 += __shfl_xor(e2, 32);
   n2 += __shfl_xor(n2, 32);
   if (g == 0) {
-    sample[((size_t)kv * kSampleSlices + slice) * kSampleKeys + at] = make_int2(min(k1, o1), min(max(k1, o1), min(k2, o2)));
-    if (slice == 0) norms[(size_t)kv * kSampleKeys + at] = make_float2(e2, (float)n2);
+    sample[((size_t)kv * kSampleSlices + slice) * (gridDim.z * kSampleKeys) + at] =
+        make_int2(min(k1, o1), min(max(k1, o1), min(k2, o2)));
+    if (slice == 0 && (!ALL || at < n_rows)) norms[(size_t)kv * (ALL ? n_rows : kSampleKeys) + at] = make_float2(e2, (float)n2);
   }
 }
 
-// Whether a KV head takes the i8 filter: every workgroup of the filter finds it from the sample (which costs less than a launch of
-// its own, or the fences with which the last workgroup of the sample could say it, 19 us).  Two threads take a key, each half of the
-// slices.
-__device__ __forceinline__ bool takes_filter8(const CodewordStat* cstat, const int2* __restrict__ sample,
-                                              const float2* __restrict__ norms, int kv, int2 (&s_half)[kSampleKeys]) {
+// The two smallest scores of key `at` over all slices, the smaller one's number and slice; two threads take a key, each half of the
+// slices, and the first of them returns true.  (Of equal scores the one or the other: they leave the key open.)
+struct SampleBest {
+  int k1, k2, slice;
+};
+__device__ __forceinline__ bool best_of_slices(const int2* __restrict__ sample, int at, int stride, SampleBest& best,
+                                               SampleBest (&s_half)[kSampleKeys]) {
   static_assert(kEncThreads == 2 * kSampleKeys, "two threads a key");
-  const int at = threadIdx.x % kSampleKeys, half = threadIdx.x / kSampleKeys;
-  const float2 n = norms[(size_t)kv * kSampleKeys + at];
+  const int half = threadIdx.x / kSampleKeys, first = half * (kSampleSlices / 2);
   int2 s[kSampleSlices / 2];
 #pragma unroll
-  for (int i = 0; i < kSampleSlices / 2; ++i)
-    s[i] = sample[((size_t)kv * kSampleSlices + half * (kSampleSlices / 2) + i) * kSampleKeys + at];
-  int k1 = 0x7fffffff, k2 = 0x7fffffff;
+  for (int i = 0; i < kSampleSlices / 2; ++i) s[i] = sample[(size_t)(first + i) * stride + at];
+  best = SampleBest{0x7fffffff, 0x7fffffff, 0};
+  auto take = [&](int k1, int k2, int slice) {
+    best.k2 = min(max(best.k1, k1), min(best.k2, k2));
+    best.slice = k1 < best.k1 ? slice : best.slice;
+    best.k1 = min(best.k1, k1);
+  };
 #pragma unroll
-  for (int i = 0; i < kSampleSlices / 2; ++i) insert8(s[i].x, s[i].y, k1, k2);
-  if (half == 1) s_half[at] = make_int2(k1, k2);
+  for (int i = 0; i < kSampleSlices / 2; ++i) take(s[i].x, s[i].y, first + i);
+  if (half == 1) s_half[threadIdx.x % kSampleKeys] = best;
   __syncthreads();
+  if (half == 1) return false;
+  const SampleBest o = s_half[threadIdx.x];
+  take(o.k1, o.k2, o.slice);
+  return true;
+}
+__device__ __forceinline__ bool leaves_open(const CodewordStat& st, const SampleBest& best, float2 norms) {
+  float key_scale, w_scale;
+  i8_scales(st, key_scale, w_scale);
+  return !((float)((best.k2 >> 9) - (best.k1 >> 9)) > reach8(st, key_scale, w_scale, norms.x, norms.y));   // (also where anything is not a number)
+}
+
+// Whether a KV head takes the i8 filter: every workgroup of the filter finds it from the sample (which costs less than a launch of
+// its own, or the fences with which the last workgroup of the sample could say it, 19 us).
+__device__ __forceinline__ bool takes_filter8(const CodewordStat* cstat, const int2* __restrict__ sample,
+                                              const float2* __restrict__ norms, int kv, SampleBest (&s_half)[kSampleKeys]) {
+  const int at = threadIdx.x % kSampleKeys;
+  const float2 n = norms[(size_t)kv * kSampleKeys + at];
+  SampleBest best;
   bool open = false;
-  if (half == 0) {
-    insert8(s_half[at].x, s_half[at].y, k1, k2);
-    const CodewordStat st = cstat[kv];
-    float key_scale, w_scale;
-    i8_scales(st, key_scale, w_scale);
-    open = !((float)(k2 - k1) > reach8(st, key_scale, w_scale, n.x, n.y));
-  }
+  if (best_of_slices(sample + (size_t)kv * kSampleSlices * kSampleKeys, at, kSampleKeys, best, s_half))
+    open = leaves_open(cstat[kv], best, n);
   return __syncthreads_count(open) <= kSampleOpen;
+}
+
+// The keys of a call that are so few that a "sample" has them all: decided or listed.
+__global__ __launch_bounds__(kEncThreads) void encode_single_decide_kernel(
+    const CodewordStat* __restrict__ cstat, const int2* __restrict__ sample, const float2* __restrict__ norms,
+    uint16_t* __restrict__ codes, uint32_t* __restrict__ near_count, uint32_t* __restrict__ near, int64_t near_cap, int n_new,
+    long n_rows, int pos0, int64_t ctx_stride) {
+  __shared__ SampleBest s_half[kSampleKeys];
+  const int kv = blockIdx.y, Hkv = gridDim.y, at = blockIdx.x * kSampleKeys + threadIdx.x % kSampleKeys;
+  const int stride = gridDim.x * kSampleKeys;
+  SampleBest best;
+  if (!best_of_slices(sample + (size_t)kv * kSampleSlices * stride, at, stride, best, s_half) || at >= n_rows) return;
+  const int number = best.k1 & 511, v = (number >> 1) & 15;
+  const int code = best.slice * (kCW / kSampleSlices) + (number >> 5) * 32 + (v >> 2) * 8 + (number & 1) * 4 + (v & 3);
+  const int seq = at / n_new;
+  codes[((size_t)seq * Hkv + kv) * ctx_stride + pos0 + (at - seq * n_new)] = (uint16_t)code;
+  if (leaves_open(cstat[kv], best, norms[(size_t)kv * n_rows + at])) {
+    const uint32_t place = atomicAdd(near_count + kv, 1u);
+    near[(size_t)kv * near_cap + place] = (uint32_t)at;
+  }
 }
 
 constexpr int kFilterWaves[2][5] = {{0, 2, 2, 0, 2}, {0, 4, 3, 0, 2}};   // per SIMD, of 32 NT keys each, without and with the i8 filter
@@ -708,7 +753,7 @@ struct FilterLds {
   __align__(16) uint8_t mem[2 * (kBuf8 > kBuf16 ? kBuf8 : kBuf16)];
   float n2[NT][kEncThreads], e2[NT][kEncThreads];   // (kept out of the registers for the main loop)
   __align__(32) float mu[kD], key[2][kD];           // (of the f16 and of the i8 operands)
-  int2 half[kSampleKeys];
+  SampleBest half[kSampleKeys];
 };
 
 template <int NT>
@@ -1451,6 +1496,12 @@ __global__ __launch_bounds__(256) void encode_single_recheck_kernel(
   }
 }
 
+// No counts yet, and no KV head takes the i8 filter.
+__global__ void encode_single_clear_kernel(uint32_t* counter, int n, uint32_t* eight, int Hkv) {
+  for (int i = threadIdx.x; i < n; i += blockDim.x) counter[i] = 0;
+  for (int i = threadIdx.x; i < Hkv; i += blockDim.x) eight[i] = 0;
+}
+
 // The few-key (append) route of a few keys in all: every key is decided by a float64 sweep, its 4096 codewords split
 // over kSlices workgroups (one workgroup would read 4 MB by itself).  With w_c = c (L L^T) the
 // distortion of codeword c is |z|^2 - 2 k . w_c + |c^z|^2, so the sweep minimises
@@ -1691,6 +1742,24 @@ LdsSlot g_factor_lds[16];
 
 }  // namespace
 
+// Which products see a call's keys first.  us of whole calls, before there were products in 8 bits -> now, keys near their codewords
+// (0.1) | normal keys; 8 KV heads unless stated:
+//   kSampleProducts: those of the sample, which then has all keys.  100 keys 57 -> 18 | 175 -> 85, 500 78 -> 26 | 183 -> 109; one
+//     KV head of 2000 57 -> 18 | 119 -> 72; 24 of 250 81 -> 35 | 211 -> 121.  By a filter that a sample chose 500 keys take 38 | 148.
+//     The line is where that becomes the better one: 1024 keys 43 by the sample's products, 40 by a chosen filter.
+//   kChosenFilter: 1024 keys 81 -> 40 | 187 -> 141, 12000 159 -> 75 | 333 -> 226, 96001 713 -> 402 | 1169 -> 1117.
+//   kFilter16: so many KV heads that the sample, which reads all their codewords, costs what it saves.  64 of 250 keys 78 -> 57 | 264
+//     -> 158 (by a chosen filter 78 | 193), 128 of 1000 156 -> 152 | 405 -> 326 (162 | 412).
+// Between the two kinds of keys lie some that the f16 filter would all decide and 8 bits not.  Their list takes 35 us at the least: at
+// a noise of 1.0 12000 keys 249 -> 147, 2000 81 -> 78, 500 78 -> 63, but 40 of 32 sequences 58 -> 75, one KV head of 4000 58 -> 68
+// and 32 of 1100 87 -> 118.
+enum Route { kSampleProducts, kChosenFilter, kFilter16 };
+static Route single_route(long n_rows, int Hkv) {   // (n_rows: keys of a KV head)
+  const long groups = (n_rows + kSampleKeys - 1) / kSampleKeys;
+  if (Hkv > 24 && n_rows < 32l * Hkv) return kFilter16;
+  return groups <= 24 && groups * Hkv <= 48 ? kSampleProducts : kChosenFilter;
+}
+
 size_t encode_single_ws_bytes(const a2ats_dims& d) { return enc_single_ws(d).bytes; }
 
 hipError_t launch_encode_single_prepare(const a2ats_dims& d, const float* codebook, const float* weights, int mode,
@@ -1818,27 +1887,47 @@ hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_ne
   int2* sample = (int2*)(base + w.off_sample);
   float2* norms = (float2*)(base + w.off_norms);
   uint32_t* eight = (uint32_t*)(base + w.off_eight);
+  const long n_rows = (long)d.batch * n_new, groups = (n_rows + kSampleKeys - 1) / kSampleKeys;
   const dim3 block(kEncThreads);
-  hipLaunchKernelGGL(encode_single_sample_kernel, dim3(kSampleSlices, Hkv), block, 0, stream, keys, center, i8, bias8, sample, norms,
-                     counter, n_counter, n_new, (long)d.batch * n_new);
-  if ((err = hipGetLastError()) != hipSuccess) return err;
-  const dim3 grid((n_new + 32 * nt * kEncWaves - 1) / (32 * nt * kEncWaves), bkv);
-#define A2ATS_LAUNCH_FILTER(NT, I8, F16)                                                                                      \
-hipLaunchKernelGGL((encode_single_filter_kernel<NT, I8, F16>), grid, block, 0, stream, keys, center, f16, fbias, i8, bias8, sample, \
-                   norms, eight, cstat, (uint16_t*)codes, counter + 1, near, (int64_t)w.near_cap, Hkv, n_new, pos0, d.ctx_stride)
-  // One launch has both filters, except with 64 keys a wave: there the i8 one has three waves per SIMD, the f16 one the
-  // registers of two.
-  if (nt == 4) {
-    A2ATS_LAUNCH_FILTER(4, true, true);
-  } else if (nt == 2) {
-    A2ATS_LAUNCH_FILTER(2, true, false);
+  const Route route = single_route(n_rows, Hkv);
+  if (route == kSampleProducts) {
+    sample = (int2*)(base + w.off_near_part);   // (used by the lists' kernels later, as the list is: 48 groups take 1.5 MB of its 2)
+    norms = (float2*)list;
+    hipLaunchKernelGGL(encode_single_sample_kernel<true>, dim3(kSampleSlices, Hkv, (unsigned)groups), block, 0, stream, keys, center,
+                       i8, bias8, sample, norms, counter, n_counter, n_new, n_rows);
     if ((err = hipGetLastError()) != hipSuccess) return err;
-    A2ATS_LAUNCH_FILTER(2, false, true);
+    hipLaunchKernelGGL(encode_single_decide_kernel, dim3((unsigned)groups, Hkv), block, 0, stream, cstat, sample, norms,
+                       (uint16_t*)codes, counter + 1, near, (int64_t)w.near_cap, n_new, n_rows, pos0, d.ctx_stride);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
   } else {
-    A2ATS_LAUNCH_FILTER(1, true, true);
-  }
+    if (route == kFilter16)
+      hipLaunchKernelGGL(encode_single_clear_kernel, dim3(1), dim3(1024), 0, stream, counter, n_counter, eight, Hkv);
+    else
+      hipLaunchKernelGGL(encode_single_sample_kernel<false>, dim3(kSampleSlices, Hkv), block, 0, stream, keys, center, i8, bias8,
+                         sample, norms, counter, n_counter, n_new, n_rows);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+    const dim3 grid((n_new + 32 * nt * kEncWaves - 1) / (32 * nt * kEncWaves), bkv);
+#define A2ATS_LAUNCH_FILTER(NT, I8, F16)                                                                                      \
+  hipLaunchKernelGGL((encode_single_filter_kernel<NT, I8, F16>), grid, block, 0, stream, keys, center, f16, fbias, i8, bias8, sample, \
+                     norms, eight, cstat, (uint16_t*)codes, counter + 1, near, (int64_t)w.near_cap, Hkv, n_new, pos0, d.ctx_stride)
+    // One launch has both filters, except with 64 keys a wave: there the i8 one has three waves per SIMD, the f16 one the
+    // registers of two.
+    if (route == kFilter16) {
+      if (nt == 4) A2ATS_LAUNCH_FILTER(4, false, true);
+      else if (nt == 2) A2ATS_LAUNCH_FILTER(2, false, true);
+      else A2ATS_LAUNCH_FILTER(1, false, true);
+    } else if (nt == 4) {
+      A2ATS_LAUNCH_FILTER(4, true, true);
+    } else if (nt == 2) {
+      A2ATS_LAUNCH_FILTER(2, true, false);
+      if ((err = hipGetLastError()) != hipSuccess) return err;
+      A2ATS_LAUNCH_FILTER(2, false, true);
+    } else {
+      A2ATS_LAUNCH_FILTER(1, true, true);
+    }
 #undef A2ATS_LAUNCH_FILTER
-  if ((err = hipGetLastError()) != hipSuccess) return err;
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+  }
   hipLaunchKernelGGL(encode_single_kernel, dim3((unsigned)near_groups(d), Hkv), block, 0, stream, keys, center, cfrag, cbias,
                      cstat, (uint16_t*)codes, counter + 1, near, (int64_t)w.near_cap, counter, list, counter + 1 + Hkv,
                      (NearPart*)(base + w.off_near_part), Hkv, n_new, pos0, d.ctx_stride);

@@ -174,6 +174,78 @@ def test_single_codebook_keys_near_their_codewords(n_new, batch, kv, mode):
             assert (lost <= 1e-13 * (half.max() + k.norm(dim=1) * w.norm(dim=1).max())).all(), float(lost.max())
 
 
+def _chosen_filters(ws, kv):
+    """What a call left in its workspace: per KV head 1 if its sample took the i8 filter and 0 if the f16 one, and neither where
+    there was no filter.  (The regions before it, as enc_single_ws lays them out.)"""
+    per_head = [128 * 128 * 8, 128 * 8, 128 * 128 * 8, 16 * 128 * 8, 4 * 128 * 4, 128 * 4096 * 8, 128 * 4096 * 8, 4096 * 8,
+                4096 * 512, 4096 * 4, 4096 * 256, 4096 * 4, 4096 * 128, 4096 * 4, 128, 32 * 128 * 8, 128 * 8]
+    at = sum((kv * n + 255) // 256 * 256 for n in per_head)
+    return ws[at:at + 4 * kv].view(torch.int32).tolist()
+
+
+@pytest.mark.parametrize("mode", ["none", "block"])
+@pytest.mark.parametrize("n_new,batch,kv,kinds,products", [
+    (9, 1, 1, "near", "sample"), (9, 1, 2, "mixed", "sample"), (128, 1, 3, "mixed", "sample"), (43, 3, 2, "mixed", "sample"),
+    (3072, 1, 2, "mixed", "sample"), (257, 3, 5, "mixed", "sample"),
+    (3073, 1, 1, "near", "chosen"), (777, 1, 8, "near", "chosen"), (777, 1, 8, "mixed", "chosen"), (401, 3, 8, "mixed", "chosen"),
+    (13001, 1, 8, "mixed", "chosen"), (13001, 1, 8, "normal", "chosen"), (6501, 2, 8, "near", "chosen"),
+    (25700, 1, 8, "mixed", "chosen"), (25700, 1, 8, "normal", "chosen"),
+    (9, 1, 25, "mixed", "f16"), (799, 1, 25, "near", "f16"), (801, 1, 25, "mixed", "chosen"),
+])
+def test_single_codebook_products(n_new, batch, kv, kinds, products, mode):
+    """Which products see the keys first, for keys near their codewords, keys drawn like the codewords and calls with KV heads of
+    both: the edges of the choice, 32, 64 and 128 keys a wave with ragged tiles, of both filters.  Some keys, not among the
+    sampled ones, are halfway between two codewords, far out, or not finite."""
+    wl = synth.Workload("enc1_products", batch, kv, kv, 128, 1, n_new + 8, 16, 16, seed=n_new + kv, n_centroids=4096)
+    weights, h64 = None, torch.eye(128, dtype=torch.float64, device="cuda").expand(kv, 128, 128)
+    if mode == "block":
+        weights = synth.make_query_second_moment(wl)["h_block"].cuda()
+        h64 = weights.double().reshape(kv, 128, 128)
+    codebook = synth.make_codebook(wl, "cuda")
+    keys = synth.make_encode_keys(wl, n_new, device="cuda")
+    normal = [kinds == "normal" or (kinds == "mixed" and h % 2 == 1) for h in range(kv)]
+    keys[:, normal] = synth.make_encode_keys(wl, n_new, device="cuda", stress=True)[:, normal]
+    rows = batch * n_new
+    sampled = {(2 * at + 1) * rows // 256 for at in range(128)}
+    free = [r for r in range(rows) if r not in sampled] if rows > 256 else list(range(rows))
+    spots = [(r // n_new, r % n_new) for r in free[:4] + free[-4:]]
+    for (b, j), (c, d) in zip(spots, [(40, 42), (1000, 1016), (3, 4095), (7, 8)]):
+        keys[b, :, j] = 0.5 * (codebook[:, 0, c] + codebook[:, 0, d])
+    keys[spots[4][0], :, spots[4][1]] *= 300.0
+    keys[spots[5][0], :, spots[5][1]] = 0.0
+    broken = spots[6:]
+    for (b, j), value in zip(broken, ("nan", "inf")):
+        keys[b, :, j, 5] = float(value)
+    dims = B.make_dims(batch, kv, kv, 128, 1, n_new + 8, n_centroids=4096)
+    ws = torch.full((B.workspace_bytes(dims, B.OP_ENCODE),), 0xA5, dtype=torch.uint8, device="cuda")
+    codes = torch.full((batch, kv, n_new + 8), -2, dtype=torch.int16, device="cuda")
+    B.encode_keys(dims, keys, n_new, 3, codebook, weights, B.W_NONE if mode == "none" else B.W_BLOCK, codes, ws)
+    torch.cuda.synchronize()
+    assert (codes[:, :, :3] == -2).all() and (codes[:, :, 3 + n_new:] == -2).all()
+    got = codes[:, :, 3:3 + n_new].long()
+    filters = _chosen_filters(ws, kv)
+    if products == "sample":
+        assert all(f not in (0, 1) for f in filters)
+    else:
+        assert filters == [1 if products == "chosen" and not x else 0 for x in normal]
+    for b, j in broken:
+        assert (got[b, :, j] == 0).all()
+        keys[b, :, j] = 0.0
+    for h in range(kv):
+        c = codebook[h, 0].double()
+        w = c @ h64[h]
+        half = 0.5 * (w * c).sum(-1)
+        for b in range(batch):
+            k = keys[b, h].double()
+            score = half - k @ w.t()
+            lost = score.gather(1, got[b, h][:, None])[:, 0] - score.min(1).values
+            for at, j in broken:
+                if at == b:
+                    lost[j] = 0.0
+            # (float64 sums of 128 products, of L L^T instead of H)
+            assert (lost <= 1e-13 * (half.max() + k.norm(dim=1) * w.norm(dim=1).max())).all(), float(lost.max())
+
+
 def test_single_codebook_ties_and_values_that_are_not_finite():
     n = 700
     wl = synth.Workload("enc1_ties", 1, 2, 2, 128, 1, n + 8, 16, 16, seed=5, n_centroids=4096)

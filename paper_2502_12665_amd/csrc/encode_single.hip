@@ -336,7 +336,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
   }
   __syncthreads();
-  float c2 = 0.f, c_elem = 0.f, w_elem = 0.f;   // (of c only for scales; in float64 the differences would stay live)
+  // (of c only for scales, so that float32 sums do: 128 squares of rounded differences are off by less than 1e-5; in float64 the
+  // differences would stay live)
+  float c2 = 0.f, c_elem = 0.f, w_elem = 0.f;
 #pragma unroll
   for (int u = 0; u < kD / 4; ++u) {
     const float x = (cv[u] - s_mu[4 * u + k]) * s_t[4 * u + k];
@@ -411,7 +413,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
   // rounded up; a float that is not negative orders like its bits
   uint32_t most[5] = {__float_as_uint(__double2float_ru(0.5 * z2)), __float_as_uint(__double2float_ru(sqrt(w2))),
-                      __float_as_uint(sqrtf(c2)), __float_as_uint(w_elem), __float_as_uint(c_elem)};
+                      __float_as_uint(1.00001f * sqrtf(c2)), __float_as_uint(w_elem), __float_as_uint(c_elem)};
   __shared__ uint32_t s_most[4][5];
 #pragma unroll
   for (int i = 0; i < 5; ++i) {

@@ -324,11 +324,13 @@ def single_codebook_encode_prefill(args, torch, B, synth, wl):
         "dtype": "i8 products with i32 accumulate; bf16 hi/lo products, then f64, where they cannot decide",
         "data": "synthetic",
         "config": {"workload": wl.name + " encode", "keys": n_keys, "codewords": 4096, "weights": "W_BLOCK"},
-        "roofline": {"kernel": "encode_single_filter8_kernel (+ factor, codeword, sample, listed-key and re-check kernels)",
-                     "bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
+        "roofline": {"kernel": "encode_single_filter_kernel, 8-bit products (+ factor, codeword, sample, listed-key and re-check "
+                               "kernels)",
+                     "bound": "mfma", "achieved": achieved, "peak": peak, "unit": "Top/s",
                      "frac": achieved / peak, "traffic": None,
                      "executed_i8_TOPs": achieved, "executed_frac": achieved / peak,
-                     "note": "algorithmic operations; each term takes one 8-bit product, the keys it leaves open three bf16 ones"},
+                     "note": "algorithmic operations; each term takes one 8-bit product (the keys of this workload are drawn near "
+                             "codewords), the keys it leaves open three bf16 ones"},
     }))
 
 
@@ -600,15 +602,15 @@ def codebook_fit(args, torch, B, synth, wl):
                   "step; plus one second-moment accumulation)",
         "value": n_keys / (ms * 1e-3), "unit": "keys/s", "n_gpus": 1, "steps": steps, "warmup": warmup,
         "ms_per_step": ms, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "assignment: i8 or f16 products, bf16 hi/lo products, then f64, where they cannot decide; f64 sums for "
-                 "means and moments",
+        "dtype": "assignment: f16 products, bf16 hi/lo products, then f64, where they cannot decide; f64 sums for means "
+                 "and moments",
         "data": "synthetic",
         "config": {"workload": wl.name + " codebook construction", "keys": n_keys, "codewords": wl.n_centroids,
                    "query_rows": N * wl.n_q_heads},
         "phase_ms_median": {"assign": ph[0], "centroid_step": ph[1], "second_moment": ph[2]},
         "kmeanspp_seed_ms": {"keys_per_kv_head": wl.batch * n_seed, "ms": seed_ms},
-        "roofline": {"kernel": "encode_single_filter8_kernel or encode_single_filter_kernel (+ factor, codeword, sample, "
-                               "listed-key and re-check kernels)",
+        "roofline": {"kernel": "encode_single_filter_kernel, f16 products: these keys are drawn like the codewords (+ factor, "
+                               "codeword, sample, listed-key and re-check kernels)",
                      "bound": "mfma", "achieved": flop / (ph[0] * 1e-3) / 1e12, "peak": 2500.0, "unit": "TFLOP/s",
                      "frac": flop / (ph[0] * 1e-3) / 1e12 / 2500.0,
                      "traffic": None, "note": "algorithmic flops of the assignment over its whole call"},

@@ -110,7 +110,8 @@ def _single(dims, keys, codebook, weights, mode, stride, prepared=False):
 @pytest.mark.parametrize("mode", ["none", "diag", "block"])
 @pytest.mark.parametrize("n_new,batch,kv", [(9, 1, 1), (129, 2, 3), (1025, 1, 8), (8200, 2, 4), (66000, 2, 2)])
 def test_single_codebook_codes_are_the_float64_argmin(mode, n_new, batch, kv):
-    """The sizes take the filter's 32, 64 and 128 keys per wave; keys drawn like the codewords leave some open."""
+    """Short calls, and the f16 filter's (odd sizes) and the i8 filter's 32 and 128 keys per wave; keys drawn like the codewords
+    leave some open.  (Both filters at each width: test_single_codebook_products.)"""
     wl = synth.Workload("enc1", batch, kv, kv, 128, 1, n_new + 8, 16, 16, seed=n_new, n_centroids=4096)
     hm = synth.make_query_second_moment(wl)
     code = {"none": B.W_NONE, "diag": B.W_DIAG, "block": B.W_BLOCK}[mode]
@@ -143,8 +144,8 @@ def test_single_codebook_codes_are_the_float64_argmin(mode, n_new, batch, kv):
 @pytest.mark.parametrize("mode", ["none", "block"])
 @pytest.mark.parametrize("n_new,batch,kv", [(10, 1, 1), (97, 2, 3), (13001, 1, 8), (25700, 1, 8)])
 def test_single_codebook_keys_near_their_codewords(n_new, batch, kv, mode):
-    """The i8 filter's 32, 64 and 128 keys a wave, whose last tiles are ragged; some keys halfway between two codewords of one
-    group of four, of one lane and of two, far out, and not finite."""
+    """Short calls and the i8 filter's 64 and 128 keys a wave, whose last tiles are ragged; some keys halfway between two
+    codewords of one group of four, of one lane and of two, far out, and not finite."""
     wl = synth.Workload("enc1_near", batch, kv, kv, 128, 1, n_new + 8, 16, 16, seed=n_new, n_centroids=4096)
     weights, h64 = None, torch.eye(128, dtype=torch.float64, device="cuda").expand(kv, 128, 128)
     if mode == "block":

@@ -148,10 +148,12 @@ def test_short_decode_select_equals_the_separate_calls(Bn, Hkv, G, M, N, K, w, n
     (8, 4, 513, 200, 0, 4, "f32", 64, True),                             # no window
     (8, 4, 1300, 600, 128, 0, "bf16", 16, True),
     (8, 4, 1300, 600, 128, 4, "f32", 0, False),
+    (8, 4, 2600, 1500, 64, 4, "bf16", 16, True),                         # (these two: pages and lengths by the split route)
+    (7, 4, 1700, 900, 100, 0, "f32", 64, True),
 ])
 def test_attention_of_many_heads_equals_that_of_few(G, Hkv, N, K, w, n_sink, dtype, page, ragged):
-    """Of many heads a workgroup takes a whole one (all cases but that with 256 window rows); the same sequences four at a
-    time take the split route."""
+    """Of many heads a workgroup of four waves takes a whole one (all cases but that with 256 window rows); the same sequences
+    four at a time take the split route, or, with some rows but not many, a workgroup of 16 waves a head."""
     Bn = 40
     wl = synth.Workload("many", Bn, G * Hkv, Hkv, 128, 16, N, K, w, n_sink=n_sink, kv_dtype=dtype, seed=N)
     xd = synth.make_decode_inputs(wl, device="cuda")
@@ -296,8 +298,8 @@ def test_decode_select_of_values_that_are_not_finite_equals_the_two_calls(Bn, G,
 
 @pytest.mark.parametrize("N,K,w,n_sink", [(700, 100, 64, 4), (700, 508, 100, 0), (5000, 4096, 64, 4), (1500, 1000, 0, 0), (900, 0, 230, 0)])
 def test_float32_attention_of_many_heads_is_as_exact_as_that_of_few(N, K, w, n_sink):
-    """The same four sequences among 40 (a workgroup takes a whole head) and alone (its rows are shared out), against
-    float64: errors of rounding only, and of the same size."""
+    """The same four sequences among 40 (a workgroup of four waves takes a whole head) and alone (its rows are shared out; the
+    first two cases: taken by 16 waves), against float64: errors of rounding only, and of the same size."""
     Bn, Hkv, G, n = 40, 4, 8, 4
     wl = synth.Workload("exact", Bn, Hkv * G, Hkv, 128, 16, N, K, w, n_sink=n_sink, kv_dtype="f32", seed=N)
     xd = synth.make_decode_inputs(wl, device="cuda")
@@ -326,7 +328,7 @@ def test_float32_attention_of_many_heads_is_as_exact_as_that_of_few(N, K, w, n_s
             for i, o in enumerate(outs):
                 err[i] += float((o[b, h] - want).pow(2).sum())
     whole, few = (err[0] / size) ** 0.5, (err[1] / size) ** 0.5
-    H.log(f"float32 attention, {K} + {w} rows: error {whole:.3e} whole, {few:.3e} shared out")
+    H.log(f"float32 attention, {K} + {w} rows: error {whole:.3e} of many heads, {few:.3e} of few")
     assert whole <= 1.1 * few and few < 4e-7
 
 

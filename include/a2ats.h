@@ -129,8 +129,8 @@ int a2ats_rope_tables(int32_t head_dim, const double* inv_freq, int32_t b, int32
  * lower triangle is read) and the argmin is over 4096 codewords of all 128 dimensions:
  * codes [dev, u16 B*Hkv*ctx_stride].  With the Cholesky factor of section 4.2 (H = L L^T,
  * c^z = c L, w = c (L L^T)) the scores 1/2||c^z||^2 - k.w are formed on the matrix cores from f16
- * roundings of both operands, or from roundings to 8 bits where a sample of a KV head's keys shows that
- * these decide nearly all of them, with a centre of the codewords subtracted from keys and codewords
+ * roundings of both operands, or from roundings to 8 bits (short calls, and where a sample of a KV head's
+ * keys shows that these decide nearly all of them), with a centre of the codewords subtracted from keys and codewords
  * (which leaves the distances as they are) and the dimensions of k and w balanced by powers of two;
  * keys whose two best scores are closer than the rounding can account
  * for are scored again from bf16 hi/lo splits (about 2^-17 relative), and those still too close in

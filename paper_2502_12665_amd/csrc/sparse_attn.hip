@@ -47,7 +47,7 @@ AttnPlan make_attn_plan(const a2ats_dims& d, int top_k, int window, int n_sink) 
 
 // Whether one workgroup takes all rows of a head and writes its output, so that nothing is left to merge: a launch less, but
 // rows that are not shared out.  Per-head selections of 256 heads or more; us, split and merged -> whole:
-//   - few rows a head, where the launch is what counts (of 256 heads those that attn_block leaves): 256 heads, bf16, 128 + 64
+//   - few rows a head, where the launch is what counts (256 heads go to attn_block above 160 rows): 256 heads, bf16, 128 + 64
 //     rows 12.8 -> 10.3, but 128 + 512 17.9 -> 21.9 (a window row costs a rotation, and the split shares them out the most); 512 heads, 192 +
 //     256 rows 22.0 -> 19.4, 128 + 512 26.8 -> 25.4; float32, 384 heads, 256 + 128 rows 26.9 -> 23.9, 896 heads, 256 + 64 39.4
 //     -> 41.1;
@@ -67,36 +67,27 @@ static bool attn_whole(const a2ats_dims& d, int top_k, int window, int n_sink, b
 }
 
 // Whether a head is one workgroup of 16 waves (attn_block_kernel): every head has a CU, and so few rows that a CU fetches them
-// in about the time of the second launch that is saved.  The most rows follow from what the other form takes, at 5000 shapes of
-// 1 to 256 heads; us, split and merged (256 heads: one workgroup of four waves, where that is what it would be) -> 16 waves:
-//   - up to 64 heads the split has its far rows in parts of 64 and so takes 7 to 8 whatever their number, but a workgroup of it
-//     takes up to 128 window rows: 4 heads, bf16, 136 + 64 rows 7.2 -> 6.8, 336 + 64 7.3 -> 7.7, 272 + 128 8.6 -> 8.4, 64 + 256
-//     8.5 -> 8.2, 144 + 256 8.5 -> 9.1, 18 + 300 8.5 -> 8.7; float32, 23 + 0 6.3 -> 6.6, 136 + 64 7.8 -> 7.5, 336 + 64 7.8 -> 9.0,
-//     256 + 128 10.3 -> 8.8;
-//   - from 96 on the chip is shared: 96 heads, bf16, 700 + 100 rows 12.5 -> 11.0, 936 + 64 13.2 -> 13.7, 400 + 400 11.9 -> 12.4;
-//     float32, 256 + 128 12.9 -> 10.1, 700 + 64 16.6 -> 16.9; 128 heads, bf16, 256 + 128 10.4 -> 8.1, 1072 + 128 17.0 -> 15.9;
-//     160 heads, float32, 512 + 256 21.7 -> 19.3, 700 + 64 19.9 -> 20.8; 255 heads, bf16, 272 + 128 16.4 -> 13.0;
-//   - 256 heads: bf16, 128 + 64 6.9 -> 7.2, 256 + 128 11.5 -> 10.0, 144 + 256 13.6 -> 9.8; float32, 128 + 64 10.8 -> 9.0, 700 +
-//     64 27.6 -> 29.1.
+// in about the time of the second launch that is saved.  From the times of whole decode steps with the one and the other form, 5300
+// shapes of 4 to 256 heads whose caches are not in L2: split and merged (256 heads of few rows: one workgroup of four waves) -> 16
+// waves, us of a step from a graph:
+//   - bf16: 48 heads of 168 + 128 rows 24.1 -> 21.4, 32 of 367 + 64 29.0 -> 28.8, but 398 + 64 + 0.4 and 94 + 400 + 1.5; 96 heads of 425
+//     + 64 34.6 -> 33.7, 951 + 128 - 1.0, but 947 + 64 + 0.7; 196 heads of 886 + 128 - 4.1, but 160 of 927 + 100 + 1.2; 224 of 397 +
+//     400 50.5 -> 46.0; 256 of 32 + 16 + 0.7;
+//   - float32, where the split has its far rows in parts of 64 and takes the same time whatever their number: 44 heads of 163 + 64
+//     rows 23.5 -> 22.4, but 8 of 217 + 64 + 0.6 and 32 of 372 + 16 + 1.6; 192 of 361 + 64 54.7 -> 51.6; 132 of 688 + 64 + 1.2, 160 of
+//     566 + 16 - 1.8, 568 + 64 + 2.3; 120 of 560 + 400 + 1.8.
+// (Attention over and over the same rows, which are in L2 then, is faster by the split from fewer rows on: 4 heads, float32, 336 +
+// 64 rows 7.8 -> 9.0.)
 static bool attn_block(const a2ats_dims& d, int top_k, int window, int n_sink, bool bf16) {
   const long heads = (long)d.batch * d.n_q_heads;
   const long rows = (long)n_sink + top_k + window;
-  if (top_k == 0 || heads > 256 || (window < 32 && rows < 64)) return false;
-  const bool half = window > 64 && window <= 128;   // a window that is one workgroup of the split
-  if (heads < 72) {
-    if (half) return rows <= 400;
-    if (heads < 4) return false;
-    if (window > 128) return window <= 256 && rows <= (bf16 ? 320 : 240);
-    return bf16 ? window >= 32 && rows <= (heads < 48 ? 200 : 400) : rows <= 200;
-  }
-  if (heads < 96) return rows <= (bf16 || window >= 64 ? 400 : 200);
-  if (heads < 128) {
-    if (half) return rows <= (bf16 ? 1000 : 800);
-    return window <= 256 && rows <= (window >= 64 ? (bf16 ? 800 : 600) : (bf16 ? 400 : 200));
-  }
-  if (heads == 256 && rows <= (window < 64 ? 512 : (!bf16 ? 0 : (window == 64 ? 256 : 160)))) return false;
-  if (bf16) return (heads >= 144 || window <= 400) && rows <= (heads <= 208 ? 1200 : 800);
-  return window <= (heads < 144 ? 320 : (heads <= 208 ? 400 : 800)) && rows <= (window > 64 ? 800 : 640);
+  if (top_k == 0 || heads > 256) return false;
+  if (heads < 96) return rows <= (bf16 || window > 64 || heads >= 72 || (heads >= 40 && window == 64) ? 400 : 260);
+  if (heads == 256 && rows <= (window < 64 ? 256 : 160)) return false;
+  if (bf16) return rows <= (heads > 208 ? 800 : (heads < 176 && window < 128 ? 960 : (heads < 128 ? 1120 : 1200)));
+  if (heads >= 192) return rows <= 800;
+  if (window <= 64) return rows <= (heads < 136 ? 540 : 600);
+  return rows <= (window <= 256 || heads >= 144 ? 800 : 560);
 }
 
 // A lane's 16-byte piece of a row, kept as loaded (so that rows in flight cost four registers

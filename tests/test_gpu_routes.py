@@ -153,7 +153,7 @@ def test_short_decode_select_equals_the_separate_calls(Bn, Hkv, G, M, N, K, w, n
 ])
 def test_attention_of_many_heads_equals_that_of_few(G, Hkv, N, K, w, n_sink, dtype, page, ragged):
     """Of many heads a workgroup of four waves takes a whole one (all cases but that with 256 window rows); the same sequences
-    four at a time take the split route, or, with some rows but not many, a workgroup of 16 waves a head."""
+    four at a time take a workgroup of 16 waves a head, or, with the window alone or many rows, the split route."""
     Bn = 40
     wl = synth.Workload("many", Bn, G * Hkv, Hkv, 128, 16, N, K, w, n_sink=n_sink, kv_dtype=dtype, seed=N)
     xd = synth.make_decode_inputs(wl, device="cuda")
@@ -346,6 +346,7 @@ def test_float32_attention_of_many_heads_is_as_exact_as_that_of_few(N, K, w, n_s
     (24, 4, 1, 300, 1, 64, 0, None),
     (5, 8, 4, 2500, 1140, 56, 4, [2500, 60, 1, 0, 1200]),
     (5, 8, 4, 1000, 400, 236, 4, [1000, 700, 200, 0, 1]),
+    (22, 8, 1, 2500, 1140, 56, 4, None),
 ])
 def test_attention_of_few_rows_by_one_workgroup(Bn, G, Hkv, N, K, w, n_sink, lens, dtype):
     """Few rows a head: a workgroup of 16 waves takes them all.  Against float64; other sequences of the batch do not matter."""

@@ -482,6 +482,7 @@ int a2ats_score_topk_stats(const a2ats_dims* dims, int32_t top_k, int32_t window
  * [3] rows each of them scores, [4] streaming workgroups (chunks) per problem, [5] rows per chunk,
  * [6] survivor segments per wave of a chunk (always 1), [7] rows per segment, [8] entries a segment can hold,
  * [9] survivors per head the final kernel can hold, [10] workspace bytes the call needs, divided by 256.
+ * (Of more than 64 head groups and up to 65536 candidates one workgroup each does all of this; [2] to [9] are then not used.)
  */
 int a2ats_score_topk_plan(const a2ats_dims* dims, int32_t top_k, int32_t window, int32_t n_sink, int32_t* plan);
 

@@ -317,7 +317,7 @@ int a2ats_decode_select(const a2ats_dims* d, const float* keys, int32_t n_new, i
   // sampling workgroups read candidate rows while others write the appended rows, so it is only
   // taken when no appended row can be a candidate of any sequence (pos0 >= ctx_len - window: the
   // usual append of the current token); otherwise the two calls run one after the other.
-  const bool sample_apart = plan.P0 > 1 && (long)d->batch * d->n_kv_heads * plan.NG * plan.P0 > 256;
+  const bool sample_apart = !plan.list && plan.P0 > 1 && (long)d->batch * d->n_kv_heads * plan.NG * plan.P0 > 256;
   const bool appended_rows_compete = n_new > 0 && (int64_t)pos0 < (int64_t)d->ctx_len - window;
   // (short contexts have a launch of their own for the whole call, under the same condition)
   const bool by_head = !streams && a2ats::takes_head_route(*d, n_new, window, n_sink, false);
@@ -378,6 +378,13 @@ int a2ats_decode_select(const a2ats_dims* d, const float* keys, int32_t n_new, i
                                           topk_count, topk_score, false, (hipStream_t)stream);
     return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
   }
+  if (plan.list) {
+    e = a2ats::launch_decode_select_list(*d, plan, keys, n_new, pos0, codebook, weights, weight_mode, codes, q, q_dtype, cos_b,
+                                         sin_b, q_rot, lut, lut_scale, seq_lens, top_k, window, n_sink, topk_idx, topk_count,
+                                         topk_score, (uint32_t*)((unsigned char*)ws + plan.off_route), false,
+                                         (hipStream_t)stream);
+    return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
+  }
   e = a2ats::launch_decode_select_prologue(
       *d, keys, n_new, pos0, codebook, weights, weight_mode, codes, q, q_dtype, cos_b, sin_b, q_rot, lut, lut_scale,
       seq_lens, (int32_t*)((unsigned char*)ws + plan.off_thr), plan.P0, plan.sample_rows, top_k, window, n_sink,
@@ -418,7 +425,7 @@ int a2ats_decode_select_shared(const a2ats_dims* d, const float* keys, int32_t n
   if (plan.wide && !holds(plan, ws, ws_bytes)) ws = nullptr;   // the exact route
   const bool streams = plan.fast || (plan.wide && ws);
   if (streams) sample_in_one_part(plan, (long)d->batch * d->n_kv_heads);
-  const bool sample_apart = plan.P0 > 1 && (long)d->batch * d->n_kv_heads * plan.P0 > 256;
+  const bool sample_apart = !plan.list && plan.P0 > 1 && (long)d->batch * d->n_kv_heads * plan.P0 > 256;
   const bool appended_rows_compete = n_new > 0 && (int64_t)pos0 < (int64_t)d->ctx_len - window;
   hipError_t e;
   if (!streams && !appended_rows_compete && a2ats::takes_head_route(*d, n_new, window, n_sink, true)) {
@@ -444,6 +451,13 @@ int a2ats_decode_select_shared(const a2ats_dims* d, const float* keys, int32_t n
     e = a2ats::launch_score_topk(dk, codes, a2ats::CodePages{nullptr, 0, 0}, lut, lut_scale, top_k, window, n_sink,
                                  seq_lens, topk_idx, topk_count, topk_score, nullptr, ws, 0,
                                  (hipStream_t)stream);
+    return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
+  }
+  if (plan.list) {
+    e = a2ats::launch_decode_select_list(*d, plan, keys, n_new, pos0, codebook, weights, mode, codes, q, q_dtype, cos_b, sin_b,
+                                         q_rot, lut, lut_scale, seq_lens, top_k, window, n_sink, topk_idx, topk_count,
+                                         topk_score, (uint32_t*)((unsigned char*)ws + plan.off_route), true,
+                                         (hipStream_t)stream);
     return e == hipSuccess ? A2ATS_OK : A2ATS_ERR_HIP;
   }
   e = a2ats::launch_decode_select_prologue(*d, keys, n_new, pos0, codebook, weights, mode, codes, q, q_dtype, cos_b,

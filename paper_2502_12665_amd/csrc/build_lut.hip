@@ -17,11 +17,26 @@
 #include "coarse_score.hpp"
 #include "exact_select.hpp"
 #include "group_select.hpp"
+#include "list_select.hpp"
 
 namespace a2ats {
 
 constexpr int kLutThreads = 1024;
 constexpr uint32_t kWriteCommon = 1u << kHeadsPerGroup, kWriteAll = 2 * kWriteCommon - 1;
+
+// LDS of build_lut_body.  Kernels that go on to score against the coarse table have it at LDS address 0 (score_coarse), so they
+// have no static LDS and place this behind the table.
+template <int DS, bool SHARED>
+struct LutLds {
+  static constexpr int M = 128 / DS;
+  alignas(16) float q[kHeadsPerGroup][128];
+  alignas(16) int32_t min[M][kHeadsPerGroup], max[M][kHeadsPerGroup];   // (aligned: the four heads are one read)
+  alignas(16) uint32_t maxbits[kHeadsPerGroup];                         // largest |entry| per head, as float bits
+  alignas(16) int32_t shift[kHeadsPerGroup];
+  float qall[SHARED ? 8 : 1][SHARED ? 128 : 1];
+};
+template <int DS, bool SHARED>
+constexpr size_t lut_lds_bytes() { return (sizeof(LutLds<DS, SHARED>) + 15) / 16 * 16; }
 
 // SHARED: one table per KV head, built from the sum of the rotated queries of its G heads (the
 // group's summed score sum_g q~_g . c equals (sum_g q~_g) . c); the rotated queries themselves
@@ -30,7 +45,7 @@ template <int DS, bool QBF16, bool SHARED = false>
 __device__ __forceinline__ void build_lut_body(
     int prob, const void* __restrict__ q_in, const float* __restrict__ cos_b,
     const float* __restrict__ sin_b, const float* __restrict__ codebook, float* __restrict__ q_rot,
-    int32_t* __restrict__ lut, float* __restrict__ lut_scale, int B, int Hq, int Hkv, int NG,
+    int32_t* __restrict__ lut, float* __restrict__ lut_scale, int B, int Hq, int Hkv, int NG, LutLds<DS, SHARED>& S,
     uint32_t write = kWriteAll, unsigned char* coarse_lds = nullptr) {
   // write: what goes to global memory, where other workgroups write the rest: bit r the exact table of head r of the
   // group, its constants and its scale, kWriteCommon the coarse table and the rotated queries; coarse_lds: the group's coarse table is also put there, in the layout the
@@ -41,10 +56,6 @@ __device__ __forceinline__ void build_lut_body(
   constexpr int MAXQ = 65535 / M;       // a sum of M coarse entries fits 16 bits
   constexpr int LOG2M = M == 16 ? 4 : 5;
   static_assert(M == 16 || M == 32, "M is 16 or 32");
-  __shared__ float s_q[kHeadsPerGroup][D];
-  __shared__ uint32_t s_maxbits[kHeadsPerGroup];   // largest |entry| per head, as float bits
-  __shared__ int32_t s_min[M][kHeadsPerGroup], s_max[M][kHeadsPerGroup];
-  __shared__ int32_t s_shift[kHeadsPerGroup];
 
   const int Gq = Hq / Hkv;                 // query heads per KV head
   const int G = SHARED ? 1 : Gq;           // table heads per KV head
@@ -70,7 +81,6 @@ __device__ __forceinline__ void build_lut_body(
   }
 
   // --- q~ = q R_b for the (up to) four heads of this group (SHARED: all G <= 8 heads of the KV head)
-  __shared__ float s_qall[SHARED ? 8 : 1][SHARED ? D : 1];
   if (tid < (SHARED ? 8 : kHeadsPerGroup) * HALF) {
     const int r = tid / HALF, t = tid % HALF;
     const int hg = SHARED ? r : g4 * kHeadsPerGroup + r;
@@ -97,11 +107,11 @@ __device__ __forceinline__ void build_lut_body(
       }
     }
     if (SHARED) {
-      s_qall[r][t] = o1;
-      s_qall[r][t + HALF] = o2;
+      S.qall[r][t] = o1;
+      S.qall[r][t + HALF] = o2;
     } else {
-      s_q[r][t] = o1;
-      s_q[r][t + HALF] = o2;
+      S.q[r][t] = o1;
+      S.q[r][t + HALF] = o2;
     }
   }
   if (SHARED) {
@@ -110,14 +120,14 @@ __device__ __forceinline__ void build_lut_body(
       const int r = tid / D, t = tid % D;
       double sum = 0.0;
       if (r == 0)
-        for (int g = 0; g < 8; ++g) sum += (double)s_qall[g][t];   // heads past G hold zeros
-      s_q[r][t] = (float)sum;
+        for (int g = 0; g < 8; ++g) sum += (double)S.qall[g][t];   // heads past G hold zeros
+      S.q[r][t] = (float)sum;
     }
   }
-  if (tid < kHeadsPerGroup) s_maxbits[tid] = 0u;
+  if (tid < kHeadsPerGroup) S.maxbits[tid] = 0u;
   if (tid < M * kHeadsPerGroup) {
-    s_min[tid / kHeadsPerGroup][tid % kHeadsPerGroup] = INT32_MAX;
-    s_max[tid / kHeadsPerGroup][tid % kHeadsPerGroup] = INT32_MIN;
+    S.min[tid / kHeadsPerGroup][tid % kHeadsPerGroup] = INT32_MAX;
+    S.max[tid / kHeadsPerGroup][tid % kHeadsPerGroup] = INT32_MIN;
   }
   __syncthreads();
 
@@ -130,7 +140,7 @@ __device__ __forceinline__ void build_lut_body(
     for (int r = 0; r < kHeadsPerGroup; ++r) {
       double acc = 0.0;
 #pragma unroll
-      for (int t = 0; t < DS; ++t) acc += (double)s_q[r][m * DS + t] * (double)cv[k][t];
+      for (int t = 0; t < DS; ++t) acc += (double)S.q[r][m * DS + t] * (double)cv[k][t];
       val[k][r] = acc;
       mxd[r] = fmax(mxd[r], fabs(acc));
     }
@@ -148,7 +158,7 @@ __device__ __forceinline__ void build_lut_body(
 #pragma unroll
   for (int r = 0; r < kHeadsPerGroup; ++r) {
     const uint32_t v = wave_max_to_last_lane(__float_as_uint(mx[r]));
-    if ((tid & 63) == 63) atomicMax(&s_maxbits[r], v);
+    if ((tid & 63) == 63) atomicMax(&S.maxbits[r], v);
   }
   __syncthreads();
   // Every thread derives the four exponents itself (M is a power of two and v a float, so the
@@ -157,7 +167,7 @@ __device__ __forceinline__ void build_lut_body(
   int s_exp[kHeadsPerGroup];
 #pragma unroll
   for (int r = 0; r < kHeadsPerGroup; ++r) {
-    const uint32_t bits = s_maxbits[r];
+    const uint32_t bits = S.maxbits[r];
     int e = 0;
     if (bits != 0u) {
       int x;   // v * M < 2^x
@@ -193,8 +203,8 @@ __device__ __forceinline__ void build_lut_body(
       }
 #pragma unroll
     for (int r = 0; r < kHeadsPerGroup; ++r) {
-      atomicMin(&s_min[m][r], mn[r]);
-      atomicMax(&s_max[m][r], mxv[r]);
+      atomicMin(&S.min[m][r], mn[r]);
+      atomicMax(&S.max[m][r], mxv[r]);
     }
   }
   __syncthreads();
@@ -203,13 +213,13 @@ __device__ __forceinline__ void build_lut_body(
     uint32_t range = 0;
     int32_t base = 0, top = 0;
     for (int mm = 0; mm < M; ++mm) {
-      range = max(range, (uint32_t)(s_max[mm][r] - s_min[mm][r]));
-      base += s_min[mm][r];
-      top += s_max[mm][r];
+      range = max(range, (uint32_t)(S.max[mm][r] - S.min[mm][r]));
+      base += S.min[mm][r];
+      top += S.max[mm][r];
     }
     int sh = 0;
     while ((range >> sh) > (uint32_t)MAXQ) ++sh;
-    s_shift[r] = sh;
+    S.shift[r] = sh;
     const int hg = g4 * kHeadsPerGroup + r;
     if (hg < G && ((write >> r) & 1u)) {
       int32_t* meta = lut + lay.off_meta + ((size_t)b * Hq + kv * G + hg) * 4;
@@ -234,8 +244,8 @@ __device__ __forceinline__ void build_lut_body(
   // --- coarse table, [half][c][m & 15][4 heads] 16-bit: one 8-byte entry per (c, m)
   {
     uint2* coarse = (uint2*)(lut + lay.off_coarse) + (size_t)prob * ENTRIES;
-    const int sh0 = s_shift[0], sh1 = s_shift[1], sh2 = s_shift[2], sh3 = s_shift[3];
-    const int mn0 = s_min[m][0], mn1 = s_min[m][1], mn2 = s_min[m][2], mn3 = s_min[m][3];
+    const int sh0 = S.shift[0], sh1 = S.shift[1], sh2 = S.shift[2], sh3 = S.shift[3];
+    const int mn0 = S.min[m][0], mn1 = S.min[m][1], mn2 = S.min[m][2], mn3 = S.min[m][3];
 #pragma unroll
     for (int k = 0; k < EPT; ++k) {
       const int c = (tid + k * kLutThreads) / M;
@@ -253,7 +263,8 @@ __global__ __launch_bounds__(kLutThreads) void build_lut_kernel(
     const void* __restrict__ q_in, const float* __restrict__ cos_b, const float* __restrict__ sin_b,
     const float* __restrict__ codebook, float* __restrict__ q_rot, int32_t* __restrict__ lut,
     float* __restrict__ lut_scale, int B, int Hq, int Hkv, int NG) {
-  build_lut_body<DS, QBF16>(blockIdx.x, q_in, cos_b, sin_b, codebook, q_rot, lut, lut_scale, B, Hq, Hkv, NG);
+  __shared__ LutLds<DS, false> S;
+  build_lut_body<DS, QBF16>(blockIdx.x, q_in, cos_b, sin_b, codebook, q_rot, lut, lut_scale, B, Hq, Hkv, NG, S);
 }
 
 template <int DS, bool QBF16>
@@ -261,7 +272,8 @@ __global__ __launch_bounds__(kLutThreads) void build_lut_shared_kernel(
     const void* __restrict__ q_in, const float* __restrict__ cos_b, const float* __restrict__ sin_b,
     const float* __restrict__ codebook, float* __restrict__ q_rot, int32_t* __restrict__ lut,
     float* __restrict__ lut_scale, int B, int Hq, int Hkv) {
-  build_lut_body<DS, QBF16, true>(blockIdx.x, q_in, cos_b, sin_b, codebook, q_rot, lut, lut_scale, B, Hq, Hkv, 1);
+  __shared__ LutLds<DS, true> S;
+  build_lut_body<DS, QBF16, true>(blockIdx.x, q_in, cos_b, sin_b, codebook, q_rot, lut, lut_scale, B, Hq, Hkv, 1, S);
 }
 
 // An encoding workgroup of the prologues below: wave w takes the pairs (block * sweeps + s) * 16 + w.
@@ -294,8 +306,9 @@ __global__ __launch_bounds__(kLutThreads) void decode_prologue_kernel(
     float* __restrict__ lut_scale, int B, int Hq, int Hkv, int NG, int n_lut,
     const float* __restrict__ keys, const float* __restrict__ weights, int mode,
     uint8_t* __restrict__ codes, int n_new, int pos0, int64_t ctx_stride, int sweeps, int folded) {
+  __shared__ LutLds<DS, false> S;
   if ((int)blockIdx.x < n_lut) {
-    build_lut_body<DS, QBF16>(blockIdx.x, q_in, cos_b, sin_b, codebook, q_rot, lut, lut_scale, B, Hq, Hkv, NG);
+    build_lut_body<DS, QBF16>(blockIdx.x, q_in, cos_b, sin_b, codebook, q_rot, lut, lut_scale, B, Hq, Hkv, NG, S);
     // folded: the table workgroups encode as well, after their stores have been issued (their tail
     // waits for those to drain anyway)
     if (folded)
@@ -326,15 +339,17 @@ __global__ __launch_bounds__(kLutThreads) void decode_select_prologue_kernel(
     int top_k, int window, int n_sink, int sweeps, int folded) {
   constexpr int M = 128 / DS;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
+  LutLds<DS, SHARED>& S = lds_at<LutLds<DS, SHARED>>(kCoarseLdsBytes + kSampleHistBytes);
   if ((int)blockIdx.x < n_sample) {
     int prob, p;
     xcd_map_sets(blockIdx.x, P0, n_sample / P0, NG, prob, p);
-    build_lut_body<DS, QBF16, SHARED>(prob, q_in, cos_b, sin_b, codebook, q_rot, lut, lut_scale, B, Hq, Hkv, NG,
+    build_lut_body<DS, QBF16, SHARED>(prob, q_in, cos_b, sin_b, codebook, q_rot, lut, lut_scale, B, Hq, Hkv, NG, S,
                                       p == 0 ? kWriteAll : 0u, dyn_lds);
     __syncthreads();
-    sample_threshold_body<M, kLutThreads, true>(prob, p, codes, CodePages{nullptr, 0, 0}, lut, seq_lens, thr, B,
+    sample_threshold_body<M, kLutThreads, true>(prob, p, codes, CodePages{nullptr, 0, 0}, lut, seq_lens,
+                                                threshold_in(thr, prob, p, P0, NG, SHARED ? Hkv : Hq, Hkv), B,
                                                 SHARED ? Hkv : Hq, Hkv, NG, P0, sample_rows, ctx_len, ctx_stride,
-                                                top_k, window, n_sink, dyn_lds);
+                                                top_k, window, n_sink, dyn_lds, lds_at<uint32_t[2][kHistBins]>(kCoarseLdsBytes));
     if (folded)   // (see decode_prologue_kernel)
       encode_few_block<DS>((int)blockIdx.x, sweeps, keys, codebook, weights, mode, codes, B, Hkv, n_new, pos0, ctx_stride);
     return;
@@ -367,10 +382,43 @@ __global__ __launch_bounds__(kLutThreads) void decode_select_group_kernel(
     const int G = SHARED ? 1 : Hq / Hkv;
     const uint32_t mine = group_part(part, split, min(G, kHeadsPerGroup), min(kHeadsPerGroup, G - g4 * kHeadsPerGroup));
     build_lut_body<DS, QBF16, SHARED>(prob, q_in, cos_b, sin_b, codebook, q_rot, lut, lut_scale, B, Hq, Hkv, NG,
+                                      lds_at<LutLds<DS, SHARED>>(kGroupLdsBytes),
                                       part == 0 ? mine | kWriteCommon : mine, dyn_lds);
     group_select_body<M, true>(b, kv, g4, prob, mine, codes, CodePages{nullptr, 0, 0}, lut, lut_scale, seq_lens, topk_idx,
                                topk_count, topk_score, B, SHARED ? Hkv : Hq, Hkv, ctx_len, ctx_stride, top_k, window,
                                n_sink, dyn_lds);
+    if (folded)
+      encode_few_block<DS>((int)blockIdx.x, sweeps, keys, codebook, weights, mode, codes, B, Hkv, n_new, pos0,
+                           ctx_stride);
+    return;
+  }
+  encode_few_block<DS>((int)blockIdx.x - n_lut, sweeps, keys, codebook, weights, mode, codes, B, Hkv, n_new, pos0,
+                       ctx_stride);
+}
+
+// The same for long contexts of many problems (list_select.hpp).
+template <int DS, bool QBF16, bool SHARED>
+__global__ __launch_bounds__(kLutThreads) void decode_select_list_kernel(
+    const void* __restrict__ q_in, const float* __restrict__ cos_b, const float* __restrict__ sin_b,
+    const float* __restrict__ codebook, float* __restrict__ q_rot, int32_t* __restrict__ lut,
+    float* __restrict__ lut_scale, int B, int Hq, int Hkv, int NG, int n_lut, GridMap gm,
+    const float* __restrict__ keys, const float* __restrict__ weights, int mode,
+    uint8_t* __restrict__ codes, int n_new, int pos0, int64_t ctx_stride, int sweeps, int folded,
+    const int32_t* __restrict__ seq_lens, int32_t* __restrict__ topk_idx, int32_t* __restrict__ topk_count,
+    float* __restrict__ topk_score, uint32_t* __restrict__ stats, int sample_rows, int ctx_len, int top_k, int window,
+    int n_sink) {
+  constexpr int M = 128 / DS;
+  static_assert(kListThreads == kLutThreads, "one workgroup does both");
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
+  if ((int)blockIdx.x < n_lut) {
+    int prob, part, b, kv, g4;
+    map_block(blockIdx.x, gm, prob, part);
+    split_problem(prob, gm, b, kv, g4);
+    build_lut_body<DS, QBF16, SHARED>(prob, q_in, cos_b, sin_b, codebook, q_rot, lut, lut_scale, B, Hq, Hkv, NG,
+                                      lds_at<LutLds<DS, SHARED>>(kListLdsBytes), kWriteAll, dyn_lds);
+    list_select_body<M, true>(b, kv, g4, prob, codes, CodePages{nullptr, 0, 0}, lut, lut_scale, seq_lens, topk_idx, topk_count,
+                              topk_score, stats, sample_rows, B, SHARED ? Hkv : Hq, Hkv, NG, ctx_len, ctx_stride, top_k, window,
+                              n_sink, dyn_lds);
     if (folded)
       encode_few_block<DS>((int)blockIdx.x, sweeps, keys, codebook, weights, mode, codes, B, Hkv, n_new, pos0,
                            ctx_stride);
@@ -665,10 +713,11 @@ hipError_t launch_decode_select_group(const a2ats_dims& d, const float* keys, in
   hipError_t err;
 #define A2ATS_LAUNCH_GRP(DS, BF, SH, SLOT)                                                                      \
   do {                                                                                                          \
-    if ((err = allow_dynamic_lds(decode_select_group_kernel<DS, BF, SH>, kGroupLdsBytes, s_lds[SLOT])) !=       \
+    const size_t lds = kGroupLdsBytes + lut_lds_bytes<DS, SH>(); \
+    if ((err = allow_dynamic_lds(decode_select_group_kernel<DS, BF, SH>, lds, s_lds[SLOT])) !=       \
         hipSuccess)                                                                                             \
       return err;                                                                                               \
-    hipLaunchKernelGGL((decode_select_group_kernel<DS, BF, SH>), grid, block, kGroupLdsBytes, stream, q, cos_b, \
+    hipLaunchKernelGGL((decode_select_group_kernel<DS, BF, SH>), grid, block, lds, stream, q, cos_b, \
                        sin_b, codebook, q_rot, lut, lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, NG, n_lut,   \
                        make_grid_map(split, groups, NG, d.n_kv_heads), split, keys, weights, mode, codes, n_new, pos0, \
                        d.ctx_stride, ap.sweeps, ap.folded, seq_lens, topk_idx, topk_count, topk_score, d.ctx_len, \
@@ -686,6 +735,45 @@ hipError_t launch_decode_select_group(const a2ats_dims& d, const float* keys, in
   }
 #undef A2ATS_LAUNCH_GRP2
 #undef A2ATS_LAUNCH_GRP
+  return hipGetLastError();
+}
+
+hipError_t launch_decode_select_list(const a2ats_dims& d, const TopkPlan& plan, const float* keys, int n_new, int pos0,
+                                     const float* codebook, const float* weights, int mode, uint8_t* codes, const void* q,
+                                     int q_dtype, const float* cos_b, const float* sin_b, float* q_rot, int32_t* lut,
+                                     float* lut_scale, const int32_t* seq_lens, int top_k, int window, int n_sink,
+                                     int32_t* topk_idx, int32_t* topk_count, float* topk_score, uint32_t* stats, bool shared,
+                                     hipStream_t stream) {
+  const int n_lut = d.batch * d.n_kv_heads * plan.NG;
+  const AppendPlan ap = append_plan((long)d.batch * d.n_kv_heads * n_new * d.n_sub, n_lut);
+  const dim3 grid(n_lut + ap.n_enc), block(kLutThreads);
+  if (grid.x == 0) return hipSuccess;
+  static LdsSlot s_lds[8][16];
+  hipError_t err;
+#define A2ATS_LAUNCH_LIST(DS, BF, SH, SLOT)                                                                    \
+  do {                                                                                                         \
+    const size_t lds = kListLdsBytes + lut_lds_bytes<DS, SH>(); \
+    if ((err = allow_dynamic_lds(decode_select_list_kernel<DS, BF, SH>, lds, s_lds[SLOT])) !=        \
+        hipSuccess)                                                                                            \
+      return err;                                                                                              \
+    hipLaunchKernelGGL((decode_select_list_kernel<DS, BF, SH>), grid, block, lds, stream, q, cos_b,  \
+                       sin_b, codebook, q_rot, lut, lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, plan.NG, n_lut, \
+                       make_grid_map(1, n_lut, plan.NG, d.n_kv_heads), keys, weights, mode, codes, n_new, pos0, \
+                       d.ctx_stride, ap.sweeps, ap.folded, seq_lens, topk_idx, topk_count, topk_score, stats,  \
+                       plan.list_rows, d.ctx_len, top_k, window, n_sink);                                      \
+  } while (0)
+#define A2ATS_LAUNCH_LIST2(DS, BF, SLOT)                   \
+  do {                                                     \
+    if (shared) A2ATS_LAUNCH_LIST(DS, BF, true, SLOT + 4); \
+    else A2ATS_LAUNCH_LIST(DS, BF, false, SLOT);           \
+  } while (0)
+  if (d.sub_dim == 8) {
+    if (q_dtype == A2ATS_BF16) A2ATS_LAUNCH_LIST2(8, true, 0); else A2ATS_LAUNCH_LIST2(8, false, 1);
+  } else {
+    if (q_dtype == A2ATS_BF16) A2ATS_LAUNCH_LIST2(4, true, 2); else A2ATS_LAUNCH_LIST2(4, false, 3);
+  }
+#undef A2ATS_LAUNCH_LIST2
+#undef A2ATS_LAUNCH_LIST
   return hipGetLastError();
 }
 
@@ -710,10 +798,11 @@ hipError_t launch_decode_select_prologue(const a2ats_dims& d, const float* keys,
   hipError_t err;
 #define A2ATS_LAUNCH_SEL(DS, BF, SH, SLOT)                                                                   \
   do {                                                                                                       \
-    if ((err = allow_dynamic_lds(decode_select_prologue_kernel<DS, BF, SH>, (size_t)kCoarseLdsBytes,         \
+    const size_t lds = kCoarseLdsBytes + kSampleHistBytes + lut_lds_bytes<DS, SH>(); \
+    if ((err = allow_dynamic_lds(decode_select_prologue_kernel<DS, BF, SH>, lds,         \
                                  s_lds[SLOT])) != hipSuccess)                                                \
       return err;                                                                                            \
-    hipLaunchKernelGGL((decode_select_prologue_kernel<DS, BF, SH>), grid, block, kCoarseLdsBytes, stream, q, \
+    hipLaunchKernelGGL((decode_select_prologue_kernel<DS, BF, SH>), grid, block, lds, stream, q, \
                        cos_b, sin_b, codebook, q_rot, lut, lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, NG, \
                        n_sample, keys, weights, mode, codes, n_new, pos0, d.ctx_stride, seq_lens, thr, P0,   \
                        sample_rows, d.ctx_len, top_k, window, n_sink, ap.sweeps, ap.folded);                               \

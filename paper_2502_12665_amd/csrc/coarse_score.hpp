@@ -25,6 +25,7 @@ constexpr float kSigma = 5.0f;   // margin of the sampled rank, in standard devi
 // integer sums.  One v_perm_b32 assembles the whole LDS address of a read from the code byte and a
 // per-lane constant.
 constexpr int kCoarseLdsBytes = kCentroids * 256;
+constexpr size_t kSampleHistBytes = 2 * kHistBins * sizeof(uint32_t);
 
 // Byte offset of the coarse entry of (centroid c, subspace m) in the LDS table.
 __device__ __forceinline__ uint32_t coarse_lds_offset(int c, int m) {
@@ -69,12 +70,10 @@ struct LaneSwizzle {
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) const u32x2_t* lds_u2_ptr;
 
-// kBaseZero: the table starts at LDS address 0 (kernel without static LDS), so the v_perm result
-// is the address itself; otherwise it is an offset from `tbl`.  `w` holds the lane's code row as
-// loaded under LaneSwizzle::row_swz.
-template <int M, bool kBaseZero>
-__device__ __forceinline__ void score_coarse(const uint4 (&w)[M / 16], const unsigned char* tbl,
-                                             const LaneSwizzle<M>& sw, uint32_t& a01, uint32_t& a23) {
+// The table starts at LDS address 0 (kernels without static LDS), so the v_perm result is the address itself.  `w` holds the
+// lane's code row as loaded under LaneSwizzle::row_swz.
+template <int M>
+__device__ __forceinline__ void score_coarse(const uint4 (&w)[M / 16], const LaneSwizzle<M>& sw, uint32_t& a01, uint32_t& a23) {
   a01 = 0;
   a23 = 0;
 #pragma unroll
@@ -86,10 +85,7 @@ __device__ __forceinline__ void score_coarse(const uint4 (&w)[M / 16], const uns
     const uint32_t z[4] = {sw.swap2 ? x2 : x0, sw.swap2 ? x3 : x1, sw.swap2 ? x0 : x2, sw.swap2 ? x1 : x3};
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
-      const uint32_t off = __builtin_amdgcn_perm(z[t >> 2], sw.mc[qd * 4 + (t >> 2)], sw.sel[t & 3]);
-      u32x2_t e;
-      if (kBaseZero) e = *(lds_u2_ptr)(uintptr_t)off;
-      else e = *(const u32x2_t*)(tbl + off);
+      const u32x2_t e = *(lds_u2_ptr)(uintptr_t)__builtin_amdgcn_perm(z[t >> 2], sw.mc[qd * 4 + (t >> 2)], sw.sel[t & 3]);
       a01 += e.x;
       a23 += e.y;
     }
@@ -136,16 +132,15 @@ __device__ __forceinline__ int wave_find_bin(const uint32_t* hist, int shift, ui
 }
 
 // One sampling workgroup: part p of the P0 parts of problem `prob` (a sequence, KV head and group
-// of four query heads).  `tbl`: kCoarseLdsBytes of LDS for the group's coarse table; TABLE_IN_LDS:
-// the caller has put the table there already (and synchronised), otherwise it is copied from `lut`.
-template <int M, int NT, bool TABLE_IN_LDS>
+// of four query heads).  put(r, t): head r's estimate of the threshold, INT32_MIN to take every row; called by one thread of
+// the workgroup for each head.  `tbl`: kCoarseLdsBytes of LDS for the group's coarse table; TABLE_IN_LDS:
+// the caller has put the table there already (and synchronised), otherwise it is copied from `lut`.  `hist`: LDS.
+template <int M, int NT, bool TABLE_IN_LDS, typename Put>
 __device__ __forceinline__ void sample_threshold_body(
     int prob, int p, const uint8_t* __restrict__ codes, const CodePages& pg, const int32_t* __restrict__ lut,
-    const int32_t* __restrict__ seq_lens, int32_t* __restrict__ thr, int B, int Hq, int Hkv, int NG,
+    const int32_t* __restrict__ seq_lens, Put put, int B, int Hq, int Hkv, int NG,
     int P0, int sample_rows, int ctx_len, int64_t ctx_stride, int top_k, int window, int n_sink,
-    unsigned char* tbl) {
-  __shared__ uint32_t s_hist[2][kHistBins];   // two heads per word, 16-bit counts (a workgroup scores at most 8192 rows)
-
+    unsigned char* tbl, uint32_t (*hist)[kHistBins]) {   // hist: two heads per word, 16-bit counts (a workgroup scores at most 8192 rows)
   const int g4 = prob % NG, kv = (prob / NG) % Hkv, b = prob / (NG * Hkv);
   const int G = Hq / Hkv, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const SeqRange sr = seq_range(ctx_len, seq_lens, b, window, n_sink, top_k);
@@ -165,7 +160,7 @@ __device__ __forceinline__ void sample_threshold_body(
   if (take_all) {
     if (tid < kHeadsPerGroup) {
       const int hg = g4 * kHeadsPerGroup + tid;
-      if (hg < G) thr[((size_t)b * Hq + kv * G + hg) * P0 + p] = INT32_MIN;
+      if (hg < G) put(tid, INT32_MIN);
     }
     return;
   }
@@ -173,7 +168,7 @@ __device__ __forceinline__ void sample_threshold_body(
   const int n_real = min(kHeadsPerGroup, G - g4 * kHeadsPerGroup);   // heads of this group that exist
   const LutLayout lay = lut_layout(B, Hq, Hkv, M);
   if (!TABLE_IN_LDS) load_coarse_table<M, NT>(lut, lay, prob, tbl);
-  for (int i = tid; i < 2 * kHistBins; i += NT) (&s_hist[0][0])[i] = 0;
+  for (int i = tid; i < 2 * kHistBins; i += NT) (&hist[0][0])[i] = 0;
   __syncthreads();
 
   // Score this workgroup's share of the strided sample.  A coarse score is below 2^16, so
@@ -213,13 +208,13 @@ __device__ __forceinline__ void sample_threshold_body(
     for (int u = 0; u < kPair; ++u) {
       if (i0 + u * NT >= s_p) continue;
       uint32_t a01, a23;
-      score_coarse<M, false>(w[u], tbl, sw, a01, a23);
+      score_coarse<M>(w[u], sw, a01, a23);
       // (a head slot past the group's last head has an all-zero table: every row would land in the same
       // bin, a thousand atomics on one address for a histogram nobody reads)
-      atomicAdd(&s_hist[0][(a01 & 0xffffu) >> 5], 1u);
-      if (n_real > 1) atomicAdd(&s_hist[0][a01 >> 21], 1u << 16);
-      if (n_real > 2) atomicAdd(&s_hist[1][(a23 & 0xffffu) >> 5], 1u);
-      if (n_real > 3) atomicAdd(&s_hist[1][a23 >> 21], 1u << 16);
+      atomicAdd(&hist[0][(a01 & 0xffffu) >> 5], 1u);
+      if (n_real > 1) atomicAdd(&hist[0][a01 >> 21], 1u << 16);
+      if (n_real > 2) atomicAdd(&hist[1][(a23 & 0xffffu) >> 5], 1u);
+      if (n_real > 3) atomicAdd(&hist[1][a23 >> 21], 1u << 16);
     }
   }
   __syncthreads();
@@ -227,15 +222,20 @@ __device__ __forceinline__ void sample_threshold_body(
   if (wv < kHeadsPerGroup) {
     const int r = wv;
     const int hg = g4 * kHeadsPerGroup + r;
-    const uint32_t* hrow = s_hist[r >> 1];
+    const uint32_t* hrow = hist[r >> 1];
     const int fsh = 16 * (r & 1);
     const int bin = wave_find_bin(hrow, fsh, (uint32_t)r_p, lane);
     // Lower edge of the bin holding the r_p-th largest sample (at least r_p samples reach it),
     // lowered by M: a row's coarse score is below its exact score by less than M coarse units,
     // and the final kernel needs that much slack to prove its result complete.
-    if (lane == 0 && bin >= 0 && hg < G) thr[((size_t)b * Hq + kv * G + hg) * P0 + p] = max(0, (bin << 5) - M);
+    if (lane == 0 && bin >= 0 && hg < G) put(r, max(0, (bin << 5) - M));
   }
 }
 
+// Where sample_threshold_body's part p of a problem puts its estimates in global memory, [B * Hq][P0].
+__device__ __forceinline__ auto threshold_in(int32_t* __restrict__ thr, int prob, int p, int P0, int NG, int Hq, int Hkv) {
+  int32_t* at = thr + ((size_t)(prob / NG) * (Hq / Hkv) + (size_t)(prob % NG) * kHeadsPerGroup) * P0 + p;
+  return [=](int r, int32_t t) { at[(size_t)r * P0] = t; };
+}
 
 }  // namespace a2ats

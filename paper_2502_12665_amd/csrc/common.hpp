@@ -24,6 +24,13 @@ __device__ __forceinline__ int lanes_below(uint64_t mask) {
                                    __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// An object at a constant LDS address, of a kernel without static LDS: reads and writes take the address as their offset.  (The
+// start of the dynamic LDS is a symbol to the compiler, 0 or not: behind it every access has an addition.)
+template <typename T>
+__device__ __forceinline__ T& lds_at(uint32_t address) {
+  return *(T*)(__attribute__((address_space(3))) T*)(uintptr_t)address;
+}
+
 // Word offsets (int32 units) of the three parts of the lookup-table blob, see a2ats.h.
 struct LutLayout {
   size_t off_exact;   // [B*Hq][256][M] int32

@@ -34,6 +34,7 @@
 #include "common.hpp"
 #include "coarse_score.hpp"
 #include "exact_select.hpp"
+#include "band_select.hpp"
 
 namespace a2ats {
 
@@ -44,13 +45,13 @@ constexpr int kGroupThreads = 1024;
 constexpr int kGroupWaves = kGroupThreads / 64;
 constexpr int kGroupRows = 16;                               // rows per thread
 constexpr int kGroupMaxCand = kGroupThreads * kGroupRows;    // candidates of a sequence, at most
-constexpr int kBandCap = 1024;                               // band rows per head
 struct GroupLds {
   uint32_t hist[2][kHistBins];   // two heads per word, 16-bit counts (at most 16384 rows)
   uint64_t won[kHeadsPerGroup][kGroupMaxCand / 64];
-  uint64_t band[kHeadsPerGroup][kBandCap];   // a position, then (exact key, position complemented)
+  uint64_t band[kHeadsPerGroup][kBandCap];
   uint32_t n_band[kHeadsPerGroup];
   uint32_t n_sure[kHeadsPerGroup];
+  uint32_t from[kHeadsPerGroup];   // where the band begins
   int32_t bin[kHeadsPerGroup];
   uint32_t wave_tot[kGroupWaves];
 };
@@ -83,7 +84,7 @@ __device__ __forceinline__ void group_select_body(
   constexpr int NT = kGroupThreads;
   constexpr int U = M == 16 ? 4 : 1;   // rows a thread requests together
   unsigned char* tbl = dyn_lds;
-  GroupLds& L = *(GroupLds*)(dyn_lds + kCoarseLdsBytes);
+  GroupLds& L = lds_at<GroupLds>(kCoarseLdsBytes);
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int G = Hq / Hkv, head0 = b * Hq + kv * G + g4 * kHeadsPerGroup;
   const SeqRange sr = seq_range(ctx_len, seq_lens, b, window, n_sink, top_k);
@@ -135,7 +136,7 @@ __device__ __forceinline__ void group_select_body(
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         if (i0 + u >= n_i) continue;   // (a chunk past the wave's last is another wave's)
-        score_coarse<M, false>(rows[q & 1][u], tbl, sw, a01[i0 + u], a23[i0 + u]);
+        score_coarse<M>(rows[q & 1][u], sw, a01[i0 + u], a23[i0 + u]);
         if (!take_all && row0 + (i0 + u) * 64 < hi) {
           const uint32_t w01 = a01[i0 + u], w23 = a23[i0 + u];
           if (mine & 1u) atomicAdd(&L.hist[0][(w01 & 0xffffu) >> 5], 1u);
@@ -163,6 +164,7 @@ __device__ __forceinline__ void group_select_body(
     const bool is_mine = (mine >> r) & 1u;
     const int bin = take_all ? 0 : __builtin_amdgcn_readfirstlane(L.bin[r]);   // (of another head: not looked at)
     kth_bin[r] = bin;
+    if (is_mine && tid == r) L.from[r] = take_all ? 0u : (uint32_t)max(0, (bin << 5) - M + 1);
     t_lo[r] = !is_mine ? 0xffffu : (take_all ? 0u : (uint32_t)max(0, (bin << 5) - M + 1));
     t_hi[r] = !is_mine ? 0xffffu : (take_all ? 0u : (uint32_t)min(0xffff, (bin << 5) + 32 + M));
   }
@@ -206,75 +208,11 @@ __device__ __forceinline__ void group_select_body(
   }
   __syncthreads();
 
-  // --- the band: exact keys, then every row counts those before it in (score, position) order
-  uint32_t first[kHeadsPerGroup + 1];
-  uint32_t redo = 0;
-  first[0] = 0;
-#pragma unroll
-  for (int r = 0; r < kHeadsPerGroup; ++r) {
-    const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.n_band[r]);
-    redo |= n > (uint32_t)kBandCap ? 1u << r : 0u;
-    first[r + 1] = first[r] + (n > (uint32_t)kBandCap ? 0u : n);
-  }
-  auto head_of = [&](uint32_t e) {
-    return (e >= first[1] ? 1 : 0) + (e >= first[2] ? 1 : 0) + (e >= first[3] ? 1 : 0);
-  };
-  auto first_of = [&](int r) { return r == 0 ? 0u : (r == 1 ? first[1] : (r == 2 ? first[2] : first[3])); };
-  auto exact_at = [&](int r, int j) {
-    const int32_t* t = lut + lay.off_exact + (size_t)(head0 + r) * (kCentroids * M);
-    const uint8_t* row = row_ptr<M>(seq_codes, j);
-    uint4 w[M / 16];
-    int32_t s = 0;
-#pragma unroll
-    for (int qd = 0; qd < M / 16; ++qd) w[qd] = *(const uint4*)(row + qd * 16);
-#pragma unroll
-    for (int qd = 0; qd < M / 16; ++qd) {
-      const uint32_t d[4] = {w[qd].x, w[qd].y, w[qd].z, w[qd].w};
-#pragma unroll
-      for (int t4 = 0; t4 < 16; ++t4) s += t[((d[t4 >> 2] >> (8 * (t4 & 3))) & 0xffu) * M + qd * 16 + t4];
-    }
-    return s;
-  };
-  for (uint32_t e = tid; e < first[4]; e += NT) {
-    const int r = head_of(e);
-    const uint32_t i = e - first_of(r);
-    const uint32_t j = (uint32_t)L.band[r][i];
-    L.band[r][i] = ((uint64_t)score_key(exact_at(r, (int)j)) << 32) | ~j;   // (of equal scores the lower position is larger)
-  }
-  __syncthreads();
-  // (eight lanes share a row: the lists are short and every step is an LDS round trip)
-  for (uint32_t e = tid >> 3; e < first[4]; e += NT / 8) {
-    const int r = head_of(e);
-    const uint32_t f = first_of(r), i = e - f, n = (r == 0 ? first[1] : (r == 1 ? first[2] : (r == 2 ? first[3] : first[4]))) - f;
-    const uint64_t own = L.band[r][i];
-    int32_t before = 0;
-#pragma unroll 4
-    for (uint32_t u = tid & 7; u < n; u += 8) before += L.band[r][u] > own ? 1 : 0;
-    before = group8_sum(before);
-    if ((tid & 7) == 0 && (uint32_t)before < (uint32_t)sr.kk - L.n_sure[r]) {
-      const uint32_t bit = ~(uint32_t)own - (uint32_t)lo;
-      atomicOr((uint32_t*)&L.won[r][0] + (bit >> 5), 1u << (bit & 31));
-    }
-  }
-  __syncthreads();
-
-  // --- winners in ascending position: head tid / 256, 64 positions per thread
-  {
-    const int r = tid >> 8, q = tid & 255;
-    uint64_t word = (q < kGroupWaves * n_i && ((mine & ~redo) >> r & 1u)) ? L.won[r][q] : 0ull;
-    const uint32_t n = (uint32_t)__popcll(word);
-    const uint32_t inc = wave_inclusive_scan(n);
-    if (lane == 63) L.wave_tot[wv] = inc;
-    __syncthreads();
-    uint32_t at = inc - n;
-    for (int w = wv & ~3; w < wv; ++w) at += L.wave_tot[w];
-    int32_t* oi = topk_idx + (size_t)(head0 + r) * top_k;
-    while (word) {
-      if (at < (uint32_t)sr.kk) oi[at] = lo + q * 64 + __ffsll((unsigned long long)word) - 1;
-      ++at;
-      word &= word - 1;
-    }
-  }
+  // --- the band, and the winners in ascending position
+  const Band band = {&L.band[0][0], &L.won[0][0], kGroupMaxCand / 64, L.n_band, L.n_sure, L.from, 32u + 2 * M,
+                     (int32_t*)tbl, L.hist, L.wave_tot};
+  const uint32_t redo = band_winners<M, M == 32>(band, mine, head0, seq_codes, lo, sr.kk, lut, lay);
+  write_winners<kGroupMaxCand / 64 / 256>(band, mine & ~redo, head0, lo, sr.ncand, sr.kk, top_k, topk_idx);
   // --- heads with more band rows than the list holds (many equal scores): the exact route.  The K-th coarse score is in the
   // bin, hence the K-th score is at least the bin's lower edge, and its own row's is below the upper edge.
 #pragma unroll 1
@@ -295,10 +233,7 @@ __device__ __forceinline__ void group_select_body(
     }
   if (topk_score) {
     __syncthreads();
-    for (int r = 0; r < kHeadsPerGroup; ++r)
-      for (int t = ((mine >> r) & 1u) ? tid : sr.kk; t < sr.kk; t += NT)
-        topk_score[(size_t)(head0 + r) * top_k + t] =
-            (float)exact_at(r, topk_idx[(size_t)(head0 + r) * top_k + t]) * lut_scale[head0 + r];
+    write_winner_scores<M>(mine, head0, seq_codes, sr.kk, top_k, lut, lay, lut_scale, topk_idx, topk_score);
   }
 }
 

@@ -27,6 +27,8 @@ struct TopkPlan {
   int sub_rows;         // rows of a wave (rows_per_chunk / 8)
   int cap;              // survivor capacity per head in the final kernel's LDS
   int row_cap;          // row entries of one survivor segment in HBM
+  bool list;            // one workgroup for a head group instead (list_select.hpp)
+  int list_rows;        // rows it samples
   size_t off_thr, off_route, off_count, off_cand, bytes;
 };
 
@@ -94,6 +96,13 @@ hipError_t launch_decode_select_head(const a2ats_dims& d, const float* keys, int
                                      const float* cos_b, const float* sin_b, float* q_rot, int32_t* lut, float* lut_scale,
                                      const int32_t* seq_lens, int top_k, int window, int n_sink, int32_t* topk_idx,
                                      int32_t* topk_count, float* topk_score, bool shared, hipStream_t stream);
+// The same where the plan (of these dims; shared: one head per KV head) takes the list route; stats: its statistics.
+hipError_t launch_decode_select_list(const a2ats_dims& d, const TopkPlan& plan, const float* keys, int n_new, int pos0,
+                                     const float* codebook, const float* weights, int mode, uint8_t* codes, const void* q,
+                                     int q_dtype, const float* cos_b, const float* sin_b, float* q_rot, int32_t* lut,
+                                     float* lut_scale, const int32_t* seq_lens, int top_k, int window, int n_sink,
+                                     int32_t* topk_idx, int32_t* topk_count, float* topk_score, uint32_t* stats, bool shared,
+                                     hipStream_t stream);
 hipError_t launch_sparse_attn(const a2ats_dims& d, const void* q, const float* q_rot, const void* k_cache,
                               const void* v_cache, int kv_dtype, const int32_t* topk_idx,
                               const int32_t* topk_count, int top_k, int window, int n_sink,

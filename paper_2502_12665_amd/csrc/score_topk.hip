@@ -1,17 +1,20 @@
 // Step 3 of a decode step: approximate scores by gather-summing fixed-point table entries
 // through the uint8 codes (section 4.2 last equation), and exact per-head top-K (section 4).
 //
-// Three routes, chosen on the host from the shape:
+// Four routes, chosen on the host from the shape:
 //
 //  group route (at most 16384 candidates, see takes_group_route): one workgroup for the four heads of a group,
 //  group_select.hpp.
+//
+//  list route (up to 65536 candidates of more than 64 head groups, see list_route): one workgroup for the four heads of a
+//  group again, list_select.hpp.
 //
 //  exact route (the other short contexts, more than 2048 winners without a workspace, and the in-kernel fallback):
 //  one workgroup per query head runs an MSB-first radix select over the 32-bit score keys by
 //  re-streaming its sequence (<= 3 histogram passes), then one ordered pass that emits the
 //  winners in ascending position, equal scores going to the lower position.
 //
-//  fast route (long contexts): the code matrix is streamed from HBM once, against a 16-bit
+//  fast route (the other long contexts): the code matrix is streamed from HBM once, against a 16-bit
 //  coarse copy of the tables, and only the survivors are scored exactly.
 //    1. sample_threshold_kernel scores a sample of each sequence (about 1/8 of it, taken in
 //       128-byte runs spread evenly over the candidates) with the coarse tables and derives, per
@@ -40,6 +43,7 @@
 #include "coarse_score.hpp"
 #include "exact_select.hpp"
 #include "group_select.hpp"
+#include "list_select.hpp"
 
 namespace a2ats {
 
@@ -48,6 +52,27 @@ constexpr int kStreamWaves = kStreamThreads / 64;
 constexpr int kSampleThreads = 512;
 constexpr int kSegMeta = 8;          // words of a segment header: rows, 4 per-head counts, padding
 constexpr int kSampleRows = 1024;    // smallest sample of a problem; a sampling workgroup scores up to 8 of these
+
+// Whether a streaming selection is taken by one workgroup for a head group (list_select.hpp), and the sample that it takes.
+// Up to 64 groups the final kernel's workgroups, one a head, fit one round of the CUs, and the streaming pass has several CUs
+// for a group.  Beyond that the heads need further rounds, while the groups fill one; the longer the context, the more groups
+// it takes.  Selections (tables included), us, streaming -> list route, 32 query and 8 KV heads, K 3 %, M = 16: 64 groups
+// 17000, 32768 tokens 35.5 -> 42.1, 39.6 -> 51.8; 80 groups 17000, 24000 47.7 -> 42.5, 48.8 -> 43.8; 96 groups 20000, 32768,
+// 40000 49.0 -> 43.2, 59.9 -> 53.0, 61.9 -> 60.7; 112 groups 50000 70.2 -> 70.4; 128 groups 32768, 60000 58.2 -> 54.7, 78.0 ->
+// 81.9; 192 groups 40000 91.5 -> 66.3; 256 groups 32768 110.5 -> 70.3; two rounds: 264 groups 32768 129.2 -> 117.7, 512 of 16500
+// 156.0 -> 106.1.  M = 32: 96 groups 24000 74.4 -> 66.9, 65536 108.0 -> 128.3; 112 groups 50000 108.4 -> 101.3, 65536 118.8 -> 128.8; 144
+// groups 65536 138.3 -> 129.2; 256 groups (7 heads a KV head) 65536 192.5 -> 143.8.  One selection per KV head: 128 groups 32768
+// 53.1 -> 45.1, 256 90.0 -> 57.4; in pages of 16 tokens 128 groups 32768 59.8 -> 63.3, 192 91.7 -> 65.4.
+// A list holds kListCap rows: what the sample lets through (see below), five standard deviations more, and 8 % for the
+// threshold's rounding to a bin.
+static void list_route(const a2ats_dims& d, TopkPlan& p, long ncand, int top_k) {
+  const long problems = (long)d.batch * d.n_kv_heads * p.NG;
+  p.list_rows = (int)std::min<long>(std::max<long>(ncand / 8 / 512 * 512, kSampleRows), kSampleMost);
+  const double r0 = (double)top_k * p.list_rows / (double)ncand;
+  const double xr = 0.5 * (kSigma + std::sqrt(kSigma * kSigma + 4.0 * r0));
+  const double rows = (xr * xr + 5.0 * xr) / p.list_rows * (double)ncand * 1.08;
+  p.list = problems > 64 && ncand <= kListMaxCand && ncand <= 500 * problems - 8000 && rows <= kListCap;
+}
 
 TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink) {
   TopkPlan p{};
@@ -124,6 +149,7 @@ TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink) 
     const size_t heads = (size_t)d.batch * d.n_q_heads;
     const size_t segs = (size_t)problems * p.chunks * kStreamWaves;
     const size_t entry_bytes = 4 + d.n_sub;   // header + code bytes
+    list_route(d, p, ncand, top_k);
     p.off_thr = 0;
     p.off_route = (p.off_thr + heads * p.P0 * sizeof(int32_t) + 255) / 256 * 256;
     p.off_count = (p.off_route + heads * sizeof(uint32_t) + 255) / 256 * 256;
@@ -243,6 +269,23 @@ __global__ __launch_bounds__(kGroupThreads) void group_select_kernel(
 }
 
 // ------------------------------------------------------------------------------------------
+// Long contexts of many problems: one workgroup per problem
+// ------------------------------------------------------------------------------------------
+template <int M>
+__global__ __launch_bounds__(kListThreads) void list_select_kernel(
+    const uint8_t* __restrict__ codes, const int32_t* __restrict__ lut, const float* __restrict__ lut_scale,
+    const int32_t* __restrict__ seq_lens, int32_t* __restrict__ topk_idx, int32_t* __restrict__ topk_count,
+    float* __restrict__ topk_score, uint32_t* __restrict__ stats, GridMap gm, CodePages pg, int sample_rows, int B, int Hq,
+    int Hkv, int NG, int ctx_len, int64_t ctx_stride, int top_k, int window, int n_sink) {
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
+  int prob, part, b, kv, g4;
+  map_block(blockIdx.x, gm, prob, part);
+  split_problem(prob, gm, b, kv, g4);
+  list_select_body<M, false>(b, kv, g4, prob, codes, pg, lut, lut_scale, seq_lens, topk_idx, topk_count, topk_score, stats,
+                             sample_rows, B, Hq, Hkv, NG, ctx_len, ctx_stride, top_k, window, n_sink, dyn_lds);
+}
+
+// ------------------------------------------------------------------------------------------
 // Debug: dense exact scores for every token (not on the fast path; used by parity tests)
 // ------------------------------------------------------------------------------------------
 template <int M>
@@ -279,8 +322,9 @@ __global__ __launch_bounds__(kSampleThreads) void sample_threshold_kernel(
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   int p, prob;
   xcd_map_sets(blockIdx.x, P0, problems, NG, prob, p);
-  sample_threshold_body<M, kSampleThreads, false>(prob, p, codes, pg, lut, seq_lens, thr, B, Hq, Hkv, NG, P0, sample_rows,
-                                                  ctx_len, ctx_stride, top_k, window, n_sink, dyn_lds);
+  sample_threshold_body<M, kSampleThreads, false>(prob, p, codes, pg, lut, seq_lens, threshold_in(thr, prob, p, P0, NG, Hq, Hkv),
+                                                  B, Hq, Hkv, NG, P0, sample_rows, ctx_len, ctx_stride, top_k, window, n_sink,
+                                                  dyn_lds, lds_at<uint32_t[2][kHistBins]>(kCoarseLdsBytes));
 }
 
 // ------------------------------------------------------------------------------------------
@@ -381,7 +425,7 @@ __device__ __forceinline__ void stream_select_body(
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         uint32_t a01, a23;
-        score_coarse<M, true>(rows[u], tbl, sw, a01, a23);
+        score_coarse<M>(rows[u], sw, a01, a23);
         const uint64_t valid = __builtin_amdgcn_ballot_w64(base + u * 64 + lane < wend);
         hit[u][0] = __builtin_amdgcn_ballot_w64((int32_t)(a01 & 0xffffu) >= T[0]) & valid;
         hit[u][1] = __builtin_amdgcn_ballot_w64((int32_t)(a01 >> 16) >= T[1]) & valid;
@@ -730,6 +774,11 @@ __global__ void fill_words_kernel(uint32_t* __restrict__ out, uint32_t value, in
   if (i < n) out[i] = value;
 }
 
+__global__ void copy_words_kernel(const uint32_t* __restrict__ in, uint32_t* __restrict__ out, int n) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) out[i] = in[i];
+}
+
 __global__ void sum_segments_kernel(const uint32_t* __restrict__ seg_meta, const uint32_t* __restrict__ route,
                                     uint32_t* __restrict__ out, int B, int Hq, int Hkv, int NG, int n_seg) {
   const int bh = blockIdx.x * blockDim.x + threadIdx.x;
@@ -746,6 +795,11 @@ hipError_t copy_topk_stats(const a2ats_dims& d, int top_k, int window, int n_sin
   const TopkPlan plan = make_topk_plan(d, top_k, window, n_sink);
   const int heads = d.batch * d.n_q_heads;
   if (heads == 0) return hipSuccess;
+  if (plan.fast && plan.list) {
+    hipLaunchKernelGGL(copy_words_kernel, dim3((heads + 255) / 256), dim3(256), 0, stream,
+                       (const uint32_t*)((const unsigned char*)ws + plan.off_route), cand_counts, heads);
+    return hipGetLastError();
+  }
   if (!plan.fast) {   // (a fill kernel, not a memset node: the call may be captured into a graph)
     hipLaunchKernelGGL(fill_words_kernel, dim3((heads + 255) / 256), dim3(256), 0, stream, cand_counts, 0xffffffffu,
                        heads);
@@ -770,7 +824,8 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
   const size_t coarse_bytes = (size_t)kCoarseLdsBytes;
   const size_t lut1_bytes = kExactLdsBytes;
   hipError_t err;
-  static LdsSlot s_dense[16], s_exact[16], s_sample[16], s_stream[16], s_stream_r[16], s_stream_p[16], s_final[16], s_group[16];
+  static LdsSlot s_dense[16], s_exact[16], s_sample[16], s_stream[16], s_stream_r[16], s_stream_p[16], s_final[16], s_group[16],
+      s_list[16];
   if (heads == 0) return hipSuccess;
 
   if (scores_out) {
@@ -800,15 +855,24 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
   }
 
   unsigned char* wsb = (unsigned char*)ws;
+  if (plan.list) {
+    if ((err = allow_dynamic_lds(list_select_kernel<M>, kListLdsBytes, s_list)) != hipSuccess) return err;
+    // (hipExtLaunchKernelGGL: the pair of events, where there is one, is attached to the dispatch)
+    hipExtLaunchKernelGGL((list_select_kernel<M>), dim3(problems), dim3(kListThreads), kListLdsBytes, stream, ev_start, ev_stop,
+                          0, codes, lut, lut_scale, seq_lens, topk_idx, topk_count, topk_score,
+                          (uint32_t*)(wsb + plan.off_route), make_grid_map(1, problems, NG, Hkv), pg, plan.list_rows, B, Hq,
+                          Hkv, NG, d.ctx_len, d.ctx_stride, top_k, window, n_sink);
+    return hipGetLastError();
+  }
   int32_t* thr = (int32_t*)(wsb + plan.off_thr);
   uint32_t* seg_meta = (uint32_t*)(wsb + plan.off_count);
   uint32_t* route = (uint32_t*)(wsb + plan.off_route);
   uint32_t* cand = (uint32_t*)(wsb + plan.off_cand);
 
   if (!presampled) {   // (the fused decode launch has written the thresholds already)
-    if ((err = allow_dynamic_lds(sample_threshold_kernel<M>, coarse_bytes, s_sample)) != hipSuccess) return err;
+    if ((err = allow_dynamic_lds(sample_threshold_kernel<M>, coarse_bytes + kSampleHistBytes, s_sample)) != hipSuccess) return err;
     hipLaunchKernelGGL((sample_threshold_kernel<M>), dim3(plan.P0 * problems), dim3(kSampleThreads),
-                       coarse_bytes, stream, codes, lut, seq_lens, thr, pg, B, Hq, Hkv, NG, plan.P0, plan.sample_rows,
+                       coarse_bytes + kSampleHistBytes, stream, codes, lut, seq_lens, thr, pg, B, Hq, Hkv, NG, plan.P0, plan.sample_rows,
                        problems, d.ctx_len, d.ctx_stride, top_k, window, n_sink);
     if ((err = hipGetLastError()) != hipSuccess) return err;
   }

@@ -209,6 +209,7 @@ def test_attention_of_many_heads_equals_that_of_few(G, Hkv, N, K, w, n_sink, dty
     (2, 4, 16, 40000, 4000, 4),       # without a workspace the exact route, its keys scored again and again
     (40, 4, 16, 12000, 300, 4),       # a workgroup per group
     (2, 4, 16, 60000, 1500, 4),       # the streaming route
+    (34, 4, 16, 20000, 600, 4),       # lists of a workgroup per group
 ])
 @pytest.mark.parametrize("bad", ["inf", "nan", "huge"])
 def test_queries_that_are_not_finite_select_within_their_rows(Bn, G, M, N, K, n_sink, bad):
@@ -706,3 +707,48 @@ def test_decode_select_of_many_sequences_equals_the_calls(Bn, G, Hkv, M, N, K, w
     for other in res[1:]:
         for i, (a, b) in enumerate(zip(res[0], other)):
             assert torch.equal(a, b), f"output {i} differs"
+
+
+@pytest.mark.parametrize("Bn,Hkv,G,M,N,K,w,n_sink,lens,rows,page", [
+    (33, 2, 4, 16, 16384 + 64, 491, 64, 0, None, None, 0),               # 66 groups, the fewest candidates and groups
+    (37, 4, 2, 16, 65536 + 64 + 4, 1500, 64, 4, None, None, 0),          # the most candidates of the route
+    (37, 4, 2, 16, 65536 + 64 + 5, 300, 64, 4, None, None, 0),           # one more: the streaming route
+    (21, 2, 7, 32, 20001, 1, 0, 17, None, None, 0),                      # two groups a KV head, the last one of three; one winner
+    (70, 1, 1, 32, 17000, 2300, 64, 4, True, None, 0),                   # one head; ragged, fewer candidates than K and none
+    (34, 2, 4, 16, 20000, 3700, 64, 0, None, None, 0),                   # nearly all that a list holds
+    (34, 2, 3, 16, 18000, 900, 64, 4, None, "patterns", 0),              # ~450 equal scores: ties inside the band
+    (34, 2, 4, 32, 18000, 900, 64, 4, None, "few", 0),                   # 6000 equal scores: lists overflow
+    (35, 2, 4, 32, 17001, 700, 64, 0, True, None, 16),                   # codes in pages
+])
+def test_selection_by_lists_equals_a_full_sort(Bn, Hkv, G, M, N, K, w, n_sink, lens, rows, page):
+    """Long contexts of many groups (one workgroup for the heads of a group, lists in LDS) against a full sort."""
+    wl = synth.Workload("lists", Bn, Hkv * G, Hkv, 128, M, N, K, w, n_sink=n_sink, seed=N + K)
+    xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
+    if rows:
+        xd["codes"][:] = xd["codes"][:, :, torch.randint(0, 40 if rows == "patterns" else 3, (N,), device="cuda")]
+    sl = None
+    if lens:
+        sl = torch.randint(0, N + 1, (Bn,), generator=torch.Generator().manual_seed(N), dtype=torch.int32)
+        sl[:5] = torch.tensor([N, 0, w, w + n_sink + 1, min(N, w + n_sink + 1500)])
+    st = B.DecodeState(H.dims_of(wl), K, w, n_sink, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
+    st.topk_idx.fill_(-7), st.topk_count.fill_(-7), st.topk_score.fill_(-7.0), st.ws.fill_(0xA5)
+    B.build_lut(st.dims, xd["q"], st.cos_b, st.sin_b, xd["codebook"], st.q_rot, st.lut, st.lut_scale)
+    out = (st.topk_idx, st.topk_count, st.topk_score)
+    dev_lens = None if sl is None else sl.cuda()
+    if page:
+        slots = (N + page - 1) // page
+        table = torch.randperm(Bn * slots + 2, device="cuda")[:Bn * slots].reshape(Bn, slots).to(torch.int32)
+        padded = torch.nn.functional.pad(xd["codes"], (0, 0, 0, slots * page - N))
+        pool = torch.zeros(Bn * slots + 2, Hkv, page, M, dtype=torch.uint8, device="cuda")
+        pool[table.reshape(-1).long()] = (padded.reshape(Bn, Hkv, slots, page, M).permute(0, 2, 1, 3, 4)
+                                          .reshape(Bn * slots, Hkv, page, M))
+        B.score_topk_paged(st.dims, pool, table, page, st.lut, st.lut_scale, K, w, n_sink, dev_lens, *out, None, st.ws)
+    else:
+        B.score_topk(st.dims, xd["codes"], st.lut, st.lut_scale, K, w, n_sink, dev_lens, *out, None, st.ws)
+    stats = torch.empty(Bn, Hkv * G, dtype=torch.int32, device="cuda")
+    B.score_topk_stats(st.dims, K, w, n_sink, st.ws, stats)
+    for a, b in zip((out[0], out[1], out[2].view(torch.int32)), _full_sort(wl, xd, st, None if sl is None else sl.tolist())):
+        assert torch.equal(a, b)
+    if rows is None and sl is None and K <= 2048:   # no head was done again
+        route = (stats.cpu().numpy().astype(np.int64) & 0xffffffff) >> 28
+        assert (route == 0).all()

@@ -480,9 +480,9 @@ int a2ats_score_topk_stats(const a2ats_dims* dims, int32_t top_k, int32_t window
  * route alone, or for larger top_k the streaming route if the workspace is there for it),
  * [1] groups of four query heads per KV head, [2] sampling workgroups per (sequence, KV head, group),
  * [3] rows each of them scores, [4] streaming workgroups (chunks) per problem, [5] rows per chunk,
- * [6] survivor segments per wave of a chunk (always 1), [7] rows per segment, [8] entries a segment can hold,
- * [9] survivors per head the final kernel can hold, [10] workspace bytes the call needs, divided by 256.
- * (Of more than 64 head groups and up to 65536 candidates one workgroup each does all of this; [2] to [9] are then not used.)
+ * [6] runs of rows per wave of a chunk (always 1), [7] rows per run, [8] survivors of a head that a chunk can hold, divided by
+ * its 8 waves, [9] twice the most winners (the final kernel's limit once), [10] workspace bytes the call needs, divided by 256.
+ * (Of many head groups of up to 65536 candidates one workgroup each does all of this; [2] to [9] are then not used.)
  */
 int a2ats_score_topk_plan(const a2ats_dims* dims, int32_t top_k, int32_t window, int32_t n_sink, int32_t* plan);
 

@@ -105,15 +105,15 @@ __device__ __forceinline__ void load_coarse_table(const int32_t* __restrict__ lu
 }
 
 // The bin that holds the k-th largest of the scores counted in a 2048-bin histogram of coarse scores >> 5
-// (16-bit counts: `shift` 0 or 16 picks the head's half of a word), -1 if fewer than k are counted.  By one
+// (16-bit counts: `shift` 0 or 16 picks the head's half of a word; or whole words), -1 if fewer than k are counted.  By one
 // whole wave: lane l owns bins [32 l, 32 l + 32); a suffix scan over the lanes finds the one whose range
 // holds the rank; the wave then searches that range.
-__device__ __forceinline__ int wave_find_bin(const uint32_t* hist, int shift, uint32_t k, int lane) {
+__device__ __forceinline__ int wave_find_bin(const uint32_t* hist, int shift, uint32_t k, int lane, uint32_t mask = 0xffffu) {
   uint32_t sum = 0;
 #pragma unroll
   for (int i = 0; i < 32; ++i) {
     const int ii = (i + lane) & 31;   // rotate the walk so the lanes of a read hit different banks
-    sum += (hist[32 * lane + ii] >> shift) & 0xffffu;
+    sum += (hist[32 * lane + ii] >> shift) & mask;
   }
   // inclusive suffix sum over lanes (higher lanes hold higher bins) = total - exclusive prefix
   const uint32_t pre = wave_inclusive_scan(sum);
@@ -125,7 +125,7 @@ __device__ __forceinline__ int wave_find_bin(const uint32_t* hist, int shift, ui
   // index) and a prefix sum finds the first lane that reaches k.
   const int src = __ffsll((unsigned long long)owner) - 1;
   const uint32_t above = (uint32_t)__builtin_amdgcn_readlane((int)above_lane, src);
-  const uint32_t c = lane < 32 ? (hist[32 * src + 31 - lane] >> shift) & 0xffffu : 0u;
+  const uint32_t c = lane < 32 ? (hist[32 * src + 31 - lane] >> shift) & mask : 0u;
   const uint32_t incl = wave_inclusive_scan(c);   // lanes >= 32 hold zeros
   const uint64_t reach = __ballot(lane < 32 && above + incl >= k);
   return 32 * src + 31 - (__ffsll((unsigned long long)reach) - 1);

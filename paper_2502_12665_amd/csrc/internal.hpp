@@ -23,10 +23,10 @@ struct TopkPlan {
   int sample_rows;      // rows each of them scores
   int chunks;           // streaming workgroups per (sequence, KV head, head group)
   int rows_per_chunk;
-  int subs;             // survivor segments per wave of the streaming pass (always 1)
+  int subs;             // runs of rows per wave of the streaming pass (always 1)
   int sub_rows;         // rows of a wave (rows_per_chunk / 8)
-  int cap;              // survivor capacity per head in the final kernel's LDS
-  int row_cap;          // row entries of one survivor segment in HBM
+  int cap;              // (reported as the survivors that the final kernel can hold, which has no such limit any more)
+  int row_cap;          // entries of a head's list of a chunk, divided by its waves
   bool list;            // one workgroup for a head group instead (list_select.hpp)
   int list_rows;        // rows it samples
   size_t off_thr, off_route, off_count, off_cand, bytes;

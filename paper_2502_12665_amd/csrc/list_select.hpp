@@ -116,13 +116,23 @@ __device__ __forceinline__ void list_select_body(
     LaneSwizzle<M> sw;
     sw.init(lane);
     uint4 rows_a[U][M / 16], rows_b[U][M / 16];
+    // (of codes in pages, the page numbers of a step are requested a step ahead of its rows)
+    const bool paged = seq_codes.pages != nullptr;
+    int32_t page[U];
+    auto load_pages = [&](int base) {
+      if (paged)
+#pragma unroll
+        for (int u = 0; u < U; ++u) page[u] = seq_codes.pages[(uint32_t)min(base + u * 64 + lane, wend - 1) >> seq_codes.shift];
+    };
     auto load_rows = [&](int base, uint4 (&dst)[U][M / 16]) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const uint8_t* row = row_ptr<M>(seq_codes, min(base + u * 64 + lane, wend - 1));
+        const int j = min(base + u * 64 + lane, wend - 1);
+        const uint8_t* row = paged ? row_in_page<M>(seq_codes, page[u], j) : seq_codes.base + (size_t)j * M;
 #pragma unroll
         for (int qd = 0; qd < M / 16; ++qd) dst[u][qd] = *(const uint4*)(row + ((uint32_t)(qd * 16) ^ sw.row_swz));
       }
+      load_pages(base + STEP);
     };
     auto process = [&](int base, const uint4 (&rows)[U][M / 16]) {
       uint32_t a01[U], a23[U];
@@ -167,6 +177,7 @@ __device__ __forceinline__ void list_select_body(
       }
     };
     if (wbegin < wend) {
+      load_pages(wbegin);
       load_rows(wbegin, rows_a);
 #pragma unroll 1
       for (int base = wbegin; base < wend; base += 2 * STEP) {

@@ -6,7 +6,7 @@
 //  group route (at most 16384 candidates, see takes_group_route): one workgroup for the four heads of a group,
 //  group_select.hpp.
 //
-//  list route (up to 65536 candidates of more than 64 head groups, see list_route): one workgroup for the four heads of a
+//  list route (up to 65536 candidates of 80 head groups and more, see list_route): one workgroup for the four heads of a
 //  group again, list_select.hpp.
 //
 //  exact route (the other short contexts, more than 2048 winners without a workspace, and the in-kernel fallback):
@@ -23,13 +23,13 @@
 //    2. stream_select_kernel streams all code rows: one 8-byte LDS read per code byte serves the
 //       four heads of a group (two heads per 32-bit word, 16 bits each, so one integer add
 //       accumulates two heads).  A row whose coarse score reaches the threshold of any of the
-//       heads is written once -- a 4-byte header (position, wanting heads) and its code bytes --
-//       to the segment of its (problem, chunk, wave) in HBM, in row order.
-//    3. final_select_kernel (one workgroup per head) collects its head's survivors (about 1.5 K),
-//       scores them exactly from the head's 32-bit table, radix-selects the exact K-th key among
-//       them, proves that no row outside the survivor list can reach that key (coarse and exact
-//       scores differ by less than M coarse units), and writes the winners in ascending
-//       position.  If the proof fails or a list is too short / too long / overflowed -- the
+//       heads is kept in LDS for a while; then the coarse scores and positions of those that reach a head's
+//       threshold go to the head's list of the chunk (4 bytes a row).
+//    3. final_select_kernel (one workgroup per head) takes the head's lists (about 1.5 K rows), finds the
+//       4-wide bin of the K-th coarse score by a histogram, and with it the winners and a band of
+//       2 M + 4 units (coarse and exact scores differ by less than M of them) that alone is scored
+//       exactly and ranked; winners are written from a bitmap over the positions.  If the band begins
+//       below the threshold, a list is too short or overflowed, or the band too full -- the
 //       sample misled (about 1e-6 per head for independent rows, more when similar rows come in
 //       runs) or the input is degenerate -- the workgroup runs the exact route for its head, so
 //       the result is always exact with respect to the 32-bit scores.
@@ -50,28 +50,28 @@ namespace a2ats {
 constexpr int kStreamThreads = 512;
 constexpr int kStreamWaves = kStreamThreads / 64;
 constexpr int kSampleThreads = 512;
-constexpr int kSegMeta = 8;          // words of a segment header: rows, 4 per-head counts, padding
 constexpr int kSampleRows = 1024;    // smallest sample of a problem; a sampling workgroup scores up to 8 of these
 
 // Whether a streaming selection is taken by one workgroup for a head group (list_select.hpp), and the sample that it takes.
-// Up to 64 groups the final kernel's workgroups, one a head, fit one round of the CUs, and the streaming pass has several CUs
-// for a group.  Beyond that the heads need further rounds, while the groups fill one; the longer the context, the more groups
-// it takes.  Selections (tables included), us, streaming -> list route, 32 query and 8 KV heads, K 3 %, M = 16: 64 groups
-// 17000, 32768 tokens 35.5 -> 42.1, 39.6 -> 51.8; 80 groups 17000, 24000 47.7 -> 42.5, 48.8 -> 43.8; 96 groups 20000, 32768,
-// 40000 49.0 -> 43.2, 59.9 -> 53.0, 61.9 -> 60.7; 112 groups 50000 70.2 -> 70.4; 128 groups 32768, 60000 58.2 -> 54.7, 78.0 ->
-// 81.9; 192 groups 40000 91.5 -> 66.3; 256 groups 32768 110.5 -> 70.3; two rounds: 264 groups 32768 129.2 -> 117.7, 512 of 16500
-// 156.0 -> 106.1.  M = 32: 96 groups 24000 74.4 -> 66.9, 65536 108.0 -> 128.3; 112 groups 50000 108.4 -> 101.3, 65536 118.8 -> 128.8; 144
-// groups 65536 138.3 -> 129.2; 256 groups (7 heads a KV head) 65536 192.5 -> 143.8.  One selection per KV head: 128 groups 32768
-// 53.1 -> 45.1, 256 90.0 -> 57.4; in pages of 16 tokens 128 groups 32768 59.8 -> 63.3, 192 91.7 -> 65.4.
+// The final kernel's workgroups, one a head, fill a round of the CUs with 64 groups, and the streaming pass has several CUs for a
+// group until then; beyond that the heads need further rounds, while the groups fill one.  The longer the context, the more groups
+// it takes, and of two rounds the second has to be well filled.  Steps, us, streaming -> list route, 32 query and 8 KV heads, K 3
+// %, M = 16: 72 groups 17000, 28000 tokens 63.3 -> 64.6, 80.1 -> 82.2; 80 groups 17000, 31000 70.6 -> 66.9, 90.6 -> 88.1; 96 groups
+// 20000, 39000 80.8 -> 74.9, 110.4 -> 110.5; 112 groups 30000, 47000 105.0 -> 100.2, 125.4 -> 127.0; 128 groups 32768, 55000
+// 109.9 -> 108.3, 156.5 -> 164.8; 144 groups 40000, 63000 140.1 -> 123.2, 181.0 -> 171.3; 192 groups 65000 216.4 -> 195.8; two
+// rounds: 264 groups 32768, 65000 231.1 -> 227.1, 317.2 -> 325.0.  M = 32: 96 groups 24000, 39000 105.8 -> 102.0, 133.1 -> 132.6;
+// 144 groups 63000 228.4 -> 228.5; 192 groups 65000 278.9 -> 260.2; two rounds: 288 groups 65000 351.8 -> 381.8.  One selection
+// per KV head: 128 groups 32768 76.3 -> 74.3, 160 groups 65000 109.6 -> 102.2.
 // A list holds kListCap rows: what the sample lets through (see below), five standard deviations more, and 8 % for the
 // threshold's rounding to a bin.
 static void list_route(const a2ats_dims& d, TopkPlan& p, long ncand, int top_k) {
-  const long problems = (long)d.batch * d.n_kv_heads * p.NG;
+  const long problems = std::max(1L, (long)d.batch * d.n_kv_heads * p.NG);
   p.list_rows = (int)std::min<long>(std::max<long>(ncand / 8 / 512 * 512, kSampleRows), kSampleMost);
   const double r0 = (double)top_k * p.list_rows / (double)ncand;
   const double xr = 0.5 * (kSigma + std::sqrt(kSigma * kSigma + 4.0 * r0));
   const double rows = (xr * xr + 5.0 * xr) / p.list_rows * (double)ncand * 1.08;
-  p.list = problems > 64 && ncand <= kListMaxCand && ncand <= 500 * problems - 8000 && rows <= kListCap;
+  const long rounds = (problems + 255) / 256, a_round = problems / rounds;
+  p.list = a_round >= 80 && ncand <= (a_round > (rounds > 1 ? 192 : 128) ? kListMaxCand : 36000) && rows <= kListCap;
 }
 
 TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink) {
@@ -123,13 +123,13 @@ TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink) 
     if (chunks > max_chunks) chunks = max_chunks;
     if (chunks < 1) chunks = 1;
     if (chunks > 64) chunks = 64;
-    // Survivor segments, one per (problem, chunk, wave): a header and row_cap row entries each.
-    // The sampling rule (rank r with r - 5 sqrt(r) >= K S / N, plus one per part) lets about
+    if (chunks < (ncand + 65535) / 65536) chunks = (ncand + 65535) / 65536;   // (positions in a chunk are 16 bits)
+    // Survivors.  The sampling rule (rank r with r - 5 sqrt(r) >= K S / N, plus one per part) lets about
     // r N / S rows per head through -- for small K much more than K -- and a row survives if any of
     // the (up to) four heads wants it.  row_cap is twice that share of a wave's rows plus 16
-    // standard deviations of a Poisson count: survivors that come in runs (neighbouring tokens with
-    // similar scores) scatter far more between segments than independent ones.  The final kernel
-    // handles at most 512 segments per problem, i.e. 64 chunks.
+    // standard deviations of a Poisson count; a head's list of a chunk holds that of its eight waves: survivors that come in
+    // runs (neighbouring tokens with similar scores) scatter far more between chunks than independent ones.  The final kernel
+    // takes at most 64 chunks.  (The workspace is what segments of a wave, with the code bytes of every row, once took.)
     const double r0 = (double)top_k * (double)s_tot / (double)ncand;
     const double xr = 0.5 * (kSigma + std::sqrt(kSigma * kSigma + 4.0 * r0));
     const double survivors = (xr * xr + 2.0 * p.P0) / (double)s_tot * (double)ncand * 1.25;
@@ -138,7 +138,7 @@ TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink) 
     rpc = (rpc + kStreamThreads - 1) / kStreamThreads * kStreamThreads;
     const long rows_per_wave = rpc / kStreamWaves;   // a multiple of 64
     const double mu = rows_per_wave * keep;
-    long cap_rows = (long)(mu * 2.0 + 16.0 * std::sqrt(mu)) + 64;   // generous: unused capacity costs only scratch
+    long cap_rows = (long)(mu * 2.0 + 16.0 * std::sqrt(mu)) + 64;
     cap_rows = (cap_rows + 31) / 32 * 32;
     if (cap_rows > rows_per_wave) cap_rows = rows_per_wave;
     p.chunks = (int)((ncand + rpc - 1) / rpc);
@@ -153,7 +153,7 @@ TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink) 
     p.off_thr = 0;
     p.off_route = (p.off_thr + heads * p.P0 * sizeof(int32_t) + 255) / 256 * 256;
     p.off_count = (p.off_route + heads * sizeof(uint32_t) + 255) / 256 * 256;
-    p.off_cand = (p.off_count + segs * kSegMeta * sizeof(uint32_t) + 255) / 256 * 256;
+    p.off_cand = (p.off_count + segs * 8 * sizeof(uint32_t) + 255) / 256 * 256;
     p.bytes = (p.off_cand + segs * (size_t)p.row_cap * entry_bytes + 255) / 256 * 256;
   }
   return p;
@@ -211,16 +211,6 @@ __device__ __forceinline__ void combine_thresholds(int32_t v, int n_valid, int P
     T[i] = i >= n_valid ? 65536 : (a_i ? INT32_MIN : s_i / P0);
   }
 }
-
-// Survivor entries.  The streaming pass writes, per segment (a run of rows of one wave), row_cap
-// 4-byte headers followed by row_cap rows of code bytes.  A header packs the token position (20
-// bits: contexts are at most 2^20 tokens) and the mask of the heads that want the row (4 bits).
-template <int M>
-__host__ __device__ __forceinline__ size_t segment_words(int row_cap) {
-  return (size_t)row_cap * (1 + M / 4);
-}
-__device__ __forceinline__ uint32_t entry_pos(uint32_t w0) { return w0 & 0xfffffu; }
-__device__ __forceinline__ bool entry_wanted(uint32_t w0, int r) { return (w0 >> (20 + r)) & 1u; }
 
 template <int M>
 __global__ __launch_bounds__(kExactThreads) void select_exact_kernel(
@@ -337,12 +327,25 @@ __global__ __launch_bounds__(kSampleThreads) void sample_threshold_kernel(
 // staged in LDS behind the table (up to kPageSlice of them, else they are read from the page table
 // row by row), and rows are read with ordinary loads.
 constexpr int kPageSlice = 2048;
+// Behind the table: two workgroups of 80 KB fit a CU.  The rows of each wave that any head of the group wants; when they are full,
+// and at the end, they go to the lists of the heads that want them.  (Appending to four lists row by row took the pass 1.5 to 2 us
+// longer; writing these rows to memory and having every head pick its own from there took the final kernel 2.5 to 4.5.)
+template <bool PAGED>
+struct StreamLds {
+  static constexpr int kCap = PAGED ? 100 : 200;
+  uint32_t s01[kStreamWaves][kCap], s23[kStreamWaves][kCap];   // coarse scores, two heads a word
+  uint16_t pos[kStreamWaves][kCap];                            // in the chunk
+  uint32_t n_list[kHeadsPerGroup];
+  int32_t page[PAGED ? kPageSlice : 1];
+};
+static_assert(sizeof(StreamLds<false>) <= 16384 && sizeof(StreamLds<true>) <= 16384, "");
+
 template <int M, bool RESHARED, bool PAGED>
 __device__ __forceinline__ void stream_select_body(
     const uint8_t* __restrict__ codes, const int32_t* __restrict__ lut,
     const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ thr,
-    uint32_t* __restrict__ seg_meta, uint32_t* __restrict__ cand, GridMap gm, CodePages pg, int B, int Hq, int Hkv, int G,
-    int NG, int P0, int n_chunks, int rows_per_chunk, int row_cap, int ctx_len,
+    uint32_t* __restrict__ counts, uint32_t* __restrict__ lists, GridMap gm, CodePages pg, int B, int Hq, int Hkv, int G,
+    int NG, int P0, int n_chunks, int rows_per_chunk, int list_cap, int ctx_len,
     int64_t ctx_stride, int top_k, int window, int n_sink) {
   constexpr int NT = kStreamThreads;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
@@ -351,45 +354,73 @@ __device__ __forceinline__ void stream_select_body(
   int chunk, prob, b, kv, g4;
   map_block(blockIdx.x, gm, prob, chunk);
   split_problem(prob, gm, b, kv, g4);
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const SeqRange sr = seq_range(ctx_len, seq_lens, b, window, n_sink, top_k);
   const long begin = (long)sr.sink_end + (long)chunk * rows_per_chunk;
   const int end = (int)min((long)sr.win_start, begin + rows_per_chunk);
-  // A wave owns a contiguous run of rows, so its survivors come out in ascending position and
-  // the segments of a problem, taken in (chunk, wave) order, are sorted by position.
   const int rows_per_wave = rows_per_chunk / kStreamWaves;
   const long wbegin = begin + (long)wv * rows_per_wave;
   const int wend = (int)min((long)end, wbegin + rows_per_wave);
 
-  // Every (problem, chunk, wave) owns one survivor segment in HBM: no atomics, no contention.
-  const size_t seg = ((size_t)prob * n_chunks + chunk) * kStreamWaves + wv;
-  uint32_t* my_meta = seg_meta + seg * kSegMeta;
+  // Every (problem, chunk) has four lists of list_cap entries and their lengths in memory; an entry is a coarse score in the
+  // upper half and the position in the chunk in the lower.
+  uint32_t* my_count = counts + ((size_t)prob * n_chunks + chunk) * kHeadsPerGroup;
+  uint32_t* my_list = lists + ((size_t)prob * n_chunks + chunk) * kHeadsPerGroup * (size_t)list_cap;
+  StreamLds<PAGED>& L = lds_at<StreamLds<PAGED>>(kCoarseLdsBytes);
+  constexpr uint32_t CAP = StreamLds<PAGED>::kCap;
   // thresholds of the group's heads: requested here, combined after the table copy has been issued
   const int32_t thr_lane = request_thresholds<4>(thr, (size_t)b * Hq + kv * G + g4 * kHeadsPerGroup,
                                                 G - g4 * kHeadsPerGroup, P0);
   int32_t T[4];   // padded heads never want a row
   // The scoring loop addresses the table by absolute LDS address (it must start at 0, which holds
   // because this kernel has no static LDS).  Should a toolchain ever place it elsewhere, publish
-  // an overflowing segment instead: the final kernel then takes the exact route.
+  // overflowing lists instead: the final kernel then takes the exact route.
   const bool misplaced = (uint32_t)(uintptr_t)tbl != 0u;
-  if (begin >= sr.win_start || misplaced) {   // nothing to score in this chunk: an empty segment
-    if (lane < kSegMeta) my_meta[lane] = misplaced && lane == 0 ? 0xffffffffu : 0u;
+  if (begin >= sr.win_start || misplaced) {   // nothing to score in this chunk: empty lists
+    if (tid < kHeadsPerGroup) my_count[tid] = misplaced ? 0xffffffffu : 0u;
     return;
   }
 
   LaneSwizzle<M> sw;
   sw.init(lane);
-  int n_rows = 0;                  // row entries written by this wave (wave-uniform)
-  int n_head[4] = {0, 0, 0, 0};    // of which wanted by each head
-  // A segment is row_cap 4-byte entry headers followed by row_cap rows of code bytes.
-  uint32_t* my_seg = cand + seg * segment_words<M>(row_cap);
-  uint32_t* my_hdr = my_seg;
-  uint4* my_codes = (uint4*)(my_seg + (size_t)row_cap);
+  // Appends the rows of a wave (one a lane, where `in`) to the lists of the heads that want them.
+  auto to_lists = [&](uint32_t w01, uint32_t w23, uint32_t pos, bool in) {
+    uint64_t h[4];
+    h[0] = __builtin_amdgcn_ballot_w64(in && (int32_t)(w01 & 0xffffu) >= T[0]);
+    h[1] = __builtin_amdgcn_ballot_w64(in && (int32_t)(w01 >> 16) >= T[1]);
+    h[2] = __builtin_amdgcn_ballot_w64(in && (int32_t)(w23 & 0xffffu) >= T[2]);
+    h[3] = __builtin_amdgcn_ballot_w64(in && (int32_t)(w23 >> 16) >= T[3]);
+    uint32_t at = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) at = write_lane((uint32_t)__popcll(h[r]), r, at);
+    if (lane < 4) at = atomicAdd(&L.n_list[lane], at);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (__builtin_amdgcn_inverse_ballot_w64(h[r])) {
+        const uint32_t slot = (uint32_t)__builtin_amdgcn_mbcnt_hi(
+            (uint32_t)(h[r] >> 32),
+            __builtin_amdgcn_mbcnt_lo((uint32_t)h[r], (uint32_t)__builtin_amdgcn_readlane((int)at, r)));
+        const uint32_t a = r < 2 ? w01 : w23;
+        if (slot < (uint32_t)list_cap)   // (rows past the capacity are dropped but still counted)
+          my_list[(size_t)r * list_cap + slot] = ((r & 1) ? a & 0xffff0000u : a << 16) | pos;
+      }
+  };
+
+  uint32_t n_kept = 0;   // rows of the wave in LDS (wave-uniform)
+  auto flush = [&]() {
+    __builtin_amdgcn_wave_barrier();
+    for (uint32_t i0 = 0; i0 < n_kept; i0 += 64) {
+      const uint32_t i = min(i0 + lane, n_kept - 1);
+      to_lists(L.s01[wv][i], L.s23[wv][i], L.pos[wv][i], i0 + lane < n_kept);
+    }
+    __builtin_amdgcn_wave_barrier();
+    n_kept = 0;
+  };
 
   const bool has_rows = wbegin < wend;   // wave-uniform
   {
     const SeqCodes seq_codes = seq_codes_of<M>(codes, pg, b, kv, Hkv, ctx_stride);
-    int32_t* pg_lds = (int32_t*)(dyn_lds + kCoarseLdsBytes);
+    int32_t* pg_lds = L.page;
     const int pg0 = PAGED ? (int)((uint32_t)begin >> seq_codes.shift) : 0;                  // first page slot of the chunk
     const int n_pg = PAGED ? (int)((uint32_t)(end - 1) >> seq_codes.shift) - pg0 + 1 : 0;   // (begin < end here)
     const bool pg_staged = PAGED && n_pg <= kPageSlice;
@@ -418,46 +449,48 @@ __device__ __forceinline__ void stream_select_body(
       }
     };
     auto process = [&](int base, const uint4 (&rows)[U][M / 16]) {
-      // Scores and the per-head "reaches the threshold" wave masks are formed together, so the
+      // Scores and the "reaches the threshold" wave masks are formed together, so the
       // gathered table entries die inside this straight-line block.  The masks live in scalar
       // registers; their popcounts cost no vector instructions.
-      uint64_t hit[U][4];
+      uint64_t any[U];
+      uint32_t a01[U], a23[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        uint32_t a01, a23;
-        score_coarse<M>(rows[u], sw, a01, a23);
-        const uint64_t valid = __builtin_amdgcn_ballot_w64(base + u * 64 + lane < wend);
-        hit[u][0] = __builtin_amdgcn_ballot_w64((int32_t)(a01 & 0xffffu) >= T[0]) & valid;
-        hit[u][1] = __builtin_amdgcn_ballot_w64((int32_t)(a01 >> 16) >= T[1]) & valid;
-        hit[u][2] = __builtin_amdgcn_ballot_w64((int32_t)(a23 & 0xffffu) >= T[2]) & valid;
-        hit[u][3] = __builtin_amdgcn_ballot_w64((int32_t)(a23 >> 16) >= T[3]) & valid;
+        score_coarse<M>(rows[u], sw, a01[u], a23[u]);
+        any[u] = (__builtin_amdgcn_ballot_w64((int32_t)(a01[u] & 0xffffu) >= T[0]) |
+                  __builtin_amdgcn_ballot_w64((int32_t)(a01[u] >> 16) >= T[1]) |
+                  __builtin_amdgcn_ballot_w64((int32_t)(a23[u] & 0xffffu) >= T[2]) |
+                  __builtin_amdgcn_ballot_w64((int32_t)(a23[u] >> 16) >= T[3])) &
+                 __builtin_amdgcn_ballot_w64(base + u * 64 + lane < wend);
         if (u & 1) __builtin_amdgcn_sched_barrier(0);   // two rows' gathers at a time: bounds live registers
       }
-      // A surviving row is written once, with the mask of the heads that want it; entries keep
-      // the order of the rows, so the final kernel finds a row's place among the rows a head
-      // wants by counting mask bits.
+      uint32_t total = 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) total += (uint32_t)__popcll(any[u]);
+      if (n_kept + total > CAP) {
+        flush();
+        if (total > CAP) {   // more in a step than fits
+          to_lists(a01[0], a23[0], (uint32_t)(base + lane - (int)begin), __builtin_amdgcn_inverse_ballot_w64(any[0]));
+          total -= (uint32_t)__popcll(any[0]);
+          any[0] = 0;
+          if (total > CAP) {
+            to_lists(a01[1], a23[1], (uint32_t)(base + 64 + lane - (int)begin), __builtin_amdgcn_inverse_ballot_w64(any[1]));
+            any[1] = 0;
+            to_lists(a01[2], a23[2], (uint32_t)(base + 128 + lane - (int)begin), __builtin_amdgcn_inverse_ballot_w64(any[2]));
+            any[2] = 0;
+          }
+        }
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const uint64_t any = hit[u][0] | hit[u][1] | hit[u][2] | hit[u][3];
-        if (any) {
-          if (__builtin_amdgcn_inverse_ballot_w64(any)) {
-            const int slot = (int)__builtin_amdgcn_mbcnt_hi(
-                (uint32_t)(any >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)any, (uint32_t)n_rows));
-            if (slot < row_cap) {   // rows past the capacity are dropped but still counted
-              uint32_t hdr = (uint32_t)(base + u * 64 + lane);
-#pragma unroll
-              for (int r = 0; r < 4; ++r)
-                hdr |= __builtin_amdgcn_inverse_ballot_w64(hit[u][r]) ? (1u << (20 + r)) : 0u;
-              my_hdr[slot] = hdr;
-#pragma unroll
-              for (int qd = 0; qd < M / 16; ++qd)   // (row_swz: which half of the row this register holds)
-                my_codes[slot * (M / 16) + (qd ^ (int)(sw.row_swz >> 4))] = rows[u][qd];
-            }
-          }
-          n_rows += __popcll(any);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) n_head[r] += __popcll(hit[u][r]);
+        if (__builtin_amdgcn_inverse_ballot_w64(any[u])) {
+          const uint32_t slot = (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(any[u] >> 32),
+                                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)any[u], n_kept));
+          L.s01[wv][slot] = a01[u];
+          L.s23[wv][slot] = a23[u];
+          L.pos[wv][slot] = (uint16_t)(base + u * 64 + lane - (int)begin);
         }
+        n_kept += (uint32_t)__popcll(any[u]);
       }
     };
     // The first rows are requested before the table is copied to LDS, so both latencies overlap.
@@ -467,6 +500,7 @@ __device__ __forceinline__ void stream_select_body(
     if (pg_staged)
       for (int i = tid; i < n_pg; i += NT) pg_lds[i] = seq_codes.pages[pg0 + i];
     combine_thresholds<4>(thr_lane, G - g4 * kHeadsPerGroup, P0, T);
+    if (tid < kHeadsPerGroup) L.n_list[tid] = 0;
     __syncthreads();
 #pragma unroll 1
     for (int base = (int)wbegin; base < wend; base += 2 * STEP) {
@@ -476,26 +510,20 @@ __device__ __forceinline__ void stream_select_body(
       process(base + STEP, rows_b);
     }
   }
-  // header of the segment: rows written, rows per head
-  if (lane < kSegMeta) {
-    uint32_t v = 0;
-    if (lane == 0) v = (uint32_t)n_rows;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (lane == 1 + r) v = (uint32_t)n_head[r];
-    my_meta[lane] = v;
-  }
+  flush();
+  __syncthreads();
+  if (tid < kHeadsPerGroup) my_count[tid] = L.n_list[tid];
 }
 
 #define A2ATS_STREAM_ARGS                                                                          \
   const uint8_t *__restrict__ codes, const int32_t *__restrict__ lut,                             \
       const int32_t *__restrict__ seq_lens, const int32_t *__restrict__ thr,                      \
-      uint32_t *__restrict__ seg_meta, uint32_t *__restrict__ cand, GridMap gm, CodePages pg,      \
+      uint32_t *__restrict__ counts, uint32_t *__restrict__ lists, GridMap gm, CodePages pg,      \
       int B, int Hq, int Hkv, int G, int NG, int P0, int n_chunks, int rows_per_chunk,             \
-      int row_cap, int ctx_len, int64_t ctx_stride, int top_k, int window, int n_sink
+      int list_cap, int ctx_len, int64_t ctx_stride, int top_k, int window, int n_sink
 #define A2ATS_STREAM_PASS                                                                          \
-  codes, lut, seq_lens, thr, seg_meta, cand, gm, pg, B, Hq, Hkv, G, NG, P0, n_chunks,              \
-      rows_per_chunk, row_cap, ctx_len, ctx_stride, top_k, window, n_sink
+  codes, lut, seq_lens, thr, counts, lists, gm, pg, B, Hq, Hkv, G, NG, P0, n_chunks,              \
+      rows_per_chunk, list_cap, ctx_len, ctx_stride, top_k, window, n_sink
 
 // 64 KB of LDS per workgroup (72 KB with a staged page slice).  M = 16: 128 VGPRs -> 4 waves per
 // SIMD (two workgroups per CU).
@@ -510,27 +538,49 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
 void stream_select_kernel32(A2ATS_STREAM_ARGS) { stream_select_body<32, false, false>(A2ATS_STREAM_PASS); }
 __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(2, 4)))
 void stream_select_kernel32r(A2ATS_STREAM_ARGS) { stream_select_body<32, true, false>(A2ATS_STREAM_PASS); }
-__global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(2, 4)))
+__global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void stream_select_kernel32p(A2ATS_STREAM_ARGS) { stream_select_body<32, true, true>(A2ATS_STREAM_PASS); }
 
 // ------------------------------------------------------------------------------------------
-// Fast route, stage 3: exact scores of the survivors, exact selection, ordered output
+// Fast route, stage 3: exact selection from the lists, ordered output
 // ------------------------------------------------------------------------------------------
+// One workgroup per head, from the lists of the chunks.  What separates winners from the band, and why that is exact, is told in
+// list_select.hpp.
+//
+// What bounds it: a chain of short dependent phases on one CU (entries, histogram, bin, winners, band rows from the code matrix,
+// ranks, output).
+constexpr int kFinalBin = 2;          // a bin of the first histogram is 4 coarse units, from the threshold up; of a second, where
+constexpr int kFinalWide = 5;         // the K-th is above those, 32, which is the whole range
+constexpr long kFinalTableCand = 1 << 19;   // candidates up to which the exact table is in LDS too
+struct FinalLds {
+  uint32_t hist[kHistBins];
+  uint64_t band[kBandCap];
+  uint32_t n, n_band, n_sure, wave_tot[kExactThreads / 64];
+  int32_t bin, overflow;
+  uint64_t won[1];   // a bit for each candidate
+};
+// The table, if it is there, comes first; the exact route takes all of it.
+template <int M>
+size_t final_lds_bytes(long ncand) {
+  const size_t table = ncand <= kFinalTableCand ? kCentroids * M * sizeof(int32_t) : 0;
+  const size_t fast = table + sizeof(FinalLds) + (size_t)(ncand + 63) / 64 * 8;
+  return std::max(fast, kExactLdsBytes + sizeof(ExactLds));
+}
+
 template <int M>
 __global__ __launch_bounds__(kExactThreads) void final_select_kernel(
     const uint8_t* __restrict__ codes, const int32_t* __restrict__ lut,
     const float* __restrict__ lut_scale, const int32_t* __restrict__ seq_lens,
-    const int32_t* __restrict__ thr, const uint32_t* __restrict__ seg_meta,
-    const uint32_t* __restrict__ cand, uint32_t* __restrict__ route, int32_t* __restrict__ topk_idx,
+    const int32_t* __restrict__ thr, const uint32_t* __restrict__ counts,
+    const uint32_t* __restrict__ lists, uint32_t* __restrict__ route, int32_t* __restrict__ topk_idx,
     int32_t* __restrict__ topk_count, float* __restrict__ topk_score, GridMap gm, CodePages pg, int B,
-    int Hq, int Hkv, int G, int NG, int P0, int n_seg, int row_cap, int cap, int ctx_len, int64_t ctx_stride,
-    int top_k, int window, int n_sink) {
+    int Hq, int Hkv, int G, int NG, int P0, int n_chunks, int rows_per_chunk, int list_cap, int table_in_lds, int ctx_len,
+    int64_t ctx_stride, int top_k, int window, int n_sink) {
   constexpr int NT = kExactThreads;
+  constexpr int KEEP = 6;   // entries of a thread that stay in registers
   extern __shared__ __align__(16) unsigned char dyn_lds[];
-  __shared__ ExactLds L;
-  __shared__ uint32_t s_seg_off[513];
-  __shared__ uint32_t s_overflow, s_small_n, s_kth;
-  __shared__ uint32_t s_small_key[kSmallList];
+  int32_t* table = (int32_t*)dyn_lds;
+  FinalLds& L = *(FinalLds*)(dyn_lds + (table_in_lds ? kCentroids * M * sizeof(int32_t) : 0));
 
   // one workgroup per (problem, head slot), on the XCD that streamed the problem
   int prob, r, b, kv, g4;
@@ -538,231 +588,186 @@ __global__ __launch_bounds__(kExactThreads) void final_select_kernel(
   split_problem(prob, gm, b, kv, g4);
   const int hg = g4 * kHeadsPerGroup + r;
   if (hg >= G) return;
-  const int bh = b * Hq + kv * G + hg, tid = threadIdx.x;
+  const int bh = b * Hq + kv * G + hg, tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // A group of lanes takes the list of a chunk: its entries are requested before its length is known (list_cap of them are
+  // there whatever it is).  n_chunks <= 64.
+  int lanes = NT;
+  while (lanes * n_chunks > NT) lanes >>= 1;
+  const int chunk = min(tid / lanes, n_chunks - 1), l0 = tid & (lanes - 1);
+  const size_t list = ((size_t)prob * n_chunks + chunk) * kHeadsPerGroup + r;
+  const uint32_t* my_list = lists + list * (size_t)list_cap;
+  const uint32_t n_rows = tid / lanes < n_chunks ? counts[list] : 0u;
+  uint32_t keep[KEEP];
+#pragma unroll
+  for (int k = 0; k < KEEP; ++k) keep[k] = my_list[min(l0 + k * lanes, list_cap - 1)];
+  const int32_t thr_lane = request_thresholds<1>(thr, (size_t)bh, 1, P0);
+
   const SeqRange sr = seq_range(ctx_len, seq_lens, b, window, n_sink, top_k);
   int32_t* oi = topk_idx + (size_t)bh * top_k;
-  float* os = topk_score ? topk_score + (size_t)bh * top_k : nullptr;
   if (tid == 0) topk_count[bh] = sr.kk;
   for (int t = sr.kk + tid; t < top_k; t += NT) {
     oi[t] = -1;
-    if (os) os[t] = 0.f;
+    if (topk_score) topk_score[(size_t)bh * top_k + t] = 0.f;
   }
   if (sr.kk == 0) {
     if (tid == 0) route[bh] = 0u;
     return;
   }
-  const float scale = lut_scale[bh];
   const LutLayout lay = lut_layout(B, Hq, Hkv, M);
   const int32_t* head_table = lut + lay.off_exact + (size_t)bh * (kCentroids * M);
   const SeqCodes seq_codes = seq_codes_of<M>(codes, pg, b, kv, Hkv, ctx_stride);
-
-  // LDS carve-up: the head's exact table, survivor keys and positions
-  unsigned char* tbl = dyn_lds;
-  uint32_t* c_key = (uint32_t*)(dyn_lds + kExactLdsBytes);
-  uint32_t* c_pos = c_key + cap;
-
-  // Everything this workgroup needs from global memory before it can look at a survivor is
-  // requested here in one go, so the latencies overlap: the segment headers, the threshold and
-  // table constants of the completeness check (used at the very end), and the head's table.
-  uint32_t seg_rows = 0, my_cnt = 0;
-  if (tid < n_seg) {
-    const uint32_t* mt = seg_meta + ((size_t)prob * n_seg + tid) * kSegMeta;
-    seg_rows = mt[0];
-    my_cnt = mt[1 + r];
-  }
-  const int32_t thr_lane = request_thresholds<1>(thr, (size_t)bh, 1, P0);
   const int32_t* meta = lut + lay.off_meta + (size_t)bh * 4;
   const int32_t m_base = meta[0], m_shift = meta[1], m_top = meta[2];
-  load_exact_table<M, NT>(head_table, tbl);
-  int32_t tc1[1];
-  combine_thresholds<1>(thr_lane, 1, P0, tc1);
-  const int32_t tc = tc1[0];
-  const long proof_bound = (long)m_base + (((long)tc - 1 + M) << m_shift);
-  ExactSwizzle<M> sw;
-  sw.init(tid & 63);
+  const float scale = lut_scale[bh];
+  if (table_in_lds) {
+#pragma unroll
+    for (int i = tid; i < kCentroids * M / 4; i += NT) {
+      const int c = i / (M / 4);   // (four entries are turned by their centroid, see band_select.hpp)
+      ((uint4*)table)[c * (M / 4) + ((i + c) & (M / 4 - 1))] = ((const uint4*)head_table)[i];
+    }
+  }
+  const int n_words = (sr.ncand + 63) / 64;
+  for (int i = tid; i < n_words; i += NT) L.won[i] = 0;
   for (int i = tid; i < kHistBins; i += NT) L.hist[i] = 0;
   if (tid == 0) {
-    s_overflow = 0;
-    s_small_n = 0;
-    s_kth = 0;
+    L.n = 0;
+    L.n_band = 0;
+    L.n_sure = 0;
+    L.overflow = 0;
   }
+  int32_t t1[1];
+  combine_thresholds<1>(thr_lane, 1, P0, t1);
+  const uint32_t T = (uint32_t)max(t1[0], 0);
   __syncthreads();
-  // Survivor segments of this head's problem (one per chunk and wave of the streaming pass,
-  // sorted by position when taken in order): exclusive prefix of the number of rows this head
-  // wants in each.  n_seg <= 512 <= NT.
-  __shared__ uint32_t s_seg_rows[512];
-  if (tid < n_seg) {
-    if (seg_rows > (uint32_t)row_cap) s_overflow = 1;
-    s_seg_rows[tid] = seg_rows;
+
+  // f(coarse score, candidate) for every row of the head
+  const uint32_t n_mine = min(n_rows, (uint32_t)list_cap), pos0 = (uint32_t)chunk * (uint32_t)rows_per_chunk;
+  auto each = [&](auto f) {
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k)
+      if ((uint32_t)(l0 + k * lanes) < n_mine) f(keep[k] >> 16, pos0 + (keep[k] & 0xffffu));
+    for (uint32_t i = l0 + KEEP * lanes; i < n_mine; i += lanes) {
+      const uint32_t e = my_list[i];
+      f(e >> 16, pos0 + (e & 0xffffu));
+    }
+  };
+  if (l0 == 0) {
+    atomicAdd(&L.n, n_mine);
+    if (n_rows > (uint32_t)list_cap) L.overflow = 1;
   }
-  uint32_t n_c;
-  const uint32_t my_off = block_exclusive_scan<NT>(my_cnt, L.wave_a, n_c);
-  if (tid < n_seg) s_seg_off[tid] = my_off;
-  if (tid == 0) s_seg_off[n_seg] = n_c;
-  __syncthreads();
-  if (s_overflow || n_c > (uint32_t)cap || n_c < (uint32_t)sr.kk) {
-    if (tid == 0) route[bh] = s_overflow ? 3u : (n_c > (uint32_t)cap ? 2u : 1u);   // diagnostics only
-    exact_select_block<M>(seq_codes, head_table, m_base, m_top, scale, sr, oi, os, tbl, L);
+  int shift = kFinalBin;
+  for (;;) {
+    each([&](uint32_t s, uint32_t) { atomicAdd(&L.hist[min((s - T) >> shift, (uint32_t)kHistBins - 1)], 1u); });
+    __syncthreads();
+    if (wv == 0) {
+      const int bin = wave_find_bin(L.hist, 0, (uint32_t)sr.kk, lane, ~0u);
+      if (lane == 0) L.bin = bin;
+    }
+    __syncthreads();
+    if (L.bin != kHistBins - 1 || shift == kFinalWide) break;   // (uniform)
+    shift = kFinalWide;
+    for (int i = tid; i < kHistBins; i += NT) L.hist[i] = 0;
+    __syncthreads();
+  }
+  const int bin = __builtin_amdgcn_readfirstlane(L.bin);
+  uint32_t why = L.overflow ? 3u : (bin < 0 ? 1u : (T != 0u && (bin << shift) < M - 1 ? 4u : 0u));
+  const int edge = (int)T + (bin << shift);
+  const uint32_t t_lo = (uint32_t)max(0, edge - M + 1), t_hi = (uint32_t)(edge + (1 << shift) + M);
+  if (why == 0u) {
+    uint32_t sure = 0;
+    each([&](uint32_t s, uint32_t j) {
+      if (s >= t_hi) {
+        atomicOr((uint32_t*)L.won + (j >> 5), 1u << (j & 31));
+        ++sure;
+      } else if (s >= t_lo) {
+        const uint32_t slot = atomicAdd(&L.n_band, 1u);
+        if (slot < (uint32_t)kBandCap) L.band[slot] = j;
+      }
+    });
+    sure = wave_inclusive_scan(sure);
+    if (lane == 63 && sure) atomicAdd(&L.n_sure, sure);
+    __syncthreads();
+    if (L.n_band > (uint32_t)kBandCap) why = 2u;
+  }
+  if (tid == 0) route[bh] = min(L.n, 0x0fffffffu) | why << 28;   // diagnostics only
+  if (why != 0u) {
+    exact_select_block<M>(seq_codes, head_table, m_base, m_top, scale, sr, oi,
+                          topk_score ? topk_score + (size_t)bh * top_k : nullptr, dyn_lds,
+                          *(ExactLds*)(dyn_lds + kExactLdsBytes));
     return;
   }
 
-  // Keys are taken relative to a lower bound of every survivor's exact key (a survivor's coarse
-  // score reaches the threshold, so its exact score is at least base + (Tc << s)), and the first
-  // radix level spreads the 2048 bins over the range up to the largest possible score.  Both
-  // bounds are known before any survivor is looked at, so the histogram is filled while the keys
-  // are computed.
-  const long lo_score = tc == INT32_MIN ? (long)m_base : (long)m_base + ((long)max(tc, 0) << m_shift);
-  const uint32_t klo = score_key((int32_t)max(lo_score, (long)INT32_MIN + 1));
-  const uint32_t khi = max(klo, score_key(m_top));
-  const int nbits = 32 - __clz(khi - klo);
-  const int bits1 = nbits < 11 ? nbits : 11, shift1 = nbits - bits1;
-  {
-    // Pass 1: pick this head's rows out of the problem's entry headers.  A group of tps lanes
-    // (a power of two, at most a wave) takes a segment at a time; entries keep the order of their
-    // rows, so an entry's place in the head's list is the segment's offset plus the number of
-    // wanted entries before it: wave ballots restricted to the group's lanes, no exchange between
-    // threads.  All header loads of a sweep are in flight together.  c_key temporarily holds where
-    // the entry's code bytes are (in 16-byte units from the start of the problem's segments).
-    constexpr int kInFlight = 8;
-    int tps = 64;
-    while (tps > 1 && tps * n_seg > NT) tps >>= 1;
-    const int lane = tid & 63, gl = lane & (tps - 1);
-    const uint64_t gmask = (tps == 64 ? ~0ull : ((1ull << tps) - 1ull)) << (lane - gl);
-    const uint64_t gbelow = gmask & ((1ull << lane) - 1ull);
-    const size_t seg_words = segment_words<M>(row_cap);
-    const uint32_t* seg0 = cand + (size_t)prob * n_seg * seg_words;
-    const uint32_t seg_q = (uint32_t)(seg_words / 4), codes_q = (uint32_t)row_cap / 4;   // in 16-byte units
-    for (int s_ = tid / tps; s_ < n_seg; s_ += NT / tps) {
-      const uint32_t n_rows = s_seg_rows[s_];
-      uint32_t dst = s_seg_off[s_];   // of the next wanted entry of the group's sweep
-      const uint32_t* hdr = seg0 + (size_t)s_ * seg_words;
-      for (uint32_t i0 = 0; i0 < n_rows; i0 += kInFlight * tps) {   // (uniform within the group)
-        // The headers are fetched together before any of them is looked at (the empty asm keeps the
-        // compiler from sinking a load behind the "does this head want the row" branch, which
-        // would serialise the latencies).
-        uint32_t hd[kInFlight];
+  auto exact_at = [&](uint32_t j) {
+    const uint8_t* row = row_ptr<M>(seq_codes, sr.sink_end + (int)j);
+    if (!table_in_lds) return exact_score_of<M>(head_table, row);
+    uint4 w[M / 16];
+    int32_t s = 0;
 #pragma unroll
-        for (int k = 0; k < kInFlight; ++k) hd[k] = hdr[min(i0 + k * tps + gl, n_rows - 1)];
+    for (int qd = 0; qd < M / 16; ++qd) w[qd] = *(const uint4*)(row + qd * 16);
 #pragma unroll
-        for (int k = 0; k < kInFlight; ++k) asm volatile("" : "+v"(hd[k]));
+    for (int qd = 0; qd < M / 16; ++qd) {
+      const uint32_t d[4] = {w[qd].x, w[qd].y, w[qd].z, w[qd].w};
 #pragma unroll
-        for (int k = 0; k < kInFlight; ++k) {
-          const uint32_t i = i0 + k * tps + gl;
-          const bool want = i < n_rows && entry_wanted(hd[k], r);
-          const uint64_t wm = __builtin_amdgcn_ballot_w64(want);
-          const uint32_t at = dst + (uint32_t)__popcll(wm & gbelow);
-          if (want && at < n_c) {   // always in range for entries the streaming pass wrote; keeps LDS writes in range whatever the workspace holds
-            c_pos[at] = entry_pos(hd[k]);
-            c_key[at] = (uint32_t)s_ * seg_q + codes_q + i * (M / 16);
-          }
-          dst += (uint32_t)__popcll(wm & gmask);
-        }
+      for (int t4 = 0; t4 < 16; ++t4) {
+        const uint32_t c = (d[t4 >> 2] >> (8 * (t4 & 3))) & 0xffu;
+        s += table[c * M + (((qd * 4 + (t4 >> 2) + c) & (M / 4 - 1)) << 2) + (t4 & 3)];
       }
     }
+    return s;
+  };
+  // --- the band: exact keys, then every row counts those before it in (score, position) order; of many rows only those in the
+  // bin of the K-th, of 2048 over the band's range (M = 32, 1000 rows: see band_select.hpp)
+  const uint32_t n_band = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.n_band), need = (uint32_t)sr.kk - L.n_sure;
+  const bool few = n_band <= 256u;
+  const uint32_t key0 = score_key((int32_t)((uint32_t)m_base + (t_lo << m_shift)));
+  const int kshift = max(0, 21 - (int)__clz((t_hi - t_lo + M) << m_shift));   // (a coarse score leaves out less than M units)
+  auto bin_of = [&](uint32_t key) { return min(key > key0 ? (key - key0) >> kshift : 0u, (uint32_t)kHistBins - 1); };
+  if (!few) {
+    for (int i = tid; i < kHistBins; i += NT) L.hist[i] = 0;
     __syncthreads();
-    // Pass 2: exact keys of this head's survivors, densely (no divergence), and their histogram.
-    const uint4* codes0 = (const uint4*)seg0;
-    const uint32_t last_q = (uint32_t)n_seg * seg_q - M / 16;   // the clamp below is a no-op for a consistent workspace
-#pragma unroll 2
-    for (uint32_t i = tid; i < n_c; i += NT) {
-      const uint4* e = codes0 + min(c_key[i], last_q);
-      uint4 w[M / 16];
-#pragma unroll
-      for (int qd = 0; qd < M / 16; ++qd) w[qd] = e[qd];
-      // (no finite table has a key above khi: an infinite query's does, and the bins have to hold every key in its place)
-      const uint32_t key = min(max(score_key(score_exact<M>(w, tbl, sw)), klo), khi) - klo;
-      c_key[i] = key;
-      atomicAdd(&L.hist[key >> shift1], 1u);
-    }
   }
-  const uint32_t kmin = klo;
+  if ((uint32_t)tid < n_band) {
+    const uint32_t j = (uint32_t)L.band[tid], key = score_key(exact_at(j));
+    L.band[tid] = ((uint64_t)key << 32) | ~j;   // (of equal scores the lower position is larger)
+    if (!few) atomicAdd(&L.hist[bin_of(key)], 1u);
+  }
   __syncthreads();
-  block_find_rank_desc<NT, kHistBins>([&](int i) { return L.hist[i]; }, (uint32_t)sr.kk, L.wave_a, L.res);
-  const uint32_t bin1 = L.res[0], above1 = L.res[1], m_bin = L.hist[bin1];
-  uint32_t k_rem = (uint32_t)sr.kk - above1;   // winners still to pick inside bin1
-  uint32_t kth;                                // K-th largest relative key
-  if (m_bin <= (uint32_t)kSmallList) {
-    // Usual case: the bin of the K-th key holds a handful of survivors; the k_rem-th largest of
-    // them is found by counting, for each member, the members above it.
-    for (uint32_t i = tid; i < n_c; i += NT)
-      if ((c_key[i] >> shift1) == bin1) s_small_key[atomicAdd(&s_small_n, 1u)] = c_key[i];
-    __syncthreads();
-    if ((uint32_t)tid < m_bin) {
-      const uint32_t key = s_small_key[tid];
-      uint32_t gt = 0, eq = 0;
-      for (uint32_t u = 0; u < m_bin; ++u) {
-        const uint32_t ku = s_small_key[u];
-        gt += ku > key ? 1u : 0u;
-        eq += ku == key ? 1u : 0u;
-      }
-      if (gt < k_rem && k_rem <= gt + eq) s_kth = key;   // every thread that qualifies holds this key
+  const int kth_bin = few ? 0 : wave_find_bin(L.hist, 0, need, lane, ~0u);
+  for (uint32_t i = tid >> 3; i < n_band; i += NT / 8) {   // eight lanes a row
+    const uint64_t own = L.band[i];
+    const int at = few ? 0 : (int)bin_of((uint32_t)(own >> 32));
+    if (at < kth_bin) continue;
+    int32_t before = 0;
+    if (at == kth_bin) {
+#pragma unroll 4
+      for (uint32_t u = tid & 7; u < n_band; u += 8) before += L.band[u] > own ? 1 : 0;
+      before = group8_sum(before);
     }
-    __syncthreads();
-    kth = s_kth;
-  } else {
-    // Heavy ties: finish the radix select level by level.
-    uint32_t prefix = bin1 << shift1, mask = ((1u << bits1) - 1u) << shift1;
-    int remaining = shift1;
-    __syncthreads();
-#pragma unroll 1
-    while (remaining > 0) {
-      const int bits = remaining < 11 ? remaining : 11;
-      const int shift = remaining - bits;
-      const uint32_t dmask = (1u << bits) - 1u;
-      for (int i = tid; i < kHistBins; i += NT) L.hist[i] = 0;
-      __syncthreads();
-      for (uint32_t i = tid; i < n_c; i += NT) {
-        const uint32_t key = c_key[i];
-        if ((key & mask) == prefix) atomicAdd(&L.hist[(key >> shift) & dmask], 1u);
-      }
-      __syncthreads();
-      block_find_rank_desc<NT, kHistBins>([&](int i) { return L.hist[i]; }, k_rem, L.wave_a, L.res);
-      const uint32_t bin = L.res[0], above = L.res[1];
-      k_rem -= above;
-      prefix |= bin << shift;
-      mask |= dmask << shift;
-      remaining = shift;
-      __syncthreads();
+    if ((tid & 7) == 0 && (uint32_t)before < need) {
+      const uint32_t j = ~(uint32_t)own;
+      atomicOr((uint32_t*)L.won + (j >> 5), 1u << (j & 31));
     }
-    kth = prefix;
   }
-
-  // Completeness: a row that is not a survivor has coarse score <= Tc - 1, hence exact score
-  // below base + ((Tc - 1 + M) << shift).  If the K-th survivor key reaches that bound, no such
-  // row can displace (or tie with) a winner.  Otherwise redo this head by the exact route.
+  __syncthreads();
+  // --- winners in ascending position
   {
-    const long kth_score = (long)key_score(kth + kmin);
-    if (tc != INT32_MIN && kth_score < proof_bound) {
-      if (tid == 0) route[bh] = 4u;
-      exact_select_block<M>(seq_codes, head_table, m_base, m_top, scale, sr, oi, os, tbl, L);
-      return;
+    const int per = (n_words + NT - 1) / NT, w0 = tid * per, w1 = min(n_words, w0 + per);
+    uint32_t n = 0;
+    for (int w = w0; w < w1; ++w) n += (uint32_t)__popcll(L.won[w]);
+    uint32_t total;
+    uint32_t at = block_exclusive_scan<NT>(n, L.wave_tot, total);
+    for (int w = w0; w < w1; ++w) {
+      uint64_t word = L.won[w];
+      while (word) {
+        const uint32_t j = (uint32_t)w * 64 + __ffsll((unsigned long long)word) - 1;
+        if (at < (uint32_t)sr.kk) {
+          oi[at] = sr.sink_end + (int)j;
+          if (topk_score) topk_score[(size_t)bh * top_k + at] = (float)exact_at(j) * scale;
+        }
+        ++at;
+        word &= word - 1;
+      }
     }
-    if (tid == 0) route[bh] = 0u;
-  }
-
-  // Winners: keys above the K-th, plus the first (K - #above) survivors equal to it.  Survivors
-  // are in ascending position, so a winner's output slot is the number of winners before it:
-  // one block scan over (above, equal) counts packed in a word.
-  const uint32_t per = (n_c + NT - 1) / NT;
-  const uint32_t i0 = min(n_c, (uint32_t)tid * per), i1 = min(n_c, i0 + per);
-  uint32_t loc = 0;
-  for (uint32_t i = i0; i < i1; ++i) {
-    const uint32_t key = c_key[i];
-    loc += (key > kth ? 1u : 0u) + (key == kth ? 0x10000u : 0u);
-  }
-  uint32_t tot;
-  uint32_t pre = block_exclusive_scan<NT>(loc, L.wave_b, tot);
-  const uint32_t k_eq = (uint32_t)sr.kk - (tot & 0xffffu);   // equal keys that still fit
-  for (uint32_t i = i0; i < i1; ++i) {
-    const uint32_t key = c_key[i];
-    const uint32_t gt_before = pre & 0xffffu, eq_before = pre >> 16;
-    const bool win = key > kth || (key == kth && eq_before < k_eq);
-    if (win) {
-      const uint32_t slot = gt_before + min(eq_before, k_eq);
-      oi[slot] = (int32_t)c_pos[i];
-      if (os) os[slot] = (float)key_score(key + kmin) * scale;
-    }
-    pre += (key > kth ? 1u : 0u) + (key == kth ? 0x10000u : 0u);
   }
 }
 
@@ -779,36 +784,18 @@ __global__ void copy_words_kernel(const uint32_t* __restrict__ in, uint32_t* __r
   if (i < n) out[i] = in[i];
 }
 
-__global__ void sum_segments_kernel(const uint32_t* __restrict__ seg_meta, const uint32_t* __restrict__ route,
-                                    uint32_t* __restrict__ out, int B, int Hq, int Hkv, int NG, int n_seg) {
-  const int bh = blockIdx.x * blockDim.x + threadIdx.x;
-  if (bh >= B * Hq) return;
-  const int G = Hq / Hkv, b = bh / Hq, h = bh % Hq, kv = h / G, hg = h % G;
-  const size_t prob = ((size_t)b * Hkv + kv) * NG + hg / kHeadsPerGroup;
-  uint32_t tot = 0;
-  for (int s = 0; s < n_seg; ++s) tot += seg_meta[(prob * n_seg + s) * kSegMeta + 1 + (hg % kHeadsPerGroup)];
-  out[bh] = min(tot, 0x0fffffffu) | (route[bh] << 28);
-}
-
 hipError_t copy_topk_stats(const a2ats_dims& d, int top_k, int window, int n_sink, const void* ws,
                            uint32_t* cand_counts, hipStream_t stream) {
   const TopkPlan plan = make_topk_plan(d, top_k, window, n_sink);
   const int heads = d.batch * d.n_q_heads;
   if (heads == 0) return hipSuccess;
-  if (plan.fast && plan.list) {
+  if (plan.fast) {
     hipLaunchKernelGGL(copy_words_kernel, dim3((heads + 255) / 256), dim3(256), 0, stream,
                        (const uint32_t*)((const unsigned char*)ws + plan.off_route), cand_counts, heads);
     return hipGetLastError();
   }
-  if (!plan.fast) {   // (a fill kernel, not a memset node: the call may be captured into a graph)
-    hipLaunchKernelGGL(fill_words_kernel, dim3((heads + 255) / 256), dim3(256), 0, stream, cand_counts, 0xffffffffu,
-                       heads);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(sum_segments_kernel, dim3((heads + 255) / 256), dim3(256), 0, stream,
-                     (const uint32_t*)((const unsigned char*)ws + plan.off_count),
-                     (const uint32_t*)((const unsigned char*)ws + plan.off_route), cand_counts, d.batch,
-                     d.n_q_heads, d.n_kv_heads, plan.NG, plan.chunks * kStreamWaves);
+  // (a fill kernel, not a memset node: the call may be captured into a graph)
+  hipLaunchKernelGGL(fill_words_kernel, dim3((heads + 255) / 256), dim3(256), 0, stream, cand_counts, 0xffffffffu, heads);
   return hipGetLastError();
 }
 
@@ -865,9 +852,9 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
     return hipGetLastError();
   }
   int32_t* thr = (int32_t*)(wsb + plan.off_thr);
-  uint32_t* seg_meta = (uint32_t*)(wsb + plan.off_count);
+  uint32_t* counts = (uint32_t*)(wsb + plan.off_count);
   uint32_t* route = (uint32_t*)(wsb + plan.off_route);
-  uint32_t* cand = (uint32_t*)(wsb + plan.off_cand);
+  uint32_t* lists = (uint32_t*)(wsb + plan.off_cand);
 
   if (!presampled) {   // (the fused decode launch has written the thresholds already)
     if ((err = allow_dynamic_lds(sample_threshold_kernel<M>, coarse_bytes + kSampleHistBytes, s_sample)) != hipSuccess) return err;
@@ -881,7 +868,8 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
   auto stream_kernel = paged ? (M == 16 ? stream_select_kernel16p : stream_select_kernel32p)
                              : (M == 16 ? (NG > 1 ? stream_select_kernel16r : stream_select_kernel16)
                                         : (NG > 1 ? stream_select_kernel32r : stream_select_kernel32));
-  const size_t stream_lds = coarse_bytes + (paged ? (size_t)kPageSlice * sizeof(int32_t) : 0);
+  const int list_cap = plan.row_cap * kStreamWaves;
+  const size_t stream_lds = coarse_bytes + (paged ? sizeof(StreamLds<true>) : sizeof(StreamLds<false>));
   if ((err = allow_dynamic_lds(stream_kernel, stream_lds, paged ? s_stream_p : (NG > 1 ? s_stream_r : s_stream))) !=
       hipSuccess)
     return err;
@@ -892,24 +880,24 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
   if (ev_start && ev_stop) {
     // events attached to the dispatch itself: their difference is the kernel's own duration
     hipExtLaunchKernelGGL(stream_kernel, dim3(plan.chunks * problems), dim3(kStreamThreads), stream_lds,
-                          stream, ev_start, ev_stop, 0, codes, lut, seq_lens, thr, seg_meta, cand, gm_stream, pg, B,
+                          stream, ev_start, ev_stop, 0, codes, lut, seq_lens, thr, counts, lists, gm_stream, pg, B,
                           Hq, Hkv, G, NG, plan.P0, plan.chunks, plan.rows_per_chunk,
-                          plan.row_cap, d.ctx_len, d.ctx_stride, top_k, window, n_sink);
+                          list_cap, d.ctx_len, d.ctx_stride, top_k, window, n_sink);
   } else {
     hipLaunchKernelGGL(stream_kernel, dim3(plan.chunks * problems), dim3(kStreamThreads), stream_lds,
-                       stream, codes, lut, seq_lens, thr, seg_meta, cand, gm_stream, pg, B, Hq, Hkv, G, NG, plan.P0,
-                       plan.chunks, plan.rows_per_chunk, plan.row_cap,
+                       stream, codes, lut, seq_lens, thr, counts, lists, gm_stream, pg, B, Hq, Hkv, G, NG, plan.P0,
+                       plan.chunks, plan.rows_per_chunk, list_cap,
                        d.ctx_len, d.ctx_stride, top_k, window, n_sink);
   }
   if ((err = hipGetLastError()) != hipSuccess) return err;
 
-  const size_t final_lds = lut1_bytes + (size_t)plan.cap * 8;
+  const size_t final_lds = final_lds_bytes<M>((long)d.ctx_len - window - n_sink);
   if ((err = allow_dynamic_lds(final_select_kernel<M>, final_lds, s_final)) != hipSuccess) return err;
   hipLaunchKernelGGL((final_select_kernel<M>), dim3(problems * kHeadsPerGroup), dim3(kExactThreads),
-                     final_lds, stream, codes, lut, lut_scale, seq_lens, thr, seg_meta, cand, route, topk_idx,
+                     final_lds, stream, codes, lut, lut_scale, seq_lens, thr, counts, lists, route, topk_idx,
                      topk_count, topk_score, make_grid_map(kHeadsPerGroup, problems, NG, Hkv), pg, B, Hq, Hkv, G, NG,
-                     plan.P0, plan.chunks * kStreamWaves, plan.row_cap, plan.cap, d.ctx_len, d.ctx_stride,
-                     top_k, window, n_sink);
+                     plan.P0, plan.chunks, plan.rows_per_chunk, list_cap,
+                     (long)d.ctx_len - window - n_sink <= kFinalTableCand ? 1 : 0, d.ctx_len, d.ctx_stride, top_k, window, n_sink);
   return hipGetLastError();
 }
 

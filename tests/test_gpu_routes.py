@@ -209,7 +209,7 @@ def test_attention_of_many_heads_equals_that_of_few(G, Hkv, N, K, w, n_sink, dty
     (2, 4, 16, 40000, 4000, 4),       # without a workspace the exact route, its keys scored again and again
     (40, 4, 16, 12000, 300, 4),       # a workgroup per group
     (2, 4, 16, 60000, 1500, 4),       # the streaming route
-    (34, 4, 16, 20000, 600, 4),       # lists of a workgroup per group
+    (42, 4, 16, 20000, 600, 4),       # lists of a workgroup per group
 ])
 @pytest.mark.parametrize("bad", ["inf", "nan", "huge"])
 def test_queries_that_are_not_finite_select_within_their_rows(Bn, G, M, N, K, n_sink, bad):
@@ -710,15 +710,15 @@ def test_decode_select_of_many_sequences_equals_the_calls(Bn, G, Hkv, M, N, K, w
 
 
 @pytest.mark.parametrize("Bn,Hkv,G,M,N,K,w,n_sink,lens,rows,page", [
-    (33, 2, 4, 16, 16384 + 64, 491, 64, 0, None, None, 0),               # 66 groups, the fewest candidates and groups
+    (40, 2, 4, 16, 16384 + 64, 491, 64, 0, None, None, 0),               # 80 groups, the fewest candidates and groups
     (37, 4, 2, 16, 65536 + 64 + 4, 1500, 64, 4, None, None, 0),          # the most candidates of the route
     (37, 4, 2, 16, 65536 + 64 + 5, 300, 64, 4, None, None, 0),           # one more: the streaming route
-    (21, 2, 7, 32, 20001, 1, 0, 17, None, None, 0),                      # two groups a KV head, the last one of three; one winner
-    (70, 1, 1, 32, 17000, 2300, 64, 4, True, None, 0),                   # one head; ragged, fewer candidates than K and none
-    (34, 2, 4, 16, 20000, 3700, 64, 0, None, None, 0),                   # nearly all that a list holds
-    (34, 2, 3, 16, 18000, 900, 64, 4, None, "patterns", 0),              # ~450 equal scores: ties inside the band
-    (34, 2, 4, 32, 18000, 900, 64, 4, None, "few", 0),                   # 6000 equal scores: lists overflow
-    (35, 2, 4, 32, 17001, 700, 64, 0, True, None, 16),                   # codes in pages
+    (25, 2, 7, 32, 20001, 1, 0, 17, None, None, 0),                      # two groups a KV head, the last one of three; one winner
+    (90, 1, 1, 32, 17000, 2300, 64, 4, True, None, 0),                   # one head; ragged, fewer candidates than K and none
+    (42, 2, 4, 16, 20000, 3700, 64, 0, None, None, 0),                   # nearly all that a list holds
+    (42, 2, 3, 16, 18000, 900, 64, 4, None, "patterns", 0),              # ~450 equal scores: ties inside the band
+    (42, 2, 4, 32, 18000, 900, 64, 4, None, "few", 0),                   # 6000 equal scores: lists overflow
+    (43, 2, 4, 32, 17001, 700, 64, 0, True, None, 16),                   # codes in pages
 ])
 def test_selection_by_lists_equals_a_full_sort(Bn, Hkv, G, M, N, K, w, n_sink, lens, rows, page):
     """Long contexts of many groups (one workgroup for the heads of a group, lists in LDS) against a full sort."""
@@ -752,3 +752,41 @@ def test_selection_by_lists_equals_a_full_sort(Bn, Hkv, G, M, N, K, w, n_sink, l
     if rows is None and sl is None and K <= 2048:   # no head was done again
         route = (stats.cpu().numpy().astype(np.int64) & 0xffffffff) >> 28
         assert (route == 0).all()
+
+
+@pytest.mark.parametrize("Hkv,G,M,N,K,rows,page", [
+    (2, 4, 16, 60000, 1500, "clumped", 0),      # the survivors of a head in two chunks: more than the LDS of a workgroup keeps
+    (1, 7, 32, 100000, 2500, "clumped", 16),
+    (1, 4, 16, 40000, 4000, "clumped", 0),      # ... and lists that overflow
+    (1, 3, 32, (1 << 20) - 3, 2048, None, 0),   # the longest context: more candidates than leave room for the exact table
+    (2, 4, 32, 65536, 1500, None, 0),           # a band of several hundred rows
+    (1, 4, 16, 33000, 700, "patterns", 0),      # ~820 rows at every score
+])
+def test_streamed_selection_equals_a_full_sort(Hkv, G, M, N, K, rows, page):
+    """The streaming route (lists of every chunk in memory) against a full sort."""
+    wl = synth.Workload("stream", 1, Hkv * G, Hkv, 128, M, N, K, 64, n_sink=4, seed=N + K)
+    xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
+    if rows == "patterns":
+        xd["codes"][:] = xd["codes"][:, :, torch.randint(0, 40, (N,), device="cuda")]
+    st = B.DecodeState(H.dims_of(wl), K, 64, 4, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
+    B.build_lut(st.dims, xd["q"], st.cos_b, st.sin_b, xd["codebook"], st.q_rot, st.lut, st.lut_scale)
+    if rows == "clumped":   # the best 2 K rows of the first head of every KV head come to stand together
+        table = st.lut[:Hkv * G * 256 * M].view(Hkv, G, 256 * M)[:, 0].long()
+        for kv in range(Hkv):
+            score = table[kv][xd["codes"][0, kv].long() * M + torch.arange(M, device="cuda")].sum(1)
+            order = torch.sort(score, descending=True).indices
+            order = torch.cat([order[2 * K:2 * K + N // 3], order[:2 * K], order[2 * K + N // 3:]])
+            xd["codes"][0, kv] = xd["codes"][0, kv][order].clone()
+    st.topk_idx.fill_(-7), st.topk_count.fill_(-7), st.topk_score.fill_(-7.0), st.ws.fill_(0xA5)
+    out = (st.topk_idx, st.topk_count, st.topk_score)
+    if page:
+        slots = (N + page - 1) // page
+        table = torch.randperm(slots + 2, device="cuda")[:slots].reshape(1, slots).to(torch.int32)
+        padded = torch.nn.functional.pad(xd["codes"], (0, 0, 0, slots * page - N))
+        pool = torch.zeros(slots + 2, Hkv, page, M, dtype=torch.uint8, device="cuda")
+        pool[table[0].long()] = padded.reshape(Hkv, slots, page, M).permute(1, 0, 2, 3).contiguous()
+        B.score_topk_paged(st.dims, pool, table, page, st.lut, st.lut_scale, K, 64, 4, None, *out, None, st.ws)
+    else:
+        B.score_topk(st.dims, xd["codes"], st.lut, st.lut_scale, K, 64, 4, None, *out, None, st.ws)
+    for a, b in zip((out[0], out[1], out[2].view(torch.int32)), _full_sort(wl, xd, st, None)):
+        assert torch.equal(a, b)

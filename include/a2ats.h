@@ -128,13 +128,13 @@ int a2ats_rope_tables(int32_t head_dim, const double* inv_freq, int32_t b, int32
  * Single codebook: H is the full D x D matrix (A2ATS_W_BLOCK: weights [dev, f32 Hkv*D*D], the
  * lower triangle is read) and the argmin is over 4096 codewords of all 128 dimensions:
  * codes [dev, u16 B*Hkv*ctx_stride].  With the Cholesky factor of section 4.2 (H = L L^T,
- * c^z = c L, w = c (L L^T)) the scores 1/2||c^z||^2 - k.w are formed on the matrix cores from f16
+ * c^z = c L, w = c H, ||c^z||^2 = c.w) the scores 1/2||c^z||^2 - k.w are formed on the matrix cores from f16
  * roundings of both operands, or from roundings to 8 bits (short calls, and where a sample of a KV head's
  * keys shows that these decide nearly all of them), with a centre of the codewords subtracted from keys and codewords
  * (which leaves the distances as they are) and the dimensions of k and w balanced by powers of two;
  * keys whose two best scores are closer than the rounding can account
  * for are scored again from bf16 hi/lo splits (about 2^-17 relative), and those still too close in
- * float64, so codes equal the float64 argmin.  Every weight mode needs the workspace (L, c^z and w
+ * float64, so codes equal the float64 argmin.  Every weight mode needs the workspace (H, the codewords and w
  * in their forms and the centre, 12.5 MB per KV head, 2.1 MB for short lists of such keys; 12 bytes
  * per key that ctx_stride allows); each call
  * derives them again unless weight_mode carries A2ATS_W_PREPARED (see a2ats_encode_prepare).  Up

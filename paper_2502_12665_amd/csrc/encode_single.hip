@@ -4,7 +4,7 @@
 //
 // With the Cholesky factor of section 4.2 (H = L L^T, z = k L, c^z = c L) the distortion is the
 // plain squared distance ||z - c^z||^2, and minimising it over c is minimising
-//     s_c = 1/2 ||c^z||^2 - k . w_c ,   w_c = c (L L^T) ,
+//     s_c = 1/2 ||c^z||^2 - k . w_c ,   w_c = c H ,  ||c^z||^2 = c . w_c ,
 // a dense [keys x 128] . [128 x 4096] contraction: 1 Mflop per key, the one matrix-core shape of
 // this library.
 //
@@ -16,12 +16,10 @@
 //
 // The kernels:
 //
-//   encode_single_factor_kernel    per KV head: L in float64 (Cholesky in LDS, or the identity /
-//                                  a diagonal for the unweighted / per-dimension modes); in other
-//                                  workgroups the means that the centre is taken from
-//   encode_single_heff_kernel      L L^T and the norms of its rows (full-matrix mode)
-//   encode_single_codewords_kernel the centre and t; c^z and w_c in float64, kept transposed for the exact decisions,
-//                                  1/2 ||c^z||^2, and the largest norms
+//   encode_single_matrix_kernel    H in float64 and the norms of its rows; in other workgroups the means that the centre is taken
+//                                  from, and a copy of the codewords
+//   encode_single_codewords_kernel the centre and t; w_c in float64, kept transposed for the exact decisions,
+//                                  1/2 ||c^z||^2 = 1/2 c . w_c, and the largest norms
 //   encode_single_operands_kernel  w_c in matrix-core operand order: rounded to f16, and as two bf16
 //                                  terms (hi + lo, 16 significant bits)
 //   encode_single_sample_kernel    128 keys of a KV head, which say which of the two filters it takes; of a short call all keys
@@ -47,6 +45,7 @@
 //                                  products k . w_c decides the key; 16 workgroups per key, then
 //                                  encode_single_sweep_pick_kernel.  More keys, and those of a decode
 //                                  step's first launch, are swept in single_codebook.hip
+//   encode_single_factor_kernel    per KV head: L in float64 (Cholesky in LDS; seeding only)
 //   encode_single_transform_kernel z = k L in float64, rounded once to float32 (seeding only)
 #include "common.hpp"
 #include "internal.hpp"
@@ -107,7 +106,7 @@ constexpr int kMaxSlices = 16;
 inline long near_groups(const a2ats_dims& d) { return d.n_kv_heads < 512 ? 512 / d.n_kv_heads : 1; }
 
 struct EncWs {
-  size_t off_L, off_sd, off_heff, off_means, off_center, off_czT, off_wT, off_chalf, off_cfrag, off_cbias, off_f16,
+  size_t off_L, off_sd, off_hmat, off_means, off_center, off_copy, off_wT, off_chalf, off_cfrag, off_cbias, off_f16,
       off_fbias, off_i8, off_bias8, off_cstat, off_sample, off_norms, off_eight, off_count, off_list, off_near,
       off_near_part, off_part, bytes;
   size_t near_cap;   // keys of a KV head
@@ -125,10 +124,10 @@ EncWs enc_single_ws(const a2ats_dims& d) {
   };
   w.off_L = take(Hkv * kD * kD * sizeof(double));
   w.off_sd = take(Hkv * kD * sizeof(double));
-  w.off_heff = take(Hkv * kD * kD * sizeof(double));
+  w.off_hmat = take(Hkv * kD * kD * sizeof(double));
   w.off_means = take(Hkv * kMeans * kD * sizeof(double));
   w.off_center = take(Hkv * sizeof(Center));
-  w.off_czT = take(Hkv * kD * kCW * sizeof(double));
+  w.off_copy = take(Hkv * kCW * kD * sizeof(double));   // (float32: the size is what callers have always brought)
   w.off_wT = take(Hkv * kD * kCW * sizeof(double));
   w.off_chalf = take(Hkv * kCW * sizeof(double));
   w.off_cfrag = take(Hkv * kBlocks * (size_t)kFragBytes);
@@ -175,7 +174,7 @@ __device__ __forceinline__ bool i8_scales(const CodewordStat& st, float& key_sca
 }
 
 // ------------------------------------------------------------------------------------------
-// Per KV head: the factor L (H = L L^T), 16 columns at a time.  Every wave holds the 16 diagonal rows of the panel in
+// Per KV head: the factor L (H = L L^T) for the seeding, 16 columns at a time.  Every wave holds the 16 diagonal rows of the panel in
 // lanes 0 .. 15 (all four factor them, so nothing is exchanged) and 48 of the rows below in the others, a row per
 // lane; a column's pivot and multipliers come from the diagonal rows by lane reads.  The rest of the matrix is then
 // updated on the float64 matrix cores.  What bounds it: the chain of square roots and divisions, 63 us (225 with a
@@ -191,24 +190,10 @@ __device__ __forceinline__ double lane_value(double v, int src_lane) {   // src_
 }
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void encode_single_factor_kernel(
-    const float* __restrict__ weights, int mode, double* __restrict__ Lmat, double* __restrict__ sd,
-    CodewordStat* __restrict__ cstat, const float* __restrict__ codebook, double* __restrict__ means) {
+    const float* __restrict__ weights, int mode, double* __restrict__ Lmat, double* __restrict__ sd) {
   extern __shared__ double s_A[];   // 128 rows, lower triangle in use
-  if (blockIdx.y > 0) {             // the mean of one share of the codewords
-    constexpr int kRows = kCW / kMeans;
-    const int t = threadIdx.x & (kD - 1), half = threadIdx.x / kD;
-    const float* c = codebook + ((size_t)blockIdx.x * kCW + (blockIdx.y - 1) * kRows + half * (kRows / 2)) * kD + t;
-    double sum = 0.0;
-#pragma unroll 16
-    for (int r = 0; r < kRows / 2; ++r) sum += (double)c[(size_t)r * kD];
-    if (half) s_A[t] = sum;
-    __syncthreads();
-    if (!half) means[((size_t)blockIdx.x * kMeans + blockIdx.y - 1) * kD + t] = (sum + s_A[t]) * (1.0 / kRows);
-    return;
-  }
   const int kv = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   double* L = Lmat + (size_t)kv * kD * kD;
-  if (tid == 0) cstat[kv] = CodewordStat{};
   if (mode != A2ATS_W_BLOCK) {
     if (tid < kD) sd[(size_t)kv * kD + tid] = mode == A2ATS_W_DIAG ? sqrt((double)weights[(size_t)kv * kD + tid]) : 1.0;
     return;
@@ -260,43 +245,68 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 
 // ------------------------------------------------------------------------------------------
-// L L^T, the matrix the factor stands for (equal to H up to rounding when H is positive definite;
-// the few-key route weighs with it so that both routes minimise the same distortion).
-// One workgroup per row i: thread j sums L[i][m] L[j][m] over m.  And the norm of the row.
+// What the codewords are weighed with: H in float64, mirrored from its lower triangle, and the norms of its rows (full-matrix
+// mode), or the square roots of the weights.  In other workgroups the means that the centre is taken from.
+// What bounds it: reading the codewords and writing the copy, 11 us for 8 KV heads.  (The Cholesky factor and L L^T stood here, 62 +
+// 9 us of a chain that used 8 CUs; scores need no L, as |c^z|^2 = c H c^T = c . w, and decisions between two codewords take H.)
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kD) void encode_single_heff_kernel(const double* __restrict__ Lmat, double* __restrict__ heff,
-                                                                double* __restrict__ row_norm) {
-  __shared__ double s_n[kD / 64];
-  const int kv = blockIdx.y, i = blockIdx.x, j = threadIdx.x;
-  const double* L = Lmat + (size_t)kv * kD * kD;
-  double s0 = 0.0, s1 = 0.0;
-  const int m_end = (i < j ? i : j) + 1;   // L[r][m] = 0 for m > r
-  int m = 0;
-  for (; m + 1 < m_end; m += 2) {
-    s0 += L[(size_t)i * kD + m] * L[(size_t)j * kD + m];
-    s1 += L[(size_t)i * kD + m + 1] * L[(size_t)j * kD + m + 1];
-  }
-  if (m < m_end) s0 += L[(size_t)i * kD + m] * L[(size_t)j * kD + m];
-  heff[((size_t)kv * kD + i) * kD + j] = s0 + s1;
-  double n = (s0 + s1) * (s0 + s1);
+constexpr int kMatrixRows = 16, kMatrixThreads = 1024;   // rows of H a workgroup
+__global__ __launch_bounds__(kMatrixThreads) void encode_single_matrix_kernel(
+    const float* __restrict__ weights, int mode, double* __restrict__ hmat, double* __restrict__ sd,
+    CodewordStat* __restrict__ cstat, const float* __restrict__ codebook, double* __restrict__ means, float* __restrict__ copy) {
+  constexpr int kSub = kMatrixThreads / kD;
+  __shared__ double s_sum[kSub][kD];
+  const int kv = blockIdx.x, part = (int)blockIdx.y - kMeans, t = threadIdx.x & (kD - 1), sub = threadIdx.x / kD;
+  if (part < 0) {   // the mean of one share of the codewords; and a copy of them, for calls that come with A2ATS_W_PREPARED
+    constexpr int kRows = kCW / kMeans;
+    const size_t at = ((size_t)kv * kCW + blockIdx.y * kRows + sub * (kRows / kSub)) * kD + t;
+    double sum = 0.0;
+#pragma unroll 16
+    for (int r = 0; r < kRows / kSub; ++r) {
+      const float c = codebook[at + (size_t)r * kD];
+      copy[at + (size_t)r * kD] = c;
+      sum += (double)c;
+    }
+    s_sum[sub][t] = sum;
+    __syncthreads();
+    if (sub == 0) {
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) n += __shfl_xor(n, off);
-  if ((j & 63) == 0) s_n[j >> 6] = n;
+      for (int i = 1; i < kSub; ++i) sum += s_sum[i][t];
+      means[((size_t)kv * kMeans + blockIdx.y) * kD + t] = sum * (1.0 / kRows);
+    }
+    return;
+  }
+  if (part == 0 && threadIdx.x == 0) cstat[kv] = CodewordStat{};
+  if (mode != A2ATS_W_BLOCK) {
+    if (part == 0 && sub == 0) sd[(size_t)kv * kD + t] = mode == A2ATS_W_DIAG ? sqrt((double)weights[(size_t)kv * kD + t]) : 1.0;
+    return;
+  }
+  const float* H = weights + (size_t)kv * kD * kD;
+  constexpr int kPer = kMatrixRows / kSub;
+  const int i0 = part * kMatrixRows + sub * kPer;
+#pragma unroll
+  for (int r = 0; r < kPer; ++r) {
+    const double h = (double)H[t <= i0 + r ? (size_t)(i0 + r) * kD + t : (size_t)t * kD + i0 + r];
+    hmat[((size_t)kv * kD + i0 + r) * kD + t] = h;
+    double n = h * h;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) n += __shfl_xor(n, off);
+    if ((t & 63) == 0) s_sum[sub][kPer * (t >> 6) + r] = n;   // (the two waves of a row)
+  }
   __syncthreads();
-  if (j == 0) row_norm[(size_t)kv * kD + i] = sqrt(s_n[0] + s_n[1]);
+  if (t < kPer) sd[(size_t)kv * kD + i0 + t] = sqrt(s_sum[sub][t] + s_sum[sub][kPer + t]);
 }
 
 // ------------------------------------------------------------------------------------------
-// c^z = c L and w = c (L L^T) in float64, c less the centre, and the largest norms.  A wave takes 16 codewords and all
+// w = c H and |c^z|^2 = c H c^T = c . w in float64, c less the centre, and the largest norms.  A wave takes 16 codewords and all
 // dimensions, on the float64 matrix cores: the matrix is the first operand (a row of the result is a dimension), the codewords the second
 // (a column is a codeword), so a lane's results belong to one codeword and are written to consecutive addresses.
-// 8 KV heads, full matrix: 99 -> 44 us (a thread per codeword and 32 dimensions before); with the centre 51: every workgroup
-// finds it again from the 16 means, which is less than one more launch takes.
+// The centre: every workgroup finds it again from the 16 means, which is less than one more launch takes.  (With c L for the norms
+// besides, and written: 51 us; now 44, 8 KV heads, full matrix.)
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void encode_single_codewords_kernel(
-    const float* __restrict__ codebook, int mode, const double* __restrict__ Lmat, const double* __restrict__ sd,
-    const double* __restrict__ heff, const double* __restrict__ means, Center* __restrict__ center,
-    double* __restrict__ czT, double* __restrict__ wT, double* __restrict__ chalf, float* __restrict__ cbias,
+    const float* __restrict__ codebook, int mode, const double* __restrict__ sd, const double* __restrict__ hmat,
+    const double* __restrict__ means, Center* __restrict__ center, double* __restrict__ wT, double* __restrict__ chalf, float* __restrict__ cbias,
     CodewordStat* __restrict__ cstat) {
   __shared__ float s_mu[kD], s_t[kD];
   const int kv = blockIdx.y, lane = threadIdx.x & 63, c = lane & 15, k = lane >> 4;
@@ -348,12 +358,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   auto centred = [&](int u) { return (double)cv[u] - (double)s_mu[4 * u + k]; };
   // register r of tile t: dimension 16 t + 4 r + k of codeword cg
   f64x4 acc[8];
-  auto times = [&](const double* m, bool lower) {   // acc = (c m)^T, m row-major, its rows above column blocks zero if lower
-    double row[3][8];                               // (two k-steps of the matrix in flight)
+  auto times = [&](const double* m) {   // acc = (c m)^T, m row-major
+    double row[3][8];                   // (two k-steps of the matrix in flight)
     auto request = [&](int u) {
 #pragma unroll
-      for (int t = 0; t < 8; ++t)
-        if (!lower || u >= 4 * t) row[u % 3][t] = m[(size_t)(4 * u + k) * kD + 16 * t + c];
+      for (int t = 0; t < 8; ++t) row[u % 3][t] = m[(size_t)(4 * u + k) * kD + 16 * t + c];
     };
     request(0);
     request(1);
@@ -365,48 +374,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       __builtin_amdgcn_sched_barrier(0);
       const double b = centred(u);
 #pragma unroll
-      for (int t = 0; t < 8; ++t)
-        if (!lower || u >= 4 * t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(row[u % 3][t], b, acc[t], 0, 0, 0);
+      for (int t = 0; t < 8; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(row[u % 3][t], b, acc[t], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  auto put = [&](double* out, bool balanced) {   // and the squared norm of the codeword's column
-    double n = 0.0;
-#pragma unroll
-    for (int t = 0; t < 8; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        out[((size_t)kv * kD + 16 * t + 4 * r + k) * kCW + cg] = acc[t][r];
-        const double x = balanced ? acc[t][r] * (double)inverse_of_power(s_t[16 * t + 4 * r + k]) : acc[t][r];
-        n += x * x;
-        if (balanced) w_elem = fmaxf(w_elem, fabsf((float)x));
-      }
+  auto column_sum = [&](double n) {
     n += __shfl_xor(n, 16);
     return n + __shfl_xor(n, 32);
   };
   c2 += __shfl_xor(c2, 16);
   c2 += __shfl_xor(c2, 32);
-  double z2, w2;
+  double z2 = 0.0, w2 = 0.0;
   if (mode == A2ATS_W_BLOCK) {
-    times(Lmat + (size_t)kv * kD * kD, true);
-    z2 = put(czT, false);
+    times(hmat + (size_t)kv * kD * kD);
     // (the differences are taken again: kept in float64, they would spill)
 #pragma unroll
     for (int u = 0; u < kD / 4; ++u) asm volatile("" : "+v"(cv[u]));
-    // the distortion is |z|^2 - 2 k . w + |c^z|^2, so scores need no z
-    times(heff + (size_t)kv * kD * kD, false);
-    w2 = put(wT, true);
+#pragma unroll
+    for (int u = 0; u < kD / 4; ++u) z2 += acc[u / 4][u % 4] * centred(u);
   } else {
-    double s[kD / 4];
 #pragma unroll
-    for (int u = 0; u < kD / 4; ++u) s[u] = sd[(size_t)kv * kD + 4 * u + k];
-#pragma unroll
-    for (int u = 0; u < kD / 4; ++u) acc[u / 4][u % 4] = centred(u) * s[u];
-    z2 = put(czT, false);
-#pragma unroll
-    for (int u = 0; u < kD / 4; ++u) acc[u / 4][u % 4] *= s[u];
-    w2 = put(wT, true);
+    for (int u = 0; u < kD / 4; ++u) {
+      const double s = sd[(size_t)kv * kD + 4 * u + k], z = centred(u) * s;
+      z2 += z * z;
+      acc[u / 4][u % 4] = z * s;
+    }
   }
+#pragma unroll
+  for (int t = 0; t < 8; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      wT[((size_t)kv * kD + 16 * t + 4 * r + k) * kCW + cg] = acc[t][r];
+      const double x = acc[t][r] * (double)inverse_of_power(s_t[16 * t + 4 * r + k]);
+      w2 += x * x;
+      w_elem = fmaxf(w_elem, fabsf((float)x));
+    }
+  z2 = column_sum(z2);
+  w2 = column_sum(w2);
   if (k == 0) {
     cbias[(size_t)kv * kCW + cg] = (float)(0.5 * z2);
     chalf[(size_t)kv * kCW + cg] = 0.5 * z2;
@@ -1404,82 +1408,79 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
 // ------------------------------------------------------------------------------------------
 // Exact decisions in float64
 // ------------------------------------------------------------------------------------------
+// Between two codewords by their distortions, e H e^T of e = k - c: half of the threads for each, a dimension a thread.  Where
+// three are close, by the smallest 1/2 |c^z|^2 - k . w_c of all, in the order of the few-key sweep.
 __global__ __launch_bounds__(256) void encode_single_recheck_kernel(
-    const float* __restrict__ keys, const Center* __restrict__ center, int mode, const double* __restrict__ Lmat,
-    const double* __restrict__ sd, const double* __restrict__ czT, uint16_t* __restrict__ codes, const uint32_t* __restrict__ counter,
+    const float* __restrict__ keys, const float* __restrict__ codebook, const Center* __restrict__ center, int mode,
+    const double* __restrict__ hmat, const double* __restrict__ sd, const double* __restrict__ wT,
+    const double* __restrict__ chalf, uint16_t* __restrict__ codes, const uint32_t* __restrict__ counter,
     const uint32_t* __restrict__ list, int Hkv, int n_new, int pos0, int64_t ctx_stride) {
-  __shared__ double s_k[kD], s_z[kD], s_d[256];
+  __shared__ double s_e[2][kD], s_d[256], s_part[4];
   __shared__ int s_i[256];
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, t = tid & (kD - 1), half = tid / kD;
   const uint32_t count = *counter;
   for (uint32_t it = blockIdx.x; it < count; it += gridDim.x) {
     const uint32_t key = list[2 * (size_t)it] & 0x7fffffffu, pair = list[2 * (size_t)it + 1];
     const bool full = (list[2 * (size_t)it] >> 31) != 0;
     const int bkv = (int)(key / (uint32_t)n_new), j = (int)(key % (uint32_t)n_new), kv = bkv % Hkv;
+    uint16_t* out = codes + (size_t)bkv * ctx_stride + pos0 + j;
+    const float x = keys[((size_t)bkv * n_new + j) * kD + t];
     __syncthreads();   // the arrays of the key before are still being read
-    if (tid < kD) s_k[tid] = (double)keys[((size_t)bkv * n_new + j) * kD + tid] - (double)center[kv].mu[tid];
-    __syncthreads();
-    if (tid < kD) {
-      double z;
-      if (mode == A2ATS_W_BLOCK) {
-        const double* L = Lmat + (size_t)kv * kD * kD;
-        z = 0.0;
-        for (int r = tid; r < kD; ++r) z += s_k[r] * L[(size_t)r * kD + tid];
-      } else {
-        z = s_k[tid] * sd[(size_t)kv * kD + tid];
-      }
-      s_z[tid] = z;
-    }
-    __syncthreads();
-    const double* cz = czT + (size_t)kv * kD * kCW;
-    double best;
-    int arg;
-    if (!full) {   // between the two candidates: dimensions over threads, two sums
+    if (!full) {
       const int ca = (int)(pair & 0xffffu), cb = (int)(pair >> 16);
-      double da = 0.0, db = 0.0;
-      if (tid < kD) {
-        const double ea = s_z[tid] - cz[(size_t)tid * kCW + ca], eb = s_z[tid] - cz[(size_t)tid * kCW + cb];
-        da = ea * ea;
-        db = eb * eb;
-      }
-      s_d[tid] = da;
+      const double e = (double)x - (double)codebook[((size_t)kv * kCW + (half ? cb : ca)) * kD + t];
+      s_e[half][t] = e;
       __syncthreads();
-      for (int s = 64; s >= 1; s >>= 1) {
-        if (tid < s) s_d[tid] += s_d[tid + s];
-        __syncthreads();
+      double d;
+      if (mode == A2ATS_W_BLOCK) {
+        const double* H = hmat + (size_t)kv * kD * kD + t;
+        double y = 0.0;
+#pragma unroll 16
+        for (int r = 0; r < kD; ++r) y += s_e[half][r] * H[(size_t)r * kD];
+        d = e * y;
+      } else {
+        const double z = e * sd[(size_t)kv * kD + t];
+        d = z * z;
       }
-      const double ta = s_d[0];
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) d += __shfl_xor(d, off);
+      if ((tid & 63) == 0) s_part[tid >> 6] = d;
       __syncthreads();
-      s_d[tid] = db;
-      __syncthreads();
-      for (int s = 64; s >= 1; s >>= 1) {
-        if (tid < s) s_d[tid] += s_d[tid + s];
-        __syncthreads();
+      if (tid == 0) {
+        const double ta = s_part[0] + s_part[1], tb = s_part[2] + s_part[3];
+        *out = (uint16_t)((tb < ta || (tb == ta && cb < ca)) ? cb : ca);
       }
-      const double tb = s_d[0];
-      arg = (tb < ta || (tb == ta && cb < ca)) ? cb : ca;
-      if (tid == 0) codes[(size_t)bkv * ctx_stride + pos0 + j] = (uint16_t)arg;
       continue;
     }
-    double d[kCW / 256];
+    if (!half) s_e[0][t] = (double)x - (double)center[kv].mu[t];
+    if (__syncthreads_or(!(fabsf(x) < INFINITY))) {   // a key that is not finite is as far from all
+      if (tid == 0) *out = 0;
+      continue;
+    }
+    double best = INFINITY;
+    int arg = tid;
 #pragma unroll
-    for (int q = 0; q < kCW / 256; ++q) d[q] = 0.0;
-    for (int t = 0; t < kD; ++t) {
-      const double zt = s_z[t];
+    for (int q0 = 0; q0 < kCW / 256; q0 += 4) {
+      const double* w = wT + (size_t)kv * kD * kCW + tid + 256 * q0;
+      double p[4][2] = {};
+      for (int r = 0; r < kD / 2; ++r) {
+        const double k0 = s_e[0][r], k1 = s_e[0][kD / 2 + r];
 #pragma unroll
-      for (int q = 0; q < kCW / 256; ++q) {
-        const double e = zt - cz[(size_t)t * kCW + tid + 256 * q];
-        d[q] += e * e;
+        for (int q = 0; q < 4; ++q) {
+          p[q][0] = __builtin_fma(k0, w[(size_t)r * kCW + 256 * q], p[q][0]);
+          p[q][1] = __builtin_fma(k1, w[(size_t)(kD / 2 + r) * kCW + 256 * q], p[q][1]);
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int c = tid + 256 * (q0 + q);
+        const double value = chalf[(size_t)kv * kCW + c] - (p[q][0] + p[q][1]);
+        if (value < best) {   // (not if it is not a number)
+          best = value;
+          arg = c;
+        }
       }
     }
-    best = d[0];
-    arg = tid;
-#pragma unroll
-    for (int q = 1; q < kCW / 256; ++q)
-      if (d[q] < best) {
-        best = d[q];
-        arg = tid + 256 * q;
-      }
     s_d[tid] = best;
     s_i[tid] = arg;
     __syncthreads();
@@ -1494,7 +1495,7 @@ __global__ __launch_bounds__(256) void encode_single_recheck_kernel(
       }
       __syncthreads();
     }
-    if (tid == 0) codes[(size_t)bkv * ctx_stride + pos0 + j] = (uint16_t)s_i[0];
+    if (tid == 0) *out = (uint16_t)s_i[0];
   }
 }
 
@@ -1505,7 +1506,7 @@ __global__ void encode_single_clear_kernel(uint32_t* counter, int n, uint32_t* e
 }
 
 // The few-key (append) route of a few keys in all: every key is decided by a float64 sweep, its 4096 codewords split
-// over kSlices workgroups (one workgroup would read 4 MB by itself).  With w_c = c (L L^T) the
+// over kSlices workgroups (one workgroup would read 4 MB by itself).  With w_c = c H the
 // distortion of codeword c is |z|^2 - 2 k . w_c + |c^z|^2, so the sweep minimises
 // 1/2 |c^z|^2 - k . w_c and needs neither z nor L: one pass of dot products over wT.
 // part[key][slice] = {smallest value of the slice, its code as a double}.
@@ -1768,25 +1769,18 @@ hipError_t launch_encode_single_prepare(const a2ats_dims& d, const float* codebo
                                         void* ws, hipStream_t stream) {
   const EncWs w = enc_single_ws(d);
   uint8_t* base = (uint8_t*)ws;
-  double* Lmat = (double*)(base + w.off_L);
   double* sd = (double*)(base + w.off_sd);
   CodewordStat* cstat = (CodewordStat*)(base + w.off_cstat);
-  const size_t factor_lds = (size_t)kD * kFactorStride * sizeof(double);
-  hipError_t err = allow_dynamic_lds(encode_single_factor_kernel, factor_lds, g_factor_lds);
-  if (err != hipSuccess) return err;
   double* means = (double*)(base + w.off_means);
+  double* hmat = (double*)(base + w.off_hmat);
   Center* center = (Center*)(base + w.off_center);
-  hipLaunchKernelGGL(encode_single_factor_kernel, dim3(d.n_kv_heads, 1 + kMeans), dim3(256), factor_lds, stream, weights,
-                     mode, Lmat, sd, cstat, codebook, means);
-  if ((err = hipGetLastError()) != hipSuccess) return err;
-  double* heff = (double*)(base + w.off_heff);
-  if (mode == A2ATS_W_BLOCK) {
-    hipLaunchKernelGGL(encode_single_heff_kernel, dim3(kD, d.n_kv_heads), dim3(kD), 0, stream, Lmat, heff, sd);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-  }
+  hipLaunchKernelGGL(encode_single_matrix_kernel, dim3(d.n_kv_heads, kMeans + kD / kMatrixRows), dim3(kMatrixThreads), 0, stream, weights,
+                     mode, hmat, sd, cstat, codebook, means, (float*)(base + w.off_copy));
+  hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return err;
   hipLaunchKernelGGL(encode_single_codewords_kernel, dim3(kCW / 64, d.n_kv_heads), dim3(256), 0, stream, codebook,
-                     mode, Lmat, sd, heff, means, center, (double*)(base + w.off_czT), (double*)(base + w.off_wT),
-                     (double*)(base + w.off_chalf), (float*)(base + w.off_cbias), cstat);
+                     mode, sd, hmat, means, center, (double*)(base + w.off_wT), (double*)(base + w.off_chalf),
+                     (float*)(base + w.off_cbias), cstat);
   if ((err = hipGetLastError()) != hipSuccess) return err;
   hipLaunchKernelGGL(encode_single_operands_kernel, dim3(kBlocks, d.n_kv_heads), dim3(512), 0, stream,
                      (const double*)(base + w.off_wT), center, (const float*)(base + w.off_cbias), (uint16_t*)(base + w.off_cfrag),
@@ -1861,10 +1855,7 @@ hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_ne
   }
   const EncWs w = enc_single_ws(d);
   uint8_t* base = (uint8_t*)ws;
-  double* Lmat = (double*)(base + w.off_L);
-  double* sd = (double*)(base + w.off_sd);
   const Center* center = (const Center*)(base + w.off_center);
-  double* czT = (double*)(base + w.off_czT);
   uint8_t* cfrag = base + w.off_cfrag;
   float* cbias = (float*)(base + w.off_cbias);
   CodewordStat* cstat = (CodewordStat*)(base + w.off_cstat);
@@ -1935,8 +1926,9 @@ hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_ne
                      (NearPart*)(base + w.off_near_part), Hkv, n_new, pos0, d.ctx_stride);
   if ((err = hipGetLastError()) != hipSuccess) return err;
   const uint32_t re_grid = n_all < 2048u ? n_all : 2048u;
-  hipLaunchKernelGGL(encode_single_recheck_kernel, dim3(re_grid), dim3(256), 0, stream, keys, center, mode, Lmat, sd, czT,
-                     (uint16_t*)codes, counter, (const uint32_t*)list, Hkv, n_new, pos0, d.ctx_stride);
+  hipLaunchKernelGGL(encode_single_recheck_kernel, dim3(re_grid), dim3(256), 0, stream, keys,
+                     (const float*)(base + w.off_copy), center, mode, (const double*)(base + w.off_hmat), (const double*)(base + w.off_sd), (const double*)(base + w.off_wT),
+                     (const double*)(base + w.off_chalf), (uint16_t*)codes, counter, (const uint32_t*)list, Hkv, n_new, pos0, d.ctx_stride);
   return hipGetLastError();
 }
 
@@ -1970,7 +1962,6 @@ hipError_t launch_kmeanspp_seed(const a2ats_dims& d, const float* keys, int n_ne
   uint8_t* base = (uint8_t*)ws;
   double* Lmat = (double*)(base + w.off_L);
   double* sd = (double*)(base + w.off_sd);
-  CodewordStat* cstat = (CodewordStat*)(base + w.off_cstat);
   float* z = (float*)(base + sw.off_z);
   double* dmin = (double*)(base + sw.off_d);
   double* partial = (double*)(base + sw.off_partial);
@@ -1979,8 +1970,7 @@ hipError_t launch_kmeanspp_seed(const a2ats_dims& d, const float* keys, int n_ne
   const size_t factor_lds = (size_t)kD * kFactorStride * sizeof(double);
   hipError_t err = allow_dynamic_lds(encode_single_factor_kernel, factor_lds, g_factor_lds);
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(encode_single_factor_kernel, dim3(Hkv), dim3(256), factor_lds, stream, weights, mode, Lmat, sd,
-                     cstat, (const float*)nullptr, (double*)nullptr);
+  hipLaunchKernelGGL(encode_single_factor_kernel, dim3(Hkv), dim3(256), factor_lds, stream, weights, mode, Lmat, sd);
   if ((err = hipGetLastError()) != hipSuccess) return err;
   if (mode == A2ATS_W_BLOCK)
     hipLaunchKernelGGL(encode_single_transform_kernel, dim3((n_new + 63) / 64, bkv), dim3(256), 0, stream, keys, Lmat,

@@ -72,10 +72,15 @@ typedef __attribute__((address_space(3))) const u32x2_t* lds_u2_ptr;
 
 // The table starts at LDS address 0 (kernels without static LDS), so the v_perm result is the address itself.  `w` holds the
 // lane's code row as loaded under LaneSwizzle::row_swz.
-template <int M>
+// AHEAD: eight reads are requested before the eight before them are added up, which takes 16 registers.  The list route has them:
+// its pass over rows 80 -> 75 us (256 groups of 65536 tokens, M = 32).  In the group route and the prologues they are spilled (64
+// sequences of 16384 tokens 93 -> 135 us), and two workgroups of the streaming kernel hide the reads from each other (a
+// step of 4 sequences of 131072 76.1 -> 77.4).
+template <int M, bool AHEAD = false>
 __device__ __forceinline__ void score_coarse(const uint4 (&w)[M / 16], const LaneSwizzle<M>& sw, uint32_t& a01, uint32_t& a23) {
   a01 = 0;
   a23 = 0;
+  u32x2_t e[2][8];
 #pragma unroll
   for (int qd = 0; qd < M / 16; ++qd) {
     // z[d] = row dword (d ^ (rho >> 2))
@@ -84,12 +89,34 @@ __device__ __forceinline__ void score_coarse(const uint4 (&w)[M / 16], const Lan
     const uint32_t x2 = sw.swap1 ? wq.w : wq.z, x3 = sw.swap1 ? wq.z : wq.w;
     const uint32_t z[4] = {sw.swap2 ? x2 : x0, sw.swap2 ? x3 : x1, sw.swap2 ? x0 : x2, sw.swap2 ? x1 : x3};
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
-      const u32x2_t e = *(lds_u2_ptr)(uintptr_t)__builtin_amdgcn_perm(z[t >> 2], sw.mc[qd * 4 + (t >> 2)], sw.sel[t & 3]);
-      a01 += e.x;
-      a23 += e.y;
+    for (int t0 = 0; t0 < 16; t0 += 8) {
+      const int now = (t0 >> 3) & 1;
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+        e[now][t] = *(lds_u2_ptr)(uintptr_t)__builtin_amdgcn_perm(z[(t0 + t) >> 2], sw.mc[qd * 4 + ((t0 + t) >> 2)], sw.sel[t & 3]);
+      if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+      if (AHEAD) {   // the eight before these
+        if (qd != 0 || t0 != 0)
+#pragma unroll
+          for (int t = 0; t < 8; ++t) {
+            a01 += e[now ^ 1][t].x;
+            a23 += e[now ^ 1][t].y;
+          }
+      } else {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          a01 += e[now][t].x;
+          a23 += e[now][t].y;
+        }
+      }
     }
   }
+  if (AHEAD)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      a01 += e[1][t].x;
+      a23 += e[1][t].y;
+    }
 }
 
 // Copy a problem's coarse table from its global order [half][c][16 m] to the LDS layout above.

@@ -1,5 +1,5 @@
 // The top-K of the (up to) four query heads of a group by one workgroup, for contexts whose scores do not fit its registers:
-// the list route of a2ats_score_topk, taken where the groups fill the CUs (takes_list_route).
+// the list route of a2ats_score_topk, taken where the groups fill the CUs (list_route).
 //
 // A sample gives every head a threshold below its K-th coarse score (coarse_score.hpp); one pass over the rows
 // scores each against the four heads' coarse table, and a row that reaches a head's threshold goes to that head's list in
@@ -14,8 +14,8 @@
 // 192 -> 143 us, tables included, 256 of 32768, M = 16, K 1000 97 -> 67.
 // What bounds it (us of those two): tables 16 and 10, sample 13 and 6, the pass 81 and 31 (M = 16: the code matrix at 4.5 TB/s;
 // M = 32: LDS reads and the vector ALU, two groups read the same rows), bin 3, winners and band rows 4 and 2, band 16 and 6,
-// output 3 and 1.5: phases of one workgroup per CU one after the other.  Eight table reads requested ahead of their sums: 75 us
-// for the pass of M = 32, and more than that lost to spills elsewhere.
+// output 3 and 1.5: phases of one workgroup per CU one after the other.  With eight table reads requested ahead of their sums in
+// the pass (score_coarse): of these 143 -> 139 us, 160 groups of 60000, M = 16, K 1500 82.1 -> 79.7.
 #pragma once
 #include "common.hpp"
 #include "coarse_score.hpp"
@@ -140,7 +140,7 @@ __device__ __forceinline__ void list_select_body(
       uint32_t c[kHeadsPerGroup] = {0, 0, 0, 0};
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        score_coarse<M>(rows[u], sw, a01[u], a23[u]);
+        score_coarse<M, true>(rows[u], sw, a01[u], a23[u]);
         const uint64_t valid = __builtin_amdgcn_ballot_w64(base + u * 64 + lane < wend);
         // The low half of a word is compared as 16 bits, the high half as the whole word against the threshold shifted up.
         hit[u][0] = __builtin_amdgcn_ballot_w64((uint16_t)a01[u] >= (uint16_t)T[0]) & valid;
@@ -150,7 +150,6 @@ __device__ __forceinline__ void list_select_body(
 #pragma unroll
         for (int r = 0; r < kHeadsPerGroup; ++r) c[r] += (uint32_t)__popcll(hit[u][r]);
         if ((u & 1) || M == 32) __builtin_amdgcn_sched_barrier(0);   // 32 reads at a time: bounds live registers
-        if ((u & 1) || M == 32) __builtin_amdgcn_sched_barrier(0);   // bounds live registers
       }
       if ((c[0] | c[1] | c[2] | c[3]) == 0u) return;
       // Places in the four lists for the step's rows by one LDS atomic.

@@ -79,20 +79,23 @@ def measured_traffic(workload):
 
 
 def profiled_kernel_us(workload):
-    """Average duration of the streaming kernel in the committed rocprofv3 --kernel-trace summary of
-    this command ((None, None) if there is none): the event pair above also covers the dispatch
-    between two commands, which the profiler's kernel time does not.  Returns (us, source)."""
+    """Average duration of the kernel that reads the code matrix (the streaming kernel, or where many head
+    groups take the list route the selection that it is a part of) in the committed rocprofv3 --kernel-trace
+    summary of this command ((None, None, "stream_select_kernel") if there is none): the event pair above also
+    covers the dispatch between two commands, which the profiler's kernel time does not.
+    Returns (us, source, kernel)."""
     rel = os.path.join("profiles", f"decode_step_{workload}_kernel_stats.txt")
     path = os.path.join(ROOT, rel)
     try:
         for line in open(path):
-            if line.startswith("a2ats::stream_select_kernel"):
-                return float(line.split()[2]), (f"{rel} (rocprofv3 --kernel-trace --stats of this command at commit "
-                                                f"{_summary_commit(path)}; read from the file, not measured in "
-                                                "this run)")
+            if line.startswith(("a2ats::stream_select_kernel", "a2ats::list_select_kernel")):
+                name = "stream_select_kernel" if "stream" in line else "list_select_kernel (sample and selection in it)"
+                return float(line.split()[-3]), (f"{rel} (rocprofv3 --kernel-trace --stats of this command at commit "
+                                                 f"{_summary_commit(path)}; read from the file, not measured in "
+                                                 "this run)"), name
     except (OSError, ValueError, IndexError):
         pass
-    return None, None
+    return None, None, "stream_select_kernel"
 
 
 def measured_machine_peaks(torch):
@@ -836,7 +839,7 @@ def main():
     e = 2 if wl.kv_dtype == "bf16" else 4
     attn_bytes = Bn * Hq * min(K, N - w) * 2 * D * e + Bn * Hkv * w * 2 * D * e
     k_us = mean(kern_us)
-    prof_us, prof_src = profiled_kernel_us(wl.name)
+    prof_us, prof_src, pass_kernel = profiled_kernel_us(wl.name)
     traffic, traffic_src = measured_traffic(wl.name)
     achieved = kernel_bytes / (k_us * 1e-6) / 1e9 if k_us == k_us else None
 
@@ -862,7 +865,7 @@ def main():
         "calls_per_step": "encode_keys, build_lut, score_topk, sparse_attn" if args.separate_prologue else
                           ("decode_prologue, score_topk, sparse_attn" if args.two_calls else
                            "decode_select (prologue and threshold sampling in one launch, then the streaming and "
-                           "final kernels), sparse_attn"),
+                           "final kernels; or prologue and list selection in one launch), sparse_attn"),
         "phase_us_median": ({"encode_1key": med(ph[0]), "wrope_lut": med(ph[1])} if args.separate_prologue else
                             {"encode_1key_and_wrope_lut": med(ph[1])}) |
                            {"score_topk": med(ph[2]), "sparse_attn": med(ph[3]),
@@ -878,7 +881,7 @@ def main():
         "survivors_per_head": {"mean": float(cc.mean()), "max": int(cc.max()), "min": int(cc.min()),
                                "heads_on_exact_fallback": int((routes != 0).sum())}
         if fast_route else None,
-        "roofline": {"kernel": "stream_select_kernel", "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
+        "roofline": {"kernel": pass_kernel, "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": (achieved / HBM_PEAK_GBS) if achieved else None,
                      "traffic": traffic, "traffic_source": traffic_src,
                      "algorithmic_bytes_per_launch": kernel_bytes,

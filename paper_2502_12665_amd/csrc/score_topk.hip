@@ -330,6 +330,7 @@ constexpr int kPageSlice = 2048;
 // Behind the table: two workgroups of 80 KB fit a CU.  The rows of each wave that any head of the group wants; when they are full,
 // and at the end, they go to the lists of the heads that want them.  (Appending to four lists row by row took the pass 1.5 to 2 us
 // longer; writing these rows to memory and having every head pick its own from there took the final kernel 2.5 to 4.5.)
+// 4 sequences of 131072 tokens, K 2048, against entries with the rows' codes: 7.9 -> 1.6 MB written, 19.3 -> 18.3 us.
 template <bool PAGED>
 struct StreamLds {
   static constexpr int kCap = PAGED ? 100 : 200;
@@ -548,7 +549,8 @@ void stream_select_kernel32p(A2ATS_STREAM_ARGS) { stream_select_body<32, true, t
 // list_select.hpp.
 //
 // What bounds it: a chain of short dependent phases on one CU (entries, histogram, bin, winners, band rows from the code matrix,
-// ranks, output).
+// ranks, output).  Against exact scores of every survivor and a radix select: 14.5 -> 12.1 us (4 sequences of 131072 tokens, K
+// 2048, 128 heads), 17.0 -> 12.2 (2 of 98301, K 2949).
 constexpr int kFinalBin = 2;          // a bin of the first histogram is 4 coarse units, from the threshold up; of a second, where
 constexpr int kFinalWide = 5;         // the K-th is above those, 32, which is the whole range
 constexpr long kFinalTableCand = 1 << 19;   // candidates up to which the exact table is in LDS too

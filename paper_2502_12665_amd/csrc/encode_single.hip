@@ -415,8 +415,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     cbias[(size_t)kv * kCW + cg] = (float)(0.5 * z2);
     chalf[(size_t)kv * kCW + cg] = 0.5 * z2;
   }
-  // rounded up; a float that is not negative orders like its bits
-  uint32_t most[5] = {__float_as_uint(__double2float_ru(0.5 * z2)), __float_as_uint(__double2float_ru(sqrt(w2))),
+  // rounded up; a float that is not negative orders like its bits (c . w is negative at times where H, rounded to float32, is
+  // singular: its sign bit would stand above every magnitude)
+  uint32_t most[5] = {__float_as_uint(__double2float_ru(0.5 * fabs(z2))), __float_as_uint(__double2float_ru(sqrt(w2))),
                       __float_as_uint(1.00001f * sqrtf(c2)), __float_as_uint(w_elem), __float_as_uint(c_elem)};
   __shared__ uint32_t s_most[4][5];
 #pragma unroll

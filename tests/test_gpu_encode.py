@@ -175,12 +175,17 @@ def test_single_codebook_keys_near_their_codewords(n_new, batch, kv, mode):
             assert (lost <= 1e-13 * (half.max() + k.norm(dim=1) * w.norm(dim=1).max())).all(), float(lost.max())
 
 
-def _chosen_filters(ws, kv):
-    """What a call left in its workspace: per KV head 1 if its sample took the i8 filter and 0 if the f16 one, and neither where
-    there was no filter.  (The regions before it, as enc_single_ws lays them out.)"""
+def _prepared_at(kv, region):
+    """Where a region of the encoder's workspace begins, as enc_single_ws lays them out."""
     per_head = [128 * 128 * 8, 128 * 8, 128 * 128 * 8, 16 * 128 * 8, 4 * 128 * 4, 128 * 4096 * 8, 128 * 4096 * 8, 4096 * 8,
                 4096 * 512, 4096 * 4, 4096 * 256, 4096 * 4, 4096 * 128, 4096 * 4, 128, 32 * 128 * 8, 128 * 8]
-    at = sum((kv * n + 255) // 256 * 256 for n in per_head)
+    return sum((kv * n + 255) // 256 * 256 for n in per_head[:region])
+
+
+def _chosen_filters(ws, kv):
+    """What a call left in its workspace: per KV head 1 if its sample took the i8 filter and 0 if the f16 one, and neither where
+    there was no filter."""
+    at = _prepared_at(kv, 17)
     return ws[at:at + 4 * kv].view(torch.int32).tolist()
 
 
@@ -295,6 +300,38 @@ def test_single_codebook_keys_short_against_codewords_of_one_length(mode):
             lost = score.gather(1, got[0, h][:, None])[:, 0] - score.min(1).values
             # (float64 sums of 128 products, of L L^T instead of H)
             assert (lost <= 1e-13 * (half.max() + k.norm(dim=1) * w.norm(dim=1).max())).all(), (size, int((lost > 1e-13).sum()))
+
+
+@pytest.mark.parametrize("rank", [1, 5])
+@pytest.mark.parametrize("n", [20, 3001])
+def test_single_codebook_weights_without_full_rank(rank, n):
+    """H of few queries: rounded to float32 it has small negative eigenvalues, and so c H c^T of some codewords (the first 64,
+    orthogonal to the queries).  The bound on |c H c^T| is that of the magnitudes, and codes still minimise the distortion."""
+    kv = 2
+    wl = synth.Workload("enc1_rank", 1, kv, kv, 128, 1, n + 8, 16, 16, seed=n + rank, n_centroids=4096)
+    codebook = synth.make_codebook(wl, "cuda")
+    g = torch.Generator(device="cuda").manual_seed(rank)
+    basis = torch.linalg.qr(torch.randn(kv, 128, rank, generator=g, device="cuda", dtype=torch.float64)).Q
+    weights = (128.0 * basis @ basis.transpose(1, 2).contiguous()).float()
+    weights = torch.tril(weights) + torch.tril(weights, -1).transpose(1, 2)
+    flat = codebook[:, 0, :64].double()
+    codebook[:, 0, :64] = (flat - (flat @ basis) @ basis.transpose(1, 2).contiguous()).float()
+    codebook = torch.stack([codebook[:, :, :2048], -codebook[:, :, :2048]], 3).reshape(codebook.shape).contiguous()   # no centre
+    keys = synth.make_encode_keys(wl, n, device="cuda", stress=True)
+    dims = B.make_dims(1, kv, kv, 128, 1, n + 8, n_centroids=4096)
+    ws = torch.full((B.workspace_bytes(dims, B.OP_ENCODE),), 0xA5, dtype=torch.uint8, device="cuda")
+    codes = torch.full((1, kv, n + 8), -2, dtype=torch.int16, device="cuda")
+    B.encode_keys(dims, keys, n, 0, codebook, weights.contiguous(), B.W_BLOCK, codes, ws)
+    most = ws[_prepared_at(kv, 14):][:kv * 128].view(torch.float32).view(kv, 32)[:, 2]
+    for h in range(kv):
+        c, k, got = codebook[h, 0].double(), keys[0, h].double(), codes[0, h, :n].long()
+        w = c @ weights[h].double()
+        half = 0.5 * (w * c).sum(-1)
+        assert half.min() < 0.0
+        assert 0.999 * half.abs().max() <= most[h] <= 1.001 * half.abs().max()
+        score = half - k @ w.t()
+        lost = score.gather(1, got[:, None])[:, 0] - score.min(1).values
+        assert (lost <= 1e-13 * (half.max() + k.norm(dim=1) * w.norm(dim=1).max())).all(), float(lost.max())
 
 
 @pytest.mark.parametrize("kv,n", [(8, 12001), (8, 20100), (2, 33000)])

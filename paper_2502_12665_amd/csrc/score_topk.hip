@@ -554,6 +554,7 @@ void stream_select_kernel32p(A2ATS_STREAM_ARGS) { stream_select_body<32, true, t
 constexpr int kFinalBin = 2;          // a bin of the first histogram is 4 coarse units, from the threshold up; of a second, where
 constexpr int kFinalWide = 5;         // the K-th is above those, 32, which is the whole range
 constexpr long kFinalTableCand = 1 << 19;   // candidates up to which the exact table is in LDS too
+constexpr long kFinalMostCand = 1 << 20;    // the longest context
 struct FinalLds {
   uint32_t hist[kHistBins];
   uint64_t band[kBandCap];
@@ -894,7 +895,9 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
   if ((err = hipGetLastError()) != hipSuccess) return err;
 
   const size_t final_lds = final_lds_bytes<M>((long)d.ctx_len - window - n_sink);
-  if ((err = allow_dynamic_lds(final_select_kernel<M>, final_lds, s_final)) != hipSuccess) return err;
+  // (allowed once for all contexts: threads that each raise it to their own call's size could lower one another's)
+  const size_t final_most = std::max(final_lds_bytes<M>(kFinalTableCand), final_lds_bytes<M>(kFinalMostCand));
+  if ((err = allow_dynamic_lds(final_select_kernel<M>, final_most, s_final)) != hipSuccess) return err;
   hipLaunchKernelGGL((final_select_kernel<M>), dim3(problems * kHeadsPerGroup), dim3(kExactThreads),
                      final_lds, stream, codes, lut, lut_scale, seq_lens, thr, counts, lists, route, topk_idx,
                      topk_count, topk_score, make_grid_map(kHeadsPerGroup, problems, NG, Hkv), pg, B, Hq, Hkv, G, NG,

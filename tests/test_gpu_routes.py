@@ -1,5 +1,7 @@
 """The routes of a2ats_score_topk against each other: the same tables and codes through two of them give
 the same indices, counts and scores, bit for bit."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -790,3 +792,41 @@ def test_streamed_selection_equals_a_full_sort(Hkv, G, M, N, K, rows, page):
         B.score_topk(st.dims, xd["codes"], st.lut, st.lut_scale, K, 64, 4, None, *out, None, st.ws)
     for a, b in zip((out[0], out[1], out[2].view(torch.int32)), _full_sort(wl, xd, st, None)):
         assert torch.equal(a, b)
+
+
+def test_streamed_selections_of_several_threads_equal_a_full_sort():
+    """The final kernel's LDS grows with the context: short and the longest contexts selected by threads side by side, each on
+    a stream of its own."""
+    def prepared(n):
+        wl = synth.Workload("threads", 1, 2, 2, 128, 16, n, 500, 64, n_sink=4, seed=n)
+        xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
+        st = B.DecodeState(H.dims_of(wl), 500, 64, 4, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
+        B.build_lut(st.dims, xd["q"], st.cos_b, st.sin_b, xd["codebook"], st.q_rot, st.lut, st.lut_scale)
+        st.topk_idx.fill_(-7), st.topk_count.fill_(-7), st.topk_score.fill_(-7.0)
+        return wl, xd, st
+
+    calls = [prepared(n) for n in (20000, 1 << 20, 33000, (1 << 20) - 70)]
+    torch.cuda.synchronize()
+    start = threading.Barrier(len(calls))
+    failed = []
+
+    def select(wl, xd, st):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                start.wait(timeout=60)
+                for _ in range(3):
+                    B.score_topk(st.dims, xd["codes"], st.lut, st.lut_scale, 500, 64, 4, None, st.topk_idx, st.topk_count,
+                                 st.topk_score, None, st.ws)
+                torch.cuda.current_stream().synchronize()
+        except Exception as e:   # (an exception of a thread would not fail the test)
+            failed.append(e)
+
+    threads = [threading.Thread(target=select, args=c) for c in calls]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed
+    for wl, xd, st in calls:
+        for a, b in zip((st.topk_idx, st.topk_count, st.topk_score.view(torch.int32)), _full_sort(wl, xd, st, None)):
+            assert torch.equal(a, b)

@@ -40,13 +40,15 @@
 //   encode_single_recheck_kernel   keys whose two smallest scores are closer than the rounding reach
 //                                  of the bf16 products are decided in float64 between those two
 //                                  codewords; keys with three that close by a float64 sweep over all
-//                                  4096.  So the emitted code is the float64 argmin.
+//                                  4096, and again between those that its rounding leaves open.  So the
+//                                  emitted code is the float64 argmin.
 //   encode_single_sweep_kernel     the few-key (decode-time append) route: one float64 pass of dot
 //                                  products k . w_c decides the key; 16 workgroups per key, then
 //                                  encode_single_sweep_pick_kernel.  More keys, and those of a decode
 //                                  step's first launch, are swept in single_codebook.hip
 //   encode_single_factor_kernel    per KV head: L in float64 (Cholesky in LDS; seeding only)
 //   encode_single_transform_kernel z = k L in float64, rounded once to float32 (seeding only)
+#include <algorithm>
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -102,6 +104,7 @@ struct NearPart {
   uint32_t codes;
 };
 constexpr int kMaxSlices = 16;
+constexpr int kFoundStride = 64;   // words between the counts of two KV heads' keys for float64 (a cache line each)
 // Workgroups per KV head that work on its list.
 inline long near_groups(const a2ats_dims& d) { return d.n_kv_heads < 512 ? 512 / d.n_kv_heads : 1; }
 
@@ -140,9 +143,9 @@ EncWs enc_single_ws(const a2ats_dims& d) {
   w.off_sample = take(Hkv * kSampleSlices * kSampleKeys * sizeof(int2));
   w.off_norms = take(Hkv * kSampleKeys * sizeof(float2));
   w.off_eight = take(Hkv * sizeof(uint32_t));
-  // keys for float64, listed keys per KV head, arrivals per KV head and chunk of its list
-  w.off_count = take((1 + Hkv + Hkv * (size_t)near_groups(d)) * sizeof(uint32_t));
-  w.off_list = take(keys_max * 2 * sizeof(uint32_t));
+  // listed keys per KV head, arrivals per KV head and chunk of its list
+  w.off_count = take((Hkv + Hkv * (size_t)near_groups(d)) * sizeof(uint32_t));
+  w.off_list = take(keys_max * 2 * sizeof(uint32_t));   // keys for float64, by KV head; their counts are in the factor's place
   w.near_cap = (size_t)d.batch * (size_t)d.ctx_stride;
   w.off_near = take(keys_max * sizeof(uint32_t));
   w.off_near_part = take(Hkv * (size_t)near_groups(d) * kKeysPerWG * sizeof(NearPart));
@@ -632,7 +635,7 @@ template <bool ALL>
 __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void encode_single_sample_kernel(
     const float* __restrict__ keys, const Center* __restrict__ center, const uint8_t* __restrict__ i8,
     const int* __restrict__ bias8, int2* __restrict__ sample, float2* __restrict__ norms, uint32_t* __restrict__ counter,
-    int n_counter, int n_new, long n_rows) {
+    int n_counter, uint32_t* __restrict__ found, int n_new, long n_rows) {
   static_assert(kSampleKeys == 32 * kEncWaves, "a wave takes 32 keys");
   constexpr int kOwn = kBlocks / kSampleSlices;
   static_assert(32 * kOwn <= 512, "a number has 9 bits");
@@ -640,6 +643,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, g = lane >> 5;
   const int slice = blockIdx.x, kv = blockIdx.y, Hkv = gridDim.y, at = blockIdx.z * kSampleKeys + wave * 32 + col;
   for (int i = (kv * kSampleSlices + slice) * kEncThreads + tid; i < n_counter; i += Hkv * kSampleSlices * kEncThreads) counter[i] = 0;
+  if (slice == 0 && tid == 0) found[kv * kFoundStride] = 0;
   if (tid < kD) {
     s_mu[tid] = center[kv].mu[tid];
     s_key[tid] = center[kv].key8[tid];
@@ -1168,7 +1172,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
     const float* __restrict__ keys, const Center* __restrict__ center, const uint8_t* __restrict__ cfrag,
     const float* __restrict__ cbias, const CodewordStat* __restrict__ cstat, uint16_t* __restrict__ codes,
     const uint32_t* __restrict__ near_count, const uint32_t* __restrict__ near, int64_t near_cap,
-    uint32_t* __restrict__ counter, uint32_t* __restrict__ list, uint32_t* __restrict__ arrived, NearPart* parts, int Hkv,
+    uint32_t* __restrict__ found, uint32_t* __restrict__ list, uint32_t* __restrict__ arrived, NearPart* parts, int Hkv,
     int n_new, int pos0, int64_t ctx_stride) {
   __shared__ __align__(16) uint8_t s_mem[2 * (kFragBytes + 128)];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, g = lane >> 5;
@@ -1397,10 +1401,10 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
         const float reach = kSplitReach * sqrtf(zn2[tile]) * wmax + kSumReach * fabsf(s1[tile]);
         codes[row / n_new * ctx_stride + pos0 + row % n_new] = (uint16_t)d1[tile];
         if (!(s2[tile] - s1[tile] > reach)) {
-          const uint32_t at = atomicAdd(counter, 1u);
           const uint32_t full = !(s3[tile] - s1[tile] > reach) ? 0x80000000u : 0u;
-          list[2 * (size_t)at] = (uint32_t)row | full;
-          list[2 * (size_t)at + 1] = (uint32_t)d1[tile] | ((uint32_t)d2[tile] << 16);
+          uint32_t* at = list + 2 * ((size_t)kv * near_cap + atomicAdd(&found[kv * kFoundStride], 1u));
+          at[0] = (uint32_t)row | full;
+          at[1] = (uint32_t)d1[tile] | ((uint32_t)d2[tile] << 16);
         }
       }
   }
@@ -1409,100 +1413,217 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2, 
 // ------------------------------------------------------------------------------------------
 // Exact decisions in float64
 // ------------------------------------------------------------------------------------------
-// Between two codewords by their distortions, e H e^T of e = k - c: half of the threads for each, a dimension a thread.  Where
-// three are close, by the smallest 1/2 |c^z|^2 - k . w_c of all, in the order of the few-key sweep.
-__global__ __launch_bounds__(256) void encode_single_recheck_kernel(
-    const float* __restrict__ keys, const float* __restrict__ codebook, const Center* __restrict__ center, int mode,
-    const double* __restrict__ hmat, const double* __restrict__ sd, const double* __restrict__ wT,
-    const double* __restrict__ chalf, uint16_t* __restrict__ codes, const uint32_t* __restrict__ counter,
-    const uint32_t* __restrict__ list, int Hkv, int n_new, int pos0, int64_t ctx_stride) {
-  __shared__ double s_e[2][kD], s_d[256], s_part[4];
+// How much further codeword c is from a key than codeword b: with e = k - c and H symmetric, e_c H e_c^T - e_b H e_b^T =
+// (w_b - w_c) . (e_b + e_c).  Differences are taken first, so the error goes with the distances |e|, not with |k|.
+//
+// Keys with two close codewords take a wave each, two dimensions a lane, two keys requested together; keys with three, the
+// whole workgroup: first the smallest 1/2 |c^z|^2 - k . w_c of all codewords, whose error goes with |k| |w|, and then every
+// codeword that this leaves open against that one.
+// What bounds it: for pairs the columns of wT, 256 cache lines for each (a KV head's keys are a list of their own, so that with 8
+// KV heads an XCD reads the columns of one); for the others the 4 MB that one workgroup reads, 60 us.  4194304 keys drawn like
+// their codewords, 8061 pairs and 14 of three: 448 -> 107 us against e H e^T of every pair and codewords one row after the other.
+constexpr int kPairsAhead = 2, kRecheckBatch = 16;   // keys of a wave: requested together, between two looks at who has three
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4))) void encode_single_recheck_kernel(
+    const float* __restrict__ keys, const float* __restrict__ codebook, const Center* __restrict__ center,
+    const CodewordStat* __restrict__ cstat, const double* __restrict__ wT, const double* __restrict__ chalf,
+    uint16_t* __restrict__ codes, const uint32_t* __restrict__ found, const uint32_t* __restrict__ lists, int64_t near_cap, int n_new,
+    int pos0, int64_t ctx_stride) {
+  constexpr int kWaves = 4, kPer = kCW / 256;
+  __shared__ double s_k[kD], s_x[kD], s_e[kD], s_w[kD], s_d[256], s_n[kWaves];
   __shared__ int s_i[256];
-  const int tid = threadIdx.x, t = tid & (kD - 1), half = tid / kD;
-  const uint32_t count = *counter;
-  for (uint32_t it = blockIdx.x; it < count; it += gridDim.x) {
-    const uint32_t key = list[2 * (size_t)it] & 0x7fffffffu, pair = list[2 * (size_t)it + 1];
-    const bool full = (list[2 * (size_t)it] >> 31) != 0;
-    const int bkv = (int)(key / (uint32_t)n_new), j = (int)(key % (uint32_t)n_new), kv = bkv % Hkv;
-    uint16_t* out = codes + (size_t)bkv * ctx_stride + pos0 + j;
-    const float x = keys[((size_t)bkv * n_new + j) * kD + t];
-    __syncthreads();   // the arrays of the key before are still being read
-    if (!full) {
-      const int ca = (int)(pair & 0xffffu), cb = (int)(pair >> 16);
-      const double e = (double)x - (double)codebook[((size_t)kv * kCW + (half ? cb : ca)) * kD + t];
-      s_e[half][t] = e;
-      __syncthreads();
-      double d;
-      if (mode == A2ATS_W_BLOCK) {
-        const double* H = hmat + (size_t)kv * kD * kD + t;
-        double y = 0.0;
-#pragma unroll 16
-        for (int r = 0; r < kD; ++r) y += s_e[half][r] * H[(size_t)r * kD];
-        d = e * y;
-      } else {
-        const double z = e * sd[(size_t)kv * kD + t];
-        d = z * z;
-      }
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) d += __shfl_xor(d, off);
-      if ((tid & 63) == 0) s_part[tid >> 6] = d;
-      __syncthreads();
-      if (tid == 0) {
-        const double ta = s_part[0] + s_part[1], tb = s_part[2] + s_part[3];
-        *out = (uint16_t)((tb < ta || (tb == ta && cb < ca)) ? cb : ca);
-      }
-      continue;
+  __shared__ uint32_t s_full[kWaves], s_n_open;
+  __shared__ uint16_t s_open[kCW];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kv = blockIdx.x;
+  codebook += (size_t)kv * kCW * kD;
+  wT += (size_t)kv * kD * kCW;
+  chalf += (size_t)kv * kCW;
+  const uint32_t* list = lists + 2 * (size_t)kv * near_cap;
+  const uint32_t count = found[kv * kFoundStride], n_waves = gridDim.y * kWaves;
+  const uint32_t per = min((uint32_t)kRecheckBatch, (count + n_waves - 1) / n_waves);
+  auto out_of = [&](uint32_t key) -> uint16_t* { return codes + (size_t)(key / (uint32_t)n_new) * ctx_stride + pos0 + key % (uint32_t)n_new; };
+  for (uint32_t base = blockIdx.y * kWaves * per; base < count; base += n_waves * per) {
+    const uint32_t first = base + (uint32_t)wv * per, n = first < count ? min(per, count - first) : 0u;
+    uint32_t key = 0, pair = 0;   // of the wave's key `lane`
+    if ((uint32_t)lane < n) {
+      const uint2 e = *(const uint2*)(list + 2 * (size_t)(first + lane));
+      key = e.x;
+      pair = e.y;
     }
-    if (!half) s_e[0][t] = (double)x - (double)center[kv].mu[t];
-    if (__syncthreads_or(!(fabsf(x) < INFINITY))) {   // a key that is not finite is as far from all
-      if (tid == 0) *out = 0;
-      continue;
-    }
-    double best = INFINITY;
-    int arg = tid;
+    const uint32_t full = (uint32_t)__builtin_amdgcn_ballot_w64((key >> 31) != 0u);   // (lanes past the wave's keys: 0)
+    if (lane == 0) s_full[wv] = full;
+    for (uint32_t i0 = 0; i0 < n; i0 += kPairsAhead) {
+      double wa[kPairsAhead][2], wb[kPairsAhead][2];
+      float x[kPairsAhead][2], a[kPairsAhead][2], b[kPairsAhead][2];
 #pragma unroll
-    for (int q0 = 0; q0 < kCW / 256; q0 += 4) {
-      const double* w = wT + (size_t)kv * kD * kCW + tid + 256 * q0;
-      double p[4][2] = {};
-      for (int r = 0; r < kD / 2; ++r) {
-        const double k0 = s_e[0][r], k1 = s_e[0][kD / 2 + r];
+      for (int u = 0; u < kPairsAhead; ++u) {
+        const int i = (int)min(i0 + u, n - 1);
+        const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)key, i) & 0x7fffffffu;
+        const uint32_t two = (full >> i) & 1u ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)pair, i);
+        const uint32_t ca = two & 0xffffu, cb = two >> 16;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          p[q][0] = __builtin_fma(k0, w[(size_t)r * kCW + 256 * q], p[q][0]);
-          p[q][1] = __builtin_fma(k1, w[(size_t)(kD / 2 + r) * kCW + 256 * q], p[q][1]);
+        for (int h = 0; h < 2; ++h) {
+          const int t = lane + 64 * h;
+          x[u][h] = keys[(size_t)row * kD + t];
+          a[u][h] = codebook[ca * kD + t];
+          b[u][h] = codebook[cb * kD + t];
+          wa[u][h] = wT[(uint32_t)t * kCW + ca];
+          wb[u][h] = wT[(uint32_t)t * kCW + cb];
         }
       }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int c = tid + 256 * (q0 + q);
-        const double value = chalf[(size_t)kv * kCW + c] - (p[q][0] + p[q][1]);
-        if (value < best) {   // (not if it is not a number)
-          best = value;
-          arg = c;
-        }
+      for (int u = 0; u < kPairsAhead; ++u) {
+        double d = 0.0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          d += (wa[u][h] - wb[u][h]) * (((double)x[u][h] - (double)a[u][h]) + ((double)x[u][h] - (double)b[u][h]));
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) d += __shfl_xor(d, off);
+        const int i = (int)(i0 + u);
+        if (i0 + u >= n || ((full >> i) & 1u)) continue;   // (uniform)
+        const uint32_t two = (uint32_t)__builtin_amdgcn_readlane((int)pair, i), ca = two & 0xffffu, cb = two >> 16;
+        if (lane == 0)
+          *out_of((uint32_t)__builtin_amdgcn_readlane((int)key, i)) = (uint16_t)(d < 0.0 || (d == 0.0 && cb < ca) ? cb : ca);
       }
     }
-    s_d[tid] = best;
-    s_i[tid] = arg;
     __syncthreads();
-    for (int s = 128; s >= 1; s >>= 1) {
-      if (tid < s) {
-        const double o = s_d[tid + s];
-        const int oi = s_i[tid + s];
-        if (o < s_d[tid] || (o == s_d[tid] && oi < s_i[tid])) {
-          s_d[tid] = o;
-          s_i[tid] = oi;
+    for (int v = 0; v < kWaves; ++v)
+      for (uint32_t left = s_full[v]; left != 0u; left &= left - 1u) {   // (uniform)
+        const uint32_t row = list[2 * (size_t)(base + v * per + (__ffs((int)left) - 1))] & 0x7fffffffu;
+        const int t = tid & (kD - 1);
+        const float x = keys[(size_t)row * kD + t];
+        const double from_mu = (double)x - (double)center[kv].mu[t];
+        __syncthreads();   // the arrays of the key before are still being read
+        if (tid < kD) {
+          s_k[t] = from_mu;
+          s_x[t] = (double)x;
         }
+        double kt = from_mu * (double)center[kv].t[t];
+        kt *= kt;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) kt += __shfl_xor(kt, off);
+        if (lane == 0) s_n[wv] = kt;
+        if (__syncthreads_or(!(fabsf(x) < INFINITY))) {   // a key that is not finite is as far from all
+          if (tid == 0) *out_of(row) = 0;
+          continue;
+        }
+        double value[kPer], best = INFINITY;
+        int arg = tid;
+        constexpr int kGo = 8, kRows = 1;   // codewords a thread sums at a time; rows of each half requested together (2: spills)
+#pragma unroll
+        for (int q0 = 0; q0 < kPer; q0 += kGo) {
+          double p[kGo][2] = {}, w[2][kRows][kGo][2];
+          auto request = [&](int r, int buffer) {
+#pragma unroll
+            for (int u = 0; u < kRows; ++u)
+#pragma unroll
+              for (int h = 0; h < 2; ++h) {
+                const double* row = wT + (size_t)(min(r + u, kD / 2 - 1) + h * (kD / 2)) * kCW + 256 * q0;
+                asm volatile("" : "+s"(row));   // (else an address of every load is kept by every lane, and spilled)
+#pragma unroll
+                for (int q = 0; q < kGo; ++q) w[buffer][u][q][h] = row[(uint32_t)(tid + 256 * q)];
+              }
+            __builtin_amdgcn_sched_barrier(0);
+          };
+          auto add = [&](int r, int buffer) {
+#pragma unroll
+            for (int u = 0; u < kRows; ++u)
+#pragma unroll
+              for (int q = 0; q < kGo; ++q)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) p[q][h] = __builtin_fma(s_k[r + u + h * (kD / 2)], w[buffer][u][q][h], p[q][h]);
+            __builtin_amdgcn_sched_barrier(0);
+          };
+          request(0, 0);
+#pragma unroll 1
+          for (int r = 0; r < kD / 2; r += 2 * kRows) {
+            request(r + kRows, 1);
+            add(r, 0);
+            request(r + 2 * kRows, 0);
+            add(r + kRows, 1);
+          }
+          const double* half = chalf + 256 * q0;
+          asm volatile("" : "+s"(half));
+#pragma unroll
+          for (int q = 0; q < kGo; ++q) {
+            value[q0 + q] = half[(uint32_t)(tid + 256 * q)] - (p[q][0] + p[q][1]);
+            if (value[q0 + q] < best) {   // (not if it is not a number)
+              best = value[q0 + q];
+              arg = tid + 256 * (q0 + q);
+            }
+          }
+        }
+        auto smallest = [&]() {   // of best, and of equal ones that of the lowest code, in s_d[0] and s_i[0]
+          s_d[tid] = best;
+          s_i[tid] = arg;
+          __syncthreads();
+          for (int s = 128; s >= 1; s >>= 1) {
+            if (tid < s) {
+              const double o = s_d[tid + s];
+              const int oi = s_i[tid + s];
+              if (o < s_d[tid] || (o == s_d[tid] && oi < s_i[tid])) {
+                s_d[tid] = o;
+                s_i[tid] = oi;
+              }
+            }
+            __syncthreads();
+          }
+        };
+        if (tid == 0) s_n_open = 0;
+        smallest();
+        const int cb = s_i[0];
+        // What two sums of two chains of 64 products each, with half of as many for 1/2 c . w, can be off by, and some more
+        const CodewordStat& st = cstat[kv];
+        const double reach = 0x1p-45 * (sqrt(s_n[0] + s_n[1]) + (double)__uint_as_float(st.c_max)) * (double)__uint_as_float(st.w_max);
+        const double most = s_d[0] + reach;
+        if (tid < kD) {
+          s_e[t] = s_x[t] - (double)codebook[cb * kD + t];
+          s_w[t] = wT[(size_t)t * kCW + cb];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kPer; ++q)
+          if (value[q] <= most && tid + 256 * q != cb) s_open[atomicAdd(&s_n_open, 1u)] = (uint16_t)(tid + 256 * q);
+        __syncthreads();
+        best = 0.0;
+        arg = cb;
+        for (uint32_t i = tid; i < s_n_open; i += 256) {
+          const int c = s_open[i];
+          const float4* row_c = (const float4*)(codebook + c * kD);
+          constexpr int kStep = 32;   // dimensions requested together
+          double d = 0.0;
+#pragma unroll 1
+          for (int r0 = 0; r0 < kD; r0 += kStep) {
+            double w[kStep];
+            float4 x4[kStep / 4];
+#pragma unroll
+            for (int r = 0; r < kStep / 4; ++r) x4[r] = row_c[r0 / 4 + r];
+#pragma unroll
+            for (int r = 0; r < kStep; ++r) w[r] = wT[(uint32_t)(r0 + r) * kCW + c];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < kStep; ++r) {
+              const float cr = r % 4 == 0 ? x4[r / 4].x : (r % 4 == 1 ? x4[r / 4].y : (r % 4 == 2 ? x4[r / 4].z : x4[r / 4].w));
+              d += (s_w[r0 + r] - w[r]) * (s_e[r0 + r] + (s_x[r0 + r] - (double)cr));
+            }
+          }
+          if (d < best || (d == best && c < arg)) {
+            best = d;
+            arg = c;
+          }
+        }
+        smallest();
+        if (tid == 0) *out_of(row) = (uint16_t)s_i[0];
       }
-      __syncthreads();
-    }
-    if (tid == 0) *out = (uint16_t)s_i[0];
+    __syncthreads();   // s_full is written again
   }
 }
 
 // No counts yet, and no KV head takes the i8 filter.
-__global__ void encode_single_clear_kernel(uint32_t* counter, int n, uint32_t* eight, int Hkv) {
+__global__ void encode_single_clear_kernel(uint32_t* counter, int n, uint32_t* found, uint32_t* eight, int Hkv) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) counter[i] = 0;
+  for (int i = threadIdx.x; i < Hkv; i += blockDim.x) found[i * kFoundStride] = 0;
   for (int i = threadIdx.x; i < Hkv; i += blockDim.x) eight[i] = 0;
 }
 
@@ -1869,7 +1990,8 @@ hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_ne
     return err;
 
   const uint32_t n_all = (uint32_t)((size_t)bkv * n_new);
-  const int n_counter = (int)(1 + Hkv + Hkv * near_groups(d));
+  uint32_t* found = (uint32_t*)(base + w.off_L);
+  const int n_counter = (int)(Hkv + Hkv * near_groups(d));
   // Keys per wave: a workgroup reads all codewords whatever its keys, so 128 where that gives about the 512
   // workgroups that are resident at once, else 64 or 32 (8 KV heads, 32 / 64 / 128 a wave, us: 2000 keys 47 / 59 / 87, 12000
   // 83 / 85 / 89, 20000 122 / 119 / 134, 26000 156 / 152 / 140, 96001 479 / 415 / 395).
@@ -1888,22 +2010,22 @@ hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_ne
     sample = (int2*)(base + w.off_near_part);   // (used by the lists' kernels later, as the list is: 48 groups take 1.5 MB of its 2)
     norms = (float2*)list;
     hipLaunchKernelGGL(encode_single_sample_kernel<true>, dim3(kSampleSlices, Hkv, (unsigned)groups), block, 0, stream, keys, center,
-                       i8, bias8, sample, norms, counter, n_counter, n_new, n_rows);
+                       i8, bias8, sample, norms, counter, n_counter, found, n_new, n_rows);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     hipLaunchKernelGGL(encode_single_decide_kernel, dim3((unsigned)groups, Hkv), block, 0, stream, cstat, sample, norms,
-                       (uint16_t*)codes, counter + 1, near, (int64_t)w.near_cap, n_new, n_rows, pos0, d.ctx_stride);
+                       (uint16_t*)codes, counter, near, (int64_t)w.near_cap, n_new, n_rows, pos0, d.ctx_stride);
     if ((err = hipGetLastError()) != hipSuccess) return err;
   } else {
     if (route == kFilter16)
-      hipLaunchKernelGGL(encode_single_clear_kernel, dim3(1), dim3(1024), 0, stream, counter, n_counter, eight, Hkv);
+      hipLaunchKernelGGL(encode_single_clear_kernel, dim3(1), dim3(1024), 0, stream, counter, n_counter, found, eight, Hkv);
     else
       hipLaunchKernelGGL(encode_single_sample_kernel<false>, dim3(kSampleSlices, Hkv), block, 0, stream, keys, center, i8, bias8,
-                         sample, norms, counter, n_counter, n_new, n_rows);
+                         sample, norms, counter, n_counter, found, n_new, n_rows);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     const dim3 grid((n_new + 32 * nt * kEncWaves - 1) / (32 * nt * kEncWaves), bkv);
 #define A2ATS_LAUNCH_FILTER(NT, I8, F16)                                                                                      \
   hipLaunchKernelGGL((encode_single_filter_kernel<NT, I8, F16>), grid, block, 0, stream, keys, center, f16, fbias, i8, bias8, sample, \
-                     norms, eight, cstat, (uint16_t*)codes, counter + 1, near, (int64_t)w.near_cap, Hkv, n_new, pos0, d.ctx_stride)
+                     norms, eight, cstat, (uint16_t*)codes, counter, near, (int64_t)w.near_cap, Hkv, n_new, pos0, d.ctx_stride)
     // One launch has both filters, except with 64 keys a wave: there the i8 one has three waves per SIMD, the f16 one the
     // registers of two.
     if (route == kFilter16) {
@@ -1923,13 +2045,13 @@ hipError_t launch_encode_single(const a2ats_dims& d, const float* keys, int n_ne
     if ((err = hipGetLastError()) != hipSuccess) return err;
   }
   hipLaunchKernelGGL(encode_single_kernel, dim3((unsigned)near_groups(d), Hkv), block, 0, stream, keys, center, cfrag, cbias,
-                     cstat, (uint16_t*)codes, counter + 1, near, (int64_t)w.near_cap, counter, list, counter + 1 + Hkv,
+                     cstat, (uint16_t*)codes, counter, near, (int64_t)w.near_cap, found, list, counter + Hkv,
                      (NearPart*)(base + w.off_near_part), Hkv, n_new, pos0, d.ctx_stride);
   if ((err = hipGetLastError()) != hipSuccess) return err;
-  const uint32_t re_grid = n_all < 2048u ? n_all : 2048u;
-  hipLaunchKernelGGL(encode_single_recheck_kernel, dim3(re_grid), dim3(256), 0, stream, keys,
-                     (const float*)(base + w.off_copy), center, mode, (const double*)(base + w.off_hmat), (const double*)(base + w.off_sd), (const double*)(base + w.off_wT),
-                     (const double*)(base + w.off_chalf), (uint16_t*)codes, counter, (const uint32_t*)list, Hkv, n_new, pos0, d.ctx_stride);
+  const unsigned re_parts = (unsigned)std::min<long>(n_rows, std::max(1, 2048 / Hkv));
+  hipLaunchKernelGGL(encode_single_recheck_kernel, dim3(Hkv, re_parts), dim3(256), 0, stream, keys,
+                     (const float*)(base + w.off_copy), center, cstat, (const double*)(base + w.off_wT),
+                     (const double*)(base + w.off_chalf), (uint16_t*)codes, found, list, (int64_t)w.near_cap, n_new, pos0, d.ctx_stride);
   return hipGetLastError();
 }
 

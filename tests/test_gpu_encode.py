@@ -334,6 +334,48 @@ def test_single_codebook_weights_without_full_rank(rank, n):
         assert (lost <= 1e-13 * (half.max() + k.norm(dim=1) * w.norm(dim=1).max())).all(), float(lost.max())
 
 
+@pytest.mark.parametrize("mode", ["none", "diag", "block"])
+@pytest.mark.parametrize("n", [12, 3001])
+@pytest.mark.parametrize("close", [2, 3, 40])
+def test_single_codebook_keys_far_out_among_codewords_close_to_them(close, n, mode):
+    """Several codewords around a long key, at distances that differ by far less than float64 rounds |k| |w|: long in the first 64
+    dimensions, where they are all alike, and told apart in the others.  Every code is the argmin of the distances themselves."""
+    kv, spots = 2, 9
+    g = torch.Generator(device="cuda").manual_seed(close * 100000 + n)
+    randn = lambda *shape: torch.randn(*shape, generator=g, device="cuda", dtype=torch.float64)
+    codebook = (randn(kv, 1, 4096, 128) * torch.where(torch.arange(128, device="cuda") < 64, 100.0, 1e-3)).float()
+    keys = torch.empty(1, kv, n, 128, device="cuda")
+    for h in range(kv):
+        at = torch.randperm(4096, generator=g, device="cuda")[:spots * close].view(spots, close)
+        codebook[h, 0, at.view(-1), :64] = codebook[h, 0, at[:, :1].expand(-1, close).reshape(-1), :64]
+        # distances of 1e-6 to 2e-6
+        near = codebook[h, 0, at[:, 0], 64:].double()[torch.arange(n, device="cuda") % spots]
+        keys[0, h, :, :64] = codebook[h, 0, at[:, 0], :64][torch.arange(n, device="cuda") % spots]
+        keys[0, h, :, 64:] = (near + 1e-9 * randn(n, 64)).float()
+        step = randn(spots, close, 64)
+        step *= 1e-6 * (1.0 + torch.rand(spots, close, 1, generator=g, device="cuda", dtype=torch.float64)) / step.norm(dim=-1, keepdim=True)
+        codebook[h, 0, at, 64:] = (codebook[h, 0, at[:, :1], 64:].double() + step).float()
+    half = randn(kv, 128, 128)
+    h64 = {"none": torch.eye(128, device="cuda", dtype=torch.float64).expand(kv, 128, 128),
+           "diag": torch.diag_embed(half[:, 0].abs() + 0.1),
+           "block": half @ half.transpose(1, 2).contiguous() / 128.0 + torch.eye(128, device="cuda", dtype=torch.float64)}[mode]
+    h32 = h64.float()
+    weights = {"none": None, "diag": torch.diagonal(h32, dim1=1, dim2=2).contiguous(), "block": h32.contiguous()}[mode]
+    dims = B.make_dims(1, kv, kv, 128, 1, n + 8, n_centroids=4096)
+    got = _single(dims, keys, codebook, weights, {"none": B.W_NONE, "diag": B.W_DIAG, "block": B.W_BLOCK}[mode], n + 8)
+    for h in range(kv):
+        low = torch.tril(h32[h]).double()
+        sym = low + torch.tril(low, -1).t().contiguous()
+        for j0 in range(0, n, 64):
+            e = keys[0, h, j0:j0 + 64, None].double() - codebook[h, 0].double()
+            dist = ((e @ sym) * e).sum(-1)
+            lost = dist.gather(1, got[0, h, j0:j0 + 64, None])[:, 0] - dist.min(1).values
+            # (w is rounded in 64 bits, 128 products of |H| |c| each, and meets sums of two distances; what the
+            # distances differ by is of the order of their squares, 1e-12)
+            bound = 128 * 2.0 ** -53 * float(sym.norm()) * 2000.0 * 4e-6
+            assert bound < 1e-14 and (lost <= bound).all(), (float(lost.max()), bound)
+
+
 @pytest.mark.parametrize("kv,n", [(8, 12001), (8, 20100), (2, 33000)])
 def test_single_codebook_long_lists_of_undecided_keys(kv, n):
     """Every codeword twice, so the filter decides no key: lists of 24 to 129 chunks of 256 keys per KV head, by 64 (of 8

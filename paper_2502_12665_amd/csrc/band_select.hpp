@@ -1,5 +1,4 @@
-// The end of a selection by coarse scores, for the (up to) four heads of a group by one workgroup of 1024 threads, four
-// waves a head: the band (rows whose coarse score does not tell whether they are winners) is scored exactly and ranked, and
+// The end of a selection by coarse scores, for the (up to) four heads of a group by one workgroup of 1024 threads: the band (rows whose coarse score does not tell whether they are winners) is scored exactly and ranked, and
 // winners are written from a bitmap over the positions.
 #pragma once
 #include "common.hpp"
@@ -22,6 +21,20 @@ struct Band {
   uint32_t (*hist)[kHistBins];   // two of them
   uint32_t* wave_tot;      // [waves]
 };
+
+// The sixteen waves divided among the heads in `heads` (a bit each, at least one of them): the head of this wave, how many
+// threads it has, and which of them this one is.  (With four waves a head whatever the heads, one selection per KV head by the list route:
+// 160 of 32768 candidates M = 16 46.4 -> 44.5 us, of 65000 68.5 -> 63.5, of 32768 M = 32 73.9 -> 70.2.)
+struct HeadShare {
+  int head, threads, at;
+};
+__device__ __forceinline__ HeadShare head_share(uint32_t heads) {
+  constexpr int kWaves = kExactThreads / 64;
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), n = __popc(heads), k = wv * n / kWaves;
+  const int w0 = (kWaves * k + n - 1) / n, w1 = (kWaves * (k + 1) + n - 1) / n;
+  for (int i = 0; i < k; ++i) heads &= heads - 1;
+  return {__ffs((int)heads) - 1, 64 * (w1 - w0), (int)threadIdx.x - 64 * w0};
+}
 
 // Exact score of a row from a head's table in global memory.
 template <int M>
@@ -52,7 +65,6 @@ __device__ __forceinline__ uint32_t band_winners(const Band& B, uint32_t mine, i
                                                  int kk, const int32_t* __restrict__ lut, const LutLayout& lay) {
   constexpr int NT = kExactThreads, HP = 64 / M;   // heads whose tables fit
   const int tid = threadIdx.x;
-  const int mr = __builtin_amdgcn_readfirstlane(tid >> 8), mt = tid & 255, lane = tid & 63;
   uint32_t first[kHeadsPerGroup + 1], left = 0;
   first[0] = 0;
 #pragma unroll
@@ -64,8 +76,11 @@ __device__ __forceinline__ uint32_t band_winners(const Band& B, uint32_t mine, i
   if (first[4] == 0u) return left;
   const bool few = !MANY || first[4] * M <= 8192u;
   auto head_of = [&](uint32_t e) { return (e >= first[1] ? 1 : 0) + (e >= first[2] ? 1 : 0) + (e >= first[3] ? 1 : 0); };
-  auto place_of = [&](uint32_t e, int r) {
-    return B.row + r * kBandCap + (e - (r == 0 ? 0u : (r == 1 ? first[1] : (r == 2 ? first[2] : first[3]))));
+  auto first_of = [&](int r) { return r == 0 ? 0u : (r == 1 ? first[1] : (r == 2 ? first[2] : first[3])); };
+  auto place_of = [&](uint32_t e, int r) { return B.row + r * kBandCap + (e - first_of(r)); };
+  auto win = [&](int r, uint64_t row) {
+    const uint32_t bit = ~(uint32_t)row - (uint32_t)lo;
+    atomicOr((uint32_t*)(B.won + (size_t)r * B.won_words) + (bit >> 5), 1u << (bit & 31));
   };
   if (few) {
     for (uint32_t e = tid; e < first[4]; e += NT) {
@@ -120,69 +135,81 @@ __device__ __forceinline__ uint32_t band_winners(const Band& B, uint32_t mine, i
     }
     __syncthreads();
   }
-  const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)B.n[mr]);
-  const bool ranks = ((mine & ~left) >> mr) & 1u && n > 0u;   // (uniform over a wave)
-  uint64_t* row = B.row + mr * kBandCap;
-  uint32_t key0 = 0;
-  int shift = 0;
-  if (ranks) {
+  // (eight lanes share a row: the lists are short and every step is an LDS round trip)
+  if (few) {
+    for (uint32_t e = tid >> 3; e < first[4]; e += NT / 8) {
+      const int r = head_of(e);
+      const uint32_t f = first_of(r), n = (r == 0 ? first[1] : (r == 1 ? first[2] : (r == 2 ? first[3] : first[4]))) - f;
+      const uint64_t* row = B.row + r * kBandCap;
+      const uint64_t own = row[e - f];
+      int32_t before = 0;
+#pragma unroll 4
+      for (uint32_t u = tid & 7; u < n; u += 8) before += row[u] > own ? 1 : 0;
+      before = group8_sum(before);
+      if ((tid & 7) == 0 && (uint32_t)before < (uint32_t)kk - B.n_sure[r]) win(r, own);
+    }
+  } else {
+    uint32_t there = 0;
+#pragma unroll
+    for (int r = 0; r < kHeadsPerGroup; ++r) there |= first[r] != first[r + 1] ? 1u << r : 0u;
+    const HeadShare own_head = head_share(there);
+    const int mr = own_head.head;
+    const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)B.n[mr]);
+    const uint64_t* row = B.row + mr * kBandCap;
     const int32_t* meta = lut + lay.off_meta + (size_t)(head0 + mr) * 4;
-    key0 = score_key((int32_t)((uint32_t)meta[0] + (B.from[mr] << meta[1])));
+    const uint32_t key0 = score_key((int32_t)((uint32_t)meta[0] + (B.from[mr] << meta[1])));
     const uint32_t range = (B.width + M) << meta[1];   // (a coarse score leaves out less than M units)
-    shift = max(0, 21 - (int)__clz(range));
-  }
-  // (the keys of a finite table lie in the range; others in the bins at its ends, which keeps the order)
-  auto bin_of = [&](uint32_t key) { return min(key > key0 ? (key - key0) >> shift : 0u, (uint32_t)kHistBins - 1); };
-  if (!few) {
+    const int shift = max(0, 21 - (int)__clz(range));
+    // (the keys of a finite table lie in the range; others in the bins at its ends, which keeps the order)
+    auto bin_of = [&](uint32_t key) { return min(key > key0 ? (key - key0) >> shift : 0u, (uint32_t)kHistBins - 1); };
     for (int i = tid; i < kHistBins / 2; i += NT) ((uint4*)B.hist)[i] = make_uint4(0, 0, 0, 0);
     __syncthreads();
-    if (ranks)
-      for (uint32_t i = mt; i < n; i += 256) atomicAdd(&B.hist[mr >> 1][bin_of((uint32_t)(row[i] >> 32))], 1u << (16 * (mr & 1)));
+    for (uint32_t i = own_head.at; i < n; i += own_head.threads)
+      atomicAdd(&B.hist[mr >> 1][bin_of((uint32_t)(row[i] >> 32))], 1u << (16 * (mr & 1)));
     __syncthreads();
-  }
-  if (ranks) {
     const uint32_t need = (uint32_t)kk - B.n_sure[mr];
-    const int bin = few ? 0 : wave_find_bin(B.hist[mr >> 1], 16 * (mr & 1), need, lane);
-    for (uint32_t i = mt >> 3; i < n; i += 32) {   // eight lanes a row
+    const int bin = wave_find_bin(B.hist[mr >> 1], 16 * (mr & 1), need, tid & 63);
+    for (uint32_t i = own_head.at >> 3; i < n; i += own_head.threads >> 3) {
       const uint64_t own = row[i];
-      const int b = few ? 0 : (int)bin_of((uint32_t)(own >> 32));
+      const int b = (int)bin_of((uint32_t)(own >> 32));
       if (b < bin) continue;
       int32_t before = 0;
       if (b == bin) {
 #pragma unroll 4
-        for (uint32_t u = mt & 7; u < n; u += 8) before += row[u] > own ? 1 : 0;
+        for (uint32_t u = tid & 7; u < n; u += 8) before += row[u] > own ? 1 : 0;
         before = group8_sum(before);
       }
-      if ((mt & 7) == 0 && (uint32_t)before < need) {
-        const uint32_t bit = ~(uint32_t)own - (uint32_t)lo;
-        atomicOr((uint32_t*)(B.won + (size_t)mr * B.won_words) + (bit >> 5), 1u << (bit & 31));
-      }
+      if ((tid & 7) == 0 && (uint32_t)before < need) win(mr, own);
     }
   }
   __syncthreads();
   return left;
 }
 
-// Writes the winners of the heads in `mine` in ascending position, PER words of the bitmap a thread; ncand: its bits.
+// Writes the winners of the heads in `mine` in ascending position; ncand: the bits of the bitmap, at most 16384 PER.
 template <int PER>
 __device__ __forceinline__ void write_winners(const Band& B, uint32_t mine, int head0, int lo, int ncand, int kk, int top_k,
                                               int32_t* __restrict__ topk_idx) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), mr = wv >> 2;
-  const int w0 = (tid & 255) * PER, n_words = (mine >> mr) & 1u ? (ncand + 63) / 64 : 0;
-  const uint64_t* won = B.won + (size_t)mr * B.won_words;
+  if (mine == 0u) return;   // (uniform)
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // (one word a thread of the four waves of a head's number is as fast as more waves could be)
+  const HeadShare own = PER > 1 ? head_share(mine) : HeadShare{wv >> 2, 256, tid & 255};
+  const int n_words = (mine >> own.head) & 1u ? (ncand + 63) / 64 : 0, per = PER > 1 ? (n_words + own.threads - 1) / own.threads : 1;
+  const int w0 = own.at * per;
+  const uint64_t* won = B.won + (size_t)own.head * B.won_words;
   uint64_t word[PER];
   uint32_t n = 0;
 #pragma unroll
   for (int w = 0; w < PER; ++w) {
-    word[w] = w0 + w < n_words ? won[w0 + w] : 0ull;
+    word[w] = w < per && w0 + w < n_words ? won[w0 + w] : 0ull;
     n += (uint32_t)__popcll(word[w]);
   }
   const uint32_t inc = wave_inclusive_scan(n);
   if (lane == 63) B.wave_tot[wv] = inc;
   __syncthreads();
   uint32_t at = inc - n;
-  for (int w = wv & ~3; w < wv; ++w) at += B.wave_tot[w];
-  int32_t* oi = topk_idx + (size_t)(head0 + mr) * top_k;
+  for (int w = wv - (own.at >> 6); w < wv; ++w) at += B.wave_tot[w];
+  int32_t* oi = topk_idx + (size_t)(head0 + own.head) * top_k;
 #pragma unroll
   for (int w = 0; w < PER; ++w)
     while (word[w]) {

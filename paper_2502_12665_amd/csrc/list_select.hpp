@@ -189,13 +189,14 @@ __device__ __forceinline__ void list_select_body(
   }
   __syncthreads();
 
-  // --- the bin of the K-th coarse score: four waves per head
+  // --- the bin of the K-th coarse score
   for (int i = tid; i < (int)(sizeof(ListEnd) / 16); i += NT) ((uint4*)&E)[i] = make_uint4(0, 0, 0, 0);
   __syncthreads();
-  const int mr = wv >> 2, mt = tid & 255;   // the head that this thread's wave looks at, and its place there
+  const HeadShare own = head_share(real);
+  const int mr = own.head, mt = own.at;
   const uint32_t n_list = (uint32_t)__builtin_amdgcn_readfirstlane((int)min(L.n[mr], (uint32_t)kListCap));
-  const uint32_t t_mr = mr < n_real ? (uint32_t)__builtin_amdgcn_readfirstlane(L.thr[mr]) : 0u;
-  for (uint32_t i = mt; i < n_list; i += 256)   // (the last bin holds all that is further up)
+  const uint32_t t_mr = (uint32_t)__builtin_amdgcn_readfirstlane(L.thr[mr]);
+  for (uint32_t i = mt; i < n_list; i += own.threads)   // (the last bin holds all that is further up)
     atomicAdd(&E.hist[mr >> 1][min(((L.entry[mr][i] >> 16) - t_mr) >> kListBin, (uint32_t)kHistBins - 1)], 1u << (16 * (mr & 1)));
   __syncthreads();
   if (wv < kHeadsPerGroup) {
@@ -214,13 +215,13 @@ __device__ __forceinline__ void list_select_body(
     if (stats && tid == r && r < n_real) stats[head0 + r] = n | why << 28;
   }
   // --- winners and band rows (hist is the band's place from here on)
-  if (mr < n_real && !((redo >> mr) & 1u)) {
+  if (!((redo >> mr) & 1u)) {
     const int bin = __builtin_amdgcn_readfirstlane(L.bin[mr]);
     const int edge = (int)t_mr + (bin << kListBin);
     const uint32_t t_lo = (uint32_t)max(0, edge - M + 1), t_hi = (uint32_t)min(0xffff, edge + (1 << kListBin) + M);
     if (mt == 0) L.from[mr] = t_lo;
     uint32_t sure = 0;
-    for (uint32_t i = mt; i < n_list; i += 256) {
+    for (uint32_t i = mt; i < n_list; i += own.threads) {
       const uint32_t e = L.entry[mr][i], s = e >> 16, j = e & 0xffffu;
       if (s >= t_hi) {
         atomicOr((uint32_t*)&E.won[mr][0] + (j >> 5), 1u << (j & 31));

@@ -466,8 +466,8 @@ int a2ats_codebook_update(const a2ats_dims* dims, const float* keys, int32_t n_n
  * After an a2ats_score_topk call with the same dims / top_k / window / n_sink and the same `ws`,
  * write per head into cand_counts [dev, out, uint32 B*Hq] (asynchronously, on `stream`): bits 0-27
  * the number of rows the streaming pass kept for that head, bits 28-31 the route the final kernel
- * took (0 = fast; 1 = too few survivors, 2 = too many, 3 = a segment overflowed, 4 = completeness
- * proof failed: 1-4 end in the exact fallback).  For shapes served by the exact route alone, and for
+ * took (0 = fast; 1 = too few survivors, 2 = too many, or too many of about the K-th score, 3 = a chunk's
+ * list overflowed, 4 = completeness proof failed: 1-4 end in the exact fallback).  For shapes served by the exact route alone, and for
  * top_k > 2048, every entry is 0xFFFFFFFF.
  */
 int a2ats_score_topk_stats(const a2ats_dims* dims, int32_t top_k, int32_t window, int32_t n_sink,
@@ -481,8 +481,9 @@ int a2ats_score_topk_stats(const a2ats_dims* dims, int32_t top_k, int32_t window
  * [1] groups of four query heads per KV head, [2] sampling workgroups per (sequence, KV head, group),
  * [3] rows each of them scores, [4] streaming workgroups (chunks) per problem, [5] rows per chunk,
  * [6] runs of rows per wave of a chunk (always 1), [7] rows per run, [8] survivors of a head that a chunk can hold, divided by
- * its 8 waves, [9] twice the most winners (the final kernel's limit once), [10] workspace bytes the call needs, divided by 256.
- * (Of many head groups of up to 65536 candidates one workgroup each does all of this; [2] to [9] are then not used.)
+ * its 8 waves, [9] rows of about the K-th score that the final kernel ranks (8192; 4000 for the longest contexts), [10] workspace bytes the call needs, divided by 256.
+ * (Of many head groups of up to 65536 candidates one workgroup each does all of this; [2] to [8] are then not used, and [9] is
+ * what its list of a head holds, 5632 rows.)
  */
 int a2ats_score_topk_plan(const a2ats_dims* dims, int32_t top_k, int32_t window, int32_t n_sink, int32_t* plan);
 

@@ -52,17 +52,44 @@ __device__ __forceinline__ int32_t exact_score_of(const int32_t* __restrict__ t,
   return s;
 }
 
+// Of the distinct values, `bits` wide, that the threads of a workgroup of NT hold: one that exactly `need` of them reach.  each(f)
+// calls f(in, value) for a thread's own (where `in`), the same every time; there are at least `need`.  In LDS: hist, kHistBins words;
+// wave_tot, one a wave; res, two.  By radix: a level takes 11 bits.
+template <int NT, typename Each>
+__device__ __forceinline__ uint64_t reached_by(uint32_t need, int bits, Each each, uint32_t* hist, uint32_t* wave_tot, uint32_t* res) {
+  uint64_t prefix = 0;
+#pragma unroll 1
+  for (int above = bits; above > 0;) {   // (uniform)
+    const int width = min(above, 11), shift = above - width;
+    __syncthreads();
+    for (int i = threadIdx.x; i < kHistBins; i += NT) hist[i] = 0;
+    __syncthreads();
+    each([&](bool in, uint64_t value) {
+      count_shared_bins(hist, (uint32_t)(value >> shift) & ((1u << width) - 1u), in && value >> above == prefix >> above);
+    });
+    __syncthreads();
+    block_find_rank_desc<NT, kHistBins>([&](int i) { return hist[i]; }, need, wave_tot, res);
+    const uint32_t bin = res[0];
+    need -= res[1];
+    prefix |= (uint64_t)bin << shift;
+    above = hist[bin] == need ? 0 : shift;
+  }
+  return prefix;
+}
+
 // Marks the K - n_sure best rows of the band in `won`, of the heads in `mine` whose band is complete.  The caller has
-// synchronised.  Returns the heads of `mine` whose band is not complete (uniform).
+// synchronised.  Returns the heads of `mine` whose band is not complete (uniform), for which, if there are any, crowded(heads) is
+// called before anything of B but the bitmaps is written.
 //
 // Few rows (512 of M = 16, 256 of M = 32) read their entries from the exact tables in global memory and are ranked by counting.
 // For more the tables come to LDS first, as many as fit 64 KB, which takes 2 us: an entry read from global memory is a cache
 // line of its own (4 x 800 rows of M = 32: 75 us against 13).  Then the K-th is found by a histogram of 2048 bins over the
-// band's range and, in its bin, by counting, 7 us for those rows instead of 41 by counting alone.  MANY false: only the first
+// band's range and, in its bin, by counting, 7 us for those rows instead of 41 by counting alone.  (More than 64 rows in that bin, equal
+// scores: four of them at a time against a row that is read, 16 sequences of 32768 tokens whose rows are of 100 kinds 145 -> 106 us.)  MANY false: only the first
 // form (the other one's code costs calls that do not use it up to 1 us).
-template <int M, bool MANY>
-__device__ __forceinline__ uint32_t band_winners(const Band& B, uint32_t mine, int head0, const SeqCodes& seq_codes, int lo,
-                                                 int kk, const int32_t* __restrict__ lut, const LutLayout& lay) {
+template <int M, bool MANY, typename Crowded>
+__device__ __forceinline__ uint32_t band_winners(const Band& B, uint32_t mine, int head0, const SeqCodes& seq_codes, int lo, int kk,
+                                                 const int32_t* __restrict__ lut, const LutLayout& lay, Crowded crowded) {
   constexpr int NT = kExactThreads, HP = 64 / M;   // heads whose tables fit
   const int tid = threadIdx.x;
   uint32_t first[kHeadsPerGroup + 1], left = 0;
@@ -73,6 +100,7 @@ __device__ __forceinline__ uint32_t band_winners(const Band& B, uint32_t mine, i
     left |= n > (uint32_t)kBandCap ? 1u << r : 0u;
     first[r + 1] = first[r] + (n > (uint32_t)kBandCap ? 0u : n);
   }
+  if (__builtin_expect(left != 0u, 0)) crowded(left);
   if (first[4] == 0u) return left;
   const bool few = !MANY || first[4] * M <= 8192u;
   auto head_of = [&](uint32_t e) { return (e >= first[1] ? 1 : 0) + (e >= first[2] ? 1 : 0) + (e >= first[3] ? 1 : 0); };
@@ -169,17 +197,44 @@ __device__ __forceinline__ uint32_t band_winners(const Band& B, uint32_t mine, i
     __syncthreads();
     const uint32_t need = (uint32_t)kk - B.n_sure[mr];
     const int bin = wave_find_bin(B.hist[mr >> 1], 16 * (mr & 1), need, tid & 63);
-    for (uint32_t i = own_head.at >> 3; i < n; i += own_head.threads >> 3) {
-      const uint64_t own = row[i];
-      const int b = (int)bin_of((uint32_t)(own >> 32));
-      if (b < bin) continue;
-      int32_t before = 0;
-      if (b == bin) {
+    // (of many rows in that bin, equal scores, four at a time against every row that is read: the reads are what takes the time)
+    const bool crowd = bin >= 0 && (B.hist[mr >> 1][bin] >> (16 * (mr & 1)) & 0xffffu) > 64u;
+    const uint32_t groups = own_head.threads >> 3;
+    if (!crowd) {
+      for (uint32_t i = own_head.at >> 3; i < n; i += groups) {
+        const uint64_t own = row[i];
+        const int b = (int)bin_of((uint32_t)(own >> 32));
+        if (b < bin) continue;
+        int32_t before = 0;
+        if (b == bin) {
 #pragma unroll 4
-        for (uint32_t u = tid & 7; u < n; u += 8) before += row[u] > own ? 1 : 0;
-        before = group8_sum(before);
+          for (uint32_t u = tid & 7; u < n; u += 8) before += row[u] > own ? 1 : 0;
+          before = group8_sum(before);
+        }
+        if ((tid & 7) == 0 && (uint32_t)before < need) win(mr, own);
       }
-      if ((tid & 7) == 0 && (uint32_t)before < need) win(mr, own);
+    } else {
+      constexpr int kRows = 4;
+      for (uint32_t i = own_head.at >> 3; i < n; i += kRows * groups) {
+        uint64_t own[kRows];
+        int32_t before[kRows];
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) {
+          own[k] = row[min(i + k * groups, n - 1)];
+          before[k] = 0;
+        }
+#pragma unroll 2
+        for (uint32_t u = tid & 7; u < n; u += 8) {
+          const uint64_t other = row[u];
+#pragma unroll
+          for (int k = 0; k < kRows; ++k) before[k] += other > own[k] ? 1 : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) {
+          before[k] = group8_sum(before[k]);
+          if ((tid & 7) == 0 && i + k * groups < n && (uint32_t)before[k] < need) win(mr, own[k]);
+        }
+      }
     }
   }
   __syncthreads();

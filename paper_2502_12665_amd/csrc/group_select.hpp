@@ -211,7 +211,7 @@ __device__ __forceinline__ void group_select_body(
   // --- the band, and the winners in ascending position
   const Band band = {&L.band[0][0], &L.won[0][0], kGroupMaxCand / 64, L.n_band, L.n_sure, L.from, 32u + 2 * M,
                      (int32_t*)tbl, L.hist, L.wave_tot};
-  const uint32_t redo = band_winners<M, M == 32>(band, mine, head0, seq_codes, lo, sr.kk, lut, lay);
+  const uint32_t redo = band_winners<M, M == 32>(band, mine, head0, seq_codes, lo, sr.kk, lut, lay, [](uint32_t) {});
   write_winners<kGroupMaxCand / 64 / 256>(band, mine & ~redo, head0, lo, sr.ncand, sr.kk, top_k, topk_idx);
   // --- heads with more band rows than the list holds (many equal scores): the exact route.  The K-th coarse score is in the
   // bin, hence the K-th score is at least the bin's lower edge, and its own row's is below the upper edge.

@@ -25,7 +25,7 @@ struct TopkPlan {
   int rows_per_chunk;
   int subs;             // runs of rows per wave of the streaming pass (always 1)
   int sub_rows;         // rows of a wave (rows_per_chunk / 8)
-  int cap;              // (reported as the survivors that the final kernel can hold, which has no such limit any more)
+  int cap;              // rows of a head that the list route's list holds, or of about the K-th score that the final kernel ranks
   int row_cap;          // entries of a head's list of a chunk, divided by its waves
   bool list;            // one workgroup for a head group instead (list_select.hpp)
   int list_rows;        // rows it samples

@@ -3,11 +3,19 @@
 //
 // A sample gives every head a threshold below its K-th coarse score (coarse_score.hpp); one pass over the rows
 // scores each against the four heads' coarse table, and a row that reaches a head's threshold goes to that head's list in
-// LDS, as its coarse score and position (16 bits each).  A histogram over a list gives the 32-wide bin of the head's K-th
+// LDS, as its coarse score and position (16 bits each).  A histogram over a list gives the 4-wide bin of the head's K-th
 // coarse score, and from there on it is the group route's (group_select.hpp): rows M units above the bin are winners, rows
 // M units below it are not, the few between are scored exactly and ranked, and winners are written from a bitmap over the
 // positions in ascending order.  The lists hold every row that the bin and the band can need, as long as the band begins
-// above the threshold; a head where it does not, or whose list or band overflows, is done by the exact route.
+// above the threshold; a head where it does not, or whose list overflows twice, is done by the exact route.
+//
+// Many equal scores.  A band of more than 1024 rows is ranked from the head's list by a radix select over (score, position); a list
+// that overflows tells a higher threshold and is made again by another pass.  A head that overflows that too is done by the exact
+// route, one after the other in their workgroup.  Tables and selection, us, by the streaming route of before (whose
+// final kernel ranked up to 8192 rows, a workgroup a head) -> with the exact route for all of these -> now, 32 query and 8 KV heads, K 3 %:
+// 16 sequences of 32768, M = 16, 1100 equal scores about the K-th of one head in four 67 -> 287 -> 74, 4000 87 -> 256 -> 95, rows of 100 kinds
+// 82 -> 144 -> 106, of 20 75 -> 491 -> 113; 32 of 60000 147 -> 509 -> 112, 180 -> 666 -> 344 (8 of 1024 heads by the exact route),
+// 194 -> 751 -> 138, 172 -> 872 -> 509 (52 of them); 32 of 32768, M = 32 165 -> 435 -> 126, 206 -> 404 -> 164, 194 -> 451 -> 167, 185 -> 730 -> 186.
 //
 // Against the streaming route this saves the survivors' way through memory (20 or 36 bytes written and read back by every head),
 // the exact scores of 1.4 K rows a head, and the rounds of one workgroup per head: 256 groups of 65536 tokens, M = 32, K 2048
@@ -29,7 +37,8 @@ constexpr int kListThreads = 1024;
 constexpr int kListWaves = kListThreads / 64;
 constexpr int kListMaxCand = 65536;   // positions are 16 bits, from the first candidate
 constexpr int kListCap = 5632;        // list entries per head
-constexpr int kListBin = 2;           // a bin of their histogram is 1 << kListBin coarse units, from the threshold up
+constexpr int kListBin = 2;           // a bin of their histogram is 1 << kListBin coarse units, from the threshold up;
+constexpr int kListWide = 5;          // 1 << kListWide, which is the whole range, where the K-th is above those
 struct ListLds {
   union {
     uint32_t entry[kHeadsPerGroup][kListCap];   // coarse score in the upper half, position in the lower
@@ -45,7 +54,7 @@ struct ListLds {
   int32_t bin[kHeadsPerGroup];
   uint32_t n_band[kHeadsPerGroup];
   uint32_t n_sure[kHeadsPerGroup];
-  uint32_t from[kHeadsPerGroup];   // where the band begins
+  uint32_t from[kHeadsPerGroup], to[kHeadsPerGroup];   // where the band begins, and the first score above it
   uint32_t wave_tot[kListWaves];
 };
 // In the coarse table's place after the pass.
@@ -59,8 +68,102 @@ struct ListEnd {
 constexpr size_t kListLdsBytes = kCoarseLdsBytes + (sizeof(ListLds) + 15) / 16 * 16;
 static_assert(sizeof(ListEnd) <= kCoarseLdsBytes && kExactLdsBytes <= kCoarseLdsBytes && kListCap < 65536, "");
 
+// Head r's list overflowed: a higher threshold from the entries that are there, which are the first rows of every wave's run.  Those
+// of a step of up to 256 rows that no longer fit are missing, so the last 256 are not looked at.
+__device__ __forceinline__ void raise_threshold(int r, uint32_t kk, ListLds& L, int lane, int wv) {
+  constexpr int NT = kListThreads, kUsed = kListCap - 256, PER = (kUsed + NT - 1) / NT;
+  const int tid = threadIdx.x;
+  uint32_t e[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) e[k] = L.entry[r][min(tid + k * NT, kUsed - 1)];
+  const uint32_t from = (uint32_t)L.thr[r];
+  __syncthreads();
+  uint32_t* hist = L.entry[r];
+  for (int i = tid; i < kHistBins; i += NT) hist[i] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < PER; ++k) count_shared_bins(hist, min(((e[k] >> 16) - from) >> 5, (uint32_t)kHistBins - 1), tid + k * NT < kUsed);
+  __syncthreads();
+  if (wv == 0) {
+    const float r0 = (float)kk * (float)kUsed / (float)L.n[r];   // (as sample_threshold_body)
+    const float x = 0.5f * (kSigma + sqrtf(kSigma * kSigma + 4.f * r0));
+    const int bin = wave_find_bin(hist, 0, (uint32_t)ceilf(x * x) + 1, lane, ~0u);
+    if (lane == 0) {
+      if (bin >= 0) L.thr[r] += max(0, (bin << 5) - 32);
+      L.n[r] = 0;
+    }
+  }
+  __syncthreads();
+}
+
+// Marks the winners of head r among the rows of its list in a band that does not hold them all, by a radix select over (score,
+// position).  The head's list is in registers then, and the table of 16 subspaces at a time in its place; the head's part
+// of the band holds the counts.
+template <int M>
+__device__ __forceinline__ void crowded_band(int r, ListLds& L, ListEnd& E, const SeqCodes& seq_codes, int lo, int kk,
+                                             const int32_t* __restrict__ head_table, const int32_t* __restrict__ meta) {
+  constexpr int NT = kListThreads, PER = (kListCap + NT - 1) / NT, kPosBits = 16;
+  static_assert(kCentroids * 16 + 2 <= kListCap && kListMaxCand <= 1 << kPosBits && sizeof(E.band[0]) >= kHistBins * 4, "");
+  const int tid = threadIdx.x;
+  const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.n[r]);
+  const uint32_t from = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.from[r]);
+  const uint32_t to = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.to[r]);
+  uint32_t e[PER];
+  int32_t s[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    if (k * NT >= (int)n) continue;   // (uniform, as below)
+    const uint32_t i = tid + k * NT;
+    e[k] = i < n ? L.entry[r][i] : 0xffffffffu;   // (no coarse score is as high)
+    if (e[k] >> 16 < from || e[k] >> 16 >= to) e[k] = 0xffffffffu;
+    s[k] = 0;
+  }
+  int32_t* table = (int32_t*)L.entry[r];
+#pragma unroll 1
+  for (int qd = 0; qd < M / 16; ++qd) {
+    uint4 w[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (k * NT < (int)n) w[k] = *(const uint4*)(row_ptr<M>(seq_codes, lo + (e[k] == 0xffffffffu ? 0 : (int)(e[k] & 0xffffu))) + qd * 16);
+    __syncthreads();
+    for (int i = tid; i < kCentroids * 4; i += NT) {
+      const int c = i / 4;   // (four entries are turned by their centroid, see band_select.hpp)
+      ((uint4*)table)[c * 4 + ((i + c) & 3)] = ((const uint4*)head_table)[c * (M / 4) + qd * 4 + (i & 3)];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      if (k * NT >= (int)n) continue;
+      const uint32_t d[4] = {w[k].x, w[k].y, w[k].z, w[k].w};
+#pragma unroll
+      for (int t = 0; t < 16; ++t) {
+        const uint32_t c = (d[t >> 2] >> (8 * (t & 3))) & 0xffu;
+        s[k] += table[c * 16 + ((((t >> 2) + c) & 3) << 2) + (t & 3)];
+      }
+    }
+  }
+  const uint32_t key0 = score_key((int32_t)((uint32_t)meta[0] + (from << meta[1])));
+  const uint32_t range = (to - from + M) << meta[1];   // (a coarse score leaves out less than M units)
+  auto row_of = [&](int k) {
+    const uint32_t key = score_key(s[k]);
+    return (uint64_t)(key > key0 ? min(key - key0, range) : 0u) << kPosBits | (0xffffu - (e[k] & 0xffffu));
+  };
+  const uint64_t last = reached_by<NT>(
+      (uint32_t)kk - L.n_sure[r], kPosBits + 32 - (int)__clz(range),
+      [&](auto f) {
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+          if (k * NT < (int)n) f(e[k] != 0xffffffffu, row_of(k));
+      },
+      (uint32_t*)E.band[r], L.wave_tot, (uint32_t*)table + kCentroids * 16);
+#pragma unroll
+  for (int k = 0; k < PER; ++k)
+    if (k * NT < (int)n && e[k] != 0xffffffffu && row_of(k) >= last)
+      atomicOr((uint32_t*)&E.won[r][0] + ((e[k] & 0xffffu) >> 5), 1u << (e[k] & 31));
+}
+
 // Called by all kListThreads threads of a workgroup.  dyn_lds: kListLdsBytes; TABLE_IN_LDS: the caller has put the group's
-// coarse table at its start (and synchronised), otherwise it is copied from `lut`.  stats (may be null): per head, the
+// coarse table at its start (a barrier follows here), otherwise it is copied from `lut`.  stats (may be null): per head, the
 // length of its list, and the route in the upper four bits (as a2ats_score_topk_stats reports them).
 template <int M, bool TABLE_IN_LDS>
 __device__ __forceinline__ void list_select_body(
@@ -109,8 +212,8 @@ __device__ __forceinline__ void list_select_body(
   for (int r = 0; r < kHeadsPerGroup; ++r)   // (no coarse score is above 65520: a head that there is not takes no row)
     T[r] = r < n_real ? (uint32_t)__builtin_amdgcn_readfirstlane(L.thr[r]) : 0xffffu;
 
-  // --- one pass over the rows, a run of them for each wave
-  {
+  // --- one pass over the rows, a run of them for each wave; and another one for lists that overflow
+  auto pass = [&]() {
     const int run = (sr.ncand + 64 * kListWaves - 1) / (64 * kListWaves) * 64;
     const int wbegin = lo + wv * run, wend = min(hi, wbegin + run);
     LaneSwizzle<M> sw;
@@ -186,40 +289,74 @@ __device__ __forceinline__ void list_select_body(
         process(base + STEP, rows_b);
       }
     }
+    __syncthreads();
+  };
+  pass();
+  uint32_t over = 0;
+#pragma unroll
+  for (int r = 0; r < kHeadsPerGroup; ++r)
+    over |= (uint32_t)__builtin_amdgcn_readfirstlane((int)L.n[r]) > (uint32_t)kListCap ? 1u << r : 0u;
+  if (__builtin_expect(over != 0u, 0)) {   // (uniform)
+#pragma unroll 1
+    for (int r = 0; r < kHeadsPerGroup; ++r)
+      if ((over >> r) & 1u) raise_threshold(r, (uint32_t)sr.kk, L, lane, wv);
+#pragma unroll
+    for (int r = 0; r < kHeadsPerGroup; ++r)
+      T[r] = (over >> r) & 1u ? (uint32_t)__builtin_amdgcn_readfirstlane(L.thr[r]) : 0xffffu;
+    pass();
+#pragma unroll
+    for (int r = 0; r < kHeadsPerGroup; ++r) T[r] = (uint32_t)__builtin_amdgcn_readfirstlane(L.thr[r]);
   }
-  __syncthreads();
 
-  // --- the bin of the K-th coarse score
-  for (int i = tid; i < (int)(sizeof(ListEnd) / 16); i += NT) ((uint4*)&E)[i] = make_uint4(0, 0, 0, 0);
-  __syncthreads();
+  // --- the bin of the K-th coarse score; of a head where it is above all of them, again with wide bins
   const HeadShare own = head_share(real);
   const int mr = own.head, mt = own.at;
-  const uint32_t n_list = (uint32_t)__builtin_amdgcn_readfirstlane((int)min(L.n[mr], (uint32_t)kListCap));
-  const uint32_t t_mr = (uint32_t)__builtin_amdgcn_readfirstlane(L.thr[mr]);
-  for (uint32_t i = mt; i < n_list; i += own.threads)   // (the last bin holds all that is further up)
-    atomicAdd(&E.hist[mr >> 1][min(((L.entry[mr][i] >> 16) - t_mr) >> kListBin, (uint32_t)kHistBins - 1)], 1u << (16 * (mr & 1)));
-  __syncthreads();
-  if (wv < kHeadsPerGroup) {
-    const int bin = wave_find_bin(E.hist[wv >> 1], 16 * (wv & 1), (uint32_t)sr.kk, lane);
-    if (lane == 0) L.bin[wv] = bin;
-  }
-  __syncthreads();
+  const bool take_all = sr.kk >= sr.ncand;   // (uniform; then the thresholds are zero)
+  uint32_t n_list, t_mr, wide = 0;           // wide: heads with wide bins
+  int32_t bin_of[kHeadsPerGroup];
+  auto bin_log = [&](int r) { return (wide >> r) & 1u ? kListWide : kListBin; };
+  auto find_bins = [&]() {
+    for (int i = tid; i < (int)(sizeof(ListEnd) / 16); i += NT) ((uint4*)&E)[i] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    n_list = (uint32_t)__builtin_amdgcn_readfirstlane((int)min(L.n[mr], (uint32_t)kListCap));
+    t_mr = (uint32_t)__builtin_amdgcn_readfirstlane(L.thr[mr]);
+    const int log = bin_log(mr);
+    if (!take_all)
+      for (uint32_t i = mt; i < n_list; i += own.threads)   // (the last bin holds all that is further up)
+        atomicAdd(&E.hist[mr >> 1][min(((L.entry[mr][i] >> 16) - t_mr) >> log, (uint32_t)kHistBins - 1)], 1u << (16 * (mr & 1)));
+    __syncthreads();
+    if (wv < kHeadsPerGroup) {
+      const int bin = take_all ? 0 : wave_find_bin(E.hist[wv >> 1], 16 * (wv & 1), (uint32_t)sr.kk, lane);
+      if (lane == 0) L.bin[wv] = bin;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kHeadsPerGroup; ++r) bin_of[r] = __builtin_amdgcn_readfirstlane(L.bin[r]);
+  };
+  find_bins();
+#pragma unroll
+  for (int r = 0; r < kHeadsPerGroup; ++r) wide |= r < n_real && bin_of[r] == kHistBins - 1 ? 1u << r : 0u;
+  if (__builtin_expect(wide != 0u, 0)) find_bins();
   // A head is done again if its list overflowed, or holds less than K rows, or the band begins below the threshold.
   uint32_t redo = 0;
 #pragma unroll
   for (int r = 0; r < kHeadsPerGroup; ++r) {
     const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.n[r]);
-    const int bin = __builtin_amdgcn_readfirstlane(L.bin[r]);
-    const uint32_t why = r >= n_real ? 0u : (n > (uint32_t)kListCap ? 2u : (bin < 0 ? 1u : (T[r] != 0u && (bin << kListBin) < M - 1 ? 4u : (bin == kHistBins - 1 ? 2u : 0u))));
+    const int bin = bin_of[r];
+    const uint32_t why = r >= n_real ? 0u : (n > (uint32_t)kListCap ? 2u : (bin < 0 ? 1u : (T[r] != 0u && (bin << bin_log(r)) < M - 1 ? 4u : 0u)));
     redo |= why ? 1u << r : 0u;
     if (stats && tid == r && r < n_real) stats[head0 + r] = n | why << 28;
   }
   // --- winners and band rows (hist is the band's place from here on)
   if (!((redo >> mr) & 1u)) {
-    const int bin = __builtin_amdgcn_readfirstlane(L.bin[mr]);
-    const int edge = (int)t_mr + (bin << kListBin);
-    const uint32_t t_lo = (uint32_t)max(0, edge - M + 1), t_hi = (uint32_t)min(0xffff, edge + (1 << kListBin) + M);
-    if (mt == 0) L.from[mr] = t_lo;
+    const int bin = mr == 0 ? bin_of[0] : (mr == 1 ? bin_of[1] : (mr == 2 ? bin_of[2] : bin_of[3]));
+    const int edge = (int)t_mr + (bin << bin_log(mr));
+    const uint32_t t_lo = (uint32_t)max(0, edge - M + 1);
+    const uint32_t t_hi = take_all ? 0u : (uint32_t)min(0xffff, edge + (1 << bin_log(mr)) + M);
+    if (mt == 0) {
+      L.from[mr] = t_lo;
+      L.to[mr] = t_hi;
+    }
     uint32_t sure = 0;
     for (uint32_t i = mt; i < n_list; i += own.threads) {
       const uint32_t e = L.entry[mr][i], s = e >> 16, j = e & 0xffffu;
@@ -238,10 +375,15 @@ __device__ __forceinline__ void list_select_body(
 
   // --- the band, and the winners in ascending position
   const Band band = {&E.band[0][0], &E.won[0][0], kListMaxCand / 64, L.n_band, L.n_sure, L.from,
-                     (1u << kListBin) + 2 * M, L.band.table, L.band.hist, L.wave_tot};
-  const uint32_t left = band_winners<M, true>(band, real & ~redo, head0, seq_codes, lo, sr.kk, lut, lay);
-  redo |= left;
-  if (stats && tid < n_real && ((left >> tid) & 1u)) stats[head0 + tid] = L.n[tid] | 2u << 28;
+                     (1u << (wide ? kListWide : kListBin)) + 2 * M, L.band.table, L.band.hist, L.wave_tot};
+  band_winners<M, true>(band, real & ~redo, head0, seq_codes, lo, sr.kk, lut, lay, [&](uint32_t crowded) {
+#pragma unroll 1
+    for (int r = 0; r < kHeadsPerGroup; ++r)   // (while the lists are there)
+      if ((crowded >> r) & 1u)
+        crowded_band<M>(r, L, E, seq_codes, lo, sr.kk, lut + lay.off_exact + (size_t)(head0 + r) * (kCentroids * M),
+                        lut + lay.off_meta + (size_t)(head0 + r) * 4);
+    __syncthreads();
+  });
   write_winners<kListMaxCand / 64 / 256>(band, real & ~redo, head0, lo, sr.ncand, sr.kk, top_k, topk_idx);
 #pragma unroll 1
   for (int r = 0; r < kHeadsPerGroup; ++r)

@@ -29,7 +29,7 @@
 //       4-wide bin of the K-th coarse score by a histogram, and with it the winners and a band of
 //       2 M + 4 units (coarse and exact scores differ by less than M of them) that alone is scored
 //       exactly and ranked; winners are written from a bitmap over the positions.  If the band begins
-//       below the threshold, a list is too short or overflowed, or the band too full -- the
+//       below the threshold, a list is too short or overflowed, or the band holds more than 8192 rows -- the
 //       sample misled (about 1e-6 per head for independent rows, more when similar rows come in
 //       runs) or the input is degenerate -- the workgroup runs the exact route for its head, so
 //       the result is always exact with respect to the 32-bit scores.
@@ -50,6 +50,7 @@ namespace a2ats {
 constexpr int kStreamThreads = 512;
 constexpr int kStreamWaves = kStreamThreads / 64;
 constexpr int kSampleThreads = 512;
+constexpr int kFinalCrowd = 8192;    // rows of about the K-th score that the final kernel ranks, where its LDS has room (4000 for the longest contexts)
 constexpr int kSampleRows = 1024;    // smallest sample of a problem; a sampling workgroup scores up to 8 of these
 
 // Whether a streaming selection is taken by one workgroup for a head group (list_select.hpp), and the sample that it takes.
@@ -72,6 +73,7 @@ static void list_route(const a2ats_dims& d, TopkPlan& p, long ncand, int top_k) 
   const double rows = (xr * xr + 5.0 * xr) / p.list_rows * (double)ncand * 1.08;
   const long rounds = (problems + 255) / 256, a_round = problems / rounds;
   p.list = a_round >= 80 && ncand <= (a_round > (rounds > 1 ? 192 : 128) ? kListMaxCand : 36000) && rows <= kListCap;
+  if (p.list) p.cap = kListCap;
 }
 
 TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink) {
@@ -80,7 +82,7 @@ TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink) 
   p.NG = (G + kHeadsPerGroup - 1) / kHeadsPerGroup;
   long ncand = (long)d.ctx_len - window - n_sink;
   if (ncand < 0) ncand = 0;
-  p.cap = 8192;
+  p.cap = kFinalCrowd;
   // The streaming route: the selection is at most a quarter of at least 16384 candidates.  Up to 4096
   // winners leave the final kernel room: its list holds 8192 survivors, and the sampled threshold lets
   // 1.3 to 1.65 K through there.  Above 2048 the route is called wide and reports no survivor statistics.
@@ -551,6 +553,13 @@ void stream_select_kernel32p(A2ATS_STREAM_ARGS) { stream_select_body<32, true, t
 // What bounds it: a chain of short dependent phases on one CU (entries, histogram, bin, winners, band rows from the code matrix,
 // ranks, output).  Against exact scores of every survivor and a radix select: 14.5 -> 12.1 us (4 sequences of 131072 tokens, K
 // 2048, 128 heads), 17.0 -> 12.2 (2 of 98301, K 2949).
+//
+// A band of more than 1024 rows, and more than 128 equal scores in the bin of the K-th, are ranked by a radix select over (score, position) from
+// registers (by the exact route: ten times slower; by counting: 66 us instead of 48 for 800 equal scores).  Tables and selection,
+// us, that exact scores of all survivors took -> now, 1100, 3000, 6000 equal scores about the K-th of one head in four: 4 sequences of 131072, M =
+// 16, 49.6 -> 51.9, 55.1 -> 56.7, 428 -> 69; 2 of 98301 42.7 -> 44.2, 47.4 -> 47.3, 307 -> 58; 2 of 65536, M = 32, 54.6 -> 57.6, 59.5 -> 62.2,
+// 330 -> 77.
+constexpr int kCounted = 128;         // rows in the bin of the K-th that are ranked by counting
 constexpr int kFinalBin = 2;          // a bin of the first histogram is 4 coarse units, from the threshold up; of a second, where
 constexpr int kFinalWide = 5;         // the K-th is above those, 32, which is the whole range
 constexpr long kFinalTableCand = 1 << 19;   // candidates up to which the exact table is in LDS too
@@ -562,12 +571,18 @@ struct FinalLds {
   int32_t bin, overflow;
   uint64_t won[1];   // a bit for each candidate
 };
-// The table, if it is there, comes first; the exact route takes all of it.
+// The table, if it is there, comes first, and the positions of a crowded band last; the exact route takes all of it.
+struct FinalRoom {
+  int crowd_cap;
+  size_t bytes;
+};
 template <int M>
-size_t final_lds_bytes(long ncand) {
+FinalRoom final_room(long ncand) {
+  constexpr size_t kMost = 160 * 1024;
   const size_t table = ncand <= kFinalTableCand ? kCentroids * M * sizeof(int32_t) : 0;
   const size_t fast = table + sizeof(FinalLds) + (size_t)(ncand + 63) / 64 * 8;
-  return std::max(fast, kExactLdsBytes + sizeof(ExactLds));
+  const int crowd_cap = (int)std::min<size_t>(kFinalCrowd, (kMost - fast) / 4);
+  return {crowd_cap, std::max(fast + crowd_cap * 4, kExactLdsBytes + sizeof(ExactLds))};
 }
 
 template <int M>
@@ -577,8 +592,8 @@ __global__ __launch_bounds__(kExactThreads) void final_select_kernel(
     const int32_t* __restrict__ thr, const uint32_t* __restrict__ counts,
     const uint32_t* __restrict__ lists, uint32_t* __restrict__ route, int32_t* __restrict__ topk_idx,
     int32_t* __restrict__ topk_count, float* __restrict__ topk_score, GridMap gm, CodePages pg, int B,
-    int Hq, int Hkv, int G, int NG, int P0, int n_chunks, int rows_per_chunk, int list_cap, int table_in_lds, int ctx_len,
-    int64_t ctx_stride, int top_k, int window, int n_sink) {
+    int Hq, int Hkv, int G, int NG, int P0, int n_chunks, int rows_per_chunk, int list_cap, int table_in_lds, int crowd_cap,
+    int ctx_len, int64_t ctx_stride, int top_k, int window, int n_sink) {
   constexpr int NT = kExactThreads;
   constexpr int KEEP = 6;   // entries of a thread that stay in registers
   extern __shared__ __align__(16) unsigned char dyn_lds[];
@@ -690,7 +705,7 @@ __global__ __launch_bounds__(kExactThreads) void final_select_kernel(
     sure = wave_inclusive_scan(sure);
     if (lane == 63 && sure) atomicAdd(&L.n_sure, sure);
     __syncthreads();
-    if (L.n_band > (uint32_t)kBandCap) why = 2u;
+    if (L.n_band > (uint32_t)crowd_cap) why = 2u;
   }
   if (tid == 0) route[bh] = min(L.n, 0x0fffffffu) | why << 28;   // diagnostics only
   if (why != 0u) {
@@ -700,13 +715,13 @@ __global__ __launch_bounds__(kExactThreads) void final_select_kernel(
     return;
   }
 
-  auto exact_at = [&](uint32_t j) {
+  auto load_row = [&](uint32_t j, uint4 (&w)[M / 16]) {
     const uint8_t* row = row_ptr<M>(seq_codes, sr.sink_end + (int)j);
-    if (!table_in_lds) return exact_score_of<M>(head_table, row);
-    uint4 w[M / 16];
-    int32_t s = 0;
 #pragma unroll
     for (int qd = 0; qd < M / 16; ++qd) w[qd] = *(const uint4*)(row + qd * 16);
+  };
+  auto exact_by_table = [&](const uint4 (&w)[M / 16]) {
+    int32_t s = 0;
 #pragma unroll
     for (int qd = 0; qd < M / 16; ++qd) {
       const uint32_t d[4] = {w[qd].x, w[qd].y, w[qd].z, w[qd].w};
@@ -718,38 +733,107 @@ __global__ __launch_bounds__(kExactThreads) void final_select_kernel(
     }
     return s;
   };
-  // --- the band: exact keys, then every row counts those before it in (score, position) order; of many rows only those in the
-  // bin of the K-th, of 2048 over the band's range (M = 32, 1000 rows: see band_select.hpp)
+  auto exact_at = [&](uint32_t j) {
+    if (!table_in_lds) return exact_score_of<M>(head_table, row_ptr<M>(seq_codes, sr.sink_end + (int)j));
+    uint4 w[M / 16];
+    load_row(j, w);
+    return exact_by_table(w);
+  };
   const uint32_t n_band = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.n_band), need = (uint32_t)sr.kk - L.n_sure;
-  const bool few = n_band <= 256u;
   const uint32_t key0 = score_key((int32_t)((uint32_t)m_base + (t_lo << m_shift)));
-  const int kshift = max(0, 21 - (int)__clz((t_hi - t_lo + M) << m_shift));   // (a coarse score leaves out less than M units)
-  auto bin_of = [&](uint32_t key) { return min(key > key0 ? (key - key0) >> kshift : 0u, (uint32_t)kHistBins - 1); };
-  if (!few) {
-    for (int i = tid; i < kHistBins; i += NT) L.hist[i] = 0;
+  const uint32_t range = (t_hi - t_lo + M) << m_shift;   // (a coarse score leaves out less than M units)
+  // (score, position) of a row in few bits: its score from the band's lower edge up, and of equal scores the lower position is larger
+  constexpr int kPosBits = 20;
+  static_assert(kFinalMostCand <= 1 << kPosBits, "");
+  const int row_bits = kPosBits + 32 - (int)__clz(range);
+  auto relative = [&](uint32_t key, uint32_t j) {
+    return (uint64_t)(key > key0 ? min(key - key0, range) : 0u) << kPosBits | ((1u << kPosBits) - 1u - j);
+  };
+  if (__builtin_expect(n_band <= (uint32_t)kBandCap, 1)) {
+    // --- the band: exact keys, then every row counts those before it in (score, position) order; of many rows only those in the
+    // bin of the K-th, of 2048 over the band's range (M = 32, 1000 rows: see band_select.hpp)
+    const bool few = n_band <= 256u;
+    const int kshift = max(0, 21 - (int)__clz(range));
+    auto bin_of = [&](uint32_t key) { return min(key > key0 ? (key - key0) >> kshift : 0u, (uint32_t)kHistBins - 1); };
+    if (!few) {
+      for (int i = tid; i < kHistBins; i += NT) L.hist[i] = 0;
+      __syncthreads();
+    }
+    if ((uint32_t)tid < n_band) {
+      const uint32_t j = (uint32_t)L.band[tid], key = score_key(exact_at(j));
+      L.band[tid] = ((uint64_t)key << 32) | ~j;   // (of equal scores the lower position is larger)
+      if (!few) atomicAdd(&L.hist[bin_of(key)], 1u);
+    }
     __syncthreads();
-  }
-  if ((uint32_t)tid < n_band) {
-    const uint32_t j = (uint32_t)L.band[tid], key = score_key(exact_at(j));
-    L.band[tid] = ((uint64_t)key << 32) | ~j;   // (of equal scores the lower position is larger)
-    if (!few) atomicAdd(&L.hist[bin_of(key)], 1u);
-  }
-  __syncthreads();
-  const int kth_bin = few ? 0 : wave_find_bin(L.hist, 0, need, lane, ~0u);
-  for (uint32_t i = tid >> 3; i < n_band; i += NT / 8) {   // eight lanes a row
-    const uint64_t own = L.band[i];
-    const int at = few ? 0 : (int)bin_of((uint32_t)(own >> 32));
-    if (at < kth_bin) continue;
-    int32_t before = 0;
-    if (at == kth_bin) {
+    const int kth_bin = few ? 0 : wave_find_bin(L.hist, 0, need, lane, ~0u);
+    if (few || L.hist[kth_bin] <= (uint32_t)kCounted) {   // (uniform)
+      for (uint32_t i = tid >> 3; i < n_band; i += NT / 8) {   // eight lanes a row
+        const uint64_t own = L.band[i];
+        const int at = few ? 0 : (int)bin_of((uint32_t)(own >> 32));
+        if (at < kth_bin) continue;
+        int32_t before = 0;
+        if (at == kth_bin) {
 #pragma unroll 4
-      for (uint32_t u = tid & 7; u < n_band; u += 8) before += L.band[u] > own ? 1 : 0;
-      before = group8_sum(before);
-    }
-    if ((tid & 7) == 0 && (uint32_t)before < need) {
+          for (uint32_t u = tid & 7; u < n_band; u += 8) before += L.band[u] > own ? 1 : 0;
+          before = group8_sum(before);
+        }
+        if ((tid & 7) == 0 && (uint32_t)before < need) {
+          const uint32_t j = ~(uint32_t)own;
+          atomicOr((uint32_t*)L.won + (j >> 5), 1u << (j & 31));
+        }
+      }
+    } else {
+      const uint64_t own = (uint32_t)tid < n_band ? L.band[tid] : 0ull;
       const uint32_t j = ~(uint32_t)own;
-      atomicOr((uint32_t*)L.won + (j >> 5), 1u << (j & 31));
+      const uint64_t row = relative((uint32_t)(own >> 32), j);
+      const uint64_t last = reached_by<NT>(need, row_bits, [&](auto f) { f((uint32_t)tid < n_band, row); }, L.hist, L.wave_tot,
+                                           (uint32_t*)L.band);
+      if ((uint32_t)tid < n_band && row >= last) atomicOr((uint32_t*)L.won + (j >> 5), 1u << (j & 31));
     }
+  } else {
+    // --- more rows than the band holds (many equal scores): their positions go to LDS, their scores to registers
+    constexpr int kTogether = 4;
+    uint32_t* crowd = (uint32_t*)(L.won + ((ctx_len - window - n_sink + 63) >> 6));
+    uint32_t* n_crowd = (uint32_t*)L.band;
+    uint64_t row[kFinalCrowd / NT];
+    __syncthreads();
+    if (tid == 0) *n_crowd = 0;
+    __syncthreads();
+    each([&](uint32_t s, uint32_t j) {
+      if (s >= t_lo && s < t_hi) crowd[atomicAdd(n_crowd, 1u)] = j;
+    });
+    __syncthreads();
+#pragma unroll
+    for (int k0 = 0; k0 < kFinalCrowd / NT; k0 += kTogether) {
+      uint4 w[kTogether][M / 16];
+      uint32_t j[kTogether];
+      if (k0 * NT >= (int)n_band) continue;   // (uniform)
+#pragma unroll
+      for (int k = 0; k < kTogether; ++k) j[k] = crowd[min((uint32_t)(tid + (k0 + k) * NT), n_band - 1)];
+      if (table_in_lds) {   // (uniform)
+#pragma unroll
+        for (int k = 0; k < kTogether; ++k) load_row(j[k], w[k]);
+#pragma unroll
+        for (int k = 0; k < kTogether; ++k) row[k0 + k] = relative(score_key(exact_by_table(w[k])), j[k]);
+      } else {
+#pragma unroll
+        for (int k = 0; k < kTogether; ++k) row[k0 + k] = relative(score_key(exact_at(j[k])), j[k]);
+      }
+    }
+    const uint64_t last = reached_by<NT>(
+        need, row_bits,
+        [&](auto f) {
+#pragma unroll
+          for (int k = 0; k < kFinalCrowd / NT; ++k)
+            if (k * NT < (int)n_band) f((uint32_t)(tid + k * NT) < n_band, row[k]);
+        },
+        L.hist, L.wave_tot, (uint32_t*)L.band);
+#pragma unroll
+    for (int k = 0; k < kFinalCrowd / NT; ++k)
+      if ((uint32_t)(tid + k * NT) < n_band && row[k] >= last) {
+        const uint32_t j = (1u << kPosBits) - 1u - ((uint32_t)row[k] & ((1u << kPosBits) - 1u));
+        atomicOr((uint32_t*)L.won + (j >> 5), 1u << (j & 31));
+      }
   }
   __syncthreads();
   // --- winners in ascending position
@@ -894,15 +978,16 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
   }
   if ((err = hipGetLastError()) != hipSuccess) return err;
 
-  const size_t final_lds = final_lds_bytes<M>((long)d.ctx_len - window - n_sink);
+  const long ncand = (long)d.ctx_len - window - n_sink;
+  const FinalRoom room = final_room<M>(ncand);
   // (allowed once for all contexts: threads that each raise it to their own call's size could lower one another's)
-  const size_t final_most = std::max(final_lds_bytes<M>(kFinalTableCand), final_lds_bytes<M>(kFinalMostCand));
+  const size_t final_most = std::max(final_room<M>(kFinalTableCand).bytes, final_room<M>(kFinalMostCand).bytes);
   if ((err = allow_dynamic_lds(final_select_kernel<M>, final_most, s_final)) != hipSuccess) return err;
   hipLaunchKernelGGL((final_select_kernel<M>), dim3(problems * kHeadsPerGroup), dim3(kExactThreads),
-                     final_lds, stream, codes, lut, lut_scale, seq_lens, thr, counts, lists, route, topk_idx,
+                     room.bytes, stream, codes, lut, lut_scale, seq_lens, thr, counts, lists, route, topk_idx,
                      topk_count, topk_score, make_grid_map(kHeadsPerGroup, problems, NG, Hkv), pg, B, Hq, Hkv, G, NG,
                      plan.P0, plan.chunks, plan.rows_per_chunk, list_cap,
-                     (long)d.ctx_len - window - n_sink <= kFinalTableCand ? 1 : 0, d.ctx_len, d.ctx_stride, top_k, window, n_sink);
+                     ncand <= kFinalTableCand ? 1 : 0, room.crowd_cap, d.ctx_len, d.ctx_stride, top_k, window, n_sink);
   return hipGetLastError();
 }
 

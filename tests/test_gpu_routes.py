@@ -830,3 +830,58 @@ def test_streamed_selections_of_several_threads_equal_a_full_sort():
     for wl, xd, st in calls:
         for a, b in zip((st.topk_idx, st.topk_count, st.topk_score.view(torch.int32)), _full_sort(wl, xd, st, None)):
             assert torch.equal(a, b)
+
+
+def _equal_rows(wl, xd, st, blocks):
+    """Gives the rows of every KV head that stand at ranks first..last of its first query head's scores the code of one of them."""
+    M, dev = wl.n_sub, "cuda"
+    B.build_lut(st.dims, xd["q"], st.cos_b, st.sin_b, xd["codebook"], st.q_rot, st.lut, st.lut_scale)
+    table = st.lut[:wl.batch * wl.n_q_heads * 256 * M].view(wl.batch, wl.n_kv_heads, wl.group, 256 * M)[:, :, 0].long()
+    for b in range(wl.batch):
+        for kv in range(wl.n_kv_heads):
+            codes = xd["codes"][b, kv]
+            score = table[b, kv][codes.long() * M + torch.arange(M, device=dev)].sum(1)
+            order = torch.sort(score[wl.n_sink:wl.ctx_len - wl.window], descending=True).indices + wl.n_sink
+            for first, last in blocks:
+                codes[order[first:last]] = codes[order[(first + last) // 2]].clone()
+
+
+# rows a head's list holds on the route of lists in LDS, and rows of about the K-th score that the final kernel of the streaming route does
+LIST_ROWS, CROWD_ROWS = 5632, 8192
+
+
+@pytest.mark.parametrize("Bn,Hkv,G,M,N,K,lens,blocks,route", [
+    (42, 2, 4, 16, 20000, 600, None, [(100, 1123)], 0),              # 1023 equal scores, one fewer than the band holds
+    (42, 2, 4, 16, 20000, 600, None, [(100, 1400)], 0),              # more than it holds
+    (42, 2, 3, 32, 20000, 600, None, [(100, 4700)], 0),              # nearly all that a list holds
+    (84, 1, 1, 32, 18000, 600, None, [(599, 1900)], 0),              # one of the equal rows wins
+    (84, 1, 2, 16, 18000, 600, None, [(0, 600), (600, 1900)], 0),    # none of the second block
+    (42, 2, 4, 16, 32768, 1000, None, [(0, 1300), (1300, 6300)], 0), # a list overflows and is made again
+    (42, 2, 4, 16, 32768, 1000, None, [(0, 6300)], 2),               # and overflows again
+    (42, 2, 4, 16, 20000, 1900, 1400, [], 0),                        # every candidate of short sequences wins
+    (42, 2, 4, 32, 20000, 1900, 2000, [], 0),                        # nearly every one: the K-th far above a threshold of zero
+    (65, 2, 3, 16, 65536 + 68, 1500, None, [(1400, 3000)], 0),       # the most candidates
+    (2, 2, 4, 16, 60000, 1500, None, [(100, 1123)], 0),              # the streaming route: in its band,
+    (2, 2, 4, 16, 60000, 1500, None, [(100, 8100)], 0),              # all that its final kernel ranks,
+    (2, 2, 4, 16, 60000, 1500, None, [(100, 8700)], 2),              # and more
+    (1, 1, 4, 32, 66000, 1500, None, [(1000, 2300)], 0),
+    (1, 1, 2, 32, 1 << 20, 2048, None, [(1000, 4500)], 0),           # the longest context, whose tables stay in memory
+])
+def test_selection_among_equal_scores_takes_no_detour(Bn, Hkv, G, M, N, K, lens, blocks, route):
+    """Many rows of the K-th score: against a full sort, and without the exact route as long as the lists hold them."""
+    wl = synth.Workload("equal", Bn, Hkv * G, Hkv, 128, M, N, K, 64, n_sink=4, seed=N + K)
+    xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
+    st = B.DecodeState(H.dims_of(wl), K, 64, 4, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
+    lists = Bn * Hkv * ((G + 3) // 4) >= 80
+    assert B.score_topk_plan(st.dims, K, 64, 4)["survivor_capacity"] == (LIST_ROWS if lists else CROWD_ROWS)
+    _equal_rows(wl, xd, st, blocks)
+    sl = None if lens is None else torch.full((Bn,), 64 + 4 + lens, dtype=torch.int32)
+    st.topk_idx.fill_(-7), st.topk_count.fill_(-7), st.topk_score.fill_(-7.0), st.ws.fill_(0xA5)
+    out = (st.topk_idx, st.topk_count, st.topk_score)
+    B.score_topk(st.dims, xd["codes"], st.lut, st.lut_scale, K, 64, 4, None if sl is None else sl.cuda(), *out, None, st.ws)
+    stats = torch.empty(Bn, Hkv * G, dtype=torch.int32, device="cuda")
+    B.score_topk_stats(st.dims, K, 64, 4, st.ws, stats)
+    for a, b in zip((out[0], out[1], out[2].view(torch.int32)), _full_sort(wl, xd, st, None if sl is None else sl.tolist())):
+        assert torch.equal(a, b)
+    routes = (stats.view(Bn, Hkv, G)[:, :, 0].cpu().numpy().astype(np.int64) & 0xffffffff) >> 28   # of the heads with equal scores
+    assert (routes == route).all()

@@ -931,11 +931,16 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
   unsigned char* wsb = (unsigned char*)ws;
   if (plan.list) {
     if ((err = allow_dynamic_lds(list_select_kernel<M>, kListLdsBytes, s_list)) != hipSuccess) return err;
-    // (hipExtLaunchKernelGGL: the pair of events, where there is one, is attached to the dispatch)
-    hipExtLaunchKernelGGL((list_select_kernel<M>), dim3(problems), dim3(kListThreads), kListLdsBytes, stream, ev_start, ev_stop,
-                          0, codes, lut, lut_scale, seq_lens, topk_idx, topk_count, topk_score,
-                          (uint32_t*)(wsb + plan.off_route), make_grid_map(1, problems, NG, Hkv), pg, plan.list_rows, B, Hq,
-                          Hkv, NG, d.ctx_len, d.ctx_stride, top_k, window, n_sink);
+    const GridMap gm = make_grid_map(1, problems, NG, Hkv);
+    uint32_t* stats = (uint32_t*)(wsb + plan.off_route);
+    if (ev_start && ev_stop)   // (attached to the dispatch)
+      hipExtLaunchKernelGGL((list_select_kernel<M>), dim3(problems), dim3(kListThreads), kListLdsBytes, stream, ev_start, ev_stop,
+                            0, codes, lut, lut_scale, seq_lens, topk_idx, topk_count, topk_score, stats, gm, pg, plan.list_rows, B,
+                            Hq, Hkv, NG, d.ctx_len, d.ctx_stride, top_k, window, n_sink);
+    else
+      hipLaunchKernelGGL((list_select_kernel<M>), dim3(problems), dim3(kListThreads), kListLdsBytes, stream, codes, lut, lut_scale,
+                         seq_lens, topk_idx, topk_count, topk_score, stats, gm, pg, plan.list_rows, B, Hq, Hkv, NG, d.ctx_len,
+                         d.ctx_stride, top_k, window, n_sink);
     return hipGetLastError();
   }
   int32_t* thr = (int32_t*)(wsb + plan.off_thr);

@@ -885,3 +885,40 @@ def test_selection_among_equal_scores_takes_no_detour(Bn, Hkv, G, M, N, K, lens,
         assert torch.equal(a, b)
     routes = (stats.view(Bn, Hkv, G)[:, :, 0].cpu().numpy().astype(np.int64) & 0xffffffff) >> 28   # of the heads with equal scores
     assert (routes == route).all()
+
+
+@pytest.mark.parametrize("call", ["score", "select"])
+@pytest.mark.parametrize("M,G", [(16, 4), (32, 3)])
+def test_selection_by_lists_replayed_from_a_graph(M, G, call):
+    """A captured selection by lists: every replay, on new codes and queries, equals the call."""
+    wl = synth.Workload("lists_graph", 42, 2 * G, 2, 128, M, 17000, 500, 64, n_sink=4, seed=M)
+    xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
+    st = B.DecodeState(H.dims_of(wl), 500, 64, 4, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
+    assert B.score_topk_plan(st.dims, 500, 64, 4)["survivor_capacity"] == LIST_ROWS
+    key = torch.randn(42, 2, 1, 128, device="cuda")
+
+    def run():
+        if call == "select":
+            B.decode_select(st.dims, key, 1, 16999, xd["codebook"], None, B.W_NONE, xd["codes"], xd["q"], st.cos_b, st.sin_b,
+                            st.q_rot, st.lut, st.lut_scale, 500, 64, 4, None, st.topk_idx, st.topk_count, st.topk_score, st.ws)
+        else:
+            B.build_lut(st.dims, xd["q"], st.cos_b, st.sin_b, xd["codebook"], st.q_rot, st.lut, st.lut_scale)
+            B.score_topk(st.dims, xd["codes"], st.lut, st.lut_scale, 500, 64, 4, None, st.topk_idx, st.topk_count, st.topk_score,
+                         None, st.ws)
+
+    run()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run()
+    for _ in range(3):
+        xd["q"].copy_(torch.randn_like(xd["q"]))
+        xd["codes"].copy_(xd["codes"].roll(1, 2))
+        st.topk_idx.fill_(-7), st.topk_count.fill_(-7), st.topk_score.fill_(-7.0)
+        graph.replay()
+        got = [t.clone() for t in (st.topk_idx, st.topk_count, st.topk_score.view(torch.int32))]
+        for a, b in zip(got, _full_sort(wl, xd, st, None)):
+            assert torch.equal(a, b)
+        run()
+        for a, b in zip(got, (st.topk_idx, st.topk_count, st.topk_score.view(torch.int32))):
+            assert torch.equal(a, b)

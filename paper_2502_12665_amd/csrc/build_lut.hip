@@ -714,7 +714,7 @@ hipError_t launch_decode_select_group(const a2ats_dims& d, const float* keys, in
 #define A2ATS_LAUNCH_GRP(DS, BF, SH, SLOT)                                                                      \
   do {                                                                                                          \
     const size_t lds = kGroupLdsBytes + lut_lds_bytes<DS, SH>(); \
-    if ((err = allow_dynamic_lds(decode_select_group_kernel<DS, BF, SH>, lds, s_lds[SLOT])) !=       \
+    if ((err = allow_dynamic_lds(decode_select_group_kernel<DS, BF, SH>, lds, s_lds[SLOT], true)) !=       \
         hipSuccess)                                                                                             \
       return err;                                                                                               \
     hipLaunchKernelGGL((decode_select_group_kernel<DS, BF, SH>), grid, block, lds, stream, q, cos_b, \
@@ -753,7 +753,7 @@ hipError_t launch_decode_select_list(const a2ats_dims& d, const TopkPlan& plan, 
 #define A2ATS_LAUNCH_LIST(DS, BF, SH, SLOT)                                                                    \
   do {                                                                                                         \
     const size_t lds = kListLdsBytes + lut_lds_bytes<DS, SH>(); \
-    if ((err = allow_dynamic_lds(decode_select_list_kernel<DS, BF, SH>, lds, s_lds[SLOT])) !=        \
+    if ((err = allow_dynamic_lds(decode_select_list_kernel<DS, BF, SH>, lds, s_lds[SLOT], true)) !=        \
         hipSuccess)                                                                                            \
       return err;                                                                                              \
     hipLaunchKernelGGL((decode_select_list_kernel<DS, BF, SH>), grid, block, lds, stream, q, cos_b,  \
@@ -800,7 +800,7 @@ hipError_t launch_decode_select_prologue(const a2ats_dims& d, const float* keys,
   do {                                                                                                       \
     const size_t lds = kCoarseLdsBytes + kSampleHistBytes + lut_lds_bytes<DS, SH>(); \
     if ((err = allow_dynamic_lds(decode_select_prologue_kernel<DS, BF, SH>, lds,         \
-                                 s_lds[SLOT])) != hipSuccess)                                                \
+                                 s_lds[SLOT], true)) != hipSuccess)                                                \
       return err;                                                                                            \
     hipLaunchKernelGGL((decode_select_prologue_kernel<DS, BF, SH>), grid, block, lds, stream, q, \
                        cos_b, sin_b, codebook, q_rot, lut, lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, NG, \

@@ -24,7 +24,7 @@ __device__ __forceinline__ int lanes_below(uint64_t mask) {
                                    __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// An object at a constant LDS address, of a kernel without static LDS: reads and writes take the address as their offset.  (The
+// An object at a constant LDS address, of a kernel without static LDS (allow_dynamic_lds checks that on the host): reads and writes take the address as their offset.  (The
 // start of the dynamic LDS is a symbol to the compiler, 0 or not: behind it every access has an addition.)
 template <typename T>
 __device__ __forceinline__ T& lds_at(uint32_t address) {

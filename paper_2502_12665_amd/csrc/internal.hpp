@@ -48,13 +48,20 @@ hipError_t copy_topk_stats(const a2ats_dims& d, int top_k, int window, int n_sin
 // once per kernel and device; `slot` (16 entries, one per device) caches the largest size set.
 // (Threads racing on a slot at worst set the same attribute twice.)
 typedef std::atomic<size_t> LdsSlot;
+// at_zero: the kernel takes its dynamic LDS to begin at address 0 (lds_at, score_coarse), so it may have no static LDS: one that has
+// is refused here, before it could read its tables from the wrong place.
 template <typename K>
-inline hipError_t allow_dynamic_lds(K kernel, size_t bytes, LdsSlot* slot) {
+inline hipError_t allow_dynamic_lds(K kernel, size_t bytes, LdsSlot* slot, bool at_zero = false) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 16) dev = 0;
   if (slot[dev].load(std::memory_order_acquire) >= bytes) return hipSuccess;
-  const hipError_t e =
-      hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  hipError_t e = hipSuccess;
+  if (at_zero) {
+    hipFuncAttributes a{};
+    if ((e = hipFuncGetAttributes(&a, (const void*)kernel)) != hipSuccess) return e;
+    if (a.sharedSizeBytes != 0) return hipErrorInvalidKernelFile;
+  }
+  e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   if (e == hipSuccess) slot[dev].store(bytes, std::memory_order_release);
   return e;
 }

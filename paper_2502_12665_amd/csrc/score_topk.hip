@@ -558,7 +558,7 @@ void stream_select_kernel32p(A2ATS_STREAM_ARGS) { stream_select_body<32, true, t
 // registers (by the exact route: ten times slower; by counting: 66 us instead of 48 for 800 equal scores).  Tables and selection,
 // us, that exact scores of all survivors took -> now, 1100, 3000, 6000 equal scores about the K-th of one head in four: 4 sequences of 131072, M =
 // 16, 49.6 -> 51.9, 55.1 -> 56.7, 428 -> 69; 2 of 98301 42.7 -> 44.2, 47.4 -> 47.3, 307 -> 58; 2 of 65536, M = 32, 54.6 -> 57.6, 59.5 -> 62.2,
-// 330 -> 77.
+// 330 -> 77.  M = 32 has such bands without equal scores: one selection per KV head, 16 of 122753, K 4096, 57.5 -> 59.4 (the exact route 608).
 constexpr int kCounted = 128;         // rows in the bin of the K-th that are ranked by counting
 constexpr int kFinalBin = 2;          // a bin of the first histogram is 4 coarse units, from the threshold up; of a second, where
 constexpr int kFinalWide = 5;         // the K-th is above those, 32, which is the whole range
@@ -691,6 +691,7 @@ __global__ __launch_bounds__(kExactThreads) void final_select_kernel(
   uint32_t why = L.overflow ? 3u : (bin < 0 ? 1u : (T != 0u && (bin << shift) < M - 1 ? 4u : 0u));
   const int edge = (int)T + (bin << shift);
   const uint32_t t_lo = (uint32_t)max(0, edge - M + 1), t_hi = (uint32_t)(edge + (1 << shift) + M);
+  uint32_t* crowd = (uint32_t*)(L.won + ((ctx_len - window - n_sink + 63) >> 6));   // positions of the band's rows
   if (why == 0u) {
     uint32_t sure = 0;
     each([&](uint32_t s, uint32_t j) {
@@ -699,7 +700,7 @@ __global__ __launch_bounds__(kExactThreads) void final_select_kernel(
         ++sure;
       } else if (s >= t_lo) {
         const uint32_t slot = atomicAdd(&L.n_band, 1u);
-        if (slot < (uint32_t)kBandCap) L.band[slot] = j;
+        if (slot < (uint32_t)crowd_cap) crowd[slot] = j;
       }
     });
     sure = wave_inclusive_scan(sure);
@@ -760,7 +761,7 @@ __global__ __launch_bounds__(kExactThreads) void final_select_kernel(
       __syncthreads();
     }
     if ((uint32_t)tid < n_band) {
-      const uint32_t j = (uint32_t)L.band[tid], key = score_key(exact_at(j));
+      const uint32_t j = crowd[tid], key = score_key(exact_at(j));
       L.band[tid] = ((uint64_t)key << 32) | ~j;   // (of equal scores the lower position is larger)
       if (!few) atomicAdd(&L.hist[bin_of(key)], 1u);
     }
@@ -791,18 +792,9 @@ __global__ __launch_bounds__(kExactThreads) void final_select_kernel(
       if ((uint32_t)tid < n_band && row >= last) atomicOr((uint32_t*)L.won + (j >> 5), 1u << (j & 31));
     }
   } else {
-    // --- more rows than the band holds (many equal scores): their positions go to LDS, their scores to registers
+    // --- more rows than are ranked so (M = 32, thousands of winners; or equal scores)
     constexpr int kTogether = 4;
-    uint32_t* crowd = (uint32_t*)(L.won + ((ctx_len - window - n_sink + 63) >> 6));
-    uint32_t* n_crowd = (uint32_t*)L.band;
     uint64_t row[kFinalCrowd / NT];
-    __syncthreads();
-    if (tid == 0) *n_crowd = 0;
-    __syncthreads();
-    each([&](uint32_t s, uint32_t j) {
-      if (s >= t_lo && s < t_hi) crowd[atomicAdd(n_crowd, 1u)] = j;
-    });
-    __syncthreads();
 #pragma unroll
     for (int k0 = 0; k0 < kFinalCrowd / NT; k0 += kTogether) {
       uint4 w[kTogether][M / 16];

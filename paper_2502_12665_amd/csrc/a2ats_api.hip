@@ -308,7 +308,7 @@ int a2ats_decode_select(const a2ats_dims* d, const float* keys, int32_t n_new, i
   if (top_k > 4096) return A2ATS_ERR_UNSUPPORTED;
   if (!codes || !lut || !lut_scale || !topk_count || (top_k > 0 && !topk_idx)) return A2ATS_ERR_INVALID_ARG;
   if (misaligned16(codes)) return A2ATS_ERR_INVALID_ARG;
-  a2ats::TopkPlan plan = a2ats::make_topk_plan(*d, top_k, window, n_sink);
+  a2ats::TopkPlan plan = a2ats::make_topk_plan(*d, top_k, window, n_sink, seq_lens != nullptr);
   if (!a2ats::single_codebook(*d) && plan.fast && !holds(plan, ws, ws_bytes)) return A2ATS_ERR_WORKSPACE;
   const bool streams = plan.fast || (plan.wide && holds(plan, ws, ws_bytes));
   if (streams) sample_in_one_part(plan, (long)d->batch * d->n_kv_heads * plan.NG);
@@ -420,7 +420,7 @@ int a2ats_decode_select_shared(const a2ats_dims* d, const float* keys, int32_t n
     return A2ATS_ERR_INVALID_ARG;
   a2ats_dims dk = *d;   // the score/top-K side sees one table head per KV head
   dk.n_q_heads = d->n_kv_heads;
-  a2ats::TopkPlan plan = a2ats::make_topk_plan(dk, top_k, window, n_sink);
+  a2ats::TopkPlan plan = a2ats::make_topk_plan(dk, top_k, window, n_sink, seq_lens != nullptr);
   if (plan.fast && !holds(plan, ws, ws_bytes)) return A2ATS_ERR_WORKSPACE;
   if (plan.wide && !holds(plan, ws, ws_bytes)) ws = nullptr;   // the exact route
   const bool streams = plan.fast || (plan.wide && ws);

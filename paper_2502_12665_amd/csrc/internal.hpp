@@ -38,7 +38,8 @@ struct AttnPlan {
   size_t bytes;
 };
 
-TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink);
+// ragged: the call comes with lengths, on which the choice of the list route depends, and nothing else.
+TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink, bool ragged = false);
 AttnPlan make_attn_plan(const a2ats_dims& d, int top_k, int window, int n_sink);
 size_t encode_ws_bytes(const a2ats_dims& d);
 hipError_t copy_topk_stats(const a2ats_dims& d, int top_k, int window, int n_sink, const void* ws,

@@ -63,20 +63,34 @@ constexpr int kSampleRows = 1024;    // smallest sample of a problem; a sampling
 // rounds: 264 groups 32768, 65000 231.1 -> 227.1, 317.2 -> 325.0.  M = 32: 96 groups 24000, 39000 105.8 -> 102.0, 133.1 -> 132.6;
 // 144 groups 63000 228.4 -> 228.5; 192 groups 65000 278.9 -> 260.2; two rounds: 288 groups 65000 351.8 -> 381.8.  One selection
 // per KV head: 128 groups 32768 76.3 -> 74.3, 160 groups 65000 109.6 -> 102.2.
+// Sequences of their own lengths (`ragged`): the streaming pass leaves out what is not there, while one workgroup takes as long as the
+// longest, so the line lies lower.  Tables and selection, lengths from a quarter up, streaming -> list route: 80 groups 24000, 28000, 36000
+// tokens 41.9 -> 41.7, 42.6 -> 47.1, 47.8 -> 54.5; 96 groups 24000, 28000, 36000 43.0 -> 42.1, 47.8 -> 47.5, 50.3 -> 54.8; 112 groups 24000, 32000, 36000
+// 47.8 -> 42.4, 50.7 -> 49.4, 52.4 -> 55.3; 120 groups 32000, 36000 52.6 -> 49.4, 54.3 -> 55.3; 128 groups 36000 56.6 -> 55.6.  M = 32: 80 groups 17000,
+// 24000 56.0 -> 56.7, 59.5 -> 63.3; 96 groups 17000, 24000 57.1 -> 56.9, 60.9 -> 63.7; 112 groups 24000, 30000 69.3 -> 64.2, 73.5 -> 74.5; 128 groups
+// 36000 86.0 -> 81.3.  Beyond 128 groups the list route gains as with full lengths (144 groups 60000 93.7 -> 78.5, two rounds, 264 groups 159.8 ->
+// 152.5).
+// Three rounds and more, full lengths: 520 groups 32768 223 -> 173, 768 268 -> 186, 1024 364 -> 248; 768 of 60000 393 -> 282; M = 32 1024 of 24000
+// 523 -> 347.
 // A list holds kListCap rows: what the sample lets through (see below), five standard deviations more, and 8 % for the
 // threshold's rounding to a bin.
-static void list_route(const a2ats_dims& d, TopkPlan& p, long ncand, int top_k) {
+static void list_route(const a2ats_dims& d, TopkPlan& p, long ncand, int top_k, bool ragged) {
   const long problems = std::max(1L, (long)d.batch * d.n_kv_heads * p.NG);
   p.list_rows = (int)std::min<long>(std::max<long>(ncand / 8 / 512 * 512, kSampleRows), kSampleMost);
   const double r0 = (double)top_k * p.list_rows / (double)ncand;
   const double xr = 0.5 * (kSigma + std::sqrt(kSigma * kSigma + 4.0 * r0));
   const double rows = (xr * xr + 5.0 * xr) / p.list_rows * (double)ncand * 1.08;
   const long rounds = (problems + 255) / 256, a_round = problems / rounds;
-  p.list = a_round >= 80 && ncand <= (a_round > (rounds > 1 ? 192 : 128) ? kListMaxCand : 36000) && rows <= kListCap;
+  long few = 36000;
+  if (ragged && a_round < 128) {
+    if (d.n_sub == 16) few = a_round < 88 ? 24000 : (a_round < 112 ? 28000 : 32000);
+    else few = a_round < 96 ? 0 : (a_round < 112 ? 18000 : 26000);
+  }
+  p.list = a_round >= 80 && ncand <= (a_round > (rounds > 1 ? 192 : 128) ? kListMaxCand : few) && rows <= kListCap;
   if (p.list) p.cap = kListCap;
 }
 
-TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink) {
+TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink, bool ragged) {
   TopkPlan p{};
   const int G = d.n_q_heads / d.n_kv_heads;
   p.NG = (G + kHeadsPerGroup - 1) / kHeadsPerGroup;
@@ -151,7 +165,7 @@ TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink) 
     const size_t heads = (size_t)d.batch * d.n_q_heads;
     const size_t segs = (size_t)problems * p.chunks * kStreamWaves;
     const size_t entry_bytes = 4 + d.n_sub;   // header + code bytes
-    list_route(d, p, ncand, top_k);
+    list_route(d, p, ncand, top_k, ragged);
     p.off_thr = 0;
     p.off_route = (p.off_thr + heads * p.P0 * sizeof(int32_t) + 255) / 256 * 256;
     p.off_count = (p.off_route + heads * sizeof(uint32_t) + 255) / 256 * 256;
@@ -1014,7 +1028,7 @@ hipError_t launch_score_topk(const a2ats_dims& d, const uint8_t* codes, const Co
                              const int32_t* seq_lens, int32_t* topk_idx, int32_t* topk_count,
                              float* topk_score, float* scores_out, void* ws, int presampled,
                              hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  TopkPlan plan = make_topk_plan(d, top_k, window, n_sink);
+  TopkPlan plan = make_topk_plan(d, top_k, window, n_sink, seq_lens != nullptr);
   if (presampled) plan.P0 = presampled;
   if (d.n_sub == 16)
     return launch_score_topk_m<16>(d, plan, codes, pg, lut, lut_scale, top_k, window, n_sink, seq_lens,

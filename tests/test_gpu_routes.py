@@ -922,3 +922,37 @@ def test_selection_by_lists_replayed_from_a_graph(M, G, call):
         run()
         for a, b in zip(got, (st.topk_idx, st.topk_count, st.topk_score.view(torch.int32))):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("call", ["score", "select", "paged"])
+@pytest.mark.parametrize("groups,M,cand", [
+    (87, 16, 24000), (87, 16, 24001), (111, 16, 28000), (111, 16, 28001), (127, 16, 32000), (127, 16, 32001), (128, 16, 36000),
+    (128, 16, 36001), (95, 32, 16384), (96, 32, 18000), (111, 32, 18001), (112, 32, 26000), (127, 32, 26001), (128, 32, 36000)])
+def test_selection_of_lengths_on_both_sides_of_the_line_for_lists(groups, M, cand, call):
+    """Sequences of their own lengths, where the choice between the lists of a workgroup and the streaming route depends on there
+    being any: either way against a full sort, by the two calls, by the one, and of codes in pages."""
+    N, K, page = cand + 68, 400, 16
+    wl = synth.Workload("line", groups, 1, 1, 128, M, N, K, 64, n_sink=4, seed=cand)
+    xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
+    st = B.DecodeState(H.dims_of(wl), K, 64, 4, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
+    sl = torch.randint(N // 4, N + 1, (groups,), generator=torch.Generator().manual_seed(N), dtype=torch.int32)
+    sl[:4] = torch.tensor([N, 0, 68, 68 + K])
+    st.topk_idx.fill_(-7), st.topk_count.fill_(-7), st.topk_score.fill_(-7.0), st.ws.fill_(0xA5)
+    if call == "select":
+        key = torch.randn(groups, 1, 1, 128, device="cuda")
+        B.decode_select(st.dims, key, 1, N - 1, xd["codebook"], None, B.W_NONE, xd["codes"], xd["q"], st.cos_b, st.sin_b, st.q_rot,
+                        st.lut, st.lut_scale, K, 64, 4, sl.cuda(), st.topk_idx, st.topk_count, st.topk_score, st.ws)
+    else:
+        B.build_lut(st.dims, xd["q"], st.cos_b, st.sin_b, xd["codebook"], st.q_rot, st.lut, st.lut_scale)
+        out = (st.topk_idx, st.topk_count, st.topk_score, None, st.ws)
+        if call == "paged":
+            slots = (N + page - 1) // page
+            table = torch.randperm(groups * slots, device="cuda").reshape(groups, slots).to(torch.int32)
+            pool = torch.zeros(groups * slots, 1, page, M, dtype=torch.uint8, device="cuda")
+            padded = torch.nn.functional.pad(xd["codes"], (0, 0, 0, slots * page - N))
+            pool[table.reshape(-1).long()] = padded.reshape(groups * slots, 1, page, M)
+            B.score_topk_paged(st.dims, pool, table, page, st.lut, st.lut_scale, K, 64, 4, sl.cuda(), *out)
+        else:
+            B.score_topk(st.dims, xd["codes"], st.lut, st.lut_scale, K, 64, 4, sl.cuda(), *out)
+    for a, b in zip((st.topk_idx, st.topk_count, st.topk_score.view(torch.int32)), _full_sort(wl, xd, st, sl.tolist())):
+        assert torch.equal(a, b)

@@ -363,7 +363,7 @@ __global__ __launch_bounds__(kLutThreads) void decode_select_prologue_kernel(
 // selection as two launches this saves a launch and the copy of the table.  Of the `split` workgroups of a problem each
 // writes the exact tables of the heads that it selects for (it reads them back).  The appended keys are encoded as in
 // decode_prologue_kernel.
-template <int DS, bool QBF16, bool SHARED>
+template <int DS, bool QBF16, bool SHARED, bool MANY>
 __global__ __launch_bounds__(kLutThreads) void decode_select_group_kernel(
     const void* __restrict__ q_in, const float* __restrict__ cos_b, const float* __restrict__ sin_b,
     const float* __restrict__ codebook, float* __restrict__ q_rot, int32_t* __restrict__ lut,
@@ -384,9 +384,9 @@ __global__ __launch_bounds__(kLutThreads) void decode_select_group_kernel(
     build_lut_body<DS, QBF16, SHARED>(prob, q_in, cos_b, sin_b, codebook, q_rot, lut, lut_scale, B, Hq, Hkv, NG,
                                       lds_at<LutLds<DS, SHARED>>(kGroupLdsBytes),
                                       part == 0 ? mine | kWriteCommon : mine, dyn_lds);
-    group_select_body<M, true>(b, kv, g4, prob, mine, codes, CodePages{nullptr, 0, 0}, lut, lut_scale, seq_lens, topk_idx,
-                               topk_count, topk_score, B, SHARED ? Hkv : Hq, Hkv, ctx_len, ctx_stride, top_k, window,
-                               n_sink, dyn_lds);
+    group_select_body<M, true, MANY>(b, kv, g4, prob, mine, codes, CodePages{nullptr, 0, 0}, lut, lut_scale, seq_lens, topk_idx,
+                                     topk_count, topk_score, B, SHARED ? Hkv : Hq, Hkv, ctx_len, ctx_stride, top_k, window,
+                                     n_sink, dyn_lds);
     if (folded)
       encode_few_block<DS>((int)blockIdx.x, sweeps, keys, codebook, weights, mode, codes, B, Hkv, n_new, pos0,
                            ctx_stride);
@@ -709,29 +709,32 @@ hipError_t launch_decode_select_group(const a2ats_dims& d, const float* keys, in
   const int n_lut = groups * split;
   const dim3 grid(n_lut + ap.n_enc), block(kLutThreads);
   if (grid.x == 0) return hipSuccess;
-  static LdsSlot s_lds[8][16];
+  static LdsSlot s_lds[12][16];
   hipError_t err;
-#define A2ATS_LAUNCH_GRP(DS, BF, SH, SLOT)                                                                      \
+#define A2ATS_LAUNCH_GRP(DS, BF, SH, MANY, SLOT)                                                                      \
   do {                                                                                                          \
     const size_t lds = kGroupLdsBytes + lut_lds_bytes<DS, SH>(); \
-    if ((err = allow_dynamic_lds(decode_select_group_kernel<DS, BF, SH>, lds, s_lds[SLOT], true)) !=       \
+    if ((err = allow_dynamic_lds(decode_select_group_kernel<DS, BF, SH, MANY>, lds, s_lds[SLOT], true)) !=       \
         hipSuccess)                                                                                             \
       return err;                                                                                               \
-    hipLaunchKernelGGL((decode_select_group_kernel<DS, BF, SH>), grid, block, lds, stream, q, cos_b, \
+    hipLaunchKernelGGL((decode_select_group_kernel<DS, BF, SH, MANY>), grid, block, lds, stream, q, cos_b, \
                        sin_b, codebook, q_rot, lut, lut_scale, d.batch, d.n_q_heads, d.n_kv_heads, NG, n_lut,   \
                        make_grid_map(split, groups, NG, d.n_kv_heads), split, keys, weights, mode, codes, n_new, pos0, \
                        d.ctx_stride, ap.sweeps, ap.folded, seq_lens, topk_idx, topk_count, topk_score, d.ctx_len, \
                        top_k, window, n_sink);                                                                  \
   } while (0)
-#define A2ATS_LAUNCH_GRP2(DS, BF, SLOT)                   \
-  do {                                                    \
-    if (shared) A2ATS_LAUNCH_GRP(DS, BF, true, SLOT + 4); \
-    else A2ATS_LAUNCH_GRP(DS, BF, false, SLOT);           \
+#define A2ATS_LAUNCH_GRP2(DS, BF, MANY, SLOT)                   \
+  do {                                                          \
+    if (shared) A2ATS_LAUNCH_GRP(DS, BF, true, MANY, SLOT + 6); \
+    else A2ATS_LAUNCH_GRP(DS, BF, false, MANY, SLOT);           \
   } while (0)
+  const int heads = shared ? 1 : std::min(G, kHeadsPerGroup);
   if (d.sub_dim == 8) {
-    if (q_dtype == A2ATS_BF16) A2ATS_LAUNCH_GRP2(8, true, 0); else A2ATS_LAUNCH_GRP2(8, false, 1);
+    if (q_dtype == A2ATS_BF16) A2ATS_LAUNCH_GRP2(8, true, false, 0); else A2ATS_LAUNCH_GRP2(8, false, false, 1);
+  } else if (!group_many(d.n_sub, (long)d.ctx_len - window - n_sink, top_k, (heads + split - 1) / split)) {
+    if (q_dtype == A2ATS_BF16) A2ATS_LAUNCH_GRP2(4, true, false, 2); else A2ATS_LAUNCH_GRP2(4, false, false, 3);
   } else {
-    if (q_dtype == A2ATS_BF16) A2ATS_LAUNCH_GRP2(4, true, 2); else A2ATS_LAUNCH_GRP2(4, false, 3);
+    if (q_dtype == A2ATS_BF16) A2ATS_LAUNCH_GRP2(4, true, true, 4); else A2ATS_LAUNCH_GRP2(4, false, true, 5);
   }
 #undef A2ATS_LAUNCH_GRP2
 #undef A2ATS_LAUNCH_GRP

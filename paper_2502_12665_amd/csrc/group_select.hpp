@@ -31,6 +31,8 @@
 // sequences of 16384 132 -> 173, 64 of them 508 -> 363; 50 different rows 30 -> 31, 78 -> 104, 277 -> 170; 8 different
 // rows 58 -> 55, 66 -> 147, 238 -> 302.
 #pragma once
+#include <algorithm>
+#include <cmath>
 #include "common.hpp"
 #include "coarse_score.hpp"
 #include "exact_select.hpp"
@@ -73,9 +75,18 @@ __device__ __forceinline__ uint32_t group_part(int part, int split, int heads, i
   return ((1u << per) - 1u) << (part * per) & ((1u << n_real) - 1u);
 }
 
+// Whether a workgroup's bands are expected to be many rows (band_winners), which is a kernel of its own.  A band is as wide for all K, so
+// its rows go with the density of scores at the K-th, K sqrt(2 ln(candidates / K)) for scores that are about normal; 36 units of M = 16
+// never have as many.  Tables and selection, one form -> the other, M = 32, 47 sequences of 8 groups of four heads, K 3 %: 2654 tokens 72.6 -> 75.9 us, 6500
+// 91.2 -> 94.2, 8228 98.7 -> 97.9, 16384 135 -> 124; K 10 %: 2654 81.0 -> 83.6, 4436 95.0 -> 90.6; 20 sequences of 8 groups of four and
+// three, K 3 %: 6500 38.8 -> 40.5, 8228 42.2 -> 42.3, 12000 50.6 -> 47.2.
+inline bool group_many(int n_sub, long ncand, int top_k, int heads) {   // heads: of a workgroup
+  return n_sub == 32 && top_k > 0 && heads * top_k * std::sqrt(2.0 * std::log(std::max(2.0, (double)ncand / top_k))) > 2440.0;
+}
+
 // Called by all kGroupThreads threads of a workgroup for the heads `mine` of its group.  dyn_lds: kGroupLdsBytes.  TABLE_IN_LDS: the caller has
 // put the group's coarse table at its start (a barrier follows here), otherwise it is copied from `lut`.
-template <int M, bool TABLE_IN_LDS>
+template <int M, bool TABLE_IN_LDS, bool MANY>
 __device__ __forceinline__ void group_select_body(
     int b, int kv, int g4, int prob, uint32_t mine, const uint8_t* __restrict__ codes, const CodePages& pg,
     const int32_t* __restrict__ lut, const float* __restrict__ lut_scale, const int32_t* __restrict__ seq_lens,
@@ -211,7 +222,7 @@ __device__ __forceinline__ void group_select_body(
   // --- the band, and the winners in ascending position
   const Band band = {&L.band[0][0], &L.won[0][0], kGroupMaxCand / 64, L.n_band, L.n_sure, L.from, 32u + 2 * M,
                      (int32_t*)tbl, L.hist, L.wave_tot};
-  const uint32_t redo = band_winners<M, M == 32>(band, mine, head0, seq_codes, lo, sr.kk, lut, lay, [](uint32_t) {});
+  const uint32_t redo = band_winners<M, MANY>(band, mine, head0, seq_codes, lo, sr.kk, lut, lay, [](uint32_t) {});
   write_winners<kGroupMaxCand / 64 / 256>(band, mine & ~redo, head0, lo, sr.ncand, sr.kk, top_k, topk_idx);
   // --- heads with more band rows than the list holds (many equal scores): the exact route.  The K-th coarse score is in the
   // bin, hence the K-th score is at least the bin's lower edge, and its own row's is below the upper edge.

@@ -15,7 +15,7 @@
 //  winners in ascending position, equal scores going to the lower position.
 //
 //  fast route (the other long contexts): the code matrix is streamed from HBM once, against a 16-bit
-//  coarse copy of the tables, and only the survivors are scored exactly.
+//  coarse copy of the tables, and of the survivors only those near the K-th score are scored exactly.
 //    1. sample_threshold_kernel scores a sample of each sequence (about 1/8 of it, taken in
 //       128-byte runs spread evenly over the candidates) with the coarse tables and derives, per
 //       head, a coarse threshold below the K-th score with a 5-sigma margin (distribution-free
@@ -97,11 +97,9 @@ TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink, 
   long ncand = (long)d.ctx_len - window - n_sink;
   if (ncand < 0) ncand = 0;
   p.cap = kFinalCrowd;
-  // The streaming route: the selection is at most a quarter of at least 16384 candidates.  Up to 4096
-  // winners leave the final kernel room: its list holds 8192 survivors, and the sampled threshold lets
-  // 1.3 to 1.65 K through there.  Above 2048 the route is called wide and reports no survivor statistics.
-  // (2 sequences of 98301 tokens, 32 heads, K 2949: the step takes 65 us; 347 us on the exact route, which
-  // streams and scores a head's rows four times on one CU.)
+  // The streaming route: the selection is at most a quarter of at least 16384 candidates, and at most the 4096 that a call may
+  // ask for.  Above 2048 the route is called wide and reports no survivor statistics.  (2 sequences of 98301 tokens, 32 heads, K
+  // 2949: the step takes 59.5 us; 347 on the exact route, which streams and scores a head's rows four times on one CU.)
   const bool streams = !single_codebook(d) && ncand >= 16384 && top_k >= 1 && top_k <= 4096 && 4L * top_k <= ncand;
   p.fast = streams && top_k <= 2048;
   p.wide = streams && top_k > 2048;
@@ -258,7 +256,7 @@ __global__ __launch_bounds__(kExactThreads) void select_exact_kernel(
 // ------------------------------------------------------------------------------------------
 // Short contexts: one workgroup per problem
 // ------------------------------------------------------------------------------------------
-template <int M>
+template <int M, bool MANY>
 __global__ __launch_bounds__(kGroupThreads) void group_select_kernel(
     const uint8_t* __restrict__ codes, const int32_t* __restrict__ lut, const float* __restrict__ lut_scale,
     const int32_t* __restrict__ seq_lens, int32_t* __restrict__ topk_idx, int32_t* __restrict__ topk_count,
@@ -270,7 +268,7 @@ __global__ __launch_bounds__(kGroupThreads) void group_select_kernel(
   split_problem(prob, gm, b, kv, g4);
   const int G = Hq / Hkv;
   const uint32_t mine = group_part(part, split, min(G, kHeadsPerGroup), min(kHeadsPerGroup, G - g4 * kHeadsPerGroup));
-  group_select_body<M, false>(b, kv, g4, prob, mine, codes, pg, lut, lut_scale, seq_lens, topk_idx, topk_count, topk_score, B,
+  group_select_body<M, false, MANY>(b, kv, g4, prob, mine, codes, pg, lut, lut_scale, seq_lens, topk_idx, topk_count, topk_score, B,
                               Hq, Hkv, ctx_len, ctx_stride, top_k, window, n_sink, dyn_lds);
 }
 
@@ -542,7 +540,7 @@ __device__ __forceinline__ void stream_select_body(
   codes, lut, seq_lens, thr, counts, lists, gm, pg, B, Hq, Hkv, G, NG, P0, n_chunks,              \
       rows_per_chunk, list_cap, ctx_len, ctx_stride, top_k, window, n_sink
 
-// 64 KB of LDS per workgroup (72 KB with a staged page slice).  M = 16: 128 VGPRs -> 4 waves per
+// 80 KB of LDS per workgroup, the table and what StreamLds has, so two fit a CU.  M = 16: 128 VGPRs -> 4 waves per
 // SIMD (two workgroups per CU).
 __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void stream_select_kernel16(A2ATS_STREAM_ARGS) { stream_select_body<16, false, false>(A2ATS_STREAM_PASS); }
@@ -904,7 +902,7 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
   const size_t coarse_bytes = (size_t)kCoarseLdsBytes;
   const size_t lut1_bytes = kExactLdsBytes;
   hipError_t err;
-  static LdsSlot s_dense[16], s_exact[16], s_sample[16], s_stream[16], s_stream_r[16], s_stream_p[16], s_final[16], s_group[16],
+  static LdsSlot s_dense[16], s_exact[16], s_sample[16], s_stream[16], s_stream_r[16], s_stream_p[16], s_final[16], s_group[16], s_group_many[16],
       s_list[16];
   if (heads == 0) return hipSuccess;
 
@@ -919,9 +917,11 @@ static hipError_t launch_score_topk_m(const a2ats_dims& d, const TopkPlan& plan,
 
   const bool streams = plan.fast || (plan.wide && ws);
   if (!streams && takes_group_route(d, window, n_sink)) {
-    if ((err = allow_dynamic_lds(group_select_kernel<M>, kGroupLdsBytes, s_group, true)) != hipSuccess) return err;
-    const int split = group_split(problems, std::min(Hq / Hkv, kHeadsPerGroup), 0);
-    hipLaunchKernelGGL((group_select_kernel<M>), dim3(problems * split), dim3(kGroupThreads), kGroupLdsBytes, stream, codes,
+    const int heads = std::min(Hq / Hkv, kHeadsPerGroup), split = group_split(problems, heads, 0);
+    const bool many = group_many(M, (long)d.ctx_len - window - n_sink, top_k, (heads + split - 1) / split);
+    auto kernel = many ? group_select_kernel<M, M == 32> : group_select_kernel<M, false>;
+    if ((err = allow_dynamic_lds(kernel, kGroupLdsBytes, many ? s_group_many : s_group, true)) != hipSuccess) return err;
+    hipLaunchKernelGGL(kernel, dim3(problems * split), dim3(kGroupThreads), kGroupLdsBytes, stream, codes,
                        lut, lut_scale, seq_lens, topk_idx, topk_count, topk_score, make_grid_map(split, problems, NG, Hkv),
                        pg, B, Hq, Hkv, d.ctx_len, d.ctx_stride, top_k, window, n_sink, split);
     return hipGetLastError();

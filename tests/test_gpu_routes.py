@@ -956,3 +956,28 @@ def test_selection_of_lengths_on_both_sides_of_the_line_for_lists(groups, M, can
             B.score_topk(st.dims, xd["codes"], st.lut, st.lut_scale, K, 64, 4, sl.cuda(), *out)
     for a, b in zip((st.topk_idx, st.topk_count, st.topk_score.view(torch.int32)), _full_sort(wl, xd, st, sl.tolist())):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("call", ["score", "select"])
+@pytest.mark.parametrize("Bn,G,N,K,rows", [(72, 4, 8300, 200, None), (72, 4, 8300, 260, None), (72, 7, 4500, 443, None), (72, 7, 1500, 40, None),
+                                           (270, 1, 8300, 800, None), (270, 1, 8300, 1200, None), (72, 4, 8300, 200, 9),
+                                           (72, 4, 8300, 260, 9), (72, 4, 16384 + 68, 3000, None)])
+def test_short_contexts_of_32_subspaces_by_either_kernel(Bn, G, N, K, rows, call):
+    """A workgroup per group, M = 32: the kernel for bands of few rows and that for many, also where all scores are among nine,
+    against a full sort."""
+    wl = synth.Workload("bands", Bn, G, 1, 128, 32, N, K, 64, n_sink=4, seed=N + K)
+    xd = synth.make_decode_inputs(wl, device="cuda", with_kv=False)
+    if rows:
+        xd["codes"][:] = xd["codes"][:, :, torch.randint(0, rows, (N,), device="cuda")]
+    st = B.DecodeState(H.dims_of(wl), K, 64, 4, xd["q"].dtype, xd["inv_freq"], wl.wrope_b)
+    st.topk_idx.fill_(-7), st.topk_count.fill_(-7), st.topk_score.fill_(-7.0)
+    out = (st.topk_idx, st.topk_count, st.topk_score)
+    if call == "select":
+        key = torch.randn(Bn, 1, 1, 128, device="cuda")
+        B.decode_select(st.dims, key, 1, N - 1, xd["codebook"], None, B.W_NONE, xd["codes"], xd["q"], st.cos_b, st.sin_b, st.q_rot,
+                        st.lut, st.lut_scale, K, 64, 4, None, *out, st.ws)
+    else:
+        B.build_lut(st.dims, xd["q"], st.cos_b, st.sin_b, xd["codebook"], st.q_rot, st.lut, st.lut_scale)
+        B.score_topk(st.dims, xd["codes"], st.lut, st.lut_scale, K, 64, 4, None, *out, None, st.ws)
+    for a, b in zip((out[0], out[1], out[2].view(torch.int32)), _full_sort(wl, xd, st, None)):
+        assert torch.equal(a, b)

@@ -127,8 +127,8 @@ int a2ats_rope_tables(int32_t head_dim, const double* inv_freq, int32_t b, int32
  * A2ATS_W_NONE needs none.  n_new == 0 is a no-op.
  * Single codebook: H is the full D x D matrix (A2ATS_W_BLOCK: weights [dev, f32 Hkv*D*D], the
  * lower triangle is read) and the argmin is over 4096 codewords of all 128 dimensions:
- * codes [dev, u16 B*Hkv*ctx_stride].  With the Cholesky factor of section 4.2 (H = L L^T,
- * c^z = c L, w = c H, ||c^z||^2 = c.w) the scores 1/2||c^z||^2 - k.w are formed on the matrix cores from f16
+ * codes [dev, u16 B*Hkv*ctx_stride].  With w = c H and ||c^z||^2 = c.w (section 4.2: H = L L^T,
+ * c^z = c L; no factor is formed) the scores 1/2||c^z||^2 - k.w are formed on the matrix cores from f16
  * roundings of both operands, or from roundings to 8 bits (short calls, and where a sample of a KV head's
  * keys shows that these decide nearly all of them), with a centre of the codewords subtracted from keys and codewords
  * (which leaves the distances as they are) and the dimensions of k and w balanced by powers of two;
@@ -147,8 +147,8 @@ int a2ats_encode_keys(const a2ats_dims* dims, const float* keys, int32_t n_new, 
                       uint8_t* codes, void* ws, size_t ws_bytes, void* stream);
 
 /*
- * The part of a2ats_encode_keys that depends on the codebook and the weights only (paper section
- * 4.2: the Cholesky factor L of H and the transformed codewords c^z = c L), for callers that
+ * The part of a2ats_encode_keys that depends on the codebook and the weights only (the codewords
+ * weighed by H of paper section 4.2, w = c H and 1/2 c.w, in their forms), for callers that
  * encode against the same codebook and weights many times (one key per decode step).  Fills the
  * codeword part of `ws`; a later a2ats_encode_keys with the same dims, codebook, weights, mode
  * and workspace may then pass weight_mode | A2ATS_W_PREPARED to skip that part (it must not have

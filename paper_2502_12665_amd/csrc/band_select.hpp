@@ -54,8 +54,10 @@ __device__ __forceinline__ int32_t exact_score_of(const int32_t* __restrict__ t,
 
 // Of the distinct values, `bits` wide, that the threads of a workgroup of NT hold: one that exactly `need` of them reach.  each(f)
 // calls f(in, value) for a thread's own (where `in`), the same every time; there are at least `need`.  In LDS: hist, kHistBins words;
-// wave_tot, one a wave; res, two.  By radix: a level takes 11 bits, 1.5 us; and by counting where 64 rows are left.
-template <int NT, typename Each>
+// wave_tot, one a wave; res, two.  By radix: a level takes 11 bits, 1.5 us.
+// TAIL: by counting where 64 rows are left, instead of further levels.  (In the list route its registers end up in memory, and heads that are done
+// again take 508 -> 658 us.)
+template <int NT, bool TAIL, typename Each>
 __device__ __forceinline__ uint64_t reached_by(uint32_t need, int bits, Each each, uint32_t* hist, uint32_t* wave_tot, uint32_t* res) {
   uint64_t prefix = 0;
 #pragma unroll 1
@@ -74,7 +76,7 @@ __device__ __forceinline__ uint64_t reached_by(uint32_t need, int bits, Each eac
     prefix |= (uint64_t)bin << shift;
     if (m == need) return prefix;
     above = shift;
-    if (m > 64u) continue;
+    if (!TAIL || m > 64u) continue;
     // a few rows are left: by counting, in one wave
     __syncthreads();
     if (threadIdx.x == 0) wave_tot[0] = 0;

@@ -13,9 +13,9 @@
 // that overflows tells a higher threshold and is made again by another pass.  A head that overflows that too is done by the exact
 // route, one after the other in their workgroup.  Tables and selection, us, by the streaming route of before (whose
 // final kernel ranked up to 8192 rows, a workgroup a head) -> with the exact route for all of these -> now, 32 query and 8 KV heads, K 3 %:
-// 16 sequences of 32768, M = 16, 1100 equal scores about the K-th of one head in four 67 -> 287 -> 74, 4000 87 -> 256 -> 95, rows of 100 kinds
-// 82 -> 144 -> 106, of 20 75 -> 491 -> 113; 32 of 60000 147 -> 509 -> 112, 180 -> 666 -> 344 (8 of 1024 heads by the exact route),
-// 194 -> 751 -> 138, 172 -> 872 -> 509 (52 of them); 32 of 32768, M = 32 165 -> 435 -> 126, 206 -> 404 -> 164, 194 -> 451 -> 167, 185 -> 730 -> 186.
+// 16 sequences of 32768, M = 16, 1100 equal scores about the K-th of one head in four 67 -> 287 -> 73, 4000 87 -> 256 -> 94, rows of 100 kinds
+// 82 -> 144 -> 106, of 20 75 -> 491 -> 112; 32 of 60000 147 -> 509 -> 111, 180 -> 666 -> 342 (8 of 1024 heads by the exact route),
+// 194 -> 751 -> 138, 172 -> 872 -> 506 (52 of them); 32 of 32768, M = 32 165 -> 435 -> 126, 206 -> 404 -> 166, 194 -> 451 -> 163, 185 -> 730 -> 186.
 //
 // Against the streaming route this saves the survivors' way through memory (20 or 36 bytes written and read back by every head),
 // the exact scores of 1.4 K rows a head, and the rounds of one workgroup per head: 256 groups of 65536 tokens, M = 32, K 2048
@@ -148,7 +148,7 @@ __device__ __forceinline__ void crowded_band(int r, ListLds& L, ListEnd& E, cons
     const uint32_t key = score_key(s[k]);
     return (uint64_t)(key > key0 ? min(key - key0, range) : 0u) << kPosBits | (0xffffu - (e[k] & 0xffffu));
   };
-  const uint64_t last = reached_by<NT>(
+  const uint64_t last = reached_by<NT, false>(
       (uint32_t)kk - L.n_sure[r], kPosBits + 32 - (int)__clz(range),
       [&](auto f) {
 #pragma unroll

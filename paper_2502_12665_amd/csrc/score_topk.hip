@@ -567,10 +567,10 @@ void stream_select_kernel32p(A2ATS_STREAM_ARGS) { stream_select_body<32, true, t
 // 2048, 128 heads), 17.0 -> 12.2 (2 of 98301, K 2949).
 //
 // A band of more than 1024 rows, and more than 128 equal scores in the bin of the K-th, are ranked by a radix select over (score, position) from
-// registers (by the exact route: ten times slower; by counting: 66 us instead of 48 for 800 equal scores).  Tables and selection,
+// registers (by the exact route: ten times slower; by counting: 65 us instead of 51 for 800 equal scores).  Tables and selection,
 // us, that exact scores of all survivors took -> now, 1100, 3000, 6000 equal scores about the K-th of one head in four: 4 sequences of 131072, M =
-// 16, 49.6 -> 51.9, 55.1 -> 56.7, 428 -> 69; 2 of 98301 42.7 -> 44.2, 47.4 -> 47.3, 307 -> 58; 2 of 65536, M = 32, 54.6 -> 57.6, 59.5 -> 62.2,
-// 330 -> 77.  M = 32 has such bands without equal scores: one selection per KV head, 16 of 122753, K 4096, 57.5 -> 59.4 (the exact route 608).
+// 16, 49.6 -> 50.4, 55.1 -> 55.3, 428 -> 67; 2 of 98301 42.7 -> 42.8, 47.4 -> 46.0, 307 -> 56; 2 of 65536, M = 32, 54.6 -> 55.8, 59.5 -> 60.3,
+// 330 -> 75.  M = 32 has such bands without equal scores: one selection per KV head, 16 of 122753, K 4096, 58 -> 59 (the exact route 608).
 constexpr int kCounted = 128;         // rows in the bin of the K-th that are ranked by counting
 constexpr int kFinalBin = 2;          // a bin of the first histogram is 4 coarse units, from the threshold up; of a second, where
 constexpr int kFinalWide = 5;         // the K-th is above those, 32, which is the whole range
@@ -762,7 +762,8 @@ __global__ __launch_bounds__(kExactThreads) void final_select_kernel(
   auto relative = [&](uint32_t key, uint32_t j) {
     return (uint64_t)(key > key0 ? min(key - key0, range) : 0u) << kPosBits | ((1u << kPosBits) - 1u - j);
   };
-  if (__builtin_expect(n_band <= (uint32_t)kBandCap, 1)) {
+  bool crowded = n_band > (uint32_t)kBandCap;   // (uniform)
+  if (!crowded) {
     // --- the band: exact keys, then every row counts those before it in (score, position) order; of many rows only those in the
     // bin of the K-th, of 2048 over the band's range (M = 32, 1000 rows: see band_select.hpp)
     const bool few = n_band <= 256u;
@@ -779,7 +780,8 @@ __global__ __launch_bounds__(kExactThreads) void final_select_kernel(
     }
     __syncthreads();
     const int kth_bin = few ? 0 : wave_find_bin(L.hist, 0, need, lane, ~0u);
-    if (few || L.hist[kth_bin] <= (uint32_t)kCounted) {   // (uniform)
+    crowded = !few && L.hist[kth_bin] > (uint32_t)kCounted;
+    if (!crowded) {
       for (uint32_t i = tid >> 3; i < n_band; i += NT / 8) {   // eight lanes a row
         const uint64_t own = L.band[i];
         const int at = few ? 0 : (int)bin_of((uint32_t)(own >> 32));
@@ -795,16 +797,10 @@ __global__ __launch_bounds__(kExactThreads) void final_select_kernel(
           atomicOr((uint32_t*)L.won + (j >> 5), 1u << (j & 31));
         }
       }
-    } else {
-      const uint64_t own = (uint32_t)tid < n_band ? L.band[tid] : 0ull;
-      const uint32_t j = ~(uint32_t)own;
-      const uint64_t row = relative((uint32_t)(own >> 32), j);
-      const uint64_t last = reached_by<NT>(need, row_bits, [&](auto f) { f((uint32_t)tid < n_band, row); }, L.hist, L.wave_tot,
-                                           (uint32_t*)L.band);
-      if ((uint32_t)tid < n_band && row >= last) atomicOr((uint32_t*)L.won + (j >> 5), 1u << (j & 31));
     }
-  } else {
-    // --- more rows than are ranked so (M = 32, thousands of winners; or equal scores)
+  }
+  if (__builtin_expect(crowded, 0)) {
+    // --- more rows than are ranked so (M = 32, thousands of winners; or equal scores): in registers
     constexpr int kTogether = 4;
     uint64_t row[kFinalCrowd / NT];
 #pragma unroll
@@ -824,7 +820,7 @@ __global__ __launch_bounds__(kExactThreads) void final_select_kernel(
         for (int k = 0; k < kTogether; ++k) row[k0 + k] = relative(score_key(exact_at(j[k])), j[k]);
       }
     }
-    const uint64_t last = reached_by<NT>(
+    const uint64_t last = reached_by<NT, true>(
         need, row_bits,
         [&](auto f) {
 #pragma unroll

@@ -137,7 +137,6 @@ TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink, 
     if (chunks > max_chunks) chunks = max_chunks;
     if (chunks < 1) chunks = 1;
     if (chunks > 64) chunks = 64;
-    if (chunks < (ncand + 65535) / 65536) chunks = (ncand + 65535) / 65536;   // (positions in a chunk are 16 bits)
     // Survivors.  The sampling rule (rank r with r - 5 sqrt(r) >= K S / N, plus one per part) lets about
     // r N / S rows per head through -- for small K much more than K -- and a row survives if any of
     // the (up to) four heads wants it.  row_cap is twice that share of a wave's rows plus 16
@@ -148,21 +147,30 @@ TopkPlan make_topk_plan(const a2ats_dims& d, int top_k, int window, int n_sink, 
     const double xr = 0.5 * (kSigma + std::sqrt(kSigma * kSigma + 4.0 * r0));
     const double survivors = (xr * xr + 2.0 * p.P0) / (double)s_tot * (double)ncand * 1.25;
     const double keep = std::min(1.0, 4.0 * survivors / (double)ncand);
-    long rpc = (ncand + chunks - 1) / chunks;
-    rpc = (rpc + kStreamThreads - 1) / kStreamThreads * kStreamThreads;
-    const long rows_per_wave = rpc / kStreamWaves;   // a multiple of 64
-    const double mu = rows_per_wave * keep;
-    long cap_rows = (long)(mu * 2.0 + 16.0 * std::sqrt(mu)) + 64;
-    cap_rows = (cap_rows + 31) / 32 * 32;
-    if (cap_rows > rows_per_wave) cap_rows = rows_per_wave;
+    auto rows_of = [&](long n) { return ((ncand + n - 1) / n + kStreamThreads - 1) / kStreamThreads * kStreamThreads; };
+    auto cap_of = [&](long rows) {
+      const long rows_per_wave = rows / kStreamWaves;   // a multiple of 64
+      const double mu = rows_per_wave * keep;
+      const long cap = (long)(mu * 2.0 + 16.0 * std::sqrt(mu)) + 64;
+      return std::min((cap + 31) / 32 * 32, rows_per_wave);
+    };
+    const size_t entry_bytes = 4 + d.n_sub;   // header + code bytes
+    long rpc = rows_of(chunks), cap_rows = cap_of(rpc);
+    if (chunks < (ncand + 65535) / 65536) {   // (positions in a chunk are 16 bits)
+      // More chunks of fewer rows would be more bytes by their deviations and lengths: the lists get what the chunks that the CUs
+      // would have been filled with had, so that a workspace sized for those still serves.
+      const long bytes = (ncand + rpc - 1) / rpc * (cap_rows * (long)entry_bytes + 32);
+      rpc = rows_of((ncand + 65535) / 65536);
+      const long most = (bytes / ((ncand + rpc - 1) / rpc) - 32) / (long)entry_bytes / 32 * 32;
+      cap_rows = std::min(cap_of(rpc), std::max(most, 64L));
+    }
     p.chunks = (int)((ncand + rpc - 1) / rpc);
     p.rows_per_chunk = (int)rpc;
     p.subs = 1;                               // (one segment per wave)
-    p.sub_rows = (int)rows_per_wave;
+    p.sub_rows = (int)(rpc / kStreamWaves);
     p.row_cap = (int)cap_rows;                // a multiple of 32
     const size_t heads = (size_t)d.batch * d.n_q_heads;
     const size_t segs = (size_t)problems * p.chunks * kStreamWaves;
-    const size_t entry_bytes = 4 + d.n_sub;   // header + code bytes
     list_route(d, p, ncand, top_k, ragged);
     p.off_thr = 0;
     p.off_route = (p.off_thr + heads * p.P0 * sizeof(int32_t) + 255) / 256 * 256;

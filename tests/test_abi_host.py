@@ -128,6 +128,23 @@ def test_score_topk_plan_invariants(binding):
     assert n_fast > 500
 
 
+@pytest.mark.parametrize("Bn,Hq,Hkv,M,N,K,w,before", [
+    (16, 32, 8, 16, 300001, 2048, 16, 141692928), (16, 32, 8, 16, 500000, 64, 16, 73535488),
+    (32, 28, 4, 32, 1 << 20, 64, 256, 118128128), (32, 28, 4, 32, 300001, 64, 16, 80379392),
+    (64, 28, 4, 32, 131072, 2048, 256, 656051200), (16, 8, 8, 16, 1 << 20, 64, 16, 128582656),
+    (128, 8, 8, 16, 1 << 20, 1024, 256, 550801408), (256, 28, 4, 32, 131072, 4096, 16, 4473892864)])
+def test_workspace_of_chunks_of_any_length_still_serves(binding, Bn, Hq, Hkv, M, N, K, w, before):
+    """Chunks hold at most 65536 rows, so long contexts of many problems have more of them than the CUs ask for.  `before` is what
+    the workspace of these calls was while a chunk could be of any length; it is still enough."""
+    d = binding.make_dims(Bn, Hq, Hkv, 128, M, N)
+    assert binding.workspace_bytes(d, binding.OP_SCORE_TOPK, K, w) <= before
+    for n_sink in (0, 4, 64):
+        p = binding.score_topk_plan(d, K, w, n_sink)
+        if p["fast"]:
+            assert p["workspace_bytes_div_256"] * 256 <= before and p["rows_per_chunk"] <= 65536
+            assert p["segment_capacity"] * 8 > 1.5 * p["rows_per_chunk"] * K / (N - w - n_sink)   # of one head, where the sample lets 1.5 K through
+
+
 def test_score_topk_workspace_covers_sink_counts(binding):
     """a2ats_workspace_bytes(OP_SCORE_TOPK) promises to cover every call with up to 64 sinks: over a grid
     of shapes it is at least what the plan of each such call asks for, and a call with one byte less

@@ -29,9 +29,11 @@ struct HeadShare {
   int head, threads, at;
 };
 __device__ __forceinline__ HeadShare head_share(uint32_t heads) {
-  constexpr int kWaves = kExactThreads / 64;
-  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), n = __popc(heads), k = wv * n / kWaves;
-  const int w0 = (kWaves * k + n - 1) / n, w1 = (kWaves * (k + 1) + n - 1) / n;
+  static_assert(kExactThreads == 16 * 64 && kHeadsPerGroup == 4, "");
+  // 16 waves each, 8, 6 + 5 + 5, or 4 (no division: two of them took 0.5 us)
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), n = __popc(heads), k = wv * n >> 4;
+  auto first = [&](int i) { return n == 3 ? 5 * i + (i > 0 ? 1 : 0) : (16 >> (n >> 1)) * i; };
+  const int w0 = first(k), w1 = first(k + 1);
   for (int i = 0; i < k; ++i) heads &= heads - 1;
   return {__ffs((int)heads) - 1, 64 * (w1 - w0), (int)threadIdx.x - 64 * w0};
 }
@@ -273,7 +275,13 @@ __device__ __forceinline__ void write_winners(const Band& B, uint32_t mine, int 
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   // (one word a thread of the four waves of a head's number is as fast as more waves could be)
   const HeadShare own = PER > 1 ? head_share(mine) : HeadShare{wv >> 2, 256, tid & 255};
-  const int n_words = (mine >> own.head) & 1u ? (ncand + 63) / 64 : 0, per = PER > 1 ? (n_words + own.threads - 1) / own.threads : 1;
+  auto words_each = [](int words, int threads) {   // their quotient, rounded up, which is 1 to PER
+    int n = 1;
+#pragma unroll
+    for (int w = 1; w < PER; ++w) n += words > w * threads ? 1 : 0;
+    return n;
+  };
+  const int n_words = (mine >> own.head) & 1u ? (ncand + 63) / 64 : 0, per = words_each(n_words, own.threads);
   const int w0 = own.at * per;
   const uint64_t* won = B.won + (size_t)own.head * B.won_words;
   uint64_t word[PER];

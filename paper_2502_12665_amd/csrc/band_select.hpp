@@ -30,7 +30,7 @@ struct HeadShare {
 };
 __device__ __forceinline__ HeadShare head_share(uint32_t heads) {
   static_assert(kExactThreads == 16 * 64 && kHeadsPerGroup == 4, "");
-  // 16 waves each, 8, 6 + 5 + 5, or 4 (no division: two of them took 0.5 us)
+  // 16 waves each, 8, 6 + 5 + 5, or 4 (no division: two of them took 0.5 us; the loop below unrolled costs M = 16 1 us of 60, in registers)
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), n = __popc(heads), k = wv * n >> 4;
   auto first = [&](int i) { return n == 3 ? 5 * i + (i > 0 ? 1 : 0) : (16 >> (n >> 1)) * i; };
   const int w0 = first(k), w1 = first(k + 1);
@@ -57,8 +57,7 @@ __device__ __forceinline__ int32_t exact_score_of(const int32_t* __restrict__ t,
 // Of the distinct values, `bits` wide, that the threads of a workgroup of NT hold: one that exactly `need` of them reach.  each(f)
 // calls f(in, value) for a thread's own (where `in`), the same every time; there are at least `need`.  In LDS: hist, kHistBins words;
 // wave_tot, one a wave; res, two.  By radix: a level takes 11 bits, 1.5 us.
-// TAIL: by counting where 64 rows are left, instead of further levels.  (In the list route its registers end up in memory, and heads that are done
-// again take 508 -> 658 us.)
+// TAIL: by counting where 64 rows are left, instead of further levels.  (Not in the list route, where it costs registers.)
 template <int NT, bool TAIL, typename Each>
 __device__ __forceinline__ uint64_t reached_by(uint32_t need, int bits, Each each, uint32_t* hist, uint32_t* wave_tot, uint32_t* res) {
   uint64_t prefix = 0;

@@ -14,8 +14,8 @@
 // route, one after the other in their workgroup.  Tables and selection, us, by the streaming route of before (whose
 // final kernel ranked up to 8192 rows, a workgroup a head) -> with the exact route for all of these -> now, 32 query and 8 KV heads, K 3 %:
 // 16 sequences of 32768, M = 16, 1100 equal scores about the K-th of one head in four 67 -> 287 -> 73, 4000 87 -> 256 -> 94, rows of 100 kinds
-// 82 -> 144 -> 106, of 20 75 -> 491 -> 112; 32 of 60000 147 -> 509 -> 111, 180 -> 666 -> 342 (8 of 1024 heads by the exact route),
-// 194 -> 751 -> 138, 172 -> 872 -> 506 (52 of them); 32 of 32768, M = 32 165 -> 435 -> 126, 206 -> 404 -> 166, 194 -> 451 -> 163, 185 -> 730 -> 186.
+// 82 -> 144 -> 106, of 20 75 -> 491 -> 112; 32 of 60000 147 -> 509 -> 111, 180 -> 666 -> 409 (8 of 1024 heads by the exact route),
+// 194 -> 751 -> 138, 172 -> 872 -> 662 (52 of them); 32 of 32768, M = 32 165 -> 435 -> 126, 206 -> 404 -> 166, 194 -> 451 -> 163, 185 -> 730 -> 186.
 //
 // Against the streaming route this saves the survivors' way through memory (20 or 36 bytes written and read back by every head),
 // the exact scores of 1.4 K rows a head, and the rounds of one workgroup per head: 256 groups of 65536 tokens, M = 32, K 2048
@@ -213,7 +213,7 @@ __device__ __forceinline__ void list_select_body(
     T[r] = r < n_real ? (uint32_t)__builtin_amdgcn_readfirstlane(L.thr[r]) : 0xffffu;
 
   // --- one pass over the rows, a run of them for each wave; and another one for lists that overflow
-  auto pass = [&]() {
+  auto pass = [&](const uint32_t (&T)[kHeadsPerGroup], int lane, SeqCodes seq_codes, int lo, int hi) {
     const int run = (sr.ncand + 64 * kListWaves - 1) / (64 * kListWaves) * 64;
     const int wbegin = lo + wv * run, wend = min(hi, wbegin + run);
     LaneSwizzle<M> sw;
@@ -291,7 +291,7 @@ __device__ __forceinline__ void list_select_body(
     }
     __syncthreads();
   };
-  pass();
+  pass(T, lane, seq_codes, lo, hi);
   uint32_t over = 0;
 #pragma unroll
   for (int r = 0; r < kHeadsPerGroup; ++r)
@@ -300,12 +300,15 @@ __device__ __forceinline__ void list_select_body(
 #pragma unroll 1
     for (int r = 0; r < kHeadsPerGroup; ++r)
       if ((over >> r) & 1u) raise_threshold(r, (uint32_t)sr.kk, L, lane, wv);
+    uint32_t higher[kHeadsPerGroup];   // (not in T: the first pass is slower if that changes later)
 #pragma unroll
     for (int r = 0; r < kHeadsPerGroup; ++r)
-      T[r] = (over >> r) & 1u ? (uint32_t)__builtin_amdgcn_readfirstlane(L.thr[r]) : 0xffffu;
-    pass();
-#pragma unroll
-    for (int r = 0; r < kHeadsPerGroup; ++r) T[r] = (uint32_t)__builtin_amdgcn_readfirstlane(L.thr[r]);
+      higher[r] = (over >> r) & 1u ? (uint32_t)__builtin_amdgcn_readfirstlane(L.thr[r]) : 0xffffu;
+    // (else what the second pass needs is kept through the first, M = 32 1 us of 140)
+    int lane2 = (int)threadIdx.x & 63, lo2 = lo, hi2 = hi;
+    SeqCodes codes2 = seq_codes;
+    asm volatile("" : "+v"(lane2), "+s"(lo2), "+s"(hi2), "+s"(codes2.base));
+    pass(higher, lane2, codes2, lo2, hi2);
   }
 
   // --- the bin of the K-th coarse score; of a head where it is above all of them, again with wide bins
@@ -343,7 +346,7 @@ __device__ __forceinline__ void list_select_body(
   for (int r = 0; r < kHeadsPerGroup; ++r) {
     const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.n[r]);
     const int bin = bin_of[r];
-    const uint32_t why = r >= n_real ? 0u : (n > (uint32_t)kListCap ? 2u : (bin < 0 ? 1u : (T[r] != 0u && (bin << bin_log(r)) < M - 1 ? 4u : 0u)));
+    const uint32_t why = r >= n_real ? 0u : (n > (uint32_t)kListCap ? 2u : (bin < 0 ? 1u : ((T[r] != 0u || (over >> r) & 1u) && (bin << bin_log(r)) < M - 1 ? 4u : 0u)));
     redo |= why ? 1u << r : 0u;
     if (stats && tid == r && r < n_real) stats[head0 + r] = n | why << 28;
   }
